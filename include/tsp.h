@@ -133,6 +133,8 @@ enum {
 };
 
 /* Kernels reported in tsp_stats.kernel_us (a prefix sum of three small launches is timed as one).
+ * By rows: CONVERT is the pass over the operands, SCAN_SYM the choice and the lists of work, SYM_COUNT the sizing of
+ * the rows, SCAN_ROWS row_ptr of C, NUMERIC the multiplication.
  * When every tile-row of C is short, the task-list kernel also runs the counting pass and the row
  * offsets; their two entries then read 0. */
 enum {
@@ -151,8 +153,9 @@ enum {
 typedef struct {
     int64_t a_tiles, b_tiles;        /* non-empty tiles of the operands                              */
     int64_t candidate_pairs;         /* (A tile, B tile) pairs with matching inner tile index         */
-    int64_t pairs;                   /* pairs left after the zero-product cull = task list length     */
-    int64_t c_tiles;                 /* output tiles (all structurally non-empty)                     */
+    int64_t pairs;                   /* pairs left after the zero-product cull = task list length; 0  */
+                                     /* when tsp_spgemm multiplied by rows, which needs no task list  */
+    int64_t c_tiles;                 /* output tiles (all structurally non-empty); 0 by rows as well  */
     int64_t c_nnz;                   /* structural nonzeros of C                                      */
     int64_t workspace_bytes;         /* bytes currently held by the handle (cache + live objects)     */
     int64_t workspace_peak_bytes;    /* high-water mark of the above                                  */
@@ -165,8 +168,8 @@ typedef struct {
                                      /* counted when TSP_OPT_COUNT_PRODUCTS is on, else -1              */
     /* The paper's selection criteria for the last product's left operand (Section 6.1): the tiled method */
     /* pays off for NNZ(A) > 300000 with more than 42 entries per row on average, and for well-filled     */
-    /* tiles (5 of 64 slots of an 8x8 tile and more, i.e. 20 entries per 16x16 tile).  Reported, not acted */
-    /* on: this library has no non-tiled path to fall back to.                                            */
+    /* tiles (5 of 64 slots of an 8x8 tile and more, i.e. 20 entries per 16x16 tile).  Reported; whether   */
+    /* tsp_spgemm multiplies by tiles or by rows follows from the products per candidate pair of tiles.    */
     float a_mean_row;                /* NNZ(A) / rows                                                  */
     float a_tile_fill;               /* NNZ(A) / tiles(A): entries per 16x16 tile                      */
     int32_t in_paper_regime;         /* 1: NNZ(A) > 300000 and a_mean_row > 42                         */
@@ -200,6 +203,11 @@ int tsp_trim(tsp_handle handle, void *stream);
  * waited for: C.nnz and the pointers are final when the call returns, the
  * contents once the stream has reached that point (hipStreamSynchronize, or further work on the
  * same stream).  With TSP_OPT_PHASE_TIMERS the call waits for the end.
+ * Operands whose tiles hold little (at most 64 intermediate products per candidate pair of tiles: graphs, meshes with
+ * one unknown per node, random matrices) are multiplied row by row instead, with the same result up to the order of
+ * the fp32 additions; an option that chooses among the tile kernels (NUMERIC_RUN, MATRIX_CORES, WORK_ORDER,
+ * STRIP_ORDER, WIDE_INDEX away from its default) keeps the tiles.  Which way suits is looked at when the sizes of the
+ * operands differ from the last product's, at the price of one more wait.
  * Errors: INVALID_ARG, SHAPE_MISMATCH, NOT_CANONICAL, ALLOC_FAILED, INDEX_OVERFLOW, HIP,
  * UNSUPPORTED (a tile-row of C spans more than 131072 tile columns between its first and its
  * last candidate tile, i.e. 2097152 columns; or a tile-row of C holds 2^32 entries or more).

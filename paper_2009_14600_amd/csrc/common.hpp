@@ -32,6 +32,13 @@ enum Scalar {
     S_MAX_ROW_PAIRS = 12,    // max over C tile-rows of the number of task-list entries
     S_MAX_ROW_ENTRIES = 13,  // max over C tile-rows of the number of structural entries
     S_PRODUCTS = 14,         // intermediate products (TSP_OPT_COUNT_PRODUCTS)
+    // the row kernels (rowwise.hip):
+    S_ROW_LISTS = 15,        // heavy rows and their tasks listed so far (one packed counter), zero between launches
+    S_ROW_DONE = 16,         // blocks of k_row_plan that have finished, zero between launches
+    S_ROW_PRODUCTS = 17,     // intermediate products
+    S_ROW_MERGED = 18,       // rows of C that are merged
+    S_ROW_HEAVY = 19,        // rows of C that are not
+    S_ROW_TASKS = 20,        // waves of k_heavy_fill
     S_PUBLISHED = 31,        // host mirror only: a slot without a value (publish_scalars tags every slot)
 };
 
@@ -44,6 +51,15 @@ struct LiveBlock {           // a block handed out: with canaries the caller's p
     size_t bytes;            // of the whole block
     size_t user_bytes;       // of the caller's part (a multiple of 256)
     bool guarded;
+};
+
+// What the row kernels found for the last product (rowwise.hip), by the sizes of its operands: whether the tile kernels
+// suit it better, and how long its lists of work are.  Only the choice of kernels and the sizes of workspaces follow
+// from it; the numbers of the product at hand are checked against it.
+struct RowHint {
+    int64_t sizes[6] = {-1, -1, -1, -1, -1, -1};   // rows and nnz of A, rows, nnz and cols of B, A is B
+    bool tiles = false, merged = false;
+    int64_t heavy = 0, tasks = 0;
 };
 
 }  // namespace tsp
@@ -70,6 +86,7 @@ struct tsp_context {
     int64_t hint_sizes[4] = {-1, -1, -1, -1};      // ... with these rows and nnz of A and of B
     int32_t *hint_order = nullptr;                 // ... and took its tile-rows in this order (heaviest first), or null
     int64_t hint_order_rows = 0;
+    tsp::RowHint row_hint;
     int last_hip = 0;
     tsp_stats stats{};
     void *chain_slots = nullptr;                   // device, for the chained scans (chain.hpp)
@@ -177,6 +194,12 @@ int scan_exclusive_i32_to_i64(tsp_context *ctx, const int32_t *in, int64_t *out,
                               int64_t *d_total, int64_t *d_max, int64_t *tmp, hipStream_t s);
 
 // ---- phases (internal forms; the C ABI wraps them) -------------------------------------
+int check_csr_host(const tsp_csr *A);                // what can be said about an operand without reading its arrays
+void fill_selection_criteria(tsp_context *ctx, int64_t rows, int64_t nnz, int64_t ntiles);   // of the left operand
+// The whole product by rows (rowwise.hip), where the structure of the operands asks for it: *taken says whether it
+// did.  Both operands have passed check_csr_host; the scalar block is zero.
+int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s,
+                   bool *taken);
 int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out,
                     hipStream_t s);
 void tiles_release(tsp_context *ctx, tsp_tiles_s *t, hipStream_t s);

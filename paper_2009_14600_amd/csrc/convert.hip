@@ -728,7 +728,7 @@ static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, in
     return TSP_OK;
 }
 
-static int check_csr_host(const tsp_csr *A) {
+int check_csr_host(const tsp_csr *A) {
     if (!A) return TSP_ERR_INVALID_ARG;
     if (A->rows < 0 || A->cols < 0 || A->nnz < 0) return TSP_ERR_INVALID_ARG;
     if (A->row_ptr_type != TSP_I32 && A->row_ptr_type != TSP_I64) return TSP_ERR_INVALID_ARG;

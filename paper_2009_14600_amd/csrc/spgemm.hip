@@ -59,20 +59,32 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
     tsp_tiles_s *ta = nullptr, *tb = nullptr;
     tsp_plan_s *plan = nullptr;
 
+    int rc = check_csr_host(A);
+    if (!rc) rc = check_csr_host(B);
+    if (rc) return rc;
     total_begin(ctx, s);
     // (the multiplication kernel of the previous call has usually left the scalar block zeroed)
     if (!ctx->scalars_clean) hipLaunchKernelGGL(k_clear_scalars_all, dim3(1), dim3(64), 0, s, ctx->d_scalars);
     ctx->scalars_clean = false;
-    phase_begin(ctx, TSP_PHASE_CONVERT, s);
-    int rc = convert_enqueue(ctx, A, alias ? (TSP_FORM_LEFT | TSP_FORM_RIGHT) : TSP_FORM_LEFT, S_TILES_A, &ta, s);
-    if (!rc && !alias) rc = convert_enqueue(ctx, B, TSP_FORM_RIGHT, S_TILES_B, &tb, s);
-    phase_end(ctx, TSP_PHASE_CONVERT, s);
-    // (behind the converters, whose host-side checks have seen both matrices; the count travels to the host
-    // with the sizes the symbolic phase reads back)
-    if (!rc && ctx->count_products) count_products(ctx, A, B, s);
-    if (!rc) rc = symbolic_run(ctx, ta, alias ? ta : tb, &plan, s);
+    // (the count travels to the host with the sizes it waits for)
+    if (ctx->count_products) count_products(ctx, A, B, s);
+    bool by_rows = false, by_tiles = false;
+    const int64_t tag = ctx->publish_tag;
+    rc = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows);
+    if (!rc && !by_rows) {
+        by_tiles = true;
+        if (ctx->publish_tag != tag) {             // the row kernels have looked at the operands and used the scalar block
+            hipLaunchKernelGGL(k_clear_scalars_all, dim3(1), dim3(64), 0, s, ctx->d_scalars);
+            if (ctx->count_products) count_products(ctx, A, B, s);
+        }
+        phase_begin(ctx, TSP_PHASE_CONVERT, s);
+        rc = convert_enqueue(ctx, A, alias ? (TSP_FORM_LEFT | TSP_FORM_RIGHT) : TSP_FORM_LEFT, S_TILES_A, &ta, s);
+        if (!rc && !alias) rc = convert_enqueue(ctx, B, TSP_FORM_RIGHT, S_TILES_B, &tb, s);
+        phase_end(ctx, TSP_PHASE_CONVERT, s);
+        if (!rc) rc = symbolic_run(ctx, ta, alias ? ta : tb, &plan, s);
+    }
     ctx->stats.products = !rc && ctx->count_products ? ctx->h_scalars[S_PRODUCTS] : -1;
-    if (!rc) rc = numeric_enqueue(ctx, ta, alias ? ta : tb, plan, C, s, /*last_of_call=*/true);   // the plan ends here
+    if (!rc && by_tiles) rc = numeric_enqueue(ctx, ta, alias ? ta : tb, plan, C, s, /*last_of_call=*/true);   // the plan ends here
     if (!rc && ctx->compact) {                    // Algorithm 1, the compaction steps: strictly sparse result
         tsp_csr structural = *C;
         bool taken = false;                       // (no entry is zero: C keeps the arrays it has)

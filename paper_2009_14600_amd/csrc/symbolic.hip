@@ -1460,6 +1460,14 @@ bool row_ptr_in_one_launch(tsp_context *ctx, const int32_t *row_len, int64_t row
     return true;
 }
 
+// The paper's selection criteria (Section 6.1) for the left operand.
+void fill_selection_criteria(tsp_context *ctx, int64_t rows, int64_t nnz, int64_t ntiles) {
+    ctx->stats.a_mean_row = rows > 0 ? (float)((double)nnz / (double)rows) : 0.f;
+    ctx->stats.a_tile_fill = ntiles > 0 ? (float)((double)nnz / (double)ntiles) : 0.f;
+    ctx->stats.in_paper_regime = nnz > 300000 && ctx->stats.a_mean_row > 42.f;
+    ctx->stats.well_filled_tiles = ctx->stats.a_tile_fill >= 20.f;
+}
+
 void plan_release(tsp_context *ctx, tsp_plan_s *p, hipStream_t s) {
     if (!p) return;
     ctx_free(ctx, p->c_tile_row_ptr, s);
@@ -1823,11 +1831,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     ctx->stats.pairs = P->pairs;
     ctx->stats.c_tiles = P->c_tiles;
     ctx->stats.c_nnz = P->c_nnz;
-    // the paper's selection criteria (Section 6.1) for the left operand
-    ctx->stats.a_mean_row = A->rows > 0 ? (float)((double)A->nnz / (double)A->rows) : 0.f;
-    ctx->stats.a_tile_fill = A->ntiles > 0 ? (float)((double)A->nnz / (double)A->ntiles) : 0.f;
-    ctx->stats.in_paper_regime = A->nnz > 300000 && ctx->stats.a_mean_row > 42.f;
-    ctx->stats.well_filled_tiles = ctx->stats.a_tile_fill >= 20.f;
+    fill_selection_criteria(ctx, A->rows, A->nnz, A->ntiles);
     *out = P;
     return cleanup(TSP_OK);
 }

@@ -1,0 +1,131 @@
+"""The row kernels (csrc/rowwise.hip), which tsp_spgemm takes for operands with little in their tiles, against the CPU
+oracle at the sizes where they can go wrong: the bounds of merged rows, the windows of columns, the span of one block's
+bitmap, workspaces kept from a product of the same sizes.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+from paper_2009_14600_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tsp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2009_14600_amd import tsp as binding
+    binding.load_library()
+    return binding
+
+
+def _matrix(rng, rows, cols, per_row, name="", dense=()):
+    """About per_row (a number or one per row) entries per row at random columns; the rows in `dense` get 40 times as many."""
+    want = np.broadcast_to(np.asarray(per_row), (rows,)).copy()
+    for r in dense:
+        want[r % rows] *= 40
+    r = np.repeat(np.arange(rows), want)
+    key = np.unique(r * cols + rng.integers(0, cols, r.size))
+    return inputs.from_coo(rows, cols, key // cols, key % cols, rng.uniform(-1, 1, key.size), name)
+
+
+def _check(h, tsp, oracle, A, B=None, by_rows=True, calls=2, **upload):
+    print(f"rows: {A.name} {A.rows}x{A.cols}x{(B or A).cols}, nnz {A.nnz}, {(B or A).nnz}", flush=True)
+    dA = tsp.to_device(A, **upload)
+    dB = dA if B is None else tsp.to_device(B, **upload)
+    ref = oracle.spgemm(A, A if B is None else B, threads=4)
+    first = None
+    for _ in range(calls):                       # (from the second call on with what the handle kept of the first)
+        C = h.spgemm(dA, dB)
+        if by_rows is not None:
+            assert (h.stats()["pairs"] == 0) == by_rows
+        row_ptr, col, val = C.to_host()
+        C.free()
+        assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+        assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+        if first is not None:
+            assert np.array_equal(first.view(np.uint32), val.view(np.uint32))       # runs are bit-identical
+        first = val
+
+
+# entries per row of A and of B either side of the bounds of merged rows (8 and 16 entries, 256 products), of the lanes
+# per segment in the sizing pass, and of one load per segment
+@pytest.mark.parametrize("a_row,b_row", [(1, 1), (3, 40), (8, 32), (8, 33), (9, 20), (16, 16), (16, 17), (17, 3), (40, 70), (5, 300)])
+def test_bounds_of_merged_rows(tsp, oracle, a_row, b_row):
+    rng = np.random.default_rng(100 * a_row + b_row)
+    h = tsp.Handle()
+    try:
+        A = _matrix(rng, 300, 3001, rng.integers(0, a_row + 1, 300), "ragged left", dense=(7,))
+        A2 = _matrix(rng, 300, 3001, a_row, "even left")
+        B = _matrix(rng, 3001, 3001, b_row, "right")
+        _check(h, tsp, oracle, A, B, value_dtype="f32", row_ptr_dtype="i64")
+        _check(h, tsp, oracle, A2, B)
+    finally:
+        h.close()
+
+
+@pytest.mark.parametrize("cols", [1, 33, 2047, 2048, 2049, 4096, 4097, 8192, 8193, 16385, 70001, 393216, 393217, 900001])
+def test_windows_of_columns(tsp, oracle, cols):
+    """Narrow results in one window of 2048, 4096 or 8192 columns, wide ones in many, and beyond the columns whose bits
+    one block of the sizing pass holds; light, heavy and very heavy rows (several tasks) side by side."""
+    rng = np.random.default_rng(cols)
+    h = tsp.Handle()
+    try:
+        A = _matrix(rng, 259, 900, rng.integers(0, 40, 259), "left", dense=(0, 100, 258))
+        B = _matrix(rng, 900, cols, min(60, cols), "right", dense=(3, 899) if cols > 100 else ())
+        _check(h, tsp, oracle, A, B, by_rows=None if cols < 100 else True)
+    finally:
+        h.close()
+
+
+def test_same_sizes_another_structure(tsp, oracle):
+    """Operands of the same sizes as the last product's, with more and with fewer heavy rows than the kept lists hold,
+    and some that suit the tile kernels."""
+    n, rng = 1600, np.random.default_rng(5)
+    even = np.full(n, 6)
+    skewed = np.full(n, 2)
+    skewed[::40] = 162                            # the same number of entries, 40 heavy rows
+    more = np.full(n, 3)
+    more[::80] = 243                              # 20 of them
+    h = tsp.Handle()
+    try:
+        def exact(lengths):
+            cols = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths])
+            return inputs.from_coo(n, n, np.repeat(np.arange(n), lengths), cols, rng.uniform(-1, 1, cols.size))
+        for lengths in (even, skewed, more, skewed, even):
+            A = exact(lengths)
+            assert A.nnz == 6 * n
+            _check(h, tsp, oracle, A, calls=1)
+        block = inputs.block_clustered(2048, seed=9)
+        _check(h, tsp, oracle, block, by_rows=False)
+        _check(h, tsp, oracle, exact(even))
+    finally:
+        h.close()
+
+
+def test_rejects_what_is_not_canonical(tsp):
+    import torch
+    h = tsp.Handle()
+    try:
+        A = tsp.to_device(inputs.random_fixed_per_row(600, 5, seed=3))
+        h.spgemm(A, A).free()
+        good_col, good_ptr = A.col_idx, A.row_ptr
+        for k, value in [(0, -1), (77, 600), (78, int(good_col[77])), (2999, 0)]:
+            A.col_idx = good_col.clone()
+            A.col_idx[k] = value
+            with pytest.raises(tsp.TspError) as e:
+                h.spgemm(A, A)
+            assert e.value.status == -3
+        A.col_idx = good_col
+        for k, value in [(0, 1), (17, -5), (300, 5000), (600, 2999)]:
+            A.row_ptr = good_ptr.clone()
+            A.row_ptr[k] = value
+            with pytest.raises(tsp.TspError) as e:
+                h.spgemm(A, A)
+            assert e.value.status == -3
+        A.row_ptr = good_ptr
+        C = h.spgemm(A, A)
+        assert C.nnz > 0 and h.stats()["pairs"] == 0
+        C.free()
+    finally:
+        h.close()
