@@ -8,25 +8,30 @@
 //   k_row_plan      candidate tile pairs (the measure by which tsp_spgemm chooses this path), the lists of work
 //   k_row_merge     rows with few, short rows of B behind them: a lane per row of B, merged in column order
 //   k_heavy_count   the other rows: a block per row, one bit per column of C in LDS
-//   k_heavy_fill    a wave per row and window of columns, a dense fp32 accumulator in LDS
+//   k_heavy_fill    a block per row and some windows of columns, a dense accumulator in LDS
 //
-// Every sum of C is formed in one wave in a fixed order (the entries of the row of A ascending; in a merge step the
-// lanes of the group as a tree), so runs are bit-identical.  Products of fp16 numbers are exact in fp32 and are
-// accumulated in fp32, as on the matrix cores.
+// Runs are bit-identical.  Products of fp16 numbers are exact in fp32.  A merged entry is summed by the lanes of its
+// group as a tree, in fp32.  A heavy entry is summed in integers where every partial sum is exact in them (all products
+// are multiples of a power of two that the operands' values say; then the order of the additions does not matter and a
+// whole block shares the accumulator), and otherwise in fp64 by one wave in the order of the entries of A.
 #include "common.hpp"
 
 #include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 namespace tsp {
 
 constexpr int kMergeProducts = 256;      // a merged row has at most this many intermediate products
 constexpr int kPlanBlocks = 128;         // blocks of k_row_plan
 constexpr int kPlanSums = 8;
-constexpr int kHeavySpan = 48 * 8192;    // columns whose bits fit the LDS of a block of k_heavy_count (48 KB)
-constexpr int kHeavyThreads = 256;
+constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
+constexpr int kSpanWindows = 64;         // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
+constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows
+constexpr int kHeavyThreads = 512;
 constexpr int32_t kNoCol = 0x7FFFFFFF;
 // Intermediate products behind one task of k_heavy_fill (a row, or some of its windows)
-constexpr int kTaskProducts = 16384;
+constexpr int kTaskProducts = 65536;
 constexpr int64_t kRowPairProducts = 64; // products per candidate pair of tiles up to which the rows are the better way
 
 struct RowMatrix {                       // an operand in the form the row kernels read
@@ -34,6 +39,7 @@ struct RowMatrix {                       // an operand in the form the row kerne
     int2 *rec = nullptr;                 // per entry {column (clamped), value rounded to fp16, as fp32 bits}
     int32_t *ntiles = nullptr;           // tiles of every tile-row
     int32_t *tile_col = nullptr;         // their columns, at the position of the tile-row's first entry; any order
+    uint32_t *range = nullptr;           // magnitude and granularity of every tile-row's values (value_range)
 };
 
 template <typename RP, typename VT>
@@ -57,6 +63,19 @@ __device__ __forceinline__ float rounded_value(uint16_t bits) {
 }
 __device__ __forceinline__ float rounded_value(float v) { return (float)(_Float16)v; }
 
+// Of a value v != 0: {256 + e} << 16 | {256 - g}, |v| < 2^e and v a multiple of 2^g; infinities and NaNs are as large as
+// can be.  The larger of each half over a set of values holds for the set.
+__device__ __forceinline__ uint32_t value_range(float v) {
+    const uint32_t b = __float_as_uint(v) & 0x7FFFFFFFu;
+    if (b == 0) return 0;
+    if (b >= 0x7F800000u) return 0x03FF03FFu;
+    const int exponent = (int)(b >> 23), low = __ffs((int)((b & 0x7FFFFFu) | 0x800000u)) - 1;
+    return (uint32_t)(256 + exponent - 126) << 16 | (uint32_t)(256 - (exponent - 150 + low));
+}
+__device__ __forceinline__ uint32_t range_max(uint32_t x, uint32_t y) {
+    return max(x & 0xFFFF0000u, y & 0xFFFF0000u) | max(x & 0xFFFFu, y & 0xFFFFu);
+}
+
 // A team of kTeam threads per tile-row (a wave, or a block of 256 for long tile-rows), its entries flat over the
 // lanes.  The team's bitmap over the tile columns tells the first entry that falls into a tile (the atomic returns the
 // word before): those lanes list the tile.  Bound by the loads of B's row pointers and by instructions.
@@ -67,6 +86,7 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     __shared__ int32_t s_ptr[kTeams][T + 1];
     __shared__ unsigned long long s_ub[kTeams][T];
     __shared__ int32_t s_count[kTeams];
+    __shared__ uint32_t s_range[2][kTeams];
     const int team = threadIdx.x / kTeam, tid = threadIdx.x % kTeam, lane = lane_id();
     uint32_t *bitmap = lds_bitmap + team * a.bitmap_words;
     const int64_t tile_rows = (a.rows + T - 1) / T;
@@ -85,13 +105,17 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
             if (tid < T) s_ub[team][tid] = 0;
             if (i < a.rows ? tid < T : true) a.out.start[i] = (int32_t)p;
         }
-        if (tid == 0) s_count[team] = 0;
+        if (tid == 0) {
+            s_count[team] = 0;
+            s_range[0][team] = s_range[1][team] = 0;
+        }
     }
     if constexpr (kTeam == 64) wave_sync();
     else __syncthreads();
     if (live) {
         const int32_t e0 = s_ptr[team][0], e1 = s_ptr[team][T];
         int32_t listed = 0;
+        uint32_t range = 0;
         for (int32_t base = e0 + (tid & ~63); base < e1; base += kTeam) {
             const int32_t k = base + lane;
             const bool on = k < e1;
@@ -113,6 +137,7 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                     c = 0;
                 }
                 a.out.rec[k] = make_int2(c, (int)__float_as_uint(v));
+                range = range_max(range, value_range(v));
                 if (a.ub && c < a.b_rows) {
                     int64_t s, e;
                     if (a.b_is_i64) {
@@ -149,13 +174,20 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                     atomicAdd(&s_ub[team][r], (unsigned long long)0 - (unsigned long long)(inc - (uint32_t)len));
             }
         }
-        if constexpr (kTeam == 64)
-            if (tid == 0) s_count[team] = listed;
+        const int e = wave_max((int)(range >> 16)), g = wave_max((int)(range & 0xFFFFu));
+        if (lane == 0) {
+            if constexpr (kTeam == 64) s_count[team] = listed;
+            atomicMax(&s_range[0][team], (uint32_t)e);
+            atomicMax(&s_range[1][team], (uint32_t)g);
+        }
     }
     if constexpr (kTeam == 64) wave_sync();
     else __syncthreads();
     if (live) {
-        if (tid == 0) a.out.ntiles[I] = s_count[team];
+        if (tid == 0) {
+            a.out.ntiles[I] = s_count[team];
+            a.out.range[I] = s_range[0][team] << 16 | s_range[1][team];
+        }
         if (a.ub && tid < T && I * T + tid < a.rows)
             a.ub[I * T + tid] = (int32_t)min(s_ub[team][tid], (unsigned long long)INT32_MAX);
         if (bad && a.validate) a.d_scalars[S_INVALID] = 1;
@@ -165,6 +197,7 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
 struct PlanArgs {
     int64_t a_rows, a_tile_rows, b_tile_rows;
     const int32_t *a_start, *ub, *a_ntiles, *a_tile_col, *b_ntiles;
+    const uint32_t *a_range, *b_range;
     int same;                            // A and B are one matrix
     int merge_lanes;                     // most entries of a row of A that is merged
     int windows;                         // of columns of C, for the heavy rows
@@ -184,23 +217,33 @@ __device__ __forceinline__ bool merged_row(int32_t entries, int32_t products, in
 // row: merged or heavy, and how many tasks a heavy row makes.
 __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
     __shared__ unsigned long long s_sum[kPlanSums];
+    __shared__ unsigned long long s_max[kPlanSums];
     __shared__ int s_last;
-    if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = 0;
+    if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = s_max[threadIdx.x] = 0;
     __syncthreads();
     const int lane = lane_id(), r = threadIdx.x & 15;
     unsigned long long cand = 0, tiles_a = 0, tiles_b = 0, products = 0, merged = 0;
+    uint32_t range_a = 0, range_b = 0;
+    int longest = 0;                     // heavy row of A
+    const int groups = (a.windows + kGroupWindows - 1) / kGroupWindows;
     unsigned long long *counters = reinterpret_cast<unsigned long long *>(a.d_scalars + S_ROW_LISTS);
     const int64_t step = (int64_t)gridDim.x * 16;
     const int64_t most = a.a_tile_rows > a.b_tile_rows ? a.a_tile_rows : a.b_tile_rows;
     for (int64_t base = (int64_t)blockIdx.x * 16; base < most; base += step) {
         const int64_t I = base + (threadIdx.x >> 4);
-        if (r == 0 && I < a.b_tile_rows && !a.same) tiles_b += (unsigned)a.b_ntiles[I];
+        if (r == 0 && I < a.b_tile_rows && !a.same) {
+            tiles_b += (unsigned)a.b_ntiles[I];
+            range_b = range_max(range_b, a.b_range[I]);
+        }
         int tasks = 0;
         bool heavy = false;
         const int64_t row = I * T + r;
         if (I < a.a_tile_rows) {
             const int32_t e0 = a.a_start[I * T], n = a.a_ntiles[I];
-            if (r == 0) tiles_a += (unsigned)n;
+            if (r == 0) {
+                tiles_a += (unsigned)n;
+                range_a = range_max(range_a, a.a_range[I]);
+            }
             for (int32_t j = r; j < n; j += 16) {
                 const int32_t K = a.a_tile_col[e0 + j];
                 if (K < a.b_tile_rows) cand += (unsigned)a.b_ntiles[K];
@@ -210,12 +253,14 @@ __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
                 products += (unsigned)ub;
                 heavy = deg > 0 && !merged_row(deg, ub, a.merge_lanes) && ub > 0;
                 merged += !heavy && ub > 0;
-                if (heavy) tasks = min(max(ub / kTaskProducts, 1), a.windows);
+                if (heavy) {
+                    tasks = min(max(ub / kTaskProducts, 1), groups);
+                    longest = max(longest, deg);
+                }
             }
         }
         const unsigned long long heavies = __ballot(heavy);
         if (heavies) {                   // (uniform in the wave) places in both lists from one atomic
-            if (tasks) tasks = (a.windows + (a.windows + tasks - 1) / tasks - 1) / ((a.windows + tasks - 1) / tasks);
             const uint32_t inc = wave_inclusive_scan((uint32_t)tasks);
             unsigned long long at = 0;
             if (lane == 63) at = atomicAdd(counters, ((unsigned long long)__popcll(heavies) << 36) | inc);
@@ -224,10 +269,11 @@ __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
             const int64_t t0 = (int64_t)(at & ((1ull << 36) - 1ull)) + inc - tasks;
             if (heavy && h < a.heavy_cap) {
                 a.heavy[h] = (int32_t)row;
-                const int per = (a.windows + tasks - 1) / tasks;
+                // (groups of windows, as even as they go)
                 for (int t = 0; t < tasks; ++t)
                     if (t0 + t < a.task_cap)
-                        a.tasks[t0 + t] = make_int4((int)row, (int)h, t * per, min((t + 1) * per, a.windows));
+                        a.tasks[t0 + t] = make_int4((int)row, (int)h, (int)((int64_t)groups * t / tasks) * kGroupWindows,
+                                                    min((int)((int64_t)groups * (t + 1) / tasks) * kGroupWindows, a.windows));
             }
         }
     }
@@ -240,6 +286,21 @@ __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
     add(2, tiles_b);
     add(3, products);
     add(4, merged);
+    auto most_of = [&](int slot, int v) {
+        v = wave_max(v);
+        if (lane == 0 && v) atomicMax(&s_max[slot], (unsigned long long)v);
+    };
+    most_of(0, (int)(range_a >> 16));
+    most_of(1, (int)(range_a & 0xFFFFu));
+    most_of(2, (int)(range_b >> 16));
+    most_of(3, (int)(range_b & 0xFFFFu));
+    most_of(4, longest);
+    __syncthreads();
+    // (sums of counts stay below 2^48, and so does the word that carries the maxima)
+    if (threadIdx.x == 0) {
+        s_sum[5] = s_max[0] << 48 | s_max[1] << 32 | s_max[2] << 16 | s_max[3];
+        s_sum[6] = s_max[4];
+    }
     __syncthreads();
     if (threadIdx.x < kPlanSums)
         __hip_atomic_store(&a.partial[blockIdx.x * kPlanSums + threadIdx.x], s_sum[threadIdx.x], __ATOMIC_RELAXED,
@@ -254,9 +315,16 @@ __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
     // the last block to finish adds up the partial sums and hands the sizes to the host
     if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = 0;
     __syncthreads();
+    if (threadIdx.x < kPlanSums) s_max[threadIdx.x] = 0;
+    __syncthreads();
     for (unsigned i = threadIdx.x; i < gridDim.x * kPlanSums; i += 256) {
         const unsigned long long v = __hip_atomic_load(&a.partial[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (v) atomicAdd(&s_sum[i % kPlanSums], v);
+        const unsigned slot = i % kPlanSums;
+        if (!v) continue;
+        if (slot == 5)
+            for (int q = 0; q < 4; ++q) atomicMax(&s_max[q], (v >> (48 - 16 * q)) & 0xFFFFull);
+        else if (slot == 6) atomicMax(&s_max[4], v);
+        else atomicAdd(&s_sum[slot], v);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -265,6 +333,10 @@ __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
         a.d_scalars[S_TILES_B] = (int64_t)(a.same ? s_sum[1] : s_sum[2]);
         a.d_scalars[S_ROW_PRODUCTS] = (int64_t)s_sum[3];
         a.d_scalars[S_ROW_MERGED] = (int64_t)s_sum[4];
+        const int from = a.same ? 0 : 2;
+        a.d_scalars[S_ROW_RANGE_A] = (int64_t)(s_max[0] << 16 | s_max[1]);
+        a.d_scalars[S_ROW_RANGE_B] = (int64_t)(s_max[from] << 16 | s_max[from + 1]);
+        a.d_scalars[S_ROW_LONGEST] = (int64_t)s_max[4];
         const unsigned long long lists = __hip_atomic_load(counters, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         a.d_scalars[S_ROW_HEAVY] = (int64_t)(lists >> 36);
         a.d_scalars[S_ROW_TASKS] = (int64_t)(lists & ((1ull << 36) - 1ull));
@@ -435,12 +507,13 @@ __global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a) {
 
 // ---- heavy rows -------------------------------------------------------------------------------------------------
 // B for the heavy rows: 4 bytes per entry {low 16 bits of the column, fp16 value}, and where every row of B enters
-// every window of columns.  Sixteen lanes per row.
+// every window of columns; the columns once more by themselves.  L lanes per row.
 struct PackArgs {
     int64_t rows;
     const int32_t *start;
     const int2 *rec;
     uint32_t *pack;
+    int32_t *col;
     int32_t *table;                      // [rows][windows + 1], or null for one window
     int windows, shift;                  // a window is 1 << shift columns
 };
@@ -454,6 +527,7 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
     for (int32_t k = s + l; k < e; k += L) {
         const int2 x = a.rec[k];
         const _Float16 v = (_Float16)__uint_as_float((uint32_t)x.y);
+        a.col[k] = x.x;
         a.pack[k] = ((uint32_t)x.x & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
         if (tab) {
             const int before = k > s ? a.rec[k - 1].x >> a.shift : -1;
@@ -466,12 +540,75 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
     }
 }
 
+// The segments of B behind up to 64 entries of A, one per lane (first entry, length, value a_ik), as a stream of pieces of
+// at most 64 entries, segment by segment: load(p) fetches entry p + lane of a piece, apply(x, a) takes what a lane below
+// the piece's length got.  Eight pieces are requested while the eight before them are applied, across the ends of
+// segments, so that a memory round trip is paid once per chunk and not per segment; everything that steers the stream
+// is scalar.  load must be allowed to read up to 63 entries past a segment.
+template <typename X, typename Load, typename Apply>
+__device__ __forceinline__ void stream_segments(int p, int len, int av, Load load, Apply apply) {
+    constexpr int kBatch = 8;
+    const int lane = lane_id();
+    const unsigned long long some = __ballot(len > 0);
+    if (!some) return;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    // the segments that hold something, in the order of their lanes
+    const int to = (len > 0 ? __popcll(some & below) : __popcll(some) + __popcll(~some & below)) * 4;
+    p = __builtin_amdgcn_ds_permute(to, p);
+    av = __builtin_amdgcn_ds_permute(to, av);
+    len = __builtin_amdgcn_ds_permute(to, max(len, 0));
+    int left = (int)wave_sum((uint32_t)(len + 63) >> 6);
+    int i = 0, sp = __builtin_amdgcn_readlane(p, 0), sl = __builtin_amdgcn_readlane(len, 0);
+    struct Batch {
+        X x[kBatch];
+        int n[kBatch];
+        int a[kBatch];
+    };
+    auto fetch = [&](Batch &b) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            b.x[u] = load(sp);
+            b.n[u] = u < left ? sl : 0;
+            b.a[u] = __builtin_amdgcn_readlane(av, i);
+            // (both ways in full, so that they become selects and not branches)
+            const int j = (i + 1) & 63;
+            const int p_next = __builtin_amdgcn_readlane(p, j), l_next = __builtin_amdgcn_readlane(len, j);
+            const int p_on = sp + 64, l_on = sl - 64;
+            const bool more = sl > 64;
+            i = more ? i : j;
+            sp = more ? p_on : p_next;
+            sl = more ? l_on : l_next;
+        }
+        left -= kBatch;
+    };
+    auto use = [&](const Batch &b) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (lane < b.n[u]) apply(b.x[u], __uint_as_float((uint32_t)b.a[u]));
+    };
+    Batch b0, b1;
+    fetch(b0);
+    // (the next batch is requested also when there is none, 8 loads of no use: behind a branch the waits could not tell
+    // the two batches apart)
+    while (true) {
+        const bool more = left > 0;
+        fetch(b1);
+        use(b0);
+        if (!more) break;
+        const bool again = left > 0;
+        fetch(b0);
+        use(b1);
+        if (!again) break;
+    }
+}
+
 struct CountArgs {
     const int32_t *heavy;
     int64_t heavy_cap;
     const int64_t *d_scalars;
     const int32_t *a_start, *b_start, *ub;
-    const int2 *a_rec, *b_rec;
+    const int2 *a_rec;
+    const int32_t *b_col;
     const int32_t *table;
     int32_t b_nnz;
     int windows;                         // of kWin columns each
@@ -481,8 +618,9 @@ struct CountArgs {
     uint32_t *offset;                    // [heavy][windows] entries of the row before each window
 };
 
-// A block per heavy row: the segments of B behind 256 entries of A at a time are listed in LDS, groups of lanes walk
-// them and set one bit per product.  OR is free of order, so the row may be spread over the whole block.
+// A block per heavy row sets one bit per product in LDS; OR is free of order, so the row may be spread over the block.
+// Long segments of B: a wave takes 64 entries of A at a time and streams the segments behind them.  Short ones: the
+// segments behind 512 entries of A are listed in LDS and groups of 8 or 16 lanes take one each.
 template <int kWin>
 __global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a) {
     extern __shared__ __align__(16) uint32_t bits[];
@@ -497,52 +635,53 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     for (int w = threadIdx.x; w < a.span_windows * kWords; w += kHeavyThreads) bits[w] = 0;
     if (threadIdx.x == 0) s_run = 0;
-    // lanes per segment, from the mean length of the rows of B behind this row
-    const int mean = e > s ? a.ub[row] / (e - s) : 0;
-    const int sh = mean > 32 ? 6 : mean > 16 ? 5 : mean > 8 ? 4 : 3;
-    const int lanes = 1 << sh, sub = threadIdx.x >> sh, j0 = threadIdx.x & (lanes - 1), subs = kHeavyThreads >> sh;
+    const int mean = e > s ? a.ub[row] / (e - s) : 0;            // length of the rows of B behind this row
     for (int w0 = 0; w0 < a.windows; w0 += a.span_windows) {
         const int w1 = min(w0 + a.span_windows, a.windows);
         const int32_t c0 = w0 * kWin;
         const uint32_t limit = (uint32_t)(w1 - w0) * kWin;
-        for (int32_t base = s; base < e; base += kHeavyThreads) {
-            const int n = min(e - base, kHeavyThreads);
-            __syncthreads();
-            if ((int)threadIdx.x < n) {
-                const int32_t c = a.a_rec[base + threadIdx.x].x;
-                int2 seg;
-                if (a.windows <= a.span_windows) seg = make_int2(a.b_start[c], a.b_start[c + 1]);
-                else seg = make_int2(max(a.table[(int64_t)c * (a.windows + 1) + w0], 0),
-                                     min(a.table[(int64_t)c * (a.windows + 1) + w1], a.b_nnz));
-                s_seg[threadIdx.x] = seg;
+        auto segment = [&](int32_t entry) {
+            const int32_t c = a.a_rec[entry].x;
+            if (a.windows <= a.span_windows) return make_int2(a.b_start[c], a.b_start[c + 1]);
+            const int32_t *tab = a.table + (int64_t)c * (a.windows + 1);
+            return make_int2(max(tab[w0], 0), min(tab[w1], a.b_nnz));
+        };
+        auto mark = [&](int32_t col) {
+            const uint32_t x = (uint32_t)(col - c0);
+            if (x < limit) atomicOr(&bits[x >> 5], 1u << (x & 31));
+        };
+        __syncthreads();
+        if (mean > 16) {
+            for (int32_t base = s + wave * 64; base < e; base += kHeavyThreads) {
+                int2 seg = make_int2(0, 0);
+                if (base + lane < e) seg = segment(base + lane);
+                stream_segments<int32_t>(
+                    seg.x, seg.y - seg.x, 0, [&](int p) { return (a.b_col + p)[(unsigned)lane]; },
+                    [&](int32_t col, float) { mark(col); });
             }
-            __syncthreads();
-            auto mark = [&](int32_t col) {
-                const uint32_t x = (uint32_t)(col - c0);
-                if (x < limit) atomicOr(&bits[x >> 5], 1u << (x & 31));
-            };
-            for (int i = sub; i < n; i += 4 * subs) {
-                int32_t p[4], q[4], c[4];
+        } else {
+            const int sh = mean > 8 ? 4 : 3, lanes = 1 << sh, subs = kHeavyThreads >> sh;
+            const int sub = threadIdx.x >> sh, j0 = threadIdx.x & (lanes - 1);
+            for (int32_t base = s; base < e; base += kHeavyThreads) {
+                const int n = min(e - base, kHeavyThreads);
+                __syncthreads();
+                if ((int)threadIdx.x < n) s_seg[threadIdx.x] = segment(base + threadIdx.x);
+                __syncthreads();
+                for (int i = sub; i < n; i += 4 * subs) {
+                    int32_t p[4], q[4], c[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int2 seg = s_seg[min(i + u * subs, n - 1)];
-                    p[u] = seg.x + j0;
-                    q[u] = i + u * subs < n ? seg.y : 0;
-                    c[u] = p[u] < q[u] ? a.b_rec[p[u]].x : -1;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (p[u] < q[u]) mark(c[u]);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    for (p[u] += lanes; p[u] < q[u]; p[u] += 4 * lanes) {
-                        int32_t d[4];
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) d[v] = p[u] + v * lanes < q[u] ? a.b_rec[p[u] + v * lanes].x : -1;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (p[u] + v * lanes < q[u]) mark(d[v]);
+                    for (int u = 0; u < 4; ++u) {
+                        const int2 seg = s_seg[min(i + u * subs, n - 1)];
+                        p[u] = seg.x + j0;
+                        q[u] = i + u * subs < n ? seg.y : 0;
+                        c[u] = p[u] < q[u] ? a.b_col[p[u]] : -1;
                     }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (p[u] < q[u]) mark(c[u]);
+                        for (p[u] += lanes; p[u] < q[u]; p[u] += lanes) mark(a.b_col[p[u]]);
+                    }
+                }
             }
         }
         __syncthreads();
@@ -585,105 +724,165 @@ struct FillArgs {
     const int64_t *c_row_ptr;
     int32_t *c_col;
     float *c_val;
+    int window;                          // columns
+    float a_scale, b_scale, c_scale;     // integers from the values, values from the integer sums
     int64_t *d_scalars_to_clear;
 };
 
-// A wave per task: a row of C, window by window of kWin columns.  The wave adds the products into a dense accumulator
-// in LDS (its own: no other wave adds to it, so the order of the sums is fixed) and sets a bit per column; the entries
-// are then listed from the bits, a word per lane and 2048 columns at a time, and written 64 to a store.
-template <int kWin>
-__global__ __launch_bounds__(64) void k_heavy_fill(const FillArgs a) {
-    __shared__ float acc[kWin];
-    __shared__ uint32_t bits[kWin / 32];
-    __shared__ uint16_t list[2048];
-    const int lane = threadIdx.x;
+// A block per task: a row of C, kWin columns at a time (some of its windows).  Its waves deal the entries of the row of
+// A among them, 64 apiece, and stream the segments of B behind them into a dense accumulator in LDS, with a bit per
+// column; then every wave lists the entries of 2048 columns from the bits (or, where more than a quarter is there, walks
+// the columns) and writes them 64 to a store.  The segments of the next step and the entries of the one after are
+// requested ahead.
+//
+// The accumulator: LDS adds an fp32 number one lane after the other (193 cycles for a wave's 64 lanes, measured), an
+// integer or an fp64 number all lanes at a time (5, 8 and 8 to 16 cycles for 32-bit and 64-bit integers and fp64).  So
+// the sums are integers where they are exact in them, and fp64 otherwise; fp64 only with a block of one wave, which
+// fixes the order of the additions.
+constexpr int kFillList = 512;           // entries a wave lists at a time
+template <typename Acc, int kWin, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_heavy_fill(const FillArgs a) {
+    constexpr int kWaves = kThreads / 64;
+    extern __shared__ __align__(16) unsigned char fill_lds[];
+    const int columns = min(kWin, a.windows * a.window);       // of a step
+    Acc *acc = reinterpret_cast<Acc *>(fill_lds);
+    uint32_t *bits = reinterpret_cast<uint32_t *>(acc + columns);
+    uint16_t *list = reinterpret_cast<uint16_t *>(bits + columns / 32) + (threadIdx.x >> 6) * kFillList;
+    __shared__ int s_total[kWaves];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    auto sync = [] {
+        if constexpr (kThreads == 64) wave_sync();
+        else __syncthreads();
+    };
     if (a.d_scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) a.d_scalars_to_clear[threadIdx.x] = 0;
     const int64_t t = blockIdx.x;
     if (t >= a.n_tasks) return;
     const int4 task = a.tasks[t];
     const int32_t row = task.x, s = a.a_start[row], e = a.a_start[row + 1];
     const int64_t row_first = a.c_row_ptr[row], row_end = a.c_row_ptr[row + 1];
-    for (int i = lane; i < kWin; i += 64) acc[i] = 0.f;
-    for (int i = lane; i < kWin / 32; i += 64) bits[i] = 0;
-    wave_sync();
-    for (int w = task.z; w < task.w; ++w) {
-        const int64_t first = row_first + a.offset[(int64_t)task.y * a.windows + w];
-        const int64_t last = w + 1 < a.windows ? row_first + a.offset[(int64_t)task.y * a.windows + w + 1] : row_end;
-        if (first >= last) continue;
-        for (int32_t base = s; base < e; base += 64) {
-            int32_t p = 0, q = 0, av = 0;
-            if (base + lane < e) {
-                const int2 x = a.a_rec[base + lane];
-                av = x.y;
-                if (a.table) {
-                    const int32_t *tab = a.table + (int64_t)x.x * (a.windows + 1) + w;
-                    p = max(tab[0], 0);              // (in bounds whatever an operand that was not validated holds)
-                    q = min(tab[1], a.b_nnz);
-                } else {
-                    p = a.b_start[x.x];
-                    q = a.b_start[x.x + 1];
-                }
-            }
-            unsigned long long left = __ballot(p < q);
-            auto add = [&](uint32_t x, float f) {
-                const uint32_t c = x & (kWin - 1);
+    const int chunks = (e - s + kThreads - 1) / kThreads;      // every wave takes its 64 entries of each
+    if (chunks <= 0 || task.z >= task.w) return;
+    for (int i = threadIdx.x; i < columns * (int)sizeof(Acc) / 16; i += kThreads)
+        reinterpret_cast<uint4 *>(acc)[i] = make_uint4(0, 0, 0, 0);
+    for (int i = threadIdx.x; i < columns / 32; i += kThreads) bits[i] = 0;
+    // (requested without branches around the loads, which would wait for them: lanes past the end repeat the last entry)
+    auto entry_at = [&](int chunk) { return s + chunk * kThreads + lane * kWaves + wave; };
+    auto entry = [&](int chunk) { return a.a_rec[min(entry_at(chunk), e - 1)]; };
+    const int steps = kWin / a.window;                         // windows per step
+    const bool one = a.table == nullptr;
+    auto segment = [&](int32_t c, int w) {
+        const int32_t *from = one ? a.b_start + c : a.table + ((int64_t)c * (a.windows + 1) + w);
+        return make_int2(from[0], from[one ? 1 : min(steps, a.windows - w)]);
+    };
+    const uint32_t *offset = a.offset + (int64_t)task.y * a.windows;
+    int w = task.z, chunk = 0, ahead = chunks > 1 ? 1 : 0;
+    int2 x0 = entry(0), seg0 = segment(x0.x, w), x1 = entry(ahead);
+    int64_t first = row_first + offset[w];
+    sync();
+    while (true) {
+        const bool step_ends = chunk == chunks - 1;
+        const int2 seg1 = segment(x1.x, min(step_ends ? w + steps : w, a.windows - 1));
+        ahead = ahead == chunks - 1 ? 0 : ahead + 1;
+        const int2 x2 = entry(ahead);
+        // (in bounds whatever an operand that was not validated holds)
+        const int32_t p = max(seg0.x, 0), q = entry_at(chunk) < e ? min(seg0.y, a.b_nnz) : 0;
+        const float scaled = __uint_as_float((uint32_t)x0.y) * a.a_scale;
+        const int av = sizeof(Acc) == 8 && !std::is_floating_point<Acc>::value ? (int)scaled : (int)__float_as_uint(scaled);
+        stream_segments<uint32_t>(
+            p, q - p, av, [&](int p) { return (a.pack + p)[(unsigned)lane]; },
+            [&](uint32_t x, float f) {
+                const uint32_t c = x & (uint32_t)(kWin - 1);
                 const float b = (float)__builtin_bit_cast(_Float16, (uint16_t)(x >> 16));
-                unsafeAtomicAdd(&acc[c], f * b);
-                atomicOr(&bits[c >> 5], 1u << (c & 31));
-            };
-            while (left) {
-                constexpr int kBatch = 8;
-                int32_t pu[kBatch], qu[kBatch];
-                float au[kBatch];
-                uint32_t x[kBatch];
+                if constexpr (std::is_floating_point<Acc>::value) unsafeAtomicAdd(&acc[c], (double)(f * b));
+                else if constexpr (sizeof(Acc) == 4) atomicAdd(&acc[c], (int)(f * b));
+                else
+                    atomicAdd(reinterpret_cast<unsigned long long *>(&acc[c]),
+                              (unsigned long long)((long long)(int)__float_as_uint(f) * (int)(b * a.b_scale)));
+                atomicOr(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(bits) + ((c >> 3) & ~3u)), 1u << (c & 31));
+            });
+        if (step_ends) {
+            const int w_next = min(w + steps, task.w);
+            const int64_t last = w_next < a.windows ? row_first + offset[w_next] : row_end;
+            sync();
+            for (int part0 = 0; part0 < columns; part0 += kWaves * 2048) {
+                const int part = part0 + wave * 2048;
+                uint32_t word = part < columns ? bits[part / 32 + lane] : 0u;
+                const uint32_t n = __popc(word), inc = wave_inclusive_scan(n);
+                const int total = __builtin_amdgcn_readlane((int)inc, 63);
+                int64_t at = first;
+                if constexpr (kWaves > 1) {
+                    if (lane == 0) s_total[wave] = total;
+                    __syncthreads();
+                    int before = 0, all = 0;
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const int src = left ? __ffsll((long long)left) - 1 : 0;
-                    pu[u] = __builtin_amdgcn_readlane(p, src);
-                    qu[u] = left ? __builtin_amdgcn_readlane(q, src) : 0;
-                    au[u] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane(av, src));
-                    left &= left - 1;
-                }
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) x[u] = pu[u] + lane < qu[u] ? a.pack[pu[u] + lane] : 0u;
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    if (pu[u] + lane < qu[u]) add(x[u], au[u]);
-                    for (int32_t k = pu[u] + 64; k < qu[u]; k += 256) {
-                        uint32_t y[4];
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) y[v] = k + 64 * v + lane < qu[u] ? a.pack[k + 64 * v + lane] : 0u;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (k + 64 * v + lane < qu[u]) add(y[v], au[u]);
+                    for (int v = 0; v < kWaves; ++v) {
+                        before += v < wave ? s_total[v] : 0;
+                        all += s_total[v];
                     }
+                    at += before;
+                    first += all;
+                } else {
+                    first += total;
                 }
+                auto emit = [&](int64_t to, int c, Acc v) {
+                    if (to >= last) return;
+                    a.c_col[to] = w * a.window + c;
+                    if constexpr (std::is_floating_point<Acc>::value) a.c_val[to] = (float)v;
+                    else a.c_val[to] = (float)v * a.c_scale;
+                };
+                if (total > 0) bits[part / 32 + lane] = 0;
+                if (total > kFillList) {
+                    const uint32_t before = inc - n;
+                    for (int i = 0; i < 32; ++i) {                     // two words, 64 columns
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * i);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * i + 1);
+                        const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)before, 2 * i);
+                        const int c = part + i * 64 + lane;
+                        if ((lane < 32 ? lo >> lane : hi >> (lane - 32)) & 1u) {
+                            const Acc v = acc[c];
+                            acc[c] = Acc(0);
+                            emit(at + from + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)), c, v);
+                        }
+                    }
+                } else if (total > 0) {
+                    uint16_t *to = list + (inc - n);
+                    while (word) {
+                        *to++ = (uint16_t)(part + lane * 32 + __ffs((int)word) - 1);
+                        word &= word - 1;
+                    }
+                    wave_sync();
+                    for (int i0 = 0; i0 < total; i0 += 128) {
+                        int c[2];
+                        Acc v[2];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) c[u] = list[min(i0 + u * 64 + lane, total - 1)];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) v[u] = acc[c[u]];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const int i = i0 + u * 64 + lane;
+                            if (i < total) {
+                                acc[c[u]] = Acc(0);
+                                emit(at + i, c[u], v[u]);
+                            }
+                        }
+                    }
+                    wave_sync();
+                }
+                if constexpr (kWaves > 1)
+                    if (part0 + kWaves * 2048 < columns) __syncthreads();
             }
+            first = last;
+            w += steps;
+            if (w >= task.w) break;
+            sync();
+            chunk = 0;
+        } else {
+            ++chunk;
         }
-        wave_sync();
-        int64_t at = first;
-        for (int part = 0; part < kWin / 2048; ++part) {
-            uint32_t word = bits[part * 64 + lane];
-            const uint32_t n = __popc(word), inc = wave_inclusive_scan(n);
-            const int total = __builtin_amdgcn_readlane((int)inc, 63);
-            if (!total) continue;
-            bits[part * 64 + lane] = 0;
-            uint32_t to = inc - n;
-            while (word) {
-                const int b = __ffs((int)word) - 1;
-                word &= word - 1;
-                list[to++] = (uint16_t)(part * 2048 + lane * 32 + b);
-            }
-            wave_sync();
-            for (int i = lane; i < total && at + i < last; i += 64) {
-                const int c = list[i];
-                a.c_col[at + i] = w * kWin + c;
-                a.c_val[at + i] = acc[c];
-                acc[c] = 0.f;
-            }
-            at += total;
-            wave_sync();
-        }
+        x0 = x1;
+        seg0 = seg1;
+        x1 = x2;
     }
 }
 
@@ -748,6 +947,36 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, int32_t *
     else f16 ? run(int64_t{}, uint16_t{}) : run(int64_t{}, float{});
 }
 
+// Which accumulator is exact: the bits of the operands' values as integers (multiples of their common granularity), and
+// of a sum of as many products as the longest heavy row of A has entries.
+void launch_fill(FillArgs &f, const int64_t *h, hipStream_t s) {
+    const int ra = (int)h[S_ROW_RANGE_A], rb = (int)h[S_ROW_RANGE_B];
+    const int ea = (ra >> 16) - 256, ga = 256 - (ra & 0xFFFF), eb = (rb >> 16) - 256, gb = 256 - (rb & 0xFFFF);
+    const bool finite = (ra >> 16) < 1023 && (rb >> 16) < 1023;
+    int bits = ea - ga + eb - gb;
+    for (int64_t n = 1; n < h[S_ROW_LONGEST]; n <<= 1) ++bits;
+    const int columns = f.windows * f.window;
+    auto launch = [&](auto kernel, int acc_bytes, int win, int threads) {
+        const int step = std::min(columns, win);
+        const size_t lds = (size_t)step * acc_bytes + step / 8 + (size_t)(threads / 64) * kFillList * 2;
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)f.n_tasks), dim3(threads), lds, s, f);
+    };
+    if (finite && ra && rb && bits <= 31) {
+        f.a_scale = std::ldexp(1.0f, -(ga + gb));
+        f.c_scale = std::ldexp(1.0f, ga + gb);
+        launch(k_heavy_fill<int32_t, 16384, 512>, 4, 16384, 512);
+    } else if (finite && ra && rb && bits <= 63 && ea - ga <= 31 && eb - gb <= 31) {
+        f.a_scale = std::ldexp(1.0f, -ga);
+        f.b_scale = std::ldexp(1.0f, -gb);
+        f.c_scale = std::ldexp(1.0f, ga + gb);
+        launch(k_heavy_fill<long long, 8192, 512>, 8, 8192, 512);
+    } else {
+        f.a_scale = 1.0f;
+        launch(k_heavy_fill<double, 4096, 64>, 8, 4096, 64);
+    }
+}
+
 }  // namespace
 
 // The product A*B has so few intermediate products per candidate pair of tiles that the row kernels are faster.
@@ -768,8 +997,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
 
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
     const int merge_lanes = A->nnz <= 8 * A->rows ? 8 : 16;
-    // windows of columns of the heavy rows: one small one for a narrow C, else 8192 columns
-    const int shift = B->cols <= 2048 ? 11 : B->cols <= 4096 ? 12 : 13;
+    const int shift = B->cols <= 2048 ? 11 : 12;
     const int windows = (int)((B->cols + (1 << shift) - 1) >> shift);
     const bool table_fits = windows == 1 || (B->rows * (windows + 1) * 4 <= (int64_t)4 << 30);
 
@@ -780,6 +1008,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         m.rec = ws.get<int2>((size_t)M->nnz);
         m.ntiles = ws.get<int32_t>((size_t)ntr);
         m.tile_col = ws.get<int32_t>((size_t)M->nnz);
+        m.range = ws.get<uint32_t>((size_t)ntr);
     };
     take(ma, A, a_ntr);
     if (alias) mb = ma;
@@ -816,6 +1045,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         a.a_ntiles = ma.ntiles;
         a.a_tile_col = ma.tile_col;
         a.b_ntiles = mb.ntiles;
+        a.a_range = ma.range;
+        a.b_range = mb.range;
         a.same = alias;
         a.merge_lanes = merge_lanes;
         a.windows = windows;
@@ -863,7 +1094,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     uint32_t *group_len = ws.get<uint32_t>((size_t)a_ntr + 4);
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
     uint32_t *pack = nullptr, *offset = nullptr;
-    int32_t *table = nullptr;
+    int32_t *table = nullptr, *heavy_col = nullptr;
     auto size_rows = [&]() {
         if (n_tasks > task_cap || n_heavy > heavy_cap) {
             // the lists did not fit: make them again, as large as they have to be
@@ -876,7 +1107,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         }
         if (n_heavy > 0) {
             if (!pack) {
-                pack = ws.get<uint32_t>((size_t)B->nnz);
+                pack = ws.get<uint32_t>((size_t)B->nnz + 64);     // (a piece is read whole)
+                heavy_col = ws.get<int32_t>((size_t)B->nnz + 64);
                 if (windows > 1) table = ws.get<int32_t>((size_t)B->rows * (windows + 1));
             }
             offset = ws.get<uint32_t>((size_t)n_heavy * windows);
@@ -896,7 +1128,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         hipLaunchKernelGGL(merge,
                            dim3((unsigned)((A->rows * merge_lanes + 255) / 256)), dim3(256), 0, s, m);
         if (n_heavy > 0) {
-            PackArgs p{B->rows, mb.start, mb.rec, pack, table, windows, shift};
+            PackArgs p{B->rows, mb.start, mb.rec, pack, heavy_col, table, windows, shift};
             if (B->nnz > 16 * B->rows)
                 hipLaunchKernelGGL(k_heavy_pack<64>, dim3((unsigned)((B->rows * 64 + 255) / 256)), dim3(256), 0, s, p);
             else
@@ -909,16 +1141,16 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             c.b_start = mb.start;
             c.ub = ub;
             c.a_rec = ma.rec;
-            c.b_rec = mb.rec;
+            c.b_col = heavy_col;
             c.table = table;
             c.b_nnz = (int32_t)B->nnz;
             c.windows = windows;
-            c.span_windows = (int)std::min<int64_t>(windows, kHeavySpan >> shift);
+            c.span_windows = std::min(windows, kSpanWindows);
             c.row_nnz = row_nnz;
             c.group_len = group_len;
             c.offset = offset;
             const size_t lds = (size_t)c.span_windows << (shift - 3);
-            auto kernel = shift == 11 ? k_heavy_count<2048> : shift == 12 ? k_heavy_count<4096> : k_heavy_count<8192>;
+            auto kernel = shift == 11 ? k_heavy_count<2048> : k_heavy_count<4096>;
             hipLaunchKernelGGL(kernel, dim3((unsigned)n_heavy), dim3(kHeavyThreads), lds, s, c);
         }
         return (int)TSP_OK;
@@ -1004,8 +1236,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             f.c_val = val;
             f.d_scalars_to_clear = clear;
             cleared = clear != nullptr;
-            auto kernel = shift == 11 ? k_heavy_fill<2048> : shift == 12 ? k_heavy_fill<4096> : k_heavy_fill<8192>;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)n_tasks), dim3(64), 0, s, f);
+            f.window = 1 << shift;
+            launch_fill(f, ctx->h_scalars, s);
         }
         TSP_HIP_CHECK(ctx, hipGetLastError());
         ctx->scalars_clean = cleared;
