@@ -31,6 +31,7 @@ constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this ma
 constexpr int kHeavyThreads = 512;
 constexpr int32_t kNoCol = 0x7FFFFFFF;
 // Intermediate products behind one task of k_heavy_fill (a row, or some of its windows)
+constexpr int64_t kKeptPattern = (int64_t)16 << 30;   // bytes of it, at most
 constexpr int kTaskProducts = 65536;
 constexpr int64_t kRowPairProducts = 64; // products per candidate pair of tiles up to which the rows are the better way
 
@@ -506,99 +507,127 @@ __global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a) {
 }
 
 // ---- heavy rows -------------------------------------------------------------------------------------------------
-// B for the heavy rows: 4 bytes per entry {low 16 bits of the column, fp16 value}, and where every row of B enters
-// every window of columns; the columns once more by themselves.  L lanes per row.
+// B for the heavy rows, L lanes per row.  For the multiplication: 4 bytes per entry {low 16 bits of the column, fp16
+// value}, and where every row of B enters every window of columns.  For the sizing: the columns of a row as words of 32
+// {index of the word, its bits}, at the position of the row's first entry (on a power-law graph, weighted by use, two
+// columns share a word).
 struct PackArgs {
     int64_t rows;
     const int32_t *start;
     const int2 *rec;
     uint32_t *pack;
-    int32_t *col;
+    uint2 *word;
+    int32_t *words;                      // per row
     int32_t *table;                      // [rows][windows + 1], or null for one window
     int windows, shift;                  // a window is 1 << shift columns
 };
 template <int L>
 __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
     const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L;
-    const int l = threadIdx.x % L;
-    if (row >= a.rows) return;
-    const int32_t s = a.start[row], e = max(s, a.start[row + 1]);
-    int32_t *tab = a.table ? a.table + row * (a.windows + 1) : nullptr;
-    for (int32_t k = s + l; k < e; k += L) {
-        const int2 x = a.rec[k];
-        const _Float16 v = (_Float16)__uint_as_float((uint32_t)x.y);
-        a.col[k] = x.x;
-        a.pack[k] = ((uint32_t)x.x & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
-        if (tab) {
-            const int before = k > s ? a.rec[k - 1].x >> a.shift : -1;
-            for (int w = before + 1; w <= (x.x >> a.shift) && w <= a.windows; ++w) tab[w] = k;
-        }
+    const int l = threadIdx.x % L, lane = lane_id();
+    int32_t s = 0, e = 0;
+    if (row < a.rows) {
+        s = a.start[row];
+        e = max(s, a.start[row + 1]);
     }
+    int32_t *tab = a.table && row < a.rows ? a.table + row * (a.windows + 1) : nullptr;
+    int32_t at = s;
+    for (int32_t k0 = s; __any(k0 < e); k0 += L) {
+        const int32_t k = k0 + l;
+        bool leads = false;                                  // the first entry of a word
+        if (k < e) {
+            const int2 x = a.rec[k];
+            const int32_t before = k > s ? a.rec[k - 1].x : -1;
+            const _Float16 v = (_Float16)__uint_as_float((uint32_t)x.y);
+            a.pack[k] = ((uint32_t)x.x & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
+            if (tab)
+                for (int w = (before >> a.shift) + 1; w <= (x.x >> a.shift) && w <= a.windows; ++w) tab[w] = k;
+            leads = before < 0 || (before >> 5) != (x.x >> 5);
+        }
+        const unsigned long long all = __ballot(leads);
+        const unsigned long long mine = L == 64 ? all : (all >> (lane & ~(L - 1))) & ((1ull << (L & 63)) - 1ull);
+        if (leads) {
+            const int32_t word = a.rec[k].x >> 5;
+            uint32_t m = 0;
+            for (int32_t j = k; j < e; ++j) {
+                const int32_t c = a.rec[j].x;
+                if ((c >> 5) != word) break;
+                m |= 1u << (c & 31);
+            }
+            a.word[at + __popcll(mine & ((1ull << l) - 1ull))] = make_uint2((uint32_t)word, m);
+        }
+        at += __popcll(mine);
+    }
+    if (row < a.rows && l == 0) a.words[row] = at - s;
     if (tab) {
         const int last = e > s ? min(a.rec[e - 1].x >> a.shift, a.windows - 1) : -1;
         for (int w = last + 1 + l; w <= a.windows; w += L) tab[w] = e;
     }
 }
 
-// The segments of B behind up to 64 entries of A, one per lane (first entry, length, value a_ik), as a stream of pieces of
-// at most 64 entries, segment by segment: load(p) fetches entry p + lane of a piece, apply(x, a) takes what a lane below
-// the piece's length got.  Eight pieces are requested while the eight before them are applied, across the ends of
-// segments, so that a memory round trip is paid once per chunk and not per segment; everything that steers the stream
-// is scalar.  load must be allowed to read up to 63 entries past a segment.
-template <typename X, typename Load, typename Apply>
-__device__ __forceinline__ void stream_segments(int p, int len, int av, Load load, Apply apply) {
-    constexpr int kBatch = 8;
+// The segments of B behind up to 64 entries of A, one per lane (first element, length, 16 bits of its own), as pieces of G
+// elements, 64 / G pieces to a step of the wave.  The lanes describe 64 pieces at a time (lane j: piece j of the
+// concatenation; the segment it lies in from a running maximum over the marks the segments leave at their first pieces)
+// in LDS, and a step reads its pieces' descriptions back: nothing is scalar and nothing is selected per piece, and up to
+// eight steps' elements are requested together.  use(x, active, bits) gets every element once; lanes past the end of a piece
+// get other elements (up to G - 1 past the segment) with active = false.
+struct PieceLds {
+    uint2 piece[64];                     // {byte offset of the first element, elements << 16 | bits}
+    uint32_t mark[64];
+};
+template <int G, typename X, typename Use>
+__device__ __forceinline__ void stream_pieces(int p, int len, uint32_t own, const X *from, PieceLds *lds, Use use) {
+    constexpr int kPer = 64 / G;
     const int lane = lane_id();
-    const unsigned long long some = __ballot(len > 0);
-    if (!some) return;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    // the segments that hold something, in the order of their lanes
-    const int to = (len > 0 ? __popcll(some & below) : __popcll(some) + __popcll(~some & below)) * 4;
-    p = __builtin_amdgcn_ds_permute(to, p);
-    av = __builtin_amdgcn_ds_permute(to, av);
-    len = __builtin_amdgcn_ds_permute(to, max(len, 0));
-    int left = (int)wave_sum((uint32_t)(len + 63) >> 6);
-    int i = 0, sp = __builtin_amdgcn_readlane(p, 0), sl = __builtin_amdgcn_readlane(len, 0);
-    struct Batch {
-        X x[kBatch];
-        int n[kBatch];
-        int a[kBatch];
-    };
-    auto fetch = [&](Batch &b) {
+    const int count = len > 0 ? (len + G - 1) / G : 0;
+    const int inc = (int)wave_inclusive_scan((uint32_t)count), first = inc - count;
+    const int total = __builtin_amdgcn_readlane(inc, 63);
+    const uint32_t my_byte = (uint32_t)(lane % G) * sizeof(X);
+    const uint2 *my_piece = lds->piece + lane / G;
+    int carry = 0;
+    for (int j0 = 0; j0 < total; j0 += 64) {
+        lds->mark[lane] = 0;
+        wave_sync();
+        if (count > 0 && (uint32_t)(first - j0) < 64u) lds->mark[first - j0] = (uint32_t)lane + 1u;
+        wave_sync();
+        int m = max((int)lds->mark[lane], lane == 0 ? carry : 0);
+        m = max(m, TSP_DPP(m, m, 0x111, 0xf, false));
+        m = max(m, TSP_DPP(m, m, 0x112, 0xf, false));
+        m = max(m, TSP_DPP(m, m, 0x114, 0xf, false));
+        m = max(m, TSP_DPP(m, m, 0x118, 0xf, false));
+        m = max(m, TSP_DPP(m, m, 0x142, 0xa, false));
+        m = max(m, TSP_DPP(m, m, 0x143, 0xc, false));
+        carry = __builtin_amdgcn_readlane(m, 63);
+        const int source = (m - 1) * 4;
+        const int skip = (j0 + lane - __builtin_amdgcn_ds_bpermute(source, first)) * G;
+        const int begin = __builtin_amdgcn_ds_bpermute(source, p) + skip;
+        const int left = __builtin_amdgcn_ds_bpermute(source, len) - skip;
+        const uint32_t bits = (uint32_t)__builtin_amdgcn_ds_bpermute(source, (int)own);
+        const bool live = j0 + lane < total;
+        lds->piece[lane] = make_uint2(live ? (uint32_t)begin * (uint32_t)sizeof(X) : 0u,
+                                      (live ? (uint32_t)min(left, G) << 16 : 0u) | bits);
+        wave_sync();
+        const int steps = (min(total - j0, 64) + kPer - 1) / kPer;
+        auto batch = [&](auto size, int t) {
+            constexpr int kBatch = decltype(size)::value;
+            uint2 d[kBatch];
+            X x[kBatch];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            b.x[u] = load(sp);
-            b.n[u] = u < left ? sl : 0;
-            b.a[u] = __builtin_amdgcn_readlane(av, i);
-            // (both ways in full, so that they become selects and not branches)
-            const int j = (i + 1) & 63;
-            const int p_next = __builtin_amdgcn_readlane(p, j), l_next = __builtin_amdgcn_readlane(len, j);
-            const int p_on = sp + 64, l_on = sl - 64;
-            const bool more = sl > 64;
-            i = more ? i : j;
-            sp = more ? p_on : p_next;
-            sl = more ? l_on : l_next;
-        }
-        left -= kBatch;
-    };
-    auto use = [&](const Batch &b) {
+            for (int u = 0; u < kBatch; ++u) d[u] = my_piece[min(t + u, G - 1) * kPer];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            if (lane < b.n[u]) apply(b.x[u], __uint_as_float((uint32_t)b.a[u]));
-    };
-    Batch b0, b1;
-    fetch(b0);
-    // (the next batch is requested also when there is none, 8 loads of no use: behind a branch the waits could not tell
-    // the two batches apart)
-    while (true) {
-        const bool more = left > 0;
-        fetch(b1);
-        use(b0);
-        if (!more) break;
-        const bool again = left > 0;
-        fetch(b0);
-        use(b1);
-        if (!again) break;
+            for (int u = 0; u < kBatch; ++u)
+                x[u] = *reinterpret_cast<const X *>(reinterpret_cast<const char *>(from) + (d[u].x + my_byte));
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) use(x[u], (uint32_t)(lane % G) < (t + u < steps ? d[u].y >> 16 : 0u), d[u].y & 0xFFFFu);
+        };
+        int t = 0;
+        for (; t + 8 <= steps; t += 8) batch(std::integral_constant<int, 8>{}, t);
+        const int rest = steps - t;
+        if (rest > 4) batch(std::integral_constant<int, 8>{}, t);
+        else if (rest > 2) batch(std::integral_constant<int, 4>{}, t);
+        else if (rest == 2) batch(std::integral_constant<int, 2>{}, t);
+        else if (rest == 1) batch(std::integral_constant<int, 1>{}, t);
+        wave_sync();
     }
 }
 
@@ -606,106 +635,98 @@ struct CountArgs {
     const int32_t *heavy;
     int64_t heavy_cap;
     const int64_t *d_scalars;
-    const int32_t *a_start, *b_start, *ub;
+    const int32_t *a_start, *b_start;
     const int2 *a_rec;
-    const int32_t *b_col;
-    const int32_t *table;
-    int32_t b_nnz;
+    const uint2 *b_word;
+    const int32_t *b_words;
     int windows;                         // of kWin columns each
     int span_windows;                    // windows whose bits the block's LDS holds
-    int32_t *row_nnz;
+    int32_t *row_nnz;                    // null: only the pattern is wanted
     uint32_t *group_len;
     uint32_t *offset;                    // [heavy][windows] entries of the row before each window
+    int heavy_from;                      // the rows of this launch begin here
+    uint32_t *bits;                      // [heavy - heavy_from][windows][kWin / 32] of the windows that hold something, or null
 };
 
-// A block per heavy row sets one bit per product in LDS; OR is free of order, so the row may be spread over the block.
-// Long segments of B: a wave takes 64 entries of A at a time and streams the segments behind them.  Short ones: the
-// segments behind 512 entries of A are listed in LDS and groups of 8 or 16 lanes take one each.
+// A block per heavy row ORs the words of the rows of B behind it into one bit per column in LDS; OR is free of order, so
+// the row may be spread over the block: entry i of the row of A goes to wave i mod the number of waves that get 16 and more.
 template <int kWin>
 __global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a) {
     extern __shared__ __align__(16) uint32_t bits[];
-    __shared__ int2 s_seg[kHeavyThreads];
-    __shared__ uint32_t s_cnt[64];
+    constexpr int kWaves = kHeavyThreads / 64;
+    __shared__ PieceLds s_piece[kWaves];
+    __shared__ uint32_t s_cnt[kSpanWindows];
     __shared__ uint32_t s_run;
     constexpr int kWords = kWin / 32, kPerLane = kWords / 64;
-    const int64_t h = blockIdx.x;
-    if (h >= a.heavy_cap || h >= a.d_scalars[S_ROW_HEAVY]) return;
+    const int64_t h = a.heavy_from + (int64_t)blockIdx.x;
+    if (h >= a.heavy_cap || (a.d_scalars && h >= a.d_scalars[S_ROW_HEAVY])) return;
     const int32_t row = a.heavy[h];
     const int32_t s = a.a_start[row], e = a.a_start[row + 1];
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    for (int w = threadIdx.x; w < a.span_windows * kWords; w += kHeavyThreads) bits[w] = 0;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int w = threadIdx.x; w < a.span_windows * kWords + 64; w += kHeavyThreads) bits[w] = 0;
     if (threadIdx.x == 0) s_run = 0;
-    const int mean = e > s ? a.ub[row] / (e - s) : 0;            // length of the rows of B behind this row
+    const int dealt = min(kWaves, (e - s + 15) / 16);
     for (int w0 = 0; w0 < a.windows; w0 += a.span_windows) {
         const int w1 = min(w0 + a.span_windows, a.windows);
-        const int32_t c0 = w0 * kWin;
-        const uint32_t limit = (uint32_t)(w1 - w0) * kWin;
-        auto segment = [&](int32_t entry) {
-            const int32_t c = a.a_rec[entry].x;
-            if (a.windows <= a.span_windows) return make_int2(a.b_start[c], a.b_start[c + 1]);
-            const int32_t *tab = a.table + (int64_t)c * (a.windows + 1);
-            return make_int2(max(tab[w0], 0), min(tab[w1], a.b_nnz));
-        };
-        auto mark = [&](int32_t col) {
-            const uint32_t x = (uint32_t)(col - c0);
-            if (x < limit) atomicOr(&bits[x >> 5], 1u << (x & 31));
-        };
+        const uint32_t first = (uint32_t)w0 * kWords, words = (uint32_t)(w1 - w0) * kWords;
         __syncthreads();
-        if (mean > 16) {
-            for (int32_t base = s + wave * 64; base < e; base += kHeavyThreads) {
-                int2 seg = make_int2(0, 0);
-                if (base + lane < e) seg = segment(base + lane);
-                stream_segments<int32_t>(
-                    seg.x, seg.y - seg.x, 0, [&](int p) { return (a.b_col + p)[(unsigned)lane]; },
-                    [&](int32_t col, float) { mark(col); });
+        for (int32_t base = s; base < e && wave < dealt; base += 64 * dealt) {
+            const int32_t k = base + lane * dealt + wave;
+            int32_t p = 0, len = 0;
+            if (k < e) {
+                const int32_t c = a.a_rec[k].x;
+                p = a.b_start[c];
+                len = a.b_words[c];
             }
-        } else {
-            const int sh = mean > 8 ? 4 : 3, lanes = 1 << sh, subs = kHeavyThreads >> sh;
-            const int sub = threadIdx.x >> sh, j0 = threadIdx.x & (lanes - 1);
-            for (int32_t base = s; base < e; base += kHeavyThreads) {
-                const int n = min(e - base, kHeavyThreads);
-                __syncthreads();
-                if ((int)threadIdx.x < n) s_seg[threadIdx.x] = segment(base + threadIdx.x);
-                __syncthreads();
-                for (int i = sub; i < n; i += 4 * subs) {
-                    int32_t p[4], q[4], c[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int2 seg = s_seg[min(i + u * subs, n - 1)];
-                        p[u] = seg.x + j0;
-                        q[u] = i + u * subs < n ? seg.y : 0;
-                        c[u] = p[u] < q[u] ? a.b_col[p[u]] : -1;
+            if (a.windows > a.span_windows) {                // the stretch of the row's words inside the span
+                int32_t lo[2];
+                for (int side = 0; side < 2; ++side) {
+                    const uint32_t bound = first + (side ? words : 0u);
+                    int32_t x = 0, y = len;
+                    while (x < y) {
+                        const int32_t mid = (x + y) >> 1;
+                        if (a.b_word[p + mid].x < bound) x = mid + 1;
+                        else y = mid;
                     }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (p[u] < q[u]) mark(c[u]);
-                        for (p[u] += lanes; p[u] < q[u]; p[u] += lanes) mark(a.b_col[p[u]]);
-                    }
+                    lo[side] = x;
                 }
+                p += lo[0];
+                len = lo[1] - lo[0];
             }
+            stream_pieces<16, uint2>(p, len, 0u, a.b_word, &s_piece[wave], [&](uint2 x, bool active, uint32_t) {
+                // (lanes without an element, and words an operand that was not validated may hold out of order, go to
+                // words behind the bits that nothing reads)
+                const uint32_t at = x.x - first;
+                atomicOr(&bits[active && at < words ? at : words + lane], x.y);
+            });
         }
         __syncthreads();
         for (int w = wave; w < w1 - w0; w += kHeavyThreads / 64) {
-            uint32_t n = 0;
+            uint32_t n = 0, word[kPerLane];
 #pragma unroll
             for (int i = 0; i < kPerLane; ++i) {
-                uint32_t *word = &bits[w * kWords + i * 64 + lane];
-                n += __popc(*word);
-                *word = 0;
+                uint32_t *at = &bits[w * kWords + i * 64 + lane];
+                word[i] = *at;
+                n += __popc(word[i]);
+                *at = 0;
             }
             n = wave_sum(n);
+            if (a.bits && n > 0)
+#pragma unroll
+                for (int i = 0; i < kPerLane; ++i)
+                    a.bits[((h - a.heavy_from) * a.windows + w0 + w) * kWords + i * 64 + lane] = word[i];
             if (lane == 0) s_cnt[w] = n;
         }
         __syncthreads();
         if (wave == 0) {
             const uint32_t n = lane < w1 - w0 ? s_cnt[lane] : 0;
             const uint32_t inc = wave_inclusive_scan(n), before = s_run;
-            if (lane < w1 - w0) a.offset[h * a.windows + w0 + lane] = before + inc - n;
+            if (lane < w1 - w0 && a.row_nnz) a.offset[h * a.windows + w0 + lane] = before + inc - n;
             if (lane == 63) s_run = before + inc;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && a.row_nnz) {
         a.row_nnz[row] = (int32_t)s_run;
         atomicAdd(&a.group_len[row / T], s_run);
     }
@@ -721,35 +742,51 @@ struct FillArgs {
     int32_t b_nnz;
     int windows;
     const uint32_t *offset;
+    const uint32_t *bits;                // pattern of heavy rows [heavy_from, heavy_to) of C from the sizing pass
+    int heavy_from, heavy_to;
     const int64_t *c_row_ptr;
     int32_t *c_col;
     float *c_val;
     int window;                          // columns
-    float a_scale, b_scale, c_scale;     // integers from the values, values from the integer sums
+    float p_scale, c_scale;              // integers from the products, values from the integer sums
     int64_t *d_scalars_to_clear;
 };
 
 // A block per task: a row of C, kWin columns at a time (some of its windows).  Its waves deal the entries of the row of
-// A among them, 64 apiece, and stream the segments of B behind them into a dense accumulator in LDS, with a bit per
-// column; then every wave lists the entries of 2048 columns from the bits (or, where more than a quarter is there, walks
-// the columns) and writes them 64 to a store.  The segments of the next step and the entries of the one after are
-// requested ahead.
+// A among them, 64 apiece, and stream the segments of B behind them into a dense accumulator in LDS.  What is there to
+// be written the sizing pass has left as a bit per column (marking a bit per product here costs as much as all the rest:
+// neighbouring columns hit one word, and LDS takes atomics on one word one by one): every wave lists the entries of its
+// 2048 columns from the bits, a word per lane (or, where more than a quarter is there, walks the columns), and writes
+// them 64 to a store.  The next step's bits and segments and the entries after those are requested ahead.
 //
 // The accumulator: LDS adds an fp32 number one lane after the other (193 cycles for a wave's 64 lanes, measured), an
 // integer or an fp64 number all lanes at a time (5, 8 and 8 to 16 cycles for 32-bit and 64-bit integers and fp64).  So
 // the sums are integers where they are exact in them, and fp64 otherwise; fp64 only with a block of one wave, which
-// fixes the order of the additions.
+// fixes the order of the additions.  64-bit integers: p * 2^k + 1.5 * 2^52 in fp64 holds the integer p * 2^k in its low
+// bits (|p * 2^k| < 2^51).
+//
+// Steps of 8192 columns with four waves: 33 KB of LDS, 16 waves per CU.  R-MAT scale 18: 16384 columns with 8 waves
+// 30.7 ms, 8192 with 2, 4, 8 waves 37.7, 27.6, 44.6 ms, 4096 with 1, 2, 4 waves 41.8, 29.4, 32.9 ms.
 constexpr int kFillList = 512;           // entries a wave lists at a time
+
+// A value that is the same for the whole wave and that no kernel running now writes, through the scalar cache.
+template <typename X>
+__device__ __forceinline__ X uniform_load(const X *p) {
+    return *(const __attribute__((address_space(4))) X *)(uintptr_t)p;
+}
+
 template <typename Acc, int kWin, int kThreads>
 __global__ __launch_bounds__(kThreads) void k_heavy_fill(const FillArgs a) {
-    constexpr int kWaves = kThreads / 64;
+    constexpr int kWaves = kThreads / 64, kParts = kWin / 2048 / kWaves;
+    static_assert(kParts >= 1 && kParts * kWaves * 2048 == kWin, "whole parts of 2048 columns for every wave");
     extern __shared__ __align__(16) unsigned char fill_lds[];
+    __shared__ union { PieceLds pieces; uint16_t list[kFillList]; } s_wave[kWaves];
+    __shared__ int s_total[kWaves * kParts];
     const int columns = min(kWin, a.windows * a.window);       // of a step
+    // (behind the accumulators a place per lane for lanes without an element)
     Acc *acc = reinterpret_cast<Acc *>(fill_lds);
-    uint32_t *bits = reinterpret_cast<uint32_t *>(acc + columns);
-    uint16_t *list = reinterpret_cast<uint16_t *>(bits + columns / 32) + (threadIdx.x >> 6) * kFillList;
-    __shared__ int s_total[kWaves];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    uint16_t *list = s_wave[wave].list;
     auto sync = [] {
         if constexpr (kThreads == 64) wave_sync();
         else __syncthreads();
@@ -757,132 +794,167 @@ __global__ __launch_bounds__(kThreads) void k_heavy_fill(const FillArgs a) {
     if (a.d_scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) a.d_scalars_to_clear[threadIdx.x] = 0;
     const int64_t t = blockIdx.x;
     if (t >= a.n_tasks) return;
-    const int4 task = a.tasks[t];
-    const int32_t row = task.x, s = a.a_start[row], e = a.a_start[row + 1];
-    const int64_t row_first = a.c_row_ptr[row], row_end = a.c_row_ptr[row + 1];
-    const int chunks = (e - s + kThreads - 1) / kThreads;      // every wave takes its 64 entries of each
-    if (chunks <= 0 || task.z >= task.w) return;
-    for (int i = threadIdx.x; i < columns * (int)sizeof(Acc) / 16; i += kThreads)
-        reinterpret_cast<uint4 *>(acc)[i] = make_uint4(0, 0, 0, 0);
-    for (int i = threadIdx.x; i < columns / 32; i += kThreads) bits[i] = 0;
-    // (requested without branches around the loads, which would wait for them: lanes past the end repeat the last entry)
-    auto entry_at = [&](int chunk) { return s + chunk * kThreads + lane * kWaves + wave; };
-    auto entry = [&](int chunk) { return a.a_rec[min(entry_at(chunk), e - 1)]; };
+    const int32_t row = uniform_load(&a.tasks[t].x), heavy = uniform_load(&a.tasks[t].y);
+    int w = uniform_load(&a.tasks[t].z);
+    const int w_end = uniform_load(&a.tasks[t].w);
+    const int32_t s = uniform_load(a.a_start + row), deg = uniform_load(a.a_start + row + 1) - s;
+    const int64_t row_first = uniform_load(a.c_row_ptr + row);
+    const uint32_t row_len = (uint32_t)(uniform_load(a.c_row_ptr + row + 1) - row_first);
+    if (heavy < a.heavy_from || heavy >= a.heavy_to || deg <= 0 || w >= w_end) return;
+    const uint32_t *offset = a.offset + (int64_t)heavy * a.windows;
+    const uint32_t *kept = a.bits + (int64_t)(heavy - a.heavy_from) * a.windows * (a.window / 32);
     const int steps = kWin / a.window;                         // windows per step
     const bool one = a.table == nullptr;
-    auto segment = [&](int32_t c, int w) {
-        const int32_t *from = one ? a.b_start + c : a.table + ((int64_t)c * (a.windows + 1) + w);
-        return make_int2(from[0], from[one ? 1 : min(steps, a.windows - w)]);
+    const int dealt = min(kWaves, (deg + 15) / 16);            // waves that take entries of A
+    const int chunks = (deg + 64 * dealt - 1) / (64 * dealt);  // 64 entries for each of them
+    const bool works = wave < dealt;
+
+    for (int i = threadIdx.x; i < columns * (int)sizeof(Acc) / 16; i += kThreads)
+        reinterpret_cast<uint4 *>(acc)[i] = make_uint4(0, 0, 0, 0);
+    auto entry_at = [&](int chunk) { return (chunk * 64 + lane) * dealt + wave; };
+    auto entry = [&](int chunk) {
+        int2 x = make_int2(-1, 0);
+        if (works && entry_at(chunk) < deg) x = a.a_rec[s + entry_at(chunk)];
+        return x;
     };
-    const uint32_t *offset = a.offset + (int64_t)task.y * a.windows;
-    int w = task.z, chunk = 0, ahead = chunks > 1 ? 1 : 0;
-    int2 x0 = entry(0), seg0 = segment(x0.x, w), x1 = entry(ahead);
-    int64_t first = row_first + offset[w];
-    sync();
-    while (true) {
-        const bool step_ends = chunk == chunks - 1;
-        const int2 seg1 = segment(x1.x, min(step_ends ? w + steps : w, a.windows - 1));
-        ahead = ahead == chunks - 1 ? 0 : ahead + 1;
-        const int2 x2 = entry(ahead);
-        // (in bounds whatever an operand that was not validated holds)
-        const int32_t p = max(seg0.x, 0), q = entry_at(chunk) < e ? min(seg0.y, a.b_nnz) : 0;
-        const float scaled = __uint_as_float((uint32_t)x0.y) * a.a_scale;
-        const int av = sizeof(Acc) == 8 && !std::is_floating_point<Acc>::value ? (int)scaled : (int)__float_as_uint(scaled);
-        stream_segments<uint32_t>(
-            p, q - p, av, [&](int p) { return (a.pack + p)[(unsigned)lane]; },
-            [&](uint32_t x, float f) {
-                const uint32_t c = x & (uint32_t)(kWin - 1);
-                const float b = (float)__builtin_bit_cast(_Float16, (uint16_t)(x >> 16));
-                if constexpr (std::is_floating_point<Acc>::value) unsafeAtomicAdd(&acc[c], (double)(f * b));
-                else if constexpr (sizeof(Acc) == 4) atomicAdd(&acc[c], (int)(f * b));
-                else
-                    atomicAdd(reinterpret_cast<unsigned long long *>(&acc[c]),
-                              (unsigned long long)((long long)(int)__float_as_uint(f) * (int)(b * a.b_scale)));
-                atomicOr(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(bits) + ((c >> 3) & ~3u)), 1u << (c & 31));
-            });
-        if (step_ends) {
-            const int w_next = min(w + steps, task.w);
-            const int64_t last = w_next < a.windows ? row_first + offset[w_next] : row_end;
-            sync();
-            for (int part0 = 0; part0 < columns; part0 += kWaves * 2048) {
-                const int part = part0 + wave * 2048;
-                uint32_t word = part < columns ? bits[part / 32 + lane] : 0u;
-                const uint32_t n = __popc(word), inc = wave_inclusive_scan(n);
-                const int total = __builtin_amdgcn_readlane((int)inc, 63);
-                int64_t at = first;
-                if constexpr (kWaves > 1) {
-                    if (lane == 0) s_total[wave] = total;
-                    __syncthreads();
-                    int before = 0, all = 0;
+    auto segment = [&](int32_t c, int v) {
+        int2 seg = make_int2(0, 0);
+        if (c >= 0 && v < w_end) {
+            const int32_t *from = one ? a.b_start + c : a.table + ((int64_t)c * (a.windows + 1) + v);
+            seg.x = from[0];
+            seg.y = from[one ? 1 : min(steps, a.windows - v)];
+        }
+        return seg;
+    };
+    auto begin_of = [&](int v) { return v < a.windows ? uniform_load(offset + v) : row_len; };
+    // the bits of the wave's parts of the step at window v (empty windows have left none behind)
+    struct Bits {
+        uint32_t word[kParts];
+    };
+    auto pattern = [&](int v) {
+        Bits b;
 #pragma unroll
-                    for (int v = 0; v < kWaves; ++v) {
-                        before += v < wave ? s_total[v] : 0;
-                        all += s_total[v];
-                    }
-                    at += before;
-                    first += all;
-                } else {
-                    first += total;
-                }
-                auto emit = [&](int64_t to, int c, Acc v) {
-                    if (to >= last) return;
-                    a.c_col[to] = w * a.window + c;
-                    if constexpr (std::is_floating_point<Acc>::value) a.c_val[to] = (float)v;
-                    else a.c_val[to] = (float)v * a.c_scale;
+        for (int q = 0; q < kParts; ++q) {
+            const int part = (wave * kParts + q) * 2048, at = v + part / a.window;
+            b.word[q] = 0;
+            if (part < columns && at < w_end && begin_of(at) != begin_of(at + 1))
+                b.word[q] = kept[(size_t)at * (a.window / 32) + (part % a.window) / 32 + lane];
+        }
+        return b;
+    };
+    int2 x0 = entry(0), seg0 = segment(x0.x, w), x1 = chunks > 1 ? entry(1) : x0;
+    Bits now = pattern(w);
+    int ahead = chunks > 1 ? 1 : 0;
+    sync();
+    for (; w < w_end; w += steps) {
+        const int w_next = min(w + steps, w_end);
+        const uint32_t first = begin_of(w), some = begin_of(w_next) - first;
+        const Bits next = pattern(w_next);
+        uint32_t inc[kParts];
+        int total[kParts];
+#pragma unroll
+        for (int q = 0; q < kParts; ++q) {
+            inc[q] = wave_inclusive_scan(__popc(now.word[q]));
+            total[q] = __builtin_amdgcn_readlane((int)inc[q], 63);
+            if (kWaves > 1 && lane == 0) s_total[wave * kParts + q] = total[q];
+        }
+        for (int chunk = 0; chunk < chunks && works; ++chunk) {
+            const bool last = chunk == chunks - 1;
+            int2 seg1, x2 = x1;
+            if (chunks == 1 && !one) {                         // the same entries: a segment begins where the last one ended
+                seg1 = make_int2(seg0.y, seg0.y);
+                if (x0.x >= 0 && w_next < w_end)
+                    seg1.y = a.table[(int64_t)x0.x * (a.windows + 1) + min(w_next + steps, a.windows)];
+            } else {
+                seg1 = segment(x1.x, last ? w_next : w);
+                ahead = ahead == chunks - 1 ? 0 : ahead + 1;
+                x2 = entry(ahead);
+            }
+            // (in bounds whatever an operand that was not validated holds)
+            const int32_t p = max(seg0.x, 0), q = min(seg0.y, a.b_nnz);
+            const _Float16 av = (_Float16)__uint_as_float((uint32_t)x0.y);
+            if (some)
+                stream_pieces<kThreads == 64 ? 64 : 16, uint32_t>(
+                    p, q - p, (uint32_t)__builtin_bit_cast(uint16_t, av), a.pack, &s_wave[wave].pieces,
+                    [&](uint32_t x, bool active, uint32_t own) {
+                        const uint32_t at = active ? x & (uint32_t)(kWin - 1) : (uint32_t)(columns + lane);
+                        // the product of two fp16 numbers is exact; + 0 makes a positive zero of a negative one
+                        const float product = __builtin_fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)(x >> 16)),
+                                                             (float)__builtin_bit_cast(_Float16, (uint16_t)own), 0.f);
+                        if constexpr (std::is_floating_point<Acc>::value) {
+                            if (active) unsafeAtomicAdd(&acc[at], (double)product);
+                        } else if constexpr (sizeof(Acc) == 4) {
+                            atomicAdd(&acc[at], (int)(product * a.p_scale));
+                        } else {
+                            const double shifted = __builtin_fma((double)product, (double)a.p_scale, 6755399441055744.0);
+                            atomicAdd(reinterpret_cast<unsigned long long *>(&acc[at]),
+                                      __builtin_bit_cast(unsigned long long, shifted) - 0x4338000000000000ull);
+                        }
+                    });
+            x0 = x1;
+            seg0 = seg1;
+            x1 = x2;
+        }
+        if (some) {
+            sync();
+            int before = 0;                                    // entries of the step in the parts before
+            if constexpr (kWaves > 1)
+                for (int v = 0; v < wave * kParts; ++v) before += s_total[v];
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) {
+                const int part = (wave * kParts + q) * 2048;
+                // (never past the step's entries, whatever an operand that was not validated holds)
+                const int n = min(total[q], (int)some - before);
+                int32_t *to_col = a.c_col + row_first + first + before;
+                float *to_val = a.c_val + row_first + first + before;
+                before += total[q];
+                const int32_t c_first = w * a.window;
+                auto emit = [&](int i, int c, Acc v) {
+                    if (i >= n) return;
+                    to_col[(unsigned)i] = c_first + c;
+                    to_val[(unsigned)i] = std::is_floating_point<Acc>::value ? (float)v : (float)v * a.c_scale;
                 };
-                if (total > 0) bits[part / 32 + lane] = 0;
-                if (total > kFillList) {
-                    const uint32_t before = inc - n;
-                    for (int i = 0; i < 32; ++i) {                     // two words, 64 columns
+                uint32_t word = now.word[q];
+                if (total[q] > kFillList) {
+                    const uint32_t mine = inc[q] - __popc(word);
+                    for (int i = 0; i < 32; ++i) {             // two words, 64 columns
                         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * i);
                         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * i + 1);
-                        const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)before, 2 * i);
+                        const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)mine, 2 * i);
                         const int c = part + i * 64 + lane;
                         if ((lane < 32 ? lo >> lane : hi >> (lane - 32)) & 1u) {
                             const Acc v = acc[c];
                             acc[c] = Acc(0);
-                            emit(at + from + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)), c, v);
+                            emit((int)(from + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))), c, v);
                         }
                     }
-                } else if (total > 0) {
-                    uint16_t *to = list + (inc - n);
+                } else if (total[q] > 0) {
+                    uint16_t *to = list + (inc[q] - __popc(word));
                     while (word) {
                         *to++ = (uint16_t)(part + lane * 32 + __ffs((int)word) - 1);
                         word &= word - 1;
                     }
                     wave_sync();
-                    for (int i0 = 0; i0 < total; i0 += 128) {
+                    for (int i0 = 0; i0 < total[q]; i0 += 128) {
                         int c[2];
                         Acc v[2];
 #pragma unroll
-                        for (int u = 0; u < 2; ++u) c[u] = list[min(i0 + u * 64 + lane, total - 1)];
+                        for (int u = 0; u < 2; ++u) c[u] = list[min(i0 + u * 64 + lane, total[q] - 1)];
 #pragma unroll
                         for (int u = 0; u < 2; ++u) v[u] = acc[c[u]];
 #pragma unroll
-                        for (int u = 0; u < 2; ++u) {
-                            const int i = i0 + u * 64 + lane;
-                            if (i < total) {
+                        for (int u = 0; u < 2; ++u)
+                            if (i0 + u * 64 + lane < total[q]) {
                                 acc[c[u]] = Acc(0);
-                                emit(at + i, c[u], v[u]);
+                                emit(i0 + u * 64 + lane, c[u], v[u]);
                             }
-                        }
                     }
                     wave_sync();
                 }
-                if constexpr (kWaves > 1)
-                    if (part0 + kWaves * 2048 < columns) __syncthreads();
             }
-            first = last;
-            w += steps;
-            if (w >= task.w) break;
-            sync();
-            chunk = 0;
-        } else {
-            ++chunk;
         }
-        x0 = x1;
-        seg0 = seg1;
-        x1 = x2;
+        now = next;
+        sync();
     }
 }
 
@@ -958,23 +1030,17 @@ void launch_fill(FillArgs &f, const int64_t *h, hipStream_t s) {
     const int columns = f.windows * f.window;
     auto launch = [&](auto kernel, int acc_bytes, int win, int threads) {
         const int step = std::min(columns, win);
-        const size_t lds = (size_t)step * acc_bytes + step / 8 + (size_t)(threads / 64) * kFillList * 2;
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const size_t lds = (size_t)(step + 64) * acc_bytes;
+        if (lds > 48 * 1024)
+            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL(kernel, dim3((unsigned)f.n_tasks), dim3(threads), lds, s, f);
     };
-    if (finite && ra && rb && bits <= 31) {
-        f.a_scale = std::ldexp(1.0f, -(ga + gb));
-        f.c_scale = std::ldexp(1.0f, ga + gb);
-        launch(k_heavy_fill<int32_t, 16384, 512>, 4, 16384, 512);
-    } else if (finite && ra && rb && bits <= 63 && ea - ga <= 31 && eb - gb <= 31) {
-        f.a_scale = std::ldexp(1.0f, -ga);
-        f.b_scale = std::ldexp(1.0f, -gb);
-        f.c_scale = std::ldexp(1.0f, ga + gb);
-        launch(k_heavy_fill<long long, 8192, 512>, 8, 8192, 512);
-    } else {
-        f.a_scale = 1.0f;
-        launch(k_heavy_fill<double, 4096, 64>, 8, 4096, 64);
-    }
+    const int product_bits = ea - ga + eb - gb;
+    f.p_scale = finite ? std::ldexp(1.0f, -(ga + gb)) : 1.0f;
+    f.c_scale = finite ? std::ldexp(1.0f, ga + gb) : 1.0f;
+    if (finite && ra && rb && bits <= 31) launch(k_heavy_fill<int32_t, 8192, 256>, 4, 8192, 256);
+    else if (finite && ra && rb && bits <= 63 && product_bits <= 51) launch(k_heavy_fill<long long, 8192, 256>, 8, 8192, 256);
+    else launch(k_heavy_fill<double, 4096, 64>, 8, 4096, 64);
 }
 
 }  // namespace
@@ -999,7 +1065,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     const int merge_lanes = A->nnz <= 8 * A->rows ? 8 : 16;
     const int shift = B->cols <= 2048 ? 11 : 12;
     const int windows = (int)((B->cols + (1 << shift) - 1) >> shift);
-    const bool table_fits = windows == 1 || (B->rows * (windows + 1) * 4 <= (int64_t)4 << 30);
+    // heavy rows: the table of windows within 4 GiB, the arrays of B within the 32-bit byte offsets of stream_pieces
+    const bool table_fits = (windows == 1 || B->rows * (windows + 1) * 4 <= (int64_t)4 << 30) && B->nnz < (1 << 28);
 
     Workspace ws{ctx, s, {}};
     RowMatrix ma, mb;
@@ -1093,8 +1160,16 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     int32_t *row_nnz = ws.get<int32_t>((size_t)A->rows + 1);
     uint32_t *group_len = ws.get<uint32_t>((size_t)a_ntr + 4);
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
-    uint32_t *pack = nullptr, *offset = nullptr;
-    int32_t *table = nullptr, *heavy_col = nullptr;
+    uint32_t *pack = nullptr, *offset = nullptr, *bits = nullptr;
+    int64_t bit_rows = 0;
+    CountArgs c{};
+    auto count_heavy = [&](int64_t rows) {
+        const size_t lds = ((size_t)c.span_windows << (shift - 3)) + 256;
+        auto kernel = shift == 11 ? k_heavy_count<2048> : k_heavy_count<4096>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(kHeavyThreads), lds, s, c);
+    };
+    int32_t *table = nullptr, *words = nullptr;
+    uint2 *word = nullptr;
     auto size_rows = [&]() {
         if (n_tasks > task_cap || n_heavy > heavy_cap) {
             // the lists did not fit: make them again, as large as they have to be
@@ -1108,10 +1183,16 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         if (n_heavy > 0) {
             if (!pack) {
                 pack = ws.get<uint32_t>((size_t)B->nnz + 64);     // (a piece is read whole)
-                heavy_col = ws.get<int32_t>((size_t)B->nnz + 64);
+                word = ws.get<uint2>((size_t)B->nnz + 64);
+                words = ws.get<int32_t>((size_t)B->rows);
                 if (windows > 1) table = ws.get<int32_t>((size_t)B->rows * (windows + 1));
             }
             offset = ws.get<uint32_t>((size_t)n_heavy * windows);
+            // the pattern of the heavy rows, kept for the multiplication: a bit per column, also of the empty windows.
+            // Where that is too much, the multiplication has it found again, some rows at a time.
+            const int64_t row_bytes = ((int64_t)windows << shift) / 8;
+            bit_rows = std::min<int64_t>(n_heavy, std::max<int64_t>(kKeptPattern / row_bytes, 1));
+            bits = ws.get<uint32_t>((size_t)(bit_rows * row_bytes / 4));
             if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
         }
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
@@ -1128,30 +1209,26 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         hipLaunchKernelGGL(merge,
                            dim3((unsigned)((A->rows * merge_lanes + 255) / 256)), dim3(256), 0, s, m);
         if (n_heavy > 0) {
-            PackArgs p{B->rows, mb.start, mb.rec, pack, heavy_col, table, windows, shift};
+            PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, windows, shift};
             if (B->nnz > 16 * B->rows)
                 hipLaunchKernelGGL(k_heavy_pack<64>, dim3((unsigned)((B->rows * 64 + 255) / 256)), dim3(256), 0, s, p);
             else
                 hipLaunchKernelGGL(k_heavy_pack<16>, dim3((unsigned)((B->rows * 16 + 255) / 256)), dim3(256), 0, s, p);
-            CountArgs c{};
             c.heavy = heavy;
             c.heavy_cap = n_heavy;
             c.d_scalars = ctx->d_scalars;
             c.a_start = ma.start;
             c.b_start = mb.start;
-            c.ub = ub;
             c.a_rec = ma.rec;
-            c.b_col = heavy_col;
-            c.table = table;
-            c.b_nnz = (int32_t)B->nnz;
+            c.b_word = word;
+            c.b_words = words;
             c.windows = windows;
             c.span_windows = std::min(windows, kSpanWindows);
             c.row_nnz = row_nnz;
             c.group_len = group_len;
             c.offset = offset;
-            const size_t lds = (size_t)c.span_windows << (shift - 3);
-            auto kernel = shift == 11 ? k_heavy_count<2048> : k_heavy_count<4096>;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)n_heavy), dim3(kHeavyThreads), lds, s, c);
+            c.bits = bit_rows == n_heavy ? bits : nullptr;
+            count_heavy(n_heavy);
         }
         return (int)TSP_OK;
     };
@@ -1231,13 +1308,26 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             f.b_nnz = (int32_t)B->nnz;
             f.windows = windows;
             f.offset = offset;
+            f.bits = bits;
             f.c_row_ptr = row_ptr;
             f.c_col = col;
             f.c_val = val;
             f.d_scalars_to_clear = clear;
             cleared = clear != nullptr;
             f.window = 1 << shift;
-            launch_fill(f, ctx->h_scalars, s);
+            for (int64_t from = 0; from < n_heavy; from += bit_rows) {
+                f.heavy_from = (int)from;
+                f.heavy_to = (int)std::min(from + bit_rows, n_heavy);
+                if (bit_rows < n_heavy) {
+                    c.d_scalars = nullptr;
+                    c.row_nnz = nullptr;
+                    c.heavy_cap = f.heavy_to;
+                    c.heavy_from = f.heavy_from;
+                    c.bits = bits;
+                    count_heavy(f.heavy_to - f.heavy_from);
+                }
+                launch_fill(f, ctx->h_scalars, s);
+            }
         }
         TSP_HIP_CHECK(ctx, hipGetLastError());
         ctx->scalars_clean = cleared;
