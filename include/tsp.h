@@ -221,7 +221,7 @@ int tsp_csr_free(tsp_handle handle, tsp_csr *C, void *stream);
  * Compaction of zeros (paper Section 4.4; the two compaction steps that end Algorithm 1): *out = C without the entries
  * whose value compares equal to zero (+0.0 and -0.0; NaN stays), order kept, so that a product
  * whose terms cancelled, or that only met stored zeros, leaves no entry behind.  C: device CSR with
- * float values (TSP_F32) and a 32- or 64-bit row_ptr, borrowed, not modified; row ranges are
+ * float values (TSP_F32) and a 32- or 64-bit row_ptr, borrowed, not modified; row starts are
  * clamped to [0, C.nnz], so a malformed row_ptr cannot cause an out-of-bounds access.  *out:
  * row_ptr (TSP_I64), col_idx, val (TSP_F32) from the handle's allocator, owned by the caller
  * (tsp_csr_free); zeroed on failure.  Synchronises the stream once (the new nnz sizes the
@@ -234,8 +234,8 @@ int tsp_compact_zeros(tsp_handle handle, const tsp_csr *C, tsp_csr *out, void *s
  * tsp_compact_zeros for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same result as tsp_compact_zeros, but the call
  * allocates nothing, on the device or through the handle's allocator: the caller brings the output
- * arrays, and the pass's scratch (survivor counts per row and per 16 rows) lives in a fixed device array
- * inside the library (about 2.2 MB per GPU the library runs on, held until the process ends).
+ * arrays, and the pass's scratch (counts and prefix sums of chunks of entries) lives in a fixed device array
+ * inside the library (0.8 MB per GPU the library runs on, held until the process ends).
  * In: C as for tsp_compact_zeros.  In/out: *out with row_ptr -> int64[C.rows + 1], col_idx ->
  * int32[capacity], val -> float[capacity], capacity >= C.nnz, device arrays owned by the caller, not
  * overlapping C's; on success rows, cols, nnz and the two type fields are filled in and the arrays hold

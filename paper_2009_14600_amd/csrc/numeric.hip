@@ -610,10 +610,10 @@ int numeric_enqueue(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s
                            (int32_t)P->c_tile_rows, P->c_tile_row_ptr, P->pair_off,
                            P->pair_ab, A->lhead, A->ldata, B->rhead, B->rdata,
                            P->c_tile_row, P->c_tile_col, P->c_row_mask, P->c_row_off, P->c_row_ptr, col, val,
-                           last_of_call && !ctx->compact ? ctx->d_scalars : nullptr,
+                           last_of_call ? ctx->d_scalars : nullptr,
                            strips ? P->strip_desc : nullptr, strips ? P->strip_block_ptr + P->strip_entries : nullptr,
                            xcd_chunk);
-        if (last_of_call && !ctx->compact && hipPeekAtLastError() == hipSuccess) ctx->scalars_clean = true;
+        if (last_of_call && hipPeekAtLastError() == hipSuccess) ctx->scalars_clean = true;
         e = hipGetLastError();
     }
     phase_end(ctx, TSP_PHASE_NUMERIC, s);

@@ -645,7 +645,7 @@ struct CountArgs {
     uint32_t *group_len;
     uint32_t *offset;                    // [heavy][windows] entries of the row before each window
     int heavy_from;                      // the rows of this launch begin here
-    uint32_t *bits;                      // [heavy - heavy_from][windows][kWin / 32] of the windows that hold something, or null
+    uint32_t *bits;                      // [heavy - heavy_from][windows][kWin / 32]; or null
 };
 
 // A block per heavy row ORs the words of the rows of B behind it into one bit per column in LDS; OR is free of order, so
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a
                 *at = 0;
             }
             n = wave_sum(n);
-            if (a.bits && n > 0)
+            if (a.bits)
 #pragma unroll
                 for (int i = 0; i < kPerLane; ++i)
                     a.bits[((h - a.heavy_from) * a.windows + w0 + w) * kWords + i * 64 + lane] = word[i];
@@ -747,27 +747,27 @@ struct FillArgs {
     const int64_t *c_row_ptr;
     int32_t *c_col;
     float *c_val;
-    int window;                          // columns
+    int window_shift;
     float p_scale, c_scale;              // integers from the products, values from the integer sums
     int64_t *d_scalars_to_clear;
 };
 
-// A block per task: a row of C, kWin columns at a time (some of its windows).  Its waves deal the entries of the row of
-// A among them, 64 apiece, and stream the segments of B behind them into a dense accumulator in LDS.  What is there to
-// be written the sizing pass has left as a bit per column (marking a bit per product here costs as much as all the rest:
-// neighbouring columns hit one word, and LDS takes atomics on one word one by one): every wave lists the entries of its
-// 2048 columns from the bits, a word per lane (or, where more than a quarter is there, walks the columns), and writes
-// them 64 to a store.  The next step's bits and segments and the entries after those are requested ahead.
+// A block per task: a row of C, or some of its windows, a step at a time: as many windows as hold at most kCap entries
+// and kSpanColumns columns.  The pattern of the step, a bit per column, is known from the sizing pass, so its entries
+// have places of their own in LDS: column c's is the number of bits before it, looked up as {32 bits, entries before
+// them}.  The waves deal the entries of the row of A among them, 64 apiece, stream the segments of B behind them and add
+// the products at their places; then the values go out as they lie, and the columns, listed from the bits.  (A dense
+// accumulator per window of 8192 columns needs no look-up but up to 32 steps for a row, most of them nearly empty.)
+// 64 registers, so that 8 waves per SIMD hide the round trips to the elements of B, half of the time: R-MAT scale 18,
+// 4096 entries with 8 waves at 8 / 6 / 4 waves per SIMD 19.5 / 22.4 / 22.3 ms, with 4 waves 22.0, 8192 entries 24.3 ms;
+// the dense accumulator 22.3 ms.
 //
 // The accumulator: LDS adds an fp32 number one lane after the other (193 cycles for a wave's 64 lanes, measured), an
 // integer or an fp64 number all lanes at a time (5, 8 and 8 to 16 cycles for 32-bit and 64-bit integers and fp64).  So
 // the sums are integers where they are exact in them, and fp64 otherwise; fp64 only with a block of one wave, which
 // fixes the order of the additions.  64-bit integers: p * 2^k + 1.5 * 2^52 in fp64 holds the integer p * 2^k in its low
 // bits (|p * 2^k| < 2^51).
-//
-// Steps of 8192 columns with four waves: 33 KB of LDS, 16 waves per CU.  R-MAT scale 18: 16384 columns with 8 waves
-// 30.7 ms, 8192 with 2, 4, 8 waves 37.7, 27.6, 44.6 ms, 4096 with 1, 2, 4 waves 41.8, 29.4, 32.9 ms.
-constexpr int kFillList = 512;           // entries a wave lists at a time
+constexpr int kSpanColumns = 1 << 16;    // the elements of B hold 16 bits of the column
 
 // A value that is the same for the whole wave and that no kernel running now writes, through the scalar cache.
 template <typename X>
@@ -775,18 +775,14 @@ __device__ __forceinline__ X uniform_load(const X *p) {
     return *(const __attribute__((address_space(4))) X *)(uintptr_t)p;
 }
 
-template <typename Acc, int kWin, int kThreads>
-__global__ __launch_bounds__(kThreads) void k_heavy_fill(const FillArgs a) {
-    constexpr int kWaves = kThreads / 64, kParts = kWin / 2048 / kWaves;
-    static_assert(kParts >= 1 && kParts * kWaves * 2048 == kWin, "whole parts of 2048 columns for every wave");
-    extern __shared__ __align__(16) unsigned char fill_lds[];
-    __shared__ union { PieceLds pieces; uint16_t list[kFillList]; } s_wave[kWaves];
-    __shared__ int s_total[kWaves * kParts];
-    const int columns = min(kWin, a.windows * a.window);       // of a step
-    // (behind the accumulators a place per lane for lanes without an element)
-    Acc *acc = reinterpret_cast<Acc *>(fill_lds);
+template <typename Acc, int kCap, int kThreads>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThreads == 64 ? 1 : 8, 8))) void k_heavy_fill(const FillArgs a) {
+    constexpr int kWaves = kThreads / 64, kWords = kSpanColumns / 32;
+    __shared__ __align__(16) Acc acc[kCap + 64];               // (behind the entries a place per lane for lanes without an element)
+    __shared__ __align__(16) int2 places[kWords];              // {bits of 32 columns, entries before them, less one}
+    __shared__ PieceLds s_piece[kWaves];
+    __shared__ int s_total[kWaves];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    uint16_t *list = s_wave[wave].list;
     auto sync = [] {
         if constexpr (kThreads == 64) wave_sync();
         else __syncthreads();
@@ -802,85 +798,76 @@ __global__ __launch_bounds__(kThreads) void k_heavy_fill(const FillArgs a) {
     const uint32_t row_len = (uint32_t)(uniform_load(a.c_row_ptr + row + 1) - row_first);
     if (heavy < a.heavy_from || heavy >= a.heavy_to || deg <= 0 || w >= w_end) return;
     const uint32_t *offset = a.offset + (int64_t)heavy * a.windows;
-    const uint32_t *kept = a.bits + (int64_t)(heavy - a.heavy_from) * a.windows * (a.window / 32);
-    const int steps = kWin / a.window;                         // windows per step
+    const int word_shift = a.window_shift - 5;                 // words per window
+    const uint32_t *kept = a.bits + (((int64_t)(heavy - a.heavy_from) * a.windows) << word_shift);
     const bool one = a.table == nullptr;
     const int dealt = min(kWaves, (deg + 15) / 16);            // waves that take entries of A
-    const int chunks = (deg + 64 * dealt - 1) / (64 * dealt);  // 64 entries for each of them
-    const bool works = wave < dealt;
-
-    for (int i = threadIdx.x; i < columns * (int)sizeof(Acc) / 16; i += kThreads)
-        reinterpret_cast<uint4 *>(acc)[i] = make_uint4(0, 0, 0, 0);
-    auto entry_at = [&](int chunk) { return (chunk * 64 + lane) * dealt + wave; };
-    auto entry = [&](int chunk) {
-        int2 x = make_int2(-1, 0);
-        if (works && entry_at(chunk) < deg) x = a.a_rec[s + entry_at(chunk)];
-        return x;
-    };
-    auto segment = [&](int32_t c, int v) {
-        int2 seg = make_int2(0, 0);
-        if (c >= 0 && v < w_end) {
-            const int32_t *from = one ? a.b_start + c : a.table + ((int64_t)c * (a.windows + 1) + v);
-            seg.x = from[0];
-            seg.y = from[one ? 1 : min(steps, a.windows - v)];
-        }
-        return seg;
-    };
     auto begin_of = [&](int v) { return v < a.windows ? uniform_load(offset + v) : row_len; };
-    // the bits of the wave's parts of the step at window v (empty windows have left none behind)
-    struct Bits {
-        uint32_t word[kParts];
+    // the end of the step that begins at window v: lane i says whether window v + i still fits
+    auto step_end = [&](int v, uint32_t first) {
+        const int last = v + lane + 1;
+        const bool fits = last <= w_end && lane < (kSpanColumns >> a.window_shift) &&
+                          (last < a.windows ? offset[last] : row_len) - first <= (uint32_t)kCap;
+        return v + max(__popcll(__ballot(fits)), 1);
     };
-    auto pattern = [&](int v) {
-        Bits b;
+    uint32_t first = begin_of(w);
+    while (w < w_end) {
+        const int w_next = step_end(w, first);
+        const uint32_t next_first = begin_of(w_next);
+        const int some = (int)min(next_first - first, (uint32_t)kCap);
+        if (some > 0) {
+            // places of the step's entries, four words per thread and round
+            const int words = (w_next - w) << word_shift;
+            int run = 0;
+            for (int base = 0; base < words; base += kThreads * 4) {
+                const int at = base + (int)threadIdx.x * 4;
+                uint4 b = make_uint4(0, 0, 0, 0);
+                if (at < words) b = *reinterpret_cast<const uint4 *>(kept + ((int64_t)w << word_shift) + at);
+                const int n0 = __popc(b.x), n1 = n0 + __popc(b.y), n2 = n1 + __popc(b.z), n3 = n2 + __popc(b.w);
+                const int inc = (int)wave_inclusive_scan((uint32_t)n3);
+                int before = run + inc - n3 - 1;
+                if constexpr (kWaves > 1) {
+                    if (lane == 63) s_total[wave] = inc;
+                    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kParts; ++q) {
-            const int part = (wave * kParts + q) * 2048, at = v + part / a.window;
-            b.word[q] = 0;
-            if (part < columns && at < w_end && begin_of(at) != begin_of(at + 1))
-                b.word[q] = kept[(size_t)at * (a.window / 32) + (part % a.window) / 32 + lane];
-        }
-        return b;
-    };
-    int2 x0 = entry(0), seg0 = segment(x0.x, w), x1 = chunks > 1 ? entry(1) : x0;
-    Bits now = pattern(w);
-    int ahead = chunks > 1 ? 1 : 0;
-    sync();
-    for (; w < w_end; w += steps) {
-        const int w_next = min(w + steps, w_end);
-        const uint32_t first = begin_of(w), some = begin_of(w_next) - first;
-        const Bits next = pattern(w_next);
-        uint32_t inc[kParts];
-        int total[kParts];
-#pragma unroll
-        for (int q = 0; q < kParts; ++q) {
-            inc[q] = wave_inclusive_scan(__popc(now.word[q]));
-            total[q] = __builtin_amdgcn_readlane((int)inc[q], 63);
-            if (kWaves > 1 && lane == 0) s_total[wave * kParts + q] = total[q];
-        }
-        for (int chunk = 0; chunk < chunks && works; ++chunk) {
-            const bool last = chunk == chunks - 1;
-            int2 seg1, x2 = x1;
-            if (chunks == 1 && !one) {                         // the same entries: a segment begins where the last one ended
-                seg1 = make_int2(seg0.y, seg0.y);
-                if (x0.x >= 0 && w_next < w_end)
-                    seg1.y = a.table[(int64_t)x0.x * (a.windows + 1) + min(w_next + steps, a.windows)];
-            } else {
-                seg1 = segment(x1.x, last ? w_next : w);
-                ahead = ahead == chunks - 1 ? 0 : ahead + 1;
-                x2 = entry(ahead);
+                    for (int v = 0; v < kWaves; ++v) {
+                        before += v < wave ? s_total[v] : 0;
+                        run += s_total[v];
+                    }
+                    if (base + kThreads * 4 < words) __syncthreads();
+                } else {
+                    run += __builtin_amdgcn_readlane(inc, 63);
+                }
+                if (at < words) {
+                    int4 *to = reinterpret_cast<int4 *>(places + at);
+                    to[0] = make_int4((int)b.x, before, (int)b.y, before + n0);
+                    to[1] = make_int4((int)b.z, before + n1, (int)b.w, before + n2);
+                }
             }
-            // (in bounds whatever an operand that was not validated holds)
-            const int32_t p = max(seg0.x, 0), q = min(seg0.y, a.b_nnz);
-            const _Float16 av = (_Float16)__uint_as_float((uint32_t)x0.y);
-            if (some)
+            for (int i = threadIdx.x; i < some; i += kThreads) acc[i] = Acc(0);
+            sync();
+            const uint32_t c0 = (uint32_t)w << a.window_shift;
+            for (int base = 0; base < deg && wave < dealt; base += 64 * dealt) {
+                const int k = base + lane * dealt + wave;
+                int p = 0, len = 0;
+                uint32_t own = 0;
+                if (k < deg) {
+                    const int2 x = a.a_rec[s + k];
+                    const int32_t *from = one ? a.b_start + x.x : a.table + ((int64_t)x.x * (a.windows + 1) + w);
+                    // (in bounds whatever an operand that was not validated holds)
+                    p = max(from[0], 0);
+                    len = min(from[one ? 1 : w_next - w], a.b_nnz) - p;
+                    own = __builtin_bit_cast(uint16_t, (_Float16)__uint_as_float((uint32_t)x.y));
+                }
                 stream_pieces<kThreads == 64 ? 64 : 16, uint32_t>(
-                    p, q - p, (uint32_t)__builtin_bit_cast(uint16_t, av), a.pack, &s_wave[wave].pieces,
-                    [&](uint32_t x, bool active, uint32_t own) {
-                        const uint32_t at = active ? x & (uint32_t)(kWin - 1) : (uint32_t)(columns + lane);
+                    p, len, own, a.pack, &s_piece[wave], [&](uint32_t x, bool active, uint32_t a16) {
+                        const uint32_t c = (x - c0) & (uint32_t)(kSpanColumns - 1);
+                        const int2 place = places[c >> 5];
+                        const int rank = __popc((uint32_t)place.x << (31u - (c & 31u))) + place.y;
+                        const int at = active ? min(rank, kCap) : kCap + lane;
                         // the product of two fp16 numbers is exact; + 0 makes a positive zero of a negative one
                         const float product = __builtin_fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)(x >> 16)),
-                                                             (float)__builtin_bit_cast(_Float16, (uint16_t)own), 0.f);
+                                                             (float)__builtin_bit_cast(_Float16, (uint16_t)a16), 0.f);
                         if constexpr (std::is_floating_point<Acc>::value) {
                             if (active) unsafeAtomicAdd(&acc[at], (double)product);
                         } else if constexpr (sizeof(Acc) == 4) {
@@ -891,70 +878,29 @@ __global__ __launch_bounds__(kThreads) void k_heavy_fill(const FillArgs a) {
                                       __builtin_bit_cast(unsigned long long, shifted) - 0x4338000000000000ull);
                         }
                     });
-            x0 = x1;
-            seg0 = seg1;
-            x1 = x2;
-        }
-        if (some) {
+            }
             sync();
-            int before = 0;                                    // entries of the step in the parts before
-            if constexpr (kWaves > 1)
-                for (int v = 0; v < wave * kParts; ++v) before += s_total[v];
-#pragma unroll
-            for (int q = 0; q < kParts; ++q) {
-                const int part = (wave * kParts + q) * 2048;
-                // (never past the step's entries, whatever an operand that was not validated holds)
-                const int n = min(total[q], (int)some - before);
-                int32_t *to_col = a.c_col + row_first + first + before;
-                float *to_val = a.c_val + row_first + first + before;
-                before += total[q];
-                const int32_t c_first = w * a.window;
-                auto emit = [&](int i, int c, Acc v) {
-                    if (i >= n) return;
-                    to_col[(unsigned)i] = c_first + c;
-                    to_val[(unsigned)i] = std::is_floating_point<Acc>::value ? (float)v : (float)v * a.c_scale;
-                };
-                uint32_t word = now.word[q];
-                if (total[q] > kFillList) {
-                    const uint32_t mine = inc[q] - __popc(word);
-                    for (int i = 0; i < 32; ++i) {             // two words, 64 columns
-                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * i);
-                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * i + 1);
-                        const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)mine, 2 * i);
-                        const int c = part + i * 64 + lane;
-                        if ((lane < 32 ? lo >> lane : hi >> (lane - 32)) & 1u) {
-                            const Acc v = acc[c];
-                            acc[c] = Acc(0);
-                            emit((int)(from + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))), c, v);
-                        }
-                    }
-                } else if (total[q] > 0) {
-                    uint16_t *to = list + (inc[q] - __popc(word));
-                    while (word) {
-                        *to++ = (uint16_t)(part + lane * 32 + __ffs((int)word) - 1);
-                        word &= word - 1;
-                    }
-                    wave_sync();
-                    for (int i0 = 0; i0 < total[q]; i0 += 128) {
-                        int c[2];
-                        Acc v[2];
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) c[u] = list[min(i0 + u * 64 + lane, total[q] - 1)];
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) v[u] = acc[c[u]];
-#pragma unroll
-                        for (int u = 0; u < 2; ++u)
-                            if (i0 + u * 64 + lane < total[q]) {
-                                acc[c[u]] = Acc(0);
-                                emit(i0 + u * 64 + lane, c[u], v[u]);
-                            }
-                    }
-                    wave_sync();
+            float *to_val = a.c_val + row_first + first;
+            for (int i = threadIdx.x; i < some; i += kThreads)
+                to_val[(unsigned)i] = std::is_floating_point<Acc>::value ? (float)acc[i] : (float)acc[i] * a.c_scale;
+            sync();
+            int32_t *col = reinterpret_cast<int32_t *>(acc);
+            for (int i = threadIdx.x; i < words; i += kThreads) {
+                const int2 place = places[i];
+                uint32_t word = (uint32_t)place.x;
+                int32_t *to = col + place.y;
+                while (word) {
+                    *++to = (int32_t)c0 + i * 32 + __ffs((int)word) - 1;
+                    word &= word - 1;
                 }
             }
+            sync();
+            int32_t *to_col = a.c_col + row_first + first;
+            for (int i = threadIdx.x; i < some; i += kThreads) to_col[(unsigned)i] = col[i];
+            sync();
         }
-        now = next;
-        sync();
+        w = w_next;
+        first = next_first;
     }
 }
 
@@ -1027,20 +973,15 @@ void launch_fill(FillArgs &f, const int64_t *h, hipStream_t s) {
     const bool finite = (ra >> 16) < 1023 && (rb >> 16) < 1023;
     int bits = ea - ga + eb - gb;
     for (int64_t n = 1; n < h[S_ROW_LONGEST]; n <<= 1) ++bits;
-    const int columns = f.windows * f.window;
-    auto launch = [&](auto kernel, int acc_bytes, int win, int threads) {
-        const int step = std::min(columns, win);
-        const size_t lds = (size_t)(step + 64) * acc_bytes;
-        if (lds > 48 * 1024)
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)f.n_tasks), dim3(threads), lds, s, f);
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)f.n_tasks), dim3(threads), 0, s, f);
     };
     const int product_bits = ea - ga + eb - gb;
     f.p_scale = finite ? std::ldexp(1.0f, -(ga + gb)) : 1.0f;
     f.c_scale = finite ? std::ldexp(1.0f, ga + gb) : 1.0f;
-    if (finite && ra && rb && bits <= 31) launch(k_heavy_fill<int32_t, 8192, 256>, 4, 8192, 256);
-    else if (finite && ra && rb && bits <= 63 && product_bits <= 51) launch(k_heavy_fill<long long, 8192, 256>, 8, 8192, 256);
-    else launch(k_heavy_fill<double, 4096, 64>, 8, 4096, 64);
+    if (finite && ra && rb && bits <= 31) launch(k_heavy_fill<int32_t, 4096, 512>, 512);
+    else if (finite && ra && rb && bits <= 63 && product_bits <= 51) launch(k_heavy_fill<long long, 4096, 512>, 512);
+    else launch(k_heavy_fill<double, 4096, 64>, 64);
 }
 
 }  // namespace
@@ -1273,7 +1214,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     {
         KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
         // (nothing reads the scalar block any more: the last kernel clears it for the next call)
-        int64_t *clear = ctx->compact ? nullptr : ctx->d_scalars;
+        int64_t *clear = ctx->d_scalars;
         bool cleared = false;
         if (any_merged && nnz > 0) {
             MergeArgs m{};
@@ -1314,7 +1255,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             f.c_val = val;
             f.d_scalars_to_clear = clear;
             cleared = clear != nullptr;
-            f.window = 1 << shift;
+            f.window_shift = shift;
             for (int64_t from = 0; from < n_heavy; from += bit_rows) {
                 f.heavy_from = (int)from;
                 f.heavy_to = (int)std::min(from + bit_rows, n_heavy);
