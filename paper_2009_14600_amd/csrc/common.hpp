@@ -33,8 +33,7 @@ enum Scalar {
     S_MAX_ROW_ENTRIES = 13,  // max over C tile-rows of the number of structural entries
     S_PRODUCTS = 14,         // intermediate products (TSP_OPT_COUNT_PRODUCTS)
     // the row kernels (rowwise.hip):
-    S_ROW_LISTS = 15,        // heavy rows and their tasks listed so far (one packed counter), zero between launches
-    S_ROW_DONE = 16,         // blocks of k_row_plan that have finished, zero between launches
+    S_ROW_LISTS = 15,        // heavy rows and their tasks listed so far (one packed counter)
     S_ROW_PRODUCTS = 17,     // intermediate products
     S_ROW_MERGED = 18,       // rows of C that are merged
     S_ROW_HEAVY = 19,        // rows of C that are not
@@ -61,7 +60,7 @@ struct LiveBlock {           // a block handed out: with canaries the caller's p
 // from it; the numbers of the product at hand are checked against it.
 struct RowHint {
     int64_t sizes[6] = {-1, -1, -1, -1, -1, -1};   // rows and nnz of A, rows, nnz and cols of B, A is B
-    bool tiles = false, merged = false;
+    bool tiles = false;
     int64_t heavy = 0, tasks = 0;
 };
 

@@ -4,8 +4,8 @@
 // intermediate product a_ik * b_kj:
 //
 //   k_row_prepare   one pass over an operand: validation, entries as {column, value} records, tiles per tile-row,
-//                   and for A the number of intermediate products of every row
-//   k_row_plan      candidate tile pairs (the measure by which tsp_spgemm chooses this path), the lists of work
+//                   and for A the number of intermediate products of every row and the lists of work
+//   k_row_finish    row_ptr of C; candidate tile pairs (the measure by which tsp_spgemm chooses this path) and other sums
 //   k_row_merge     rows with few, short rows of B behind them: a lane per row of B, merged in column order
 //   k_heavy_count   the other rows: a block per row, one bit per column of C in LDS
 //   k_heavy_fill    a block per row and some windows of columns, a dense accumulator in LDS
@@ -23,7 +23,9 @@
 namespace tsp {
 
 constexpr int kMergeProducts = 256;      // a merged row has at most this many intermediate products
-constexpr int kPlanBlocks = 128;         // blocks of k_row_plan
+constexpr int kPlanBlocks = 256;         // blocks that add up tile-rows, at most
+constexpr int64_t kFinishRows = 1 << 21; // rows of which k_row_finish makes row_ptr (every block reads all groups before it)
+constexpr int kChunkTileRows = 128, kChunkRows = kChunkTileRows * T;   // rows whose row_ptr one block writes
 constexpr int kPlanSums = 8;
 constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
 constexpr int kSpanWindows = 64;         // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
@@ -52,10 +54,18 @@ struct PrepareArgs {
     int bitmap_words;
     int validate;
     RowMatrix out;
-    int32_t *ub;                         // products per row (of A), or null
+    // of A only (ub null for B):
+    int32_t *ub;                         // products per row
+    unsigned long long *products;        // ... per tile-row
     const void *b_row_ptr;               // of B, as the caller gave it
     int b_is_i64;
-    int64_t b_rows, b_nnz;
+    int64_t b_rows;
+    int merge_lanes;                     // most entries of a row of A that is merged
+    int windows;                         // of columns of C, for the heavy rows
+    int32_t *heavy;                      // rows that are not merged
+    int4 *tasks;                         // {row, index into heavy, first window, one past the last window}
+    int64_t heavy_cap, task_cap;
+    int32_t *rows_of;                    // of every tile-row: 32 * entries of its longest heavy row + its merged rows
     int64_t *d_scalars;
 };
 
@@ -77,10 +87,15 @@ __device__ __forceinline__ uint32_t range_max(uint32_t x, uint32_t y) {
     return max(x & 0xFFFF0000u, y & 0xFFFF0000u) | max(x & 0xFFFFu, y & 0xFFFFu);
 }
 
-// A team of kTeam threads per tile-row (a wave, or a block of 256 for long tile-rows), its entries flat over the
-// lanes.  The team's bitmap over the tile columns tells the first entry that falls into a tile (the atomic returns the
-// word before): those lanes list the tile.  Bound by the loads of B's row pointers and by instructions.
-template <int kTeam, typename RP, typename VT>
+__device__ __forceinline__ bool merged_row(int32_t entries, int32_t products, int merge_lanes) {
+    return entries <= merge_lanes && products <= kMergeProducts;
+}
+
+// A team of kTeam threads per tile-row (a wave, or a block for long tile-rows), its entries flat over the lanes, kU of
+// them per lane in flight.  The team's bitmap over the tile columns tells the first entry that falls into a tile (the
+// atomic returns the word before): those lanes list the tile.  At the end a lane per row of A says whether the row is
+// merged or heavy and lists the heavy one with its tasks.
+template <int kTeam, int kU, typename RP, typename VT>
 __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a) {
     constexpr int kTeams = 256 / kTeam;
     extern __shared__ uint32_t lds_bitmap[];
@@ -117,62 +132,74 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
         const int32_t e0 = s_ptr[team][0], e1 = s_ptr[team][T];
         int32_t listed = 0;
         uint32_t range = 0;
-        for (int32_t base = e0 + (tid & ~63); base < e1; base += kTeam) {
-            const int32_t k = base + lane;
-            const bool on = k < e1;
-            int r = T;
-            int32_t c = 0, len = 0, prev = -1;
-            if (on) {
-                r = 0;
+        for (int32_t base = e0 + (tid & ~63); base < e1; base += kTeam * kU) {
+            int32_t c[kU], prev[kU], len[kU];
+            VT v[kU];
 #pragma unroll
-                for (int step = T / 2; step >= 1; step >>= 1)
-                    if (s_ptr[team][r + step] <= k) r += step;
-                c = a.col[k];
-                const float v = rounded_value(a.val[k]);
-                if (k > s_ptr[team][r]) {
-                    prev = a.col[k - 1];
-                    bad = bad || prev >= c;
-                }
-                if ((uint32_t)c >= (uint64_t)a.cols) {
-                    bad = true;
-                    c = 0;
-                }
-                a.out.rec[k] = make_int2(c, (int)__float_as_uint(v));
-                range = range_max(range, value_range(v));
-                if (a.ub && c < a.b_rows) {
+            for (int u = 0; u < kU; ++u) {
+                const int32_t k = min(base + u * kTeam + lane, e1 - 1);
+                c[u] = a.col[k];
+                prev[u] = a.col[max(k - 1, 0)];
+                v[u] = a.val[k];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                bad = bad || (uint32_t)c[u] >= (uint64_t)a.cols;
+                if ((uint32_t)c[u] >= (uint64_t)a.cols) c[u] = 0;
+                len[u] = 0;
+                if (a.ub && c[u] < a.b_rows) {
                     int64_t s, e;
                     if (a.b_is_i64) {
-                        s = static_cast<const int64_t *>(a.b_row_ptr)[c];
-                        e = static_cast<const int64_t *>(a.b_row_ptr)[c + 1];
+                        s = static_cast<const int64_t *>(a.b_row_ptr)[c[u]];
+                        e = static_cast<const int64_t *>(a.b_row_ptr)[c[u] + 1];
                     } else {
-                        s = static_cast<const int32_t *>(a.b_row_ptr)[c];
-                        e = static_cast<const int32_t *>(a.b_row_ptr)[c + 1];
+                        s = static_cast<const int32_t *>(a.b_row_ptr)[c[u]];
+                        e = static_cast<const int32_t *>(a.b_row_ptr)[c[u] + 1];
                     }
-                    len = (int32_t)min(max(e - s, (int64_t)0), (int64_t)((1 << 25) - 1));
+                    len[u] = (int32_t)min(max(e - s, (int64_t)0), (int64_t)((1 << 25) - 1));
                 }
             }
-            const int32_t t = c >> 4;
-            bool first = on && (prev < 0 || (prev >> 4) != t);
-            if (first) {
-                const uint32_t bit = 1u << (t & 31);
-                first = !(atomicOr(&bitmap[t >> 5], bit) & bit);
-            }
-            const unsigned long long firsts = __ballot(first);
-            int32_t at = listed;
-            if constexpr (kTeam == 64) {
-                listed += __popcll(firsts);
-            } else if (firsts) {
-                if (lane == 0) at = atomicAdd(&s_count[team], __popcll(firsts));
-                at = __builtin_amdgcn_readfirstlane(at);
-            }
-            if (first) a.out.tile_col[e0 + at + __popcll(firsts & ((1ull << lane) - 1ull))] = t;
-            if (a.ub) {
-                // products per row: differences of the running sum at the ends of the rows' stretches in this wave
-                const uint32_t inc = wave_inclusive_scan((uint32_t)len);
-                const int r_next = __shfl_down(r, 1, 64), r_prev = __shfl_up(r, 1, 64);
-                if (on && (lane == 63 || r_next != r)) atomicAdd(&s_ub[team][r], (unsigned long long)inc);
-                if (on && lane > 0 && r_prev != r)
-                    atomicAdd(&s_ub[team][r], (unsigned long long)0 - (unsigned long long)(inc - (uint32_t)len));
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int32_t k = base + u * kTeam + lane;
+                if (base + u * kTeam >= e1) break;                   // (the whole wave)
+                const bool on = k < e1;
+                int r = T;
+                bool starts = false;
+                if (on) {
+                    r = 0;
+#pragma unroll
+                    for (int step = T / 2; step >= 1; step >>= 1)
+                        if (s_ptr[team][r + step] <= k) r += step;
+                    starts = k == s_ptr[team][r];
+                    bad = bad || (!starts && prev[u] >= c[u]);
+                    const float x = rounded_value(v[u]);
+                    a.out.rec[k] = make_int2(c[u], (int)__float_as_uint(x));
+                    range = range_max(range, value_range(x));
+                }
+                const int32_t t = c[u] >> 4;
+                bool first = on && (starts || (prev[u] >> 4) != t);
+                if (first) {
+                    const uint32_t bit = 1u << (t & 31);
+                    first = !(atomicOr(&bitmap[t >> 5], bit) & bit);
+                }
+                const unsigned long long firsts = __ballot(first);
+                int32_t at = listed;
+                if constexpr (kTeam == 64) {
+                    listed += __popcll(firsts);
+                } else if (firsts) {
+                    if (lane == 0) at = atomicAdd(&s_count[team], __popcll(firsts));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                }
+                if (first) a.out.tile_col[e0 + at + __popcll(firsts & ((1ull << lane) - 1ull))] = t;
+                if (a.ub) {
+                    // products per row: differences of the running sum at the ends of the rows' stretches in this wave
+                    const uint32_t mine = on ? (uint32_t)len[u] : 0u, inc = wave_inclusive_scan(mine);
+                    const int r_next = __shfl_down(r, 1, 64), r_prev = __shfl_up(r, 1, 64);
+                    if (on && (lane == 63 || r_next != r)) atomicAdd(&s_ub[team][r], (unsigned long long)inc);
+                    if (on && lane > 0 && r_prev != r)
+                        atomicAdd(&s_ub[team][r], (unsigned long long)0 - (unsigned long long)(inc - mine));
+                }
             }
         }
         const int e = wave_max((int)(range >> 16)), g = wave_max((int)(range & 0xFFFFu));
@@ -184,97 +211,108 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     }
     if constexpr (kTeam == 64) wave_sync();
     else __syncthreads();
-    if (live) {
-        if (tid == 0) {
-            a.out.ntiles[I] = s_count[team];
-            a.out.range[I] = s_range[0][team] << 16 | s_range[1][team];
-        }
-        if (a.ub && tid < T && I * T + tid < a.rows)
-            a.ub[I * T + tid] = (int32_t)min(s_ub[team][tid], (unsigned long long)INT32_MAX);
-        if (bad && a.validate) a.d_scalars[S_INVALID] = 1;
+    if (!live) return;
+    if (bad && a.validate) a.d_scalars[S_INVALID] = 1;
+    if (tid == 0) {
+        a.out.ntiles[I] = s_count[team];
+        a.out.range[I] = s_range[0][team] << 16 | s_range[1][team];
     }
+    if (!a.ub || tid >= 64) return;
+    // a lane per row
+    const int64_t row = I * T + tid;
+    int tasks = 0, deg = 0;
+    unsigned long long ub = 0;
+    const int groups = (a.windows + kGroupWindows - 1) / kGroupWindows;
+    if (tid < T && row < a.rows) {
+        ub = min(s_ub[team][tid], (unsigned long long)INT32_MAX);
+        deg = s_ptr[team][tid + 1] - s_ptr[team][tid];
+        a.ub[row] = (int32_t)ub;
+        if (deg > 0 && ub > 0 && !merged_row(deg, (int32_t)ub, a.merge_lanes)) tasks = min(max((int)ub / kTaskProducts, 1), groups);
+    }
+    unsigned long long all = tid < T ? s_ub[team][tid] : 0ull;
+    for (int d = 1; d < T; d <<= 1) all += __shfl_xor(all, d, T);
+    if (tid == 0) a.products[I] = all;
+    const unsigned long long heavies = __ballot(tasks > 0);
+    if (heavies) {                       // places in both lists from one atomic
+        const uint32_t inc = wave_inclusive_scan((uint32_t)tasks);
+        unsigned long long at = 0;
+        if (lane == 63)
+            at = atomicAdd(reinterpret_cast<unsigned long long *>(a.d_scalars + S_ROW_LISTS),
+                           ((unsigned long long)__popcll(heavies) << 36) | inc);
+        at = __shfl(at, 63, 64);
+        const int64_t h = (int64_t)(at >> 36) + __popcll(heavies & ((1ull << lane) - 1ull));
+        const int64_t t0 = (int64_t)(at & ((1ull << 36) - 1ull)) + inc - tasks;
+        if (tasks > 0 && h < a.heavy_cap) {
+            a.heavy[h] = (int32_t)row;
+            // (groups of windows, as even as they go)
+            for (int t = 0; t < tasks; ++t)
+                if (t0 + t < a.task_cap)
+                    a.tasks[t0 + t] = make_int4((int)row, (int)h, (int)((int64_t)groups * t / tasks) * kGroupWindows,
+                                                min((int)((int64_t)groups * (t + 1) / tasks) * kGroupWindows, a.windows));
+        }
+    }
+    const int longest = heavies ? wave_max(tasks > 0 ? deg : 0) : 0, merged = __popcll(__ballot(deg > 0 && ub > 0 && tasks == 0));
+    if (lane == 0) a.rows_of[I] = min(longest, (1 << 26) - 1) * 32 + merged;
 }
 
-struct PlanArgs {
-    int64_t a_rows, a_tile_rows, b_tile_rows;
-    const int32_t *a_start, *ub, *a_ntiles, *a_tile_col, *b_ntiles;
+// What the operands are like, summed over their tile-rows.  The blocks leave their sums in `partial`; k_row_finish, which
+// runs after them, adds those up.  (Letting the block that finishes last do it takes a device-wide fence in every block,
+// which writes back its L2: 90 us instead of 8 on a 512^2 mesh.)
+struct SumArgs {
+    int64_t a_tile_rows, b_tile_rows;
+    const int32_t *a_start, *a_ntiles, *a_tile_col, *b_ntiles, *rows_of;
     const uint32_t *a_range, *b_range;
+    const unsigned long long *products;
     int same;                            // A and B are one matrix
-    int merge_lanes;                     // most entries of a row of A that is merged
-    int windows;                         // of columns of C, for the heavy rows
-    int32_t *heavy;                      // rows that are not merged
-    int4 *tasks;                         // {row, index into heavy, first window, one past the last window}
-    int64_t heavy_cap, task_cap;
-    int64_t *d_scalars, *h_scalars_dev;
-    int64_t publish_tag;                 // 0: the sizes stay on the device
-    unsigned long long *partial;         // [kPlanBlocks][kPlanSums]
+    unsigned long long *partial;         // [kPlanSums][kPlanBlocks]
 };
+enum { kSumCandidates, kSumTilesA, kSumTilesB, kSumProducts, kSumMerged, kSumRanges, kSumLongest };
 
-__device__ __forceinline__ bool merged_row(int32_t entries, int32_t products, int merge_lanes) {
-    return entries <= merge_lanes && products <= kMergeProducts;
-}
-
-// Sixteen lanes per tile-row: its candidate pairs (sum of the tiles of B's tile-rows behind its tiles), then a lane per
-// row: merged or heavy, and how many tasks a heavy row makes.
-__global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
-    __shared__ unsigned long long s_sum[kPlanSums];
-    __shared__ unsigned long long s_max[kPlanSums];
-    __shared__ int s_last;
+// Sixteen lanes per tile-row: tiles, candidate pairs (the tiles of B's tile-rows behind the tiles of A: the measure by
+// which tsp_spgemm chooses this path), products, value ranges.
+__device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int blocks) {
+    __shared__ unsigned long long s_sum[kPlanSums], s_max[kPlanSums];
+    const int lane = lane_id(), r = threadIdx.x & 15;
     if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = s_max[threadIdx.x] = 0;
     __syncthreads();
-    const int lane = lane_id(), r = threadIdx.x & 15;
     unsigned long long cand = 0, tiles_a = 0, tiles_b = 0, products = 0, merged = 0;
     uint32_t range_a = 0, range_b = 0;
-    int longest = 0;                     // heavy row of A
-    const int groups = (a.windows + kGroupWindows - 1) / kGroupWindows;
-    unsigned long long *counters = reinterpret_cast<unsigned long long *>(a.d_scalars + S_ROW_LISTS);
-    const int64_t step = (int64_t)gridDim.x * 16;
-    const int64_t most = a.a_tile_rows > a.b_tile_rows ? a.a_tile_rows : a.b_tile_rows;
-    for (int64_t base = (int64_t)blockIdx.x * 16; base < most; base += step) {
+    int longest = 0;
+    const int64_t most = max(a.a_tile_rows, a.same ? (int64_t)0 : a.b_tile_rows);
+    for (int64_t base = (int64_t)block * 16; base < most; base += (int64_t)blocks * 16) {
         const int64_t I = base + (threadIdx.x >> 4);
         if (r == 0 && I < a.b_tile_rows && !a.same) {
             tiles_b += (unsigned)a.b_ntiles[I];
             range_b = range_max(range_b, a.b_range[I]);
         }
-        int tasks = 0;
-        bool heavy = false;
-        const int64_t row = I * T + r;
+        int32_t e0 = 0, n = 0;
         if (I < a.a_tile_rows) {
-            const int32_t e0 = a.a_start[I * T], n = a.a_ntiles[I];
+            e0 = a.a_start[I * T];
+            n = a.a_ntiles[I];
             if (r == 0) {
                 tiles_a += (unsigned)n;
                 range_a = range_max(range_a, a.a_range[I]);
+                products += a.products[I];
+                const int32_t rows_of = a.rows_of[I];
+                longest = max(longest, rows_of >> 5);
+                merged += rows_of & 31;
             }
-            for (int32_t j = r; j < n; j += 16) {
+            for (int32_t j = r; j < min(n, 64); j += 16) {
                 const int32_t K = a.a_tile_col[e0 + j];
                 if (K < a.b_tile_rows) cand += (unsigned)a.b_ntiles[K];
             }
-            if (row < a.a_rows) {
-                const int32_t deg = a.a_start[row + 1] - a.a_start[row], ub = a.ub[row];
-                products += (unsigned)ub;
-                heavy = deg > 0 && !merged_row(deg, ub, a.merge_lanes) && ub > 0;
-                merged += !heavy && ub > 0;
-                if (heavy) {
-                    tasks = min(max(ub / kTaskProducts, 1), groups);
-                    longest = max(longest, deg);
-                }
-            }
         }
-        const unsigned long long heavies = __ballot(heavy);
-        if (heavies) {                   // (uniform in the wave) places in both lists from one atomic
-            const uint32_t inc = wave_inclusive_scan((uint32_t)tasks);
-            unsigned long long at = 0;
-            if (lane == 63) at = atomicAdd(counters, ((unsigned long long)__popcll(heavies) << 36) | inc);
-            at = __shfl(at, 63, 64);
-            const int64_t h = (int64_t)(at >> 36) + __popcll(heavies & ((1ull << lane) - 1ull));
-            const int64_t t0 = (int64_t)(at & ((1ull << 36) - 1ull)) + inc - tasks;
-            if (heavy && h < a.heavy_cap) {
-                a.heavy[h] = (int32_t)row;
-                // (groups of windows, as even as they go)
-                for (int t = 0; t < tasks; ++t)
-                    if (t0 + t < a.task_cap)
-                        a.tasks[t0 + t] = make_int4((int)row, (int)h, (int)((int64_t)groups * t / tasks) * kGroupWindows,
-                                                    min((int)((int64_t)groups * (t + 1) / tasks) * kGroupWindows, a.windows));
+        // long tile-rows: the rest of their tiles by the whole wave
+        for (unsigned long long more = __ballot(r == 0 && n > 64); more; more &= more - 1) {
+            const int from = __ffsll((long long)more) - 1;
+            const int32_t first = __builtin_amdgcn_readlane(e0, from), count = __builtin_amdgcn_readlane(n, from);
+            for (int32_t j = 64 + lane; j < count; j += 256) {
+                int32_t K[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) K[u] = a.a_tile_col[first + min(j + 64 * u, count - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j + 64 * u < count && K[u] < a.b_tile_rows) cand += (unsigned)a.b_ntiles[K[u]];
             }
         }
     }
@@ -282,11 +320,11 @@ __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
         for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
         if (lane == 0 && v) atomicAdd(&s_sum[slot], v);
     };
-    add(0, cand);
-    add(1, tiles_a);
-    add(2, tiles_b);
-    add(3, products);
-    add(4, merged);
+    add(kSumCandidates, cand);
+    add(kSumTilesA, tiles_a);
+    add(kSumTilesB, tiles_b);
+    add(kSumProducts, products);
+    add(kSumMerged, merged);
     auto most_of = [&](int slot, int v) {
         v = wave_max(v);
         if (lane == 0 && v) atomicMax(&s_max[slot], (unsigned long long)v);
@@ -297,82 +335,139 @@ __global__ __launch_bounds__(256) void k_row_plan(const PlanArgs a) {
     most_of(3, (int)(range_b & 0xFFFFu));
     most_of(4, longest);
     __syncthreads();
-    // (sums of counts stay below 2^48, and so does the word that carries the maxima)
     if (threadIdx.x == 0) {
-        s_sum[5] = s_max[0] << 48 | s_max[1] << 32 | s_max[2] << 16 | s_max[3];
-        s_sum[6] = s_max[4];
+        s_sum[kSumRanges] = s_max[0] << 48 | s_max[1] << 32 | s_max[2] << 16 | s_max[3];
+        s_sum[kSumLongest] = s_max[4];
     }
     __syncthreads();
-    if (threadIdx.x < kPlanSums)
-        __hip_atomic_store(&a.partial[blockIdx.x * kPlanSums + threadIdx.x], s_sum[threadIdx.x], __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0)
-        s_last = atomicAdd(reinterpret_cast<unsigned long long *>(a.d_scalars + S_ROW_DONE), 1ull) == gridDim.x - 1;
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-    // the last block to finish adds up the partial sums and hands the sizes to the host
-    if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = 0;
-    __syncthreads();
-    if (threadIdx.x < kPlanSums) s_max[threadIdx.x] = 0;
-    __syncthreads();
-    for (unsigned i = threadIdx.x; i < gridDim.x * kPlanSums; i += 256) {
-        const unsigned long long v = __hip_atomic_load(&a.partial[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned slot = i % kPlanSums;
-        if (!v) continue;
-        if (slot == 5)
-            for (int q = 0; q < 4; ++q) atomicMax(&s_max[q], (v >> (48 - 16 * q)) & 0xFFFFull);
-        else if (slot == 6) atomicMax(&s_max[4], v);
-        else atomicAdd(&s_sum[slot], v);
+    if (threadIdx.x < kPlanSums) a.partial[threadIdx.x * kPlanBlocks + block] = s_sum[threadIdx.x];
+}
+__global__ __launch_bounds__(256) void k_row_sums(const SumArgs a) { sum_tile_rows(a, blockIdx.x, gridDim.x); }
+
+struct FinishArgs {
+    int64_t rows;                        // 0: only the sizes are wanted
+    const int32_t *row_nnz;
+    const uint32_t *group_len;           // sums of row_nnz over 16 rows, padded to a multiple of four
+    int64_t *c_row_ptr;
+    const unsigned long long *partial;   // of k_row_sums
+    int partials, same;
+    int64_t *d_scalars, *h_scalars_dev;
+    int64_t publish_tag;
+};
+
+// row_ptr of C from the row lengths: block b takes rows [2048 b, 2048 b + 2048), adds up the groups of 16 rows before
+// them and scans its own.  The last block also adds up the sums over the tile-rows and hands all sizes to the host.
+__global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
+    __shared__ uint64_t lds[256 / 64];
+    __shared__ unsigned long long s_sum[kPlanSums], s_max[kPlanSums];
+    const bool last = blockIdx.x == gridDim.x - 1;
+    constexpr int kItems = kChunkRows / 256;
+    const int64_t base = (int64_t)blockIdx.x * kChunkRows + (int64_t)threadIdx.x * kItems;
+    int32_t x[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) x[i] = base + i < a.rows ? a.row_nnz[base + i] : 0;
+    if (last) {                          // two sums per wave
+        const int lane = lane_id();
+        for (int slot = (int)(threadIdx.x >> 6) * 2; slot < (int)(threadIdx.x >> 6) * 2 + 2; ++slot) {
+            unsigned long long v[kPlanBlocks / 64], sum = 0;
+#pragma unroll
+            for (int u = 0; u < kPlanBlocks / 64; ++u)
+                v[u] = u * 64 + lane < a.partials ? a.partial[slot * kPlanBlocks + u * 64 + lane] : 0ull;
+            if (slot == kSumRanges || slot == kSumLongest) {
+                int most[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int u = 0; u < kPlanBlocks / 64; ++u) {
+                    if (slot == kSumLongest) most[0] = max(most[0], (int)v[u]);
+                    else
+                        for (int q = 0; q < 4; ++q) most[q] = max(most[q], (int)((v[u] >> (48 - 16 * q)) & 0xFFFFull));
+                }
+                for (int q = 0; q < 4; ++q) most[q] = wave_max(most[q]);
+                if (lane == 0)
+                    for (int q = 0; q < (slot == kSumLongest ? 1 : 4); ++q) s_max[slot == kSumLongest ? 4 : q] = (unsigned long long)most[q];
+            } else {
+#pragma unroll
+                for (int u = 0; u < kPlanBlocks / 64; ++u) sum += v[u];
+                for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+                if (lane == 0) s_sum[slot] = sum;
+            }
+        }
+        __syncthreads();
     }
-    __syncthreads();
+    uint64_t before = 0;
+    const uint4 *groups4 = reinterpret_cast<const uint4 *>(a.group_len);
+    const int64_t quads = a.rows > 0 ? (int64_t)blockIdx.x * kChunkTileRows / 4 : 0;
+    for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 4 * 256) {
+        uint4 g[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) g[u] = q0 + u * 256 < quads ? groups4[q0 + u * 256] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) before += (uint64_t)g[u].x + g[u].y + g[u].z + g[u].w;
+    }
+    uint64_t entries_before;
+    (void)block_exclusive_scan64<256>(before, &entries_before, lds);
+    uint64_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) mine += (uint32_t)x[i];
+    uint64_t total;
+    uint64_t run = entries_before + block_exclusive_scan64<256>(mine, &total, lds);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        if (base + i < a.rows) a.c_row_ptr[base + i] = (int64_t)run;
+        run += (uint32_t)x[i];
+    }
+    if (!last) return;
     if (threadIdx.x == 0) {
-        a.d_scalars[S_CANDIDATES] = (int64_t)s_sum[0];
-        a.d_scalars[S_TILES_A] = (int64_t)s_sum[1];
-        a.d_scalars[S_TILES_B] = (int64_t)(a.same ? s_sum[1] : s_sum[2]);
-        a.d_scalars[S_ROW_PRODUCTS] = (int64_t)s_sum[3];
-        a.d_scalars[S_ROW_MERGED] = (int64_t)s_sum[4];
+        if (a.rows > 0) {
+            a.c_row_ptr[a.rows] = (int64_t)(entries_before + total);
+            a.d_scalars[S_C_NNZ] = (int64_t)(entries_before + total);
+        }
+        a.d_scalars[S_CANDIDATES] = (int64_t)s_sum[kSumCandidates];
+        a.d_scalars[S_TILES_A] = (int64_t)s_sum[kSumTilesA];
+        a.d_scalars[S_TILES_B] = (int64_t)(a.same ? s_sum[kSumTilesA] : s_sum[kSumTilesB]);
+        a.d_scalars[S_ROW_PRODUCTS] = (int64_t)s_sum[kSumProducts];
+        a.d_scalars[S_ROW_MERGED] = (int64_t)s_sum[kSumMerged];
         const int from = a.same ? 0 : 2;
         a.d_scalars[S_ROW_RANGE_A] = (int64_t)(s_max[0] << 16 | s_max[1]);
         a.d_scalars[S_ROW_RANGE_B] = (int64_t)(s_max[from] << 16 | s_max[from + 1]);
         a.d_scalars[S_ROW_LONGEST] = (int64_t)s_max[4];
-        const unsigned long long lists = __hip_atomic_load(counters, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long lists = (unsigned long long)a.d_scalars[S_ROW_LISTS];
         a.d_scalars[S_ROW_HEAVY] = (int64_t)(lists >> 36);
         a.d_scalars[S_ROW_TASKS] = (int64_t)(lists & ((1ull << 36) - 1ull));
-        a.d_scalars[S_ROW_LISTS] = 0;
-        a.d_scalars[S_ROW_DONE] = 0;
     }
-    if (a.publish_tag) publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag);
+    publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag);
 }
 
 // ---- merged rows ------------------------------------------------------------------------------------------------
+#define TSP_LANES(v, ctrl) __builtin_amdgcn_update_dpp(0, (v), (ctrl), 0xf, 0xf, true)
 template <int G>
 __device__ __forceinline__ int lanes_min(int v) {
     if constexpr (G == 8) {
-        v = min(v, TSP_DPP(v, v, 0xB1, 0xf, false));      // quad_perm [1,0,3,2]
-        v = min(v, TSP_DPP(v, v, 0x4E, 0xf, false));      // quad_perm [2,3,0,1]
-        v = min(v, TSP_DPP(v, v, 0x141, 0xf, false));     // row_half_mirror
-        return v;
+        v = min(v, TSP_LANES(v, 0xB1));                  // quad_perm [1,0,3,2]
+        v = min(v, TSP_LANES(v, 0x4E));                  // quad_perm [2,3,0,1]
+        v = min(v, TSP_LANES(v, 0x141));                 // row_half_mirror
     } else {
-        return group16_min(v);
+        v = min(v, TSP_LANES(v, 0x128));                 // row_ror:8, 4, 2, 1
+        v = min(v, TSP_LANES(v, 0x124));
+        v = min(v, TSP_LANES(v, 0x122));
+        v = min(v, TSP_LANES(v, 0x121));
     }
+    return v;
 }
 template <int G>
 __device__ __forceinline__ float lanes_sum(float v) {     // the same tree, and so the same bits, in all lanes of the group
-#define TSP_ADD_DPP(ctrl) v = v + __uint_as_float((uint32_t)TSP_DPP((int)__float_as_uint(v), (int)__float_as_uint(v), ctrl, 0xf, false))
+    auto moved = [](float x, auto ctrl) {
+        return __builtin_bit_cast(float, TSP_LANES(__builtin_bit_cast(int, x), decltype(ctrl)::value));
+    };
     if constexpr (G == 8) {
-        TSP_ADD_DPP(0xB1);
-        TSP_ADD_DPP(0x4E);
-        TSP_ADD_DPP(0x141);
+        v += moved(v, std::integral_constant<int, 0xB1>{});
+        v += moved(v, std::integral_constant<int, 0x4E>{});
+        v += moved(v, std::integral_constant<int, 0x141>{});
     } else {
-        TSP_ADD_DPP(0x128);
-        TSP_ADD_DPP(0x124);
-        TSP_ADD_DPP(0x122);
-        TSP_ADD_DPP(0x121);
+        v += moved(v, std::integral_constant<int, 0x128>{});
+        v += moved(v, std::integral_constant<int, 0x124>{});
+        v += moved(v, std::integral_constant<int, 0x122>{});
+        v += moved(v, std::integral_constant<int, 0x121>{});
     }
-#undef TSP_ADD_DPP
     return v;
 }
 
@@ -380,9 +475,11 @@ struct MergeArgs {
     int64_t rows;
     const int32_t *a_start, *b_start, *ub;
     const int2 *a_rec, *b_rec;
+    const int32_t *b_col;                // the columns of b_rec by themselves, as the caller gave them
     // sizing pass
     int32_t *row_nnz;
     uint32_t *group_len;                 // entries per 16 rows
+    int blocks;                          // that merge; the ones behind them sum (SumArgs)
     // multiplication pass
     const int64_t *c_row_ptr;
     int32_t *c_col;
@@ -391,19 +488,42 @@ struct MergeArgs {
     int64_t *d_scalars_to_clear;
 };
 
-// A group of G lanes per row of A, a lane per entry a_ik: every lane holds the next entry of its row of B, and a step
-// takes the smallest column of the group and adds up the lanes that stand at it.  One entry of C per step, in column
-// order; the next entry of every list is requested one step ahead.  The sizing pass counts the steps, the
-// multiplication pass collects the entries of its wave's rows, which are neighbours in C, in LDS and writes them whole.
+// A group of G lanes per row of A, a lane per entry a_ik, which holds the next entry of its row of B: a step takes the
+// smallest column of the group and adds up the lanes that stand at it, one entry of C per step, in column order.  The
+// rows of B lie in LDS, G entries of each at a time, fetched by the lanes of the group side by side (64 lanes that each
+// fetch their own list cost the load path as many cycles as they are); a list that is longer is fetched on by its lane.
+// The sizing pass counts the steps; the multiplication pass collects the entries of its wave's rows, which are
+// neighbours in C, in LDS and writes them whole.
 template <int G, bool kFill>
-__global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a) {
+__global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a, const SumArgs sums) {
     constexpr int kRows = 64 / G;        // per wave
-    extern __shared__ uint32_t lds_stage[];
+    constexpr int kPitch = 65;           // (one more than the lanes: the lanes of a group write to different banks)
+    constexpr int32_t kMore = -1;        // behind the G entries in LDS of a list that goes on
+    using Item = typename std::conditional<kFill, int2, int32_t>::type;
+    extern __shared__ __align__(8) int2 lds_stage[];
+    __shared__ Item s_list[4][(G + 1) * kPitch];
     __shared__ uint32_t s_len[256 / G];
+    if constexpr (!kFill)
+        if ((int)blockIdx.x >= a.blocks) {
+            sum_tile_rows(sums, (int)blockIdx.x - a.blocks, (int)gridDim.x - a.blocks);
+            return;
+        }
     const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
     const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
     if constexpr (kFill)
         if (a.d_scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) a.d_scalars_to_clear[threadIdx.x] = 0;
+    auto none = [] {
+        if constexpr (kFill) return make_int2(kNoCol, 0);
+        else return kNoCol;
+    };
+    auto column = [](const Item &x) -> int32_t {
+        if constexpr (kFill) return x.x;
+        else return x;
+    };
+    auto item = [&](int32_t k) {
+        if constexpr (kFill) return a.b_rec[k];
+        else return a.b_col[k];
+    };
     int32_t p = 0, e = 0, deg = 0, ub = 0;
     float av = 0.f;
     bool merged = false;
@@ -411,7 +531,7 @@ __global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a) {
         const int32_t s = a.a_start[row];
         deg = a.a_start[row + 1] - s;
         ub = a.ub[row];
-        merged = ub > 0 && merged_row(deg, ub, G);
+        merged = ub > 0 && deg > 0 && merged_row(deg, ub, G);
         if (merged && l < deg) {
             const int2 x = a.a_rec[s + l];
             p = a.b_start[x.x];
@@ -419,27 +539,70 @@ __global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a) {
             av = __uint_as_float((uint32_t)x.y);
         }
     }
-    int2 head = make_int2(kNoCol, 0), next = head;
-    if (p < e) head = a.b_rec[p];
-    if (p + 1 < e) next = a.b_rec[p + 1];
-    p += 2;
+    Item *mine = &s_list[wave][lane];
+    {
+        const int longest = wave_max(merged ? deg : 0);
+        Item x[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            x[i] = none();
+            if (i < longest) {
+                const int32_t pi = __shfl(p, i, G), ei = __shfl(e, i, G);
+                if (pi + l < ei) x[i] = item(pi + l);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) s_list[wave][l * kPitch + (lane - l) + i] = x[i];
+        Item end = none();
+        if (e - p > G) {
+            if constexpr (kFill) end.x = kMore;
+            else end = kMore;
+        }
+        mine[G * kPitch] = end;
+        p += G;
+    }
+    wave_sync();
+    Item head = *mine;
+    const Item *at = mine;
+    auto advance = [&] {
+        at += kPitch;
+        head = *at;
+    };
+    auto refill = [&] {                  // lanes whose list goes on behind the G entries they had
+        if (column(head) < 0) {
+            Item x[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                x[j] = none();
+                if (p + j < e) x[j] = item(p + j);
+            }
+#pragma unroll
+            for (int j = 0; j < G; ++j) mine[j * kPitch] = x[j];
+            p += G;
+            Item end = none();
+            if (e - p > 0) {
+                if constexpr (kFill) end.x = kMore;
+                else end = kMore;
+            }
+            mine[G * kPitch] = end;
+            at = mine;
+            head = *at;
+        }
+    };
     if constexpr (!kFill) {
         int count = 0;
         while (true) {
-            const int m = lanes_min<G>(head.x);
-            const bool more = m != kNoCol;
-            if (!__any(more)) break;
-            count += more ? 1 : 0;
-            if (more && head.x == m) {
-                head.x = next.x;
-                next.x = kNoCol;
-                if (p < e) next.x = a.b_rec[p].x;
-                ++p;
+            const int m = lanes_min<G>(head);
+            if (!__any(m != kNoCol)) break;
+            if (m != kNoCol) {
+                ++count;
+                if (head == m) advance();
             }
+            if (__any(head < 0)) refill();
         }
-        // (rows of other kernels count as empty here)
         if (l == 0) {
-            if (row < a.rows && (merged || ub == 0 || deg == 0)) a.row_nnz[row] = count;
+            // (rows of other kernels count as empty here)
+            if (row < a.rows && (merged || ub == 0 || deg <= 0)) a.row_nnz[row] = count;
             s_len[threadIdx.x / G] = (uint32_t)count;
         }
         __syncthreads();
@@ -452,55 +615,48 @@ __global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a) {
     } else {
         int64_t first = 0;
         int n = 0;
-        if (merged) {
+        if (row < a.rows) {
             first = a.c_row_ptr[row];
-            n = (int)(a.c_row_ptr[row + 1] - first);
+            if (merged) n = (int)(a.c_row_ptr[row + 1] - first);
         }
         // where the row's entries lie among those of the wave
-        int off[kRows + 1];
-        off[0] = 0;
-#pragma unroll
-        for (int i = 0; i < kRows; ++i) off[i + 1] = off[i] + __builtin_amdgcn_readlane(n, i * G);
-        const int total = off[kRows];
+        const uint32_t inc = wave_inclusive_scan(l == 0 ? (uint32_t)n : 0u);
+        const int total = __builtin_amdgcn_readlane((int)inc, 63), off = (int)inc - n;
+        const int steps = wave_max(n);
         const bool staged = total <= a.stage;
-        int at = 0;
-#pragma unroll
-        for (int i = 0; i < kRows; ++i)
-            if (lane / G == i) at = off[i];
-        uint32_t *st_col = lds_stage + wave * 2 * a.stage, *st_val = st_col + a.stage;
-        int done = 0;
-        while (true) {
+        int2 *stage = lds_stage + wave * a.stage, *to = stage + off;
+        for (int t = 0; t < steps; ++t) {
             const int m = lanes_min<G>(head.x);
-            const bool more = m != kNoCol;
-            if (!__any(more)) break;
-            const bool mine = more && head.x == m;
-            const float sum = lanes_sum<G>(mine ? av * __uint_as_float((uint32_t)head.y) : 0.f);
-            if (l == 0 && more && done < n) {
+            const bool here = head.x == m && m != kNoCol;
+            const float sum = lanes_sum<G>(here ? av * __uint_as_float((uint32_t)head.y) : 0.f);
+            if (l == 0 && t < n) {
                 if (staged) {
-                    st_col[at + done] = (uint32_t)m;
-                    st_val[at + done] = __float_as_uint(sum);
+                    to[t] = make_int2(m, (int)__float_as_uint(sum));
                 } else {
-                    a.c_col[first + done] = m;
-                    a.c_val[first + done] = sum;
+                    a.c_col[first + t] = m;
+                    a.c_val[first + t] = sum;
                 }
             }
-            ++done;
-            if (mine) {
-                head = next;
-                next.x = kNoCol;
-                if (p < e) next = a.b_rec[p];
-                ++p;
-            }
+            if (here) advance();
+            if (__any(head.x < 0)) refill();
         }
-        if (!staged) return;
+        if (!staged || total == 0) return;
         wave_sync();
-#pragma unroll
-        for (int i = 0; i < kRows; ++i) {
-            // rows that follow one another in C without a gap are written in one go
-            const int64_t to = __shfl(first, i * G, 64);
-            for (int j = off[i] + lane; j < off[i + 1]; j += 64) {
-                a.c_col[to + (j - off[i])] = (int32_t)st_col[j];
-                a.c_val[to + (j - off[i])] = __uint_as_float(st_val[j]);
+        // the wave's rows follow one another in C unless a row of another kernel lies between them
+        const int64_t wave_first = __shfl(first, 0, 64);
+        if (!__any(n > 0 && first - wave_first != off)) {
+            int32_t *col = a.c_col + wave_first;
+            float *val = a.c_val + wave_first;
+            for (int j = lane; j < total; j += 64) {
+                const int2 x = stage[j];
+                col[(unsigned)j] = x.x;
+                val[(unsigned)j] = __uint_as_float((uint32_t)x.y);
+            }
+        } else {
+            for (int j = l; j < n; j += G) {
+                const int2 x = stage[off + j];
+                a.c_col[first + j] = x.x;
+                a.c_val[first + j] = __uint_as_float((uint32_t)x.y);
             }
         }
     }
@@ -534,7 +690,11 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
     int32_t at = s;
     for (int32_t k0 = s; __any(k0 < e); k0 += L) {
         const int32_t k = k0 + l;
-        bool leads = false;                                  // the first entry of a word
+        // A word's bits are the difference of the running sum of the bits (all distinct, so that carries cancel) at the two
+        // ends of its stretch; a word that goes on in the next trip is listed twice.
+        bool leads = false;
+        uint32_t bit = 0;
+        int32_t word = 0;
         if (k < e) {
             const int2 x = a.rec[k];
             const int32_t before = k > s ? a.rec[k - 1].x : -1;
@@ -542,20 +702,17 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
             a.pack[k] = ((uint32_t)x.x & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
             if (tab)
                 for (int w = (before >> a.shift) + 1; w <= (x.x >> a.shift) && w <= a.windows; ++w) tab[w] = k;
-            leads = before < 0 || (before >> 5) != (x.x >> 5);
+            word = x.x >> 5;
+            bit = 1u << (x.x & 31);
+            leads = l == 0 || before < 0 || (before >> 5) != word;
         }
-        const unsigned long long all = __ballot(leads);
+        const unsigned long long all = __ballot(leads), live = __ballot(k < e);
+        const uint32_t sum = wave_inclusive_scan(bit);
+        const int start = 63 - __clzll((long long)(all & ((2ull << lane) - 1ull)));
+        const uint32_t before_start = (uint32_t)__shfl((int)(sum - bit), max(start, 0), 64);
         const unsigned long long mine = L == 64 ? all : (all >> (lane & ~(L - 1))) & ((1ull << (L & 63)) - 1ull);
-        if (leads) {
-            const int32_t word = a.rec[k].x >> 5;
-            uint32_t m = 0;
-            for (int32_t j = k; j < e; ++j) {
-                const int32_t c = a.rec[j].x;
-                if ((c >> 5) != word) break;
-                m |= 1u << (c & 31);
-            }
-            a.word[at + __popcll(mine & ((1ull << l) - 1ull))] = make_uint2((uint32_t)word, m);
-        }
+        if (k < e && (l == L - 1 || !((live >> (lane + 1)) & 1ull) || ((all >> (lane + 1)) & 1ull)))
+            a.word[at + __popcll(mine & ((2ull << l) - 1ull)) - 1] = make_uint2((uint32_t)word, sum - before_start);
         at += __popcll(mine);
     }
     if (row < a.rows && l == 0) a.words[row] = at - s;
@@ -659,7 +816,8 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a
     __shared__ uint32_t s_run;
     constexpr int kWords = kWin / 32, kPerLane = kWords / 64;
     const int64_t h = a.heavy_from + (int64_t)blockIdx.x;
-    if (h >= a.heavy_cap || (a.d_scalars && h >= a.d_scalars[S_ROW_HEAVY])) return;
+    // (the lists of a product whose numbers the host does not have yet may be shorter than the launch)
+    if (h >= a.heavy_cap || (a.d_scalars && h >= a.d_scalars[S_ROW_LISTS] >> 36)) return;
     const int32_t row = a.heavy[h];
     const int32_t s = a.a_start[row], e = a.a_start[row + 1];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -929,16 +1087,28 @@ template <typename RP, typename VT>
 void launch_prepare(const PrepareArgs<RP, VT> &a, hipStream_t s) {
     const int64_t tile_rows = (a.rows + T - 1) / T;
     if (tile_rows == 0) return;
-    // a wave per tile-row while a tile-row is a few dozen trips at most; longer ones get a block
-    if (a.nnz <= 2048 * tile_rows && (size_t)a.bitmap_words * 16 <= 60 * 1024)
-        hipLaunchKernelGGL((k_row_prepare<64, RP, VT>), dim3((unsigned)((tile_rows + 3) / 4)), dim3(256),
+    // A wave per tile-row of up to two trips; longer ones get a block, four entries per thread in flight (the hub rows of
+    // a graph: one wave took 1.9 ms for the longest tile-row of an R-MAT graph of scale 18)
+    if (a.nnz <= 128 * tile_rows && (size_t)a.bitmap_words * 16 <= 60 * 1024)
+        hipLaunchKernelGGL((k_row_prepare<64, 2, RP, VT>), dim3((unsigned)((tile_rows + 3) / 4)), dim3(256),
                            (size_t)a.bitmap_words * 16, s, a);
     else
-        hipLaunchKernelGGL((k_row_prepare<256, RP, VT>), dim3((unsigned)tile_rows), dim3(256),
+        hipLaunchKernelGGL((k_row_prepare<256, 4, RP, VT>), dim3((unsigned)tile_rows), dim3(256),
                            (size_t)a.bitmap_words * 4, s, a);
 }
 
-void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, int32_t *ub, const tsp_csr *B, hipStream_t s) {
+// What k_row_prepare needs beyond the operand, for A (null members for B)
+struct LeftOperand {
+    int32_t *ub, *rows_of;
+    unsigned long long *products;
+    const tsp_csr *B;
+    int merge_lanes, windows;
+    int32_t *heavy;
+    int4 *tasks;
+    int64_t heavy_cap, task_cap;
+};
+
+void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const LeftOperand *left, hipStream_t s) {
     auto run = [&](auto rp, auto v) {
         using RP = decltype(rp);
         using VT = decltype(v);
@@ -952,11 +1122,20 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, int32_t *
         a.bitmap_words = (int)((M->cols + T * 32 - 1) / (T * 32));
         a.validate = ctx->validate;
         a.out = out;
-        a.ub = ub;
-        a.b_row_ptr = B->row_ptr;
-        a.b_is_i64 = B->row_ptr_type == TSP_I64;
-        a.b_rows = B->rows;
-        a.b_nnz = B->nnz;
+        if (left) {
+            a.ub = left->ub;
+            a.products = left->products;
+            a.b_row_ptr = left->B->row_ptr;
+            a.b_is_i64 = left->B->row_ptr_type == TSP_I64;
+            a.b_rows = left->B->rows;
+            a.merge_lanes = left->merge_lanes;
+            a.windows = left->windows;
+            a.heavy = left->heavy;
+            a.tasks = left->tasks;
+            a.heavy_cap = left->heavy_cap;
+            a.task_cap = left->task_cap;
+            a.rows_of = left->rows_of;
+        }
         a.d_scalars = ctx->d_scalars;
         launch_prepare(a, s);
     };
@@ -985,6 +1164,10 @@ void launch_fill(FillArgs &f, const int64_t *h, hipStream_t s) {
 }
 
 }  // namespace
+
+__global__ void k_clear_lists(int64_t *d_scalars) {
+    if (threadIdx.x == 0) d_scalars[S_ROW_LISTS] = 0;
+}
 
 // The product A*B has so few intermediate products per candidate pair of tiles that the row kernels are faster.
 static bool rows_preferred(int64_t products, int64_t candidates) { return products <= kRowPairProducts * candidates; }
@@ -1021,85 +1204,100 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     take(ma, A, a_ntr);
     if (alias) mb = ma;
     else take(mb, B, b_ntr);
-    int32_t *ub = ws.get<int32_t>((size_t)A->rows);
+    const int64_t chunks = (A->rows + kChunkRows - 1) / kChunkRows;
+    LeftOperand left{};
+    left.ub = ws.get<int32_t>((size_t)A->rows);
+    left.rows_of = ws.get<int32_t>((size_t)a_ntr);
+    left.products = ws.get<unsigned long long>((size_t)a_ntr);
+    left.B = B;
+    left.merge_lanes = merge_lanes;
+    left.windows = windows;
     unsigned long long *partial = ws.get<unsigned long long>((size_t)kPlanBlocks * kPlanSums);
-    int64_t heavy_cap = known ? hint.heavy : A->rows, task_cap = known ? hint.tasks : 0;
-    if (!known) {
-        // (tasks: one per heavy row and one more per kTaskProducts products, at most one per window; the products are not
-        // known yet, so a second plan run follows in the rare case that this guess is too small)
-        task_cap = std::min<int64_t>(A->rows * (int64_t)windows, 2 * A->rows + 4096);
-    }
-    int32_t *heavy = ws.get<int32_t>((size_t)std::max<int64_t>(heavy_cap, 1));
-    int4 *tasks = ws.get<int4>((size_t)std::max<int64_t>(task_cap, 1));
+    // (tasks of a product not seen before: one per heavy row and some more; where that is too few the lists are made again)
+    left.heavy_cap = known ? hint.heavy : A->rows;
+    left.task_cap = known ? hint.tasks : std::min<int64_t>(A->rows * (int64_t)windows, 2 * A->rows + 4096);
+    left.heavy = ws.get<int32_t>((size_t)std::max<int64_t>(left.heavy_cap, 1));
+    left.tasks = ws.get<int4>((size_t)std::max<int64_t>(left.task_cap, 1));
+    int32_t *row_nnz = ws.get<int32_t>((size_t)A->rows + 1);
+    uint32_t *group_len = ws.get<uint32_t>((size_t)chunks * kChunkTileRows);
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
 
     phase_begin(ctx, TSP_PHASE_CONVERT, s);
     {
         KernelTimer kt(ctx, TSP_KERNEL_CONVERT, s);
-        prepare(ctx, A, ma, ub, B, s);
-        if (!alias) prepare(ctx, B, mb, nullptr, B, s);
+        prepare(ctx, A, ma, &left, s);
+        if (!alias) prepare(ctx, B, mb, nullptr, s);
     }
     phase_end(ctx, TSP_PHASE_CONVERT, s);
     TSP_HIP_CHECK(ctx, hipGetLastError());
 
-    phase_begin(ctx, TSP_PHASE_SYMBOLIC, s);
-    auto plan = [&](bool publish) {
-        PlanArgs a{};
-        a.a_rows = A->rows;
-        a.a_tile_rows = a_ntr;
-        a.b_tile_rows = b_ntr;
-        a.a_start = ma.start;
-        a.ub = ub;
-        a.a_ntiles = ma.ntiles;
-        a.a_tile_col = ma.tile_col;
-        a.b_ntiles = mb.ntiles;
-        a.a_range = ma.range;
-        a.b_range = mb.range;
+    SumArgs sums{};
+    sums.a_tile_rows = a_ntr;
+    sums.b_tile_rows = b_ntr;
+    sums.a_start = ma.start;
+    sums.a_ntiles = ma.ntiles;
+    sums.a_tile_col = ma.tile_col;
+    sums.b_ntiles = mb.ntiles;
+    sums.rows_of = left.rows_of;
+    sums.a_range = ma.range;
+    sums.b_range = mb.range;
+    sums.products = left.products;
+    sums.same = alias;
+    sums.partial = partial;
+    const int sum_blocks = (int)std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, alias ? 0 : b_ntr) + 15) / 16);
+    // row_ptr of C when the sizes of its rows are there, and the sizes of everything to the host
+    int64_t *row_ptr = nullptr;
+    auto finish = [&](int timer) {
+        FinishArgs a{};
+        a.partial = partial;
+        a.partials = sum_blocks;
         a.same = alias;
-        a.merge_lanes = merge_lanes;
-        a.windows = windows;
-        a.heavy = heavy;
-        a.tasks = tasks;
-        a.heavy_cap = heavy_cap;
-        a.task_cap = task_cap;
         a.d_scalars = ctx->d_scalars;
         a.h_scalars_dev = ctx->h_scalars_dev;
-        a.publish_tag = publish ? ++ctx->publish_tag : 0;
-        a.partial = partial;
-        const int64_t blocks = std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, b_ntr) + 15) / 16);
-        KernelTimer kt(ctx, TSP_KERNEL_SCAN_SYM, s);
-        hipLaunchKernelGGL(k_row_plan, dim3((unsigned)blocks), dim3(256), 0, s, a);
+        KernelTimer kt(ctx, timer, s);
+        unsigned blocks = 1;
+        if (!row_ptr) {
+            hipLaunchKernelGGL(k_row_sums, dim3((unsigned)sum_blocks), dim3(256), 0, s, sums);
+        } else if (A->rows <= kFinishRows) {
+            a.rows = A->rows;
+            a.row_nnz = row_nnz;
+            a.group_len = group_len;
+            a.c_row_ptr = row_ptr;
+            blocks = (unsigned)chunks;
+        } else {
+            int64_t *tmp = ws.get<int64_t>(scan_tmp_entries(A->rows));
+            if (!tmp) return (int)TSP_ERR_ALLOC_FAILED;
+            const int rc = scan_exclusive_i32_to_i64(ctx, row_nnz, row_ptr, A->rows, ctx->d_scalars + S_C_NNZ, nullptr, tmp, s);
+            if (rc) return rc;
+        }
+        a.publish_tag = ++ctx->publish_tag;
+        hipLaunchKernelGGL(k_row_finish, dim3(blocks), dim3(256), 0, s, a);
+        TSP_HIP_CHECK(ctx, hipGetLastError());
+        return (int)TSP_OK;
     };
-    plan(!known);
-    TSP_HIP_CHECK(ctx, hipGetLastError());
-    int64_t n_heavy = heavy_cap, n_tasks = task_cap;
-    bool any_merged = !known || hint.merged;
-    auto sizes_known = [&]() {               // the host has the numbers of k_row_plan
+    int64_t n_heavy = left.heavy_cap, n_tasks = left.task_cap;
+    auto sizes_known = [&]() {               // the host has the numbers of k_row_finish
         const int64_t *h = ctx->h_scalars;
         if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
-        if (h[S_INTERNAL]) return (int)TSP_ERR_HIP;
         n_heavy = h[S_ROW_HEAVY];
         n_tasks = h[S_ROW_TASKS];
-        any_merged = h[S_ROW_MERGED] > 0;
         std::copy(sizes, sizes + 6, hint.sizes);
-        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) ||
-                     n_tasks >= INT32_MAX;
+        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
-        hint.merged = any_merged;
         return (int)TSP_OK;
     };
     if (!known) {
-        int rc = wait_published_scalars(ctx, ctx->publish_tag, s);
+        int rc = finish(TSP_KERNEL_SCAN_SYM);
+        if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);
         if (!rc) rc = sizes_known();
         if (rc) return rc;
         if (hint.tiles) return TSP_OK;       // (the tile kernels start over; the scalars they use are cleared for them)
     }
     *taken = true;
 
-    int64_t *row_ptr = ws.get<int64_t>((size_t)A->rows + 1);
-    int32_t *row_nnz = ws.get<int32_t>((size_t)A->rows + 1);
-    uint32_t *group_len = ws.get<uint32_t>((size_t)a_ntr + 4);
+    phase_begin(ctx, TSP_PHASE_SYMBOLIC, s);
+    row_ptr = ws.get<int64_t>((size_t)A->rows + 1);
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
     uint32_t *pack = nullptr, *offset = nullptr, *bits = nullptr;
     int64_t bit_rows = 0;
@@ -1111,15 +1309,28 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     };
     int32_t *table = nullptr, *words = nullptr;
     uint2 *word = nullptr;
-    auto size_rows = [&]() {
-        if (n_tasks > task_cap || n_heavy > heavy_cap) {
+    MergeArgs m{};
+    m.rows = A->rows;
+    m.a_start = ma.start;
+    m.b_start = mb.start;
+    m.ub = left.ub;
+    m.a_rec = ma.rec;
+    m.b_rec = mb.rec;
+    m.b_col = B->col_idx;
+    m.row_nnz = row_nnz;
+    m.group_len = group_len;
+    const unsigned merge_blocks = (unsigned)((A->rows * merge_lanes + 255) / 256);
+    m.blocks = (int)merge_blocks;
+    auto size_rows = [&](bool again) {
+        if (again || n_tasks > left.task_cap || n_heavy > left.heavy_cap) {
             // the lists did not fit: make them again, as large as they have to be
-            heavy_cap = n_heavy;
-            task_cap = n_tasks;
-            heavy = ws.get<int32_t>((size_t)heavy_cap);
-            tasks = ws.get<int4>((size_t)task_cap);
+            left.heavy_cap = n_heavy;
+            left.task_cap = n_tasks;
+            left.heavy = ws.get<int32_t>((size_t)std::max<int64_t>(n_heavy, 1));
+            left.tasks = ws.get<int4>((size_t)std::max<int64_t>(n_tasks, 1));
             if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
-            plan(false);
+            hipLaunchKernelGGL(k_clear_lists, dim3(1), dim3(64), 0, s, ctx->d_scalars);
+            prepare(ctx, A, ma, &left, s);
         }
         if (n_heavy > 0) {
             if (!pack) {
@@ -1137,25 +1348,15 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
         }
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
-        MergeArgs m{};
-        m.rows = A->rows;
-        m.a_start = ma.start;
-        m.b_start = mb.start;
-        m.ub = ub;
-        m.a_rec = ma.rec;
-        m.b_rec = mb.rec;
-        m.row_nnz = row_nnz;
-        m.group_len = group_len;
         auto merge = merge_lanes == 8 ? k_row_merge<8, false> : k_row_merge<16, false>;
-        hipLaunchKernelGGL(merge,
-                           dim3((unsigned)((A->rows * merge_lanes + 255) / 256)), dim3(256), 0, s, m);
+        hipLaunchKernelGGL(merge, dim3(merge_blocks + (unsigned)sum_blocks), dim3(256), 0, s, m, sums);
         if (n_heavy > 0) {
             PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, windows, shift};
             if (B->nnz > 16 * B->rows)
                 hipLaunchKernelGGL(k_heavy_pack<64>, dim3((unsigned)((B->rows * 64 + 255) / 256)), dim3(256), 0, s, p);
             else
                 hipLaunchKernelGGL(k_heavy_pack<16>, dim3((unsigned)((B->rows * 16 + 255) / 256)), dim3(256), 0, s, p);
-            c.heavy = heavy;
+            c.heavy = left.heavy;
             c.heavy_cap = n_heavy;
             c.d_scalars = ctx->d_scalars;
             c.a_start = ma.start;
@@ -1173,38 +1374,24 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         }
         return (int)TSP_OK;
     };
-    auto offsets = [&]() {                   // row_ptr of C, nnz(C) to the host: the wait that sizes C
-        bool published = false;
-        {
-            KernelTimer kt(ctx, TSP_KERNEL_SCAN_ROWS, s);
-            published = row_ptr_in_one_launch(ctx, row_nnz, A->rows, group_len, row_ptr, s);
-            if (!published) {
-                int64_t *tmp = ws.get<int64_t>(scan_tmp_entries(A->rows));
-                if (!tmp) return (int)TSP_ERR_ALLOC_FAILED;
-                int rc = scan_exclusive_i32_to_i64(ctx, row_nnz, row_ptr, A->rows, ctx->d_scalars + S_C_NNZ, nullptr, tmp, s);
-                if (rc) return rc;
-            }
-        }
-        TSP_HIP_CHECK(ctx, hipGetLastError());
-        return published ? wait_published_scalars(ctx, ctx->publish_tag, s) : read_scalars(ctx, s);
-    };
-    int rc = size_rows();
+    int rc = size_rows(false);
     if (rc) return rc;
     phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
     phase_begin(ctx, TSP_PHASE_COUNT, s);
-    rc = offsets();
-    if (rc) return rc;
-    if (known) {
-        const int64_t had_heavy = n_heavy, had_tasks = n_tasks;
-        rc = sizes_known();
-        if (rc) return rc;
-        if (n_heavy > had_heavy || n_tasks > had_tasks) {       // another matrix of the same sizes, with more work in it
-            rc = size_rows();
-            if (!rc) rc = offsets();
-            if (rc) return rc;
-        }
-    }
+    rc = finish(TSP_KERNEL_SCAN_ROWS);
     phase_end(ctx, TSP_PHASE_COUNT, s);
+    if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);           // the wait that sizes C
+    if (rc) return rc;
+    const int64_t had_heavy = n_heavy, had_tasks = n_tasks;
+    rc = sizes_known();
+    if (rc) return rc;
+    if (n_heavy > had_heavy || n_tasks > had_tasks) {                // another matrix of the same sizes, with more work in it
+        rc = size_rows(true);
+        if (rc) return rc;
+        rc = finish(TSP_KERNEL_SCAN_ROWS);
+        if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);
+        if (rc) return rc;
+    }
     const int64_t nnz = ctx->h_scalars[S_C_NNZ];
     int32_t *col = ws.get<int32_t>((size_t)nnz);
     float *val = ws.get<float>((size_t)nnz);
@@ -1216,30 +1403,23 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         // (nothing reads the scalar block any more: the last kernel clears it for the next call)
         int64_t *clear = ctx->d_scalars;
         bool cleared = false;
-        if (any_merged && nnz > 0) {
-            MergeArgs m{};
-            m.rows = A->rows;
-            m.a_start = ma.start;
-            m.b_start = mb.start;
-            m.ub = ub;
-            m.a_rec = ma.rec;
-            m.b_rec = mb.rec;
+        if (nnz > 0 && ctx->h_scalars[S_ROW_MERGED] > 0) {
             m.c_row_ptr = row_ptr;
             m.c_col = col;
             m.c_val = val;
-            // entries of C a wave collects: twice the mean of its rows, at most 8 KB
+            // entries of C a wave collects: twice the mean of its rows
             const int64_t mean = nnz * (64 / merge_lanes) / A->rows;
             m.stage = 128;
-            while (m.stage < 1024 && m.stage < 2 * mean) m.stage <<= 1;
+            const int most = merge_lanes == 8 ? 1024 : 512;      // (with the lists within 64 KB of LDS)
+            while (m.stage < most && m.stage < 2 * mean) m.stage <<= 1;
             m.d_scalars_to_clear = n_tasks > 0 ? nullptr : clear;
             cleared = m.d_scalars_to_clear != nullptr;
             auto merge = merge_lanes == 8 ? k_row_merge<8, true> : k_row_merge<16, true>;
-            hipLaunchKernelGGL(merge,
-                               dim3((unsigned)((A->rows * merge_lanes + 255) / 256)), dim3(256), (size_t)m.stage * 32, s, m);
+            hipLaunchKernelGGL(merge, dim3(merge_blocks), dim3(256), (size_t)m.stage * 32, s, m, sums);
         }
         if (n_tasks > 0) {
             FillArgs f{};
-            f.tasks = tasks;
+            f.tasks = left.tasks;
             f.n_tasks = n_tasks;
             f.a_start = ma.start;
             f.b_start = mb.start;
