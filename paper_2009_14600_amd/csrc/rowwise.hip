@@ -541,18 +541,17 @@ __global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a, const SumA
     }
     Item *mine = &s_list[wave][lane];
     {
-        const int longest = wave_max(merged ? deg : 0);
+        // (all requested before any is used, and without branches, which the waits could not see through)
         Item x[G];
+        bool there[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) {
-            x[i] = none();
-            if (i < longest) {
-                const int32_t pi = __shfl(p, i, G), ei = __shfl(e, i, G);
-                if (pi + l < ei) x[i] = item(pi + l);
-            }
+            const int32_t k = __shfl(p, i, G) + l;
+            there[i] = k < __shfl(e, i, G);
+            x[i] = item(there[i] ? k : 0);
         }
 #pragma unroll
-        for (int i = 0; i < G; ++i) s_list[wave][l * kPitch + (lane - l) + i] = x[i];
+        for (int i = 0; i < G; ++i) s_list[wave][l * kPitch + (lane - l) + i] = there[i] ? x[i] : none();
         Item end = none();
         if (e - p > G) {
             if constexpr (kFill) end.x = kMore;
@@ -572,12 +571,9 @@ __global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a, const SumA
         if (column(head) < 0) {
             Item x[G];
 #pragma unroll
-            for (int j = 0; j < G; ++j) {
-                x[j] = none();
-                if (p + j < e) x[j] = item(p + j);
-            }
+            for (int j = 0; j < G; ++j) x[j] = item(min(p + j, max(e - 1, 0)));
 #pragma unroll
-            for (int j = 0; j < G; ++j) mine[j * kPitch] = x[j];
+            for (int j = 0; j < G; ++j) mine[j * kPitch] = p + j < e ? x[j] : none();
             p += G;
             Item end = none();
             if (e - p > 0) {

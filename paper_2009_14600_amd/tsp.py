@@ -135,11 +135,22 @@ def _check(status: int):
         raise TspError(status, load_library().tsp_strerror(status).decode())
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("tsp needs a GPU (torch.cuda.is_available() is False); there is no CPU path")
-    return torch
+    global _torch_module
+    if _torch_module is None:                 # (asked once: the answer takes longer than the rest of a call's marshalling)
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("tsp needs a GPU (torch.cuda.is_available() is False); there is no CPU path")
+        _ROW_PTR_TYPES.update({torch.int32: TSP_I32, torch.int64: TSP_I64})
+        _VALUE_TYPES.update({torch.float16: TSP_F16, torch.uint16: TSP_F16, torch.int16: TSP_F16, torch.float32: TSP_F32})
+        _torch_module = torch
+    return _torch_module
+
+
+_ROW_PTR_TYPES, _VALUE_TYPES = {}, {}
 
 
 @dataclass
@@ -159,14 +170,13 @@ class DeviceCSR:
 
     def _struct(self) -> _Csr:
         torch = _torch()
-        rp_type = {torch.int32: TSP_I32, torch.int64: TSP_I64}[self.row_ptr.dtype]
-        v_type = {torch.float16: TSP_F16, torch.uint16: TSP_F16, torch.int16: TSP_F16,
-                  torch.float32: TSP_F32}[self.val.dtype]
-        assert self.col_idx.dtype == torch.int32
-        for t in (self.row_ptr, self.col_idx, self.val):
+        row_ptr, col_idx, val = self.row_ptr, self.col_idx, self.val
+        rp_type, v_type = _ROW_PTR_TYPES[row_ptr.dtype], _VALUE_TYPES[val.dtype]
+        assert col_idx.dtype == torch.int32
+        for t in (row_ptr, col_idx, val):
             assert t.is_cuda and t.is_contiguous()
-        return _Csr(self.rows, self.cols, self.nnz, self.row_ptr.data_ptr(), self.col_idx.data_ptr(),
-                    self.val.data_ptr(), rp_type, v_type)
+        return _Csr(self.rows, self.cols, col_idx.shape[0], row_ptr.data_ptr(), col_idx.data_ptr(),
+                    val.data_ptr(), rp_type, v_type)
 
     def free(self):
         if self._owner is not None and self._raw is not None:
@@ -200,6 +210,8 @@ class Handle:
         torch = _torch()
         self._torch = torch
         self._blocks = {}
+        self._typed = {}             # views of whole blocks, by address and type
+        self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
         def _alloc(_user, nbytes, _stream):
             try:
@@ -211,6 +223,7 @@ class Handle:
 
         def _free(_user, ptr, _stream):
             self._blocks.pop(ptr, None)
+            self._typed.pop(ptr, None)
 
         self._alloc_cb, self._free_cb = _ALLOC_FN(_alloc), _FREE_FN(_free)
         self._allocator = _Allocator(self._alloc_cb, self._free_cb, None)
@@ -221,14 +234,25 @@ class Handle:
 
     # -- plumbing ---------------------------------------------------------------------------
     def _stream(self):
-        return ctypes.c_void_p(self._torch.cuda.current_stream().cuda_stream)
+        if self._raw_stream is not None:
+            return self._raw_stream(self._torch.cuda.current_device())
+        return self._torch.cuda.current_stream().cuda_stream
 
     def _view(self, ptr: int, count: int, dtype):
         """Tensor view of `count` elements at device address `ptr` inside one of our blocks."""
         torch = self._torch
-        itemsize = torch.empty((), dtype=dtype).element_size()
         if count == 0 or not ptr:
             return torch.empty(0, dtype=dtype, device="cuda")
+        block = self._blocks.get(ptr)
+        if block is not None:                 # an array at the start of its block, as outputs are
+            views = self._typed.get(ptr)
+            if views is None:
+                views = self._typed[ptr] = {}
+            whole = views.get(dtype)
+            if whole is None:
+                whole = views[dtype] = block.view(dtype)
+            return whole.narrow(0, 0, count)
+        itemsize = dtype.itemsize
         for base, block in self._blocks.items():
             if base <= ptr and ptr + count * itemsize <= base + block.numel():
                 off = ptr - base
@@ -240,6 +264,7 @@ class Handle:
             self._lib.tsp_destroy(self._h)
             self._h = ctypes.c_void_p()
             self._blocks.clear()
+            self._typed.clear()
 
     def __del__(self):
         try:
