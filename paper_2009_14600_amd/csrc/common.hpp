@@ -35,12 +35,12 @@ enum Scalar {
     // the row kernels (rowwise.hip):
     S_ROW_LISTS = 15,        // heavy rows and their tasks listed so far (one packed counter)
     S_ROW_PRODUCTS = 17,     // intermediate products
-    S_ROW_MERGED = 18,       // rows of C that are merged
+    S_ROW_SMALL = 18,        // rows of C that go through a table in LDS
     S_ROW_HEAVY = 19,        // rows of C that are not
     S_ROW_TASKS = 20,        // blocks of k_heavy_fill
     S_ROW_RANGE_A = 21,      // magnitude and granularity of the values (value_range)
     S_ROW_RANGE_B = 22,
-    S_ROW_LONGEST = 23,      // entries of the longest row of A that is not merged
+    S_ROW_LONGEST = 23,      // entries of the longest heavy row of A
     S_PUBLISHED = 31,        // host mirror only: a slot without a value (publish_scalars tags every slot)
 };
 

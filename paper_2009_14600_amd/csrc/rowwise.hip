@@ -6,12 +6,12 @@
 //   k_row_prepare   one pass over an operand: validation, entries as {column, value} records, tiles per tile-row,
 //                   and for A the number of intermediate products of every row and the lists of work
 //   k_row_finish    row_ptr of C; candidate tile pairs (the measure by which tsp_spgemm chooses this path) and other sums
-//   k_row_merge     rows with few, short rows of B behind them: a lane per row of B, merged in column order
+//   k_row_small     rows with few, short rows of B behind them: a hash table per row in LDS; k_small_copy puts them in place
 //   k_heavy_count   the other rows: a block per row, one bit per column of C in LDS
 //   k_heavy_fill    a block per row and some windows of columns, a dense accumulator in LDS
 //
-// Runs are bit-identical.  Products of fp16 numbers are exact in fp32.  A merged entry is summed by the lanes of its
-// group as a tree, in fp32.  A heavy entry is summed in integers where every partial sum is exact in them (all products
+// Runs are bit-identical.  Products of fp16 numbers are exact in fp32.  An entry of a small row is summed in fp32 in
+// the order of the entries of A.  A heavy entry is summed in integers where every partial sum is exact in them (all products
 // are multiples of a power of two that the operands' values say; then the order of the additions does not matter and a
 // whole block shares the accumulator), and otherwise in fp64 by one wave in the order of the entries of A.
 #include "common.hpp"
@@ -22,7 +22,6 @@
 
 namespace tsp {
 
-constexpr int kMergeProducts = 256;      // a merged row has at most this many intermediate products
 constexpr int kPlanBlocks = 256;         // blocks that add up tile-rows, at most
 constexpr int64_t kFinishRows = 1 << 21; // rows of which k_row_finish makes row_ptr (every block reads all groups before it)
 constexpr int kChunkTileRows = 128, kChunkRows = kChunkTileRows * T;   // rows whose row_ptr one block writes
@@ -34,6 +33,7 @@ constexpr int kHeavyThreads = 512;
 constexpr int32_t kNoCol = 0x7FFFFFFF;
 // Intermediate products behind one task of k_heavy_fill (a row, or some of its windows)
 constexpr int64_t kKeptPattern = (int64_t)16 << 30;   // bytes of it, at most
+constexpr int64_t kFoundEntries = (int64_t)2 << 30;   // of the small rows before they are moved into C, at most
 constexpr int kTaskProducts = 65536;
 constexpr int64_t kRowPairProducts = 64; // products per candidate pair of tiles up to which the rows are the better way
 
@@ -44,6 +44,12 @@ struct RowMatrix {                       // an operand in the form the row kerne
     int32_t *tile_col = nullptr;         // their columns, at the position of the tile-row's first entry; any order
     uint32_t *range = nullptr;           // magnitude and granularity of every tile-row's values (value_range)
 };
+
+// A value that is the same for the whole wave and that no kernel running now writes, through the scalar cache.
+template <typename X>
+__device__ __forceinline__ X uniform_load(const X *p) {
+    return *(const __attribute__((address_space(4))) X *)(uintptr_t)p;
+}
 
 template <typename RP, typename VT>
 struct PrepareArgs {
@@ -60,12 +66,12 @@ struct PrepareArgs {
     const void *b_row_ptr;               // of B, as the caller gave it
     int b_is_i64;
     int64_t b_rows;
-    int merge_lanes;                     // most entries of a row of A that is merged
+    int small_lanes, small_products;     // most entries and products of a small row of A
     int windows;                         // of columns of C, for the heavy rows
-    int32_t *heavy;                      // rows that are not merged
+    int32_t *heavy;                      // rows that are not small
     int4 *tasks;                         // {row, index into heavy, first window, one past the last window}
     int64_t heavy_cap, task_cap;
-    int32_t *rows_of;                    // of every tile-row: 32 * entries of its longest heavy row + its merged rows
+    int32_t *rows_of;                    // of every tile-row: 32 * entries of its longest heavy row + its small rows
     int64_t *d_scalars;
 };
 
@@ -87,14 +93,14 @@ __device__ __forceinline__ uint32_t range_max(uint32_t x, uint32_t y) {
     return max(x & 0xFFFF0000u, y & 0xFFFF0000u) | max(x & 0xFFFFu, y & 0xFFFFu);
 }
 
-__device__ __forceinline__ bool merged_row(int32_t entries, int32_t products, int merge_lanes) {
-    return entries <= merge_lanes && products <= kMergeProducts;
+__device__ __forceinline__ bool small_row(int32_t entries, int32_t products, int most_entries, int most_products) {
+    return entries <= most_entries && products <= most_products;
 }
 
 // A team of kTeam threads per tile-row (a wave, or a block for long tile-rows), its entries flat over the lanes, kU of
 // them per lane in flight.  The team's bitmap over the tile columns tells the first entry that falls into a tile (the
 // atomic returns the word before): those lanes list the tile.  At the end a lane per row of A says whether the row is
-// merged or heavy and lists the heavy one with its tasks.
+// small or heavy and lists the heavy one with its tasks.
 template <int kTeam, int kU, typename RP, typename VT>
 __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a) {
     constexpr int kTeams = 256 / kTeam;
@@ -227,7 +233,7 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
         ub = min(s_ub[team][tid], (unsigned long long)INT32_MAX);
         deg = s_ptr[team][tid + 1] - s_ptr[team][tid];
         a.ub[row] = (int32_t)ub;
-        if (deg > 0 && ub > 0 && !merged_row(deg, (int32_t)ub, a.merge_lanes)) tasks = min(max((int)ub / kTaskProducts, 1), groups);
+        if (deg > 0 && ub > 0 && !small_row(deg, (int32_t)ub, a.small_lanes, a.small_products)) tasks = min(max((int)ub / kTaskProducts, 1), groups);
     }
     unsigned long long all = tid < T ? s_ub[team][tid] : 0ull;
     for (int d = 1; d < T; d <<= 1) all += __shfl_xor(all, d, T);
@@ -251,8 +257,8 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                                                 min((int)((int64_t)groups * (t + 1) / tasks) * kGroupWindows, a.windows));
         }
     }
-    const int longest = heavies ? wave_max(tasks > 0 ? deg : 0) : 0, merged = __popcll(__ballot(deg > 0 && ub > 0 && tasks == 0));
-    if (lane == 0) a.rows_of[I] = min(longest, (1 << 26) - 1) * 32 + merged;
+    const int longest = heavies ? wave_max(tasks > 0 ? deg : 0) : 0, small = __popcll(__ballot(deg > 0 && ub > 0 && tasks == 0));
+    if (lane == 0) a.rows_of[I] = min(longest, (1 << 26) - 1) * 32 + small;
 }
 
 // What the operands are like, summed over their tile-rows.  The blocks leave their sums in `partial`; k_row_finish, which
@@ -266,7 +272,7 @@ struct SumArgs {
     int same;                            // A and B are one matrix
     unsigned long long *partial;         // [kPlanSums][kPlanBlocks]
 };
-enum { kSumCandidates, kSumTilesA, kSumTilesB, kSumProducts, kSumMerged, kSumRanges, kSumLongest };
+enum { kSumCandidates, kSumTilesA, kSumTilesB, kSumProducts, kSumSmall, kSumRanges, kSumLongest };
 
 // Sixteen lanes per tile-row: tiles, candidate pairs (the tiles of B's tile-rows behind the tiles of A: the measure by
 // which tsp_spgemm chooses this path), products, value ranges.
@@ -275,7 +281,7 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
     const int lane = lane_id(), r = threadIdx.x & 15;
     if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = s_max[threadIdx.x] = 0;
     __syncthreads();
-    unsigned long long cand = 0, tiles_a = 0, tiles_b = 0, products = 0, merged = 0;
+    unsigned long long cand = 0, tiles_a = 0, tiles_b = 0, products = 0, small = 0;
     uint32_t range_a = 0, range_b = 0;
     int longest = 0;
     const int64_t most = max(a.a_tile_rows, a.same ? (int64_t)0 : a.b_tile_rows);
@@ -295,7 +301,7 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
                 products += a.products[I];
                 const int32_t rows_of = a.rows_of[I];
                 longest = max(longest, rows_of >> 5);
-                merged += rows_of & 31;
+                small += rows_of & 31;
             }
             for (int32_t j = r; j < min(n, 64); j += 16) {
                 const int32_t K = a.a_tile_col[e0 + j];
@@ -324,7 +330,7 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
     add(kSumTilesA, tiles_a);
     add(kSumTilesB, tiles_b);
     add(kSumProducts, products);
-    add(kSumMerged, merged);
+    add(kSumSmall, small);
     auto most_of = [&](int slot, int v) {
         v = wave_max(v);
         if (lane == 0 && v) atomicMax(&s_max[slot], (unsigned long long)v);
@@ -425,7 +431,7 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
         a.d_scalars[S_TILES_A] = (int64_t)s_sum[kSumTilesA];
         a.d_scalars[S_TILES_B] = (int64_t)(a.same ? s_sum[kSumTilesA] : s_sum[kSumTilesB]);
         a.d_scalars[S_ROW_PRODUCTS] = (int64_t)s_sum[kSumProducts];
-        a.d_scalars[S_ROW_MERGED] = (int64_t)s_sum[kSumMerged];
+        a.d_scalars[S_ROW_SMALL] = (int64_t)s_sum[kSumSmall];
         const int from = a.same ? 0 : 2;
         a.d_scalars[S_ROW_RANGE_A] = (int64_t)(s_max[0] << 16 | s_max[1]);
         a.d_scalars[S_ROW_RANGE_B] = (int64_t)(s_max[from] << 16 | s_max[from + 1]);
@@ -437,224 +443,246 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
     publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag);
 }
 
-// ---- merged rows ------------------------------------------------------------------------------------------------
-#define TSP_LANES(v, ctrl) __builtin_amdgcn_update_dpp(0, (v), (ctrl), 0xf, 0xf, true)
-template <int G>
-__device__ __forceinline__ int lanes_min(int v) {
-    if constexpr (G == 8) {
-        v = min(v, TSP_LANES(v, 0xB1));                  // quad_perm [1,0,3,2]
-        v = min(v, TSP_LANES(v, 0x4E));                  // quad_perm [2,3,0,1]
-        v = min(v, TSP_LANES(v, 0x141));                 // row_half_mirror
-    } else {
-        v = min(v, TSP_LANES(v, 0x128));                 // row_ror:8, 4, 2, 1
-        v = min(v, TSP_LANES(v, 0x124));
-        v = min(v, TSP_LANES(v, 0x122));
-        v = min(v, TSP_LANES(v, 0x121));
-    }
-    return v;
-}
-template <int G>
-__device__ __forceinline__ float lanes_sum(float v) {     // the same tree, and so the same bits, in all lanes of the group
-    auto moved = [](float x, auto ctrl) {
-        return __builtin_bit_cast(float, TSP_LANES(__builtin_bit_cast(int, x), decltype(ctrl)::value));
-    };
-    if constexpr (G == 8) {
-        v += moved(v, std::integral_constant<int, 0xB1>{});
-        v += moved(v, std::integral_constant<int, 0x4E>{});
-        v += moved(v, std::integral_constant<int, 0x141>{});
-    } else {
-        v += moved(v, std::integral_constant<int, 0x128>{});
-        v += moved(v, std::integral_constant<int, 0x124>{});
-        v += moved(v, std::integral_constant<int, 0x122>{});
-        v += moved(v, std::integral_constant<int, 0x121>{});
-    }
-    return v;
+// ---- small rows -------------------------------------------------------------------------------------------------
+// Element i of an array of less than 4 GiB: the address is a scalar base and a 32-bit offset.
+template <typename X>
+__device__ __forceinline__ X element(const X *base, uint32_t i) {
+    return *reinterpret_cast<const X *>(reinterpret_cast<const char *>(base) + (size_t)(uint32_t)(i * (uint32_t)sizeof(X)));
 }
 
-struct MergeArgs {
+// How the small rows of a launch are worked off: lanes per row of A, lanes per row of B (a power of two, at most as
+// many), slots of the row's table (a power of two), and the most products of a small row.
+struct SmallShape {
+    int lanes, list_lanes, slots, products;
+    bool narrow() const { return list_lanes < lanes; }
+    int wave_rows() const { return 64 / lanes; }
+    size_t wave_bytes() const { return (size_t)wave_rows() * (slots * 5 + products * (narrow() ? 12 : 8)); }   // LDS
+};
+
+struct SmallArgs {
+    SmallShape shape;
+    int wave_bytes;
     int64_t rows;
     const int32_t *a_start, *b_start, *ub;
     const int2 *a_rec, *b_rec;
-    const int32_t *b_col;                // the columns of b_rec by themselves, as the caller gave them
-    // sizing pass
     int32_t *row_nnz;
     uint32_t *group_len;                 // entries per 16 rows
-    int blocks;                          // that merge; the ones behind them sum (SumArgs)
-    // multiplication pass
+    int2 *found;                         // [waves][wave_rows * products] entries {column, value} of a wave's rows, in order
+    int32_t *wave_total;                 // ... and how many
+    int blocks;                          // of rows; the ones behind them sum (SumArgs)
+};
+
+// A group of G lanes per row of A with at most G entries and shape.products intermediate products.  The rows of B behind
+// it are fetched by the group's lanes side by side (a lane per list costs the load path a cycle per lane), all before the
+// first is used, and go through a hash table of the row in LDS.  New columns get places in a list, where the products
+// are added up.  Then the rank of every column among the row's is found (each lane compares its columns with all), and
+// the wave's rows go in order into memory of their own: k_small_copy moves them into C when its row_ptr is known.  (Doing
+// all of it twice, once for the sizes, costs more than the copy.)
+// Bound by the vector instructions of every wave, many of which do not depend on what its rows hold.  Measured, this
+// kernel and the copy, against merging the lists in LDS once to size C and once to fill it: a 512x512 mesh 36 + 13 us (64
+// before), 65536 rows of 8 random entries 45 + 13 us (68), the light rows of R-MAT scale 14 31 + 6 us (135).
+// A whole group per row of B (kNarrow false): one row of B at a time, whose columns are distinct, so no two lanes meet at
+// an entry and the fp32 sums form in the order of the entries of A.  Short rows of B (kNarrow): several at a time, added
+// with LDS atomics in fp64.
+template <int G, bool kNarrow>
+__global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums) {
+    constexpr int kRows = 64 / G;        // per wave
+    constexpr int kAhead = kNarrow ? G / 2 : G;
+    constexpr int32_t kFree = -1;
+    using Sum = typename std::conditional<kNarrow, double, float>::type;
+    extern __shared__ __align__(16) unsigned char small_lds[];
+    __shared__ uint32_t s_len[256 / G];
+    if ((int)blockIdx.x >= a.blocks) {
+        sum_tile_rows(sums, (int)blockIdx.x - a.blocks, (int)gridDim.x - a.blocks);
+        return;
+    }
+    const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
+    const uint32_t row = blockIdx.x * (256 / G) + threadIdx.x / G;
+    const int slots = a.shape.slots, most = a.shape.products;
+    unsigned char *lds = small_lds + wave * a.wave_bytes;
+    int32_t *table = reinterpret_cast<int32_t *>(lds) + (lane / G) * slots;
+    Sum *sum = reinterpret_cast<Sum *>(lds + kRows * slots * 4) + (lane / G) * most;
+    int32_t *keys = reinterpret_cast<int32_t *>(lds + kRows * (slots * 4 + most * (int)sizeof(Sum))) + (lane / G) * most;
+    uint8_t *place = lds + kRows * (slots * 4 + most * ((int)sizeof(Sum) + 4)) + (lane / G) * slots;
+    for (int i = lane; i < kRows * slots / 4; i += 64) reinterpret_cast<int4 *>(lds)[i] = make_int4(kFree, kFree, kFree, kFree);
+    if constexpr (kNarrow) {
+        int4 *zero = reinterpret_cast<int4 *>(lds + kRows * slots * 4);
+        for (int i = lane; i < kRows * most / 2; i += 64) zero[i] = make_int4(0, 0, 0, 0);
+    }
+    int4 *no_keys = reinterpret_cast<int4 *>(lds + kRows * (slots * 4 + most * (int)sizeof(Sum)));
+    for (int i = lane; i < kRows * most / 4; i += 64) no_keys[i] = make_int4(kNoCol, kNoCol, kNoCol, kNoCol);
+    int32_t p = 0, e = 0, deg = 0, ub = 0;
+    uint32_t av = 0;
+    bool small = false;
+    if (row < a.rows) {
+        const int32_t s = element(a.a_start, row);
+        deg = element(a.a_start, row + 1) - s;
+        ub = element(a.ub, row);
+        small = ub > 0 && deg > 0 && small_row(deg, ub, G, most);
+        if (small && l < deg) {
+            const int2 x = element(a.a_rec, (uint32_t)(s + l));
+            p = element(a.b_start, (uint32_t)x.x);
+            e = element(a.b_start, (uint32_t)x.x + 1);
+            av = (uint32_t)x.y;
+        }
+    }
+    const int lists = wave_max(small ? deg : 0), longest = wave_max(e - p);
+    // round t: list t, or with narrow lists the lists t * (G / width) ... of the group, and element j of each
+    const int width = kNarrow ? a.shape.list_lanes : G, per = kNarrow ? G / width : 1;
+    const int j = kNarrow ? l & (width - 1) : l;
+    const int rounds = kNarrow ? (lists + per - 1) / per : lists;
+    const int from0 = (lane - l + (kNarrow ? l / width : 0)) * 4;          // lane of the round's list, in bytes
+    auto of_list = [&](auto v, int t) { return __builtin_amdgcn_ds_bpermute(from0 + t * per * 4, (int)v); };
+    // (all requested before any is used, and without branches, which the waits could not see through)
+    int2 x[kAhead];
+    bool there[kAhead];
+#pragma unroll
+    for (int t = 0; t < kAhead; ++t) {
+        const int32_t k = of_list(p, t) + j;
+        there[t] = t < rounds && k < of_list(e, t);
+        x[t] = element(a.b_rec, there[t] ? (uint32_t)k : 0u);
+    }
+    wave_sync();
+    const int group_shift = lane & ~(G - 1);
+    const int bits = 31 - __builtin_clz(slots);
+    int listed = 0;                                          // columns of the row so far
+    auto take = [&](const int2 &y, uint32_t f, bool on) {
+        bool made = false;
+        uint32_t slot = ((uint32_t)__umul24((uint32_t)y.x, 0x9E3779u) >> (24 - bits)) & (uint32_t)(slots - 1);
+        if (on)
+            while (true) {
+                const int32_t old = atomicCAS(&table[slot], kFree, y.x);
+                made = old == kFree;
+                if (made || old == y.x) break;
+                slot = (slot + 1) & (uint32_t)(slots - 1);
+            }
+        const float product = __uint_as_float(f) * __uint_as_float((uint32_t)y.y);
+        const uint32_t mine = (uint32_t)(__ballot(made) >> group_shift) & ((1u << G) - 1u);
+        // (no more than `most`, whatever an operand that was not validated holds)
+        int at = min(listed + __popc(mine & ((1u << l) - 1u)), most - 1);
+        if (made) {
+            place[slot] = (uint8_t)at;
+            keys[at] = y.x;
+            if constexpr (!kNarrow) sum[at] = product + 0.f;
+        }
+        listed += __popc(mine);
+        if constexpr (kNarrow) {
+            wave_sync();                                     // (another list of the round may have made the place)
+            if (on) unsafeAtomicAdd(&sum[min((int)place[slot], most - 1)], (double)product);
+        } else {
+            if (on && !made) sum[min((int)place[slot], most - 1)] += product;
+        }
+        wave_sync();
+    };
+#pragma unroll
+    for (int t = 0; t < kAhead; ++t)
+        if (t < rounds) take(x[t], (uint32_t)of_list(av, t), there[t]);
+    // lists that are longer than their lanes (the order of the sums stays fixed: by chunks, in them by lists)
+    for (int c = width; c < longest; c += width)
+        for (int t = 0; t < rounds; ++t) {
+            const int32_t k = of_list(p, t) + j + c;
+            const bool on = k < of_list(e, t);
+            take(element(a.b_rec, on ? (uint32_t)k : 0u), (uint32_t)of_list(av, t), on);
+        }
+    const int n = min(listed, most);
+    const uint32_t inc = wave_inclusive_scan(l == 0 ? (uint32_t)n : 0u);
+    const int total = __builtin_amdgcn_readlane((int)inc, 63), longest_row = wave_max(n);
+    const int off = __builtin_amdgcn_ds_bpermute(group_shift * 4, (int)inc) - n;       // of the row among the entries of the wave
+    int2 *found = a.found + (size_t)(blockIdx.x * 4 + wave) * (kRows * most);
+    int2 *stage = reinterpret_cast<int2 *>(lds);             // (the table is done with; the sums too for all but the widest rows)
+    const bool staged = total * 8 <= kRows * slots * 4;
+    int2 *to = staged ? stage : found;
+    // ranks: eight of the row's columns at a time (behind the last one: kNoCol) against some of every lane's
+    auto place_columns = [&](auto lane_columns) {
+        constexpr int kQ = decltype(lane_columns)::value;
+        for (int q0 = l; q0 < longest_row + l; q0 += kQ * G) {
+            int32_t k[kQ];
+            int r[kQ];
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                k[q] = q0 + q * G < n ? keys[q0 + q * G] : kNoCol;
+                r[q] = off;
+            }
+            for (int i = 0; i < longest_row; i += 8) {
+                const int4 y = *reinterpret_cast<const int4 *>(keys + i), z = *reinterpret_cast<const int4 *>(keys + i + 4);
+#pragma unroll
+                for (int q = 0; q < kQ; ++q)
+                    r[q] += (y.x < k[q]) + (y.y < k[q]) + (y.z < k[q]) + (y.w < k[q]) + (z.x < k[q]) + (z.y < k[q]) +
+                            (z.z < k[q]) + (z.w < k[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < kQ; ++q)
+                if (q0 + q * G < n) to[r[q]] = make_int2(k[q], (int)__float_as_uint((float)sum[q0 + q * G]));
+        }
+    };
+    if (longest_row > 2 * G) place_columns(std::integral_constant<int, 4>{});
+    else place_columns(std::integral_constant<int, 2>{});
+    if (staged) {
+        wave_sync();
+        for (int i = lane; i < total; i += 64) found[(unsigned)i] = stage[i];
+    }
+    if (lane == 0) a.wave_total[blockIdx.x * 4 + wave] = total;
+    if (l == 0) {
+        // (rows of other kernels count as empty here)
+        if (row < a.rows && (small || ub == 0 || deg <= 0)) a.row_nnz[row] = n;
+        s_len[threadIdx.x / G] = (uint32_t)n;
+    }
+    __syncthreads();
+    const int64_t g = (int64_t)blockIdx.x * (256 / G / T) + threadIdx.x;
+    if (threadIdx.x < 256 / G / T && g * T < a.rows) {
+        uint32_t sum_len = 0;
+        for (int i = 0; i < T; ++i) sum_len += s_len[threadIdx.x * T + i];
+        a.group_len[g] = sum_len;
+    }
+}
+
+struct CopyArgs {
+    SmallShape shape;
+    int64_t rows, waves;
+    const int32_t *a_start, *ub;
+    const int2 *found;
+    const int32_t *wave_total;
     const int64_t *c_row_ptr;
     int32_t *c_col;
     float *c_val;
-    int stage;                           // entries of the output a wave keeps in LDS
     int64_t *d_scalars_to_clear;
 };
 
-// A group of G lanes per row of A, a lane per entry a_ik, which holds the next entry of its row of B: a step takes the
-// smallest column of the group and adds up the lanes that stand at it, one entry of C per step, in column order.  The
-// rows of B lie in LDS, G entries of each at a time, fetched by the lanes of the group side by side (64 lanes that each
-// fetch their own list cost the load path as many cycles as they are); a list that is longer is fetched on by its lane.
-// The sizing pass counts the steps; the multiplication pass collects the entries of its wave's rows, which are
-// neighbours in C, in LDS and writes them whole.
-template <int G, bool kFill>
-__global__ __launch_bounds__(256) void k_row_merge(const MergeArgs a, const SumArgs sums) {
-    constexpr int kRows = 64 / G;        // per wave
-    constexpr int kPitch = 65;           // (one more than the lanes: the lanes of a group write to different banks)
-    constexpr int32_t kMore = -1;        // behind the G entries in LDS of a list that goes on
-    using Item = typename std::conditional<kFill, int2, int32_t>::type;
-    extern __shared__ __align__(8) int2 lds_stage[];
-    __shared__ Item s_list[4][(G + 1) * kPitch];
-    __shared__ uint32_t s_len[256 / G];
-    if constexpr (!kFill)
-        if ((int)blockIdx.x >= a.blocks) {
-            sum_tile_rows(sums, (int)blockIdx.x - a.blocks, (int)gridDim.x - a.blocks);
-            return;
+// The entries of the small rows into C, a wave per wave of k_row_small: in one piece, since its rows follow one another
+// in C, unless a row of another kernel lies between them.
+__global__ __launch_bounds__(256) void k_small_copy(const CopyArgs a) {
+    if (a.d_scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) a.d_scalars_to_clear[threadIdx.x] = 0;
+    const int lane = lane_id();
+    const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (w >= a.waves) return;
+    const int rows = 64 / a.shape.lanes;
+    const int64_t r0 = w * rows, r1 = min(r0 + rows, a.rows);
+    const int total = uniform_load(a.wave_total + w);
+    if (total == 0) return;
+    const int64_t first = uniform_load(a.c_row_ptr + r0), last = uniform_load(a.c_row_ptr + r1);
+    const int2 *found = a.found + w * (int64_t)(rows * a.shape.products);
+    if (last - first == total) {
+        int32_t *col = a.c_col + first;
+        float *val = a.c_val + first;
+        for (int i = lane; i < total; i += 64) {
+            const int2 x = found[(unsigned)i];
+            col[(unsigned)i] = x.x;
+            val[(unsigned)i] = __uint_as_float((uint32_t)x.y);
         }
-    const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
-    const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
-    if constexpr (kFill)
-        if (a.d_scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) a.d_scalars_to_clear[threadIdx.x] = 0;
-    auto none = [] {
-        if constexpr (kFill) return make_int2(kNoCol, 0);
-        else return kNoCol;
-    };
-    auto column = [](const Item &x) -> int32_t {
-        if constexpr (kFill) return x.x;
-        else return x;
-    };
-    auto item = [&](int32_t k) {
-        if constexpr (kFill) return a.b_rec[k];
-        else return a.b_col[k];
-    };
-    int32_t p = 0, e = 0, deg = 0, ub = 0;
-    float av = 0.f;
-    bool merged = false;
-    if (row < a.rows) {
-        const int32_t s = a.a_start[row];
-        deg = a.a_start[row + 1] - s;
-        ub = a.ub[row];
-        merged = ub > 0 && deg > 0 && merged_row(deg, ub, G);
-        if (merged && l < deg) {
-            const int2 x = a.a_rec[s + l];
-            p = a.b_start[x.x];
-            e = a.b_start[x.x + 1];
-            av = __uint_as_float((uint32_t)x.y);
-        }
+        return;
     }
-    Item *mine = &s_list[wave][lane];
-    {
-        // (all requested before any is used, and without branches, which the waits could not see through)
-        Item x[G];
-        bool there[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-            const int32_t k = __shfl(p, i, G) + l;
-            there[i] = k < __shfl(e, i, G);
-            x[i] = item(there[i] ? k : 0);
+    int from = 0;
+    for (int64_t r = r0; r < r1; ++r) {
+        const int32_t deg = uniform_load(a.a_start + r + 1) - uniform_load(a.a_start + r), ub = uniform_load(a.ub + r);
+        if (deg <= 0 || ub <= 0 || !small_row(deg, ub, a.shape.lanes, a.shape.products)) continue;
+        const int64_t to = uniform_load(a.c_row_ptr + r);
+        const int n = min((int)(uniform_load(a.c_row_ptr + r + 1) - to), total - from);
+        for (int i = lane; i < n; i += 64) {
+            const int2 x = found[(unsigned)(from + i)];
+            a.c_col[to + i] = x.x;
+            a.c_val[to + i] = __uint_as_float((uint32_t)x.y);
         }
-#pragma unroll
-        for (int i = 0; i < G; ++i) s_list[wave][l * kPitch + (lane - l) + i] = there[i] ? x[i] : none();
-        Item end = none();
-        if (e - p > G) {
-            if constexpr (kFill) end.x = kMore;
-            else end = kMore;
-        }
-        mine[G * kPitch] = end;
-        p += G;
-    }
-    wave_sync();
-    Item head = *mine;
-    const Item *at = mine;
-    auto advance = [&] {
-        at += kPitch;
-        head = *at;
-    };
-    auto refill = [&] {                  // lanes whose list goes on behind the G entries they had
-        if (column(head) < 0) {
-            Item x[G];
-#pragma unroll
-            for (int j = 0; j < G; ++j) x[j] = item(min(p + j, max(e - 1, 0)));
-#pragma unroll
-            for (int j = 0; j < G; ++j) mine[j * kPitch] = p + j < e ? x[j] : none();
-            p += G;
-            Item end = none();
-            if (e - p > 0) {
-                if constexpr (kFill) end.x = kMore;
-                else end = kMore;
-            }
-            mine[G * kPitch] = end;
-            at = mine;
-            head = *at;
-        }
-    };
-    if constexpr (!kFill) {
-        int count = 0;
-        while (true) {
-            const int m = lanes_min<G>(head);
-            if (!__any(m != kNoCol)) break;
-            if (m != kNoCol) {
-                ++count;
-                if (head == m) advance();
-            }
-            if (__any(head < 0)) refill();
-        }
-        if (l == 0) {
-            // (rows of other kernels count as empty here)
-            if (row < a.rows && (merged || ub == 0 || deg <= 0)) a.row_nnz[row] = count;
-            s_len[threadIdx.x / G] = (uint32_t)count;
-        }
-        __syncthreads();
-        const int64_t g = (int64_t)blockIdx.x * (256 / G / T) + threadIdx.x;
-        if (threadIdx.x < 256 / G / T && g * T < a.rows) {
-            uint32_t sum = 0;
-            for (int i = 0; i < T; ++i) sum += s_len[threadIdx.x * T + i];
-            a.group_len[g] = sum;
-        }
-    } else {
-        int64_t first = 0;
-        int n = 0;
-        if (row < a.rows) {
-            first = a.c_row_ptr[row];
-            if (merged) n = (int)(a.c_row_ptr[row + 1] - first);
-        }
-        // where the row's entries lie among those of the wave
-        const uint32_t inc = wave_inclusive_scan(l == 0 ? (uint32_t)n : 0u);
-        const int total = __builtin_amdgcn_readlane((int)inc, 63), off = (int)inc - n;
-        const int steps = wave_max(n);
-        const bool staged = total <= a.stage;
-        int2 *stage = lds_stage + wave * a.stage, *to = stage + off;
-        for (int t = 0; t < steps; ++t) {
-            const int m = lanes_min<G>(head.x);
-            const bool here = head.x == m && m != kNoCol;
-            const float sum = lanes_sum<G>(here ? av * __uint_as_float((uint32_t)head.y) : 0.f);
-            if (l == 0 && t < n) {
-                if (staged) {
-                    to[t] = make_int2(m, (int)__float_as_uint(sum));
-                } else {
-                    a.c_col[first + t] = m;
-                    a.c_val[first + t] = sum;
-                }
-            }
-            if (here) advance();
-            if (__any(head.x < 0)) refill();
-        }
-        if (!staged || total == 0) return;
-        wave_sync();
-        // the wave's rows follow one another in C unless a row of another kernel lies between them
-        const int64_t wave_first = __shfl(first, 0, 64);
-        if (!__any(n > 0 && first - wave_first != off)) {
-            int32_t *col = a.c_col + wave_first;
-            float *val = a.c_val + wave_first;
-            for (int j = lane; j < total; j += 64) {
-                const int2 x = stage[j];
-                col[(unsigned)j] = x.x;
-                val[(unsigned)j] = __uint_as_float((uint32_t)x.y);
-            }
-        } else {
-            for (int j = l; j < n; j += G) {
-                const int2 x = stage[off + j];
-                a.c_col[first + j] = x.x;
-                a.c_val[first + j] = __uint_as_float((uint32_t)x.y);
-            }
-        }
+        from += n;
     }
 }
 
@@ -923,12 +951,6 @@ struct FillArgs {
 // bits (|p * 2^k| < 2^51).
 constexpr int kSpanColumns = 1 << 16;    // the elements of B hold 16 bits of the column
 
-// A value that is the same for the whole wave and that no kernel running now writes, through the scalar cache.
-template <typename X>
-__device__ __forceinline__ X uniform_load(const X *p) {
-    return *(const __attribute__((address_space(4))) X *)(uintptr_t)p;
-}
-
 template <typename Acc, int kCap, int kThreads>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThreads == 64 ? 1 : 8, 8))) void k_heavy_fill(const FillArgs a) {
     constexpr int kWaves = kThreads / 64, kWords = kSpanColumns / 32;
@@ -1098,7 +1120,8 @@ struct LeftOperand {
     int32_t *ub, *rows_of;
     unsigned long long *products;
     const tsp_csr *B;
-    int merge_lanes, windows;
+    SmallShape shape;
+    int windows;
     int32_t *heavy;
     int4 *tasks;
     int64_t heavy_cap, task_cap;
@@ -1124,7 +1147,8 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
             a.b_row_ptr = left->B->row_ptr;
             a.b_is_i64 = left->B->row_ptr_type == TSP_I64;
             a.b_rows = left->B->rows;
-            a.merge_lanes = left->merge_lanes;
+            a.small_lanes = left->shape.lanes;
+            a.small_products = left->shape.products;
             a.windows = left->windows;
             a.heavy = left->heavy;
             a.tasks = left->tasks;
@@ -1181,8 +1205,27 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     const bool known = std::equal(sizes, sizes + 6, hint.sizes);
     if (known && hint.tiles) return TSP_OK;
 
+    if (A->nnz >= (1 << 28) || B->nnz >= (1 << 28)) return TSP_OK;      // (32-bit byte offsets into 8-byte records)
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
-    const int merge_lanes = A->nnz <= 8 * A->rows ? 8 : 16;
+    // Small rows: 8 lanes where the mean row of A has no more entries, else 16; for a row of B as many as its mean has
+    // entries; a table of the row that is three quarters full at most, with a margin over the mean number of products, 256
+    // slots at most
+    SmallShape shape{A->nnz <= 8 * A->rows ? 8 : 16, 1, 32, 24};
+    {
+        const double list = (double)B->nnz / (double)std::max<int64_t>(B->rows, 1), mean = (double)A->nnz / (double)A->rows * list;
+        while (shape.slots < 256 && shape.slots * 3 / 4 < 1.25 * mean) shape.slots *= 2;
+        shape.products = shape.slots * 3 / 4;
+        if (shape.slots > 128) shape.lanes = 16;             // (eight rows of a wave would not fit LDS four times)
+        while (shape.list_lanes < shape.lanes && shape.list_lanes < list) shape.list_lanes *= 2;
+    }
+    // (16 GiB for the entries of the small rows at most: up to 89 million rows)
+    auto found_entries = [&] { return ((A->rows * shape.lanes + 255) / 256) * 256 / shape.lanes * shape.products; };
+    while (shape.slots > 32 && found_entries() > kFoundEntries) {
+        shape.slots /= 2;
+        shape.products = shape.slots * 3 / 4;
+    }
+    if (found_entries() > kFoundEntries) return TSP_OK;
+    const int64_t small_waves = ((A->rows * shape.lanes + 255) / 256) * 4;
     const int shift = B->cols <= 2048 ? 11 : 12;
     const int windows = (int)((B->cols + (1 << shift) - 1) >> shift);
     // heavy rows: the table of windows within 4 GiB, the arrays of B within the 32-bit byte offsets of stream_pieces
@@ -1206,7 +1249,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     left.rows_of = ws.get<int32_t>((size_t)a_ntr);
     left.products = ws.get<unsigned long long>((size_t)a_ntr);
     left.B = B;
-    left.merge_lanes = merge_lanes;
+    left.shape = shape;
     left.windows = windows;
     unsigned long long *partial = ws.get<unsigned long long>((size_t)kPlanBlocks * kPlanSums);
     // (tasks of a product not seen before: one per heavy row and some more; where that is too few the lists are made again)
@@ -1216,6 +1259,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     left.tasks = ws.get<int4>((size_t)std::max<int64_t>(left.task_cap, 1));
     int32_t *row_nnz = ws.get<int32_t>((size_t)A->rows + 1);
     uint32_t *group_len = ws.get<uint32_t>((size_t)chunks * kChunkTileRows);
+    int2 *found = nullptr;
+    int32_t *wave_total = nullptr;
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
 
     phase_begin(ctx, TSP_PHASE_CONVERT, s);
@@ -1294,6 +1339,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
 
     phase_begin(ctx, TSP_PHASE_SYMBOLIC, s);
     row_ptr = ws.get<int64_t>((size_t)A->rows + 1);
+    found = ws.get<int2>((size_t)found_entries());
+    wave_total = ws.get<int32_t>((size_t)small_waves);
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
     uint32_t *pack = nullptr, *offset = nullptr, *bits = nullptr;
     int64_t bit_rows = 0;
@@ -1305,18 +1352,21 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     };
     int32_t *table = nullptr, *words = nullptr;
     uint2 *word = nullptr;
-    MergeArgs m{};
+    SmallArgs m{};
+    m.shape = shape;
     m.rows = A->rows;
     m.a_start = ma.start;
     m.b_start = mb.start;
     m.ub = left.ub;
     m.a_rec = ma.rec;
     m.b_rec = mb.rec;
-    m.b_col = B->col_idx;
+    m.wave_bytes = (int)shape.wave_bytes();
+    m.found = found;
+    m.wave_total = wave_total;
     m.row_nnz = row_nnz;
     m.group_len = group_len;
-    const unsigned merge_blocks = (unsigned)((A->rows * merge_lanes + 255) / 256);
-    m.blocks = (int)merge_blocks;
+    const unsigned small_blocks = (unsigned)(small_waves / 4);
+    m.blocks = (int)small_blocks;
     auto size_rows = [&](bool again) {
         if (again || n_tasks > left.task_cap || n_heavy > left.heavy_cap) {
             // the lists did not fit: make them again, as large as they have to be
@@ -1344,8 +1394,9 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
         }
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
-        auto merge = merge_lanes == 8 ? k_row_merge<8, false> : k_row_merge<16, false>;
-        hipLaunchKernelGGL(merge, dim3(merge_blocks + (unsigned)sum_blocks), dim3(256), 0, s, m, sums);
+        auto kernel = shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true> : k_row_small<8, false>)
+                                       : (shape.narrow() ? k_row_small<16, true> : k_row_small<16, false>);
+        hipLaunchKernelGGL(kernel, dim3(small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums);
         if (n_heavy > 0) {
             PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, windows, shift};
             if (B->nnz > 16 * B->rows)
@@ -1399,19 +1450,11 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         // (nothing reads the scalar block any more: the last kernel clears it for the next call)
         int64_t *clear = ctx->d_scalars;
         bool cleared = false;
-        if (nnz > 0 && ctx->h_scalars[S_ROW_MERGED] > 0) {
-            m.c_row_ptr = row_ptr;
-            m.c_col = col;
-            m.c_val = val;
-            // entries of C a wave collects: twice the mean of its rows
-            const int64_t mean = nnz * (64 / merge_lanes) / A->rows;
-            m.stage = 128;
-            const int most = merge_lanes == 8 ? 1024 : 512;      // (with the lists within 64 KB of LDS)
-            while (m.stage < most && m.stage < 2 * mean) m.stage <<= 1;
-            m.d_scalars_to_clear = n_tasks > 0 ? nullptr : clear;
-            cleared = m.d_scalars_to_clear != nullptr;
-            auto merge = merge_lanes == 8 ? k_row_merge<8, true> : k_row_merge<16, true>;
-            hipLaunchKernelGGL(merge, dim3(merge_blocks), dim3(256), (size_t)m.stage * 32, s, m, sums);
+        if (nnz > 0 && ctx->h_scalars[S_ROW_SMALL] > 0) {
+            CopyArgs p{shape, A->rows, small_waves, ma.start, left.ub, found, wave_total, row_ptr, col, val,
+                       n_tasks > 0 ? nullptr : clear};
+            cleared = p.d_scalars_to_clear != nullptr;
+            hipLaunchKernelGGL(k_small_copy, dim3(small_blocks), dim3(256), 0, s, p);
         }
         if (n_tasks > 0) {
             FillArgs f{};

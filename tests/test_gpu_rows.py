@@ -50,8 +50,8 @@ def _check(h, tsp, oracle, A, B=None, by_rows=True, calls=2, **upload):
 
 # entries per row of A and of B either side of the bounds of merged rows (8 and 16 entries, 256 products), of the lanes
 # per segment in the sizing pass, and of one load per segment
-@pytest.mark.parametrize("a_row,b_row", [(1, 1), (3, 40), (8, 32), (8, 33), (9, 20), (16, 16), (16, 17), (17, 3), (40, 70), (5, 300)])
-def test_bounds_of_merged_rows(tsp, oracle, a_row, b_row):
+@pytest.mark.parametrize("a_row,b_row", [(1, 1), (8, 3), (16, 4), (16, 12), (3, 40), (8, 32), (8, 33), (9, 20), (16, 16), (16, 17), (17, 3), (40, 70), (5, 300)])
+def test_bounds_of_small_rows(tsp, oracle, a_row, b_row):
     rng = np.random.default_rng(100 * a_row + b_row)
     h = tsp.Handle()
     try:
