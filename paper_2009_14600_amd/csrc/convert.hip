@@ -7,8 +7,8 @@
 // and at most e1-e0 groups per form, so the stretches of different tile-rows cannot meet; the slots
 // in between stay unused (the arrays are sized by nnz and never touched there).
 //
-// A group of G threads (one wave, or one block for long tile-rows) owns one tile-row and visits its
-// entries in parallel:
+// A group of G threads (one wave; a block, and a kernel of its own, for long tile-rows) owns one tile-row and
+// visits its entries in parallel:
 //   1. every entry marks its tile column in an LDS bitmap that spans the tile-row's first to last
 //      tile column; the popcount is the number of tiles and the rank of a bit is the tile's
 //      position inside the tile-row, so the tiles come out sorted by column without a sort;
@@ -44,12 +44,7 @@ template <> struct ConvCfg<64> {                  // one wave per tile-row, four
     static constexpr int kStage = 0;              // element groups a window may assemble in LDS (0: none; this
                                                   // kernel lives on blocks per CU, and LDS decides how many)
 };
-template <> struct ConvCfg<128> {                 // one 128-thread block per tile-row
-    static constexpr int kWords = 1024;
-    static constexpr int kWindow = 64;
-    static constexpr int kStage = 512;
-};
-template <> struct ConvCfg<256> {                 // one 256-thread block per tile-row
+template <> struct ConvCfg<256> {                 // one 256-thread block per tile-row (of very many entries)
     static constexpr int kWords = 1024;           // span of 32768 tile columns
     static constexpr int kWindow = 128;
     static constexpr int kStage = 1024;
@@ -66,6 +61,8 @@ struct ConvArgs {
     int64_t rows, cols, nnz, tile_rows, tile_capacity, group_capacity;
     int forms, validate;
     int32_t *row_class;                 // per tile-row: which path takes it
+    int32_t *large;                     // tile-rows for k_convert_large
+    int large_slot;                     // ... and which scalar says how many
     int32_t *tile_row_ptr, *tile_row_end;  // per tile-row: first tile slot, one past the last
     // tile arrays
     int32_t *tile_col;
@@ -143,7 +140,7 @@ __device__ __forceinline__ uint32_t group_exclusive_scan(uint32_t *arr, int n, i
 // kConvCache: entries per thread kept in registers between the passes (tile-rows with more entries
 // than G*kConvCache read the CSR arrays again in every pass)
 template <int G, int kConvCache, typename RP, typename VT>
-__device__ __forceinline__ void convert_rows(const ConvArgs<RP, VT> &a) {
+__device__ __forceinline__ void convert_rows(const ConvArgs<RP, VT> &a, int64_t first_row) {
     constexpr int kWords = ConvCfg<G>::kWords, kWindow = ConvCfg<G>::kWindow, kGroups = conv_block_threads<G>() / G;
     constexpr int kStage = ConvCfg<G>::kStage;
     static_assert(kStage == 0 || kGroups == 1, "the staging area belongs to one tile-row");
@@ -159,7 +156,7 @@ __device__ __forceinline__ void convert_rows(const ConvArgs<RP, VT> &a) {
     uint32_t *s_bm = s_bm_all[gi], *s_pre = s_pre_all[gi], *s_mask = s_mask_all[gi];
     uint32_t *s_lm = s_lm_all[gi], *s_rm = s_rm_all[gi], *s_lo = s_lo_all[gi], *s_ro = s_ro_all[gi];
     int *s_red = s_red_all[gi];
-    const int64_t I = (int64_t)blockIdx.x * kGroups + gi;
+    const int64_t I = first_row + gi;
     if (I >= a.tile_rows) return;                 // whole group (G > 64: whole block)
     bool bad = false;
 
@@ -549,7 +546,7 @@ __device__ __forceinline__ void convert_rows(const ConvArgs<RP, VT> &a) {
 
 template <int G, int kConvCache, typename RP, typename VT>
 __global__ __launch_bounds__(conv_block_threads<G>()) void k_convert_rows(const ConvArgs<RP, VT> a) {
-    convert_rows<G, kConvCache, RP, VT>(a);
+    convert_rows<G, kConvCache, RP, VT>(a, (int64_t)blockIdx.x * (conv_block_threads<G>() / G));
 }
 // The same for short tile-rows (few entries per thread in registers): asking for seven waves per SIMD
 // (as many as the LDS of seven blocks per CU allows) makes the compiler fit 72 registers with three
@@ -557,14 +554,229 @@ __global__ __launch_bounds__(conv_block_threads<G>()) void k_convert_rows(const 
 template <int G, int kConvCache, typename RP, typename VT>
 __global__ __launch_bounds__(conv_block_threads<G>()) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_convert_rows_light(
     const ConvArgs<RP, VT> a) {
-    convert_rows<G, kConvCache, RP, VT>(a);
+    convert_rows<G, kConvCache, RP, VT>(a, (int64_t)blockIdx.x * (conv_block_threads<G>() / G));
 }
 
-// ... and for six entries per thread: four waves per SIMD cost the compiler seven registers.
-template <int G, int kConvCache, typename RP, typename VT>
-__global__ __launch_bounds__(conv_block_threads<G>()) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_convert_rows_mid(
-    const ConvArgs<RP, VT> a) {
-    convert_rows<G, kConvCache, RP, VT>(a);
+// ------------------------------------------------------------------------------------------------
+// Tile-rows of some hundred to 256*kCache entries: a block of four waves, entries in registers, and as few steps that
+// the whole block has to take together as the data allows (what such a kernel waits for is its barriers and loads, and
+// there have to be enough blocks on a CU to wait side by side).  The groups are put together in a dense image of a
+// window of tiles in LDS, where every entry has a place of its own without knowing the others, first the left form, then
+// the right one; empty groups are left out when the image is written.
+// Bound by vector instructions and LDS together (72 % and 70 % of the time on the stencil).  Measured against convert_rows
+// for such tile-rows (sixteen steps of the whole block, 127 registers): 27-point stencil with 3 unknowns on 48^3 nodes
+// 272 -> 152 us, 131072 rows of 4 half-full tiles 54 -> 45 us.  Asking for the next tile-row's entries ahead costs
+// registers, and with them more than it gives (213 and 48 us).
+// ------------------------------------------------------------------------------------------------
+constexpr int kBlockTiles = 32;          // tiles of a window
+constexpr int kBlockWords = 1024;        // bitmap words: tile columns may span 32768
+template <int kCache, typename RP, typename VT>
+__global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_block(const ConvArgs<RP, VT> a) {
+    __shared__ uint4 s_image[kBlockTiles * 32];
+    __shared__ uint2 s_bm[kBlockWords];                          // {tile columns, tiles before the word}
+    __shared__ uint32_t s_mask[kBlockTiles * 8];
+    __shared__ uint32_t s_lm[kBlockTiles + 1], s_rm[kBlockTiles + 1], s_lat[kBlockTiles], s_rat[kBlockTiles];
+    __shared__ int s_rp_all[kConvThreads / 64][20];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5, g = lane & 31;
+    int *const s_rp = s_rp_all[wave];
+    const int64_t I = blockIdx.x;
+    bool bad = false;
+    // every wave reads the row pointers for itself (clamped and made non-decreasing, as in convert_rows)
+    const int64_t row = min(I * T + min(lane, T), a.rows), raw = (int64_t)a.row_ptr[row];
+    int rp = (int)min(max(raw, (int64_t)0), a.nnz);
+    rp = max(rp, TSP_DPP(rp, rp, 0x111, 0xf, false));
+    rp = max(rp, TSP_DPP(rp, rp, 0x112, 0xf, false));
+    rp = max(rp, TSP_DPP(rp, rp, 0x114, 0xf, false));
+    rp = max(rp, TSP_DPP(rp, rp, 0x118, 0xf, false));
+    rp = max(rp, TSP_DPP(rp, rp, 0x142, 0xa, false));
+    if (lane <= T) {
+        s_rp[lane] = rp;
+        bad = raw != (int64_t)rp || (row == 0 && raw != 0) || (row == a.rows && raw != a.nnz);
+    }
+    const int e0 = __builtin_amdgcn_readlane(rp, 0), e1 = __builtin_amdgcn_readlane(rp, T);
+    const bool large = e1 - e0 > kConvThreads * kCache;
+    auto finish = [&](int ntiles, int row_class) {
+        if (tid == 0) {
+            a.tile_row_ptr[I] = e0;
+            a.tile_row_end[I] = e0 + ntiles;
+            a.row_class[I] = row_class;
+        }
+        if (a.validate && __any(bad) && lane == 0) a.d_scalars[S_INVALID] = 1;
+    };
+    if (e0 == e1 || large) {                                     // (the large ones are for convert_rows)
+        if (large && tid == 0) {
+            const unsigned long long at = atomicAdd(reinterpret_cast<unsigned long long *>(a.d_scalars + a.large_slot), 1ull);
+            if (at < (unsigned long long)a.tile_rows) a.large[at] = (int32_t)I;
+        }
+        finish(0, ROW_FAST);
+        return;
+    }
+    wave_sync();
+    // first and last tile column: of the ends of the rows
+    const int rp_next = s_rp[min(lane + 1, T)];
+    int c_reg[kCache], p_reg[kCache];
+    VT v_reg[kCache];
+    {
+        const bool some = lane < T && rp < rp_next;
+        const int lo = some ? a.col[rp] : INT_MAX, hi = some ? a.col[rp_next - 1] : INT_MIN;
+#pragma unroll
+        for (int k = 0; k < kCache; ++k) {
+            const int e = min(e0 + tid + k * kConvThreads, e1 - 1);
+            c_reg[k] = a.col[e];
+            p_reg[k] = a.col[max(e - 1, e0)];
+            v_reg[k] = a.val[e];
+        }
+        for (int i = tid; i < kBlockTiles * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
+        if (tid < kBlockTiles * 8) s_mask[tid] = 0;
+        rp = -wave_max(-lo) >> 4;                                // (from here on: first tile column)
+        bad |= lo < 0;
+        const int jmax = wave_max(hi) >> 4;
+        const int64_t span = (int64_t)jmax - rp + 1;
+        if (rp < 0 || span <= 0 || ((span + 31) >> 5) > kBlockWords) {
+            // the merge path takes this tile-row, see convert_rows
+            bad |= rp < 0 || jmax >= (a.cols + T - 1) / T;
+            finish(0, ROW_MERGE);
+            return;
+        }
+        for (int w = tid; w < (int)((span + 31) >> 5); w += kConvThreads) s_bm[w].x = 0;
+        __syncthreads();
+        // 1. tile columns: the first entry of a row in a tile marks it
+        const int jmin = rp;
+#pragma unroll
+        for (int k = 0; k < kCache; ++k) {
+            const int e = e0 + tid + k * kConvThreads;
+            int r = e >= s_rp[8] ? 8 : 0;
+            r += e >= s_rp[r + 4] ? 4 : 0;
+            r += e >= s_rp[r + 2] ? 2 : 0;
+            r += e >= s_rp[r + 1] ? 1 : 0;
+            const int c = c_reg[k];
+            const uint32_t j = (uint32_t)((c >> 4) - jmin);
+            const bool on = e < e1, first = e == s_rp[r];
+            if (on && j < (uint32_t)span && (first || (p_reg[k] >> 4) != (c >> 4))) atomicOr(&s_bm[j >> 5].x, 1u << (j & 31));
+            bad |= on && (c < 0 || c >= a.cols || j >= (uint32_t)span || (!first && c <= p_reg[k]));
+            // column in the tile-row's span (all ones: none), row
+            p_reg[k] = on && j < (uint32_t)span ? (int)(j << 8 | r << 4 | (c & 15)) : -1;
+        }
+        __syncthreads();
+        // 2. tiles before every word: each wave for itself, a stretch of words per lane
+        const int words = (int)((span + 31) >> 5), stretch = (words + 63) >> 6;
+        uint32_t mine = 0;
+        for (int i = 0; i < stretch; ++i) {
+            const int w = lane * stretch + i;
+            mine += w < words ? (uint32_t)__popc(s_bm[w].x) : 0u;
+        }
+        const uint32_t inc = wave_inclusive_scan(mine);
+        uint32_t before = inc - mine;
+        for (int i = 0; i < stretch; ++i) {
+            const int w = lane * stretch + i;
+            if (w >= words) break;
+            uint32_t left = s_bm[w].x;
+            s_bm[w].y = before;
+            if ((lane & (kConvThreads / 64 - 1)) == wave)        // tile columns, ascending
+                for (uint32_t t = before; left; left &= left - 1) a.tile_col[e0 + (int)t++] = jmin + w * 32 + __ffs(left) - 1;
+            before += (uint32_t)__popc(s_bm[w].x);
+        }
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < kCache; ++k) {
+            const uint32_t x = (uint32_t)p_reg[k], j = x >> 8;
+            const uint2 word = s_bm[x == 0xFFFFFFFFu ? 0 : j >> 5];
+            const uint32_t t = word.y + (uint32_t)__popc(word.x & ((1u << (j & 31)) - 1u));
+            p_reg[k] = x == 0xFFFFFFFFu ? -1 : (int)(t << 8 | (x & 255u));
+        }
+        rp = __builtin_amdgcn_readlane((int)inc, 63);                                        // (from here on: tiles)
+    }
+    const int ntiles = rp;
+    uint32_t lrun = (uint32_t)e0, rrun = (uint32_t)e0;
+    uint16_t *const image16 = reinterpret_cast<uint16_t *>(s_image);
+    const bool both = (a.forms & TSP_FORM_LEFT) && (a.forms & TSP_FORM_RIGHT);
+    for (int win0 = 0; win0 < ntiles; win0 += kBlockTiles) {
+        const int nw = min(kBlockTiles, ntiles - win0);
+        if (win0 > 0) {
+            __syncthreads();
+            for (int i = tid; i < nw * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
+            if (tid < kBlockTiles * 8) s_mask[tid] = 0;
+            __syncthreads();
+        }
+        // 3. bitmaps, and the values of the first form
+        auto place = [&](bool left, bool masks) {
+#pragma unroll
+            for (int k = 0; k < kCache; ++k) {
+                // bits of x: 7-4 row, 3-0 column; the place in the image has the upper bit of the one, the other, and the
+                // lower bits of the one
+                const uint32_t x = (uint32_t)p_reg[k] - (uint32_t)win0 * 256u;
+                if (x < (uint32_t)nw * 256u) {
+                    if (masks) atomicOr(&s_mask[x >> 5], 1u << (x & 31u));
+                    const uint32_t at = left ? (x & ~0xFFu) | (x & 8u) << 4 | (x >> 1 & 0x78u) | (x & 7u)
+                                             : (x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u);
+                    image16[at] = to_half_bits(v_reg[k]);
+                }
+            }
+        };
+        place((a.forms & TSP_FORM_LEFT) != 0, true);
+        __syncthreads();
+        // group masks: 32 lanes per tile, lane g group g
+        for (int t = wave * 2 + half; t < nw + half; t += kConvThreads / 32) {       // (both halves of a wave, or none)
+            const uint32_t rows2 = s_mask[t * 8 + ((g & 15) >> 1)];
+            const uint64_t l = __ballot((rows2 >> ((g & 1) * 16 + (g >> 4) * 8)) & 0xFFu);
+            const uint4 rows8 = *reinterpret_cast<const uint4 *>(&s_mask[t * 8 + (g >> 4) * 4]);
+            const uint32_t any = rows8.x | rows8.y | rows8.z | rows8.w;
+            const uint64_t r = __ballot(((any | any >> 16) >> (g & 15)) & 1u);
+            if (g == 0) {
+                s_lm[t] = (uint32_t)(l >> (half * 32));
+                s_rm[t] = (uint32_t)(r >> (half * 32));
+            }
+        }
+        __syncthreads();
+        // where the groups of every tile go: each wave for itself, lane = tile
+        const uint32_t lm = g < nw ? s_lm[g] : 0u, rm = g < nw ? s_rm[g] : 0u;
+        const uint32_t linc = wave_inclusive_scan(half ? 0u : (uint32_t)__popc(lm)), rinc = wave_inclusive_scan(half ? 0u : (uint32_t)__popc(rm));
+        const uint32_t lat = lrun + linc - (uint32_t)__popc(lm), rat = rrun + rinc - (uint32_t)__popc(rm);
+        if (wave == 0 && lane < nw) {
+            const int t = e0 + win0 + lane;
+            a.lmask[t] = lm;
+            a.rmask[t] = rm;
+            if (a.forms & TSP_FORM_LEFT) a.lhead[t] = make_uint2(lm, lat);
+            if (a.forms & TSP_FORM_RIGHT) a.rhead[t] = make_uint2(rm, rat);
+        }
+        if (wave == 1 && lane < nw * 2)
+            reinterpret_cast<uint4 *>(a.row_mask + (int64_t)(e0 + win0) * T)[lane] = reinterpret_cast<const uint4 *>(s_mask)[lane];
+        auto write = [&](uint4 *data, const uint32_t *masks, const uint32_t *tile_at) {
+            for (int t = wave * 2 + half; t < nw; t += kConvThreads / 32) {
+                const uint32_t mask = masks[t];
+                const uint32_t to = (uint32_t)tile_at[t] + (uint32_t)__popc(mask & ((1u << g) - 1u));
+                if ((mask >> g) & 1u) data[to] = s_image[t * 32 + g];
+            }
+        };
+        if (lane < kBlockTiles) {                                // (the same from every wave)
+            s_lat[lane] = lat;
+            s_rat[lane] = rat;
+        }
+        wave_sync();
+        if (a.forms & TSP_FORM_LEFT) write(a.ldata, s_lm, s_lat);
+        else write(a.rdata, s_rm, s_rat);
+        if (both) {
+            __syncthreads();
+            for (int i = tid; i < nw * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            place(false, false);
+            __syncthreads();
+            write(a.rdata, s_rm, s_rat);
+        }
+        lrun += (uint32_t)__builtin_amdgcn_readlane((int)linc, 63);
+        rrun += (uint32_t)__builtin_amdgcn_readlane((int)rinc, 63);
+    }
+    finish(ntiles, ROW_FAST);
+}
+
+// ... and the tile-rows of more entries, listed by it
+template <typename RP, typename VT>
+__global__ __launch_bounds__(kConvThreads) void k_convert_large(const ConvArgs<RP, VT> a) {
+    const int64_t n = min(a.d_scalars[a.large_slot], a.tile_rows);
+    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+        convert_rows<256, 8, RP, VT>(a, a.large[i]);
+        __syncthreads();
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -664,7 +876,7 @@ __global__ __launch_bounds__(kConvThreads) void k_convert_merge(const ConvArgs<R
 }
 
 template <typename RP, typename VT>
-static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, int32_t *row_class, hipStream_t s) {
+static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, int32_t *row_class, int32_t *large, hipStream_t s) {
     const int64_t ntr = t->tile_rows;
     ConvArgs<RP, VT> a{};
     a.row_ptr = static_cast<const RP *>(A->row_ptr);
@@ -679,6 +891,8 @@ static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, in
     a.forms = t->forms;
     a.validate = ctx->validate;
     a.row_class = row_class;
+    a.large = large;
+    a.large_slot = t->scalar_slot == S_TILES_B ? S_LARGE_B : S_LARGE_A;
     a.tile_row_ptr = t->tile_row_ptr;
     a.tile_row_end = t->tile_row_end;
     a.tile_col = t->tile_col;
@@ -691,36 +905,31 @@ static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, in
     a.rdata = t->rdata;
     a.d_scalars = ctx->d_scalars;
     // threads per tile-row from the mean number of entries per tile-row (the kernel is bound by
-    // dependent steps, so small groups, many in flight, win as long as the entries fit their registers);
+    // dependent steps, so small groups, many in flight, win as long as the entries fit their registers: a wave up to
+    // 512 entries, beyond that a block);
     // the merge path only when a tile-row could span more tile columns than the chosen bitmap holds
     // Registers per thread for the entries: the mean tile-row plus 15 %, so that most tile-rows stay in
     // registers without the kernel paying (in occupancy) for registers it does not use.
     const int64_t per_row = ntr > 0 ? A->nnz / ntr : 0, need = per_row + (3 * per_row + 19) / 20;
-    const int G = need <= 64 * 8 ? 64 : need <= 128 * 8 ? 128 : 256;
-    const int64_t want = (need + G - 1) / G;
-    const int cache = G == 64 ? (want <= 2 ? 2 : want <= 4 ? 4 : 8) : (want <= 6 ? 6 : 8);
-    const int64_t bitmap_span =
-        32ll * (G == 64 ? ConvCfg<64>::kWords : G == 128 ? ConvCfg<128>::kWords : ConvCfg<256>::kWords);
+    const bool blocks = need > 64 * 8;
+    const int64_t want = (need + (blocks ? kConvThreads : 64) - 1) / (blocks ? kConvThreads : 64);
+    const int64_t bitmap_span = 32ll * (blocks ? kBlockWords : ConvCfg<64>::kWords);
     // (tile-rows of a narrow matrix cannot exceed the bitmap, and then the merge kernel is not launched)
     const bool may_merge = t->tile_cols > bitmap_span;
-    const unsigned grid_fast = (unsigned)(G == 64 ? (ntr + 3) / 4 : ntr);
     const unsigned grid_merge = (unsigned)((ntr + kMergeGroupsPerBlock - 1) / kMergeGroupsPerBlock);
     if (ntr > 0) {
         KernelTimer kt(ctx, TSP_KERNEL_CONVERT, s);
-#define TSP_LAUNCH_ROWS(g, c, threads) \
-    hipLaunchKernelGGL((k_convert_rows<g, c, RP, VT>), dim3(grid_fast), dim3(threads), 0, s, a)
-        if (G == 64 && cache == 2)
-            hipLaunchKernelGGL((k_convert_rows_light<64, 2, RP, VT>), dim3(grid_fast), dim3(256), 0, s, a);
-        else if (G == 64 && cache == 4)
-            hipLaunchKernelGGL((k_convert_rows_light<64, 4, RP, VT>), dim3(grid_fast), dim3(256), 0, s, a);
-        else if (G == 64) TSP_LAUNCH_ROWS(64, 8, 256);
-        else if (G == 128 && cache == 6)
-            hipLaunchKernelGGL((k_convert_rows_mid<128, 6, RP, VT>), dim3(grid_fast), dim3(128), 0, s, a);
-        else if (G == 128) TSP_LAUNCH_ROWS(128, 8, 128);
-        else if (cache == 6)
-            hipLaunchKernelGGL((k_convert_rows_mid<256, 6, RP, VT>), dim3(grid_fast), dim3(256), 0, s, a);
-        else TSP_LAUNCH_ROWS(256, 8, 256);
-#undef TSP_LAUNCH_ROWS
+        const dim3 waves((unsigned)((ntr + 3) / 4)), rows((unsigned)ntr), threads(kConvThreads);
+        if (!blocks && want <= 2) hipLaunchKernelGGL((k_convert_rows_light<64, 2, RP, VT>), waves, threads, 0, s, a);
+        else if (!blocks && want <= 4) hipLaunchKernelGGL((k_convert_rows_light<64, 4, RP, VT>), waves, threads, 0, s, a);
+        else if (!blocks) hipLaunchKernelGGL((k_convert_rows<64, 8, RP, VT>), waves, threads, 0, s, a);
+        else {
+            const int cache = want <= 4 ? 4 : want <= 6 ? 6 : 8;
+            auto kernel = cache == 4 ? k_convert_block<4, RP, VT> : cache == 6 ? k_convert_block<6, RP, VT> : k_convert_block<8, RP, VT>;
+            hipLaunchKernelGGL(kernel, rows, threads, 0, s, a);
+            if (std::min(A->nnz, A->cols * T) > kConvThreads * cache)
+                hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min<int64_t>(ntr, 256)), threads, 0, s, a);
+        }
         if (may_merge)
             hipLaunchKernelGGL((k_convert_merge<RP, VT>), dim3(grid_merge), dim3(kConvThreads), 0, s, a);
     }
@@ -794,15 +1003,15 @@ int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_sl
         t->rdata = ctx_alloc_n<uint4>(ctx, (size_t)t->group_capacity, s);
         ok = ok && t->rhead && t->rdata;
     }
-    int32_t *scratch = ctx_alloc_n<int32_t>(ctx, (size_t)t->tile_rows + 1, s);   // path of every tile-row
+    int32_t *scratch = ctx_alloc_n<int32_t>(ctx, 2 * (size_t)t->tile_rows + 1, s);   // path of every tile-row; the large ones
     ok = ok && scratch;
     rc = ok ? TSP_OK : TSP_ERR_ALLOC_FAILED;
     if (!rc) {
         const bool i32 = A->row_ptr_type == TSP_I32, f16 = A->val_type == TSP_F16;
-        rc = i32 ? (f16 ? launch_convert<int32_t, uint16_t>(ctx, A, t, scratch, s)
-                        : launch_convert<int32_t, float>(ctx, A, t, scratch, s))
-                 : (f16 ? launch_convert<int64_t, uint16_t>(ctx, A, t, scratch, s)
-                        : launch_convert<int64_t, float>(ctx, A, t, scratch, s));
+        rc = i32 ? (f16 ? launch_convert<int32_t, uint16_t>(ctx, A, t, scratch, scratch + t->tile_rows, s)
+                        : launch_convert<int32_t, float>(ctx, A, t, scratch, scratch + t->tile_rows, s))
+                 : (f16 ? launch_convert<int64_t, uint16_t>(ctx, A, t, scratch, scratch + t->tile_rows, s)
+                        : launch_convert<int64_t, float>(ctx, A, t, scratch, scratch + t->tile_rows, s));
     }
     ctx_free(ctx, scratch, s);
     if (rc) {

@@ -1,0 +1,86 @@
+"""The conversion of tile-rows of hundreds to thousands of entries (k_convert_block and k_convert_large of csrc/convert.hip)
+against the CPU oracle's tiles, at the sizes where it can go wrong: entries either side of what the registers of a block
+hold, tiles either side of a window, spans either side of the bitmap, empty tile-rows.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+from paper_2009_14600_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tsp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2009_14600_amd import tsp as binding
+    binding.load_library()
+    return binding
+
+
+def _tile_rows(rng, cols, tiles, entries):
+    """Tile-row i: entries[i] entries spread over tiles[i] tiles (every tile holds one at least)."""
+    keys = []
+    for i, (t, n) in enumerate(zip(tiles, entries)):
+        if n == 0:
+            continue
+        col = np.sort(rng.choice(cols // 16, t, replace=False))
+        slots = rng.permutation(t * 256)
+        first = np.arange(t) * 256 + rng.integers(0, 256, t)
+        pick = np.unique(np.concatenate([first, slots[:n]]))[:max(n, t)]
+        tile, r, c = pick // 256, pick % 256 // 16, pick % 16
+        keys.append((i * 16 + r) * cols + col[tile] * 16 + c)
+    key = np.unique(np.concatenate(keys))
+    return inputs.from_coo(16 * len(tiles), cols, key // cols, key % cols, rng.uniform(-1, 1, key.size), "tile-rows")
+
+
+def _dense(view, form, t):
+    mask = int(view[f"{form}_group_mask"][t]) & 0xFFFFFFFF
+    off = int(view[f"{form}_group_off"][t]) & 0xFFFFFFFF
+    groups = [g for g in range(32) if (mask >> g) & 1]
+    rows = view[f"{form}_elements"][off * 8:(off + len(groups)) * 8].reshape(-1, 8)
+    out = np.zeros((16, 16), dtype=np.float16)
+    for g, x in zip(groups, rows):
+        if form == "left":
+            out[g % 16, 8 * (g // 16):8 * (g // 16) + 8] = x
+        else:
+            out[8 * (g // 16):8 * (g // 16) + 8, g % 16] = x
+    return out
+
+
+@pytest.mark.parametrize("cols,tiles,entries", [
+    (4096, (4, 5, 4), (1023, 1024, 1025)),
+    (4096, (31, 32, 33, 34), (1024, 1024, 1024, 1025)),
+    (4096, (8, 0, 8, 7), (1536, 0, 1537, 1500)),
+    (4096, (64, 65, 9), (2047, 2048, 2049)),
+    (4096, (256, 1, 200), (9000, 256, 700)),
+    (524288, (40, 40), (900, 1000)),
+    (600000, (40, 2, 40), (900, 300, 1000)),
+])
+@pytest.mark.parametrize("upload", [{}, {"value_dtype": "f32", "row_ptr_dtype": "i64"}])
+def test_tile_rows_of_many_entries(tsp, oracle, cols, tiles, entries, upload):
+    rng = np.random.default_rng(cols + sum(entries))
+    A = _tile_rows(rng, cols, tiles, entries)
+    print(f"convert: {A.rows}x{A.cols}, nnz {A.nnz}", flush=True)
+    bm = oracle.bitmap_format(A, 16)
+    h = tsp.Handle(validate=True)
+    try:
+        dA = tsp.to_device(A, **upload)
+        for forms in (tsp.FORM_LEFT, tsp.FORM_RIGHT, tsp.FORM_LEFT | tsp.FORM_RIGHT):
+            t = h.convert(dA, forms)
+            view = t.view()
+            slot = tsp.tile_indices(view).cpu().numpy()
+            v = {k: (x.cpu().numpy() if hasattr(x, "cpu") else x) for k, x in view.items()}
+            assert np.array_equal(v["tile_col"][slot], bm.tile_col)
+            assert np.array_equal(v["row_mask"].view(np.uint16).reshape(-1, 16)[slot], bm.row_mask.astype(np.uint16))
+            for i in range(slot.size):
+                occ = (bm.row_mask[i].astype(np.uint32)[:, None] >> np.arange(16)) & 1 == 1
+                want = np.zeros((16, 16), dtype=np.float16)
+                want[occ] = bm.elements[bm.index[i]:bm.index[i + 1]]
+                for form, bit in (("left", tsp.FORM_LEFT), ("right", tsp.FORM_RIGHT)):
+                    if forms & bit:
+                        assert np.array_equal(_dense(v, form, int(slot[i])).view(np.uint16), want.view(np.uint16)), (i, form)
+            t.free()
+    finally:
+        h.close()
