@@ -97,7 +97,7 @@ struct tsp_context {
     int64_t chain_capacity = 0;                    // slots allocated
     unsigned chain_epoch = 0;                      // tag of the last chained scan
     int64_t *d_scalars = nullptr;                  // device, kScalars entries
-    bool scalars_clean = false;                    // all zero: the previous tsp_spgemm left them so
+    bool scalars_clean = false;                    // all zero: the last kernel of the previous call left them so
     int64_t *h_scalars = nullptr;                  // pinned host mirror
     int64_t *h_scalars_dev = nullptr;              // the mirror's address on the device
     int64_t publish_tag = 0;                       // tag of the last publication asked for
@@ -150,12 +150,6 @@ void *ctx_alloc(tsp_context *ctx, size_t bytes, hipStream_t s);          // NULL
 void ctx_free(tsp_context *ctx, void *p, hipStream_t s);                 // back into the cache
 int hip_fail(tsp_context *ctx, hipError_t e);                            // records e, returns TSP_ERR_HIP
 int read_scalars(tsp_context *ctx, hipStream_t s);                       // d_scalars -> h_scalars, syncs
-// row_ptr[0..rows] = exclusive prefix of row_len[0..rows) in one launch, the total into S_C_NNZ of the
-// scalar block, which the launch also hands to the host (wait_published_scalars with ctx->publish_tag).
-// group_len[g] = sum of row_len over rows 16g..16g+15, padded with zeros to a multiple of four entries.
-// Returns false, without launching anything, for more rows than one launch covers.
-bool row_ptr_in_one_launch(tsp_context *ctx, const int32_t *row_len, int64_t rows, const uint32_t *group_len,
-                           int64_t *row_ptr, hipStream_t s);
 // Waits until the kernel that was given `tag` has put the scalar block into h_scalars (publish_scalars).
 int wait_published_scalars(tsp_context *ctx, int64_t tag, hipStream_t s);
 // Slots for a chained scan over `blocks` blocks and a fresh epoch tag; nullptr on failure.
@@ -256,7 +250,8 @@ inline int64_t xcd_chunked_grid(int64_t blocks, int chunk) {
 // no store has to be ordered behind another across the bus, and the kernel does not wait for a fence.
 constexpr int kPublishTagShift = 48;
 __host__ __device__ inline uint64_t publish_tag16(int64_t tag) { return (uint64_t)(tag % 65535) + 1u; }   // never 0
-__device__ __forceinline__ void publish_scalars(int64_t *d_scalars, int64_t *h_scalars_dev, int64_t tag) {
+// `clear`: the block is zeroed for the next call, whose kernels no kernel behind this one may disturb.
+__device__ __forceinline__ void publish_scalars(int64_t *d_scalars, int64_t *h_scalars_dev, int64_t tag, bool clear = false) {
     __threadfence();                               // this block's own plain stores to the scalar block
     __syncthreads();
     if (threadIdx.x < kScalars) {
@@ -265,6 +260,7 @@ __device__ __forceinline__ void publish_scalars(int64_t *d_scalars, int64_t *h_s
                                : (uint64_t)__hip_atomic_load(&d_scalars[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint64_t slot = (publish_tag16(tag) << kPublishTagShift) | (v & ((1ull << kPublishTagShift) - 1u));
         __hip_atomic_store(&h_scalars_dev[threadIdx.x], (int64_t)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (clear) d_scalars[threadIdx.x] = 0;
     }
 }
 

@@ -771,8 +771,8 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_bl
 
 // ... and the tile-rows of more entries, listed by it
 template <typename RP, typename VT>
-__global__ __launch_bounds__(kConvThreads) void k_convert_large(const ConvArgs<RP, VT> a) {
-    const int64_t n = min(a.d_scalars[a.large_slot], a.tile_rows);
+__global__ __launch_bounds__(kConvThreads) void k_convert_large(const ConvArgs<RP, VT> a, int64_t listed) {
+    const int64_t n = min(listed >= 0 ? listed : a.d_scalars[a.large_slot], a.tile_rows);
     for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
         convert_rows<256, 8, RP, VT>(a, a.large[i]);
         __syncthreads();
@@ -875,8 +875,13 @@ __global__ __launch_bounds__(kConvThreads) void k_convert_merge(const ConvArgs<R
     }
 }
 
+// Which kernels of a conversion: all of them, or first without the one for the large tile-rows, and then that one for the
+// number listed, which the host knows by then
+enum : int64_t { kAllRows = -1, kNotLargeRows = -2 };
+
 template <typename RP, typename VT>
-static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, int32_t *row_class, int32_t *large, hipStream_t s) {
+static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, int32_t *row_class, int32_t *large,
+                          int64_t which, hipStream_t s) {
     const int64_t ntr = t->tile_rows;
     ConvArgs<RP, VT> a{};
     a.row_ptr = static_cast<const RP *>(A->row_ptr);
@@ -920,15 +925,16 @@ static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, in
     if (ntr > 0) {
         KernelTimer kt(ctx, TSP_KERNEL_CONVERT, s);
         const dim3 waves((unsigned)((ntr + 3) / 4)), rows((unsigned)ntr), threads(kConvThreads);
-        if (!blocks && want <= 2) hipLaunchKernelGGL((k_convert_rows_light<64, 2, RP, VT>), waves, threads, 0, s, a);
+        if (which >= 0) hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min<int64_t>(which, 256)), threads, 0, s, a, which);
+        else if (!blocks && want <= 2) hipLaunchKernelGGL((k_convert_rows_light<64, 2, RP, VT>), waves, threads, 0, s, a);
         else if (!blocks && want <= 4) hipLaunchKernelGGL((k_convert_rows_light<64, 4, RP, VT>), waves, threads, 0, s, a);
         else if (!blocks) hipLaunchKernelGGL((k_convert_rows<64, 8, RP, VT>), waves, threads, 0, s, a);
         else {
             const int cache = want <= 4 ? 4 : want <= 6 ? 6 : 8;
             auto kernel = cache == 4 ? k_convert_block<4, RP, VT> : cache == 6 ? k_convert_block<6, RP, VT> : k_convert_block<8, RP, VT>;
             hipLaunchKernelGGL(kernel, rows, threads, 0, s, a);
-            if (std::min(A->nnz, A->cols * T) > kConvThreads * cache)
-                hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min<int64_t>(ntr, 256)), threads, 0, s, a);
+            if (which == kAllRows && std::min(A->nnz, A->cols * T) > kConvThreads * cache)
+                hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min<int64_t>(ntr, 256)), threads, 0, s, a, (int64_t)-1);
         }
         if (may_merge)
             hipLaunchKernelGGL((k_convert_merge<RP, VT>), dim3(grid_merge), dim3(kConvThreads), 0, s, a);
@@ -967,8 +973,18 @@ void tiles_release(tsp_context *ctx, tsp_tiles_s *t, hipStream_t s) {
 // Enqueues the whole conversion without synchronising: the tile arrays have one slot per stored entry
 // (see the top of the file); the number of tiles is the sum of tile_row_end - tile_row_ptr, which the
 // symbolic phase (or tsp_convert) adds up.
-int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out,
-                    hipStream_t s) {
+static int convert_kernels(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, int32_t *scratch, int64_t which, hipStream_t s) {
+    int32_t *row_class = scratch, *large = scratch + t->tile_rows;
+    const bool i32 = A->row_ptr_type == TSP_I32, f16 = A->val_type == TSP_F16;
+    return i32 ? (f16 ? launch_convert<int32_t, uint16_t>(ctx, A, t, row_class, large, which, s)
+                      : launch_convert<int32_t, float>(ctx, A, t, row_class, large, which, s))
+               : (f16 ? launch_convert<int64_t, uint16_t>(ctx, A, t, row_class, large, which, s)
+                      : launch_convert<int64_t, float>(ctx, A, t, row_class, large, which, s));
+}
+
+// keep_scratch: the kernel for the large tile-rows is left to the caller, who gets the scratch array
+static int convert_begin(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out,
+                         int32_t **keep_scratch, hipStream_t s) {
     *out = nullptr;
     int rc = check_csr_host(A);
     if (rc) return rc;
@@ -1006,14 +1022,9 @@ int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_sl
     int32_t *scratch = ctx_alloc_n<int32_t>(ctx, 2 * (size_t)t->tile_rows + 1, s);   // path of every tile-row; the large ones
     ok = ok && scratch;
     rc = ok ? TSP_OK : TSP_ERR_ALLOC_FAILED;
-    if (!rc) {
-        const bool i32 = A->row_ptr_type == TSP_I32, f16 = A->val_type == TSP_F16;
-        rc = i32 ? (f16 ? launch_convert<int32_t, uint16_t>(ctx, A, t, scratch, scratch + t->tile_rows, s)
-                        : launch_convert<int32_t, float>(ctx, A, t, scratch, scratch + t->tile_rows, s))
-                 : (f16 ? launch_convert<int64_t, uint16_t>(ctx, A, t, scratch, scratch + t->tile_rows, s)
-                        : launch_convert<int64_t, float>(ctx, A, t, scratch, scratch + t->tile_rows, s));
-    }
-    ctx_free(ctx, scratch, s);
+    if (!rc) rc = convert_kernels(ctx, A, t, scratch, keep_scratch ? kNotLargeRows : kAllRows, s);
+    if (!rc && keep_scratch) *keep_scratch = scratch;
+    else ctx_free(ctx, scratch, s);
     if (rc) {
         tiles_release(ctx, t, s);
         return rc;
@@ -1022,7 +1033,40 @@ int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_sl
     return TSP_OK;
 }
 
-// Number of tiles of a tile matrix (tsp_convert only; tsp_spgemm lets the symbolic phase add them up).
+int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out, hipStream_t s) {
+    return convert_begin(ctx, A, forms, scalar_slot, out, nullptr, s);
+}
+
+// Number of tiles of a tile matrix (tsp_convert only; tsp_spgemm lets the symbolic phase add them up), by one block, which
+// hands the scalar block to the host: up to kTotalRows tile-rows (a megabyte to read, 10 us).
+constexpr int64_t kTotalRows = 1 << 17;
+__global__ __launch_bounds__(1024) void k_tiles_total_publish(int64_t tile_rows, const int32_t *__restrict__ trp,
+                                                             const int32_t *__restrict__ tend, int64_t *d_scalars, int slot,
+                                                             int64_t *h_scalars_dev, int64_t publish_tag) {
+    __shared__ uint32_t part[1024 / 64];
+    uint32_t n = 0;
+    for (int64_t i0 = threadIdx.x; i0 < tile_rows; i0 += 8 * 1024) {
+        int32_t first[8], last[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = min(i0 + u * 1024, tile_rows - 1);
+            first[u] = trp[i];
+            last[u] = tend[i];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) n += i0 + u * 1024 < tile_rows ? (uint32_t)(last[u] - first[u]) : 0u;
+    }
+    n = wave_sum(n);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t all = 0;
+        for (int w = 0; w < 1024 / 64; ++w) all += part[w];
+        d_scalars[slot] = all;
+    }
+    publish_scalars(d_scalars, h_scalars_dev, publish_tag, true);
+}
+// ... of more tile-rows
 __global__ __launch_bounds__(256) void k_tiles_total(int64_t tile_rows, const int32_t *__restrict__ trp,
                                                     const int32_t *__restrict__ tend, int64_t *d_scalars, int slot) {
     __shared__ uint32_t part[4];
@@ -1050,19 +1094,35 @@ extern "C" int tsp_convert(tsp_handle ctx, const tsp_csr *A, int forms, tsp_tile
     if (!ctx || !out) return TSP_ERR_INVALID_ARG;
     *out = nullptr;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_clear_scalars, dim3(1), dim3(64), 0, s, ctx->d_scalars);
+    if (!ctx->scalars_clean) hipLaunchKernelGGL(k_clear_scalars, dim3(1), dim3(64), 0, s, ctx->d_scalars);
     ctx->scalars_clean = false;
     phase_begin(ctx, TSP_PHASE_CONVERT, s);
     tsp_tiles_s *t = nullptr;
-    int rc = convert_enqueue(ctx, A, forms, S_TILES_A, &t, s);
+    int32_t *scratch = nullptr;
+    int rc = convert_begin(ctx, A, forms, S_TILES_A, &t, &scratch, s);
     phase_end(ctx, TSP_PHASE_CONVERT, s);
     if (rc) return rc;
-    if (t->tile_rows > 0) {
-        const unsigned blocks = (unsigned)std::min<int64_t>(64, (t->tile_rows + 255) / 256);
-        hipLaunchKernelGGL(k_tiles_total, dim3(blocks), dim3(256), 0, s, t->tile_rows, t->tile_row_ptr, t->tile_row_end,
-                           ctx->d_scalars, (int)S_TILES_A);
+    auto total = [&] {                       // tiles and what else the kernels have to say
+        if (t->tile_rows > kTotalRows) {
+            hipLaunchKernelGGL(k_tiles_total, dim3(64), dim3(256), 0, s, t->tile_rows, t->tile_row_ptr, t->tile_row_end,
+                               ctx->d_scalars, (int)S_TILES_A);
+            return read_scalars(ctx, s);
+        }
+        hipLaunchKernelGGL(k_tiles_total_publish, dim3(1), dim3(1024), 0, s, t->tile_rows, t->tile_row_ptr, t->tile_row_end,
+                           ctx->d_scalars, (int)S_TILES_A, ctx->h_scalars_dev, ++ctx->publish_tag);
+        const hipError_t e = hipGetLastError();
+        ctx->scalars_clean = e == hipSuccess;
+        return e == hipSuccess ? wait_published_scalars(ctx, ctx->publish_tag, s) : hip_fail(ctx, e);
+    };
+    rc = total();
+    // tile-rows of more entries than a block holds are rare: their kernel is launched when the host knows of some
+    if (!rc && ctx->h_scalars[S_LARGE_A] > 0 && !ctx->h_scalars[S_INVALID]) {
+        const int64_t large = ctx->h_scalars[S_LARGE_A];
+        if (!ctx->scalars_clean) hipLaunchKernelGGL(k_clear_scalars, dim3(1), dim3(64), 0, s, ctx->d_scalars);
+        rc = convert_kernels(ctx, A, t, scratch, large, s);
+        if (!rc) rc = total();
     }
-    rc = read_scalars(ctx, s);
+    ctx_free(ctx, scratch, s);
     if (!rc && ctx->h_scalars[S_INVALID]) rc = TSP_ERR_NOT_CANONICAL;
     if (rc) {
         tiles_release(ctx, t, s);

@@ -159,7 +159,10 @@ __global__ __launch_bounds__(kNumThreads) void k_numeric(
     const int32_t *__restrict__ c_tile_col, const uint16_t *__restrict__ c_row_mask,
     const uint32_t *__restrict__ c_row_off, const int64_t *__restrict__ c_row_ptr, int32_t *__restrict__ c_col,
     float *__restrict__ c_val, int64_t *__restrict__ scalars_to_clear, const int2 *__restrict__ strip_desc,
-    const int32_t *__restrict__ strip_total, const int xcd_chunk) {
+    const int32_t *__restrict__ strip_total, const int xcd_chunk, int64_t *__restrict__ row_ptr_copy) {
+    if (row_ptr_copy)                                  // (a plan that is kept: C gets row pointers of its own)
+        for (int64_t i = (int64_t)blockIdx.x * kNumThreads + threadIdx.x; i <= c_rows; i += (int64_t)gridDim.x * kNumThreads)
+            row_ptr_copy[i] = c_row_ptr[i];
     if (scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) scalars_to_clear[threadIdx.x] = 0;
     static_assert(kTilesPerWave % kGroupTiles == 0 && kTilesPerWave < 64, "whole groups; offsets fit one wave load");
     // headers of the 64 task-list entries a wave is working on, one 16-byte record per entry; one
@@ -565,7 +568,8 @@ int numeric_enqueue(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s
     }
     phase_begin(ctx, TSP_PHASE_NUMERIC, s);
     hipError_t e = hipSuccess;
-    if (!last_of_call)
+    int64_t *const to_clear = last_of_call && !ctx->scalars_clean ? ctx->d_scalars : nullptr;
+    if (!last_of_call && P->c_tiles == 0)
         e = hipMemcpyAsync(row_ptr, P->c_row_ptr, sizeof(int64_t) * (size_t)(P->c_rows + 1), hipMemcpyDeviceToDevice, s);
     if (e == hipSuccess && P->c_tiles > 0) {
         KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
@@ -610,10 +614,10 @@ int numeric_enqueue(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s
                            (int32_t)P->c_tile_rows, P->c_tile_row_ptr, P->pair_off,
                            P->pair_ab, A->lhead, A->ldata, B->rhead, B->rdata,
                            P->c_tile_row, P->c_tile_col, P->c_row_mask, P->c_row_off, P->c_row_ptr, col, val,
-                           last_of_call ? ctx->d_scalars : nullptr,
+                           to_clear,
                            strips ? P->strip_desc : nullptr, strips ? P->strip_block_ptr + P->strip_entries : nullptr,
-                           xcd_chunk);
-        if (last_of_call && hipPeekAtLastError() == hipSuccess) ctx->scalars_clean = true;
+                           xcd_chunk, last_of_call ? nullptr : row_ptr);
+        if (to_clear && hipPeekAtLastError() == hipSuccess) ctx->scalars_clean = true;
         e = hipGetLastError();
     }
     phase_end(ctx, TSP_PHASE_NUMERIC, s);

@@ -1296,7 +1296,7 @@ __global__ __launch_bounds__(256) void k_count_masks(int64_t c_tiles, const int6
 __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row_nnz, int64_t c_rows,
                                                  const uint32_t *__restrict__ tile_row_entries, int64_t c_tile_rows,
                                                  int64_t *__restrict__ c_row_ptr, int64_t *d_scalars,
-                                                 int64_t *h_scalars_dev, int64_t publish_tag) {
+                                                 int64_t *h_scalars_dev, int64_t publish_tag, bool clear) {
     __shared__ uint64_t lds[256 / 64];
     constexpr int kItems = kChunkRows / 256;
     const bool last = blockIdx.x == gridDim.x - 1;
@@ -1351,7 +1351,7 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
             d_scalars[S_MAX_ROW_ENTRIES] = (int64_t)largest;
         }
         // no other block of this launch writes a scalar, and the kernels before it have finished
-        publish_scalars(d_scalars, h_scalars_dev, publish_tag);
+        publish_scalars(d_scalars, h_scalars_dev, publish_tag, clear);
     }
 }
 
@@ -1449,15 +1449,6 @@ __global__ __launch_bounds__(256) void k_row_offsets_wide(int64_t c_rows, const 
         c_row_off[c * T + r] = run;
         run += __popc(c_row_mask[c * T + r]);
     }
-}
-
-bool row_ptr_in_one_launch(tsp_context *ctx, const int32_t *row_len, int64_t rows, const uint32_t *group_len,
-                           int64_t *row_ptr, hipStream_t s) {
-    const int64_t groups = (rows + T - 1) / T, chunks = (groups + kChunkTileRows - 1) / kChunkTileRows;
-    if (chunks < 1 || chunks > kMaxChunks) return false;
-    hipLaunchKernelGGL(k_row_ptr, dim3((unsigned)chunks), dim3(256), 0, s, row_len, rows, group_len, groups, row_ptr,
-                       ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag);
-    return true;
 }
 
 // The paper's selection criteria (Section 6.1) for the left operand.
@@ -1810,9 +1801,10 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         KernelTimer kt(ctx, TSP_KERNEL_SCAN_ROWS, s);
         if (n_chunks > 0 && n_chunks <= kMaxChunks) {
             hipLaunchKernelGGL(k_row_ptr, dim3((unsigned)n_chunks), dim3(256), 0, s, row_nnz, P->c_rows, tile_row_entries,
-                               ntr, P->c_row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag);
+                               ntr, P->c_row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, true);
             SYM_CHECK(hipGetLastError());
             published = true;
+            ctx->scalars_clean = true;             // (nothing of this call uses the block any more)
         } else {
             rc = scan_exclusive_i32_to_i64(ctx, row_nnz, P->c_row_ptr, P->c_rows, ctx->d_scalars + S_C_NNZ,
                                            ctx->d_scalars + S_MAX_ROW_ENTRIES, tmp, s);
@@ -1850,7 +1842,8 @@ __global__ void k_clear_scalars_sym(int64_t *d_scalars) {
 extern "C" int tsp_symbolic(tsp_handle ctx, tsp_tiles A, tsp_tiles B, tsp_plan *out, void *stream) {
     if (!ctx || !A || !B || !out) return TSP_ERR_INVALID_ARG;
     if (A->ntiles < 0 || B->ntiles < 0) return TSP_ERR_INVALID_ARG;   // tiles must come from tsp_convert
-    hipLaunchKernelGGL(k_clear_scalars_sym, dim3(1), dim3(64), 0, (hipStream_t)stream, ctx->d_scalars);
+    if (!ctx->scalars_clean)
+        hipLaunchKernelGGL(k_clear_scalars_sym, dim3(1), dim3(64), 0, (hipStream_t)stream, ctx->d_scalars);
     ctx->scalars_clean = false;
     return symbolic_run(ctx, A, B, out, (hipStream_t)stream);
 }
