@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of libtsp.so (gfx950 only).
 #pragma once
 
+#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -57,6 +58,26 @@ struct LiveBlock {           // a block handed out: with canaries the caller's p
     bool guarded;
 };
 
+// Sizes of a task list and of its tile-rows
+struct ListSizes {
+    int64_t c_tiles = 0, pairs = 0, candidates = 0, max_row_c_tiles = 0, max_row_pairs = 0, max_row_words = 0, b_tiles = 0;
+    bool holds(const ListSizes &o) const {
+        return o.c_tiles <= c_tiles && o.pairs <= pairs && o.max_row_c_tiles <= max_row_c_tiles &&
+               o.max_row_pairs <= max_row_pairs && o.max_row_words <= max_row_words;
+    }
+    ListSizes with(const ListSizes &o) const {     // enough for both
+        return {std::max(c_tiles, o.c_tiles), std::max(pairs, o.pairs), std::max(candidates, o.candidates),
+                std::max(max_row_c_tiles, o.max_row_c_tiles), std::max(max_row_pairs, o.max_row_pairs),
+                std::max(max_row_words, o.max_row_words), std::max(b_tiles, o.b_tiles)};
+    }
+};
+// What symbolic_run goes by for a product of the sizes of an earlier one, see there
+struct ListHint {
+    int64_t sizes[5] = {-1, -1, -1, -1, -1};
+    bool usable = false;
+    ListSizes most;
+};
+
 // What the row kernels found for the last product (rowwise.hip), by the sizes of its operands: whether the tile kernels
 // suit it better, and how long its lists of work are.  Only the choice of kernels and the sizes of workspaces follow
 // from it; the numbers of the product at hand are checked against it.
@@ -91,6 +112,7 @@ struct tsp_context {
     int32_t *hint_order = nullptr;                 // ... and took its tile-rows in this order (heaviest first), or null
     int64_t hint_order_rows = 0;
     tsp::RowHint row_hint;
+    tsp::ListHint list_hint;
     int last_hip = 0;
     tsp_stats stats{};
     void *chain_slots = nullptr;                   // device, for the chained scans (chain.hpp)

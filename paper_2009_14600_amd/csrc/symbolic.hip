@@ -1004,7 +1004,8 @@ __global__ __launch_bounds__(kTeamLanes ? 64 : kSymThreads) void k_sym_emit_list
     int32_t *__restrict__ c_tile_row, int32_t *__restrict__ c_tile_col, int64_t *__restrict__ pair_off,
     int2 *__restrict__ pair_ab, const uint16_t *__restrict__ a_row_mask,
     const uint16_t *__restrict__ b_row_mask, uint16_t *__restrict__ c_row_mask, uint32_t *__restrict__ c_row_off,
-    int32_t *__restrict__ row_nnz, int64_t c_rows, int64_t *d_scalars, uint32_t *__restrict__ tile_row_entries) {
+    int32_t *__restrict__ row_nnz, int64_t c_rows, int64_t *d_scalars, uint32_t *__restrict__ tile_row_entries,
+    int64_t c_tiles_most, int64_t pairs_most) {
     extern __shared__ uint32_t lds_dyn[];
     using team = Team<kTeamLanes>;
     constexpr int kTeams = kTeamLanes ? 64 / kTeamLanes : 1;
@@ -1029,8 +1030,11 @@ __global__ __launch_bounds__(kTeamLanes ? 64 : kSymThreads) void k_sym_emit_list
     const int I = (int)blockIdx.x * kTeams + team_index, nthreads = team::size();
     if (I >= A.tile_rows) return;                    // (an odd number of tile-rows: the last team idles)
     const int c0 = c_tile_row_ptr[I], nC = c_tile_row_ptr[I + 1] - c0;
-    if (I == A.tile_rows - 1 && tid == 0) pair_off[c_tile_row_ptr[A.tile_rows]] = row_pair_ptr[A.tile_rows];
-    if (nC <= 0) {                                   // an empty tile-row of C: its 16 rows are empty
+    if (I == A.tile_rows - 1 && tid == 0 && c_tile_row_ptr[A.tile_rows] <= c_tiles_most)
+        pair_off[c_tile_row_ptr[A.tile_rows]] = row_pair_ptr[A.tile_rows];
+    // an empty tile-row of C: its 16 rows are empty; so is one that does not fit the arrays (the kernel then runs again)
+    if (nC <= 0 || nC > window || c0 + nC > c_tiles_most || row_words[I] > words_cap || row_pair_ptr[I + 1] > pairs_most ||
+        row_pair_ptr[I + 1] - row_pair_ptr[I] > list_cap) {
         if (kFuseMasks && tid < T && (int64_t)I * T + tid < c_rows) row_nnz[(int64_t)I * T + tid] = 0;
         if (kFuseMasks && tid == 0) tile_row_entries[I] = 0;
         return;
@@ -1483,9 +1487,9 @@ static bool strips_wanted(const tsp_context *ctx, const tsp_plan_s *, const tsp_
     return ctx->strip_order == 1 || ctx->strip_order >= 16;
 }
 
-static int lanes_per_a_tile(const tsp_tiles_s *B) {
+static int lanes_per_a_tile(int64_t tile_rows, int64_t ntiles) {
     // lanes that share one A tile stride over the tiles of one tile-row of B: match its mean length
-    const double mean = B->tile_rows > 0 && B->ntiles > 0 ? (double)B->ntiles / (double)B->tile_rows : 1.0;
+    const double mean = tile_rows > 0 && ntiles > 0 ? (double)ntiles / (double)tile_rows : 1.0;
     // (with the unrolled candidate loop a lane takes kSurvivorUnroll tiles per trip, so a quarter of
     // the lanes do: more A tiles are then in flight per block)
     int l = 4;
@@ -1563,7 +1567,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         while (lanes < 8 && lanes * 4 < mean_bound) lanes <<= 1;
         long_rows = mean_bound > 128.0;
         if (B->ntiles >= 0) {
-            lanes = lanes_per_a_tile(B);
+            lanes = lanes_per_a_tile(B->tile_rows, B->ntiles);
             long_rows = (double)B->ntiles > 8.0 * (double)B->tile_rows;
         }
     }
@@ -1641,27 +1645,64 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
                            ctx->d_scalars, ca, cb, ctx->h_scalars_dev, ++ctx->publish_tag);
         SYM_CHECK(hipGetLastError());
     }
-    if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);        // ---- sync 1: sizes of the task list
-    if (rc) return cleanup(rc);
+    // Sizes of the task list.  For operands of the sizes of earlier products of this handle that the list kernel has worked
+    // off, counting pass and all, its arrays get the largest sizes seen (and a sixteenth more) without waiting for the
+    // ones of this product: k_sym_emit_listed leaves out a tile-row that does not fit, and the numbers of the product at
+    // hand, checked below, then say that it has to run again with arrays that do.
     const int64_t *h = ctx->h_scalars;
-    if (h[S_INVALID]) return cleanup(TSP_ERR_NOT_CANONICAL);
-    if (h[S_UNSUPPORTED]) return cleanup(TSP_ERR_UNSUPPORTED);
-    if (h[S_INTERNAL]) return cleanup(TSP_ERR_HIP);
-    if (A->ntiles < 0) A->ntiles = h[A->scalar_slot];
-    if (B->ntiles < 0) B->ntiles = h[B->scalar_slot];
-    P->c_tiles = h[S_C_TILES];
-    P->pairs = h[S_PAIRS];
-    P->candidates = h[S_CANDIDATES];
-    P->max_row_c_tiles = h[S_MAX_ROW_C_TILES];
-    P->max_row_pairs = h[S_MAX_ROW_PAIRS];
-    if (P->c_tiles >= INT32_MAX) return cleanup(TSP_ERR_INDEX_OVERFLOW);
+    ListHint &hint = ctx->list_hint;
+    const int64_t hint_key[5] = {A->rows, A->nnz, B->rows, B->nnz, B->cols};
+    const bool key_known = std::equal(hint_key, hint_key + 5, hint.sizes);
+    bool hinted = key_known && hint.usable && ntr > 0 && n_chunks <= kMaxChunks && !strips_wanted(ctx, P, B);
+    bool ran_again = false, arrived = false;                          // the host has the numbers of the counting kernels
+    int64_t first_numbers[kScalars];               // ... and got them before the list kernel ran again
+    auto free_lists = [&]() {
+        for (auto p : {(void **)&P->c_tile_row, (void **)&P->c_tile_col, (void **)&P->pair_off, (void **)&P->pair_ab, (void **)&P->c_row_mask,
+                       (void **)&P->c_row_off, (void **)&P->c_row_ptr, (void **)&row_nnz, (void **)&tile_row_entries}) {
+            ctx_free(ctx, *p, s);
+            *p = nullptr;
+        }
+        listed = fused_masks = hinted = false;
+    };
+    ListSizes z;
+    auto sizes_arrived = [&]() {
+        arrived = true;
+        if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
+        if (h[S_UNSUPPORTED]) return (int)TSP_ERR_UNSUPPORTED;
+        if (h[S_INTERNAL]) return (int)TSP_ERR_HIP;
+        if (A->ntiles < 0) A->ntiles = h[A->scalar_slot];
+        if (B->ntiles < 0) B->ntiles = h[B->scalar_slot];
+        P->c_tiles = h[S_C_TILES];
+        P->pairs = h[S_PAIRS];
+        P->candidates = h[S_CANDIDATES];
+        P->max_row_c_tiles = h[S_MAX_ROW_C_TILES];
+        P->max_row_pairs = h[S_MAX_ROW_PAIRS];
+        return P->c_tiles >= INT32_MAX ? (int)TSP_ERR_INDEX_OVERFLOW : (int)TSP_OK;
+    };
+    auto true_sizes = [&]() {
+        return ListSizes{h[S_C_TILES], h[S_PAIRS], h[S_CANDIDATES], h[S_MAX_ROW_C_TILES], h[S_MAX_ROW_PAIRS], h[S_MAX_ROW_WORDS],
+                         B->ntiles};
+    };
+list_kernels:
+    if (!hinted) {
+        if (!arrived) {
+            if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);        // ---- sync 1: sizes of the task list
+            if (!rc) rc = sizes_arrived();
+            if (rc) return cleanup(rc);
+        }
+        z = true_sizes();
+    } else {
+        z = hint.most;
+        z.c_tiles += z.c_tiles / 16;
+        z.pairs += z.pairs / 16;
+    }
 
-    P->c_tile_row = ctx_alloc_n<int32_t>(ctx, (size_t)P->c_tiles, s);
-    P->c_tile_col = ctx_alloc_n<int32_t>(ctx, (size_t)P->c_tiles, s);
-    P->pair_off = ctx_alloc_n<int64_t>(ctx, (size_t)P->c_tiles + 1, s);
-    P->pair_ab = ctx_alloc_n<int2>(ctx, (size_t)P->pairs, s);
-    P->c_row_mask = ctx_alloc_n<uint16_t>(ctx, (size_t)P->c_tiles * T, s);
-    P->c_row_off = ctx_alloc_n<uint32_t>(ctx, (size_t)P->c_tiles * T, s);
+    P->c_tile_row = ctx_alloc_n<int32_t>(ctx, (size_t)z.c_tiles, s);
+    P->c_tile_col = ctx_alloc_n<int32_t>(ctx, (size_t)z.c_tiles, s);
+    P->pair_off = ctx_alloc_n<int64_t>(ctx, (size_t)z.c_tiles + 1, s);
+    P->pair_ab = ctx_alloc_n<int2>(ctx, (size_t)z.pairs, s);
+    P->c_row_mask = ctx_alloc_n<uint16_t>(ctx, (size_t)z.c_tiles * T, s);
+    P->c_row_off = ctx_alloc_n<uint32_t>(ctx, (size_t)z.c_tiles * T, s);
     // padded to whole tile-rows: the numeric pass reads the 16 row starts of a tile-row unconditionally
     P->c_row_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)P->c_tile_rows * T + T + 1, s);
     row_nnz = ctx_alloc_n<int32_t>(ctx, (size_t)P->c_rows + 1, s);
@@ -1671,30 +1712,30 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         return cleanup(TSP_ERR_ALLOC_FAILED);
 
     if (ntr > 0) {
-        const int words_cap = (int)(h[S_MAX_ROW_WORDS] > 0 ? h[S_MAX_ROW_WORDS] : 1);
-        int window = (int)(h[S_MAX_ROW_C_TILES] < kWindow ? h[S_MAX_ROW_C_TILES] : kWindow);
+        const int words_cap = (int)(z.max_row_words > 0 ? z.max_row_words : 1);
+        int window = (int)(z.max_row_c_tiles < kWindow ? z.max_row_c_tiles : kWindow);
         if (window < 1) window = 1;
         const size_t lds = (size_t)(2 * words_cap + 2 * window) * sizeof(uint32_t);
-        lanes = lanes_per_a_tile(B);
-        long_rows = (double)B->ntiles > 48.0 * (double)B->tile_rows;
+        lanes = lanes_per_a_tile(B->tile_rows, z.b_tiles);
+        long_rows = (double)z.b_tiles > 48.0 * (double)B->tile_rows;
         // tile-rows with more C tiles than the LDS window holds are worked off in several windows and keep,
         // in one word per tile of A, where the previous window ended in B's tile-row
-        if (h[S_MAX_ROW_C_TILES] > window) {
+        if (z.max_row_c_tiles > window) {
             cursor = ctx_alloc_n<int32_t>(ctx, 2 * (size_t)A->tile_capacity, s);    // and one per chunk of 32 of them
             if (!cursor) return cleanup(TSP_ERR_ALLOC_FAILED);
         }
         KernelTimer kt(ctx, TSP_KERNEL_SYM_EMIT, s);
-        const int64_t per_row = P->candidates / ntr;
+        const int64_t per_row = z.candidates / ntr;
         // (the fused counting pass of the list kernel wants more lanes than the enumeration does)
         const int threads = per_row <= 256 ? 64 : per_row <= 512 ? 128 : kSymThreads;
-        listed = h[S_MAX_ROW_PAIRS] <= kListCap && h[S_MAX_ROW_C_TILES] <= kListTiles;
+        listed = z.max_row_pairs <= kListCap && z.max_row_c_tiles <= kListTiles;
         // LDS of the list kernel per tile-row: bitmap and its prefix, per-tile words of the window, the list, and
         // the row masks of the window when it also runs the counting pass.  A launch may ask for 64 KB: a product
         // against a very wide B (a bitmap of thousands of words) takes one tile-row per block instead of two
         // per wave, and the general kernel when even that does not fit.
         constexpr size_t kLdsLimit = 64 * 1024;
         constexpr int kTeamsPerWave = 64 / kListTeamLanes;
-        const int list_cap = (int)std::max<int64_t>(h[S_MAX_ROW_PAIRS], 1);
+        const int list_cap = (int)std::max<int64_t>(z.max_row_pairs, 1);
         int team_words = 0;
         bool halves = false;
         if (listed) {
@@ -1706,6 +1747,10 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
                 listed = false;
                 fused_masks = false;
             }
+        }
+        if (hinted && !fused_masks) {              // (the largest sizes seen belong to different products)
+            free_lists();
+            goto list_kernels;
         }
         ctx->hint_general = !listed;
         // (the order of the previous product goes; the general branch below may keep a new one)
@@ -1727,12 +1772,12 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
                                row_words, P->c_tile_row_ptr,
                                row_pair_ptr, P->c_tile_row, P->c_tile_col, P->pair_off, P->pair_ab,
                                A->row_mask, B->row_mask, P->c_row_mask, P->c_row_off, row_nnz, P->c_rows,
-                               ctx->d_scalars, tile_row_entries);
+                               ctx->d_scalars, tile_row_entries, z.c_tiles, z.pairs);
         } else {
             // a few tile-rows far heavier than the rest (and enough work for two small launches to pay):
             // the heaviest go first
             const bool skewed =
-                ntr >= 1024 && P->candidates >= (int64_t)1 << 22 && h[S_MAX_ROW_PAIRS] > 8 * (P->pairs / ntr + 1);
+                ntr >= 1024 && z.candidates >= (int64_t)1 << 22 && z.max_row_pairs > 8 * (z.pairs / ntr + 1);
             if (ctx->work_order == 1 || (ctx->work_order == 0 && skewed)) {
                 order = ctx_alloc_n<int32_t>(ctx, (size_t)ntr, s);
                 order_hist = ctx_alloc_n<uint32_t>(ctx, 2 * kOrderBuckets, s);
@@ -1754,7 +1799,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
                                lds, s, ra, rb, lanes, words_cap, window, row_jmin, row_words,
                                P->c_tile_row_ptr,
                                row_pair_ptr, P->c_tile_row, P->c_tile_col, P->pair_off, P->pair_ab, cursor,
-                               A->tile_capacity, order, saved_bitmap, saved_cnt, saved_words, P->pairs);
+                               A->tile_capacity, order, saved_bitmap, saved_cnt, saved_words, z.pairs);
         }
         SYM_CHECK(hipGetLastError());
     } else {
@@ -1813,8 +1858,24 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     phase_end(ctx, TSP_PHASE_COUNT, s);
     if (!rc) rc = published ? wait_published_scalars(ctx, ctx->publish_tag, s) : read_scalars(ctx, s);   // ---- sync 2: nnz(C)
     if (rc) return cleanup(rc);
+    if (hinted) {
+        rc = sizes_arrived();
+        if (rc) return cleanup(rc);
+        if (!z.holds(true_sizes())) {              // another product of the same sizes, with more in it
+            std::copy(h, h + kScalars, first_numbers);
+            ran_again = true;
+            free_lists();
+            goto list_kernels;
+        }
+    }
+    if (ran_again)                                 // (the scalars were cleared after the first time)
+        for (int i = 0; i < kScalars; ++i)
+            if (i != S_C_NNZ && i != S_MAX_ROW_ENTRIES && i != S_UNSUPPORTED && i != S_INTERNAL) ctx->h_scalars[i] = first_numbers[i];
     if (ctx->h_scalars[S_UNSUPPORTED]) return cleanup(TSP_ERR_UNSUPPORTED);
     if (ctx->h_scalars[S_INTERNAL]) return cleanup(TSP_ERR_HIP);
+    std::copy(hint_key, hint_key + 5, hint.sizes);
+    hint.usable = listed && fused_masks;
+    hint.most = key_known ? hint.most.with(true_sizes()) : true_sizes();
     P->c_nnz = ctx->h_scalars[S_C_NNZ];
     P->max_row_entries = ctx->h_scalars[S_MAX_ROW_ENTRIES];
     ctx->stats.a_tiles = A->ntiles;

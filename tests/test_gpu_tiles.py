@@ -1,6 +1,7 @@
-"""The conversion of tile-rows of hundreds to thousands of entries (k_convert_block and k_convert_large of csrc/convert.hip)
-against the CPU oracle's tiles, at the sizes where it can go wrong: entries either side of what the registers of a block
-hold, tiles either side of a window, spans either side of the bitmap, empty tile-rows.  Needs an MI355X."""
+"""The tile kernels at the sizes where they can go wrong, against the CPU oracle: the conversion of tile-rows of hundreds to
+thousands of entries (k_convert_block and k_convert_large of csrc/convert.hip), with entries either side of what the
+registers of a block hold, tiles either side of a window, spans either side of the bitmap and empty tile-rows; and task
+lists in arrays sized after another product.  Needs an MI355X."""
 import numpy as np
 import pytest
 
@@ -82,5 +83,47 @@ def test_tile_rows_of_many_entries(tsp, oracle, cols, tiles, entries, upload):
                     if forms & bit:
                         assert np.array_equal(_dense(v, form, int(slot[i])).view(np.uint16), want.view(np.uint16)), (i, form)
             t.free()
+    finally:
+        h.close()
+
+
+def _full_tiles(rng, tile_rows, tile_cols_of):
+    """Four full tiles per tile-row, in the tile columns tile_cols_of(tile-row)."""
+    r, c = [], []
+    rr, cc = np.repeat(np.arange(16), 16), np.tile(np.arange(16), 16)
+    for i in range(tile_rows):
+        for j in tile_cols_of(i):
+            r.append(i * 16 + rr)
+            c.append(int(j) * 16 + cc)
+    r, c = np.concatenate(r), np.concatenate(c)
+    return inputs.from_coo(16 * tile_rows, 16 * tile_rows, r, c, rng.uniform(-1, 1, r.size), "full tiles")
+
+
+@pytest.mark.parametrize("phases", [False, True])
+def test_another_structure_of_the_same_sizes(tsp, oracle, phases):
+    """Products of the same rows and entries, with few and with many tiles in C: the second one does not fit the arrays
+    sized after the first, the third one does."""
+    n = 1025
+    rng = np.random.default_rng(5)
+    narrow = _full_tiles(rng, n, lambda i: (np.arange(4) + i // 4 * 4) % n)
+    wide = _full_tiles(rng, n, lambda i: rng.choice(n, 4, replace=False))
+    ref = [oracle.spgemm(A, A, threads=4) for A in (narrow, wide)]
+    h = tsp.Handle(validate=True)
+    try:
+        dev = [tsp.to_device(A) for A in (narrow, wide)]
+        for which in (0, 0, 1, 0, 1, 1):
+            if phases:
+                t = h.convert(dev[which])
+                plan = h.symbolic(t, t)
+                C = h.numeric(t, t, plan)
+                plan.free(), t.free()
+            else:
+                C = h.spgemm(dev[which], dev[which])
+                assert h.stats()["pairs"] == n * 16
+            row_ptr, col, val = C.to_host()
+            C.free()
+            want = ref[which]
+            assert np.array_equal(row_ptr, want.row_ptr) and np.array_equal(col, want.col)
+            assert np.all(np.abs(val.astype(np.float64) - want.val) <= 1e-5 * want.mag + 1e-7)
     finally:
         h.close()
