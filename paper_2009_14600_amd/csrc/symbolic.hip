@@ -993,6 +993,7 @@ __device__ __forceinline__ uint32_t boolean_row_product(uint32_t am, const uint4
 constexpr int kPairsPerTrip = 2;       // pairs a lane group of the fused counting pass takes per trip
 constexpr int kListCap = 1024;
 constexpr int kListTeamLanes = 32;     // lanes that share a tile-row where tile-rows have few candidates (16: slower)
+constexpr int64_t kResidentTileRows = 4096;   // blocks of 128 threads that are on the chip at once
 constexpr int kListTiles = 512;        // and at most this many C tiles per tile-row (their bitmaps sit in LDS)
 // kFuseMasks: also run the counting pass (worth it when there are enough tile-rows to fill the chip;
 // with few, long tile-rows the separate kernel, one lane group per C tile, has more parallelism).
@@ -1741,8 +1742,10 @@ list_kernels:
         if (listed) {
             fused_masks = ntr >= 1024;
             team_words = 2 * words_cap + 2 * window + 3 * list_cap + (fused_masks ? 8 * window : 0);
-            // tile-rows with few candidates: two per wave (see k_sym_count_half)
-            halves = fused_masks && threads == 64 && (size_t)team_words * kTeamsPerWave * sizeof(uint32_t) <= kLdsLimit;
+            // tile-rows with few candidates: two per wave (see k_sym_count_half), where there are more of them than the
+            // chip holds blocks of two waves (36 pairs per tile-row, 1536 tile-rows: 12 us with a block each, 18 us so; 16
+            // pairs, 8192 tile-rows: 26 and 20 us)
+            halves = fused_masks && threads == 64 && ntr > kResidentTileRows && (size_t)team_words * kTeamsPerWave * sizeof(uint32_t) <= kLdsLimit;
             if ((size_t)team_words * sizeof(uint32_t) > kLdsLimit) {
                 listed = false;
                 fused_masks = false;
