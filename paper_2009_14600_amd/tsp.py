@@ -210,7 +210,7 @@ class Handle:
         torch = _torch()
         self._torch = torch
         self._blocks = {}
-        self._typed = {}             # views of whole blocks, by address and type
+        self._typed = {}             # the last view of a block, by address and type
         self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
         def _alloc(_user, nbytes, _stream):
@@ -248,10 +248,10 @@ class Handle:
             views = self._typed.get(ptr)
             if views is None:
                 views = self._typed[ptr] = {}
-            whole = views.get(dtype)
-            if whole is None:
-                whole = views[dtype] = block.view(dtype)
-            return whole.narrow(0, 0, count)
+            view = views.get(dtype)
+            if view is None or view[0] != count:     # (the view handed out last, where it is the one wanted again)
+                view = views[dtype] = (count, block.view(dtype).narrow(0, 0, count))
+            return view[1]
         itemsize = dtype.itemsize
         for base, block in self._blocks.items():
             if base <= ptr and ptr + count * itemsize <= base + block.numel():
