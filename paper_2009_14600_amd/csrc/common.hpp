@@ -85,6 +85,9 @@ struct RowHint {
     int64_t sizes[6] = {-1, -1, -1, -1, -1, -1};   // rows and nnz of A, rows, nnz and cols of B, A is B
     bool tiles = false;
     int64_t heavy = 0, tasks = 0;
+    int64_t nnz = -1;                              // of C
+    bool small = false;                            // small rows among its rows
+    int sum = 0, scale = 0;                        // how the heavy rows are summed
 };
 
 }  // namespace tsp

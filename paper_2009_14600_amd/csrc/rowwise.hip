@@ -350,6 +350,39 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
 }
 __global__ __launch_bounds__(256) void k_row_sums(const SumArgs a) { sum_tile_rows(a, blockIdx.x, gridDim.x); }
 
+// The accumulator that is exact for the heavy rows: int32_t, long long or double; the integers are values times 2^-scale.
+struct FillKind {
+    enum Sum : int { kInt32, kInt64, kDouble } sum;
+    int scale;
+};
+// Bits of the operands' values as integers (multiples of their common granularity), and of a sum of as many products as
+// the longest heavy row of A has entries, if those are the integers of `scale`.
+__host__ __device__ inline bool fill_exact(FillKind k, int64_t range_a, int64_t range_b, int64_t longest) {
+    if (k.sum == FillKind::kDouble) return true;
+    const int ra = (int)range_a, rb = (int)range_b;
+    if (!ra || !rb || (ra >> 16) >= 1023 || (rb >> 16) >= 1023) return false;
+    const int product_bits = (ra >> 16) + (rb >> 16) - 512 - k.scale, granularity = 512 - (ra & 0xFFFF) - (rb & 0xFFFF);
+    int bits = product_bits;
+    for (int64_t n = 1; n < longest; n <<= 1) ++bits;
+    return granularity >= k.scale && (k.sum == FillKind::kInt32 ? bits <= 31 : bits <= 63 && product_bits <= 51);
+}
+inline FillKind fill_kind(const int64_t *h) {
+    const int scale = 512 - (int)(h[S_ROW_RANGE_A] & 0xFFFF) - (int)(h[S_ROW_RANGE_B] & 0xFFFF);
+    for (auto sum : {FillKind::kInt32, FillKind::kInt64})
+        if (fill_exact({sum, scale}, h[S_ROW_RANGE_A], h[S_ROW_RANGE_B], h[S_ROW_LONGEST])) return {sum, scale};
+    return {FillKind::kDouble, 0};
+}
+
+// What the kernels of the multiplication have been launched with before the host knows the sizes
+struct Expected {
+    int64_t nnz, heavy, tasks;
+    FillKind kind;
+    __host__ __device__ bool holds(const int64_t *scalars) const {
+        return !scalars[S_INVALID] && scalars[S_C_NNZ] <= nnz && scalars[S_ROW_HEAVY] <= heavy && scalars[S_ROW_TASKS] <= tasks &&
+               fill_exact(kind, scalars[S_ROW_RANGE_A], scalars[S_ROW_RANGE_B], scalars[S_ROW_LONGEST]);
+    }
+};
+
 struct FinishArgs {
     int64_t rows;                        // 0: only the sizes are wanted
     const int32_t *row_nnz;
@@ -359,6 +392,9 @@ struct FinishArgs {
     int partials, same;
     int64_t *d_scalars, *h_scalars_dev;
     int64_t publish_tag;
+    bool clear;                          // the scalar block, for the next call
+    Expected expected;
+    int32_t *live;                       // [2]: whether what is expected holds, and the number of tasks
 };
 
 // row_ptr of C from the row lengths: block b takes rows [2048 b, 2048 b + 2048), adds up the groups of 16 rows before
@@ -439,8 +475,12 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
         const unsigned long long lists = (unsigned long long)a.d_scalars[S_ROW_LISTS];
         a.d_scalars[S_ROW_HEAVY] = (int64_t)(lists >> 36);
         a.d_scalars[S_ROW_TASKS] = (int64_t)(lists & ((1ull << 36) - 1ull));
+        if (a.live) {
+            a.live[0] = a.expected.holds(a.d_scalars);
+            a.live[1] = (int32_t)a.d_scalars[S_ROW_TASKS];
+        }
     }
-    publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag);
+    publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, a.clear);
 }
 
 // ---- small rows -------------------------------------------------------------------------------------------------
@@ -645,13 +685,13 @@ struct CopyArgs {
     const int64_t *c_row_ptr;
     int32_t *c_col;
     float *c_val;
-    int64_t *d_scalars_to_clear;
+    const int32_t *live;                 // of k_row_finish, or null
 };
 
 // The entries of the small rows into C, a wave per wave of k_row_small: in one piece, since its rows follow one another
 // in C, unless a row of another kernel lies between them.
 __global__ __launch_bounds__(256) void k_small_copy(const CopyArgs a) {
-    if (a.d_scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) a.d_scalars_to_clear[threadIdx.x] = 0;
+    if (a.live && !uniform_load(a.live)) return;
     const int lane = lane_id();
     const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (w >= a.waves) return;
@@ -931,7 +971,7 @@ struct FillArgs {
     float *c_val;
     int window_shift;
     float p_scale, c_scale;              // integers from the products, values from the integer sums
-    int64_t *d_scalars_to_clear;
+    const int32_t *live;                 // of k_row_finish, or null
 };
 
 // A block per task: a row of C, or some of its windows, a step at a time: as many windows as hold at most kCap entries
@@ -963,9 +1003,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
         if constexpr (kThreads == 64) wave_sync();
         else __syncthreads();
     };
-    if (a.d_scalars_to_clear && blockIdx.x == 0 && threadIdx.x < kScalars) a.d_scalars_to_clear[threadIdx.x] = 0;
     const int64_t t = blockIdx.x;
-    if (t >= a.n_tasks) return;
+    if (a.live ? !uniform_load(a.live) || t >= uniform_load(a.live + 1) : t >= a.n_tasks) return;
     const int32_t row = uniform_load(&a.tasks[t].x), heavy = uniform_load(&a.tasks[t].y);
     int w = uniform_load(&a.tasks[t].z);
     const int w_end = uniform_load(&a.tasks[t].w);
@@ -1164,22 +1203,14 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
     else f16 ? run(int64_t{}, uint16_t{}) : run(int64_t{}, float{});
 }
 
-// Which accumulator is exact: the bits of the operands' values as integers (multiples of their common granularity), and
-// of a sum of as many products as the longest heavy row of A has entries.
-void launch_fill(FillArgs &f, const int64_t *h, hipStream_t s) {
-    const int ra = (int)h[S_ROW_RANGE_A], rb = (int)h[S_ROW_RANGE_B];
-    const int ea = (ra >> 16) - 256, ga = 256 - (ra & 0xFFFF), eb = (rb >> 16) - 256, gb = 256 - (rb & 0xFFFF);
-    const bool finite = (ra >> 16) < 1023 && (rb >> 16) < 1023;
-    int bits = ea - ga + eb - gb;
-    for (int64_t n = 1; n < h[S_ROW_LONGEST]; n <<= 1) ++bits;
+void launch_fill(FillArgs &f, FillKind kind, hipStream_t s) {
     auto launch = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)f.n_tasks), dim3(threads), 0, s, f);
     };
-    const int product_bits = ea - ga + eb - gb;
-    f.p_scale = finite ? std::ldexp(1.0f, -(ga + gb)) : 1.0f;
-    f.c_scale = finite ? std::ldexp(1.0f, ga + gb) : 1.0f;
-    if (finite && ra && rb && bits <= 31) launch(k_heavy_fill<int32_t, 4096, 512>, 512);
-    else if (finite && ra && rb && bits <= 63 && product_bits <= 51) launch(k_heavy_fill<long long, 4096, 512>, 512);
+    f.p_scale = std::ldexp(1.0f, -kind.scale);
+    f.c_scale = std::ldexp(1.0f, kind.scale);
+    if (kind.sum == FillKind::kInt32) launch(k_heavy_fill<int32_t, 4096, 512>, 512);
+    else if (kind.sum == FillKind::kInt64) launch(k_heavy_fill<long long, 4096, 512>, 512);
     else launch(k_heavy_fill<double, 4096, 64>, 64);
 }
 
@@ -1260,7 +1291,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     int32_t *row_nnz = ws.get<int32_t>((size_t)A->rows + 1);
     uint32_t *group_len = ws.get<uint32_t>((size_t)chunks * kChunkTileRows);
     int2 *found = nullptr;
-    int32_t *wave_total = nullptr;
+    int32_t *wave_total = nullptr, *live = nullptr;
+    Expected expected{};
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
 
     phase_begin(ctx, TSP_PHASE_CONVERT, s);
@@ -1311,12 +1343,16 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             const int rc = scan_exclusive_i32_to_i64(ctx, row_nnz, row_ptr, A->rows, ctx->d_scalars + S_C_NNZ, nullptr, tmp, s);
             if (rc) return rc;
         }
+        a.clear = row_ptr != nullptr;
+        a.expected = expected;
+        a.live = live;
         a.publish_tag = ++ctx->publish_tag;
         hipLaunchKernelGGL(k_row_finish, dim3(blocks), dim3(256), 0, s, a);
         TSP_HIP_CHECK(ctx, hipGetLastError());
         return (int)TSP_OK;
     };
     int64_t n_heavy = left.heavy_cap, n_tasks = left.task_cap;
+    FillKind kind{};
     auto sizes_known = [&]() {               // the host has the numbers of k_row_finish
         const int64_t *h = ctx->h_scalars;
         if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
@@ -1326,6 +1362,11 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
+        hint.small = h[S_ROW_SMALL] > 0;
+        hint.nnz = row_ptr ? h[S_C_NNZ] : -1;
+        kind = fill_kind(h);
+        hint.sum = kind.sum;
+        hint.scale = kind.scale;
         return (int)TSP_OK;
     };
     if (!known) {
@@ -1421,39 +1462,13 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         }
         return (int)TSP_OK;
     };
-    int rc = size_rows(false);
-    if (rc) return rc;
-    phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
-    phase_begin(ctx, TSP_PHASE_COUNT, s);
-    rc = finish(TSP_KERNEL_SCAN_ROWS);
-    phase_end(ctx, TSP_PHASE_COUNT, s);
-    if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);           // the wait that sizes C
-    if (rc) return rc;
-    const int64_t had_heavy = n_heavy, had_tasks = n_tasks;
-    rc = sizes_known();
-    if (rc) return rc;
-    if (n_heavy > had_heavy || n_tasks > had_tasks) {                // another matrix of the same sizes, with more work in it
-        rc = size_rows(true);
-        if (rc) return rc;
-        rc = finish(TSP_KERNEL_SCAN_ROWS);
-        if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);
-        if (rc) return rc;
-    }
-    const int64_t nnz = ctx->h_scalars[S_C_NNZ];
-    int32_t *col = ws.get<int32_t>((size_t)nnz);
-    float *val = ws.get<float>((size_t)nnz);
-    if (ws.failed) return TSP_ERR_ALLOC_FAILED;
-
-    phase_begin(ctx, TSP_PHASE_NUMERIC, s);
-    {
+    int32_t *col = nullptr;
+    float *val = nullptr;
+    auto multiply = [&](bool small, FillKind how) {
+        phase_begin(ctx, TSP_PHASE_NUMERIC, s);
         KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
-        // (nothing reads the scalar block any more: the last kernel clears it for the next call)
-        int64_t *clear = ctx->d_scalars;
-        bool cleared = false;
-        if (nnz > 0 && ctx->h_scalars[S_ROW_SMALL] > 0) {
-            CopyArgs p{shape, A->rows, small_waves, ma.start, left.ub, found, wave_total, row_ptr, col, val,
-                       n_tasks > 0 ? nullptr : clear};
-            cleared = p.d_scalars_to_clear != nullptr;
+        if (small) {
+            const CopyArgs p{shape, A->rows, small_waves, ma.start, left.ub, found, wave_total, row_ptr, col, val, live};
             hipLaunchKernelGGL(k_small_copy, dim3(small_blocks), dim3(256), 0, s, p);
         }
         if (n_tasks > 0) {
@@ -1472,8 +1487,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             f.c_row_ptr = row_ptr;
             f.c_col = col;
             f.c_val = val;
-            f.d_scalars_to_clear = clear;
-            cleared = clear != nullptr;
+            f.live = live;
             f.window_shift = shift;
             for (int64_t from = 0; from < n_heavy; from += bit_rows) {
                 f.heavy_from = (int)from;
@@ -1486,13 +1500,64 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
                     c.bits = bits;
                     count_heavy(f.heavy_to - f.heavy_from);
                 }
-                launch_fill(f, ctx->h_scalars, s);
+                launch_fill(f, how, s);
             }
         }
+        phase_end(ctx, TSP_PHASE_NUMERIC, s);
         TSP_HIP_CHECK(ctx, hipGetLastError());
-        ctx->scalars_clean = cleared;
+        return (int)TSP_OK;
+    };
+    int rc = size_rows(false);
+    if (rc) return rc;
+    phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
+    // A product of the sizes of the last one: the kernels of the multiplication follow at once, into arrays for as many
+    // entries as that one had and some more, and k_row_finish lets them run if this product fits; the GPU does not
+    // wait for the host to learn nnz(C) (8 us of 78 on a 512x512 mesh).  Otherwise they are launched again below.
+    const bool ahead = known && hint.nnz >= 0 && bit_rows == n_heavy;
+    int64_t room = 0;
+    if (ahead) {
+        room = hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20);
+        col = ws.get<int32_t>((size_t)room);
+        val = ws.get<float>((size_t)room);
+        live = ws.get<int32_t>(2);
+        if (ws.failed) return TSP_ERR_ALLOC_FAILED;
+        kind = FillKind{(FillKind::Sum)hint.sum, hint.scale};
+        expected = Expected{room, n_heavy, n_tasks, kind};
     }
-    phase_end(ctx, TSP_PHASE_NUMERIC, s);
+    const bool had_small = hint.small;
+    phase_begin(ctx, TSP_PHASE_COUNT, s);
+    rc = finish(TSP_KERNEL_SCAN_ROWS);
+    ctx->scalars_clean = !rc;                // (it has cleared the scalar block for the next call)
+    phase_end(ctx, TSP_PHASE_COUNT, s);
+    if (!rc && ahead) rc = multiply(had_small, kind);
+    if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);           // the wait that sizes C
+    if (rc) return rc;
+    const int64_t had_heavy = n_heavy, had_tasks = n_tasks, products = ctx->h_scalars[S_PRODUCTS];
+    rc = sizes_known();
+    if (rc) return rc;
+    const bool done = ahead && expected.holds(ctx->h_scalars) && (had_small || ctx->h_scalars[S_ROW_SMALL] == 0);
+    if (!done) {
+        live = nullptr;
+        if (n_heavy > had_heavy || n_tasks > had_tasks) {            // another matrix of the same sizes, with more work in it
+            ctx->scalars_clean = false;
+            rc = size_rows(true);
+            if (rc) return rc;
+            rc = finish(TSP_KERNEL_SCAN_ROWS);
+            ctx->scalars_clean = !rc;
+            if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);
+            if (rc) return rc;
+            ctx->h_scalars[S_PRODUCTS] = products;
+            hint.nnz = ctx->h_scalars[S_C_NNZ];
+        }
+        if (ctx->h_scalars[S_C_NNZ] > room || !ahead) {
+            col = ws.get<int32_t>((size_t)ctx->h_scalars[S_C_NNZ]);
+            val = ws.get<float>((size_t)ctx->h_scalars[S_C_NNZ]);
+            if (ws.failed) return TSP_ERR_ALLOC_FAILED;
+        }
+        if (ctx->h_scalars[S_C_NNZ] > 0) rc = multiply(ctx->h_scalars[S_ROW_SMALL] > 0, kind);
+        if (rc) return rc;
+    }
+    const int64_t nnz = ctx->h_scalars[S_C_NNZ];
     const int64_t *h = ctx->h_scalars;
     ctx->stats.a_tiles = h[S_TILES_A];
     ctx->stats.b_tiles = h[S_TILES_B];
