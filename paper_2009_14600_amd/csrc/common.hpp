@@ -42,6 +42,7 @@ enum Scalar {
     S_ROW_RANGE_A = 21,      // magnitude and granularity of the values (value_range)
     S_ROW_RANGE_B = 22,
     S_ROW_LONGEST = 23,      // entries of the longest heavy row of A
+    S_ROW_ARRIVED = 16,      // blocks of k_row_small that are done
     S_LARGE_A = 24,          // tile-rows of an operand whose entries do not fit the registers of k_convert_block
     S_LARGE_B = 25,
     S_PUBLISHED = 31,        // host mirror only: a slot without a value (publish_scalars tags every slot)

@@ -261,9 +261,23 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     if (lane == 0) a.rows_of[I] = min(longest, (1 << 26) - 1) * 32 + small;
 }
 
+// A store that a block of the same launch on another XCD can read (get_shared), past the L2 caches, which do not see each
+// other's; plain otherwise.
+template <typename X>
+__device__ __forceinline__ void put_for(bool shared, X *p, X v) {
+    if (shared) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+template <bool kShared, typename X>
+__device__ __forceinline__ X get_shared(const X *p) {
+    if constexpr (kShared) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
+}
+
 // What the operands are like, summed over their tile-rows.  The blocks leave their sums in `partial`; k_row_finish, which
-// runs after them, adds those up.  (Letting the block that finishes last do it takes a device-wide fence in every block,
-// which writes back its L2: 90 us instead of 8 on a 512^2 mesh.)
+// runs after them, adds those up, or for products of a few rows the block of k_row_small that finishes last.  (With many
+// blocks that takes too long: an addition per block to one counter is 9 ns, and device-wide fences write back the L2 caches:
+// 90 us instead of 8 on a 512^2 mesh.)
 struct SumArgs {
     int64_t a_tile_rows, b_tile_rows;
     const int32_t *a_start, *a_ntiles, *a_tile_col, *b_ntiles, *rows_of;
@@ -276,7 +290,8 @@ enum { kSumCandidates, kSumTilesA, kSumTilesB, kSumProducts, kSumSmall, kSumRang
 
 // Sixteen lanes per tile-row: tiles, candidate pairs (the tiles of B's tile-rows behind the tiles of A: the measure by
 // which tsp_spgemm chooses this path), products, value ranges.
-__device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int blocks) {
+// `shared`: another block of this launch reads the sums.
+__device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int blocks, bool shared = false) {
     __shared__ unsigned long long s_sum[kPlanSums], s_max[kPlanSums];
     const int lane = lane_id(), r = threadIdx.x & 15;
     if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = s_max[threadIdx.x] = 0;
@@ -346,7 +361,7 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
         s_sum[kSumLongest] = s_max[4];
     }
     __syncthreads();
-    if (threadIdx.x < kPlanSums) a.partial[threadIdx.x * kPlanBlocks + block] = s_sum[threadIdx.x];
+    if (threadIdx.x < kPlanSums) put_for(shared, &a.partial[threadIdx.x * kPlanBlocks + block], s_sum[threadIdx.x]);
 }
 __global__ __launch_bounds__(256) void k_row_sums(const SumArgs a) { sum_tile_rows(a, blockIdx.x, gridDim.x); }
 
@@ -399,22 +414,24 @@ struct FinishArgs {
 
 // row_ptr of C from the row lengths: block b takes rows [2048 b, 2048 b + 2048), adds up the groups of 16 rows before
 // them and scans its own.  The last block also adds up the sums over the tile-rows and hands all sizes to the host.
-__global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
+// kShared: other blocks of the same launch have left row_nnz and partial (put_for).
+template <bool kShared>
+__device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int blocks) {
     __shared__ uint64_t lds[256 / 64];
     __shared__ unsigned long long s_sum[kPlanSums], s_max[kPlanSums];
-    const bool last = blockIdx.x == gridDim.x - 1;
+    const bool last = block == blocks - 1;
     constexpr int kItems = kChunkRows / 256;
-    const int64_t base = (int64_t)blockIdx.x * kChunkRows + (int64_t)threadIdx.x * kItems;
+    const int64_t base = (int64_t)block * kChunkRows + (int64_t)threadIdx.x * kItems;
     int32_t x[kItems];
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) x[i] = base + i < a.rows ? a.row_nnz[base + i] : 0;
+    for (int i = 0; i < kItems; ++i) x[i] = base + i < a.rows ? get_shared<kShared>(a.row_nnz + base + i) : 0;
     if (last) {                          // two sums per wave
         const int lane = lane_id();
         for (int slot = (int)(threadIdx.x >> 6) * 2; slot < (int)(threadIdx.x >> 6) * 2 + 2; ++slot) {
             unsigned long long v[kPlanBlocks / 64], sum = 0;
 #pragma unroll
             for (int u = 0; u < kPlanBlocks / 64; ++u)
-                v[u] = u * 64 + lane < a.partials ? a.partial[slot * kPlanBlocks + u * 64 + lane] : 0ull;
+                v[u] = u * 64 + lane < a.partials ? get_shared<kShared>(a.partial + slot * kPlanBlocks + u * 64 + lane) : 0ull;
             if (slot == kSumRanges || slot == kSumLongest) {
                 int most[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -437,7 +454,7 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
     }
     uint64_t before = 0;
     const uint4 *groups4 = reinterpret_cast<const uint4 *>(a.group_len);
-    const int64_t quads = a.rows > 0 ? (int64_t)blockIdx.x * kChunkTileRows / 4 : 0;
+    const int64_t quads = a.rows > 0 ? (int64_t)block * kChunkTileRows / 4 : 0;
     for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 4 * 256) {
         uint4 g[4];
 #pragma unroll
@@ -482,6 +499,7 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
     }
     publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, a.clear);
 }
+__global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) { row_finish<false>(a, blockIdx.x, gridDim.x); }
 
 // ---- small rows -------------------------------------------------------------------------------------------------
 // Element i of an array of less than 4 GiB: the address is a scalar base and a 32-bit offset.
@@ -510,6 +528,7 @@ struct SmallArgs {
     int2 *found;                         // [waves][wave_rows * products] entries {column, value} of a wave's rows, in order
     int32_t *wave_total;                 // ... and how many
     int blocks;                          // of rows; the ones behind them sum (SumArgs)
+    int finish;                          // the last block does the work of k_row_finish (FinishArgs; rows of one chunk)
 };
 
 // A group of G lanes per row of A with at most G entries and shape.products intermediate products.  The rows of B behind
@@ -525,17 +544,13 @@ struct SmallArgs {
 // an entry and the fp32 sums form in the order of the entries of A.  Short rows of B (kNarrow): several at a time, added
 // with LDS atomics in fp64.
 template <int G, bool kNarrow>
-__global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums) {
+__device__ __forceinline__ void row_small(const SmallArgs &a) {
     constexpr int kRows = 64 / G;        // per wave
     constexpr int kAhead = kNarrow ? G / 2 : G;
     constexpr int32_t kFree = -1;
     using Sum = typename std::conditional<kNarrow, double, float>::type;
     extern __shared__ __align__(16) unsigned char small_lds[];
     __shared__ uint32_t s_len[256 / G];
-    if ((int)blockIdx.x >= a.blocks) {
-        sum_tile_rows(sums, (int)blockIdx.x - a.blocks, (int)gridDim.x - a.blocks);
-        return;
-    }
     const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
     const uint32_t row = blockIdx.x * (256 / G) + threadIdx.x / G;
     const int slots = a.shape.slots, most = a.shape.products;
@@ -664,7 +679,7 @@ __global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumA
     if (lane == 0) a.wave_total[blockIdx.x * 4 + wave] = total;
     if (l == 0) {
         // (rows of other kernels count as empty here)
-        if (row < a.rows && (small || ub == 0 || deg <= 0)) a.row_nnz[row] = n;
+        if (row < a.rows && (small || ub == 0 || deg <= 0)) put_for(a.finish, a.row_nnz + row, (int32_t)n);
         s_len[threadIdx.x / G] = (uint32_t)n;
     }
     __syncthreads();
@@ -674,6 +689,20 @@ __global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumA
         for (int i = 0; i < T; ++i) sum_len += s_len[threadIdx.x * T + i];
         a.group_len[g] = sum_len;
     }
+}
+
+template <int G, bool kNarrow>
+__global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin) {
+    __shared__ int s_last;
+    if ((int)blockIdx.x >= a.blocks) sum_tile_rows(sums, (int)blockIdx.x - a.blocks, (int)gridDim.x - a.blocks, a.finish);
+    else row_small<G, kNarrow>(a);
+    if (!a.finish) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left for the last block has arrived
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_last = atomicAdd(reinterpret_cast<unsigned long long *>(fin.d_scalars + S_ROW_ARRIVED), 1ull) == gridDim.x - 1;
+    __syncthreads();
+    if (s_last) row_finish<true>(fin, 0, 1);
 }
 
 struct CopyArgs {
@@ -1320,22 +1349,31 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     const int sum_blocks = (int)std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, alias ? 0 : b_ntr) + 15) / 16);
     // row_ptr of C when the sizes of its rows are there, and the sizes of everything to the host
     int64_t *row_ptr = nullptr;
-    auto finish = [&](int timer) {
+    auto finish_args = [&] {
         FinishArgs a{};
         a.partial = partial;
         a.partials = sum_blocks;
         a.same = alias;
         a.d_scalars = ctx->d_scalars;
         a.h_scalars_dev = ctx->h_scalars_dev;
+        a.clear = row_ptr != nullptr;
+        a.expected = expected;
+        a.live = live;
+        if (row_ptr && A->rows <= kFinishRows) {
+            a.rows = A->rows;
+            a.row_nnz = row_nnz;
+            a.group_len = group_len;
+            a.c_row_ptr = row_ptr;
+        }
+        a.publish_tag = ++ctx->publish_tag;
+        return a;
+    };
+    auto finish = [&](int timer) {
         KernelTimer kt(ctx, timer, s);
         unsigned blocks = 1;
         if (!row_ptr) {
             hipLaunchKernelGGL(k_row_sums, dim3((unsigned)sum_blocks), dim3(256), 0, s, sums);
         } else if (A->rows <= kFinishRows) {
-            a.rows = A->rows;
-            a.row_nnz = row_nnz;
-            a.group_len = group_len;
-            a.c_row_ptr = row_ptr;
             blocks = (unsigned)chunks;
         } else {
             int64_t *tmp = ws.get<int64_t>(scan_tmp_entries(A->rows));
@@ -1343,11 +1381,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             const int rc = scan_exclusive_i32_to_i64(ctx, row_nnz, row_ptr, A->rows, ctx->d_scalars + S_C_NNZ, nullptr, tmp, s);
             if (rc) return rc;
         }
-        a.clear = row_ptr != nullptr;
-        a.expected = expected;
-        a.live = live;
-        a.publish_tag = ++ctx->publish_tag;
-        hipLaunchKernelGGL(k_row_finish, dim3(blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_row_finish, dim3(blocks), dim3(256), 0, s, finish_args());
         TSP_HIP_CHECK(ctx, hipGetLastError());
         return (int)TSP_OK;
     };
@@ -1391,6 +1425,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         auto kernel = shift == 11 ? k_heavy_count<2048> : k_heavy_count<4096>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(kHeavyThreads), lds, s, c);
     };
+    // heavy rows whose pattern is kept at a time
+    auto pattern_rows = [&](int64_t heavy) { return std::min(heavy, std::max<int64_t>(kKeptPattern / (((int64_t)windows << shift) / 8), 1)); };
     int32_t *table = nullptr, *words = nullptr;
     uint2 *word = nullptr;
     SmallArgs m{};
@@ -1408,6 +1444,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     m.group_len = group_len;
     const unsigned small_blocks = (unsigned)(small_waves / 4);
     m.blocks = (int)small_blocks;
+    // (a small product without heavy rows: the last block of the small ones finishes)
+    bool finish_too = known && hint.nnz >= 0 && chunks == 1 && n_heavy == 0;
     auto size_rows = [&](bool again) {
         if (again || n_tasks > left.task_cap || n_heavy > left.heavy_cap) {
             // the lists did not fit: make them again, as large as they have to be
@@ -1430,14 +1468,16 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             // the pattern of the heavy rows, kept for the multiplication: a bit per column, also of the empty windows.
             // Where that is too much, the multiplication has it found again, some rows at a time.
             const int64_t row_bytes = ((int64_t)windows << shift) / 8;
-            bit_rows = std::min<int64_t>(n_heavy, std::max<int64_t>(kKeptPattern / row_bytes, 1));
+            bit_rows = pattern_rows(n_heavy);
             bits = ws.get<uint32_t>((size_t)(bit_rows * row_bytes / 4));
             if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
         }
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
         auto kernel = shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true> : k_row_small<8, false>)
                                        : (shape.narrow() ? k_row_small<16, true> : k_row_small<16, false>);
-        hipLaunchKernelGGL(kernel, dim3(small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums);
+        m.finish = finish_too;
+        hipLaunchKernelGGL(kernel, dim3(small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums,
+                           finish_too ? finish_args() : FinishArgs{});
         if (n_heavy > 0) {
             PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, windows, shift};
             if (B->nnz > 16 * B->rows)
@@ -1507,13 +1547,10 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         TSP_HIP_CHECK(ctx, hipGetLastError());
         return (int)TSP_OK;
     };
-    int rc = size_rows(false);
-    if (rc) return rc;
-    phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
     // A product of the sizes of the last one: the kernels of the multiplication follow at once, into arrays for as many
     // entries as that one had and some more, and k_row_finish lets them run if this product fits; the GPU does not
     // wait for the host to learn nnz(C) (8 us of 78 on a 512x512 mesh).  Otherwise they are launched again below.
-    const bool ahead = known && hint.nnz >= 0 && bit_rows == n_heavy;
+    const bool ahead = known && hint.nnz >= 0 && pattern_rows(n_heavy) == n_heavy;
     int64_t room = 0;
     if (ahead) {
         room = hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20);
@@ -1524,9 +1561,12 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         kind = FillKind{(FillKind::Sum)hint.sum, hint.scale};
         expected = Expected{room, n_heavy, n_tasks, kind};
     }
+    int rc = size_rows(false);
+    if (rc) return rc;
+    phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
     const bool had_small = hint.small;
     phase_begin(ctx, TSP_PHASE_COUNT, s);
-    rc = finish(TSP_KERNEL_SCAN_ROWS);
+    if (!finish_too) rc = finish(TSP_KERNEL_SCAN_ROWS);
     ctx->scalars_clean = !rc;                // (it has cleared the scalar block for the next call)
     phase_end(ctx, TSP_PHASE_COUNT, s);
     if (!rc && ahead) rc = multiply(had_small, kind);
@@ -1539,7 +1579,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     if (!done) {
         live = nullptr;
         if (n_heavy > had_heavy || n_tasks > had_tasks) {            // another matrix of the same sizes, with more work in it
-            ctx->scalars_clean = false;
+            ctx->scalars_clean = finish_too = false;
             rc = size_rows(true);
             if (rc) return rc;
             rc = finish(TSP_KERNEL_SCAN_ROWS);
