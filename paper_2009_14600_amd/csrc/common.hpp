@@ -39,7 +39,7 @@ enum Scalar {
     S_ROW_SMALL = 18,        // rows of C that go through a table in LDS
     S_ROW_HEAVY = 19,        // rows of C that are not
     S_ROW_TASKS = 20,        // blocks of k_heavy_fill
-    S_ROW_RANGE_A = 21,      // magnitude and granularity of the values (value_range)
+    S_ROW_RANGE_A = 21,      // magnitude and granularity of the values (ValueRange)
     S_ROW_RANGE_B = 22,
     S_ROW_LONGEST = 23,      // entries of the longest heavy row of A
     S_ROW_ARRIVED = 16,      // blocks of k_row_small that are done

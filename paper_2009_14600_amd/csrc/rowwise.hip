@@ -42,7 +42,7 @@ struct RowMatrix {                       // an operand in the form the row kerne
     int2 *rec = nullptr;                 // per entry {column (clamped), value rounded to fp16, as fp32 bits}
     int32_t *ntiles = nullptr;           // tiles of every tile-row
     int32_t *tile_col = nullptr;         // their columns, at the position of the tile-row's first entry; any order
-    uint32_t *range = nullptr;           // magnitude and granularity of every tile-row's values (value_range)
+    uint32_t *range = nullptr;           // magnitude and granularity of every tile-row's values (ValueRange)
 };
 
 // A value that is the same for the whole wave and that no kernel running now writes, through the scalar cache.
@@ -75,20 +75,27 @@ struct PrepareArgs {
     int64_t *d_scalars;
 };
 
-__device__ __forceinline__ float rounded_value(uint16_t bits) {
-    return (float)__builtin_bit_cast(_Float16, bits);
-}
-__device__ __forceinline__ float rounded_value(float v) { return (float)(_Float16)v; }
+__device__ __forceinline__ uint32_t half_bits(uint16_t bits) { return bits; }
+__device__ __forceinline__ uint32_t half_bits(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
 
-// Of a value v != 0: {256 + e} << 16 | {256 - g}, |v| < 2^e and v a multiple of 2^g; infinities and NaNs are as large as
-// can be.  The larger of each half over a set of values holds for the set.
-__device__ __forceinline__ uint32_t value_range(float v) {
-    const uint32_t b = __float_as_uint(v) & 0x7FFFFFFFu;
-    if (b == 0) return 0;
-    if (b >= 0x7F800000u) return 0x03FF03FFu;
-    const int exponent = (int)(b >> 23), low = __ffs((int)((b & 0x7FFFFFu) | 0x800000u)) - 1;
-    return (uint32_t)(256 + exponent - 126) << 16 | (uint32_t)(256 - (exponent - 150 + low));
-}
+// What a set of fp16 values spans: {256 + e} << 16 | {256 - g}, every |v| < 2^e and a multiple of 2^g; infinities and NaNs
+// are as large as can be, zeros are left out.  The larger of each half over two sets holds for both.  ValueRange goes
+// through the values of a set: the largest |v|, and the least exponent of a last bit (plus 25).
+struct ValueRange {
+    uint32_t most = 0, last = 1u << 20;
+    __device__ __forceinline__ void take(uint32_t bits) {
+        const uint32_t x = bits & 0x7FFFu, e = max(x >> 10, 1u);
+        const uint32_t m = (x & 0x3FFu) | (x >= 0x400u ? 0x400u : 0u) | ((x - 1u) & 0x80000000u);
+        most = max(most, x);
+        last = min(last, e + (uint32_t)__builtin_ctz(m));
+    }
+    static __device__ __forceinline__ uint32_t range(uint32_t most, uint32_t last) {
+        if (most == 0) return 0;
+        if (most >= 0x7C00u) return 0x03FF03FFu;
+        const int exponent = (int)(__float_as_uint((float)__builtin_bit_cast(_Float16, (uint16_t)most)) >> 23);
+        return (uint32_t)(256 + exponent - 126) << 16 | (256u + 25u - last);
+    }
+};
 __device__ __forceinline__ uint32_t range_max(uint32_t x, uint32_t y) {
     return max(x & 0xFFFF0000u, y & 0xFFFF0000u) | max(x & 0xFFFFu, y & 0xFFFFu);
 }
@@ -108,7 +115,7 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     __shared__ int32_t s_ptr[kTeams][T + 1];
     __shared__ unsigned long long s_ub[kTeams][T];
     __shared__ int32_t s_count[kTeams];
-    __shared__ uint32_t s_range[2][kTeams];
+    __shared__ uint32_t s_most[kTeams], s_last[kTeams];
     const int team = threadIdx.x / kTeam, tid = threadIdx.x % kTeam, lane = lane_id();
     uint32_t *bitmap = lds_bitmap + team * a.bitmap_words;
     const int64_t tile_rows = (a.rows + T - 1) / T;
@@ -116,28 +123,29 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     const bool live = I < tile_rows;
     bool bad = false;
     if (live) {
-        for (int w = tid; w < a.bitmap_words; w += kTeam) bitmap[w] = 0;
+        for (int w = tid; w < a.bitmap_words / 4; w += kTeam) reinterpret_cast<uint4 *>(bitmap)[w] = make_uint4(0, 0, 0, 0);
         if (tid <= T) {
             const int64_t i = min(I * T + tid, a.rows);
-            const int64_t raw = (int64_t)a.row_ptr[i];
-            const int64_t p = min(max(raw, (int64_t)0), a.nnz);
-            bad = raw != p || (i == 0 && raw != 0) || (i == a.rows && raw != a.nnz) ||
-                  (i < a.rows && (int64_t)a.row_ptr[i + 1] < raw);
+            const RP raw = a.row_ptr[i];
+            const RP p = min(max(raw, (RP)0), (RP)a.nnz);
+            bad = raw != p || (i == 0 && raw != 0) || (i == a.rows && raw != (RP)a.nnz);
             s_ptr[team][tid] = (int32_t)p;
             if (tid < T) s_ub[team][tid] = 0;
             if (i < a.rows ? tid < T : true) a.out.start[i] = (int32_t)p;
         }
         if (tid == 0) {
             s_count[team] = 0;
-            s_range[0][team] = s_range[1][team] = 0;
+            s_most[team] = 0;
+            s_last[team] = 1u << 20;
         }
     }
     if constexpr (kTeam == 64) wave_sync();
     else __syncthreads();
     if (live) {
         const int32_t e0 = s_ptr[team][0], e1 = s_ptr[team][T];
+        if (tid < T) bad = bad || s_ptr[team][tid + 1] < s_ptr[team][tid];
         int32_t listed = 0;
-        uint32_t range = 0;
+        ValueRange range;
         for (int32_t base = e0 + (tid & ~63); base < e1; base += kTeam * kU) {
             int32_t c[kU], prev[kU], len[kU];
             VT v[kU];
@@ -179,9 +187,9 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                         if (s_ptr[team][r + step] <= k) r += step;
                     starts = k == s_ptr[team][r];
                     bad = bad || (!starts && prev[u] >= c[u]);
-                    const float x = rounded_value(v[u]);
-                    a.out.rec[k] = make_int2(c[u], (int)__float_as_uint(x));
-                    range = range_max(range, value_range(x));
+                    const uint32_t bits = half_bits(v[u]);
+                    a.out.rec[k] = make_int2(c[u], (int)__float_as_uint((float)__builtin_bit_cast(_Float16, (uint16_t)bits)));
+                    range.take(bits);
                 }
                 const int32_t t = c[u] >> 4;
                 bool first = on && (starts || (prev[u] >> 4) != t);
@@ -198,7 +206,9 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                     at = __builtin_amdgcn_readfirstlane(at);
                 }
                 if (first) a.out.tile_col[e0 + at + __popcll(firsts & ((1ull << lane) - 1ull))] = t;
-                if (a.ub) {
+                if (a.ub && kTeam == 64) {
+                    if (on) atomicAdd(&s_ub[team][r], (unsigned long long)(uint32_t)len[u]);    // (rows of few entries)
+                } else if (a.ub) {
                     // products per row: differences of the running sum at the ends of the rows' stretches in this wave
                     const uint32_t mine = on ? (uint32_t)len[u] : 0u, inc = wave_inclusive_scan(mine);
                     const int r_next = __shfl_down(r, 1, 64), r_prev = __shfl_up(r, 1, 64);
@@ -208,11 +218,11 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                 }
             }
         }
-        const int e = wave_max((int)(range >> 16)), g = wave_max((int)(range & 0xFFFFu));
+        const int most = wave_max((int)range.most), last = -wave_max(-(int)range.last);
         if (lane == 0) {
             if constexpr (kTeam == 64) s_count[team] = listed;
-            atomicMax(&s_range[0][team], (uint32_t)e);
-            atomicMax(&s_range[1][team], (uint32_t)g);
+            atomicMax(&s_most[team], (uint32_t)most);
+            atomicMin(&s_last[team], (uint32_t)last);
         }
     }
     if constexpr (kTeam == 64) wave_sync();
@@ -221,7 +231,7 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     if (bad && a.validate) a.d_scalars[S_INVALID] = 1;
     if (tid == 0) {
         a.out.ntiles[I] = s_count[team];
-        a.out.range[I] = s_range[0][team] << 16 | s_range[1][team];
+        a.out.range[I] = ValueRange::range(s_most[team], s_last[team]);
     }
     if (!a.ub || tid >= 64) return;
     // a lane per row
@@ -455,12 +465,14 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
     uint64_t before = 0;
     const uint4 *groups4 = reinterpret_cast<const uint4 *>(a.group_len);
     const int64_t quads = a.rows > 0 ? (int64_t)block * kChunkTileRows / 4 : 0;
-    for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 4 * 256) {
-        uint4 g[4];
+    // (all of them in flight up to 16384 groups: a round trip, not four)
+    for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 16 * 256) {
+        uint4 g[16];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) g[u] = q0 + u * 256 < quads ? groups4[q0 + u * 256] : make_uint4(0, 0, 0, 0);
+        for (int u = 0; u < 16; ++u) g[u] = groups4[min(q0 + u * 256, quads - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) before += (uint64_t)g[u].x + g[u].y + g[u].z + g[u].w;
+        for (int u = 0; u < 16; ++u)
+            if (q0 + u * 256 < quads) before += (uint64_t)g[u].x + g[u].y + g[u].z + g[u].w;
     }
     uint64_t entries_before;
     (void)block_exclusive_scan64<256>(before, &entries_before, lds);
@@ -1206,7 +1218,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
         a.rows = M->rows;
         a.cols = M->cols;
         a.nnz = M->nnz;
-        a.bitmap_words = (int)((M->cols + T * 32 - 1) / (T * 32));
+        a.bitmap_words = (int)((M->cols + T * 32 - 1) / (T * 32) + 3) & ~3;
         a.validate = ctx->validate;
         a.out = out;
         if (left) {
