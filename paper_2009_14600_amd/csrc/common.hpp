@@ -276,17 +276,24 @@ inline int64_t xcd_chunked_grid(int64_t blocks, int chunk) {
 // no store has to be ordered behind another across the bus, and the kernel does not wait for a fence.
 constexpr int kPublishTagShift = 48;
 __host__ __device__ inline uint64_t publish_tag16(int64_t tag) { return (uint64_t)(tag % 65535) + 1u; }   // never 0
+// `standing`: scalar threadIdx.x as other kernels, or other blocks of this one, have left it (standing_scalar).  own, own_slots:
+// what this block itself has to say, in LDS, and for which slots; it takes no way through the scalar block, where a fence
+// would have to wait until everything this XCD has written is out of its L2 cache.
 // `clear`: the block is zeroed for the next call, whose kernels no kernel behind this one may disturb.
-__device__ __forceinline__ void publish_scalars(int64_t *d_scalars, int64_t *h_scalars_dev, int64_t tag, bool clear = false) {
-    __threadfence();                               // this block's own plain stores to the scalar block
+__device__ __forceinline__ int64_t standing_scalar(const int64_t *d_scalars) {
+    return threadIdx.x < kScalars ? __hip_atomic_load(&d_scalars[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+}
+constexpr uint32_t own_slot(int slot) { return 1u << slot; }
+__device__ __forceinline__ void publish_scalars(int64_t *d_scalars, int64_t *h_scalars_dev, int64_t tag, int64_t standing,
+                                                const int64_t *own, uint32_t own_slots, bool clear = false) {
     __syncthreads();
     if (threadIdx.x < kScalars) {
-        const uint64_t v = threadIdx.x == S_PUBLISHED
-                               ? 0u
-                               : (uint64_t)__hip_atomic_load(&d_scalars[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool mine = (own_slots >> threadIdx.x) & 1u;
+        const uint64_t v = threadIdx.x == S_PUBLISHED ? 0u : (uint64_t)(mine ? own[threadIdx.x] : standing);
         const uint64_t slot = (publish_tag16(tag) << kPublishTagShift) | (v & ((1ull << kPublishTagShift) - 1u));
         __hip_atomic_store(&h_scalars_dev[threadIdx.x], (int64_t)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (clear) d_scalars[threadIdx.x] = 0;
+        else if (mine) d_scalars[threadIdx.x] = (int64_t)v;
     }
 }
 

@@ -72,24 +72,31 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<R
     if (threadIdx.x == 0) count[blockIdx.x] = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
 }
 
-// Survivors before every chunk, by one block; the total to the host.  (At most 65,536 numbers, 64 per thread.)  The
+// Survivors before every chunk, by one block, 4096 chunks at a time; the total to the host.  (At most 65,536 numbers.)  The
 // scalar block is left as it was.
 __global__ __launch_bounds__(1024) void k_compact_scan(const uint32_t *__restrict__ count, int chunks, int64_t *__restrict__ before,
                                                       int64_t *d_scalars, int64_t *h_scalars_dev, int64_t publish_tag) {
     __shared__ uint64_t lds[1024 / 64];
-    const int per = (chunks + 1023) / 1024, first = (int)threadIdx.x * per, last = min(first + per, chunks);
-    uint64_t mine = 0;
-    for (int i = first; i < last; ++i) mine += count[i];
-    uint64_t total;
-    uint64_t run = block_exclusive_scan64<1024>(mine, &total, lds);
-    if (threadIdx.x == 0) d_scalars[S_C_NNZ] = (int64_t)total;
-    publish_scalars(d_scalars, h_scalars_dev, publish_tag);
-    for (int i = first; i < last; ++i) {
-        before[i] = (int64_t)run;
-        run += count[i];
+    __shared__ int64_t own[kScalars];
+    const int64_t standing = standing_scalar(d_scalars);
+    uint64_t carry = 0;
+    for (int t0 = 0; t0 < chunks; t0 += 4096) {
+        const int first = t0 + (int)threadIdx.x * 4;
+        uint32_t x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = first + i < chunks ? count[first + i] : 0u;
+        uint64_t total;
+        uint64_t run = carry + block_exclusive_scan64<1024>((uint64_t)x[0] + x[1] + x[2] + x[3], &total, lds);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (first + i < chunks) before[first + i] = (int64_t)run;
+            run += x[i];
+        }
+        carry += total;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) d_scalars[S_C_NNZ] = 0;
+    if (threadIdx.x == 0) own[S_C_NNZ] = (int64_t)carry;
+    publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing, own, own_slot(S_C_NNZ));
+    if (threadIdx.x == S_C_NNZ) d_scalars[S_C_NNZ] = 0;
 }
 
 // First row whose entries begin at `begin` or later (rows: none), by the 64 lanes of a wave.

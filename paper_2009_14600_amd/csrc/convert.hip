@@ -1044,6 +1044,8 @@ __global__ __launch_bounds__(1024) void k_tiles_total_publish(int64_t tile_rows,
                                                              const int32_t *__restrict__ tend, int64_t *d_scalars, int slot,
                                                              int64_t *h_scalars_dev, int64_t publish_tag) {
     __shared__ uint32_t part[1024 / 64];
+    __shared__ int64_t own[kScalars];
+    const int64_t standing = standing_scalar(d_scalars);
     uint32_t n = 0;
     for (int64_t i0 = threadIdx.x; i0 < tile_rows; i0 += 8 * 1024) {
         int32_t first[8], last[8];
@@ -1062,9 +1064,9 @@ __global__ __launch_bounds__(1024) void k_tiles_total_publish(int64_t tile_rows,
     if (threadIdx.x == 0) {
         int64_t all = 0;
         for (int w = 0; w < 1024 / 64; ++w) all += part[w];
-        d_scalars[slot] = all;
+        own[slot] = all;
     }
-    publish_scalars(d_scalars, h_scalars_dev, publish_tag, true);
+    publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing, own, own_slot(slot), true);
 }
 // ... of more tile-rows
 __global__ __launch_bounds__(256) void k_tiles_total(int64_t tile_rows, const int32_t *__restrict__ trp,

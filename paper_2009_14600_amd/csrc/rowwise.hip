@@ -429,7 +429,9 @@ template <bool kShared>
 __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int blocks) {
     __shared__ uint64_t lds[256 / 64];
     __shared__ unsigned long long s_sum[kPlanSums], s_max[kPlanSums];
+    __shared__ int64_t own[kScalars];
     const bool last = block == blocks - 1;
+    const int64_t standing = last ? standing_scalar(a.d_scalars) : 0;
     constexpr int kItems = kChunkRows / 256;
     const int64_t base = (int64_t)block * kChunkRows + (int64_t)threadIdx.x * kItems;
     int32_t x[kItems];
@@ -487,29 +489,33 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
         run += (uint32_t)x[i];
     }
     if (!last) return;
+    if (threadIdx.x == S_C_NNZ) own[S_C_NNZ] = a.rows > 0 ? (int64_t)(entries_before + total) : standing;
+    if (threadIdx.x == S_INVALID) own[S_INVALID] = standing;
+    if (threadIdx.x == S_ROW_LISTS) own[S_ROW_LISTS] = standing;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        if (a.rows > 0) {
-            a.c_row_ptr[a.rows] = (int64_t)(entries_before + total);
-            a.d_scalars[S_C_NNZ] = (int64_t)(entries_before + total);
-        }
-        a.d_scalars[S_CANDIDATES] = (int64_t)s_sum[kSumCandidates];
-        a.d_scalars[S_TILES_A] = (int64_t)s_sum[kSumTilesA];
-        a.d_scalars[S_TILES_B] = (int64_t)(a.same ? s_sum[kSumTilesA] : s_sum[kSumTilesB]);
-        a.d_scalars[S_ROW_PRODUCTS] = (int64_t)s_sum[kSumProducts];
-        a.d_scalars[S_ROW_SMALL] = (int64_t)s_sum[kSumSmall];
+        if (a.rows > 0) a.c_row_ptr[a.rows] = (int64_t)(entries_before + total);
+        own[S_CANDIDATES] = (int64_t)s_sum[kSumCandidates];
+        own[S_TILES_A] = (int64_t)s_sum[kSumTilesA];
+        own[S_TILES_B] = (int64_t)(a.same ? s_sum[kSumTilesA] : s_sum[kSumTilesB]);
+        own[S_ROW_PRODUCTS] = (int64_t)s_sum[kSumProducts];
+        own[S_ROW_SMALL] = (int64_t)s_sum[kSumSmall];
         const int from = a.same ? 0 : 2;
-        a.d_scalars[S_ROW_RANGE_A] = (int64_t)(s_max[0] << 16 | s_max[1]);
-        a.d_scalars[S_ROW_RANGE_B] = (int64_t)(s_max[from] << 16 | s_max[from + 1]);
-        a.d_scalars[S_ROW_LONGEST] = (int64_t)s_max[4];
-        const unsigned long long lists = (unsigned long long)a.d_scalars[S_ROW_LISTS];
-        a.d_scalars[S_ROW_HEAVY] = (int64_t)(lists >> 36);
-        a.d_scalars[S_ROW_TASKS] = (int64_t)(lists & ((1ull << 36) - 1ull));
+        own[S_ROW_RANGE_A] = (int64_t)(s_max[0] << 16 | s_max[1]);
+        own[S_ROW_RANGE_B] = (int64_t)(s_max[from] << 16 | s_max[from + 1]);
+        own[S_ROW_LONGEST] = (int64_t)s_max[4];
+        const unsigned long long lists = (unsigned long long)own[S_ROW_LISTS];
+        own[S_ROW_HEAVY] = (int64_t)(lists >> 36);
+        own[S_ROW_TASKS] = (int64_t)(lists & ((1ull << 36) - 1ull));
         if (a.live) {
-            a.live[0] = a.expected.holds(a.d_scalars);
-            a.live[1] = (int32_t)a.d_scalars[S_ROW_TASKS];
+            a.live[0] = a.expected.holds(own);
+            a.live[1] = (int32_t)own[S_ROW_TASKS];
         }
     }
-    publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, a.clear);
+    constexpr uint32_t kOwn = own_slot(S_C_NNZ) | own_slot(S_CANDIDATES) | own_slot(S_TILES_A) | own_slot(S_TILES_B) |
+                              own_slot(S_ROW_PRODUCTS) | own_slot(S_ROW_SMALL) | own_slot(S_ROW_RANGE_A) | own_slot(S_ROW_RANGE_B) |
+                              own_slot(S_ROW_LONGEST) | own_slot(S_ROW_HEAVY) | own_slot(S_ROW_TASKS);
+    publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, standing, own, kOwn, a.clear);
 }
 __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) { row_finish<false>(a, blockIdx.x, gridDim.x); }
 

@@ -580,6 +580,7 @@ __global__ __launch_bounds__(kRowScanThreads) void k_sym_row_scan(
     __shared__ uint64_t lds[kRowScanThreads / 64 + kChainValues];
     __shared__ int lds_m[3][kRowScanThreads / 64];
     __shared__ uint32_t lds_t[2][kRowScanThreads / 64];
+    __shared__ int64_t own[kScalars];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i0 = (int64_t)blockIdx.x * kRowScanBlock + (int64_t)threadIdx.x * kRowScanItems;
     int32_t xc[kRowScanItems], xp[kRowScanItems];
@@ -667,11 +668,12 @@ __global__ __launch_bounds__(kRowScanThreads) void k_sym_row_scan(
         if (threadIdx.x == 0) {
             c_tile_row_ptr[ntr] = (int32_t)(prefix[0] + agg[0]);
             row_pair_ptr[ntr] = (int64_t)(prefix[1] + agg[1]);
-            d_scalars[S_C_TILES] = (int64_t)(prefix[0] + agg[0]);
-            d_scalars[S_PAIRS] = (int64_t)(prefix[1] + agg[1]);
-            d_scalars[S_CANDIDATES] = (int64_t)(prefix[2] + agg[2]);
+            own[S_C_TILES] = (int64_t)(prefix[0] + agg[0]);
+            own[S_PAIRS] = (int64_t)(prefix[1] + agg[1]);
+            own[S_CANDIDATES] = (int64_t)(prefix[2] + agg[2]);
         }
-        publish_scalars(d_scalars, h_scalars_dev, publish_tag);
+        publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing_scalar(d_scalars), own,
+                        own_slot(S_C_TILES) | own_slot(S_PAIRS) | own_slot(S_CANDIDATES));
     }
 }
 
@@ -1303,8 +1305,10 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
                                                  int64_t *__restrict__ c_row_ptr, int64_t *d_scalars,
                                                  int64_t *h_scalars_dev, int64_t publish_tag, bool clear) {
     __shared__ uint64_t lds[256 / 64];
+    __shared__ int64_t own[kScalars];
     constexpr int kItems = kChunkRows / 256;
     const bool last = blockIdx.x == gridDim.x - 1;
+    const int64_t standing = last ? standing_scalar(d_scalars) : 0;
     const int64_t tile_rows_before = (int64_t)blockIdx.x * kChunkTileRows;
     // the block's own row lengths, requested first: they travel while the tile-rows before are added up
     const int64_t base = (int64_t)blockIdx.x * kChunkRows + (int64_t)threadIdx.x * kItems;
@@ -1352,11 +1356,11 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
         if (threadIdx.x == 0) {
             for (int w = 1; w < 256 / 64; ++w) largest = max(largest, (uint32_t)lds[w]);
             c_row_ptr[c_rows] = (int64_t)(entries_before + total);
-            d_scalars[S_C_NNZ] = (int64_t)(entries_before + total);
-            d_scalars[S_MAX_ROW_ENTRIES] = (int64_t)largest;
+            own[S_C_NNZ] = (int64_t)(entries_before + total);
+            own[S_MAX_ROW_ENTRIES] = (int64_t)largest;
         }
         // no other block of this launch writes a scalar, and the kernels before it have finished
-        publish_scalars(d_scalars, h_scalars_dev, publish_tag, clear);
+        publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing, own, own_slot(S_C_NNZ) | own_slot(S_MAX_ROW_ENTRIES), clear);
     }
 }
 

@@ -127,3 +127,27 @@ def test_another_structure_of_the_same_sizes(tsp, oracle, phases):
             assert np.all(np.abs(val.astype(np.float64) - want.val) <= 1e-5 * want.mag + 1e-7)
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("tile_rows", [1, 1024, 1025, 65537])
+def test_prefix_sums_over_tile_rows(tsp, oracle, tile_rows):
+    """Tile-rows either side of a block of the prefix sums, and more than 64 blocks."""
+    rng = np.random.default_rng(tile_rows)
+    n = 16 * tile_rows - 3
+    r = np.concatenate([np.arange(n), rng.integers(0, n, n // 4)])
+    c = np.concatenate([(np.arange(n) * 7) % n, rng.integers(0, n, n // 4)])
+    key = np.unique(r * n + c)
+    A = inputs.from_coo(n, n, key // n, key % n, rng.uniform(-1, 1, key.size), "two per row")
+    want = oracle.spgemm(A, A, threads=4)
+    h = tsp.Handle(validate=True)
+    try:
+        dA = tsp.to_device(A)
+        t = h.convert(dA)
+        plan = h.symbolic(t, t)
+        C = h.numeric(t, t, plan)
+        row_ptr, col, val = C.to_host()
+        assert np.array_equal(row_ptr, want.row_ptr) and np.array_equal(col, want.col)
+        assert np.all(np.abs(val.astype(np.float64) - want.val) <= 1e-5 * want.mag + 1e-7)
+        C.free(), plan.free(), t.free()
+    finally:
+        h.close()
