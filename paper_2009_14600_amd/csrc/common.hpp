@@ -61,15 +61,17 @@ struct LiveBlock {           // a block handed out: with canaries the caller's p
 
 // Sizes of a task list and of its tile-rows
 struct ListSizes {
-    int64_t c_tiles = 0, pairs = 0, candidates = 0, max_row_c_tiles = 0, max_row_pairs = 0, max_row_words = 0, b_tiles = 0;
+    int64_t c_tiles = 0, pairs = 0, candidates = 0, max_row_c_tiles = 0, max_row_pairs = 0, max_row_words = 0,
+            max_row_a_tiles = 0, b_tiles = 0;
     bool holds(const ListSizes &o) const {
         return o.c_tiles <= c_tiles && o.pairs <= pairs && o.max_row_c_tiles <= max_row_c_tiles &&
-               o.max_row_pairs <= max_row_pairs && o.max_row_words <= max_row_words;
+               o.max_row_pairs <= max_row_pairs && o.max_row_words <= max_row_words &&
+               o.max_row_a_tiles <= max_row_a_tiles;
     }
     ListSizes with(const ListSizes &o) const {     // enough for both
         return {std::max(c_tiles, o.c_tiles), std::max(pairs, o.pairs), std::max(candidates, o.candidates),
                 std::max(max_row_c_tiles, o.max_row_c_tiles), std::max(max_row_pairs, o.max_row_pairs),
-                std::max(max_row_words, o.max_row_words), std::max(b_tiles, o.b_tiles)};
+                std::max(max_row_words, o.max_row_words), std::max(max_row_a_tiles, o.max_row_a_tiles), std::max(b_tiles, o.b_tiles)};
     }
 };
 // What symbolic_run goes by for a product of the sizes of an earlier one, see there
@@ -252,6 +254,18 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A value that is the same for the whole wave and that no kernel running now writes, through the scalar cache.
+template <typename X>
+__device__ __forceinline__ X uniform_load(const X *p) {
+    return *(const __attribute__((address_space(4))) X *)(uintptr_t)p;
+}
+
+// Element i of an array of less than 4 GiB: the address is a scalar base and a 32-bit offset.
+template <typename X>
+__device__ __forceinline__ X element(const X *base, uint32_t i) {
+    return *reinterpret_cast<const X *>(reinterpret_cast<const char *>(base) + (size_t)(uint32_t)(i * (uint32_t)sizeof(X)));
 }
 
 // Workgroup b of a launch runs on XCD b % 8, each XCD with an L2 cache of its own.  Logical block index

@@ -45,12 +45,6 @@ struct RowMatrix {                       // an operand in the form the row kerne
     uint32_t *range = nullptr;           // magnitude and granularity of every tile-row's values (ValueRange)
 };
 
-// A value that is the same for the whole wave and that no kernel running now writes, through the scalar cache.
-template <typename X>
-__device__ __forceinline__ X uniform_load(const X *p) {
-    return *(const __attribute__((address_space(4))) X *)(uintptr_t)p;
-}
-
 template <typename RP, typename VT>
 struct PrepareArgs {
     const RP *row_ptr;
@@ -520,12 +514,6 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
 __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) { row_finish<false>(a, blockIdx.x, gridDim.x); }
 
 // ---- small rows -------------------------------------------------------------------------------------------------
-// Element i of an array of less than 4 GiB: the address is a scalar base and a 32-bit offset.
-template <typename X>
-__device__ __forceinline__ X element(const X *base, uint32_t i) {
-    return *reinterpret_cast<const X *>(reinterpret_cast<const char *>(base) + (size_t)(uint32_t)(i * (uint32_t)sizeof(X)));
-}
-
 // How the small rows of a launch are worked off: lanes per row of A, lanes per row of B (a power of two, at most as
 // many), slots of the row's table (a power of two), and the most products of a small row.
 struct SmallShape {

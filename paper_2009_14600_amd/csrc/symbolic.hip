@@ -21,7 +21,8 @@
 // Kernels: k_sym_count (steps 1-3, sizes per tile-row; k_sym_count_half gives short tile-rows half a wave
 // each, k_sym_count_segmented does so against a very wide B), k_sym_row_scan (their prefix sums, one chained launch), then either k_sym_emit_listed (tile-rows
 // with few pairs: survivors enumerated once into an LDS list; with enough tile-rows it also runs the
-// counting pass and the row offsets; a block or half a wave per tile-row) or k_sym_emit (any tile-row; more
+// counting pass and the row offsets; a block or half a wave per tile-row), k_sym_emit_block (the same where a tile-row of
+// A has few tiles, a block per tile-row) or k_sym_emit (any tile-row; more
 // C tiles than the LDS window holds are worked off window by window; on skewed products the heaviest
 // tile-rows first, in the order k_work_hist and k_work_order set up), k_count_masks and k_row_offsets
 // (k_row_offsets_wide for tile-rows with many tiles) where the list kernel has not done their work, and
@@ -575,17 +576,17 @@ __global__ __launch_bounds__(kRowScanThreads) void k_sym_row_scan(
     int64_t ntr, const int32_t *__restrict__ row_c_tiles, const int32_t *__restrict__ row_pairs,
     const int32_t *__restrict__ row_words, const int32_t *__restrict__ row_cand,
     int32_t *__restrict__ c_tile_row_ptr, int64_t *__restrict__ row_pair_ptr, ChainSlot *slots, unsigned epoch,
-    int64_t *__restrict__ d_scalars, TileCount count_a, TileCount count_b, int64_t *h_scalars_dev,
+    const int32_t *__restrict__ a_trp, const int32_t *__restrict__ a_tend, int64_t *__restrict__ d_scalars, TileCount count_a, TileCount count_b, int64_t *h_scalars_dev,
     int64_t publish_tag) {
     __shared__ uint64_t lds[kRowScanThreads / 64 + kChainValues];
-    __shared__ int lds_m[3][kRowScanThreads / 64];
+    __shared__ int lds_m[4][kRowScanThreads / 64];
     __shared__ uint32_t lds_t[2][kRowScanThreads / 64];
     __shared__ int64_t own[kScalars];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i0 = (int64_t)blockIdx.x * kRowScanBlock + (int64_t)threadIdx.x * kRowScanItems;
     int32_t xc[kRowScanItems], xp[kRowScanItems];
     uint64_t sc = 0, sp = 0, cand = 0;
-    int max_c = 0, max_w = 0, max_p = 0;
+    int max_c = 0, max_w = 0, max_p = 0, max_a = 0;
 #pragma unroll
     for (int k = 0; k < kRowScanItems; ++k) {
         const bool in = i0 + k < ntr;
@@ -596,6 +597,7 @@ __global__ __launch_bounds__(kRowScanThreads) void k_sym_row_scan(
         max_c = max(max_c, xc[k]);
         max_p = max(max_p, xp[k]);
         max_w = max(max_w, in ? row_words[i0 + k] : 0);
+        max_a = max(max_a, in ? a_tend[i0 + k] - a_trp[i0 + k] : 0);
         cand += in ? (uint32_t)row_cand[i0 + k] : 0u;
     }
     // tiles of the operands whose converter has not been waited for: summed here, one atomic per block
@@ -616,20 +618,24 @@ __global__ __launch_bounds__(kRowScanThreads) void k_sym_row_scan(
     max_c = wave_max(max_c);
     max_w = wave_max(max_w);
     max_p = wave_max(max_p);
+    max_a = wave_max(max_a);
     __syncthreads();
     if (lane == 0) {
         lds_m[0][wave] = max_c;
         lds_m[1][wave] = max_w;
         lds_m[2][wave] = max_p;
+        lds_m[3][wave] = max_a;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        int mc = 0, mw = 0, mp = 0;
+        int mc = 0, mw = 0, mp = 0, ma = 0;
         for (int w = 0; w < kRowScanThreads / 64; ++w) {
             mc = max(mc, lds_m[0][w]);
             mw = max(mw, lds_m[1][w]);
             mp = max(mp, lds_m[2][w]);
+            ma = max(ma, lds_m[3][w]);
         }
+        atomicMax((unsigned long long *)&d_scalars[S_MAX_ROW_A_TILES], (unsigned long long)ma);
         atomicMax((unsigned long long *)&d_scalars[S_MAX_ROW_PAIRS], (unsigned long long)mp);
         atomicMax((unsigned long long *)&d_scalars[S_MAX_ROW_C_TILES], (unsigned long long)mc);
         atomicMax((unsigned long long *)&d_scalars[S_MAX_ROW_WORDS], (unsigned long long)mw);
@@ -1230,6 +1236,224 @@ __global__ __launch_bounds__(kTeamLanes ? 64 : kSymThreads) void k_sym_emit_list
     }
 }
 
+// The same with a block per tile-row, counting pass and all, for tile-rows of up to kBlockATiles tiles of A: four lanes
+// per tile of A take the boolean products of its pairs, four rows of C each, against its rows spread out to words in
+// registers once.  No list: the pairs are walked three times, to mark the tile columns, for the products and
+// contributors, and to place them.  Bound by vector instructions (83 % of the time), two thirds of them in the products:
+// 27-point stencil with 3 unknowns on 48^3 nodes (27 tiles of A and 567 pairs per tile-row) 244 us; 318 us with sixteen
+// lanes per pair, which select rows of B through a table in LDS and fetch every bitmap sixteen times.
+// Dynamic LDS: 2*words_cap + 11*window words.
+constexpr int kBlockATiles = 64, kBlockListThreads = 128;
+__global__ __launch_bounds__(kBlockListThreads) void k_sym_emit_block(
+    TileRefs A, TileRefs B, int words_cap, int window, const int32_t *__restrict__ row_jmin,
+    const int32_t *__restrict__ row_words, const int32_t *__restrict__ c_tile_row_ptr, const int64_t *__restrict__ row_pair_ptr,
+    int32_t *__restrict__ c_tile_row, int32_t *__restrict__ c_tile_col, int64_t *__restrict__ pair_off,
+    int2 *__restrict__ pair_ab, const uint16_t *__restrict__ a_row_mask, const uint16_t *__restrict__ b_row_mask,
+    uint16_t *__restrict__ c_row_mask, uint32_t *__restrict__ c_row_off, int32_t *__restrict__ row_nnz, int64_t c_rows,
+    int64_t *d_scalars, uint32_t *__restrict__ tile_row_entries, int64_t c_tiles_most, int64_t pairs_most) {
+    constexpr int kThreads = kBlockListThreads, kLanes = 4;
+    extern __shared__ __align__(16) uint32_t lds_dyn[];
+    __shared__ uint32_t s_part[kThreads / 16][T];
+    unsigned long long *const cmask = reinterpret_cast<unsigned long long *>(lds_dyn);   // four row masks each, four per C tile
+    unsigned long long *const contrib = cmask + window * 4;                              // tiles of A that contribute
+    uint32_t *const cnt = reinterpret_cast<uint32_t *>(contrib + window);                // pairs of the C tiles before
+    uint32_t *const bm = cnt + window, *const wpre = bm + words_cap;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & (kLanes - 1);
+    const int I = (int)blockIdx.x;
+    const int c0 = uniform_load(c_tile_row_ptr + I), nC = uniform_load(c_tile_row_ptr + I + 1) - c0;
+    const int64_t row_base = uniform_load(row_pair_ptr + I), row_end = uniform_load(row_pair_ptr + I + 1);
+    if (I == A.tile_rows - 1 && tid == 0 && c_tile_row_ptr[A.tile_rows] <= c_tiles_most)
+        pair_off[c_tile_row_ptr[A.tile_rows]] = row_pair_ptr[A.tile_rows];
+    const int a0 = uniform_load(A.trp + I), nA = uniform_load(A.tend + I) - a0;
+    const int jmin = uniform_load(row_jmin + I), words = uniform_load(row_words + I);
+    // an empty tile-row of C: its 16 rows are empty; so is one that does not fit the arrays (the kernel then runs again)
+    if (nC <= 0 || nC > window || c0 + nC > c_tiles_most || words > words_cap || row_end > pairs_most || nA > kBlockATiles) {
+        if (tid < T && (int64_t)I * T + tid < c_rows) row_nnz[(int64_t)I * T + tid] = 0;
+        if (tid == 0) tile_row_entries[I] = 0;
+        return;
+    }
+    const uint32_t span = (uint32_t)words * 32u;
+    for (int w = tid; w < words; w += kThreads) bm[w] = 0;
+    for (int w = tid; w < nC * 4; w += kThreads) cmask[w] = 0;
+    for (int c = tid; c < nC; c += kThreads) contrib[c] = 0;
+    __syncthreads();
+    // f(A tile, B tile, column from jmin) for every surviving pair, four lanes per tile of A side by side over the tiles of
+    // B, four each per trip
+    auto for_each_pair = [&](auto f) {
+        for (int a = a0 + tid / kLanes; a < a0 + nA; a += kThreads / kLanes) {
+            const uint32_t K = (uint32_t)element(A.tcol, (uint32_t)a);
+            if (K >= (uint32_t)B.tile_rows) continue;            // only possible for a non-canonical input
+            const uint32_t col_occ = fold16(element(A.rmask, (uint32_t)a));
+            const int b0 = element(B.trp, K), b1 = element(B.tend, K);
+            for (int b = b0 + l; b < b1; b += 4 * kLanes) {
+                uint32_t occ[4], at[4];
+                int col[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    at[u] = (uint32_t)min(b + u * kLanes, b1 - 1);
+                    occ[u] = element(B.lmask, at[u]);
+                    col[u] = element(B.tcol, at[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t j = (uint32_t)(col[u] - jmin);
+                    if (b + u * kLanes < b1 && (col_occ & fold16(occ[u])) && j < span) f(a, (int)at[u], j);
+                }
+            }
+        }
+    };
+    for_each_pair([&](int, int, uint32_t j) { atomicOr(&bm[j >> 5], 1u << (j & 31)); });
+    __syncthreads();
+    {   // C tiles before every word, each wave for itself; their coordinates, ascending J
+        const int stretch = (words + 63) >> 6;
+        uint32_t mine = 0;
+        for (int i = 0; i < stretch; ++i) mine += lane * stretch + i < words ? (uint32_t)__popc(bm[lane * stretch + i]) : 0u;
+        uint32_t before = wave_inclusive_scan(mine) - mine;
+        for (int i = 0; i < stretch; ++i) {
+            const int w = lane * stretch + i;
+            if (w >= words) break;
+            const uint32_t bits = bm[w];
+            wpre[w] = before;
+            if ((lane & (kThreads / 64 - 1)) == wave) {
+                int c = c0 + (int)before;
+                for (uint32_t left = bits; left; left &= left - 1, ++c) {
+                    c_tile_row[c] = I;
+                    c_tile_col[c] = jmin + w * 32 + __ffs(left) - 1;
+                }
+            }
+            before += (uint32_t)__popc(bits);
+        }
+        wave_sync();
+    }
+    auto rank = [&](uint32_t j) -> int { return (int)(wpre[j >> 5] + (uint32_t)__popc(bm[j >> 5] & ((1u << (j & 31)) - 1u))); };
+    for (int a = a0 + tid / kLanes; a < a0 + nA; a += kThreads / kLanes) {
+        const uint32_t K = (uint32_t)A.tcol[a];
+        const bool in = K < (uint32_t)B.tile_rows;                // (otherwise a non-canonical input)
+        const int b0 = in ? B.trp[K] : 0, b1 = in ? B.tend[K] : 0;
+        const uint2 rows = *reinterpret_cast<const uint2 *>(a_row_mask + (int64_t)a * T + 4 * l);
+        if (b0 >= b1) continue;
+        uint32_t sel[4][8];                                       // of row 4l+i: all ones in the half words whose row of B is wanted
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t bits = i < 2 ? rows.x : rows.y;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)bits, (i & 1) * 16 + 2 * w, 1);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_sbfe((int)bits, (i & 1) * 16 + 2 * w + 1, 1);
+                sel[i][w] = (lo & 0xFFFFu) | (hi & 0xFFFF0000u);
+            }
+        }
+        const unsigned long long me = 1ull << (a - a0);
+        // two pairs per trip, the next two's bitmaps and columns requested before their products are formed (past the end:
+        // the last tile again)
+        const uint4 *const bitmaps = reinterpret_cast<const uint4 *>(b_row_mask);
+        uint4 x[2], y[2];
+        int col[2];
+        auto request = [&](int b) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t at = (uint32_t)min(b + u, b1 - 1);
+                x[u] = element(bitmaps, 2 * at);
+                y[u] = element(bitmaps, 2 * at + 1);
+                col[u] = element(B.tcol, at);
+            }
+        };
+        request(b0);
+        for (int b = b0; b < b1; b += 2) {
+            uint4 x_now[2] = {x[0], x[1]}, y_now[2] = {y[0], y[1]};
+            const uint32_t j_now[2] = {(uint32_t)(col[0] - jmin), b + 1 < b1 ? (uint32_t)(col[1] - jmin) : 0xFFFFFFFFu};
+            request(b + 2);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                uint32_t m[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    m[i] = x_now[u].x & sel[i][0];
+                    m[i] |= x_now[u].y & sel[i][1];
+                    m[i] |= x_now[u].z & sel[i][2];
+                    m[i] |= x_now[u].w & sel[i][3];
+                    m[i] |= y_now[u].x & sel[i][4];
+                    m[i] |= y_now[u].y & sel[i][5];
+                    m[i] |= y_now[u].z & sel[i][6];
+                    m[i] |= y_now[u].w & sel[i][7];
+                }
+                // the sixteen bits of a row are the two halves together: of two rows at a time
+                auto two_rows = [](uint32_t first, uint32_t second) {
+                    return __builtin_amdgcn_perm(second, first, 0x05040100u) | __builtin_amdgcn_perm(second, first, 0x07060302u);
+                };
+                const uint32_t low = two_rows(m[0], m[1]), high = two_rows(m[2], m[3]);
+                uint32_t any = low | high;
+                any |= (uint32_t)TSP_DPP((int)any, (int)any, 0xB1, 0xf, false);   // of the four lanes
+                any |= (uint32_t)TSP_DPP((int)any, (int)any, 0x4E, 0xf, false);
+                if (any && j_now[u] < span) {
+                    const int c = rank(j_now[u]);
+                    atomicOr(&cmask[c * 4 + l], (unsigned long long)high << 32 | low);
+                    if (l == 0) atomicOr(&contrib[c], me);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    {   // pairs of the C tiles before, each wave for itself
+        const int stretch = (nC + 63) >> 6;
+        uint32_t mine = 0;
+        for (int i = 0; i < stretch; ++i) mine += lane * stretch + i < nC ? (uint32_t)__popcll(contrib[lane * stretch + i]) : 0u;
+        uint32_t before = wave_inclusive_scan(mine) - mine;
+        for (int i = 0; i < stretch; ++i) {
+            const int c = lane * stretch + i;
+            if (c >= nC) break;
+            cnt[c] = before;
+            if ((lane & (kThreads / 64 - 1)) == wave) pair_off[c0 + c] = row_base + (int64_t)before;
+            before += (uint32_t)__popcll(contrib[c]);
+        }
+        wave_sync();
+    }
+    for_each_pair([&](int a, int b, uint32_t j) {
+        const int c = rank(j);
+        const int64_t pos = row_base + (int64_t)(cnt[c] + (uint32_t)__popcll(contrib[c] & ((1ull << (a - a0)) - 1ull)));
+        if (pos < pairs_most) pair_ab[pos] = make_int2(a, b);    // (always: both walks see the same pairs)
+    });
+    const uint32_t *const masks = reinterpret_cast<const uint32_t *>(cmask);
+    uint4 *const out = reinterpret_cast<uint4 *>(c_row_mask + (int64_t)c0 * T);
+    for (int w = tid; w < nC * 2; w += kThreads) out[w] = reinterpret_cast<const uint4 *>(cmask)[w];
+    // Lengths of the rows and places of the tiles' entries in them: lane r of every 16 takes CSR row 16I+r for a stretch of
+    // the C tiles, the groups' sums are exchanged through LDS.
+    const int g = tid >> 4, r = tid & 15;
+    constexpr int kGroups = kThreads / 16;
+    const int word = r >> 1, shift = (r & 1) * 16;
+    const int stretch = (nC + kGroups - 1) / kGroups, cb = min(nC, g * stretch), ce = min(nC, cb + stretch);
+    uint32_t part = 0;
+    for (int c = cb; c < ce; ++c) part += __popc((masks[c * 8 + word] >> shift) & 0xFFFFu);
+    s_part[g][r] = part;
+    __syncthreads();
+    uint32_t total = 0, earlier = 0;               // entries of row r in the tile-row, and in the stretches before this one
+#pragma unroll
+    for (int h = 0; h < kGroups; ++h) {
+        const uint32_t v = s_part[h][r];
+        total += v;
+        earlier += h < g ? v : 0u;
+    }
+    uint64_t before = total;                       // inclusive prefix over the 16 rows
+#pragma unroll
+    for (int d = 1; d < T; d <<= 1) {
+        const uint64_t up = __shfl_up(before, d, T);
+        if (r >= d) before += up;
+    }
+    if (g == 0) {
+        const int64_t row = (int64_t)I * T + r;
+        if (row < c_rows) row_nnz[row] = (int32_t)total;
+        if (r == T - 1) {
+            if (before > 0xFFFFFFFFull) d_scalars[S_UNSUPPORTED] = 1;
+            tile_row_entries[I] = (uint32_t)before;
+        }
+    }
+    uint32_t run = (uint32_t)(before - total) + earlier;
+    for (int c = cb; c < ce; ++c) {
+        c_row_off[(int64_t)(c0 + c) * T + r] = run;
+        run += __popc((masks[c * 8 + word] >> shift) & 0xFFFFu);
+    }
+}
+
 // Counting pass (Section 4.2) as a kernel of its own: a block takes 16 consecutive C tiles, whose task-list
 // segments are one contiguous stretch, and every lane takes one entry of the stretch at a time: it fetches
 // the 16 row masks of the A tile and of the B tile (32 bytes each), forms all 16 rows of the boolean
@@ -1647,7 +1871,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         if (!slots) return cleanup(TSP_ERR_ALLOC_FAILED);
         hipLaunchKernelGGL(k_sym_row_scan, dim3((unsigned)blocks), dim3(kRowScanThreads), 0, s, ntr, row_c_tiles,
                            row_pairs, row_words, row_cand, P->c_tile_row_ptr, row_pair_ptr, slots, epoch,
-                           ctx->d_scalars, ca, cb, ctx->h_scalars_dev, ++ctx->publish_tag);
+                           A->tile_row_ptr, A->tile_row_end, ctx->d_scalars, ca, cb, ctx->h_scalars_dev, ++ctx->publish_tag);
         SYM_CHECK(hipGetLastError());
     }
     // Sizes of the task list.  For operands of the sizes of earlier products of this handle that the list kernel has worked
@@ -1686,7 +1910,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     };
     auto true_sizes = [&]() {
         return ListSizes{h[S_C_TILES], h[S_PAIRS], h[S_CANDIDATES], h[S_MAX_ROW_C_TILES], h[S_MAX_ROW_PAIRS], h[S_MAX_ROW_WORDS],
-                         B->ntiles};
+                         h[S_MAX_ROW_A_TILES], B->ntiles};
     };
 list_kernels:
     if (!hinted) {
@@ -1768,7 +1992,14 @@ list_kernels:
         ctx->hint_sizes[1] = A->nnz;
         ctx->hint_sizes[2] = B->rows;
         ctx->hint_sizes[3] = B->nnz;
-        if (listed) {
+        const size_t block_lds = (size_t)(2 * words_cap + 11 * window) * sizeof(uint32_t);
+        if (listed && fused_masks && !halves && z.max_row_a_tiles <= kBlockATiles && block_lds <= kLdsLimit &&
+            std::max(A->tile_capacity, B->tile_capacity) < (int64_t)1 << 27) {         // (32-bit offsets into the bitmaps)
+            hipLaunchKernelGGL(k_sym_emit_block, dim3((unsigned)ntr), dim3(kBlockListThreads),
+                               block_lds, s, ra, rb, words_cap, window, row_jmin, row_words, P->c_tile_row_ptr, row_pair_ptr,
+                               P->c_tile_row, P->c_tile_col, P->pair_off, P->pair_ab, A->row_mask, B->row_mask, P->c_row_mask,
+                               P->c_row_off, row_nnz, P->c_rows, ctx->d_scalars, tile_row_entries, z.c_tiles, z.pairs);
+        } else if (listed) {
             auto kernel = !fused_masks ? (long_rows ? k_sym_emit_listed<true, false, 0> : k_sym_emit_listed<false, false, 0>)
                           : halves     ? (long_rows ? k_sym_emit_listed<true, true, kListTeamLanes> : k_sym_emit_listed<false, true, kListTeamLanes>)
                                        : (long_rows ? k_sym_emit_listed<true, true, 0> : k_sym_emit_listed<false, true, 0>);

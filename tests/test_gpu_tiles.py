@@ -151,3 +151,28 @@ def test_prefix_sums_over_tile_rows(tsp, oracle, tile_rows):
         C.free(), plan.free(), t.free()
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("left_tiles", [1, 31, 32, 33, 63, 64, 65])
+def test_tile_rows_of_many_left_tiles(tsp, oracle, left_tiles):
+    """A tile-row of A with as many tiles as the words of contributors hold, one more and one less, among short ones."""
+    n = 1030
+    rng = np.random.default_rng(left_tiles)
+    A = _full_tiles(rng, n, lambda i: rng.choice(n, left_tiles, replace=False) if i in (7, n - 1) else (np.array([i, i * 5 + 1]) % n))
+    keep = rng.random(A.col_idx.size) < 0.3
+    rows = np.repeat(np.arange(A.rows), np.diff(A.row_ptr))[keep]
+    A = inputs.from_coo(A.rows, A.cols, rows, A.col_idx[keep], rng.uniform(-1, 1, rows.size), "many left tiles")
+    want = oracle.spgemm(A, A, threads=4)
+    h = tsp.Handle(validate=True)
+    try:
+        dA = tsp.to_device(A)
+        for _ in range(2):
+            t = h.convert(dA)
+            plan = h.symbolic(t, t)
+            C = h.numeric(t, t, plan)
+            row_ptr, col, val = C.to_host()
+            assert np.array_equal(row_ptr, want.row_ptr) and np.array_equal(col, want.col)
+            assert np.all(np.abs(val.astype(np.float64) - want.val) <= 1e-5 * want.mag + 1e-7)
+            C.free(), plan.free(), t.free()
+    finally:
+        h.close()
