@@ -42,6 +42,7 @@ enum Scalar {
     S_ROW_RANGE_A = 21,      // magnitude and granularity of the values (ValueRange)
     S_ROW_RANGE_B = 22,
     S_ROW_LONGEST = 23,      // entries of the longest heavy row of A
+    S_ROW_WIDE = 26,         // rows that would be small if a row had 16 lanes
     S_ROW_ARRIVED = 16,      // blocks of k_row_small that are done
     S_LARGE_A = 24,          // tile-rows of an operand whose entries do not fit the registers of k_convert_block
     S_LARGE_B = 25,
@@ -90,6 +91,7 @@ struct RowHint {
     int64_t heavy = 0, tasks = 0;
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows
+    bool wide = false;                             // so many rows of 9 to 16 entries that 16 lanes per row pay
     int sum = 0, scale = 0;                        // how the heavy rows are summed
 };
 

@@ -29,13 +29,16 @@ constexpr int kPlanSums = 8;
 constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
 constexpr int kSpanWindows = 64;         // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
 constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows
-constexpr int kHeavyThreads = 512;
+constexpr int kCountThreads = 256;       // of k_heavy_count
 constexpr int32_t kNoCol = 0x7FFFFFFF;
 // Intermediate products behind one task of k_heavy_fill (a row, or some of its windows)
 constexpr int64_t kKeptPattern = (int64_t)16 << 30;   // bytes of it, at most
 constexpr int64_t kFoundEntries = (int64_t)2 << 30;   // of the small rows before they are moved into C, at most
 constexpr int kTaskProducts = 65536;
-constexpr int64_t kRowPairProducts = 64; // products per candidate pair of tiles up to which the rows are the better way
+
+// Of a tile-row: the entries of its longest heavy row (23 bits hold the columns that k_row_prepare allows), its small rows,
+// and the rows of 9 to 16 entries with no more products than a small row has; of either at most 16.
+__host__ __device__ constexpr uint32_t pack_rows(uint32_t longest, uint32_t small, uint32_t wide) { return longest << 9 | (small * 17u + wide); }
 
 struct RowMatrix {                       // an operand in the form the row kernels read
     int32_t *start = nullptr;            // int32[rows + 1], clamped to [0, nnz]
@@ -65,7 +68,7 @@ struct PrepareArgs {
     int32_t *heavy;                      // rows that are not small
     int4 *tasks;                         // {row, index into heavy, first window, one past the last window}
     int64_t heavy_cap, task_cap;
-    int32_t *rows_of;                    // of every tile-row: 32 * entries of its longest heavy row + its small rows
+    uint32_t *rows_of;                   // of every tile-row: pack_rows()
     int64_t *d_scalars;
 };
 
@@ -262,7 +265,8 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
         }
     }
     const int longest = heavies ? wave_max(tasks > 0 ? deg : 0) : 0, small = __popcll(__ballot(deg > 0 && ub > 0 && tasks == 0));
-    if (lane == 0) a.rows_of[I] = min(longest, (1 << 26) - 1) * 32 + small;
+    const int wide = __popcll(__ballot(deg > 8 && ub > 0 && small_row(deg, (int32_t)ub, 16, a.small_products)));
+    if (lane == 0) a.rows_of[I] = pack_rows((uint32_t)min(longest, (1 << 23) - 1), (uint32_t)small, (uint32_t)wide);
 }
 
 // A store that a block of the same launch on another XCD can read (get_shared), past the L2 caches, which do not see each
@@ -284,13 +288,14 @@ __device__ __forceinline__ X get_shared(const X *p) {
 // 90 us instead of 8 on a 512^2 mesh.)
 struct SumArgs {
     int64_t a_tile_rows, b_tile_rows;
-    const int32_t *a_start, *a_ntiles, *a_tile_col, *b_ntiles, *rows_of;
+    const int32_t *a_start, *a_ntiles, *a_tile_col, *b_ntiles;
+    const uint32_t *rows_of;
     const uint32_t *a_range, *b_range;
     const unsigned long long *products;
     int same;                            // A and B are one matrix
     unsigned long long *partial;         // [kPlanSums][kPlanBlocks]
 };
-enum { kSumCandidates, kSumTilesA, kSumTilesB, kSumProducts, kSumSmall, kSumRanges, kSumLongest };
+enum { kSumCandidates, kSumTilesA, kSumTilesB, kSumProducts, kSumSmall, kSumRanges, kSumLongest, kSumWide };
 
 // Sixteen lanes per tile-row: tiles, candidate pairs (the tiles of B's tile-rows behind the tiles of A: the measure by
 // which tsp_spgemm chooses this path), products, value ranges.
@@ -300,7 +305,7 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
     const int lane = lane_id(), r = threadIdx.x & 15;
     if (threadIdx.x < kPlanSums) s_sum[threadIdx.x] = s_max[threadIdx.x] = 0;
     __syncthreads();
-    unsigned long long cand = 0, tiles_a = 0, tiles_b = 0, products = 0, small = 0;
+    unsigned long long cand = 0, tiles_a = 0, tiles_b = 0, products = 0, small = 0, wide = 0;
     uint32_t range_a = 0, range_b = 0;
     int longest = 0;
     const int64_t most = max(a.a_tile_rows, a.same ? (int64_t)0 : a.b_tile_rows);
@@ -318,9 +323,10 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
                 tiles_a += (unsigned)n;
                 range_a = range_max(range_a, a.a_range[I]);
                 products += a.products[I];
-                const int32_t rows_of = a.rows_of[I];
-                longest = max(longest, rows_of >> 5);
-                small += rows_of & 31;
+                const uint32_t rows_of = a.rows_of[I], rows = rows_of & 511u;
+                longest = max(longest, (int)(rows_of >> 9));
+                small += rows / 17u;
+                wide += rows % 17u;
             }
             for (int32_t j = r; j < min(n, 64); j += 16) {
                 const int32_t K = a.a_tile_col[e0 + j];
@@ -350,6 +356,7 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
     add(kSumTilesB, tiles_b);
     add(kSumProducts, products);
     add(kSumSmall, small);
+    add(kSumWide, wide);
     auto most_of = [&](int slot, int v) {
         v = wave_max(v);
         if (lane == 0 && v) atomicMax(&s_max[slot], (unsigned long long)v);
@@ -494,6 +501,7 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
         own[S_TILES_B] = (int64_t)(a.same ? s_sum[kSumTilesA] : s_sum[kSumTilesB]);
         own[S_ROW_PRODUCTS] = (int64_t)s_sum[kSumProducts];
         own[S_ROW_SMALL] = (int64_t)s_sum[kSumSmall];
+        own[S_ROW_WIDE] = (int64_t)s_sum[kSumWide];
         const int from = a.same ? 0 : 2;
         own[S_ROW_RANGE_A] = (int64_t)(s_max[0] << 16 | s_max[1]);
         own[S_ROW_RANGE_B] = (int64_t)(s_max[from] << 16 | s_max[from + 1]);
@@ -507,7 +515,7 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
         }
     }
     constexpr uint32_t kOwn = own_slot(S_C_NNZ) | own_slot(S_CANDIDATES) | own_slot(S_TILES_A) | own_slot(S_TILES_B) |
-                              own_slot(S_ROW_PRODUCTS) | own_slot(S_ROW_SMALL) | own_slot(S_ROW_RANGE_A) | own_slot(S_ROW_RANGE_B) |
+                              own_slot(S_ROW_PRODUCTS) | own_slot(S_ROW_SMALL) | own_slot(S_ROW_WIDE) | own_slot(S_ROW_RANGE_A) | own_slot(S_ROW_RANGE_B) |
                               own_slot(S_ROW_LONGEST) | own_slot(S_ROW_HEAVY) | own_slot(S_ROW_TASKS);
     publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, standing, own, kOwn, a.clear);
 }
@@ -906,10 +914,12 @@ struct CountArgs {
 
 // A block per heavy row ORs the words of the rows of B behind it into one bit per column in LDS; OR is free of order, so
 // the row may be spread over the block: entry i of the row of A goes to wave i mod the number of waves that get 16 and more.
+// Four waves: light rows are bound by the block's own steps (a graph's 4100 rows of 165 entries 114 -> 103 us for the whole
+// product with 8 -> 4 waves), heavy ones by the words they stream (R-MAT scale 14, 680 -> 660; scale 18, no difference).
 template <int kWin>
-__global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a) {
+__global__ __launch_bounds__(kCountThreads) void k_heavy_count(const CountArgs a) {
     extern __shared__ __align__(16) uint32_t bits[];
-    constexpr int kWaves = kHeavyThreads / 64;
+    constexpr int kWaves = kCountThreads / 64;
     __shared__ PieceLds s_piece[kWaves];
     __shared__ uint32_t s_cnt[kSpanWindows];
     __shared__ uint32_t s_run;
@@ -920,7 +930,7 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a
     const int32_t row = a.heavy[h];
     const int32_t s = a.a_start[row], e = a.a_start[row + 1];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    for (int w = threadIdx.x; w < a.span_windows * kWords + 64; w += kHeavyThreads) bits[w] = 0;
+    for (int w = threadIdx.x; w < a.span_windows * kWords + 64; w += kCountThreads) bits[w] = 0;
     if (threadIdx.x == 0) s_run = 0;
     const int dealt = min(kWaves, (e - s + 15) / 16);
     for (int w0 = 0; w0 < a.windows; w0 += a.span_windows) {
@@ -958,7 +968,7 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(const CountArgs a
             });
         }
         __syncthreads();
-        for (int w = wave; w < w1 - w0; w += kHeavyThreads / 64) {
+        for (int w = wave; w < w1 - w0; w += kCountThreads / 64) {
             uint32_t n = 0, word[kPerLane];
 #pragma unroll
             for (int i = 0; i < kPerLane; ++i) {
@@ -1025,10 +1035,14 @@ struct FillArgs {
 // fixes the order of the additions.  64-bit integers: p * 2^k + 1.5 * 2^52 in fp64 holds the integer p * 2^k in its low
 // bits (|p * 2^k| < 2^51).
 constexpr int kSpanColumns = 1 << 16;    // the elements of B hold 16 bits of the column
+// The table of a C of at most so many columns is a quarter as long, which is what many light rows spend their time on:
+// 6000 rows of 60 entries, 6000 columns, 139 -> 119 us; with more columns a row takes more steps (R-MAT scale 17, 2.75 ->
+// 3.05 ms with a table of 32768 columns, 3.67 with one of 16384; scales 13 and 14 the same with either).
+constexpr int kNarrowColumns = 1 << 14;
 
-template <typename Acc, int kCap, int kThreads>
+template <typename Acc, int kCap, int kThreads, int kSpan>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThreads == 64 ? 1 : 8, 8))) void k_heavy_fill(const FillArgs a) {
-    constexpr int kWaves = kThreads / 64, kWords = kSpanColumns / 32;
+    constexpr int kWaves = kThreads / 64, kWords = kSpan / 32;
     __shared__ __align__(16) Acc acc[kCap + 64];               // (behind the entries a place per lane for lanes without an element)
     __shared__ __align__(16) int2 places[kWords];              // {bits of 32 columns, entries before them, less one}
     __shared__ PieceLds s_piece[kWaves];
@@ -1056,7 +1070,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
     // the end of the step that begins at window v: lane i says whether window v + i still fits
     auto step_end = [&](int v, uint32_t first) {
         const int last = v + lane + 1;
-        const bool fits = last <= w_end && lane < (kSpanColumns >> a.window_shift) &&
+        const bool fits = last <= w_end && lane < (kSpan >> a.window_shift) &&
                           (last < a.windows ? offset[last] : row_len) - first <= (uint32_t)kCap;
         return v + max(__popcll(__ballot(fits)), 1);
     };
@@ -1111,7 +1125,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
                 }
                 stream_pieces<kThreads == 64 ? 64 : 16, uint32_t>(
                     p, len, own, a.pack, &s_piece[wave], [&](uint32_t x, bool active, uint32_t a16) {
-                        const uint32_t c = (x - c0) & (uint32_t)(kSpanColumns - 1);
+                        const uint32_t c = (x - c0) & (uint32_t)(kSpan - 1);
                         const int2 place = places[c >> 5];
                         const int rank = __popc((uint32_t)place.x << (31u - (c & 31u))) + place.y;
                         const int at = active ? min(rank, kCap) : kCap + lane;
@@ -1191,7 +1205,8 @@ void launch_prepare(const PrepareArgs<RP, VT> &a, hipStream_t s) {
 
 // What k_row_prepare needs beyond the operand, for A (null members for B)
 struct LeftOperand {
-    int32_t *ub, *rows_of;
+    int32_t *ub;
+    uint32_t *rows_of;
     unsigned long long *products;
     const tsp_csr *B;
     SmallShape shape;
@@ -1244,9 +1259,12 @@ void launch_fill(FillArgs &f, FillKind kind, hipStream_t s) {
     };
     f.p_scale = std::ldexp(1.0f, -kind.scale);
     f.c_scale = std::ldexp(1.0f, kind.scale);
-    if (kind.sum == FillKind::kInt32) launch(k_heavy_fill<int32_t, 4096, 512>, 512);
-    else if (kind.sum == FillKind::kInt64) launch(k_heavy_fill<long long, 4096, 512>, 512);
-    else launch(k_heavy_fill<double, 4096, 64>, 64);
+    const bool narrow = (int64_t)f.windows << f.window_shift <= kNarrowColumns;
+    if (kind.sum == FillKind::kInt32)
+        launch(narrow ? k_heavy_fill<int32_t, 4096, 512, kNarrowColumns> : k_heavy_fill<int32_t, 4096, 512, kSpanColumns>, 512);
+    else if (kind.sum == FillKind::kInt64)
+        launch(narrow ? k_heavy_fill<long long, 4096, 512, kNarrowColumns> : k_heavy_fill<long long, 4096, 512, kSpanColumns>, 512);
+    else launch(k_heavy_fill<double, 4096, 64, kSpanColumns>, 64);
 }
 
 }  // namespace
@@ -1255,8 +1273,15 @@ __global__ void k_clear_lists(int64_t *d_scalars) {
     if (threadIdx.x == 0) d_scalars[S_ROW_LISTS] = 0;
 }
 
-// The product A*B has so few intermediate products per candidate pair of tiles that the row kernels are faster.
-static bool rows_preferred(int64_t products, int64_t candidates) { return products <= kRowPairProducts * candidates; }
+// Whether the row kernels are faster for A*B than the tile kernels: what the two take beyond the 30 us that both do, from
+// times of 90 products of meshes, stencils, blocks, random and power-law graphs (in ns).  Rows: 13 per heavy row, 1 per
+// thousand products behind it, 1 per thousand products of the small rows and lane of such a row.  Tiles: 30 us (more
+// launches) and 0.15 per candidate pair of tiles, which is what they cost at least.  So a stencil or dense blocks go by tiles
+// from 2500 rows on (27 points on a 24^3 grid: 83 us, by rows 157), a mesh, graph or random matrix by rows (a 300^2 mesh: 42
+// us, by tiles 73; 4000 rows of 73 entries at random: 105, 739).  The two lie within 20 % of one another about the line.
+static bool rows_preferred(int64_t products, int64_t small_products, int lanes, int64_t heavy, int64_t candidates) {
+    return 13 * heavy + products / 1000 + lanes * (small_products / 1000) <= 30000 + candidates / 20 * 3;
+}
 
 int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s,
                    bool *taken) {
@@ -1273,10 +1298,12 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
 
     if (A->nnz >= (1 << 28) || B->nnz >= (1 << 28)) return TSP_OK;      // (32-bit byte offsets into 8-byte records)
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
-    // Small rows: 8 lanes where the mean row of A has no more entries, else 16; for a row of B as many as its mean has
+    // Small rows: 8 lanes where the mean row of A has no more entries, else 16, or where the last product of these sizes had
+    // more than one row in 64 that is small but for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the
+    // lanes 0.1 ns per row); for a row of B as many as its mean has
     // entries; a table of the row that is three quarters full at most, with a margin over the mean number of products, 256
     // slots at most
-    SmallShape shape{A->nnz <= 8 * A->rows ? 8 : 16, 1, 32, 24};
+    SmallShape shape{A->nnz <= 8 * A->rows && !(known && hint.wide) ? 8 : 16, 1, 32, 24};
     {
         const double list = (double)B->nnz / (double)std::max<int64_t>(B->rows, 1), mean = (double)A->nnz / (double)A->rows * list;
         while (shape.slots < 256 && shape.slots * 3 / 4 < 1.25 * mean) shape.slots *= 2;
@@ -1312,7 +1339,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     const int64_t chunks = (A->rows + kChunkRows - 1) / kChunkRows;
     LeftOperand left{};
     left.ub = ws.get<int32_t>((size_t)A->rows);
-    left.rows_of = ws.get<int32_t>((size_t)a_ntr);
+    left.rows_of = ws.get<uint32_t>((size_t)a_ntr);
     left.products = ws.get<unsigned long long>((size_t)a_ntr);
     left.B = B;
     left.shape = shape;
@@ -1399,7 +1426,10 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         n_heavy = h[S_ROW_HEAVY];
         n_tasks = h[S_ROW_TASKS];
         std::copy(sizes, sizes + 6, hint.sizes);
-        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
+        hint.wide = h[S_ROW_WIDE] > A->rows / 64;
+        const int64_t heavy = shape.lanes == 8 && hint.wide ? n_heavy - std::min(n_heavy, h[S_ROW_WIDE]) : n_heavy;
+        const int64_t small = std::min(h[S_ROW_PRODUCTS], (A->rows - heavy) * shape.products);      // (at most)
+        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : shape.lanes, heavy, h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
         hint.small = h[S_ROW_SMALL] > 0;
@@ -1429,7 +1459,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     auto count_heavy = [&](int64_t rows) {
         const size_t lds = ((size_t)c.span_windows << (shift - 3)) + 256;
         auto kernel = shift == 11 ? k_heavy_count<2048> : k_heavy_count<4096>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(kHeavyThreads), lds, s, c);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(kCountThreads), lds, s, c);
     };
     // heavy rows whose pattern is kept at a time
     auto pattern_rows = [&](int64_t heavy) { return std::min(heavy, std::max<int64_t>(kKeptPattern / (((int64_t)windows << shift) / 8), 1)); };

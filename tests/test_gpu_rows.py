@@ -96,9 +96,30 @@ def test_same_sizes_another_structure(tsp, oracle):
             A = exact(lengths)
             assert A.nnz == 6 * n
             _check(h, tsp, oracle, A, calls=1)
-        block = inputs.block_clustered(2048, seed=9)
+        block = inputs.block_clustered(8192, seed=9)
         _check(h, tsp, oracle, block, by_rows=False)
         _check(h, tsp, oracle, exact(even))
+    finally:
+        h.close()
+
+
+def test_more_lanes_for_rows_of_up_to_16_entries(tsp, oracle):
+    """The lanes of a small row follow the last product of the same sizes: rows of 9 and of 16 entries, small but for the
+    eight lanes of a mean row, come and go."""
+    n, rng = 1600, np.random.default_rng(8)
+    even, nine, most = np.full(n, 4), np.full(n, 3), np.full(n, 2)
+    nine[::6] = 9
+    nine[1:3] -= 1
+    most[::7] = 16
+    most[1:4] -= 2
+    assert nine.sum() == most.sum() == even.sum()
+    h = tsp.Handle()
+    try:
+        for lengths in (even, nine, nine, even, most, most, nine):
+            cols = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths])
+            A = inputs.from_coo(n, n, np.repeat(np.arange(n), lengths), cols, rng.uniform(-1, 1, cols.size))
+            B = inputs.random_fixed_per_row(n, 1, seed=4)
+            _check(h, tsp, oracle, A, B, calls=1, by_rows=True)
     finally:
         h.close()
 
