@@ -1967,8 +1967,13 @@ list_kernels:
         const int list_cap = (int)std::max<int64_t>(z.max_row_pairs, 1);
         int team_words = 0;
         bool halves = false;
+        const size_t block_lds = (size_t)(2 * words_cap + 11 * window) * sizeof(uint32_t);
+        const bool by_block = z.max_row_a_tiles <= kBlockATiles && block_lds <= kLdsLimit &&
+                              std::max(A->tile_capacity, B->tile_capacity) < (int64_t)1 << 27;    // (32-bit offsets into the bitmaps)
         if (listed) {
-            fused_masks = ntr >= 1024;
+            // (k_sym_emit_block at any number of tile-rows: with the counting pass and the row offsets in launches of their
+            // own the product of 300 blocks of 16x16, 48 entries per row, takes 59 us instead of 49)
+            fused_masks = ntr >= 1024 || by_block;
             team_words = 2 * words_cap + 2 * window + 3 * list_cap + (fused_masks ? 8 * window : 0);
             // tile-rows with few candidates: two per wave (see k_sym_count_half), where there are more of them than the
             // chip holds blocks of two waves (36 pairs per tile-row, 1536 tile-rows: 12 us with a block each, 18 us so; 16
@@ -1992,9 +1997,7 @@ list_kernels:
         ctx->hint_sizes[1] = A->nnz;
         ctx->hint_sizes[2] = B->rows;
         ctx->hint_sizes[3] = B->nnz;
-        const size_t block_lds = (size_t)(2 * words_cap + 11 * window) * sizeof(uint32_t);
-        if (listed && fused_masks && !halves && z.max_row_a_tiles <= kBlockATiles && block_lds <= kLdsLimit &&
-            std::max(A->tile_capacity, B->tile_capacity) < (int64_t)1 << 27) {         // (32-bit offsets into the bitmaps)
+        if (listed && fused_masks && !halves && by_block) {
             hipLaunchKernelGGL(k_sym_emit_block, dim3((unsigned)ntr), dim3(kBlockListThreads),
                                block_lds, s, ra, rb, words_cap, window, row_jmin, row_words, P->c_tile_row_ptr, row_pair_ptr,
                                P->c_tile_row, P->c_tile_col, P->pair_off, P->pair_ab, A->row_mask, B->row_mask, P->c_row_mask,
