@@ -64,7 +64,7 @@ struct LiveBlock {           // a block handed out: with canaries the caller's p
 struct ListSizes {
     int64_t c_tiles = 0, pairs = 0, candidates = 0, max_row_c_tiles = 0, max_row_pairs = 0, max_row_words = 0,
             max_row_a_tiles = 0, b_tiles = 0;
-    bool holds(const ListSizes &o) const {
+    __host__ __device__ bool holds(const ListSizes &o) const {
         return o.c_tiles <= c_tiles && o.pairs <= pairs && o.max_row_c_tiles <= max_row_c_tiles &&
                o.max_row_pairs <= max_row_pairs && o.max_row_words <= max_row_words &&
                o.max_row_a_tiles <= max_row_a_tiles;
@@ -80,6 +80,21 @@ struct ListHint {
     int64_t sizes[5] = {-1, -1, -1, -1, -1};
     bool usable = false;
     ListSizes most;
+    int64_t nnz = -1, c_tiles = 0, a_tiles = 0;    // of the last one
+    int64_t max_row_entries = 0;
+};
+// What the multiplication has been launched with before the host knows the sizes; k_row_ptr sees whether it holds
+struct ListExpected {
+    ListSizes most;
+    int64_t nnz, max_row_entries;
+    static __host__ __device__ ListSizes sizes(const int64_t *scalars) {
+        return ListSizes{scalars[S_C_TILES], scalars[S_PAIRS], scalars[S_CANDIDATES], scalars[S_MAX_ROW_C_TILES], scalars[S_MAX_ROW_PAIRS],
+                         scalars[S_MAX_ROW_WORDS], scalars[S_MAX_ROW_A_TILES], 0};
+    }
+    __host__ __device__ bool holds(const int64_t *scalars) const {
+        return !scalars[S_INVALID] && !scalars[S_UNSUPPORTED] && !scalars[S_INTERNAL] && most.holds(sizes(scalars)) &&
+               scalars[S_C_NNZ] <= nnz && scalars[S_MAX_ROW_ENTRIES] <= max_row_entries;
+    }
 };
 
 // What the row kernels found for the last product (rowwise.hip), by the sizes of its operands: whether the tile kernels
@@ -231,15 +246,30 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
 int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out,
                     hipStream_t s);
 void tiles_release(tsp_context *ctx, tsp_tiles_s *t, hipStream_t s);
-int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **out, hipStream_t s);
+// C of a multiplication that symbolic_run has launched itself (`done`): its arrays
+struct TilesAhead {
+    int32_t *col = nullptr;
+    float *val = nullptr;
+    bool done = false;
+};
+int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **out, hipStream_t s, TilesAhead *ahead = nullptr);
 void plan_release(tsp_context *ctx, tsp_plan_s *p, hipStream_t s);
 // Order of work in vertical strips for the kernels that walk the task list of a plan with long tile-rows.
 int strips_build(tsp_context *ctx, tsp_plan_s *P, const tsp_tiles_s *B, hipStream_t s);
 // last_of_call (tsp_spgemm): C gets the plan's row_ptr array itself instead of a copy, so the plan cannot
 // be used again, and the kernel zeroes the handle's scalar block, which nothing reads any more, for the
 // next call (one launch less per call).
+// ahead: the kernel has been launched (numeric_launch) into these arrays.
 int numeric_enqueue(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s *plan, tsp_csr *C,
-                    hipStream_t s, bool last_of_call = false);
+                    hipStream_t s, bool last_of_call = false, const TilesAhead *ahead = nullptr);
+// The sizes by which the multiplication kernel is chosen and launched
+struct NumericLaunch {
+    int64_t c_tiles, pairs, c_nnz, max_row_c_tiles, max_row_pairs, max_row_entries, a_tiles, b_tiles;
+    int64_t *to_clear, *row_ptr_copy;        // or null
+    const int32_t *live;                     // or null: {whether to run at all, output tiles}, where the sizes are bounds only
+};
+hipError_t numeric_launch(tsp_context *ctx, const tsp_tiles_s *A, const tsp_tiles_s *B, const tsp_plan_s *P, const NumericLaunch &n,
+                          int32_t *col, float *val, hipStream_t s);
 // taken (may be null): the caller owns C and gives it up; when no entry is zero *out takes C's arrays as they
 // are (no copy) and *taken is set, so that the caller does not free them.
 int compact_zeros(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStream_t s, bool *taken);

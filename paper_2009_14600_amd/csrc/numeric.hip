@@ -152,14 +152,18 @@ __device__ __forceinline__ void swap_rows(float &x, float &y, bool halves) {
 // step takes four of them, of up to four different pairs: 0.29 steps and operand loads per pair instead of 0.5.
 template <bool kNarrow, int kTilesPerWave, bool kMatrixCores, bool kWholeRows = false, bool kHalves = false>
 __global__ __launch_bounds__(kNumThreads) void k_numeric(
-    const int64_t c_tiles, const int64_t c_nnz, const NumericSizes z, const int64_t c_rows, const int32_t c_tile_rows,
+    int64_t c_tiles, const int64_t c_nnz, const NumericSizes z, const int64_t c_rows, const int32_t c_tile_rows,
     const int32_t *__restrict__ c_tile_row_ptr, const int64_t *__restrict__ pair_off,
     const int2 *__restrict__ pair_ab_, const uint2 *__restrict__ a_lhead_,
     const uint4 *__restrict__ a_ldata_, const uint2 *__restrict__ b_rhead_, const uint4 *__restrict__ b_rdata_, const int32_t *__restrict__ c_tile_row,
     const int32_t *__restrict__ c_tile_col, const uint16_t *__restrict__ c_row_mask,
     const uint32_t *__restrict__ c_row_off, const int64_t *__restrict__ c_row_ptr, int32_t *__restrict__ c_col,
     float *__restrict__ c_val, int64_t *__restrict__ scalars_to_clear, const int2 *__restrict__ strip_desc,
-    const int32_t *__restrict__ strip_total, const int xcd_chunk, int64_t *__restrict__ row_ptr_copy) {
+    const int32_t *__restrict__ strip_total, const int xcd_chunk, int64_t *__restrict__ row_ptr_copy, const int32_t *__restrict__ live) {
+    if (live) {                                        // (launched before the host knew the sizes)
+        if (!uniform_load(live)) return;
+        c_tiles = min(c_tiles, (int64_t)uniform_load(live + 1));
+    }
     if (row_ptr_copy)                                  // (a plan that is kept: C gets row pointers of its own)
         for (int64_t i = (int64_t)blockIdx.x * kNumThreads + threadIdx.x; i <= c_rows; i += (int64_t)gridDim.x * kNumThreads)
             row_ptr_copy[i] = c_row_ptr[i];
@@ -551,76 +555,85 @@ __global__ __launch_bounds__(kNumThreads) void k_numeric(
     }
 }
 
+hipError_t numeric_launch(tsp_context *ctx, const tsp_tiles_s *A, const tsp_tiles_s *B, const tsp_plan_s *P, const NumericLaunch &n,
+                          int32_t *col, float *val, hipStream_t s) {
+    KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
+    // Tiles one wave walks: one group of four measured fastest on all workloads (more waves in
+    // flight); two groups per wave remain available through TSP_OPT_NUMERIC_RUN.
+    int tiles_per_wave = kGroupTiles;
+    if (ctx->numeric_run_len == 4 || ctx->numeric_run_len == 8) tiles_per_wave = ctx->numeric_run_len;
+    if (!ctx->matrix_cores) tiles_per_wave = kGroupTiles;
+    // Short, sparse tile-rows (meshes in two dimensions, for one): a wave per tile-row, output through LDS
+    const bool whole_rows = ctx->matrix_cores && ctx->numeric_run_len == 0 && n.max_row_c_tiles <= kRowTiles &&
+                            n.max_row_pairs <= kBlockEntries && n.max_row_entries <= kRowEntries;
+    const int64_t tiles_per_block = (int64_t)(kNumThreads / 64) * tiles_per_wave;
+    int64_t blocks = whole_rows ? (P->c_tile_rows + kNumThreads / 64 - 1) / (kNumThreads / 64)
+                                : (n.c_tiles + tiles_per_block - 1) / tiles_per_block;
+    const bool strips = P->strip_desc && !whole_rows && tiles_per_wave == kGroupTiles;
+    static_assert(kGroupTiles * (kNumThreads / 64) == 16, "a strip descriptor names the 16 tiles of one block");
+    if (strips) blocks = P->strip_capacity;
+    // Consecutive blocks share tiles of B, so they should share an L2 cache: on even products every XCD
+    // takes one contiguous eighth of the blocks; where a few tile-rows are far heavier than the rest
+    // (hubs of a power-law graph sit at the low indices) short runs of blocks are dealt to the XCDs in turn
+    const bool skewed = n.max_row_pairs > 8 * (n.pairs / std::max<int64_t>(P->c_tile_rows, 1) + 1);
+    const int xcd_chunk = skewed || strips ? 8 : (int)std::max<int64_t>((blocks + kXcds - 1) / kXcds, 1);
+    blocks = xcd_chunked_grid(blocks, xcd_chunk);
+    const NumericSizes z{(uint64_t)n.pairs, (uint64_t)A->tile_capacity, (uint64_t)B->tile_capacity,
+                         (uint64_t)A->group_capacity, (uint64_t)B->group_capacity};
+    const uint64_t limit = (1ull << 32) - 64;
+    const bool narrow = z.pairs * 8 < limit && z.a_groups * 16 < limit && z.b_groups * 16 < limit &&
+                        z.a_tiles * 8 < limit && z.b_tiles * 8 < limit && (uint64_t)n.c_tiles * T * 4 < limit &&
+                        (uint64_t)n.c_nnz * 4 < limit && !ctx->force_wide;
+    auto kernel = narrow ? (tiles_per_wave == 4 ? k_numeric<true, 4, true> : k_numeric<true, 8, true>)
+                         : (tiles_per_wave == 4 ? k_numeric<false, 4, true> : k_numeric<false, 8, true>);
+    // operands whose tiles hold a handful of entries: a step takes the halves that meet (see kHalves)
+    const bool sparse_tiles = ctx->matrix_cores && tiles_per_wave == kGroupTiles && n.a_tiles > 0 && n.b_tiles > 0 &&
+                              A->nnz <= kSparseTileEntries * n.a_tiles && B->nnz <= kSparseTileEntries * n.b_tiles;
+    if (sparse_tiles) kernel = narrow ? k_numeric<true, 4, true, false, true> : k_numeric<false, 4, true, false, true>;
+    if (!ctx->matrix_cores) kernel = narrow ? k_numeric<true, 4, false> : k_numeric<false, 4, false>;
+    if (whole_rows && n.max_row_c_tiles <= kRowTilesUnrolled)
+        kernel = narrow ? k_numeric<true, kRowTilesUnrolled, true, true> : k_numeric<false, kRowTilesUnrolled, true, true>;
+    else if (whole_rows)
+        kernel = narrow ? k_numeric<true, kRowTiles, true, true> : k_numeric<false, kRowTiles, true, true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kNumThreads), 0, s, n.c_tiles, n.c_nnz, z, P->c_rows,
+                       (int32_t)P->c_tile_rows, P->c_tile_row_ptr, P->pair_off,
+                       P->pair_ab, A->lhead, A->ldata, B->rhead, B->rdata,
+                       P->c_tile_row, P->c_tile_col, P->c_row_mask, P->c_row_off, P->c_row_ptr, col, val,
+                       n.to_clear,
+                       strips ? P->strip_desc : nullptr, strips ? P->strip_block_ptr + P->strip_entries : nullptr,
+                       xcd_chunk, n.row_ptr_copy, n.live);
+    return hipGetLastError();
+}
+
 int numeric_enqueue(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s *P, tsp_csr *C, hipStream_t s,
-                    bool last_of_call) {
+                    bool last_of_call, const TilesAhead *ahead) {
     std::memset(C, 0, sizeof(*C));
     if (!(A->forms & TSP_FORM_LEFT) || !(B->forms & TSP_FORM_RIGHT)) return TSP_ERR_INVALID_ARG;
     if (A->cols != B->rows || P->c_rows != A->rows || P->c_cols != B->cols) return TSP_ERR_SHAPE_MISMATCH;
     if (!P->c_row_ptr) return TSP_ERR_INVALID_ARG;                       // a plan whose row_ptr has been handed over
     int64_t *row_ptr = last_of_call ? P->c_row_ptr : ctx_alloc_n<int64_t>(ctx, (size_t)P->c_rows + 1, s);
-    int32_t *col = ctx_alloc_n<int32_t>(ctx, (size_t)P->c_nnz, s);
-    float *val = ctx_alloc_n<float>(ctx, (size_t)P->c_nnz, s);
+    const bool launched = ahead && ahead->done;
+    int32_t *col = launched ? ahead->col : ctx_alloc_n<int32_t>(ctx, (size_t)P->c_nnz, s);
+    float *val = launched ? ahead->val : ctx_alloc_n<float>(ctx, (size_t)P->c_nnz, s);
     if (!row_ptr || !col || !val) {
         if (!last_of_call) ctx_free(ctx, row_ptr, s);
         ctx_free(ctx, col, s);
         ctx_free(ctx, val, s);
         return TSP_ERR_ALLOC_FAILED;
     }
-    phase_begin(ctx, TSP_PHASE_NUMERIC, s);
+    if (!launched) phase_begin(ctx, TSP_PHASE_NUMERIC, s);
     hipError_t e = hipSuccess;
     int64_t *const to_clear = last_of_call && !ctx->scalars_clean ? ctx->d_scalars : nullptr;
     if (!last_of_call && P->c_tiles == 0)
         e = hipMemcpyAsync(row_ptr, P->c_row_ptr, sizeof(int64_t) * (size_t)(P->c_rows + 1), hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess && P->c_tiles > 0) {
-        KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
-        // Tiles one wave walks: one group of four measured fastest on all workloads (more waves in
-        // flight); two groups per wave remain available through TSP_OPT_NUMERIC_RUN.
-        int tiles_per_wave = kGroupTiles;
-        if (ctx->numeric_run_len == 4 || ctx->numeric_run_len == 8) tiles_per_wave = ctx->numeric_run_len;
-        if (!ctx->matrix_cores) tiles_per_wave = kGroupTiles;
-        // Short, sparse tile-rows (meshes in two dimensions, for one): a wave per tile-row, output through LDS
-        const bool whole_rows = ctx->matrix_cores && ctx->numeric_run_len == 0 && P->max_row_c_tiles <= kRowTiles &&
-                                P->max_row_pairs <= kBlockEntries && P->max_row_entries <= kRowEntries;
-        const int64_t tiles_per_block = (int64_t)(kNumThreads / 64) * tiles_per_wave;
-        int64_t blocks = whole_rows ? (P->c_tile_rows + kNumThreads / 64 - 1) / (kNumThreads / 64)
-                                    : (P->c_tiles + tiles_per_block - 1) / tiles_per_block;
-        const bool strips = P->strip_desc && !whole_rows && tiles_per_wave == kGroupTiles;
-        static_assert(kGroupTiles * (kNumThreads / 64) == 16, "a strip descriptor names the 16 tiles of one block");
-        if (strips) blocks = P->strip_capacity;
-        // Consecutive blocks share tiles of B, so they should share an L2 cache: on even products every XCD
-        // takes one contiguous eighth of the blocks; where a few tile-rows are far heavier than the rest
-        // (hubs of a power-law graph sit at the low indices) short runs of blocks are dealt to the XCDs in turn
-        const bool skewed = P->max_row_pairs > 8 * (P->pairs / std::max<int64_t>(P->c_tile_rows, 1) + 1);
-        const int xcd_chunk = skewed || strips ? 8 : (int)std::max<int64_t>((blocks + kXcds - 1) / kXcds, 1);
-        blocks = xcd_chunked_grid(blocks, xcd_chunk);
-        const NumericSizes z{(uint64_t)P->pairs, (uint64_t)A->tile_capacity, (uint64_t)B->tile_capacity,
-                             (uint64_t)A->group_capacity, (uint64_t)B->group_capacity};
-        const uint64_t limit = (1ull << 32) - 64;
-        const bool narrow = z.pairs * 8 < limit && z.a_groups * 16 < limit && z.b_groups * 16 < limit &&
-                            z.a_tiles * 8 < limit && z.b_tiles * 8 < limit && (uint64_t)P->c_tiles * T * 4 < limit &&
-                            (uint64_t)P->c_nnz * 4 < limit && !ctx->force_wide;
-        auto kernel = narrow ? (tiles_per_wave == 4 ? k_numeric<true, 4, true> : k_numeric<true, 8, true>)
-                             : (tiles_per_wave == 4 ? k_numeric<false, 4, true> : k_numeric<false, 8, true>);
-        // operands whose tiles hold a handful of entries: a step takes the halves that meet (see kHalves)
-        const bool sparse_tiles = ctx->matrix_cores && tiles_per_wave == kGroupTiles && A->ntiles > 0 && B->ntiles > 0 &&
-                                  A->nnz <= kSparseTileEntries * A->ntiles && B->nnz <= kSparseTileEntries * B->ntiles;
-        if (sparse_tiles) kernel = narrow ? k_numeric<true, 4, true, false, true> : k_numeric<false, 4, true, false, true>;
-        if (!ctx->matrix_cores) kernel = narrow ? k_numeric<true, 4, false> : k_numeric<false, 4, false>;
-        if (whole_rows && P->max_row_c_tiles <= kRowTilesUnrolled)
-            kernel = narrow ? k_numeric<true, kRowTilesUnrolled, true, true> : k_numeric<false, kRowTilesUnrolled, true, true>;
-        else if (whole_rows)
-            kernel = narrow ? k_numeric<true, kRowTiles, true, true> : k_numeric<false, kRowTiles, true, true>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kNumThreads), 0, s, P->c_tiles, P->c_nnz, z, P->c_rows,
-                           (int32_t)P->c_tile_rows, P->c_tile_row_ptr, P->pair_off,
-                           P->pair_ab, A->lhead, A->ldata, B->rhead, B->rdata,
-                           P->c_tile_row, P->c_tile_col, P->c_row_mask, P->c_row_off, P->c_row_ptr, col, val,
-                           to_clear,
-                           strips ? P->strip_desc : nullptr, strips ? P->strip_block_ptr + P->strip_entries : nullptr,
-                           xcd_chunk, last_of_call ? nullptr : row_ptr);
-        if (to_clear && hipPeekAtLastError() == hipSuccess) ctx->scalars_clean = true;
-        e = hipGetLastError();
+    if (e == hipSuccess && P->c_tiles > 0 && !launched) {
+        e = numeric_launch(ctx, A, B, P,
+                           {P->c_tiles, P->pairs, P->c_nnz, P->max_row_c_tiles, P->max_row_pairs, P->max_row_entries, A->ntiles, B->ntiles,
+                            to_clear, last_of_call ? nullptr : row_ptr, nullptr},
+                           col, val, s);
+        if (to_clear && e == hipSuccess) ctx->scalars_clean = true;
     }
-    phase_end(ctx, TSP_PHASE_NUMERIC, s);
+    if (!launched) phase_end(ctx, TSP_PHASE_NUMERIC, s);
     if (e != hipSuccess) {
         if (!last_of_call) ctx_free(ctx, row_ptr, s);
         ctx_free(ctx, col, s);

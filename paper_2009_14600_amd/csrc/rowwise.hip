@@ -1275,12 +1275,12 @@ __global__ void k_clear_lists(int64_t *d_scalars) {
 
 // Whether the row kernels are faster for A*B than the tile kernels: what the two take beyond the 30 us that both do, from
 // times of 90 products of meshes, stencils, blocks, random and power-law graphs (in ns).  Rows: 13 per heavy row, 1 per
-// thousand products behind it, 1 per thousand products of the small rows and lane of such a row.  Tiles: 30 us (more
-// launches) and 0.15 per candidate pair of tiles, which is what they cost at least.  So a stencil or dense blocks go by tiles
-// from 2500 rows on (27 points on a 24^3 grid: 83 us, by rows 157), a mesh, graph or random matrix by rows (a 300^2 mesh: 42
-// us, by tiles 73; 4000 rows of 73 entries at random: 105, 739).  The two lie within 20 % of one another about the line.
+// thousand products, and 1 per thousand products of the small rows and lane of such a row.  Tiles: 19 us (more launches) and
+// 0.15 per candidate pair of tiles, which is what they cost at least.  So a stencil or dense blocks go by tiles from 1500
+// rows on (27 points on a 24^3 grid: 69 us, by rows 157), a mesh, graph or random matrix by rows (a 300^2 mesh: 42 us, by
+// tiles 68; 4000 rows of 73 entries at random: 105, 742).  Of the 90 the choice loses more than 6 % on three, 23 % on one.
 static bool rows_preferred(int64_t products, int64_t small_products, int lanes, int64_t heavy, int64_t candidates) {
-    return 13 * heavy + products / 1000 + lanes * (small_products / 1000) <= 30000 + candidates / 20 * 3;
+    return 13 * heavy + products / 1000 + lanes * (small_products / 1000) <= 19000 + candidates / 20 * 3;
 }
 
 int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s,

@@ -68,6 +68,7 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
     ctx->scalars_clean = false;
     // (the count travels to the host with the sizes it waits for)
     if (ctx->count_products) count_products(ctx, A, B, s);
+    TilesAhead ahead;
     bool by_rows = false, by_tiles = false;
     const int64_t tag = ctx->publish_tag;
     rc = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows);
@@ -81,10 +82,10 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
         rc = convert_enqueue(ctx, A, alias ? (TSP_FORM_LEFT | TSP_FORM_RIGHT) : TSP_FORM_LEFT, S_TILES_A, &ta, s);
         if (!rc && !alias) rc = convert_enqueue(ctx, B, TSP_FORM_RIGHT, S_TILES_B, &tb, s);
         phase_end(ctx, TSP_PHASE_CONVERT, s);
-        if (!rc) rc = symbolic_run(ctx, ta, alias ? ta : tb, &plan, s);
+        if (!rc) rc = symbolic_run(ctx, ta, alias ? ta : tb, &plan, s, &ahead);
     }
     ctx->stats.products = !rc && ctx->count_products ? ctx->h_scalars[S_PRODUCTS] : -1;
-    if (!rc && by_tiles) rc = numeric_enqueue(ctx, ta, alias ? ta : tb, plan, C, s, /*last_of_call=*/true);   // the plan ends here
+    if (!rc && by_tiles) rc = numeric_enqueue(ctx, ta, alias ? ta : tb, plan, C, s, /*last_of_call=*/true, &ahead);   // the plan ends here
     if (!rc && ctx->compact) {                    // Algorithm 1, the compaction steps: strictly sparse result
         tsp_csr structural = *C;
         bool taken = false;                       // (no entry is zero: C keeps the arrays it has)

@@ -1527,7 +1527,7 @@ __global__ __launch_bounds__(256) void k_count_masks(int64_t c_tiles, const int6
 __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row_nnz, int64_t c_rows,
                                                  const uint32_t *__restrict__ tile_row_entries, int64_t c_tile_rows,
                                                  int64_t *__restrict__ c_row_ptr, int64_t *d_scalars,
-                                                 int64_t *h_scalars_dev, int64_t publish_tag, bool clear) {
+                                                 int64_t *h_scalars_dev, int64_t publish_tag, bool clear, const ListExpected expected, int32_t *live) {
     __shared__ uint64_t lds[256 / 64];
     __shared__ int64_t own[kScalars];
     constexpr int kItems = kChunkRows / 256;
@@ -1582,6 +1582,14 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
             c_row_ptr[c_rows] = (int64_t)(entries_before + total);
             own[S_C_NNZ] = (int64_t)(entries_before + total);
             own[S_MAX_ROW_ENTRIES] = (int64_t)largest;
+        }
+        if (live) {
+            if (threadIdx.x < kScalars && threadIdx.x != S_C_NNZ && threadIdx.x != S_MAX_ROW_ENTRIES) own[threadIdx.x] = standing;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                live[0] = expected.holds(own);
+                live[1] = (int32_t)own[S_C_TILES];
+            }
         }
         // no other block of this launch writes a scalar, and the kernels before it have finished
         publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing, own, own_slot(S_C_NNZ) | own_slot(S_MAX_ROW_ENTRIES), clear);
@@ -1726,7 +1734,7 @@ static int lanes_per_a_tile(int64_t tile_rows, int64_t ntiles) {
     return l;
 }
 
-int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **out, hipStream_t s) {
+int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **out, hipStream_t s, TilesAhead *ahead) {
     *out = nullptr;
     if (A->cols != B->rows) return TSP_ERR_SHAPE_MISMATCH;
     tsp_plan_s *P = new (std::nothrow) tsp_plan_s();
@@ -1744,7 +1752,16 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     uint32_t *saved_bitmap = nullptr, *saved_cnt = nullptr;   // kept by the counting kernel for the task-list kernel
     int saved_words = 0;
     int64_t *row_pair_ptr = nullptr, *tmp = nullptr;
+    int32_t *live = nullptr;
+    auto drop_ahead = [&]() {
+        if (!ahead || ahead->done) return;
+        ctx_free(ctx, ahead->col, s);
+        ctx_free(ctx, ahead->val, s);
+        *ahead = {};
+    };
     auto cleanup = [&](int code) {
+        drop_ahead();
+        ctx_free(ctx, live, s);
         ctx_free(ctx, row_jmin, s);
         ctx_free(ctx, row_c_tiles, s);
         ctx_free(ctx, row_pairs, s);
@@ -1909,8 +1926,9 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         return P->c_tiles >= INT32_MAX ? (int)TSP_ERR_INDEX_OVERFLOW : (int)TSP_OK;
     };
     auto true_sizes = [&]() {
-        return ListSizes{h[S_C_TILES], h[S_PAIRS], h[S_CANDIDATES], h[S_MAX_ROW_C_TILES], h[S_MAX_ROW_PAIRS], h[S_MAX_ROW_WORDS],
-                         h[S_MAX_ROW_A_TILES], B->ntiles};
+        ListSizes true_ones = ListExpected::sizes(h);
+        true_ones.b_tiles = B->ntiles;
+        return true_ones;
     };
 list_kernels:
     if (!hinted) {
@@ -2082,12 +2100,26 @@ list_kernels:
                                tile_row_entries);
     }
     SYM_CHECK(hipGetLastError());
+    // A product of the sizes of an earlier one (tsp_spgemm): the multiplication follows at once, into arrays for as many
+    // entries as that one had and some more; k_row_ptr lets it run if this product fits.
+    ListExpected expected{};
+    const bool early = ahead && hinted && hint.nnz > 0;
+    if (early) {
+        expected = {z, hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20), hint.max_row_entries};
+        // (no more output tiles than that one had: the XCDs get equal shares of the tiles the launch is for; an eighth of
+        // them with a sixteenth to spare took 2 % longer on a stencil)
+        expected.most.c_tiles = hint.c_tiles;
+        ahead->col = ctx_alloc_n<int32_t>(ctx, (size_t)expected.nnz, s);
+        ahead->val = ctx_alloc_n<float>(ctx, (size_t)expected.nnz, s);
+        live = ctx_alloc_n<int32_t>(ctx, 2, s);
+        if (!ahead->col || !ahead->val || !live) return cleanup(TSP_ERR_ALLOC_FAILED);
+    }
     bool published = false;                        // k_row_ptr puts the scalar block into the host's mirror
     {
         KernelTimer kt(ctx, TSP_KERNEL_SCAN_ROWS, s);
         if (n_chunks > 0 && n_chunks <= kMaxChunks) {
             hipLaunchKernelGGL(k_row_ptr, dim3((unsigned)n_chunks), dim3(256), 0, s, row_nnz, P->c_rows, tile_row_entries,
-                               ntr, P->c_row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, true);
+                               ntr, P->c_row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, true, expected, live);
             SYM_CHECK(hipGetLastError());
             published = true;
             ctx->scalars_clean = true;             // (nothing of this call uses the block any more)
@@ -2097,6 +2129,14 @@ list_kernels:
         }
     }
     phase_end(ctx, TSP_PHASE_COUNT, s);
+    if (early) {
+        phase_begin(ctx, TSP_PHASE_NUMERIC, s);
+        SYM_CHECK(numeric_launch(ctx, A, B, P,
+                                 {hint.c_tiles, z.pairs, expected.nnz, z.max_row_c_tiles, z.max_row_pairs, expected.max_row_entries, hint.a_tiles,
+                                  z.b_tiles, nullptr, nullptr, live},
+                                 ahead->col, ahead->val, s));
+        phase_end(ctx, TSP_PHASE_NUMERIC, s);
+    }
     if (!rc) rc = published ? wait_published_scalars(ctx, ctx->publish_tag, s) : read_scalars(ctx, s);   // ---- sync 2: nnz(C)
     if (rc) return cleanup(rc);
     if (hinted) {
@@ -2105,6 +2145,9 @@ list_kernels:
         if (!z.holds(true_sizes())) {              // another product of the same sizes, with more in it
             std::copy(h, h + kScalars, first_numbers);
             ran_again = true;
+            drop_ahead();
+            ctx_free(ctx, live, s);
+            live = nullptr;
             free_lists();
             goto list_kernels;
         }
@@ -2114,6 +2157,11 @@ list_kernels:
             if (i != S_C_NNZ && i != S_MAX_ROW_ENTRIES && i != S_UNSUPPORTED && i != S_INTERNAL) ctx->h_scalars[i] = first_numbers[i];
     if (ctx->h_scalars[S_UNSUPPORTED]) return cleanup(TSP_ERR_UNSUPPORTED);
     if (ctx->h_scalars[S_INTERNAL]) return cleanup(TSP_ERR_HIP);
+    if (early && !ran_again) ahead->done = expected.holds(ctx->h_scalars);
+    hint.nnz = ctx->h_scalars[S_C_NNZ];
+    hint.a_tiles = A->ntiles;
+    hint.c_tiles = P->c_tiles;
+    hint.max_row_entries = std::max(key_known ? hint.max_row_entries : 0, ctx->h_scalars[S_MAX_ROW_ENTRIES]);
     std::copy(hint_key, hint_key + 5, hint.sizes);
     hint.usable = listed && fused_masks;
     hint.most = key_known ? hint.most.with(true_sizes()) : true_sizes();

@@ -129,6 +129,39 @@ def test_another_structure_of_the_same_sizes(tsp, oracle, phases):
         h.close()
 
 
+@pytest.mark.parametrize("tile_rows", [1, 40, 1025])
+def test_another_result_of_the_same_tiles(tsp, oracle, tile_rows):
+    """Products of one tile structure with more and with fewer entries in C, and with longer and with shorter rows of
+    tiles: the multiplication that has been launched for as many entries as the last product had may not run."""
+    k = np.arange(16)
+    near = (np.concatenate([k, k[1:]]), np.concatenate([k, k[:-1]]))                # two diagonals
+    arrow = (np.concatenate([k, 0 * k[1:]]), np.concatenate([0 * k, k[1:]]))        # a row and a column: a full product
+    rng = np.random.default_rng(tile_rows)
+
+    def blocks(local, shift):
+        cols = (np.arange(tile_rows) + shift * (np.arange(tile_rows) % 3 == 0)) % tile_rows
+        r = (np.arange(tile_rows)[:, None] * 16 + local[0]).ravel()
+        c = (cols[:, None] * 16 + local[1]).ravel()
+        return inputs.from_coo(16 * tile_rows, 16 * tile_rows, r, c, rng.uniform(-1, 1, r.size), "tiles")
+
+    all_of = [blocks(near, 0), blocks(arrow, 0), blocks(arrow, 1)]
+    ref = [oracle.spgemm(A, A, threads=4) for A in all_of]
+    h = tsp.Handle(validate=True)
+    try:
+        h.set_option(tsp.OPT_WORK_ORDER, 2)        # (the tile kernels, whatever the operands)
+        dev = [tsp.to_device(A) for A in all_of]
+        for which in (0, 0, 1, 1, 0, 2, 2, 1):
+            C = h.spgemm(dev[which], dev[which])
+            row_ptr, col, val = C.to_host()
+            C.free()
+            want = ref[which]
+            assert h.stats()["pairs"] == tile_rows
+            assert np.array_equal(row_ptr, want.row_ptr) and np.array_equal(col, want.col)
+            assert np.all(np.abs(val.astype(np.float64) - want.val) <= 1e-5 * want.mag + 1e-7)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("tile_rows", [1, 1024, 1025, 65537])
 def test_prefix_sums_over_tile_rows(tsp, oracle, tile_rows):
     """Tile-rows either side of a block of the prefix sums, and more than 64 blocks."""
