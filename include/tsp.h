@@ -113,6 +113,11 @@ enum {
                                /*    compared when it is released; tsp_stats.workspace_violations counts the   */
                                /*    words found changed: a kernel wrote outside its array.  A debugging aid:  */
                                /*    two small launches per block.  0 (default): none                          */
+    TSP_OPT_PATTERN_BYTES = 12, /* most bytes in which tsp_spgemm keeps the pattern of C's long rows  */
+                               /*    (a bit per column of C) from the sizing to the multiplication   */
+                               /*    when it multiplies by rows; beyond that it is found again, some */
+                               /*    rows at a time (one at least).  0 (default): 16 GiB.  The       */
+                               /*    result does not depend on it                                    */
     TSP_OPT_STRIP_ORDER = 8    /* order in which the counting and the multiplication kernel (4.2,   */
                                /*    4.3) take the output tiles: 1: in vertical strips of tile      */
                                /*    columns sized so that the tiles of B a strip meets stay in the  */

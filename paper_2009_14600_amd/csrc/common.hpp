@@ -129,6 +129,7 @@ struct tsp_context {
     int count_products = 0;                        // TSP_OPT_COUNT_PRODUCTS
     int numeric_run_len = 0;                       // tiles per wave of the multiplication kernel, 0: automatic
     int matrix_cores = 1;                          // 0: block products on the vector ALUs
+    int64_t pattern_bytes = (int64_t)16 << 30;     // TSP_OPT_PATTERN_BYTES
     int compact = 0;                               // 1: tsp_spgemm removes zero-valued entries from C
     bool hint_general = false;                     // the last product took the general task-list kernel ...
     int64_t hint_sizes[4] = {-1, -1, -1, -1};      // ... with these rows and nnz of A and of B

@@ -31,10 +31,8 @@ constexpr int kSpanWindows = 64;         // windows whose bits the LDS of a bloc
 constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows
 constexpr int kCountThreads = 256;       // of k_heavy_count
 constexpr int32_t kNoCol = 0x7FFFFFFF;
-// Intermediate products behind one task of k_heavy_fill (a row, or some of its windows)
-constexpr int64_t kKeptPattern = (int64_t)16 << 30;   // bytes of it, at most
 constexpr int64_t kFoundEntries = (int64_t)2 << 30;   // of the small rows before they are moved into C, at most
-constexpr int kTaskProducts = 65536;
+constexpr int kTaskProducts = 65536;     // intermediate products behind one task of k_heavy_fill (a row, or some of its windows)
 
 // Of a tile-row: the entries of its longest heavy row (23 bits hold the columns that k_row_prepare allows), its small rows,
 // and the rows of 9 to 16 entries with no more products than a small row has; of either at most 16.
@@ -1454,7 +1452,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     wave_total = ws.get<int32_t>((size_t)small_waves);
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
     uint32_t *pack = nullptr, *offset = nullptr, *bits = nullptr;
-    int64_t bit_rows = 0;
+    int64_t bit_rows = 0;                    // rows whose pattern `bits` holds
+    bool pattern_kept = false;               // ... and the sizing pass has left that of all heavy rows there
     CountArgs c{};
     auto count_heavy = [&](int64_t rows) {
         const size_t lds = ((size_t)c.span_windows << (shift - 3)) + 256;
@@ -1462,7 +1461,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(kCountThreads), lds, s, c);
     };
     // heavy rows whose pattern is kept at a time
-    auto pattern_rows = [&](int64_t heavy) { return std::min(heavy, std::max<int64_t>(kKeptPattern / (((int64_t)windows << shift) / 8), 1)); };
+    auto pattern_rows = [&](int64_t heavy) { return std::min(heavy, std::max<int64_t>(ctx->pattern_bytes / (((int64_t)windows << shift) / 8), 1)); };
     int32_t *table = nullptr, *words = nullptr;
     uint2 *word = nullptr;
     SmallArgs m{};
@@ -1533,7 +1532,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             c.row_nnz = row_nnz;
             c.group_len = group_len;
             c.offset = offset;
-            c.bits = bit_rows == n_heavy ? bits : nullptr;
+            pattern_kept = bit_rows == n_heavy;
+            c.bits = pattern_kept ? bits : nullptr;
             count_heavy(n_heavy);
         }
         return (int)TSP_OK;
@@ -1568,7 +1568,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             for (int64_t from = 0; from < n_heavy; from += bit_rows) {
                 f.heavy_from = (int)from;
                 f.heavy_to = (int)std::min(from + bit_rows, n_heavy);
-                if (bit_rows < n_heavy) {
+                // (by what the sizing pass did: it went by the heavy rows of the last product, which may have been more)
+                if (!pattern_kept) {
                     c.d_scalars = nullptr;
                     c.row_nnz = nullptr;
                     c.heavy_cap = f.heavy_to;

@@ -103,6 +103,28 @@ def test_same_sizes_another_structure(tsp, oracle):
         h.close()
 
 
+@pytest.mark.parametrize("cols,kept_rows", [(1600, 0), (1600, 1), (1600, 30), (1600, 64), (9000, 30)])
+def test_pattern_of_the_heavy_rows_kept_or_found_again(tsp, oracle, cols, kept_rows):
+    """The pattern of the heavy rows within a limit of some rows: products of the same sizes with more heavy rows than that
+    and with fewer, in either order (the room for the pattern follows the last product, the pattern the one at hand)."""
+    n, rng = 1600, np.random.default_rng(11)
+    many, few = np.full(n, 2), np.full(n, 3)
+    many[::40] = 162                              # 40 heavy rows
+    few[::80] = 243                               # 20, and as many entries
+    assert many.sum() == few.sum()
+    row_bytes = 256 if cols <= 2048 else 3 * 512  # a bit per column, in whole windows
+    B = _matrix(rng, n, cols, 6, "right")
+    h = tsp.Handle()
+    try:
+        h.set_option(tsp.OPT_PATTERN_BYTES, kept_rows * row_bytes)
+        for lengths in (many, many, few, few, many, few):
+            col = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths])
+            A = inputs.from_coo(n, n, np.repeat(np.arange(n), lengths), col, rng.uniform(-1, 1, col.size), "left")
+            _check(h, tsp, oracle, A, B, calls=1)
+    finally:
+        h.close()
+
+
 def test_more_lanes_for_rows_of_up_to_16_entries(tsp, oracle):
     """The lanes of a small row follow the last product of the same sizes: rows of 9 and of 16 entries, small but for the
     eight lanes of a mean row, come and go."""
