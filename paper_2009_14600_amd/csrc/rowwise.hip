@@ -39,7 +39,9 @@ constexpr int kTaskProducts = 65536;     // intermediate products behind one tas
 __host__ __device__ constexpr uint32_t pack_rows(uint32_t longest, uint32_t small, uint32_t wide) { return longest << 9 | (small * 17u + wide); }
 
 struct RowMatrix {                       // an operand in the form the row kernels read
-    int32_t *start = nullptr;            // int32[rows + 1], clamped to [0, nnz]
+    // int32[rows + 1], clamped to [0, nnz] and non-decreasing inside a tile-row (16 rows and the start of the next), whatever
+    // the operand holds: rows take no other entries than k_row_prepare has counted for them
+    int32_t *start = nullptr;
     int2 *rec = nullptr;                 // per entry {column (clamped), value rounded to fp16, as fp32 bits}
     int32_t *ntiles = nullptr;           // tiles of every tile-row
     int32_t *tile_col = nullptr;         // their columns, at the position of the tile-row's first entry; any order
@@ -61,6 +63,7 @@ struct PrepareArgs {
     const void *b_row_ptr;               // of B, as the caller gave it
     int b_is_i64;
     int64_t b_rows;
+    int32_t b_nnz;
     int small_lanes, small_products;     // most entries and products of a small row of A
     int windows;                         // of columns of C, for the heavy rows
     int32_t *heavy;                      // rows that are not small
@@ -122,11 +125,16 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
         if (tid <= T) {
             const int64_t i = min(I * T + tid, a.rows);
             const RP raw = a.row_ptr[i];
-            const RP p = min(max(raw, (RP)0), (RP)a.nnz);
-            bad = raw != p || (i == 0 && raw != 0) || (i == a.rows && raw != (RP)a.nnz);
-            s_ptr[team][tid] = (int32_t)p;
+            int32_t p = (int32_t)min(max(raw, (RP)0), (RP)a.nnz);
+            p = max(p, TSP_DPP(p, p, 0x111, 0xf, false));
+            p = max(p, TSP_DPP(p, p, 0x112, 0xf, false));
+            p = max(p, TSP_DPP(p, p, 0x114, 0xf, false));
+            p = max(p, TSP_DPP(p, p, 0x118, 0xf, false));
+            p = max(p, TSP_DPP(p, p, 0x142, 0xa, false));
+            bad = raw != (RP)p || (i == 0 && raw != 0) || (i == a.rows && raw != (RP)a.nnz);
+            s_ptr[team][tid] = p;
             if (tid < T) s_ub[team][tid] = 0;
-            if (i < a.rows ? tid < T : true) a.out.start[i] = (int32_t)p;
+            if (i < a.rows ? tid < T : true) a.out.start[i] = p;
         }
         if (tid == 0) {
             s_count[team] = 0;
@@ -138,7 +146,6 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     else __syncthreads();
     if (live) {
         const int32_t e0 = s_ptr[team][0], e1 = s_ptr[team][T];
-        if (tid < T) bad = bad || s_ptr[team][tid + 1] < s_ptr[team][tid];
         int32_t listed = 0;
         ValueRange range;
         for (int32_t base = e0 + (tid & ~63); base < e1; base += kTeam * kU) {
@@ -157,15 +164,16 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                 if ((uint32_t)c[u] >= (uint64_t)a.cols) c[u] = 0;
                 len[u] = 0;
                 if (a.ub && c[u] < a.b_rows) {
-                    int64_t s, e;
+                    // (no less than B's own start array will say, which is clamped the same and then made non-decreasing)
+                    int32_t s, e;
                     if (a.b_is_i64) {
-                        s = static_cast<const int64_t *>(a.b_row_ptr)[c[u]];
-                        e = static_cast<const int64_t *>(a.b_row_ptr)[c[u] + 1];
+                        s = (int32_t)min(max(static_cast<const int64_t *>(a.b_row_ptr)[c[u]], (int64_t)0), (int64_t)a.b_nnz);
+                        e = (int32_t)min(max(static_cast<const int64_t *>(a.b_row_ptr)[c[u] + 1], (int64_t)0), (int64_t)a.b_nnz);
                     } else {
-                        s = static_cast<const int32_t *>(a.b_row_ptr)[c[u]];
-                        e = static_cast<const int32_t *>(a.b_row_ptr)[c[u] + 1];
+                        s = min(max(static_cast<const int32_t *>(a.b_row_ptr)[c[u]], 0), a.b_nnz);
+                        e = min(max(static_cast<const int32_t *>(a.b_row_ptr)[c[u] + 1], 0), a.b_nnz);
                     }
-                    len[u] = (int32_t)min(max(e - s, (int64_t)0), (int64_t)((1 << 25) - 1));
+                    len[u] = min(max(e - s, 0), (1 << 25) - 1);
                 }
             }
 #pragma unroll
@@ -593,6 +601,15 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
             av = (uint32_t)x.y;
         }
     }
+    // The search for a slot ends because the row has no more products than three quarters of them.  ub says so, and so do the
+    // start arrays of operands that are canonical; of others the lists are counted here, and a row that has more takes none.
+    // (A counter in the search itself makes 65536 rows of 8 random entries take 74 us instead of 70.)
+    int products = min(max(e - p, 0), most + 1);
+    products += TSP_DPP(0, products, 0xB1, 0xf, true);                     // of the group: pairs, quads, halves of a row, rows
+    products += TSP_DPP(0, products, 0x4E, 0xf, true);
+    products += TSP_DPP(0, products, 0x141, 0xf, true);
+    if constexpr (G == 16) products += TSP_DPP(0, products, 0x140, 0xf, true);
+    if (products > most) e = p;
     const int lists = wave_max(small ? deg : 0), longest = wave_max(e - p);
     // round t: list t, or with narrow lists the lists t * (G / width) ... of the group, and element j of each
     const int width = kNarrow ? a.shape.list_lanes : G, per = kNarrow ? G / width : 1;
@@ -617,7 +634,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
         bool made = false;
         uint32_t slot = ((uint32_t)__umul24((uint32_t)y.x, 0x9E3779u) >> (24 - bits)) & (uint32_t)(slots - 1);
         if (on)
-            while (true) {
+            while (true) {                                   // (a free slot is always left: the row has been checked above)
                 const int32_t old = atomicCAS(&table[slot], kFree, y.x);
                 made = old == kFree;
                 if (made || old == y.x) break;
@@ -1126,7 +1143,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
                         const uint32_t c = (x - c0) & (uint32_t)(kSpan - 1);
                         const int2 place = places[c >> 5];
                         const int rank = __popc((uint32_t)place.x << (31u - (c & 31u))) + place.y;
-                        const int at = active ? min(rank, kCap) : kCap + lane;
+                        // (inside acc also for a column that the pattern does not have)
+                        const int at = active ? min(max(rank, 0), kCap) : kCap + lane;
                         // the product of two fp16 numbers is exact; + 0 makes a positive zero of a negative one
                         const float product = __builtin_fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)(x >> 16)),
                                                              (float)__builtin_bit_cast(_Float16, (uint16_t)a16), 0.f);
@@ -1234,6 +1252,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
             a.b_row_ptr = left->B->row_ptr;
             a.b_is_i64 = left->B->row_ptr_type == TSP_I64;
             a.b_rows = left->B->rows;
+            a.b_nnz = (int32_t)left->B->nnz;
             a.small_lanes = left->shape.lanes;
             a.small_products = left->shape.products;
             a.windows = left->windows;

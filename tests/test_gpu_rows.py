@@ -172,3 +172,48 @@ def test_rejects_what_is_not_canonical(tsp):
         C.free()
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("row_ptr_dtype", ["i32", "i64"])
+def test_rejects_row_pointers_that_go_up_and_down(tsp, row_ptr_dtype):
+    """On sizes seen before, where the kernels run before the host knows that an operand is not canonical: rows that begin
+    behind the next one, so that a row has entries that were counted for another, with long rows of B behind them; lengths
+    of rows of B that do not fit their type.  tests/test_row_bounds.py models what the kernels rest on."""
+    import torch
+    n = 600
+    rng = np.random.default_rng(2)
+    b_len = np.ones(n, np.int64)
+    b_len[::50] = 40
+    B = inputs.from_coo(n, n, np.repeat(np.arange(n), b_len), np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in b_len]),
+                        rng.uniform(-1, 1, b_len.sum()))
+    A = inputs.from_coo(n, n, np.repeat(np.arange(n), 4), np.concatenate([np.sort(rng.choice(n, 4, replace=False)) for _ in range(n)]),
+                        rng.uniform(-1, 1, 4 * n))
+    far = 2 ** 31 - 1 if row_ptr_dtype == "i32" else 2 ** 62
+    h = tsp.Handle()
+    try:
+        dA, dB = tsp.to_device(A, row_ptr_dtype=row_ptr_dtype), tsp.to_device(B, row_ptr_dtype=row_ptr_dtype)
+        # rows 50 * i of B are long: the entries that change hands below meet three of them
+        dA.col_idx[12:15] = torch.tensor([0, 50, 100], dtype=torch.int32)
+        dA.col_idx[15] = 150
+        good_a, good_b = dA.row_ptr, dB.row_ptr
+        for _ in range(2):
+            h.spgemm(dA, dB).free()
+            assert h.stats()["pairs"] == 0
+        bumps = [("A", {3: 15, 4: 12}), ("A", {3: 15}), ("A", {16: 80, 17: 70}), ("A", {15: 66, 16: 63}), ("A", {20: 2400, 21: 0}), ("A", {599: 2399, 598: 2400}),
+                 ("B", {3: 40, 4: 2}), ("B", {16: 120, 17: 10}), ("B", {1: -far, 2: far}), ("B", {5: far, 6: -far}), ("A", {7: -far, 8: far}),
+                 ("B", {i: (i * 977) % B.nnz for i in range(1, 500)})]
+        for which, values in bumps:
+            print("row pointers:", which, str(values)[:60], flush=True)
+            M, good = (dA, good_a) if which == "A" else (dB, good_b)
+            M.row_ptr = good.clone()
+            for at, value in values.items():
+                M.row_ptr[at] = value
+            with pytest.raises(tsp.TspError) as e:
+                h.spgemm(dA, dB)
+            assert e.value.status == -3
+            M.row_ptr = good
+        C = h.spgemm(dA, dB)
+        assert C.nnz > 0 and h.stats()["pairs"] == 0
+        C.free()
+    finally:
+        h.close()
