@@ -769,7 +769,11 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_bl
     finish(ntiles, ROW_FAST);
 }
 
-// ... and the tile-rows of more entries, listed by it
+// ... and the tile-rows of more entries, listed by it.  As many blocks as the LDS of the chip holds: with one per CU 8192
+// tile-rows, every other one too large, take 603 us instead of 525, an R-MAT graph of scale 17 with 28 entries per row 1864
+// instead of 1581.  From a list, since a share of the tile-rows by index meets the hubs of a graph all in one block where
+// their number is a power of two (12.5 ms with 256 blocks).
+constexpr int64_t kLargeBlocks = 5 * 256;
 template <typename RP, typename VT>
 __global__ __launch_bounds__(kConvThreads) void k_convert_large(const ConvArgs<RP, VT> a, int64_t listed) {
     const int64_t n = min(listed >= 0 ? listed : a.d_scalars[a.large_slot], a.tile_rows);
@@ -925,16 +929,19 @@ static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, in
     if (ntr > 0) {
         KernelTimer kt(ctx, TSP_KERNEL_CONVERT, s);
         const dim3 waves((unsigned)((ntr + 3) / 4)), rows((unsigned)ntr), threads(kConvThreads);
-        if (which >= 0) hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min<int64_t>(which, 256)), threads, 0, s, a, which);
+        if (which >= 0) hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min(which, kLargeBlocks)), threads, 0, s, a, which);
         else if (!blocks && want <= 2) hipLaunchKernelGGL((k_convert_rows_light<64, 2, RP, VT>), waves, threads, 0, s, a);
         else if (!blocks && want <= 4) hipLaunchKernelGGL((k_convert_rows_light<64, 4, RP, VT>), waves, threads, 0, s, a);
         else if (!blocks) hipLaunchKernelGGL((k_convert_rows<64, 8, RP, VT>), waves, threads, 0, s, a);
+        // (most tile-rows are too large for k_convert_block: a block each, and no list.  27 points with 5 and 6 unknowns on 28^3
+        // nodes, 135 and 162 entries per row: 305 and 452 us, 597 and 848 with every tile-row listed)
+        else if (per_row > kConvThreads * 8) hipLaunchKernelGGL((k_convert_rows<256, 8, RP, VT>), rows, threads, 0, s, a);
         else {
             const int cache = want <= 4 ? 4 : want <= 6 ? 6 : 8;
             auto kernel = cache == 4 ? k_convert_block<4, RP, VT> : cache == 6 ? k_convert_block<6, RP, VT> : k_convert_block<8, RP, VT>;
             hipLaunchKernelGGL(kernel, rows, threads, 0, s, a);
             if (which == kAllRows && std::min(A->nnz, A->cols * T) > kConvThreads * cache)
-                hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min<int64_t>(ntr, 256)), threads, 0, s, a, (int64_t)-1);
+                hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min(ntr, kLargeBlocks)), threads, 0, s, a, (int64_t)-1);
         }
         if (may_merge)
             hipLaunchKernelGGL((k_convert_merge<RP, VT>), dim3(grid_merge), dim3(kConvThreads), 0, s, a);

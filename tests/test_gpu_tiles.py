@@ -87,6 +87,43 @@ def test_tile_rows_of_many_entries(tsp, oracle, cols, tiles, entries, upload):
         h.close()
 
 
+@pytest.mark.parametrize("tile_rows,large,small", [
+    (40, 2100, 0), (40, 2049, 2049), (40, 2060, 2037),      # a mean either side of what k_convert_block is for, all or half of them large
+    (1300, 2100, 1500), (2100, 2050, 60),                   # the same with more tile-rows than k_convert_large has blocks
+])
+@pytest.mark.parametrize("phases", [False, True])
+def test_large_tile_rows_beside_others(tsp, tile_rows, large, small, phases):
+    """Times the identity: C is A.  Every third tile-row has `small` entries, the others `large` ones, in 400 columns."""
+    rng = np.random.default_rng(tile_rows + large)
+    cols = 400
+    r, c = [], []
+    for i in range(tile_rows):
+        pick = np.sort(rng.choice(16 * cols, small if i % 3 == 1 else large, replace=False))
+        r.append(16 * i + pick // cols), c.append(pick % cols)
+    r, c = np.concatenate(r), np.concatenate(c)
+    A = inputs.from_coo(16 * tile_rows, cols, r, c, rng.uniform(-1, 1, r.size), "large tile-rows")
+    eye = inputs.from_coo(cols, cols, np.arange(cols), np.arange(cols), np.ones(cols), "identity")
+    print(f"large tile-rows: {A.rows}x{cols}, nnz {A.nnz}", flush=True)
+    h = tsp.Handle(validate=True)
+    try:
+        h.set_option(tsp.OPT_WORK_ORDER, 2)                 # (the tile kernels, whatever the operands)
+        dA, dI = tsp.to_device(A), tsp.to_device(eye)
+        for _ in range(2):
+            if phases:
+                left, right = h.convert(dA, tsp.FORM_LEFT), h.convert(dI, tsp.FORM_RIGHT)
+                plan = h.symbolic(left, right)
+                C = h.numeric(left, right, plan)
+                plan.free(), left.free(), right.free()
+            else:
+                C = h.spgemm(dA, dI)
+            row_ptr, col, val = C.to_host()
+            C.free()
+            assert np.array_equal(row_ptr, A.row_ptr) and np.array_equal(col, A.col_idx)
+            assert np.array_equal(val, np.asarray(A.val, dtype=np.float16).astype(np.float32))
+    finally:
+        h.close()
+
+
 def _full_tiles(rng, tile_rows, tile_cols_of):
     """Four full tiles per tile-row, in the tile columns tile_cols_of(tile-row)."""
     r, c = [], []
