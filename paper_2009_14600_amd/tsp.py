@@ -211,7 +211,7 @@ class Handle:
         torch = _torch()
         self._torch = torch
         self._blocks = {}
-        self._typed = {}             # the last view of a block, by address and type
+        self._typed = {}             # the last view of a block, by address and type; never handed out itself
         self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
         def _alloc(_user, nbytes, _stream):
@@ -250,9 +250,9 @@ class Handle:
             if views is None:
                 views = self._typed[ptr] = {}
             view = views.get(dtype)
-            if view is None or view[0] != count:     # (the view handed out last, where it is the one wanted again)
+            if view is None or view[0] != count:     # (the last view of the block, where it is the one wanted again)
                 view = views[dtype] = (count, block.view(dtype).narrow(0, 0, count))
-            return view[1]
+            return view[1].data               # a tensor of the caller's own: its shape may be changed in place
         itemsize = dtype.itemsize
         for base, block in self._blocks.items():
             if base <= ptr and ptr + count * itemsize <= base + block.numel():

@@ -54,3 +54,26 @@ def test_bench_refuses_more_than_one_gpu():
                          capture_output=True, text=True, timeout=120)
     assert res.returncode == 2
     assert "one GPU" in res.stderr
+
+
+def test_every_result_is_a_tensor_of_its_own():
+    """Views of one block for results of one length share memory and nothing else: what a caller does to the shape or the
+    flags of one in place does not show in the next."""
+    import torch
+    from paper_2009_14600_amd import tsp
+    h = object.__new__(tsp.Handle)                # (the views alone: no library, no GPU)
+    h._h = None
+    h._torch, h._typed = torch, {}
+    block = torch.zeros(4096, dtype=torch.uint8)
+    h._blocks = {block.data_ptr(): block}
+    first = h._view(block.data_ptr(), 100, torch.float32)
+    first.fill_(2.0)
+    first.requires_grad_(True)
+    with torch.no_grad():
+        first.unsqueeze_(0)
+    second = h._view(block.data_ptr(), 100, torch.float32)
+    assert second is not first and second.shape == (100,) and not second.requires_grad
+    assert second.data_ptr() == first.data_ptr() and bool((second == 2.0).all())
+    second.resize_(10)
+    assert h._view(block.data_ptr(), 100, torch.float32).shape == (100,)
+    assert h._view(block.data_ptr(), 7, torch.int64).shape == (7,)
