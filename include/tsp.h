@@ -226,8 +226,10 @@ int tsp_csr_free(tsp_handle handle, tsp_csr *C, void *stream);
  * Compaction of zeros (paper Section 4.4; the two compaction steps that end Algorithm 1): *out = C without the entries
  * whose value compares equal to zero (+0.0 and -0.0; NaN stays), order kept, so that a product
  * whose terms cancelled, or that only met stored zeros, leaves no entry behind.  C: device CSR with
- * float values (TSP_F32) and a 32- or 64-bit row_ptr, borrowed, not modified; row starts are
- * clamped to [0, C.nnz], so a malformed row_ptr cannot cause an out-of-bounds access.  *out:
+ * float values (TSP_F32) and a 32- or 64-bit row_ptr, borrowed, not modified.  Its rows may begin behind the first
+ * entry and end before the last one (a slice of rows; entries outside are not C's); row pointers are clamped to
+ * [0, C.nnz], and one that is smaller than one before it counts as that one, so that any row_ptr gives a well-formed
+ * result of no more than C.nnz entries and none an out-of-bounds access (at the price of another pass and wait).  *out:
  * row_ptr (TSP_I64), col_idx, val (TSP_F32) from the handle's allocator, owned by the caller
  * (tsp_csr_free); zeroed on failure.  Synchronises the stream once (the new nnz sizes the
  * allocation).  C and out must be different objects.

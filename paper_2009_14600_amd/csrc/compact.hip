@@ -8,7 +8,13 @@
 // All three passes go by the entries and not by the rows, so that rows of any length weigh the same: a block takes a
 // chunk of 4096 consecutive entries (a multiple of that on very large matrices) and finds the rows that begin in it by a
 // search in row_ptr.  Bound by memory: the values twice, the columns once, the survivors.  200,003 rows of 60 entries on
-// average, a fifth zero: count 9 us, prefix sum 5 us, copy 47 us (by rows, 16 lanes to a row: 35 + 8 + 51 us).
+// average, a fifth zero: count 9 us, prefix sum 3 us, copy 31 us (by rows, 16 lanes to a row: 35 + 8 + 51 us).
+// Only the entries between the first and the last row pointer are C's.  A block finds the new pointers of the first 4096 rows
+// that begin in its part; where there are more (empty ones, then), blocks for 4096 rows each find the others (300,000 rows
+// of 2000 entries 37 us for the call, 663 with all rows of a part left to its block; 81 by rows).
+//
+// The searches need row pointers that do not go down.  The counting pass looks, and where they do (no CSR matrix, but none
+// that is refused) the pass is made again with every pointer replaced by the largest so far.
 #include "common.hpp"
 
 #include <algorithm>
@@ -19,15 +25,42 @@ namespace tsp {
 constexpr int kCompactThreads = 256;
 constexpr int kCompactPart = 4096;             // entries a block holds at a time, 16 per thread
 constexpr int64_t kCompactChunks = 65536;      // at most
+constexpr int kCheckRows = 1024;               // rows per block that looks whether row pointers ascend
+constexpr int kCompactRows = 4096;             // rows whose new pointers a part's block finds, and rows of a block of their own
 
 template <typename RP>
 struct CompactArgs {
     const RP *row_ptr;
     const int32_t *col;
     const float *val;
-    int64_t rows, nnz;
+    int64_t rows, nnz;                         // (rows: -1 where only columns and values are wanted)
+    int64_t last;                              // index of the last row pointer
     int64_t chunk;                             // entries per block, a multiple of kCompactPart
+    int chunks;
+    // blocks for `per` rows each; they come before the chunks' in a launch (behind them they would end it)
+    __host__ __device__ int row_blocks(int per) const { return rows < 0 ? 0 : (int)(rows / per) + 1; }
 };
+template <typename RP>
+__device__ __forceinline__ int64_t clamped(const CompactArgs<RP> &a, int64_t row) {
+    return min(max((int64_t)a.row_ptr[row], (int64_t)0), a.nnz);
+}
+// The entries of the matrix.  (A part is loaded without waiting for these: those outside count as zeros.)
+struct EntryRange {
+    int64_t lo, hi;
+};
+template <typename RP>
+__device__ __forceinline__ EntryRange entry_range(const CompactArgs<RP> &a) {
+    return {min(max((int64_t)uniform_load(a.row_ptr), (int64_t)0), a.nnz),
+            min(max((int64_t)uniform_load(a.row_ptr + a.last), (int64_t)0), a.nnz)};
+}
+__device__ __forceinline__ void drop_outside(const EntryRange &range, int64_t begin, float (&v)[16]) {
+    if (begin >= range.lo && begin + kCompactPart <= range.hi) return;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int64_t e = begin + u * kCompactThreads + threadIdx.x;
+        v[u] = e >= range.lo && e < range.hi ? v[u] : 0.0f;
+    }
+}
 
 // entries per chunk so that at most kCompactChunks cover nnz
 static int64_t compact_chunk(int64_t nnz) {
@@ -55,25 +88,42 @@ __device__ __forceinline__ void load_part(const X *from, int64_t begin, int64_t 
     }
 }
 
+// Survivors per chunk, and where the entries begin (before[chunks + 1]); the blocks of the rows look whether the row pointers
+// ascend.
 template <typename RP>
-__global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<RP> a, uint32_t *__restrict__ count) {
+__global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<RP> a, uint32_t *__restrict__ count,
+                                                                   int64_t *__restrict__ before, int64_t *d_scalars) {
     __shared__ uint32_t s_wave[kCompactThreads / 64];
-    const int64_t c0 = (int64_t)blockIdx.x * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
+    const int b = (int)blockIdx.x - a.row_blocks(kCheckRows);
+    if (b < 0) {
+        bool down = false;
+#pragma unroll
+        for (int u = 0; u < kCheckRows / kCompactThreads; ++u) {
+            const int64_t r = (int64_t)blockIdx.x * kCheckRows + u * kCompactThreads + threadIdx.x;
+            down |= clamped(a, min(r, a.last)) > clamped(a, min(r + 1, a.last));
+        }
+        if (down) d_scalars[S_DESCENDS] = 1;
+        return;
+    }
+    const int64_t c0 = (int64_t)b * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
+    const EntryRange range = entry_range(a);
+    if (b == 0 && threadIdx.x == 0) before[a.chunks + 1] = range.lo;
     uint32_t n = 0;
     for (int64_t begin = c0; begin < c1; begin += kCompactPart) {
         float v[16];
         load_part(a.val, begin, c1, v);
+        drop_outside(range, begin, v);
 #pragma unroll
         for (int u = 0; u < 16; ++u) n += survives(v[u]) ? 1u : 0u;
     }
     n = wave_sum(n);
     if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = n;
     __syncthreads();
-    if (threadIdx.x == 0) count[blockIdx.x] = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+    if (threadIdx.x == 0) count[b] = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
 }
 
-// Survivors before every chunk, by one block, 4096 chunks at a time; the total to the host.  (At most 65,536 numbers.)  The
-// scalar block is left as it was.
+// Survivors before every chunk, by one block, 4096 chunks at a time; the total to the host.  (At most 65,536 numbers.)
+// before[chunks]: whether the row pointers go down somewhere.  The scalar block is left as it was.
 __global__ __launch_bounds__(1024) void k_compact_scan(const uint32_t *__restrict__ count, int chunks, int64_t *__restrict__ before,
                                                       int64_t *d_scalars, int64_t *h_scalars_dev, int64_t publish_tag) {
     __shared__ uint64_t lds[1024 / 64];
@@ -95,8 +145,9 @@ __global__ __launch_bounds__(1024) void k_compact_scan(const uint32_t *__restric
         carry += total;
     }
     if (threadIdx.x == 0) own[S_C_NNZ] = (int64_t)carry;
+    if (threadIdx.x == S_DESCENDS) before[chunks] = standing;
     publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing, own, own_slot(S_C_NNZ));
-    if (threadIdx.x == S_C_NNZ) d_scalars[S_C_NNZ] = 0;
+    if (threadIdx.x == S_C_NNZ || threadIdx.x == S_DESCENDS) d_scalars[threadIdx.x] = 0;
 }
 
 // First row whose entries begin at `begin` or later (rows: none), by the 64 lanes of a wave.
@@ -105,7 +156,7 @@ __device__ __forceinline__ int64_t first_row_from(const RP *row_ptr, int64_t row
     int64_t lo = 0, hi = rows;                 // the answer lies in [lo, hi]
     while (lo < hi) {
         const int64_t step = (hi - lo + 63) / 64, at = lo + step * lane_id();
-        const bool before = at < hi && (int64_t)row_ptr[at] < begin;
+        const bool before = at < hi && max((int64_t)row_ptr[at], (int64_t)0) < begin;
         const int n = __popcll(__ballot(before));        // (the answer lies behind the n-th probe)
         if (n == 0) return lo;
         const int64_t base = lo;
@@ -115,16 +166,77 @@ __device__ __forceinline__ int64_t first_row_from(const RP *row_ptr, int64_t row
     return lo;
 }
 
+// The survivors of the part at `begin`: lane l of every wave gets those of the part's 64-entry word l, and returns how many
+// there are in the words before it.  (s_mask: as many words; a barrier before it is written again.)
+__device__ __forceinline__ uint32_t part_words(const float (&v)[16], unsigned long long *s_mask, unsigned long long *word, uint32_t *all) {
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const unsigned long long m = __ballot(survives(v[u]));
+        if (lane == 0) s_mask[u * (kCompactThreads / 64) + wave] = m;
+    }
+    __syncthreads();
+    *word = s_mask[lane];
+    const uint32_t n = (uint32_t)__popcll(*word), inc = wave_inclusive_scan(n);
+    *all = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    return inc - n;
+}
+// ... and how many of them lie before entry `offset` of the part; all lanes take part
+__device__ __forceinline__ int survivors_before(int offset, unsigned long long word, uint32_t prefix) {
+    const int w = offset >> 6, words_before = __shfl((int)prefix, min(w, 63), 64);
+    const unsigned long long own = __shfl(word, min(w, 63), 64);
+    return words_before + (w < 64 ? __popcll(own & ((1ull << (offset & 63)) - 1ull)) : __popcll(own));
+}
+
 template <typename RP>
 __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP> a, const int64_t *__restrict__ before,
                                                                  int64_t *__restrict__ new_row_ptr,
                                                                  int32_t *__restrict__ out_col,
                                                                  float *__restrict__ out_val) {
     __shared__ unsigned long long s_mask[kCompactPart / 64];
+    const int64_t descends = uniform_load(before + a.chunks);
+    const EntryRange range = entry_range(a);
+    if (descends) return;                                        // (the host makes the pass again, see compact_descending)
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const int64_t c0 = (int64_t)blockIdx.x * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
-    const bool last_chunk = blockIdx.x == gridDim.x - 1;
-    int64_t base = before[blockIdx.x];
+    const int b = (int)blockIdx.x - a.row_blocks(kCompactRows);
+    if (b < 0) {
+        // 4096 rows: those that begin in the part in which the first of them does, and behind the first 4096 that do
+        const int64_t r0 = (int64_t)blockIdx.x * kCompactRows, at0 = clamped(a, r0);
+        // (the end of the arrays belongs to the last chunk's last part)
+        const int64_t chunk = min(at0 / a.chunk, (int64_t)a.chunks - 1), c0 = chunk * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
+        const int64_t parts = max((c1 - c0 + kCompactPart - 1) / kCompactPart, (int64_t)1);
+        const int64_t part = min((at0 - c0) / kCompactPart, parts - 1), begin = c0 + part * kCompactPart;
+        const int64_t end = min(begin + kCompactPart, c1);
+        const bool rest = chunk == a.chunks - 1 && part == parts - 1;
+        const int64_t from = (begin == 0 ? 0 : first_row_from(a.row_ptr, a.rows, begin)) + kCompactRows;
+        if (from >= r0 + kCompactRows) return;
+        int64_t base = before[chunk];
+        float v[16];
+        unsigned long long word;
+        uint32_t prefix, all;
+        for (int64_t p = c0; p < begin; p += kCompactPart) {
+            load_part(a.val, p, c1, v);
+            drop_outside(range, p, v);
+            prefix = part_words(v, s_mask, &word, &all);
+            base += all;
+            __syncthreads();
+        }
+        load_part(a.val, begin, c1, v);
+        drop_outside(range, begin, v);
+        prefix = part_words(v, s_mask, &word, &all);
+#pragma unroll 4
+        for (int u = 0; u < kCompactRows / kCompactThreads; ++u) {
+            const int64_t r = r0 + u * kCompactThreads + threadIdx.x;
+            const int64_t at = r <= a.rows ? clamped(a, r) : INT64_MAX;
+            const bool here = r >= from && r <= a.rows && (at < end || rest);
+            const int n = survivors_before(here ? (int)(at - begin) : 0, word, prefix);
+            if (here) new_row_ptr[r] = base + n;
+        }
+        return;
+    }
+    const int64_t c0 = (int64_t)b * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
+    const bool last_chunk = b == a.chunks - 1;
+    int64_t base = before[b];
     int64_t row = c0 == 0 ? 0 : first_row_from(a.row_ptr, a.rows, c0);
     for (int64_t begin = c0; begin < c1 || begin == c0; begin += kCompactPart) {
         const int64_t end = min(begin + kCompactPart, c1);
@@ -132,65 +244,110 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
         int32_t c[16];
         load_part(a.val, begin, c1, v);
         load_part(a.col, begin, c1, c);
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const unsigned long long m = __ballot(survives(v[u]));
-            if (lane == 0) s_mask[u * (kCompactThreads / 64) + wave] = m;
-        }
-        __syncthreads();
-        // every wave: lane l holds the survivors of the part's 64-entry words before word l
-        const unsigned long long word = s_mask[lane];
-        const uint32_t n = (uint32_t)__popcll(word), inc = wave_inclusive_scan(n);
-        const int prefix = (int)(inc - n);
+        drop_outside(range, begin, v);
+        unsigned long long word;
+        uint32_t all;
+        const uint32_t prefix = part_words(v, s_mask, &word, &all);
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int w = u * (kCompactThreads / 64) + wave;
             const unsigned long long m = __ballot(survives(v[u]));
-            const int first = __builtin_amdgcn_readlane(prefix, __builtin_amdgcn_readfirstlane(w));
+            const int first = __builtin_amdgcn_readlane((int)prefix, __builtin_amdgcn_readfirstlane(w));
             if (survives(v[u])) {
                 const int64_t p = base + first + __popcll(m & ((1ull << lane) - 1ull));
                 out_col[p] = c[u];
                 out_val[p] = v[u];
             }
         }
-        // the rows that begin in this part; behind the last part all that are left, row_ptr's end among them
+        // the rows that begin in this part, the first 4096 of them; behind the last part all that are left, row_ptr's end
+        // among them
         const bool rest = last_chunk && end >= c1;
-        for (int64_t r0 = row;; r0 += kCompactThreads) {
+        for (int64_t r0 = row; r0 < row + kCompactRows; r0 += kCompactThreads) {
             const int64_t r = r0 + threadIdx.x;
             const int64_t at = r <= a.rows ? min(max((int64_t)a.row_ptr[r], begin), rest ? end : INT64_MAX) : INT64_MAX;
             const bool here = r <= a.rows && (at < end || rest);
-            // (the look-up of a lane's own word: all lanes take part)
-            const int offset = here ? (int)(at - begin) : 0, w = offset >> 6;
-            const int words_before = __shfl(prefix, min(w, 63), 64);
-            const unsigned long long own = __shfl(word, min(w, 63), 64);
-            if (here) {
-                const int in_word = w < 64 ? __popcll(own & ((1ull << (offset & 63)) - 1ull)) : __popcll(own);
-                new_row_ptr[r] = base + words_before + in_word;
-            }
+            const int n = survivors_before(here ? (int)(at - begin) : 0, word, prefix);
+            if (here) new_row_ptr[r] = base + n;
             if (!__syncthreads_and(here)) break;
         }
-        base += __builtin_amdgcn_readlane((int)inc, 63);
+        base += all;
         if (end >= c1) break;
         row = first_row_from(a.row_ptr, a.rows, end);
         __syncthreads();
     }
 }
 
+// ---- row pointers that go down somewhere --------------------------------------------------------
+// The largest of the row pointers up to each, by one block.
 template <typename RP>
-static void compact_launch(tsp_context *ctx, CompactArgs<RP> &a, uint32_t *count, int64_t *before, hipStream_t s) {
-    a.chunk = compact_chunk(a.nnz);
-    const int chunks = (int)compact_chunks(a.nnz);
-    hipLaunchKernelGGL(k_compact_count<RP>, dim3(chunks), dim3(kCompactThreads), 0, s, a, count);
-    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, s, count, chunks, before, ctx->d_scalars, ctx->h_scalars_dev,
+__global__ __launch_bounds__(1024) void k_compact_ascending(CompactArgs<RP> a, int64_t *__restrict__ ascending) {
+    __shared__ int64_t s_most[1024];
+    int64_t carry = 0;
+    for (int64_t r0 = 0; r0 <= a.rows; r0 += 1024) {
+        const int64_t r = r0 + threadIdx.x;
+        int64_t x = r <= a.rows ? max(clamped(a, r), carry) : carry;
+        s_most[threadIdx.x] = x;
+        __syncthreads();
+        for (unsigned d = 1; d < 1024; d <<= 1) {
+            const int64_t left = threadIdx.x >= d ? s_most[threadIdx.x - d] : 0;
+            __syncthreads();
+            x = max(x, left);
+            s_most[threadIdx.x] = x;
+            __syncthreads();
+        }
+        if (r <= a.rows) ascending[r] = x;
+        carry = s_most[1023];
+        __syncthreads();
+    }
+}
+// The new row pointers in their place, a wave per row: the survivors of the chunk before the row's first entry.
+__global__ __launch_bounds__(256) void k_compact_row_ptr(int64_t *__restrict__ row_ptr, int64_t rows, const float *__restrict__ val,
+                                                         int64_t chunk, int chunks, const int64_t *__restrict__ before) {
+    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r > rows) return;
+    const int64_t at = row_ptr[r], b = min(at / chunk, (int64_t)chunks - 1);
+    uint32_t n = 0;
+    for (int64_t e = max(b * chunk, before[chunks + 1]) + lane_id(); e < at; e += 64) n += survives(val[e]) ? 1u : 0u;
+    n = wave_sum(n);
+    if (lane_id() == 0) row_ptr[r] = before[b] + n;
+}
+
+template <typename RP>
+static CompactArgs<RP> compact_args(const tsp_csr *C) {
+    return {static_cast<const RP *>(C->row_ptr), C->col_idx, static_cast<const float *>(C->val), C->rows, C->nnz, C->rows,
+            compact_chunk(C->nnz), (int)compact_chunks(C->nnz)};
+}
+template <typename RP>
+static dim3 compact_grid(const CompactArgs<RP> &a, int rows_per_block) {
+    return dim3((unsigned)(a.chunks + a.row_blocks(rows_per_block)));
+}
+template <typename RP>
+static void compact_launch(tsp_context *ctx, const CompactArgs<RP> &a, uint32_t *count, int64_t *before, hipStream_t s) {
+    hipLaunchKernelGGL(k_compact_count<RP>, compact_grid(a, kCheckRows), dim3(kCompactThreads), 0, s, a, count, before, ctx->d_scalars);
+    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, s, count, a.chunks, before, ctx->d_scalars, ctx->h_scalars_dev,
                        ++ctx->publish_tag);
+}
+// The pass again for a matrix whose row pointers go down, with ascending ones in `row_ptr`: the counts, for which it waits.
+template <typename RP>
+static int compact_descending(tsp_context *ctx, const CompactArgs<RP> &a, int64_t *row_ptr, uint32_t *count, int64_t *before,
+                              CompactArgs<int64_t> *again, hipStream_t s) {
+    hipLaunchKernelGGL(k_compact_ascending<RP>, dim3(1), dim3(1024), 0, s, a, row_ptr);
+    *again = {row_ptr, a.col, a.val, -1, a.nnz, a.rows, a.chunk, a.chunks};
+    compact_launch(ctx, *again, count, before, s);
+    TSP_HIP_CHECK(ctx, hipGetLastError());
+    return wait_published_scalars(ctx, ctx->publish_tag, s);
+}
+static void compact_descending_fill(const CompactArgs<int64_t> &a, const int64_t *before, int64_t *row_ptr, int32_t *col, float *val, hipStream_t s) {
+    hipLaunchKernelGGL(k_compact_fill<int64_t>, compact_grid(a, kCompactRows), dim3(kCompactThreads), 0, s, a, before, row_ptr, col, val);
+    hipLaunchKernelGGL(k_compact_row_ptr, dim3((unsigned)((a.last + 4) / 4)), dim3(256), 0, s, row_ptr, a.last, a.val, a.chunk,
+                       a.chunks, before);
 }
 
 template <typename RP>
 static int compact_run(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStream_t s, bool *taken) {
-    CompactArgs<RP> a{static_cast<const RP *>(C->row_ptr), C->col_idx, static_cast<const float *>(C->val), C->rows, C->nnz, 0};
-    const int64_t chunks = compact_chunks(C->nnz);
-    uint32_t *count = ctx_alloc_n<uint32_t>(ctx, (size_t)chunks, s);
-    int64_t *before = ctx_alloc_n<int64_t>(ctx, (size_t)chunks, s);
+    const CompactArgs<RP> a = compact_args<RP>(C);
+    uint32_t *count = ctx_alloc_n<uint32_t>(ctx, (size_t)a.chunks, s);
+    int64_t *before = ctx_alloc_n<int64_t>(ctx, (size_t)a.chunks + 2, s);
     int64_t *new_row_ptr = nullptr;
     int32_t *col = nullptr;
     float *val = nullptr;
@@ -206,20 +363,28 @@ static int compact_run(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStre
     compact_launch(ctx, a, count, before, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(hip_fail(ctx, e));
-    const int rc = wait_published_scalars(ctx, ctx->publish_tag, s);      // host synchronisation: the new nnz
+    int rc = wait_published_scalars(ctx, ctx->publish_tag, s);            // host synchronisation: the new nnz
     if (rc) return fail(rc);
+    const bool descends = ctx->h_scalars[S_DESCENDS] != 0;
+    CompactArgs<int64_t> again{};
+    if (descends) {
+        new_row_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)C->rows + 1, s);
+        rc = new_row_ptr ? compact_descending(ctx, a, new_row_ptr, count, before, &again, s) : (int)TSP_ERR_ALLOC_FAILED;
+        if (rc) return fail(rc);
+    }
     const int64_t nnz = ctx->h_scalars[S_C_NNZ];
-    if (taken && nnz == C->nnz) {                        // nothing to drop: the caller's arrays are the result
+    if (taken && !descends && nnz == C->nnz) {                        // nothing to drop: the caller's arrays are the result
         fail(TSP_OK);                                    // (releases the scratch arrays)
         *out = *C;
         *taken = true;
         return TSP_OK;
     }
-    new_row_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)C->rows + 1, s);
+    if (!new_row_ptr) new_row_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)C->rows + 1, s);
     col = ctx_alloc_n<int32_t>(ctx, (size_t)nnz, s);
     val = ctx_alloc_n<float>(ctx, (size_t)nnz, s);
     if (!new_row_ptr || !col || !val) return fail(TSP_ERR_ALLOC_FAILED);
-    hipLaunchKernelGGL(k_compact_fill<RP>, dim3((unsigned)chunks), dim3(kCompactThreads), 0, s, a, before, new_row_ptr, col, val);
+    if (descends) compact_descending_fill(again, before, new_row_ptr, col, val, s);
+    else hipLaunchKernelGGL(k_compact_fill<RP>, compact_grid(a, kCompactRows), dim3(kCompactThreads), 0, s, a, before, new_row_ptr, col, val);
     e = hipGetLastError();
     if (e != hipSuccess) return fail(hip_fail(ctx, e));
     ctx_free(ctx, count, s);
@@ -254,7 +419,7 @@ int compact_zeros(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStream_t 
 // (static_scratch_setup) and only that pointer is ever handed to kernels.
 constexpr int64_t kStaticMaxRows = TSP_COMPACT_STATIC_MAX_ROWS;
 constexpr size_t kStaticCountBytes = (size_t)kCompactChunks * sizeof(uint32_t);
-constexpr size_t kStaticBeforeBytes = (size_t)kCompactChunks * sizeof(int64_t);
+constexpr size_t kStaticBeforeBytes = (size_t)(kCompactChunks + 32) * sizeof(int64_t);
 static __device__ __align__(256) unsigned char scratch[kStaticBeforeBytes + kStaticCountBytes];
 
 constexpr int kMaxDevices = 64;
@@ -284,15 +449,23 @@ static int compact_run_static(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, 
     if (rc) return rc;
     int64_t *before = reinterpret_cast<int64_t *>(base);
     uint32_t *count = reinterpret_cast<uint32_t *>(base + kStaticBeforeBytes);
-    CompactArgs<RP> a{static_cast<const RP *>(C->row_ptr), C->col_idx, static_cast<const float *>(C->val), C->rows, C->nnz, 0};
+    const CompactArgs<RP> a = compact_args<RP>(C);
+    int64_t *const new_row_ptr = static_cast<int64_t *>(out->row_ptr);
+    float *const val = static_cast<float *>(out->val);
     // (nothing in the scratch array has to start at zero; the copy does not wait for the host)
     compact_launch(ctx, a, count, before, s);
-    hipLaunchKernelGGL(k_compact_fill<RP>, dim3((unsigned)compact_chunks(C->nnz)), dim3(kCompactThreads), 0, s, a, before,
-                       static_cast<int64_t *>(out->row_ptr), out->col_idx, static_cast<float *>(out->val));
+    hipLaunchKernelGGL(k_compact_fill<RP>, compact_grid(a, kCompactRows), dim3(kCompactThreads), 0, s, a, before, new_row_ptr, out->col_idx, val);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e);
     rc = wait_published_scalars(ctx, ctx->publish_tag, s);       // host synchronisation: the new nnz
     if (rc) return rc;
+    if (ctx->h_scalars[S_DESCENDS]) {
+        CompactArgs<int64_t> again{};
+        rc = compact_descending(ctx, a, new_row_ptr, count, before, &again, s);
+        if (rc) return rc;
+        compact_descending_fill(again, before, new_row_ptr, out->col_idx, val, s);
+        TSP_HIP_CHECK(ctx, hipGetLastError());
+    }
     const int64_t nnz = ctx->h_scalars[S_C_NNZ];
     out->rows = C->rows;
     out->cols = C->cols;

@@ -1,0 +1,95 @@
+"""tsp_compact_zeros and tsp_compact_zeros_static against numpy, on row pointers that chunks of entries could get wrong: rows
+that begin behind the first entry and end before the last (a slice of a matrix), many more rows than entries, runs of empty
+rows either side of what one block finds, and pointers that go down.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+PART, ROWS = 4096, 4096                  # entries of a part and rows of a block in csrc/compact.hip
+
+
+@pytest.fixture(scope="module")
+def tsp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2009_14600_amd import tsp as binding
+    binding.load_library()
+    return binding
+
+
+def _expected(row_ptr, col, val):
+    starts = np.maximum.accumulate(np.clip(np.array([int(x) for x in row_ptr], dtype=object), 0, val.size).astype(np.int64))
+    keep = ~(val == 0)
+    keep[:starts[0]] = keep[starts[-1]:] = False
+    before = np.concatenate([[0], np.cumsum(keep)])
+    return before[starts], col[keep], val[keep]
+
+
+def _check(tsp, what, row_ptr, nnz, i64=True, seed=0):
+    import torch
+    rng = np.random.default_rng(seed)
+    print(f"compaction: {what}, {len(row_ptr) - 1} rows, {nnz} entries", flush=True)
+    val = np.where(rng.random(nnz) < 0.3, 0.0, rng.uniform(0.5, 1, nnz)).astype(np.float32)
+    val[::97] = np.nan
+    val[5::101] = -0.0
+    col = np.arange(nnz, dtype=np.int32)
+    want = _expected(row_ptr, col, val)
+    dev = [torch.from_numpy(x).cuda() for x in (np.array([int(x) for x in row_ptr], dtype=np.int64 if i64 else np.int32), col, val)]
+    h = tsp.Handle()
+    try:
+        A = tsp.DeviceCSR(len(row_ptr) - 1, max(nnz, 1), *dev)
+        for static in (False, True):
+            if static:
+                if A.rows < 1:
+                    continue
+                out = [torch.full((A.rows + 1,), -7, dtype=torch.int64, device="cuda"), torch.zeros(max(nnz, 1), dtype=torch.int32, device="cuda"),
+                       torch.zeros(max(nnz, 1), dtype=torch.float32, device="cuda")]
+                n = h.compact_zeros_static(A, *out)
+                got = [out[0].cpu().numpy(), out[1][:n].cpu().numpy(), out[2][:n].cpu().numpy()]
+            else:
+                C = h.compact_zeros(A)
+                n, got = C.nnz, C.to_host()
+                C.free()
+            assert n == want[2].size
+            for x, y in zip(got, want):
+                assert np.array_equal(x, y, equal_nan=x.dtype == np.float32), (what, static)
+    finally:
+        h.close()
+
+
+def _pointers(lengths, first=0):
+    return first + np.concatenate([[0], np.cumsum(lengths)])
+
+
+@pytest.mark.parametrize("i64", [False, True])
+@pytest.mark.parametrize("first,slack", [(1, 0), (0, 1), (PART, PART), (PART - 1, 3 * PART + 1), (17, 5000), (9 * PART + 5, 0)])
+def test_a_slice_of_rows(tsp, i64, first, slack):
+    rng = np.random.default_rng(first + slack)
+    p = _pointers(rng.integers(0, 30, 700), first)
+    _check(tsp, "slice", p, int(p[-1]) + slack, i64)
+    _check(tsp, "slice without entries", np.full(9, first), first + slack + 1, i64)
+
+
+@pytest.mark.parametrize("empty", [ROWS - 1, ROWS, ROWS + 1, 3 * ROWS + 5, 100001])
+@pytest.mark.parametrize("entries", [0, 1, PART, 2 * PART + 9])
+def test_runs_of_empty_rows(tsp, empty, entries):
+    full = np.full(entries, 1)
+    none = np.zeros(empty, np.int64)
+    for what, lengths in (("behind", [full, none]), ("in front", [none, full]), ("between", [full[:entries // 2], none, full[entries // 2:], none, full])):
+        p = _pointers(np.concatenate(lengths).astype(np.int64), 3)
+        _check(tsp, f"empty rows {what}", p, int(p[-1]) + 2, seed=entries)
+
+
+@pytest.mark.parametrize("i64", [False, True])
+@pytest.mark.parametrize("seed", range(6))
+def test_row_pointers_that_go_down(tsp, i64, seed):
+    rng = np.random.default_rng(seed)
+    p = [int(x) for x in _pointers(rng.integers(0, 30, 1500))]
+    nnz = p[-1]
+    far = 2 ** 62 if i64 else 2 ** 31 - 1
+    for _ in range(1 + 3 * seed):
+        p[int(rng.integers(0, len(p)))] = int(rng.choice([-far, far, 0, nnz, int(rng.integers(0, nnz)), -1, nnz + 1]))
+    _check(tsp, "pointers that go down", p, nnz, i64, seed)
+    _check(tsp, "negative and none", [-5, -7, 0, 0], 2 * PART, i64)
