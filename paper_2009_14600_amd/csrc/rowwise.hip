@@ -1193,10 +1193,15 @@ struct Workspace {                       // everything the path allocates, relea
     std::vector<void *> blocks;
     bool failed = false;
     template <typename Tp>
-    Tp *get(size_t n) {
+    Tp *get_if_there(size_t n) {
         Tp *p = ctx_alloc_n<Tp>(ctx, n, s);
         if (p) blocks.push_back(p);
-        else failed = true;
+        return p;
+    }
+    template <typename Tp>
+    Tp *get(size_t n) {
+        Tp *p = get_if_there<Tp>(n);
+        failed = failed || !p;
         return p;
     }
     void keep(void *p) { blocks.erase(std::find(blocks.begin(), blocks.end(), p)); }
@@ -1500,6 +1505,22 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     m.blocks = (int)small_blocks;
     // (a small product without heavy rows: the last block of the small ones finishes)
     bool finish_too = known && hint.nnz >= 0 && chunks == 1 && n_heavy == 0;
+    auto heavy_arrays = [&]() {
+        if (n_heavy == 0) return (int)TSP_OK;
+        if (!pack) {
+            pack = ws.get<uint32_t>((size_t)B->nnz + 64);     // (a piece is read whole)
+            word = ws.get<uint2>((size_t)B->nnz + 64);
+            words = ws.get<int32_t>((size_t)B->rows);
+            if (windows > 1) table = ws.get<int32_t>((size_t)B->rows * (windows + 1));
+        }
+        offset = ws.get<uint32_t>((size_t)n_heavy * windows);
+        // the pattern of the heavy rows, kept for the multiplication: a bit per column, also of the empty windows.
+        // Where that is too much, the multiplication has it found again, some rows at a time.
+        const int64_t row_words = ((int64_t)windows << shift) / 32;
+        bit_rows = pattern_rows(n_heavy);
+        while (!(bits = ws.get_if_there<uint32_t>((size_t)(bit_rows * row_words))) && bit_rows > 1) bit_rows /= 2;
+        return ws.failed || !bits ? (int)TSP_ERR_ALLOC_FAILED : (int)TSP_OK;
+    };
     auto size_rows = [&](bool again) {
         if (again || n_tasks > left.task_cap || n_heavy > left.heavy_cap) {
             // the lists did not fit: make them again, as large as they have to be
@@ -1510,21 +1531,10 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
             hipLaunchKernelGGL(k_clear_lists, dim3(1), dim3(64), 0, s, ctx->d_scalars);
             prepare(ctx, A, ma, &left, s);
-        }
-        if (n_heavy > 0) {
-            if (!pack) {
-                pack = ws.get<uint32_t>((size_t)B->nnz + 64);     // (a piece is read whole)
-                word = ws.get<uint2>((size_t)B->nnz + 64);
-                words = ws.get<int32_t>((size_t)B->rows);
-                if (windows > 1) table = ws.get<int32_t>((size_t)B->rows * (windows + 1));
+            if (again) {
+                const int rc = heavy_arrays();
+                if (rc) return rc;
             }
-            offset = ws.get<uint32_t>((size_t)n_heavy * windows);
-            // the pattern of the heavy rows, kept for the multiplication: a bit per column, also of the empty windows.
-            // Where that is too much, the multiplication has it found again, some rows at a time.
-            const int64_t row_bytes = ((int64_t)windows << shift) / 8;
-            bit_rows = pattern_rows(n_heavy);
-            bits = ws.get<uint32_t>((size_t)(bit_rows * row_bytes / 4));
-            if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
         }
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
         auto kernel = shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true> : k_row_small<8, false>)
@@ -1606,7 +1616,9 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     // A product of the sizes of the last one: the kernels of the multiplication follow at once, into arrays for as many
     // entries as that one had and some more, and k_row_finish lets them run if this product fits; the GPU does not
     // wait for the host to learn nnz(C) (8 us of 78 on a 512x512 mesh).  Otherwise they are launched again below.
-    const bool ahead = known && hint.nnz >= 0 && pattern_rows(n_heavy) == n_heavy;
+    int rc = heavy_arrays();
+    if (rc) return rc;
+    const bool ahead = known && hint.nnz >= 0 && bit_rows == n_heavy;
     int64_t room = 0;
     if (ahead) {
         room = hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20);
@@ -1617,7 +1629,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         kind = FillKind{(FillKind::Sum)hint.sum, hint.scale};
         expected = Expected{room, n_heavy, n_tasks, kind};
     }
-    int rc = size_rows(false);
+    rc = size_rows(false);
     if (rc) return rc;
     phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
     const bool had_small = hint.small;

@@ -72,9 +72,13 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
     bool by_rows = false, by_tiles = false;
     const int64_t tag = ctx->publish_tag;
     rc = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows);
-    if (!rc && !by_rows) {
+    // (no memory for the row kernels, whose arrays go by rows and columns: the tiles' go by entries and may fit)
+    const bool no_memory = rc == TSP_ERR_ALLOC_FAILED;
+    if ((!rc && !by_rows) || no_memory) {
         by_tiles = true;
-        if (ctx->publish_tag != tag) {             // the row kernels have looked at the operands and used the scalar block
+        rc = TSP_OK;
+        ctx->scalars_clean = false;
+        if (no_memory || ctx->publish_tag != tag) {   // the row kernels have looked at the operands and used the scalar block
             hipLaunchKernelGGL(k_clear_scalars_all, dim3(1), dim3(64), 0, s, ctx->d_scalars);
             if (ctx->count_products) count_products(ctx, A, B, s);
         }

@@ -22,17 +22,20 @@ def tsp():
 
 
 class _FailingHandle:
-    """A handle whose allocator callback returns NULL from its k-th call on (k counted from 0)."""
+    """A handle whose allocator callback returns NULL from its k-th call on (k counted from 0), or for blocks larger than
+    most_bytes."""
 
-    def __init__(self, tsp, fail_from):
+    def __init__(self, tsp, fail_from, most_bytes=1 << 62):
         import torch
         self.calls = 0
+        self.refused = 0
         self.blocks = {}
 
         def alloc(_user, nbytes, _stream):
             k = self.calls
             self.calls += 1
-            if k >= fail_from:
+            if k >= fail_from or nbytes > most_bytes:
+                self.refused += 1
                 return None
             t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
             self.blocks[t.data_ptr()] = t
@@ -104,6 +107,50 @@ def test_allocator_returning_null_at_every_call_site(tsp, maker, tile_edge):
         assert out.nnz == want_nnz
         assert h.lib.tsp_csr_free(h.h, ctypes.byref(out), None) == 0
         h.close()
+
+
+@pytest.mark.parametrize("what,most_bytes", [("entries of the small rows", 2 << 20), ("pattern of the heavy rows", 1 << 20)])
+def test_row_kernels_without_the_memory_they_ask_for(tsp, oracle, what, most_bytes):
+    """An allocator that refuses large blocks: a product by rows whose small rows ask for more goes by tiles, one whose heavy
+    rows do takes them some at a time; on a new handle, and on one that knows the product."""
+    import torch
+    rng = np.random.default_rng(3)
+    if what.startswith("entries"):                  # 20000 rows of one entry: 3.8 MB, everything else less than 1 MB
+        n = 20000
+        A = inputs.from_coo(n, n, np.arange(n), rng.integers(0, n, n), rng.uniform(-1, 1, n))
+        B = A
+    else:                                           # 400 rows of 17 entries, 70001 columns: a pattern of 3.7 MB
+        A = inputs.from_coo(400, 500, np.repeat(np.arange(400), 17), np.concatenate([np.sort(rng.choice(500, 17, replace=False)) for _ in range(400)]),
+                            rng.uniform(-1, 1, 400 * 17))
+        B = inputs.from_coo(500, 70001, np.repeat(np.arange(500), 2), np.sort(rng.integers(0, 35000, (500, 2)) * 2 + [0, 1], axis=1).ravel(),
+                            rng.uniform(-1, 1, 1000))
+    want = oracle.spgemm(A, B, threads=2)
+    dA = tsp.to_device(A)
+    dB = dA if B is A else tsp.to_device(B)
+    sA, sB = dA._struct(), dB._struct()
+
+    def multiply(h):
+        out, st = tsp._Csr(), tsp._Stats()
+        status = h.lib.tsp_spgemm(h.h, ctypes.byref(sA), ctypes.byref(sA if B is A else sB), ctypes.byref(out), None)
+        torch.cuda.synchronize()
+        assert status == 0 and h.lib.tsp_get_stats(h.h, ctypes.byref(st)) == 0
+        got = []
+        for ptr, count, dtype in ((out.row_ptr, out.rows + 1, torch.int64), (out.col_idx, out.nnz, torch.int32), (out.val, out.nnz, torch.float32)):
+            got.append(h.blocks[ptr].view(dtype)[:count].cpu().numpy())
+        assert h.lib.tsp_csr_free(h.h, ctypes.byref(out), None) == 0
+        assert np.array_equal(got[0], want.row_ptr) and np.array_equal(got[1], want.col)
+        assert np.all(np.abs(got[2].astype(np.float64) - want.val) <= 1e-5 * want.mag + 1e-7)
+        return st.pairs
+
+    plenty = _FailingHandle(tsp, fail_from=1 << 30)
+    assert multiply(plenty) == 0 and plenty.refused == 0
+    plenty.close()
+    h = _FailingHandle(tsp, fail_from=1 << 30, most_bytes=most_bytes)
+    for _ in range(3):
+        refused = h.refused
+        assert (multiply(h) == 0) == what.startswith("pattern")
+        assert h.refused > refused
+    h.close()
 
 
 def test_index_overflow_and_unsupported_span(tsp):
