@@ -212,7 +212,9 @@ class Handle:
         self._torch = torch
         self._blocks = {}
         self._typed = {}             # the last view of a block, by address and type; never handed out itself
+        torch.cuda.init()            # (so that the two functions below need not look)
         self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        self._device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
         def _alloc(_user, nbytes, _stream):
             try:
@@ -236,7 +238,7 @@ class Handle:
     # -- plumbing ---------------------------------------------------------------------------
     def _stream(self):
         if self._raw_stream is not None:
-            return self._raw_stream(self._torch.cuda.current_device())
+            return self._raw_stream(self._device())
         return self._torch.cuda.current_stream().cuda_stream
 
     def _view(self, ptr: int, count: int, dtype):
@@ -244,15 +246,16 @@ class Handle:
         torch = self._torch
         if count == 0 or not ptr:
             return torch.empty(0, dtype=dtype, device="cuda")
+        views = self._typed.get(ptr)
+        if views is not None:
+            view = views.get(dtype)
+            if view is not None and view[0] == count:    # (the last view of the block, where it is the one wanted again)
+                return view[1].data           # a tensor of the caller's own: its shape may be changed in place
         block = self._blocks.get(ptr)
         if block is not None:                 # an array at the start of its block, as outputs are
-            views = self._typed.get(ptr)
-            if views is None:
-                views = self._typed[ptr] = {}
-            view = views.get(dtype)
-            if view is None or view[0] != count:     # (the last view of the block, where it is the one wanted again)
-                view = views[dtype] = (count, block.view(dtype).narrow(0, 0, count))
-            return view[1].data               # a tensor of the caller's own: its shape may be changed in place
+            view = block.view(dtype).narrow(0, 0, count)
+            self._typed.setdefault(ptr, {})[dtype] = (count, view)
+            return view.data
         itemsize = dtype.itemsize
         for base, block in self._blocks.items():
             if base <= ptr and ptr + count * itemsize <= base + block.numel():
