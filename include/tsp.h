@@ -213,6 +213,7 @@ int tsp_trim(tsp_handle handle, void *stream);
  * the fp32 additions; an option that chooses among the tile kernels (NUMERIC_RUN, MATRIX_CORES, WORK_ORDER,
  * STRIP_ORDER, WIDE_INDEX away from its default) keeps the tiles.  Which way suits is looked at when the sizes of the
  * operands differ from the last product's, at the price of one more wait.
+ * A product that is repeated on a handle with the same options has the same bits every time.
  * Errors: INVALID_ARG, SHAPE_MISMATCH, NOT_CANONICAL, ALLOC_FAILED, INDEX_OVERFLOW, HIP,
  * UNSUPPORTED (a tile-row of C spans more than 131072 tile columns between its first and its
  * last candidate tile, i.e. 2097152 columns; or a tile-row of C holds 2^32 entries or more).

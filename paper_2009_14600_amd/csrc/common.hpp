@@ -270,6 +270,8 @@ struct NumericLaunch {
     int64_t *to_clear, *row_ptr_copy;        // or null
     const int32_t *live;                     // or null: {whether to run at all, output tiles}, where the sizes are bounds only
 };
+// Which kernel that is: with the same one the sums of an entry have the same order
+int numeric_kernel(const tsp_context *ctx, const tsp_tiles_s *A, const tsp_tiles_s *B, const NumericLaunch &n);
 hipError_t numeric_launch(tsp_context *ctx, const tsp_tiles_s *A, const tsp_tiles_s *B, const tsp_plan_s *P, const NumericLaunch &n,
                           int32_t *col, float *val, hipStream_t s);
 // taken (may be null): the caller owns C and gives it up; when no entry is zero *out takes C's arrays as they

@@ -555,17 +555,40 @@ __global__ __launch_bounds__(kNumThreads) void k_numeric(
     }
 }
 
+namespace {
+struct NumericChoice {
+    int tiles_per_wave;
+    bool whole_rows, unrolled, sparse_tiles;
+};
+NumericChoice numeric_choice(const tsp_context *ctx, const tsp_tiles_s *A, const tsp_tiles_s *B, const NumericLaunch &n) {
+    NumericChoice c{};
+    // Tiles one wave walks: one group of four measured fastest on all workloads (more waves in
+    // flight); two groups per wave remain available through TSP_OPT_NUMERIC_RUN.
+    c.tiles_per_wave = kGroupTiles;
+    if (ctx->numeric_run_len == 4 || ctx->numeric_run_len == 8) c.tiles_per_wave = ctx->numeric_run_len;
+    if (!ctx->matrix_cores) c.tiles_per_wave = kGroupTiles;
+    // Short, sparse tile-rows (meshes in two dimensions, for one): a wave per tile-row, output through LDS
+    c.whole_rows = ctx->matrix_cores && ctx->numeric_run_len == 0 && n.max_row_c_tiles <= kRowTiles &&
+                   n.max_row_pairs <= kBlockEntries && n.max_row_entries <= kRowEntries;
+    c.unrolled = c.whole_rows && n.max_row_c_tiles <= kRowTilesUnrolled;
+    // operands whose tiles hold a handful of entries: a step takes the halves that meet (see kHalves)
+    c.sparse_tiles = !c.whole_rows && ctx->matrix_cores && c.tiles_per_wave == kGroupTiles && n.a_tiles > 0 && n.b_tiles > 0 &&
+                     A->nnz <= kSparseTileEntries * n.a_tiles && B->nnz <= kSparseTileEntries * n.b_tiles;
+    return c;
+}
+}  // namespace
+
+int numeric_kernel(const tsp_context *ctx, const tsp_tiles_s *A, const tsp_tiles_s *B, const NumericLaunch &n) {
+    const NumericChoice c = numeric_choice(ctx, A, B, n);
+    return c.whole_rows ? 1 + c.unrolled : c.sparse_tiles ? 3 : 0;
+}
+
 hipError_t numeric_launch(tsp_context *ctx, const tsp_tiles_s *A, const tsp_tiles_s *B, const tsp_plan_s *P, const NumericLaunch &n,
                           int32_t *col, float *val, hipStream_t s) {
     KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
-    // Tiles one wave walks: one group of four measured fastest on all workloads (more waves in
-    // flight); two groups per wave remain available through TSP_OPT_NUMERIC_RUN.
-    int tiles_per_wave = kGroupTiles;
-    if (ctx->numeric_run_len == 4 || ctx->numeric_run_len == 8) tiles_per_wave = ctx->numeric_run_len;
-    if (!ctx->matrix_cores) tiles_per_wave = kGroupTiles;
-    // Short, sparse tile-rows (meshes in two dimensions, for one): a wave per tile-row, output through LDS
-    const bool whole_rows = ctx->matrix_cores && ctx->numeric_run_len == 0 && n.max_row_c_tiles <= kRowTiles &&
-                            n.max_row_pairs <= kBlockEntries && n.max_row_entries <= kRowEntries;
+    const NumericChoice choice = numeric_choice(ctx, A, B, n);
+    const int tiles_per_wave = choice.tiles_per_wave;
+    const bool whole_rows = choice.whole_rows;
     const int64_t tiles_per_block = (int64_t)(kNumThreads / 64) * tiles_per_wave;
     int64_t blocks = whole_rows ? (P->c_tile_rows + kNumThreads / 64 - 1) / (kNumThreads / 64)
                                 : (n.c_tiles + tiles_per_block - 1) / tiles_per_block;
@@ -586,12 +609,9 @@ hipError_t numeric_launch(tsp_context *ctx, const tsp_tiles_s *A, const tsp_tile
                         (uint64_t)n.c_nnz * 4 < limit && !ctx->force_wide;
     auto kernel = narrow ? (tiles_per_wave == 4 ? k_numeric<true, 4, true> : k_numeric<true, 8, true>)
                          : (tiles_per_wave == 4 ? k_numeric<false, 4, true> : k_numeric<false, 8, true>);
-    // operands whose tiles hold a handful of entries: a step takes the halves that meet (see kHalves)
-    const bool sparse_tiles = ctx->matrix_cores && tiles_per_wave == kGroupTiles && n.a_tiles > 0 && n.b_tiles > 0 &&
-                              A->nnz <= kSparseTileEntries * n.a_tiles && B->nnz <= kSparseTileEntries * n.b_tiles;
-    if (sparse_tiles) kernel = narrow ? k_numeric<true, 4, true, false, true> : k_numeric<false, 4, true, false, true>;
+    if (choice.sparse_tiles) kernel = narrow ? k_numeric<true, 4, true, false, true> : k_numeric<false, 4, true, false, true>;
     if (!ctx->matrix_cores) kernel = narrow ? k_numeric<true, 4, false> : k_numeric<false, 4, false>;
-    if (whole_rows && n.max_row_c_tiles <= kRowTilesUnrolled)
+    if (choice.unrolled)
         kernel = narrow ? k_numeric<true, kRowTilesUnrolled, true, true> : k_numeric<false, kRowTilesUnrolled, true, true>;
     else if (whole_rows)
         kernel = narrow ? k_numeric<true, kRowTiles, true, true> : k_numeric<false, kRowTiles, true, true>;

@@ -10,7 +10,7 @@
 //   k_heavy_count   the other rows: a block per row, one bit per column of C in LDS
 //   k_heavy_fill    a block per row and some windows of columns, a dense accumulator in LDS
 //
-// Runs are bit-identical.  Products of fp16 numbers are exact in fp32.  An entry of a small row is summed in fp32 in
+// A product that is repeated on a handle has the same bits every time.  Products of fp16 numbers are exact in fp32.  An entry of a small row is summed in fp32 in
 // the order of the entries of A.  A heavy entry is summed in integers where every partial sum is exact in them (all products
 // are multiples of a power of two that the operands' values say; then the order of the additions does not matter and a
 // whole block shares the accumulator), and otherwise in fp64 by one wave in the order of the entries of A.
@@ -398,7 +398,7 @@ __host__ __device__ inline bool fill_exact(FillKind k, int64_t range_a, int64_t 
     for (int64_t n = 1; n < longest; n <<= 1) ++bits;
     return granularity >= k.scale && (k.sum == FillKind::kInt32 ? bits <= 31 : bits <= 63 && product_bits <= 51);
 }
-inline FillKind fill_kind(const int64_t *h) {
+__host__ __device__ inline FillKind fill_kind(const int64_t *h) {
     const int scale = 512 - (int)(h[S_ROW_RANGE_A] & 0xFFFF) - (int)(h[S_ROW_RANGE_B] & 0xFFFF);
     for (auto sum : {FillKind::kInt32, FillKind::kInt64})
         if (fill_exact({sum, scale}, h[S_ROW_RANGE_A], h[S_ROW_RANGE_B], h[S_ROW_LONGEST])) return {sum, scale};
@@ -411,7 +411,9 @@ struct Expected {
     FillKind kind;
     __host__ __device__ bool holds(const int64_t *scalars) const {
         return !scalars[S_INVALID] && scalars[S_C_NNZ] <= nnz && scalars[S_ROW_HEAVY] <= heavy && scalars[S_ROW_TASKS] <= tasks &&
-               fill_exact(kind, scalars[S_ROW_RANGE_A], scalars[S_ROW_RANGE_B], scalars[S_ROW_LONGEST]);
+               fill_exact(kind, scalars[S_ROW_RANGE_A], scalars[S_ROW_RANGE_B], scalars[S_ROW_LONGEST]) &&
+               // (fp64 does for any values, but where integers do their sums have other last bits)
+               (kind.sum != FillKind::kDouble || fill_kind(scalars).sum == FillKind::kDouble);
     }
 };
 
@@ -1294,6 +1296,10 @@ void launch_fill(FillArgs &f, FillKind kind, hipStream_t s) {
 __global__ void k_clear_lists(int64_t *d_scalars) {
     if (threadIdx.x == 0) d_scalars[S_ROW_LISTS] = 0;
 }
+// all but the count of products, which has run before anything else of the call
+__global__ void k_clear_rows(int64_t *d_scalars, int64_t products) {
+    if (threadIdx.x < kScalars) d_scalars[threadIdx.x] = threadIdx.x == S_PRODUCTS ? products : 0;
+}
 
 // Whether the row kernels are faster for A*B than the tile kernels: what the two take beyond the 30 us that both do, from
 // times of 90 products of meshes, stencils, blocks, random and power-law graphs (in ns).  Rows: 13 per heavy row, 1 per
@@ -1305,9 +1311,11 @@ static bool rows_preferred(int64_t products, int64_t small_products, int lanes, 
     return 13 * heavy + products / 1000 + lanes * (small_products / 1000) <= 19000 + candidates / 20 * 3;
 }
 
-int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s,
-                   bool *taken) {
-    *taken = false;
+// What a run of the row kernels has come to
+enum RowsEnd { kRowsNotTaken, kRowsTaken, kRowsOtherLanes };
+
+static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, RowsEnd *end) {
+    *end = kRowsNotTaken;
     // Options that choose among the tile kernels, and shapes this path is not for: fewer rows than CUs (the sizing pass
     // has a block per heavy row), rows of more columns than the bitmaps of k_row_prepare hold (60 KB)
     if (!ctx->matrix_cores || ctx->numeric_run_len || ctx->work_order || ctx->strip_order || ctx->force_wide) return TSP_OK;
@@ -1325,7 +1333,8 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     // lanes 0.1 ns per row); for a row of B as many as its mean has
     // entries; a table of the row that is three quarters full at most, with a margin over the mean number of products, 256
     // slots at most
-    SmallShape shape{A->nnz <= 8 * A->rows && !(known && hint.wide) ? 8 : 16, 1, 32, 24};
+    const int lanes_unless_wide = A->nnz <= 8 * A->rows ? 8 : 16;
+    SmallShape shape{known && hint.wide ? 16 : lanes_unless_wide, 1, 32, 24};
     {
         const double list = (double)B->nnz / (double)std::max<int64_t>(B->rows, 1), mean = (double)A->nnz / (double)A->rows * list;
         while (shape.slots < 256 && shape.slots * 3 / 4 < 1.25 * mean) shape.slots *= 2;
@@ -1442,6 +1451,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     };
     int64_t n_heavy = left.heavy_cap, n_tasks = left.task_cap;
     FillKind kind{};
+    bool other_lanes = false;                // the product at hand wants its small rows by another number of lanes
     auto sizes_known = [&]() {               // the host has the numbers of k_row_finish
         const int64_t *h = ctx->h_scalars;
         if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
@@ -1449,6 +1459,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         n_tasks = h[S_ROW_TASKS];
         std::copy(sizes, sizes + 6, hint.sizes);
         hint.wide = h[S_ROW_WIDE] > A->rows / 64;
+        other_lanes = shape.slots <= 128 && shape.lanes != (hint.wide ? 16 : lanes_unless_wide);
         const int64_t heavy = shape.lanes == 8 && hint.wide ? n_heavy - std::min(n_heavy, h[S_ROW_WIDE]) : n_heavy;
         const int64_t small = std::min(h[S_ROW_PRODUCTS], (A->rows - heavy) * shape.products);      // (at most)
         hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : shape.lanes, heavy, h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
@@ -1466,9 +1477,11 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
         if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);
         if (!rc) rc = sizes_known();
         if (rc) return rc;
-        if (hint.tiles) return TSP_OK;       // (the tile kernels start over; the scalars they use are cleared for them)
+        if (hint.tiles || other_lanes) {     // (the tile kernels start over; the scalars they use are cleared for them)
+            *end = hint.tiles ? kRowsNotTaken : kRowsOtherLanes;
+            return TSP_OK;
+        }
     }
-    *taken = true;
 
     phase_begin(ctx, TSP_PHASE_SYMBOLIC, s);
     row_ptr = ws.get<int64_t>((size_t)A->rows + 1);
@@ -1643,6 +1656,10 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     const int64_t had_heavy = n_heavy, had_tasks = n_tasks, products = ctx->h_scalars[S_PRODUCTS];
     rc = sizes_known();
     if (rc) return rc;
+    if (hint.tiles || other_lanes) {         // another matrix of the same sizes: as it would be done if it had come first
+        *end = hint.tiles ? kRowsNotTaken : kRowsOtherLanes;
+        return TSP_OK;
+    }
     const bool done = ahead && expected.holds(ctx->h_scalars) && (had_small || ctx->h_scalars[S_ROW_SMALL] == 0);
     if (!done) {
         live = nullptr;
@@ -1685,7 +1702,28 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     C->val = val;
     C->row_ptr_type = TSP_I64;
     C->val_type = TSP_F32;
+    *end = kRowsTaken;
     return TSP_OK;
+}
+
+// What has been learnt of a product decides how the next one of the same sizes is started, and not how its entries are
+// summed: where the product at hand asks for another number of lanes or for tiles it is started again.  So a product has
+// the same bits as often as it is repeated.
+int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, bool *taken) {
+    RowsEnd end = kRowsNotTaken;
+    int rc = TSP_OK;
+    for (int runs = 0; runs < 2; ++runs) {
+        const int64_t tag = ctx->publish_tag;
+        rc = rowwise_run(ctx, A, B, alias, C, s, &end);
+        if (rc || end == kRowsTaken) break;
+        if (ctx->publish_tag != tag) {
+            hipLaunchKernelGGL(k_clear_rows, dim3(1), dim3(64), 0, s, ctx->d_scalars, ctx->h_scalars[S_PRODUCTS]);
+            ctx->scalars_clean = false;
+        }
+        if (end != kRowsOtherLanes) break;
+    }
+    *taken = end == kRowsTaken;
+    return rc;
 }
 
 }  // namespace tsp

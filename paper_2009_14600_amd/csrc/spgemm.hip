@@ -70,7 +70,6 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
     if (ctx->count_products) count_products(ctx, A, B, s);
     TilesAhead ahead;
     bool by_rows = false, by_tiles = false;
-    const int64_t tag = ctx->publish_tag;
     rc = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows);
     // (no memory for the row kernels, whose arrays go by rows and columns: the tiles' go by entries and may fit)
     const bool no_memory = rc == TSP_ERR_ALLOC_FAILED;
@@ -78,7 +77,7 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
         by_tiles = true;
         rc = TSP_OK;
         ctx->scalars_clean = false;
-        if (no_memory || ctx->publish_tag != tag) {   // the row kernels have looked at the operands and used the scalar block
+        if (no_memory) {                           // (the row kernels have left the scalar block somewhere in between)
             hipLaunchKernelGGL(k_clear_scalars_all, dim3(1), dim3(64), 0, s, ctx->d_scalars);
             if (ctx->count_products) count_products(ctx, A, B, s);
         }

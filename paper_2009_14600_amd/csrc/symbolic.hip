@@ -2103,6 +2103,7 @@ list_kernels:
     // A product of the sizes of an earlier one (tsp_spgemm): the multiplication follows at once, into arrays for as many
     // entries as that one had and some more; k_row_ptr lets it run if this product fits.
     ListExpected expected{};
+    NumericLaunch launched{};
     const bool early = ahead && hinted && hint.nnz > 0;
     if (early) {
         expected = {z, hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20), hint.max_row_entries};
@@ -2131,10 +2132,9 @@ list_kernels:
     phase_end(ctx, TSP_PHASE_COUNT, s);
     if (early) {
         phase_begin(ctx, TSP_PHASE_NUMERIC, s);
-        SYM_CHECK(numeric_launch(ctx, A, B, P,
-                                 {hint.c_tiles, z.pairs, expected.nnz, z.max_row_c_tiles, z.max_row_pairs, expected.max_row_entries, hint.a_tiles,
-                                  z.b_tiles, nullptr, nullptr, live},
-                                 ahead->col, ahead->val, s));
+        launched = {hint.c_tiles, z.pairs, expected.nnz, z.max_row_c_tiles, z.max_row_pairs, expected.max_row_entries, hint.a_tiles,
+                    z.b_tiles, nullptr, nullptr, live};
+        SYM_CHECK(numeric_launch(ctx, A, B, P, launched, ahead->col, ahead->val, s));
         phase_end(ctx, TSP_PHASE_NUMERIC, s);
     }
     if (!rc) rc = published ? wait_published_scalars(ctx, ctx->publish_tag, s) : read_scalars(ctx, s);   // ---- sync 2: nnz(C)
@@ -2157,7 +2157,11 @@ list_kernels:
             if (i != S_C_NNZ && i != S_MAX_ROW_ENTRIES && i != S_UNSUPPORTED && i != S_INTERNAL) ctx->h_scalars[i] = first_numbers[i];
     if (ctx->h_scalars[S_UNSUPPORTED]) return cleanup(TSP_ERR_UNSUPPORTED);
     if (ctx->h_scalars[S_INTERNAL]) return cleanup(TSP_ERR_HIP);
-    if (early && !ran_again) ahead->done = expected.holds(ctx->h_scalars);
+    // (by the kernel that its own sizes ask for, so that a product has the same bits whatever came before it)
+    if (early && !ran_again)
+        ahead->done = expected.holds(h) && numeric_kernel(ctx, A, B, launched) ==
+                      numeric_kernel(ctx, A, B, {P->c_tiles, P->pairs, h[S_C_NNZ], P->max_row_c_tiles, P->max_row_pairs, h[S_MAX_ROW_ENTRIES],
+                                                 A->ntiles, B->ntiles, nullptr, nullptr, nullptr});
     hint.nnz = ctx->h_scalars[S_C_NNZ];
     hint.a_tiles = A->ntiles;
     hint.c_tiles = P->c_tiles;

@@ -146,6 +146,87 @@ def test_more_lanes_for_rows_of_up_to_16_entries(tsp, oracle):
         h.close()
 
 
+def _bits(h, tsp, A, B=None):
+    C = h.spgemm(A, A if B is None else B)
+    by_rows = h.stats()["pairs"] == 0
+    out = [x.view(np.uint32) if x.dtype == np.float32 else x for x in C.to_host()]
+    C.free()
+    return by_rows, out
+
+
+def _exact_lengths(rng, cols, lengths, values):
+    col = np.concatenate([np.sort(rng.choice(cols, k, replace=False)) for k in lengths])
+    return inputs.from_coo(len(lengths), cols, np.repeat(np.arange(len(lengths)), lengths), col, values(col.size), "exact lengths")
+
+
+def _full_tiles(rng, n):
+    """64 entries per row: four full tiles in every tile-row."""
+    tile = np.sort(np.argsort(rng.random((n // 16, n // 16)), axis=1)[:, :4], axis=1)
+    col = (tile[:, None, :, None] * 16 + np.arange(16)).repeat(16, axis=1).reshape(n, 64)
+    return inputs.from_coo(n, n, np.repeat(np.arange(n), 64), col.ravel(), rng.normal(size=64 * n), "full tiles")
+
+
+@pytest.mark.parametrize("what", ["lanes of small rows", "sums of heavy rows", "rows, then tiles", "kernels by tiles"])
+def test_the_same_bits_whatever_came_before(tsp, oracle, what):
+    """Products of the same sizes on one handle, in several orders and each of them repeated, against the bits of a new
+    handle: what the handle has learnt of the last one may not show in the result."""
+    rng = np.random.default_rng(21)
+    B = None
+    if what == "lanes of small rows":               # rows of up to 16 entries are small or not, by how many there are
+        n = 1600
+        even, nine, most = np.full(n, 4), np.full(n, 3), np.full(n, 2)
+        nine[::6] = 9
+        nine[1:3] -= 1
+        most[::7] = 16
+        most[1:4] -= 2
+        all_of = [_exact_lengths(rng, n, k, lambda m: rng.normal(size=m)) for k in (even, nine, most)]
+        B = _exact_lengths(rng, n, np.full(n, 8), lambda m: rng.normal(size=m))
+    elif what == "sums of heavy rows":              # 32-bit integers, 64-bit integers, fp64
+        n = 900
+        values = [lambda m: rng.choice([-1.0, 1.0], m), lambda m: rng.uniform(-1, 1, m), lambda m: rng.normal(size=m) * 10.0 ** rng.integers(-3, 4, m)]
+        all_of = [_exact_lengths(rng, n, np.full(n, 30), v) for v in values]
+    elif what == "rows, then tiles":
+        n = 4096
+        all_of = [_exact_lengths(rng, n, np.full(n, 64), lambda m: rng.normal(size=m)), _full_tiles(rng, n)]
+    else:                                           # whole tile-rows, tiles of a few entries, full tiles
+        n = 1600
+        r = np.arange(n)
+        band = inputs.from_coo(n, n, np.repeat(r, 3), np.sort((r[:, None] + [0, 1, 2]) % n, axis=1).ravel(), rng.normal(size=3 * n), "band")
+        long = np.full(n, 3)
+        long[:16], long[16:792] = 100, 1            # (as many entries in all)
+        all_of = [band, _exact_lengths(rng, n, np.full(n, 3), lambda m: rng.normal(size=m)), _exact_lengths(rng, n, long, lambda m: rng.normal(size=m))]
+        assert len({A.nnz for A in all_of}) == 1
+    dev = [tsp.to_device(A) for A in all_of]
+    dB = None if B is None else tsp.to_device(B)
+
+    def handle():
+        h = tsp.Handle()
+        if what == "kernels by tiles":
+            h.set_option(tsp.OPT_WORK_ORDER, 2)
+        return h
+
+    want = []
+    for A, dA in zip(all_of, dev):
+        h = handle()
+        want.append(_bits(h, tsp, dA, dB))
+        ref = oracle.spgemm(A, A if B is None else B, threads=4)
+        assert np.array_equal(want[-1][1][0], ref.row_ptr) and np.array_equal(want[-1][1][1], ref.col)
+        assert np.all(np.abs(want[-1][1][2].view(np.float32).astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+        h.close()
+    h = handle()
+    try:
+        k = len(dev)
+        order = [0, 0, 1, 1] if what == "rows, then tiles" else [0, 0, 0, 1, 1, k - 1, k - 1, 1, 0, k - 1, 0, 0]
+        for i in order:
+            print(f"{what}: product {i}", flush=True)
+            by_rows, got = _bits(h, tsp, dev[i], dB)
+            assert by_rows == want[i][0]
+            for x, y in zip(got, want[i][1]):
+                assert np.array_equal(x, y)
+    finally:
+        h.close()
+
+
 def test_rejects_what_is_not_canonical(tsp):
     import torch
     h = tsp.Handle()
