@@ -212,8 +212,11 @@ int tsp_trim(tsp_handle handle, void *stream);
  * one unknown per node, random matrices) are multiplied row by row instead, with the same result up to the order of
  * the fp32 additions; an option that chooses among the tile kernels (NUMERIC_RUN, MATRIX_CORES, WORK_ORDER,
  * STRIP_ORDER, WIDE_INDEX away from its default) keeps the tiles.  Which way suits is looked at when the sizes of the
- * operands differ from the last product's, at the price of one more wait.
- * A product that is repeated on a handle with the same options has the same bits every time.
+ * operands are not those of one of the last eight products of the handle, at the price of one more wait, and again when a
+ * product by tiles turns out to have another number of pairs of tiles than the one it was decided on.
+ * A product that is repeated on a handle with the same options has the same bits every time (unless an operand of the
+ * same rows, columns and number of entries, but another structure, came in between: the two may then share the choice
+ * between rows and tiles).
  * Errors: INVALID_ARG, SHAPE_MISMATCH, NOT_CANONICAL, ALLOC_FAILED, INDEX_OVERFLOW, HIP,
  * UNSUPPORTED (a tile-row of C spans more than 131072 tile columns between its first and its
  * last candidate tile, i.e. 2097152 columns; or a tile-row of C holds 2^32 entries or more).

@@ -78,11 +78,13 @@ struct ListSizes {
 };
 // What symbolic_run goes by for a product of the sizes of an earlier one, see there
 struct ListHint {
-    int64_t sizes[5] = {-1, -1, -1, -1, -1};
     bool usable = false;
     ListSizes most;
     int64_t nnz = -1, c_tiles = 0, a_tiles = 0;    // of the last one
     int64_t max_row_entries = 0;
+    bool general = false;                          // it took the general task-list kernel ...
+    int32_t *order = nullptr;                      // ... and its tile-rows in this order (heaviest first), or null
+    int64_t order_rows = 0;
 };
 // What the multiplication has been launched with before the host knows the sizes; k_row_ptr sees whether it holds
 struct ListExpected {
@@ -98,17 +100,50 @@ struct ListExpected {
     }
 };
 
-// What the row kernels found for the last product (rowwise.hip), by the sizes of its operands: whether the tile kernels
+// What the row kernels found for the last product of the same sizes (rowwise.hip): whether the tile kernels
 // suit it better, and how long its lists of work are.  Only the choice of kernels and the sizes of workspaces follow
 // from it; the numbers of the product at hand are checked against it.
 struct RowHint {
-    int64_t sizes[6] = {-1, -1, -1, -1, -1, -1};   // rows and nnz of A, rows, nnz and cols of B, A is B
+    bool ready = false;
     bool tiles = false;
+    int64_t candidates = 0;                        // pairs of tiles, by which that was decided
     int64_t heavy = 0, tasks = 0;
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows
     bool wide = false;                             // so many rows of 9 to 16 entries that 16 lanes per row pay
     int sum = 0, scale = 0;                        // how the heavy rows are summed
+};
+
+// The hints of the last products, by the sizes of their operands: a program that multiplies several matrices in turn (A*P,
+// then R*(AP), say) finds what it left.
+template <typename Hint>
+struct HintMemory {
+    static constexpr int kProducts = 8;
+    struct Sizes {                                 // rows and nnz of A, rows, nnz and cols of B, A is B
+        int64_t of[6] = {-1, -1, -1, -1, -1, -1};
+        bool operator==(const Sizes &o) const { return std::equal(of, of + 6, o.of); }
+    };
+    Sizes sizes[kProducts];
+    Hint hints[kProducts];
+    int64_t used[kProducts] = {}, uses = 0;
+    // The hint for these sizes, a new one in the place of the one not used for longest where there is none; drop(hint) gets
+    // that one first.
+    template <typename Drop>
+    Hint &find(const Sizes &of, Drop drop) {
+        int at = 0;
+        for (int i = 0; i < kProducts; ++i) {
+            if (sizes[i] == of) {
+                used[i] = ++uses;
+                return hints[i];
+            }
+            if (used[i] < used[at]) at = i;
+        }
+        drop(hints[at]);
+        sizes[at] = of;
+        hints[at] = Hint{};
+        used[at] = ++uses;
+        return hints[at];
+    }
 };
 
 }  // namespace tsp
@@ -132,12 +167,8 @@ struct tsp_context {
     int matrix_cores = 1;                          // 0: block products on the vector ALUs
     int64_t pattern_bytes = (int64_t)16 << 30;     // TSP_OPT_PATTERN_BYTES
     int compact = 0;                               // 1: tsp_spgemm removes zero-valued entries from C
-    bool hint_general = false;                     // the last product took the general task-list kernel ...
-    int64_t hint_sizes[4] = {-1, -1, -1, -1};      // ... with these rows and nnz of A and of B
-    int32_t *hint_order = nullptr;                 // ... and took its tile-rows in this order (heaviest first), or null
-    int64_t hint_order_rows = 0;
-    tsp::RowHint row_hint;
-    tsp::ListHint list_hint;
+    tsp::HintMemory<tsp::RowHint> row_hints;
+    tsp::HintMemory<tsp::ListHint> list_hints;
     int last_hip = 0;
     tsp_stats stats{};
     void *chain_slots = nullptr;                   // device, for the chained scans (chain.hpp)
@@ -242,9 +273,9 @@ int scan_exclusive_i32_to_i64(tsp_context *ctx, const int32_t *in, int64_t *out,
 int check_csr_host(const tsp_csr *A);                // what can be said about an operand without reading its arrays
 void fill_selection_criteria(tsp_context *ctx, int64_t rows, int64_t nnz, int64_t ntiles);   // of the left operand
 // The whole product by rows (rowwise.hip), where the structure of the operands asks for it: *taken says whether it
-// did.  Both operands have passed check_csr_host; the scalar block is zero.
+// did, *remembered that it did not by what it found earlier.  Both operands have passed check_csr_host; the scalar block is zero.
 int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s,
-                   bool *taken);
+                   bool *taken, RowHint **remembered);
 int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out,
                     hipStream_t s);
 void tiles_release(tsp_context *ctx, tsp_tiles_s *t, hipStream_t s);

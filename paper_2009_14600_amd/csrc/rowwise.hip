@@ -1314,18 +1314,20 @@ static bool rows_preferred(int64_t products, int64_t small_products, int lanes, 
 // What a run of the row kernels has come to
 enum RowsEnd { kRowsNotTaken, kRowsTaken, kRowsOtherLanes };
 
-static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, RowsEnd *end) {
+static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, RowsEnd *end,
+                       RowHint **remembered) {
     *end = kRowsNotTaken;
     // Options that choose among the tile kernels, and shapes this path is not for: fewer rows than CUs (the sizing pass
     // has a block per heavy row), rows of more columns than the bitmaps of k_row_prepare hold (60 KB)
     if (!ctx->matrix_cores || ctx->numeric_run_len || ctx->work_order || ctx->strip_order || ctx->force_wide) return TSP_OK;
     int64_t most_cols = (int64_t)60 * 1024 * 8 * T;
     if (A->rows < 256 || A->rows > (1 << 27) || A->nnz == 0 || B->nnz == 0 || A->cols > most_cols || B->cols > most_cols) return TSP_OK;
-    RowHint &hint = ctx->row_hint;
-    const int64_t sizes[6] = {A->rows, A->nnz, B->rows, B->nnz, B->cols, alias};
-    const bool known = std::equal(sizes, sizes + 6, hint.sizes);
-    if (known && hint.tiles) return TSP_OK;
-
+    RowHint &hint = ctx->row_hints.find({{A->rows, A->nnz, B->rows, B->nnz, B->cols, alias}}, [](RowHint &) {});
+    const bool known = hint.ready;
+    if (known && hint.tiles) {
+        *remembered = &hint;
+        return TSP_OK;
+    }
     if (A->nnz >= (1 << 28) || B->nnz >= (1 << 28)) return TSP_OK;      // (32-bit byte offsets into 8-byte records)
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
     // Small rows: 8 lanes where the mean row of A has no more entries, else 16, or where the last product of these sizes had
@@ -1457,12 +1459,13 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
         n_heavy = h[S_ROW_HEAVY];
         n_tasks = h[S_ROW_TASKS];
-        std::copy(sizes, sizes + 6, hint.sizes);
+        hint.ready = true;
         hint.wide = h[S_ROW_WIDE] > A->rows / 64;
         other_lanes = shape.slots <= 128 && shape.lanes != (hint.wide ? 16 : lanes_unless_wide);
         const int64_t heavy = shape.lanes == 8 && hint.wide ? n_heavy - std::min(n_heavy, h[S_ROW_WIDE]) : n_heavy;
         const int64_t small = std::min(h[S_ROW_PRODUCTS], (A->rows - heavy) * shape.products);      // (at most)
         hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : shape.lanes, heavy, h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
+        hint.candidates = h[S_CANDIDATES];
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
         hint.small = h[S_ROW_SMALL] > 0;
@@ -1709,12 +1712,14 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
 // What has been learnt of a product decides how the next one of the same sizes is started, and not how its entries are
 // summed: where the product at hand asks for another number of lanes or for tiles it is started again.  So a product has
 // the same bits as often as it is repeated.
-int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, bool *taken) {
+int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, bool *taken,
+                   RowHint **remembered) {
+    *remembered = nullptr;
     RowsEnd end = kRowsNotTaken;
     int rc = TSP_OK;
     for (int runs = 0; runs < 2; ++runs) {
         const int64_t tag = ctx->publish_tag;
-        rc = rowwise_run(ctx, A, B, alias, C, s, &end);
+        rc = rowwise_run(ctx, A, B, alias, C, s, &end, remembered);
         if (rc || end == kRowsTaken) break;
         if (ctx->publish_tag != tag) {
             hipLaunchKernelGGL(k_clear_rows, dim3(1), dim3(64), 0, s, ctx->d_scalars, ctx->h_scalars[S_PRODUCTS]);

@@ -2,6 +2,7 @@
 #include "common.hpp"
 
 #include <algorithm>
+#include <cstdlib>
 
 namespace tsp {
 __global__ void k_clear_scalars_all(int64_t *d_scalars) {
@@ -70,7 +71,8 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
     if (ctx->count_products) count_products(ctx, A, B, s);
     TilesAhead ahead;
     bool by_rows = false, by_tiles = false;
-    rc = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows);
+    RowHint *remembered = nullptr;
+    rc = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows, &remembered);
     // (no memory for the row kernels, whose arrays go by rows and columns: the tiles' go by entries and may fit)
     const bool no_memory = rc == TSP_ERR_ALLOC_FAILED;
     if ((!rc && !by_rows) || no_memory) {
@@ -88,6 +90,22 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
         if (!rc) rc = symbolic_run(ctx, ta, alias ? ta : tb, &plan, s, &ahead);
     }
     ctx->stats.products = !rc && ctx->count_products ? ctx->h_scalars[S_PRODUCTS] : -1;
+    // Tiles because an earlier product of the same sizes was for them, and this one has other pairs of tiles: the operands are
+    // looked at again, and the tiles dropped if they are for rows.
+    if (!rc && remembered && std::abs(plan->candidates - remembered->candidates) > remembered->candidates / 4) {
+        remembered->ready = false;
+        if (!ctx->scalars_clean) hipLaunchKernelGGL(k_clear_scalars_all, dim3(1), dim3(64), 0, s, ctx->d_scalars);
+        ctx->scalars_clean = false;
+        const int looked = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows, &remembered);
+        if (looked && looked != TSP_ERR_ALLOC_FAILED) rc = looked;
+        by_tiles = !by_rows;
+        if (rc || by_rows) {
+            ctx_free(ctx, ahead.col, s);
+            ctx_free(ctx, ahead.val, s);
+        } else {
+            ctx->scalars_clean = false;
+        }
+    }
     if (!rc && by_tiles) rc = numeric_enqueue(ctx, ta, alias ? ta : tb, plan, C, s, /*last_of_call=*/true, &ahead);   // the plan ends here
     if (!rc && ctx->compact) {                    // Algorithm 1, the compaction steps: strictly sparse result
         tsp_csr structural = *C;

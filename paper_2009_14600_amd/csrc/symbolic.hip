@@ -1753,6 +1753,13 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     int saved_words = 0;
     int64_t *row_pair_ptr = nullptr, *tmp = nullptr;
     int32_t *live = nullptr;
+    auto drop_order = [&](ListHint &h) {
+        ctx_free(ctx, h.order, s);
+        h.order = nullptr;
+        h.order_rows = 0;
+    };
+    ListHint &hint = ctx->list_hints.find({{A->rows, A->nnz, B->rows, B->nnz, B->cols, A == B}}, drop_order);
+    const bool key_known = hint.nnz >= 0;
     auto drop_ahead = [&]() {
         if (!ahead || ahead->done) return;
         ctx_free(ctx, ahead->col, s);
@@ -1768,7 +1775,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         ctx_free(ctx, row_words, s);
         ctx_free(ctx, row_cand, s);
         ctx_free(ctx, cursor, s);
-        if (order != ctx->hint_order) ctx_free(ctx, order, s);
+        if (order != hint.order) ctx_free(ctx, order, s);
         ctx_free(ctx, order_hist, s);
         ctx_free(ctx, row_nnz, s);
         ctx_free(ctx, tile_row_entries, s);
@@ -1839,8 +1846,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         // they are wasted; which kernel will run is known only after this pass, so the handle goes by what the
         // previous call with operands of the same sizes did.  The result is the same either way.
         size_t count_lds = (size_t)max_words * sizeof(uint32_t);
-        const bool general_expected = ctx->hint_general && ctx->hint_sizes[0] == A->rows && ctx->hint_sizes[1] == A->nnz &&
-                                      ctx->hint_sizes[2] == B->rows && ctx->hint_sizes[3] == B->nnz;
+        const bool general_expected = hint.general;
         if (direct_words > 0 && general_expected && (int64_t)ntr * direct_words * 17 * 4 <= ((int64_t)1 << 30) &&
             (size_t)direct_words * 17 * sizeof(uint32_t) <= 60 * 1024) {
             saved_words = direct_words;
@@ -1871,7 +1877,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
                                count_lds, s, ra, rb, lanes, max_words, direct_words,
                                /*only_marked=*/0, row_jmin, row_c_tiles, row_pairs, row_words, row_cand, ctx->d_scalars,
                                saved_bitmap, saved_cnt,
-                               general_expected && ctx->hint_order_rows == ntr ? ctx->hint_order : nullptr);
+                               general_expected && hint.order_rows == ntr ? hint.order : nullptr);
         SYM_CHECK(hipGetLastError());
     }
     {
@@ -1896,9 +1902,6 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     // ones of this product: k_sym_emit_listed leaves out a tile-row that does not fit, and the numbers of the product at
     // hand, checked below, then say that it has to run again with arrays that do.
     const int64_t *h = ctx->h_scalars;
-    ListHint &hint = ctx->list_hint;
-    const int64_t hint_key[5] = {A->rows, A->nnz, B->rows, B->nnz, B->cols};
-    const bool key_known = std::equal(hint_key, hint_key + 5, hint.sizes);
     bool hinted = key_known && hint.usable && ntr > 0 && n_chunks <= kMaxChunks && !strips_wanted(ctx, P, B);
     bool ran_again = false, arrived = false;                          // the host has the numbers of the counting kernels
     int64_t first_numbers[kScalars];               // ... and got them before the list kernel ran again
@@ -2006,15 +2009,9 @@ list_kernels:
             free_lists();
             goto list_kernels;
         }
-        ctx->hint_general = !listed;
+        hint.general = !listed;
         // (the order of the previous product goes; the general branch below may keep a new one)
-        ctx_free(ctx, ctx->hint_order, s);
-        ctx->hint_order = nullptr;
-        ctx->hint_order_rows = 0;
-        ctx->hint_sizes[0] = A->rows;
-        ctx->hint_sizes[1] = A->nnz;
-        ctx->hint_sizes[2] = B->rows;
-        ctx->hint_sizes[3] = B->nnz;
+        drop_order(hint);
         if (listed && fused_masks && !halves && by_block) {
             hipLaunchKernelGGL(k_sym_emit_block, dim3((unsigned)ntr), dim3(kBlockListThreads),
                                block_lds, s, ra, rb, words_cap, window, row_jmin, row_words, P->c_tile_row_ptr, row_pair_ptr,
@@ -2048,8 +2045,8 @@ list_kernels:
                                    order_hist + kOrderBuckets, order);
                 // the handle keeps the order: the counting kernel of the next call of this product starts with
                 // the heaviest tile-rows too
-                ctx->hint_order = order;
-                ctx->hint_order_rows = ntr;
+                hint.order = order;
+                hint.order_rows = ntr;
             }
             // tile-rows with very many candidates: larger blocks (each tile-row is one block's work, and the
             // longest ones end the launch; 256, 512, 768, 1024 threads: 69, 51, 54, 67 ms on the same graph)
@@ -2166,7 +2163,6 @@ list_kernels:
     hint.a_tiles = A->ntiles;
     hint.c_tiles = P->c_tiles;
     hint.max_row_entries = std::max(key_known ? hint.max_row_entries : 0, ctx->h_scalars[S_MAX_ROW_ENTRIES]);
-    std::copy(hint_key, hint_key + 5, hint.sizes);
     hint.usable = listed && fused_masks;
     hint.most = key_known ? hint.most.with(true_sizes()) : true_sizes();
     P->c_nnz = ctx->h_scalars[S_C_NNZ];

@@ -216,12 +216,45 @@ def test_the_same_bits_whatever_came_before(tsp, oracle, what):
     h = handle()
     try:
         k = len(dev)
-        order = [0, 0, 1, 1] if what == "rows, then tiles" else [0, 0, 0, 1, 1, k - 1, k - 1, 1, 0, k - 1, 0, 0]
-        for i in order:
+        for i in (0, 0, 0, 1, 1, k - 1, k - 1, 1, 0, k - 1, 0, 0):
             print(f"{what}: product {i}", flush=True)
             by_rows, got = _bits(h, tsp, dev[i], dB)
             assert by_rows == want[i][0]
             for x, y in zip(got, want[i][1]):
+                assert np.array_equal(x, y)
+    finally:
+        h.close()
+
+
+@pytest.mark.parametrize("count", [2, 8, 9, 11])
+@pytest.mark.parametrize("options", [{}, {"OPT_WORK_ORDER": 1}])
+def test_products_in_turn(tsp, oracle, count, options):
+    """Two and more products in turn on one handle, which remembers eight: by rows, by tiles, graphs by tiles (with an order
+    of their tile-rows that the handle keeps), rectangles; every result against the oracle's, the repeated ones bit by bit."""
+    rng = np.random.default_rng(count)
+    all_of = []
+    for i in range(count):
+        if i % 4 == 0:
+            all_of.append((_matrix(rng, 500 + 16 * i, 700, 5, "A"), _matrix(rng, 700, 300 + i, 4, "P")))
+        elif i % 4 == 1:
+            all_of.append((inputs.block_clustered(2048 + 16 * i, seed=i), None))
+        elif i % 4 == 2:
+            all_of.append((inputs.random_fixed_per_row(1100 + i, 12, seed=i), None))
+        else:
+            all_of.append((_matrix(rng, 300 + i, 500, 3, "R", dense=(1, 7)), _matrix(rng, 500, 900, rng.integers(0, 9, 500), "AP", dense=(0, 9))))
+    want = [oracle.spgemm(A, B or A, threads=4) for A, B in all_of]
+    h = tsp.Handle()
+    try:
+        for key, value in options.items():
+            h.set_option(getattr(tsp, key), value)
+        dev = [(tsp.to_device(A), None if B is None else tsp.to_device(B)) for A, B in all_of]
+        first = {}
+        for i in list(range(count)) * 3 + [int(x) for x in rng.integers(0, count, 12)]:
+            print(f"product {i} of {count}", flush=True)
+            _, got = _bits(h, tsp, *dev[i])
+            assert np.array_equal(got[0], want[i].row_ptr) and np.array_equal(got[1], want[i].col)
+            assert np.all(np.abs(got[2].view(np.float32).astype(np.float64) - want[i].val) <= 1e-5 * want[i].mag + 1e-7)
+            for x, y in zip(got, first.setdefault(i, got)):
                 assert np.array_equal(x, y)
     finally:
         h.close()
