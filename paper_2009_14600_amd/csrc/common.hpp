@@ -43,7 +43,10 @@ enum Scalar {
     S_ROW_RANGE_B = 22,
     S_ROW_LONGEST = 23,      // entries of the longest heavy row of A
     S_ROW_WIDE = 26,         // rows that would be small if a row had 16 lanes
-    S_ROW_ARRIVED = 16,      // blocks of k_row_small that are done
+    S_ROW_ARRIVED = 16,      // blocks of k_row_small, or of k_row_sample, that are done
+    S_SAMPLE_TILES = 28,     // k_row_sample: tiles in the tile-rows looked at, of A and (<< 32) of B
+    S_SAMPLE_COST = 29,      // ... and what their rows cost by rows
+    S_ROW_SKIP = 30,         // != 0: clearly a product by tiles, and its pairs of tiles as estimated, plus one
     S_LARGE_A = 24,          // tile-rows of an operand whose entries do not fit the registers of k_convert_block
     S_LARGE_B = 25,
     S_DESCENDS = 27,         // != 0: the row pointers of a matrix to be compacted go down somewhere
@@ -107,6 +110,8 @@ struct RowHint {
     bool ready = false;
     bool tiles = false;
     int64_t candidates = 0;                        // pairs of tiles, by which that was decided
+    bool estimated = false;                        // ... from some of the tile-rows
+    bool sample = true;                            // (a look at some of the tile-rows has not misled yet)
     int64_t heavy = 0, tasks = 0;
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows

@@ -3,6 +3,7 @@
 // task list, the counting pass and the block products all cost by the pair.  Here everything costs by the
 // intermediate product a_ik * b_kj:
 //
+//   k_row_sample    operands of sizes not seen before: a look at some of their tile-rows, whether they are clearly for tiles
 //   k_row_prepare   one pass over an operand: validation, entries as {column, value} records, tiles per tile-row,
 //                   and for A the number of intermediate products of every row and the lists of work
 //   k_row_finish    row_ptr of C; candidate tile pairs (the measure by which tsp_spgemm chooses this path) and other sums
@@ -71,6 +72,7 @@ struct PrepareArgs {
     int64_t heavy_cap, task_cap;
     uint32_t *rows_of;                   // of every tile-row: pack_rows()
     int64_t *d_scalars;
+    const int64_t *skip;                 // S_ROW_SKIP, or null
 };
 
 __device__ __forceinline__ uint32_t half_bits(uint16_t bits) { return bits; }
@@ -109,6 +111,7 @@ __device__ __forceinline__ bool small_row(int32_t entries, int32_t products, int
 template <int kTeam, int kU, typename RP, typename VT>
 __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a) {
     constexpr int kTeams = 256 / kTeam;
+    if (a.skip && uniform_load(a.skip)) return;
     extern __shared__ uint32_t lds_bitmap[];
     __shared__ int32_t s_ptr[kTeams][T + 1];
     __shared__ unsigned long long s_ub[kTeams][T];
@@ -300,6 +303,7 @@ struct SumArgs {
     const unsigned long long *products;
     int same;                            // A and B are one matrix
     unsigned long long *partial;         // [kPlanSums][kPlanBlocks]
+    const int64_t *skip;                 // S_ROW_SKIP, or null
 };
 enum { kSumCandidates, kSumTilesA, kSumTilesB, kSumProducts, kSumSmall, kSumRanges, kSumLongest, kSumWide };
 
@@ -380,7 +384,10 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
     __syncthreads();
     if (threadIdx.x < kPlanSums) put_for(shared, &a.partial[threadIdx.x * kPlanBlocks + block], s_sum[threadIdx.x]);
 }
-__global__ __launch_bounds__(256) void k_row_sums(const SumArgs a) { sum_tile_rows(a, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void k_row_sums(const SumArgs a) {
+    if (a.skip && uniform_load(a.skip)) return;
+    sum_tile_rows(a, blockIdx.x, gridDim.x);
+}
 
 // The accumulator that is exact for the heavy rows: int32_t, long long or double; the integers are values times 2^-scale.
 struct FillKind {
@@ -429,6 +436,7 @@ struct FinishArgs {
     bool clear;                          // the scalar block, for the next call
     Expected expected;
     int32_t *live;                       // [2]: whether what is expected holds, and the number of tasks
+    const int64_t *skip;                 // S_ROW_SKIP, or null: nothing has been counted then
 };
 
 // row_ptr of C from the row lengths: block b takes rows [2048 b, 2048 b + 2048), adds up the groups of 16 rows before
@@ -527,7 +535,10 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
                               own_slot(S_ROW_LONGEST) | own_slot(S_ROW_HEAVY) | own_slot(S_ROW_TASKS);
     publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, standing, own, kOwn, a.clear);
 }
-__global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) { row_finish<false>(a, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
+    if (a.skip && uniform_load(a.skip)) publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, standing_scalar(a.d_scalars), nullptr, 0);
+    else row_finish<false>(a, blockIdx.x, gridDim.x);
+}
 
 // ---- small rows -------------------------------------------------------------------------------------------------
 // How the small rows of a launch are worked off: lanes per row of A, lanes per row of B (a power of two, at most as
@@ -1212,6 +1223,12 @@ struct Workspace {                       // everything the path allocates, relea
     }
 };
 
+constexpr int kSampleRows = 128;         // tile-rows of an operand that are looked at
+constexpr int kSampleEntries = 4096;     // ... and entries of each, at most
+// A look pays where the pass over the operands takes long, and where a product by tiles is not out of the question: the pass
+// takes 26 ns per thousand entries, the look and the launches that then find nothing to do 20 us together.
+bool sample_pays(int64_t rows, int64_t nnz) { return nnz >= (1 << 18) && nnz > 8 * rows; }
+
 template <typename RP, typename VT>
 void launch_prepare(const PrepareArgs<RP, VT> &a, hipStream_t s) {
     const int64_t tile_rows = (a.rows + T - 1) / T;
@@ -1239,7 +1256,7 @@ struct LeftOperand {
     int64_t heavy_cap, task_cap;
 };
 
-void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const LeftOperand *left, hipStream_t s) {
+void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const LeftOperand *left, hipStream_t s, const int64_t *skip = nullptr) {
     auto run = [&](auto rp, auto v) {
         using RP = decltype(rp);
         using VT = decltype(v);
@@ -1270,6 +1287,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
             a.rows_of = left->rows_of;
         }
         a.d_scalars = ctx->d_scalars;
+        a.skip = skip;
         launch_prepare(a, s);
     };
     const bool f16 = M->val_type == TSP_F16;
@@ -1309,6 +1327,97 @@ __global__ void k_clear_rows(int64_t *d_scalars, int64_t products) {
 // tiles 68; 4000 rows of 73 entries at random: 105, 742).  Of the 90 the choice loses more than 6 % on three, 23 % on one.
 static bool rows_preferred(int64_t products, int64_t small_products, int lanes, int64_t heavy, int64_t candidates) {
     return 13 * heavy + products / 1000 + lanes * (small_products / 1000) <= 19000 + candidates / 20 * 3;
+}
+
+// The same from some of the tile-rows, a block each: what their rows cost by rows, and their tiles.  The pairs of tiles are
+// estimated as the tiles of A times the mean tile-row of B.  On a graph, whose long tile-rows are met most, that is too low,
+// by less than the distance at which it is a product by rows; elsewhere the tile kernels' own count shows it (tsp_spgemm).
+// Clearly for tiles: by rows at least twice as long.  The kernels of the look at all tile-rows, launched behind this one, then
+// have nothing to do, and the host waits for the end of it once either way.  10 us; first products of 131072 and of 24000
+// rows of blocks 348 -> 235 and 150 -> 122 us.
+struct SampleArgs {
+    const void *row_ptr[2];              // of A and B, as the caller gave them
+    const int32_t *col[2];
+    int64_t rows[2], cols[2], nnz[2];
+    int is_i64[2];
+    int blocks[2];                       // tile-rows looked at (0 of B: A and B are one matrix)
+    int small_lanes, small_products;
+    int64_t *d_scalars;
+};
+__global__ __launch_bounds__(256) void k_row_sample(const SampleArgs a) {
+    extern __shared__ uint32_t lds_bitmap[];
+    __shared__ int32_t s_ptr[T + 1];
+    __shared__ unsigned long long s_ub[T];
+    __shared__ unsigned s_tiles;
+    const int of = (int)blockIdx.x >= a.blocks[0], tid = threadIdx.x;
+    const int64_t at = (int64_t)blockIdx.x - of * a.blocks[0], tile_rows = (a.rows[of] + T - 1) / T;
+    const int64_t I = (2 * at + 1) * tile_rows / (2 * a.blocks[of]);
+    auto pointer = [&](int m, int64_t i) {
+        const int64_t p = a.is_i64[m] ? static_cast<const int64_t *>(a.row_ptr[m])[i] : static_cast<const int32_t *>(a.row_ptr[m])[i];
+        return (int32_t)min(max(p, (int64_t)0), a.nnz[m]);
+    };
+    const int words = (int)((a.cols[of] + T * 32 - 1) / (T * 32));
+    for (int w = tid; w < words; w += 256) lds_bitmap[w] = 0;
+    if (tid <= T) {
+        int32_t p = pointer(of, min(I * T + tid, a.rows[of]));
+        p = max(p, TSP_DPP(p, p, 0x111, 0xf, false));
+        p = max(p, TSP_DPP(p, p, 0x112, 0xf, false));
+        p = max(p, TSP_DPP(p, p, 0x114, 0xf, false));
+        p = max(p, TSP_DPP(p, p, 0x118, 0xf, false));
+        p = max(p, TSP_DPP(p, p, 0x142, 0xa, false));
+        s_ptr[tid] = p;
+        if (tid < T) s_ub[tid] = 0;
+    }
+    if (tid == 0) s_tiles = 0;
+    __syncthreads();
+    const int32_t e0 = s_ptr[0], entries = s_ptr[T] - e0, n = min(entries, kSampleEntries);
+    unsigned tiles = 0;
+    for (int k0 = tid; k0 < n; k0 += 4 * 256) {
+        int32_t c[4], len[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            c[u] = a.col[of][e0 + min(k0 + u * 256, n - 1)];
+            c[u] = (uint32_t)c[u] < (uint64_t)a.cols[of] ? c[u] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) len[u] = of ? 0 : min(max(pointer(a.blocks[1] ? 1 : 0, c[u] + 1) - pointer(a.blocks[1] ? 1 : 0, c[u]), 0), (1 << 25) - 1);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (k0 + u * 256 >= n) break;
+            const int32_t k = e0 + k0 + u * 256;
+            const uint32_t bit = 1u << ((c[u] >> 4) & 31);
+            tiles += !(atomicOr(&lds_bitmap[c[u] >> 9], bit) & bit);
+            if (of) continue;
+            int r = 0;
+#pragma unroll
+            for (int step = T / 2; step >= 1; step >>= 1)
+                if (s_ptr[r + step] <= k) r += step;
+            atomicAdd(&s_ub[r], (unsigned long long)(uint32_t)len[u]);
+        }
+    }
+    tiles = wave_sum(tiles);
+    if (lane_id() == 0) atomicAdd(&s_tiles, tiles);
+    __syncthreads();
+    if (tid >= T) return;
+    // (as if the rest of a longer tile-row were like its first entries)
+    const double more = n > 0 ? (double)entries / n : 1.0;
+    const int32_t ub = (int32_t)min(s_ub[tid], (unsigned long long)INT32_MAX);
+    const bool small = small_row(s_ptr[tid + 1] - s_ptr[tid], ub, a.small_lanes, a.small_products);
+    double cost = ub == 0 ? 0.0 : small ? (a.small_lanes + 1.0) * ub : 13000.0 + ub;        // rows_preferred, in ps
+    for (int d = 1; d < T; d <<= 1) cost += __shfl_xor(cost, d, T);
+    if (tid > 0) return;
+    auto *scalars = reinterpret_cast<unsigned long long *>(a.d_scalars);
+    atomicAdd(scalars + S_SAMPLE_TILES, (unsigned long long)(s_tiles * more) << (32 * of));
+    if (!of) atomicAdd(scalars + S_SAMPLE_COST, (unsigned long long)(cost * more));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (before this block counts as done)
+    if (atomicAdd(scalars + S_ROW_ARRIVED, 1ull) != gridDim.x - 1) return;
+    const unsigned long long both = __hip_atomic_load(scalars + S_SAMPLE_TILES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long all = __hip_atomic_load(scalars + S_SAMPLE_COST, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double scale = (double)((a.rows[0] + T - 1) / T) / a.blocks[0], tiles_a = (double)(both & 0xFFFFFFFFull);
+    const double mean_b = a.blocks[1] ? (double)(both >> 32) / a.blocks[1] : tiles_a / a.blocks[0];
+    const double candidates = tiles_a * scale * mean_b;
+    a.d_scalars[S_ROW_SKIP] = all * scale > 2.0 * (19e6 + 150.0 * candidates) ? (int64_t)candidates + 1 : 0;
+    a.d_scalars[S_ROW_ARRIVED] = 0;
 }
 
 // What a run of the row kernels has come to
@@ -1391,10 +1500,31 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
 
     phase_begin(ctx, TSP_PHASE_CONVERT, s);
+    const int64_t *skip = nullptr;
+    if (!known && hint.sample && sample_pays(A->rows, A->nnz)) {
+        skip = ctx->d_scalars + S_ROW_SKIP;
+        SampleArgs a{};
+        const tsp_csr *M[2] = {A, B};
+        int64_t words = 0;
+        for (int m = 0; m < 2; ++m) {
+            a.row_ptr[m] = M[m]->row_ptr;
+            a.col[m] = M[m]->col_idx;
+            a.rows[m] = M[m]->rows;
+            a.cols[m] = M[m]->cols;
+            a.nnz[m] = M[m]->nnz;
+            a.is_i64[m] = M[m]->row_ptr_type == TSP_I64;
+            a.blocks[m] = m && alias ? 0 : (int)std::min<int64_t>(kSampleRows, m ? b_ntr : a_ntr);
+            words = std::max(words, (M[m]->cols + T * 32 - 1) / (T * 32));
+        }
+        a.small_lanes = shape.lanes;
+        a.small_products = shape.products;
+        a.d_scalars = ctx->d_scalars;
+        hipLaunchKernelGGL(k_row_sample, dim3((unsigned)(a.blocks[0] + a.blocks[1])), dim3(256), (size_t)words * 4, s, a);
+    }
     {
         KernelTimer kt(ctx, TSP_KERNEL_CONVERT, s);
-        prepare(ctx, A, ma, &left, s);
-        if (!alias) prepare(ctx, B, mb, nullptr, s);
+        prepare(ctx, A, ma, &left, s, skip);
+        if (!alias) prepare(ctx, B, mb, nullptr, s, skip);
     }
     phase_end(ctx, TSP_PHASE_CONVERT, s);
     TSP_HIP_CHECK(ctx, hipGetLastError());
@@ -1412,6 +1542,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     sums.products = left.products;
     sums.same = alias;
     sums.partial = partial;
+    sums.skip = skip;
     const int sum_blocks = (int)std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, alias ? 0 : b_ntr) + 15) / 16);
     // row_ptr of C when the sizes of its rows are there, and the sizes of everything to the host
     int64_t *row_ptr = nullptr;
@@ -1425,6 +1556,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         a.clear = row_ptr != nullptr;
         a.expected = expected;
         a.live = live;
+        a.skip = skip;
         if (row_ptr && A->rows <= kFinishRows) {
             a.rows = A->rows;
             a.row_nnz = row_nnz;
@@ -1478,6 +1610,13 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     if (!known) {
         int rc = finish(TSP_KERNEL_SCAN_SYM);
         if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);
+        if (!rc && skip && ctx->h_scalars[S_ROW_SKIP]) {
+            hint.ready = hint.tiles = hint.estimated = true;
+            hint.candidates = ctx->h_scalars[S_ROW_SKIP] - 1;
+            *remembered = &hint;
+            return TSP_OK;
+        }
+        sums.skip = skip = nullptr;
         if (!rc) rc = sizes_known();
         if (rc) return rc;
         if (hint.tiles || other_lanes) {     // (the tile kernels start over; the scalars they use are cleared for them)

@@ -93,7 +93,7 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
     // Tiles because an earlier product of the same sizes was for them, and this one has other pairs of tiles: the operands are
     // looked at again, and the tiles dropped if they are for rows.
     if (!rc && remembered && std::abs(plan->candidates - remembered->candidates) > remembered->candidates / 4) {
-        remembered->ready = false;
+        remembered->ready = remembered->sample = false;
         if (!ctx->scalars_clean) hipLaunchKernelGGL(k_clear_scalars_all, dim3(1), dim3(64), 0, s, ctx->d_scalars);
         ctx->scalars_clean = false;
         const int looked = rowwise_spgemm(ctx, A, B, alias, C, s, &by_rows, &remembered);
@@ -105,6 +105,9 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
         } else {
             ctx->scalars_clean = false;
         }
+    } else if (!rc && remembered && remembered->estimated) {
+        remembered->estimated = false;
+        remembered->candidates = plan->candidates;
     }
     if (!rc && by_tiles) rc = numeric_enqueue(ctx, ta, alias ? ta : tb, plan, C, s, /*last_of_call=*/true, &ahead);   // the plan ends here
     if (!rc && ctx->compact) {                    // Algorithm 1, the compaction steps: strictly sparse result

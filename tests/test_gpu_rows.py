@@ -260,6 +260,37 @@ def test_products_in_turn(tsp, oracle, count, options):
         h.close()
 
 
+@pytest.mark.parametrize("what,by_rows", [("blocks", False), ("stencil", False), ("random", True), ("rectangles", True), ("rectangles of tiles", False),
+                                          ("looks like tiles", True)])
+@pytest.mark.parametrize("upload", [{}, {"value_dtype": "f32", "row_ptr_dtype": "i64"}])
+def test_rows_or_tiles_at_first_sight(tsp, oracle, what, by_rows, upload):
+    """Operands large enough for a look at some of their tile-rows before the look at all of them; in the last case every
+    tile-row that is looked at (the odd ones of 256) holds four full tiles and the others are random."""
+    rng = np.random.default_rng(6)
+    n, B = 4096, None
+    if what == "blocks":
+        A = inputs.block_clustered(16384, seed=2)
+    elif what == "stencil":
+        A = inputs.stencil27_3d(13, dof=3)
+    elif what == "random":
+        A = _matrix(rng, n, n, 70)
+    elif what == "rectangles":
+        A, B = _matrix(rng, 5000, 3000, 60), _matrix(rng, 3000, 7001, 20)
+    elif what == "rectangles of tiles":
+        A = _full_tiles(rng, n)
+        B = inputs.from_coo(n, 160, np.repeat(np.arange(n), 16), (np.arange(n)[:, None] // 16 % 10 * 16 + np.arange(16)).ravel(), rng.normal(size=16 * n))
+    else:
+        T, R = _full_tiles(rng, n), _exact_lengths(rng, n, np.full(n, 64), lambda m: rng.normal(size=m))
+        odd = np.repeat(np.arange(n) // 16 % 2 == 1, 64)
+        A = inputs.from_coo(n, n, np.repeat(np.arange(n), 64), np.where(odd, T.col_idx, R.col_idx), np.where(odd, T.val, R.val))
+    assert A.nnz >= 1 << 18
+    h = tsp.Handle()
+    try:
+        _check(h, tsp, oracle, A, B, by_rows=by_rows, calls=3, **upload)
+    finally:
+        h.close()
+
+
 def test_rejects_what_is_not_canonical(tsp):
     import torch
     h = tsp.Handle()
