@@ -214,9 +214,9 @@ int tsp_trim(tsp_handle handle, void *stream);
  * STRIP_ORDER, WIDE_INDEX away from its default) keeps the tiles.  Which way suits is looked at when the sizes of the
  * operands are not those of one of the last eight products of the handle, at the price of one more wait, and again when a
  * product by tiles turns out to have another number of pairs of tiles than the one it was decided on.
- * A product that is repeated on a handle with the same options has the same bits every time (unless an operand of the
- * same rows, columns and number of entries, but another structure, came in between: the two may then share the choice
- * between rows and tiles).
+ * A product that is repeated on a handle with the same options has the same bits every time (unless one of another
+ * structure or of values of another range, but the same rows, columns and numbers of entries, came in between: the two
+ * may then share the choice between rows and tiles).
  * Errors: INVALID_ARG, SHAPE_MISMATCH, NOT_CANONICAL, ALLOC_FAILED, INDEX_OVERFLOW, HIP,
  * UNSUPPORTED (a tile-row of C spans more than 131072 tile columns between its first and its
  * last candidate tile, i.e. 2097152 columns; or a tile-row of C holds 2^32 entries or more).

@@ -1321,12 +1321,16 @@ __global__ void k_clear_rows(int64_t *d_scalars, int64_t products) {
 
 // Whether the row kernels are faster for A*B than the tile kernels: what the two take beyond the 30 us that both do, from
 // times of 90 products of meshes, stencils, blocks, random and power-law graphs (in ns).  Rows: 13 per heavy row, 1 per
-// thousand products, and 1 per thousand products of the small rows and lane of such a row.  Tiles: 19 us (more launches) and
-// 0.15 per candidate pair of tiles, which is what they cost at least.  So a stencil or dense blocks go by tiles from 1500
-// rows on (27 points on a 24^3 grid: 69 us, by rows 157), a mesh, graph or random matrix by rows (a 300^2 mesh: 42 us, by
-// tiles 68; 4000 rows of 73 entries at random: 105, 742).  Of the 90 the choice loses more than 6 % on three, 23 % on one.
-static bool rows_preferred(int64_t products, int64_t small_products, int lanes, int64_t heavy, int64_t candidates) {
-    return 13 * heavy + products / 1000 + lanes * (small_products / 1000) <= 19000 + candidates / 20 * 3;
+// thousand products, 8 where the heavy rows are summed in fp64 (3 on even rows, 8 to 20 on graphs), and 1 per thousand
+// products of the small rows and lane of such a row.  Tiles: 19 us (more launches) and 0.15 per candidate pair of tiles, which
+// is what they cost at least.  So a stencil or dense blocks go by tiles from 1500 rows on (27 points on a 24^3 grid: 69 us, by
+// rows 157), a mesh, graph or random matrix by rows (a 300^2 mesh: 42 us, by tiles 68; 4000 rows of 73 entries at random: 105,
+// 742).  Of the 90 the choice loses more than 6 % on three, 23 % on one.  Values of a normal distribution, which integers do not
+// hold: 3000 rows, a fifth full, by rows 2469 us, by tiles 865; R-MAT scale 13 with 110 entries per row 5060, 3560; scale 18
+// with 30 per row 98 ms, 207.
+static bool rows_preferred(int64_t products, int64_t small_products, int lanes, int64_t heavy, bool integers, int64_t candidates) {
+    return 13 * heavy + products / 1000 + (integers ? 0 : 7 * ((products - small_products) / 1000)) + lanes * (small_products / 1000) <=
+           19000 + candidates / 20 * 3;
 }
 
 // The same from some of the tile-rows, a block each: what their rows cost by rows, and their tiles.  The pairs of tiles are
@@ -1596,13 +1600,14 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         other_lanes = shape.slots <= 128 && shape.lanes != (hint.wide ? 16 : lanes_unless_wide);
         const int64_t heavy = shape.lanes == 8 && hint.wide ? n_heavy - std::min(n_heavy, h[S_ROW_WIDE]) : n_heavy;
         const int64_t small = std::min(h[S_ROW_PRODUCTS], (A->rows - heavy) * shape.products);      // (at most)
-        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : shape.lanes, heavy, h[S_CANDIDATES]) || (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
+        kind = fill_kind(h);
+        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : shape.lanes, heavy, kind.sum != FillKind::kDouble, h[S_CANDIDATES]) ||
+                      (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
         hint.candidates = h[S_CANDIDATES];
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
         hint.small = h[S_ROW_SMALL] > 0;
         hint.nnz = row_ptr ? h[S_C_NNZ] : -1;
-        kind = fill_kind(h);
         hint.sum = kind.sum;
         hint.scale = kind.scale;
         return (int)TSP_OK;

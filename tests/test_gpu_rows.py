@@ -260,6 +260,63 @@ def test_products_in_turn(tsp, oracle, count, options):
         h.close()
 
 
+_VALUES = {
+    "ones": lambda rng, m: rng.choice([-1.0, 1.0], m),                                # 32-bit sums
+    "below one": lambda rng, m: rng.uniform(-1, 1, m),                                # 64-bit sums
+    "normal": lambda rng, m: rng.normal(size=m),                                      # beyond them: fp64
+    "up to 100": lambda rng, m: rng.uniform(-100, 100, m),
+    "largest and smallest": lambda rng, m: rng.choice([65504.0, -65504.0, 2.0 ** -24, -2.0 ** -24, 1.0], m),
+    "zeros": lambda rng, m: np.where(rng.random(m) < 0.5, 0.0, -0.0),
+    "some zeros": lambda rng, m: np.where(rng.random(m) < 0.5, 0.0, rng.normal(size=m)),
+    "infinities": lambda rng, m: np.where(rng.random(m) < 0.01, np.inf, rng.normal(size=m)),
+    "both infinities": lambda rng, m: np.where(rng.random(m) < 0.02, rng.choice([-np.inf, np.inf], m), rng.normal(size=m)),
+    "NaN": lambda rng, m: np.where(rng.random(m) < 0.01, np.nan, rng.uniform(-1, 1, m)),
+}
+
+
+@pytest.mark.parametrize("values", sorted(_VALUES))
+@pytest.mark.parametrize("left,right,cols", [(60, 40, 900), (300, 25, 20001)])
+def test_values_of_heavy_rows(tsp, oracle, values, left, right, cols):
+    """Every accumulator of the heavy rows, in a first call and launched ahead: sums against the oracle's within 1e-5 of the
+    sum of the products' magnitudes, infinities and NaN where the oracle has them."""
+    rng = np.random.default_rng(17)
+    make = lambda m: _VALUES[values](rng, m)
+    A = _exact_lengths(rng, 700, np.full(400, left), make)
+    B = _exact_lengths(rng, cols, np.full(700, right), make)
+    want = oracle.spgemm(A, B, threads=4)
+    h = tsp.Handle()
+    try:
+        dA, dB = tsp.to_device(A), tsp.to_device(B)
+        print(f"heavy rows: {values}, {left} x {right}", flush=True)
+        first = None
+        for _ in range(3):
+            by_rows, got = _bits(h, tsp, dA, dB)
+            assert by_rows
+            assert np.array_equal(got[0], want.row_ptr) and np.array_equal(got[1], want.col)
+            val, finite = got[2].view(np.float32).astype(np.float64), np.isfinite(want.val)
+            assert np.array_equal(val[~finite], want.val[~finite], equal_nan=True)
+            assert np.all(np.abs(val[finite] - want.val[finite]) <= 1e-5 * want.mag[finite] + 1e-7)
+            for x, y in zip(got, first or got):
+                assert np.array_equal(x, y)
+            first = got
+    finally:
+        h.close()
+
+
+def test_values_that_integers_do_not_hold_by_tiles(tsp, oracle):
+    """A product that is faster by rows while its sums are integers and by tiles otherwise."""
+    rng = np.random.default_rng(4)
+    n = 1000
+    lengths = np.full(n, 200)
+    h = tsp.Handle()
+    try:
+        for values, by_rows in (("below one", True), ("normal", False), ("normal", False)):
+            A = _exact_lengths(rng, n, lengths, lambda m: _VALUES[values](rng, m))
+            _check(h, tsp, oracle, A, by_rows=by_rows, calls=2)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("what,by_rows", [("blocks", False), ("stencil", False), ("random", True), ("rectangles", True), ("rectangles of tiles", False),
                                           ("looks like tiles", True)])
 @pytest.mark.parametrize("upload", [{}, {"value_dtype": "f32", "row_ptr_dtype": "i64"}])
