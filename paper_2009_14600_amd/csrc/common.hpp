@@ -50,6 +50,7 @@ enum Scalar {
     S_LARGE_A = 24,          // tile-rows of an operand whose entries do not fit the registers of k_convert_block
     S_LARGE_B = 25,
     S_DESCENDS = 27,         // != 0: the row pointers of a matrix to be compacted go down somewhere
+    S_EMPTY_RUNS = 28,       // != 0: more of its rows may begin in 4096 entries than one block finds (a slot of k_row_sample's)
     S_PUBLISHED = 31,        // host mirror only: a slot without a value (publish_scalars tags every slot)
 };
 

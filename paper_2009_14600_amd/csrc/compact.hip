@@ -88,8 +88,8 @@ __device__ __forceinline__ void load_part(const X *from, int64_t begin, int64_t 
     }
 }
 
-// Survivors per chunk, and where the entries begin (before[chunks + 1]); the blocks of the rows look whether the row pointers
-// ascend.
+// Survivors per chunk, and where the entries begin and end (before[chunks + 1], before[chunks + 2]); the blocks of the rows look
+// whether the row pointers ascend, and whether more than kCompactRows rows may begin in one part.
 template <typename RP>
 __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<RP> a, uint32_t *__restrict__ count,
                                                                    int64_t *__restrict__ before, int64_t *d_scalars) {
@@ -103,11 +103,20 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<R
             down |= clamped(a, min(r, a.last)) > clamped(a, min(r + 1, a.last));
         }
         if (down) d_scalars[S_DESCENDS] = 1;
+        // (such rows have the first row of some block among them, and 3072 behind it)
+        if (threadIdx.x == 0) {
+            const int64_t r = (int64_t)blockIdx.x * kCheckRows, last = min(r + kCompactRows - kCheckRows, a.last);
+            auto part = [&](int64_t row) { return min(clamped(a, row), max(a.nnz - 1, (int64_t)0)) / kCompactPart; };
+            if (r < a.last && part(r) == part(last)) d_scalars[S_EMPTY_RUNS] = 1;
+        }
         return;
     }
     const int64_t c0 = (int64_t)b * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
     const EntryRange range = entry_range(a);
-    if (b == 0 && threadIdx.x == 0) before[a.chunks + 1] = range.lo;
+    if (b == 0 && threadIdx.x == 0) {
+        before[a.chunks + 1] = range.lo;
+        before[a.chunks + 2] = range.hi;
+    }
     uint32_t n = 0;
     for (int64_t begin = c0; begin < c1; begin += kCompactPart) {
         float v[16];
@@ -123,7 +132,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<R
 }
 
 // Survivors before every chunk, by one block, 4096 chunks at a time; the total to the host.  (At most 65,536 numbers.)
-// before[chunks]: whether the row pointers go down somewhere.  The scalar block is left as it was.
+// before[chunks]: 1 where the row pointers go down, 2 where there are long runs of empty rows.  The scalar block is left as it was.
 __global__ __launch_bounds__(1024) void k_compact_scan(const uint32_t *__restrict__ count, int chunks, int64_t *__restrict__ before,
                                                       int64_t *d_scalars, int64_t *h_scalars_dev, int64_t publish_tag) {
     __shared__ uint64_t lds[1024 / 64];
@@ -145,9 +154,10 @@ __global__ __launch_bounds__(1024) void k_compact_scan(const uint32_t *__restric
         carry += total;
     }
     if (threadIdx.x == 0) own[S_C_NNZ] = (int64_t)carry;
-    if (threadIdx.x == S_DESCENDS) before[chunks] = standing;
+    const int64_t runs = __shfl(standing, S_EMPTY_RUNS, 64);
+    if (threadIdx.x == S_DESCENDS) before[chunks] = standing | runs << 1;
     publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing, own, own_slot(S_C_NNZ));
-    if (threadIdx.x == S_C_NNZ || threadIdx.x == S_DESCENDS) d_scalars[threadIdx.x] = 0;
+    if (threadIdx.x == S_C_NNZ || threadIdx.x == S_DESCENDS || threadIdx.x == S_EMPTY_RUNS) d_scalars[threadIdx.x] = 0;
 }
 
 // First row whose entries begin at `begin` or later (rows: none), by the 64 lanes of a wave.
@@ -194,12 +204,14 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
                                                                  int32_t *__restrict__ out_col,
                                                                  float *__restrict__ out_val) {
     __shared__ unsigned long long s_mask[kCompactPart / 64];
-    const int64_t descends = uniform_load(before + a.chunks);
-    const EntryRange range = entry_range(a);
-    if (descends) return;                                        // (the host makes the pass again, see compact_descending)
+    // (where the row pointers go down nothing is written, and the host makes the pass again, see compact_descending)
+    const int64_t found = uniform_load(before + a.chunks);
+    const EntryRange range{uniform_load(before + a.chunks + 1), uniform_load(before + a.chunks + 2)};
+    const bool descends = found & 1;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int b = (int)blockIdx.x - a.row_blocks(kCompactRows);
     if (b < 0) {
+        if (!(found & 2)) return;
         // 4096 rows: those that begin in the part in which the first of them does, and behind the first 4096 that do
         const int64_t r0 = (int64_t)blockIdx.x * kCompactRows, at0 = clamped(a, r0);
         // (the end of the arrays belongs to the last chunk's last part)
@@ -209,7 +221,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
         const int64_t end = min(begin + kCompactPart, c1);
         const bool rest = chunk == a.chunks - 1 && part == parts - 1;
         const int64_t from = (begin == 0 ? 0 : first_row_from(a.row_ptr, a.rows, begin)) + kCompactRows;
-        if (from >= r0 + kCompactRows) return;
+        if (from >= r0 + kCompactRows || descends) return;
         int64_t base = before[chunk];
         float v[16];
         unsigned long long word;
@@ -248,6 +260,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
         unsigned long long word;
         uint32_t all;
         const uint32_t prefix = part_words(v, s_mask, &word, &all);
+        if (descends) return;
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int w = u * (kCompactThreads / 64) + wave;
@@ -347,7 +360,7 @@ template <typename RP>
 static int compact_run(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStream_t s, bool *taken) {
     const CompactArgs<RP> a = compact_args<RP>(C);
     uint32_t *count = ctx_alloc_n<uint32_t>(ctx, (size_t)a.chunks, s);
-    int64_t *before = ctx_alloc_n<int64_t>(ctx, (size_t)a.chunks + 2, s);
+    int64_t *before = ctx_alloc_n<int64_t>(ctx, (size_t)a.chunks + 3, s);
     int64_t *new_row_ptr = nullptr;
     int32_t *col = nullptr;
     float *val = nullptr;

@@ -72,7 +72,7 @@ def test_a_slice_of_rows(tsp, i64, first, slack):
     _check(tsp, "slice without entries", np.full(9, first), first + slack + 1, i64)
 
 
-@pytest.mark.parametrize("empty", [ROWS - 1, ROWS, ROWS + 1, 3 * ROWS + 5, 100001])
+@pytest.mark.parametrize("empty", [900, 3000, ROWS - 1, ROWS, ROWS + 1, 3 * ROWS + 5, 100001])
 @pytest.mark.parametrize("entries", [0, 1, PART, 2 * PART + 9])
 def test_runs_of_empty_rows(tsp, empty, entries):
     full = np.full(entries, 1)
@@ -80,6 +80,7 @@ def test_runs_of_empty_rows(tsp, empty, entries):
     for what, lengths in (("behind", [full, none]), ("in front", [none, full]), ("between", [full[:entries // 2], none, full[entries // 2:], none, full])):
         p = _pointers(np.concatenate(lengths).astype(np.int64), 3)
         _check(tsp, f"empty rows {what}", p, int(p[-1]) + 2, seed=entries)
+        _check(tsp, f"empty rows {what}, whole parts", p - 3, int(p[-1]) - 3, seed=entries)
 
 
 @pytest.mark.parametrize("i64", [False, True])
