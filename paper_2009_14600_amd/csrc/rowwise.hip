@@ -14,7 +14,7 @@
 // A product that is repeated on a handle has the same bits every time.  Products of fp16 numbers are exact in fp32.  An entry of a small row is summed in fp32 in
 // the order of the entries of A.  A heavy entry is summed in integers where every partial sum is exact in them (all products
 // are multiples of a power of two that the operands' values say; then the order of the additions does not matter and a
-// whole block shares the accumulator), and otherwise in fp64 by one wave in the order of the entries of A.
+// whole block shares the accumulator), and otherwise in fp64 by one wave, entry after entry of A or four at a time.
 #include "common.hpp"
 
 #include <algorithm>
@@ -29,11 +29,15 @@ constexpr int kChunkTileRows = 128, kChunkRows = kChunkTileRows * T;   // rows w
 constexpr int kPlanSums = 8;
 constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
 constexpr int kSpanWindows = 64;         // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
-constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows
+constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows, those of very long rows of A at any
 constexpr int kCountThreads = 256;       // of k_heavy_count
 constexpr int32_t kNoCol = 0x7FFFFFFF;
 constexpr int64_t kFoundEntries = (int64_t)2 << 30;   // of the small rows before they are moved into C, at most
-constexpr int kTaskProducts = 65536;     // intermediate products behind one task of k_heavy_fill (a row, or some of its windows)
+// Intermediate products behind one task of k_heavy_fill (a row, or some of its windows), and entries of the row of A times
+// windows: every step of a task goes through all entries, however few of them have anything in its windows.  (A row of 45,000
+// entries among 100,000 of two, values in (-1, 1): 29 ms in one task of 25 windows, 3.4 in one each; by tiles 5.3.)
+constexpr int kTaskProducts = 65536;
+constexpr int kTaskEntries = 32768;
 
 // Of a tile-row: the entries of its longest heavy row (23 bits hold the columns that k_row_prepare allows), its small rows,
 // and the rows of 9 to 16 entries with no more products than a small row has; of either at most 16.
@@ -249,7 +253,8 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
         ub = min(s_ub[team][tid], (unsigned long long)INT32_MAX);
         deg = s_ptr[team][tid + 1] - s_ptr[team][tid];
         a.ub[row] = (int32_t)ub;
-        if (deg > 0 && ub > 0 && !small_row(deg, (int32_t)ub, a.small_lanes, a.small_products)) tasks = min(max((int)ub / kTaskProducts, 1), groups);
+        if (deg > 0 && ub > 0 && !small_row(deg, (int32_t)ub, a.small_lanes, a.small_products))
+            tasks = max(min(max((int)ub / kTaskProducts, 1), groups), (int)min((int64_t)deg * a.windows / kTaskEntries, (int64_t)a.windows));
     }
     unsigned long long all = tid < T ? s_ub[team][tid] : 0ull;
     for (int d = 1; d < T; d <<= 1) all += __shfl_xor(all, d, T);
@@ -266,11 +271,12 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
         const int64_t t0 = (int64_t)(at & ((1ull << 36) - 1ull)) + inc - tasks;
         if (tasks > 0 && h < a.heavy_cap) {
             a.heavy[h] = (int32_t)row;
-            // (groups of windows, as even as they go)
+            // (groups of windows, as even as they go; single ones where there are more tasks than groups)
+            const int unit = tasks > groups ? 1 : kGroupWindows, units = tasks > groups ? a.windows : groups;
             for (int t = 0; t < tasks; ++t)
                 if (t0 + t < a.task_cap)
-                    a.tasks[t0 + t] = make_int4((int)row, (int)h, (int)((int64_t)groups * t / tasks) * kGroupWindows,
-                                                min((int)((int64_t)groups * (t + 1) / tasks) * kGroupWindows, a.windows));
+                    a.tasks[t0 + t] = make_int4((int)row, (int)h, (int)((int64_t)units * t / tasks) * unit,
+                                                min((int)((int64_t)units * (t + 1) / tasks) * unit, a.windows));
         }
     }
     const int longest = heavies ? wave_max(tasks > 0 ? deg : 0) : 0, small = __popcll(__ballot(deg > 0 && ub > 0 && tasks == 0));
@@ -1059,8 +1065,8 @@ struct FillArgs {
 //
 // The accumulator: LDS adds an fp32 number one lane after the other (193 cycles for a wave's 64 lanes, measured), an
 // integer or an fp64 number all lanes at a time (5, 8 and 8 to 16 cycles for 32-bit and 64-bit integers and fp64).  So
-// the sums are integers where they are exact in them, and fp64 otherwise; fp64 only with a block of one wave, which
-// fixes the order of the additions.  64-bit integers: p * 2^k + 1.5 * 2^52 in fp64 holds the integer p * 2^k in its low
+// the sums are integers where they are exact in them, and fp64 otherwise; fp64 only with a block of one wave, whose
+// steps follow one another (lanes of a step that meet at an entry are added by the LDS one after the other).  64-bit integers: p * 2^k + 1.5 * 2^52 in fp64 holds the integer p * 2^k in its low
 // bits (|p * 2^k| < 2^51).
 constexpr int kSpanColumns = 1 << 16;    // the elements of B hold 16 bits of the column
 // The table of a C of at most so many columns is a quarter as long, which is what many light rows spend their time on:
@@ -1068,7 +1074,7 @@ constexpr int kSpanColumns = 1 << 16;    // the elements of B hold 16 bits of th
 // 3.05 ms with a table of 32768 columns, 3.67 with one of 16384; scales 13 and 14 the same with either).
 constexpr int kNarrowColumns = 1 << 14;
 
-template <typename Acc, int kCap, int kThreads, int kSpan>
+template <typename Acc, int kCap, int kThreads, int kSpan, int kPiece = 16>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThreads == 64 ? 1 : 8, 8))) void k_heavy_fill(const FillArgs a) {
     constexpr int kWaves = kThreads / 64, kWords = kSpan / 32;
     __shared__ __align__(16) Acc acc[kCap + 64];               // (behind the entries a place per lane for lanes without an element)
@@ -1151,7 +1157,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
                     len = min(from[one ? 1 : w_next - w], a.b_nnz) - p;
                     own = __builtin_bit_cast(uint16_t, (_Float16)__uint_as_float((uint32_t)x.y));
                 }
-                stream_pieces<kThreads == 64 ? 64 : 16, uint32_t>(
+                stream_pieces<kPiece, uint32_t>(
                     p, len, own, a.pack, &s_piece[wave], [&](uint32_t x, bool active, uint32_t a16) {
                         const uint32_t c = (x - c0) & (uint32_t)(kSpan - 1);
                         const int2 place = places[c >> 5];
@@ -1295,7 +1301,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
     else f16 ? run(int64_t{}, uint16_t{}) : run(int64_t{}, float{});
 }
 
-void launch_fill(FillArgs &f, FillKind kind, hipStream_t s) {
+void launch_fill(FillArgs &f, FillKind kind, bool short_rows, hipStream_t s) {
     auto launch = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)f.n_tasks), dim3(threads), 0, s, f);
     };
@@ -1306,7 +1312,8 @@ void launch_fill(FillArgs &f, FillKind kind, hipStream_t s) {
         launch(narrow ? k_heavy_fill<int32_t, 4096, 512, kNarrowColumns> : k_heavy_fill<int32_t, 4096, 512, kSpanColumns>, 512);
     else if (kind.sum == FillKind::kInt64)
         launch(narrow ? k_heavy_fill<long long, 4096, 512, kNarrowColumns> : k_heavy_fill<long long, 4096, 512, kSpanColumns>, 512);
-    else launch(k_heavy_fill<double, 4096, 64, kSpanColumns>, 64);
+    // (rows of B shorter than a wave: four at a time.  20,000 rows of 3 entries, five of 6600, normal values: 2338 -> 1285 us)
+    else launch(short_rows ? k_heavy_fill<double, 4096, 64, kSpanColumns, 16> : k_heavy_fill<double, 4096, 64, kSpanColumns, 64>, 64);
 }
 
 }  // namespace
@@ -1766,7 +1773,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
                     c.bits = bits;
                     count_heavy(f.heavy_to - f.heavy_from);
                 }
-                launch_fill(f, how, s);
+                launch_fill(f, how, B->nnz <= 16 * B->rows, s);
             }
         }
         phase_end(ctx, TSP_PHASE_NUMERIC, s);

@@ -303,6 +303,25 @@ def test_values_of_heavy_rows(tsp, oracle, values, left, right, cols):
         h.close()
 
 
+@pytest.mark.parametrize("values", ["below one", "normal"])
+@pytest.mark.parametrize("per_row", [2, 17])
+@pytest.mark.parametrize("entries", [1820, 1821, 3641, 9000, 21000])
+def test_tasks_of_very_long_rows(tsp, oracle, values, per_row, entries):
+    """Rows of A so long that their windows of columns (18) are dealt to one task, to two, to groups and one by one, among
+    rows of three entries; short and longer rows of B, which the fp64 sums take four at a time and one at a time."""
+    rng = np.random.default_rng(entries + per_row)
+    make = lambda m: _VALUES[values](rng, m)
+    lengths = np.full(300, 3)
+    lengths[[0, 131, 299]] = entries
+    A = _exact_lengths(rng, 25000, lengths, make)
+    B = _exact_lengths(rng, 70001, np.full(25000, per_row), make)
+    h = tsp.Handle()
+    try:
+        _check(h, tsp, oracle, A, B)
+    finally:
+        h.close()
+
+
 def test_values_that_integers_do_not_hold_by_tiles(tsp, oracle):
     """A product that is faster by rows while its sums are integers and by tiles otherwise."""
     rng = np.random.default_rng(4)
