@@ -29,12 +29,13 @@ class _FailingHandle:
         import torch
         self.calls = 0
         self.refused = 0
+        self.fail_from = fail_from
         self.blocks = {}
 
         def alloc(_user, nbytes, _stream):
             k = self.calls
             self.calls += 1
-            if k >= fail_from or nbytes > most_bytes:
+            if k >= self.fail_from or nbytes > most_bytes:
                 self.refused += 1
                 return None
             t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
@@ -54,17 +55,23 @@ class _FailingHandle:
         self.lib.tsp_destroy(self.h)
 
 
-@pytest.mark.parametrize("maker,tile_edge", [
-    (lambda: inputs.config(2, small=True), 0),   # list kernel, whole-tile-row multiplication kernel
-    (lambda: inputs.config(4, small=True), 0),   # general task-list kernel, separate counting kernel
-    (lambda: inputs.config(1, small=True), 8),   # the paper's pipeline (tsp_spgemm_paper) at two tile edges
-    (lambda: inputs.config(5, small=True), 32),
+# (WORK_ORDER keeps the tile kernels, whatever the operands)
+@pytest.mark.parametrize("maker,tile_edge,work_order,by_rows", [
+    (lambda: inputs.config(2, small=True), 0, 0, True),     # rows: small ones, the multiplication launched ahead on a warm handle
+    (lambda: inputs.config(4, small=True), 0, 0, True),     # rows: heavy ones too
+    (lambda: inputs.config(2, small=True), 0, 2, False),    # list kernel, whole-tile-row multiplication kernel
+    (lambda: inputs.config(4, small=True), 0, 1, False),    # general task-list kernel, separate counting kernel, order kept
+    (lambda: inputs.config(5, small=True), 0, 0, False),    # list kernel with a block per tile-row, full tiles
+    (lambda: inputs.config(1, small=True), 8, 0, False),    # the paper's pipeline (tsp_spgemm_paper) at two tile edges
+    (lambda: inputs.config(5, small=True), 32, 0, False),
 ])
-def test_allocator_returning_null_at_every_call_site(tsp, maker, tile_edge):
+@pytest.mark.parametrize("warm", [False, True])
+def test_allocator_returning_null_at_every_call_site(tsp, maker, tile_edge, work_order, by_rows, warm):
     """tsp_spgemm (tile_edge 0) or tsp_spgemm_paper with an allocator that runs dry after k calls, for every k
     up to the number of calls a successful product makes: status -4 (TSP_ERR_ALLOC_FAILED), *C zeroed, nothing
     leaked (after tsp_trim the handle holds no byte and the allocator has every block back), and the handle
-    works again once memory is there."""
+    works again once memory is there.  On a new handle, and on one that has multiplied these operands twice and given its
+    cached memory back: it sizes arrays and launches kernels by what it remembers."""
     import torch
     A = maker()
     dA = tsp.to_device(A)
@@ -75,37 +82,52 @@ def test_allocator_returning_null_at_every_call_site(tsp, maker, tile_edge):
             return handle.lib.tsp_spgemm_paper(handle.h, tile_edge, ctypes.byref(sA), ctypes.byref(sA), ctypes.byref(out), None)
         return handle.lib.tsp_spgemm(handle.h, ctypes.byref(sA), ctypes.byref(sA), ctypes.byref(out), None)
 
-    ok = _FailingHandle(tsp, fail_from=1 << 30)
-    out = tsp._Csr()
-    assert multiply(ok, out) == 0
-    torch.cuda.synchronize()
-    want_nnz, calls = out.nnz, ok.calls
-    # what a handle keeps for its whole life (the slots of its chained prefix sums), to tell it from a leak
-    assert ok.lib.tsp_csr_free(ok.h, ctypes.byref(out), None) == 0 and ok.lib.tsp_trim(ok.h, None) == 0
-    st = tsp._Stats()
-    assert ok.lib.tsp_get_stats(ok.h, ctypes.byref(st)) == 0
+    def trimmed(handle):
+        assert handle.lib.tsp_trim(handle.h, None) == 0
+        st = tsp._Stats()
+        assert handle.lib.tsp_get_stats(handle.h, ctypes.byref(st)) == 0
+        return st
+
+    def good(handle):
+        out = tsp._Csr()
+        assert multiply(handle, out) == 0
+        torch.cuda.synchronize()
+        nnz = out.nnz
+        assert handle.lib.tsp_csr_free(handle.h, ctypes.byref(out), None) == 0
+        return nnz
+
+    def new_handle():
+        h = _FailingHandle(tsp, fail_from=1 << 30)
+        assert h.lib.tsp_set_option(h.h, tsp.OPT_WORK_ORDER, work_order) == 0
+        if warm:
+            good(h), good(h), trimmed(h)
+        h.calls = 0
+        return h
+
+    ok = new_handle()
+    want_nnz, calls = good(ok), ok.calls
+    # what a handle keeps for its whole life (the slots of its chained prefix sums, an order of the tile-rows), to tell it
+    # from a leak
+    st = trimmed(ok)
     kept_bytes, kept_blocks = st.workspace_bytes, len(ok.blocks)
-    assert kept_blocks <= 1
+    assert kept_blocks <= 1 + (work_order == 1)
+    if not tile_edge:
+        assert (st.pairs == 0) == by_rows
     ok.close()
     assert calls >= 10
     for k in range(calls):
-        h = _FailingHandle(tsp, fail_from=k)
+        h = new_handle()
+        h.fail_from = k
         out = tsp._Csr(7, 7, 7, 1, 1, 1, 1, 1)
         status = multiply(h, out)
         torch.cuda.synchronize()
         assert status == -4, (k, status)
         assert (out.rows, out.cols, out.nnz, out.row_ptr, out.col_idx, out.val) == (0, 0, 0, None, None, None), k
-        assert h.lib.tsp_trim(h.h, None) == 0
-        st = tsp._Stats()
-        assert h.lib.tsp_get_stats(h.h, ctypes.byref(st)) == 0
-        assert st.workspace_bytes in (0, kept_bytes) and len(h.blocks) <= kept_blocks, (k, st.workspace_bytes, len(h.blocks))
+        st = trimmed(h)
+        assert st.workspace_bytes <= kept_bytes and len(h.blocks) <= kept_blocks, (k, st.workspace_bytes, len(h.blocks))
         # memory comes back: the same handle multiplies
-        h.calls = -(1 << 30)
-        out = tsp._Csr()
-        assert multiply(h, out) == 0
-        torch.cuda.synchronize()
-        assert out.nnz == want_nnz
-        assert h.lib.tsp_csr_free(h.h, ctypes.byref(out), None) == 0
+        h.fail_from = 1 << 30
+        assert good(h) == want_nnz
         h.close()
 
 

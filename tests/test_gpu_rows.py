@@ -66,7 +66,7 @@ def test_bounds_of_small_rows(tsp, oracle, a_row, b_row):
 
 @pytest.mark.parametrize("cols", [1, 33, 2047, 2048, 2049, 4096, 4097, 8192, 8193, 16385, 70001, 393216, 393217, 900001])
 def test_windows_of_columns(tsp, oracle, cols):
-    """Narrow results in one window of 2048, 4096 or 8192 columns, wide ones in many, and beyond the columns whose bits
+    """Narrow results in one window of 2048 or of 4096 columns, wide ones in many, and beyond the columns whose bits
     one block of the sizing pass holds; light, heavy and very heavy rows (several tasks) side by side."""
     rng = np.random.default_rng(cols)
     h = tsp.Handle()
