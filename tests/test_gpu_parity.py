@@ -22,9 +22,13 @@ def tsp():
     return binding
 
 
-@pytest.fixture(scope="module")
-def handle(tsp):
+# Every test that takes a handle runs twice: with the choice between rows and tiles left to the library, and with tiles
+# (an option of theirs away from its default), which the tests that name tile kernels mean.
+@pytest.fixture(scope="module", params=["chosen", "tiles"])
+def handle(tsp, request):
     h = tsp.Handle(validate=True)
+    if request.param == "tiles":
+        h.set_option(tsp.OPT_WORK_ORDER, 2)
     yield h
     h.close()
 
@@ -642,12 +646,13 @@ def test_tile_rows_taken_in_order_of_work(tsp, oracle):
         by_index.close()
 
 
-def test_tile_rows_with_very_many_candidates_take_larger_blocks(tsp, oracle):
+@pytest.mark.parametrize("options", [{}, {"OPT_WORK_ORDER": 1}])          # (the second: tiles)
+def test_tile_rows_with_very_many_candidates_take_larger_blocks(tsp, oracle, options):
     """Nearly every tile-row of A meets every tile-row of B in full: about 127 x 127 candidate pairs per
     tile-row, above the 8192 from which the general task-list kernel runs in blocks of 512 threads; so does the counting
     kernel on the second call of the same product, when it keeps the bitmaps and the pairs per tile
     column for the task-list kernel.  Both calls against the oracle."""
-    h = tsp.Handle(validate=True)
+    h = _variant_handle(tsp, **options)
     try:
         A = inputs.random_sparse(2048, 2048, 0.02, 4711, values="smallint")
         print(f"very many candidates: 2048^2, nnz {A.nnz}", flush=True)
@@ -657,6 +662,7 @@ def test_tile_rows_with_very_many_candidates_take_larger_blocks(tsp, oracle):
             C = h.spgemm(dA, dA)
             st = h.stats()
             assert st["candidate_pairs"] >= 8192 * 128, st["candidate_pairs"]
+            assert (st["pairs"] > 0) == bool(options)
             assert_matches_oracle(C, ref, f"dense tile grid, call {call}")
             C.free()
     finally:
@@ -729,6 +735,7 @@ def _mesh_cases():
 
 @pytest.mark.parametrize("options", [
     {},                                             # automatic choice
+    {"OPT_WORK_ORDER": 2},                          # ... among the tile kernels
     {"OPT_WIDE_INDEX": 1},                          # 64-bit addressing, as for arrays of 4 GiB and more
     {"OPT_NUMERIC_RUN": 4},                         # four tiles per wave whatever the shape of the tile-rows
     {"OPT_NUMERIC_RUN": 8},
@@ -772,7 +779,8 @@ def test_seeded_sweep_of_small_products(tsp, handle, oracle):
         run_and_check(tsp, handle, oracle, A, B, **upload)
 
 
-def test_seeded_sweep_with_hub_rows_wide_outputs_and_repeated_calls(tsp, oracle):
+@pytest.mark.parametrize("options", [{}, {"OPT_WORK_ORDER": 1}])          # (the second: tiles)
+def test_seeded_sweep_with_hub_rows_wide_outputs_and_repeated_calls(tsp, oracle, options):
     """Forty-eight products of four kinds (square with hub rows and a dense tile grid, which take the general
     task-list kernel; a few rows times a very wide B, whose tile-rows of C pass the symbolic window; tall and
     thin; small and ragged), each multiplied twice on one handle: the second call of a product takes what the
@@ -785,7 +793,7 @@ def test_seeded_sweep_with_hub_rows_wide_outputs_and_repeated_calls(tsp, oracle)
         v = rng.integers(1, 4, r.size).astype(np.float64) if rng.random() < 0.5 else rng.uniform(-1, 1, r.size)
         return inputs.from_coo(M, K, r, c, v, name)
 
-    h = tsp.Handle(validate=True)
+    h = _variant_handle(tsp, **options)
     try:
         for case in range(48):
             rng = np.random.default_rng(31_000 + case)
