@@ -174,7 +174,7 @@ typedef struct {
     /* The paper's selection criteria for the last product's left operand (Section 6.1): the tiled method */
     /* pays off for NNZ(A) > 300000 with more than 42 entries per row on average, and for well-filled     */
     /* tiles (5 of 64 slots of an 8x8 tile and more, i.e. 20 entries per 16x16 tile).  Reported; whether   */
-    /* tsp_spgemm multiplies by tiles or by rows follows from the products per candidate pair of tiles.    */
+    /* tsp_spgemm multiplies by tiles or by rows follows from what either would cost (see there).          */
     float a_mean_row;                /* NNZ(A) / rows                                                  */
     float a_tile_fill;               /* NNZ(A) / tiles(A): entries per 16x16 tile                      */
     int32_t in_paper_regime;         /* 1: NNZ(A) > 300000 and a_mean_row > 42                         */
@@ -208,10 +208,13 @@ int tsp_trim(tsp_handle handle, void *stream);
  * waited for: C.nnz and the pointers are final when the call returns, the
  * contents once the stream has reached that point (hipStreamSynchronize, or further work on the
  * same stream).  With TSP_OPT_PHASE_TIMERS the call waits for the end.
- * Operands whose tiles hold little (at most 64 intermediate products per candidate pair of tiles: graphs, meshes with
- * one unknown per node, random matrices) are multiplied row by row instead, with the same result up to the order of
- * the fp32 additions; an option that chooses among the tile kernels (NUMERIC_RUN, MATRIX_CORES, WORK_ORDER,
- * STRIP_ORDER, WIDE_INDEX away from its default) keeps the tiles.  Which way suits is looked at when the sizes of the
+ * Operands whose tiles hold little (graphs, meshes with one unknown per node, random matrices) are multiplied row by row
+ * instead, with the same result up to the order of the fp32 additions, where that is the faster by an estimate: on one
+ * side the rows with many products, the intermediate products and whether integers hold their sums, on the other the
+ * candidate pairs of tiles.  C of fewer than 256 rows, or operands of more than 7.8 million columns, 134 million rows or
+ * 268 million entries, go by tiles; so do products for whose row kernels the allocator has no memory.  An option that
+ * chooses among the tile kernels (NUMERIC_RUN, MATRIX_CORES, WORK_ORDER, STRIP_ORDER, WIDE_INDEX away from its default)
+ * keeps the tiles.  Which way suits is looked at when the sizes of the
  * operands are not those of one of the last eight products of the handle, at the price of one more wait, and again when a
  * product by tiles turns out to have another number of pairs of tiles than the one it was decided on.
  * A product that is repeated on a handle with the same options has the same bits every time (unless one of another

@@ -7,8 +7,9 @@
 // and at most e1-e0 groups per form, so the stretches of different tile-rows cannot meet; the slots
 // in between stay unused (the arrays are sized by nnz and never touched there).
 //
-// A group of G threads (one wave; a block, and a kernel of its own, for long tile-rows) owns one tile-row and
-// visits its entries in parallel:
+// A wave takes a tile-row of up to 512 entries or so (k_convert_rows), a block one of up to 2048 (k_convert_block), and a block
+// with more passes over the entries a longer one (k_convert_rows again where most are, k_convert_large where some are).
+// Either visits the entries in parallel:
 //   1. every entry marks its tile column in an LDS bitmap that spans the tile-row's first to last
 //      tile column; the popcount is the number of tiles and the rank of a bit is the tile's
 //      position inside the tile-row, so the tiles come out sorted by column without a sort;

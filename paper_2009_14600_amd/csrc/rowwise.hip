@@ -1450,9 +1450,9 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     }
     if (A->nnz >= (1 << 28) || B->nnz >= (1 << 28)) return TSP_OK;      // (32-bit byte offsets into 8-byte records)
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
-    // Small rows: 8 lanes where the mean row of A has no more entries, else 16, or where the last product of these sizes had
-    // more than one row in 64 that is small but for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the
-    // lanes 0.1 ns per row); for a row of B as many as its mean has
+    // Small rows: 8 lanes where the mean row of A has no more entries, else 16, or where more than one row in 64 is small but
+    // for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the lanes 0.1 ns per row; by the last product
+    // of these sizes, and where the one at hand turns out otherwise it is started again); for a row of B as many as its mean has
     // entries; a table of the row that is three quarters full at most, with a margin over the mean number of products, 256
     // slots at most
     const int lanes_unless_wide = A->nnz <= 8 * A->rows ? 8 : 16;
