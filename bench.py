@@ -18,7 +18,9 @@ to move in one launch (packed fp16 elements, a 32-byte bitmap and a 16-byte reco
 per task-list entry, 8 bytes per entry of C: `algorithmic_bytes`) divided by the kernel's average
 duration (HIP events on the launch stream, recorded by the library around every kernel), against the
 8 TB/s HBM peak.  `layout_bytes_per_launch` is the same count for the arrays this library actually
-keeps (operand groups of 16 bytes, row offsets per output tile), for comparison.
+keeps (operand groups of 16 bytes, row offsets per output tile), for comparison.  A product that the
+library multiplies by rows (`config.path`) has no tiles and no task list: entries in, entries as
+records of 8 bytes between its kernels, entries of C out (`row_bytes`).
 phase_hbm: the same for the conversion, the symbolic phase (with the counting pass), the numeric
 phase with its CSR emission, and a separately timed tsp_compact_zeros call on the result.
 cpu_baseline: the CPU oracle (row-wise Gustavson, fp64) timed on this machine's host cores.
@@ -47,58 +49,44 @@ CSRC = os.path.join(ROOT, "paper_2009_14600_amd", "csrc")
 # copy: fetched bytes = 2048 * FETCH_SIZE, written bytes = 1024 * WRITE_SIZE.  Every reading carries the
 # first 12 hex digits of the SHA-256 of the kernel's source file as it was when the reading was taken; a
 # reading whose source has changed since is not reported (traffic: null) instead of going stale silently.
-# profiles/hbm_traffic_all_kernels.txt holds the readings and the commands.
+# profiles/hbm_traffic_all_kernels.txt holds the readings and the commands.  By rows (rowwise.hip) a timed kernel is a group:
+# sym_count the sizing of the small and of the heavy rows, numeric the move into C and the multiplication of the heavy rows.
 #   (workload, kernel): (source file, sha256[:12] at the time, FETCH_SIZE, WRITE_SIZE)
 MEASURED_TRAFFIC = {
-    (1, "convert"): ("convert.hip", "67ac7a722d7c", 201.6, 782.7),
-    (1, "count_masks"): ("symbolic.hip", "65d32d837ef3", 733.6, 128.0),
-    (1, "numeric"): ("numeric.hip", "ed6fb3a14cf6", 1264.8, 499.0),
-    (1, "row_offsets"): ("symbolic.hip", "65d32d837ef3", 91.1, 262.0),
-    (1, "scan_rows"): ("symbolic.hip", "65d32d837ef3", 6.4, 8.3),
-    (1, "scan_sym"): ("symbolic.hip", "65d32d837ef3", 7.2, 1.3),
-    (1, "sym_count"): ("symbolic.hip", "65d32d837ef3", 190.2, 10.0),
-    (1, "sym_emit"): ("symbolic.hip", "65d32d837ef3", 203.6, 478.3),
-    (2, "convert"): ("convert.hip", "67ac7a722d7c", 6120.4, 43223.1),
-    (2, "numeric"): ("numeric.hip", "ed6fb3a14cf6", 30663.9, 26555.3),
-    (2, "scan_rows"): ("symbolic.hip", "65d32d837ef3", 790.2, 2048.5),
-    (2, "scan_sym"): ("symbolic.hip", "65d32d837ef3", 256.6, 214.2),
-    (2, "sym_count"): ("symbolic.hip", "65d32d837ef3", 6153.1, 1280.0),
-    (2, "sym_emit"): ("symbolic.hip", "65d32d837ef3", 11418.3, 24504.0),
-    (3, "convert"): ("convert.hip", "67ac7a722d7c", 82440.9, 294561.7),
-    (3, "numeric"): ("numeric.hip", "ed6fb3a14cf6", 340006.1, 1194490.5),
-    (3, "scan_rows"): ("symbolic.hip", "65d32d837ef3", 994.2, 2592.3),
-    (3, "scan_sym"): ("symbolic.hip", "65d32d837ef3", 312.2, 271.0),
-    (3, "sym_count"): ("symbolic.hip", "65d32d837ef3", 22562.4, 3241.0),
-    (3, "sym_emit"): ("symbolic.hip", "65d32d837ef3", 71423.4, 266006.1),
-    (4, "convert"): ("convert.hip", "67ac7a722d7c", 38660.3, 473242.6),
-    (4, "count_masks"): ("symbolic.hip", "65d32d837ef3", 119848216.4, 4612574.6),
-    (4, "numeric"): ("numeric.hip", "ed6fb3a14cf6", 269244343.1, 33419349.5),
-    (4, "row_offsets"): ("symbolic.hip", "65d32d837ef3", 4666779.8, 9241581.6),
-    (4, "scan_rows"): ("symbolic.hip", "65d32d837ef3", 790.4, 2049.1),
-    (4, "scan_sym"): ("symbolic.hip", "65d32d837ef3", 255.9, 196.9),
-    (4, "sym_count"): ("symbolic.hip", "65d32d837ef3", 15365684.4, 508990.6),
-    (4, "sym_emit"): ("symbolic.hip", "65d32d837ef3", 50858751.2, 70878252.9),
-    (5, "convert"): ("convert.hip", "67ac7a722d7c", 14192.6, 50065.9),
-    (5, "numeric"): ("numeric.hip", "ed6fb3a14cf6", 53954.3, 270245.2),
-    (5, "scan_rows"): ("symbolic.hip", "65d32d837ef3", 406.2, 1024.5),
-    (5, "scan_sym"): ("symbolic.hip", "65d32d837ef3", 153.4, 98.5),
-    (5, "sym_count"): ("symbolic.hip", "65d32d837ef3", 4864.1, 1280.0),
-    (5, "sym_emit"): ("symbolic.hip", "65d32d837ef3", 8703.7, 16309.8),
+    (1, "convert"): ("rowwise.hip", "12cf7e50cf12", 87.0, 88.6),
+    (1, "sym_count"): ("rowwise.hip", "12cf7e50cf12", 360.7, 515.6),
+    (1, "scan_rows"): ("rowwise.hip", "12cf7e50cf12", 0.0, 0.0),
+    (1, "numeric"): ("rowwise.hip", "12cf7e50cf12", 283.0, 500.2),
+    (2, "convert"): ("rowwise.hip", "12cf7e50cf12", 5383.2, 13668.3),
+    (2, "sym_count"): ("rowwise.hip", "12cf7e50cf12", 9904.8, 28152.0),
+    (2, "scan_rows"): ("rowwise.hip", "12cf7e50cf12", 752.5, 1877.9),
+    (2, "numeric"): ("rowwise.hip", "12cf7e50cf12", 17401.9, 27076.1),
+    (3, "convert"): ("convert.hip", "30d2ada6508e", 83555.5, 241199.2),
+    (3, "sym_count"): ("symbolic.hip", "dffb5d515039", 22571.3, 3241.0),
+    (3, "scan_sym"): ("symbolic.hip", "dffb5d515039", 318.0, 250.0),
+    (3, "sym_emit"): ("symbolic.hip", "dffb5d515039", 77137.2, 267166.7),
+    (3, "scan_rows"): ("symbolic.hip", "dffb5d515039", 994.3, 2592.6),
+    (3, "numeric"): ("numeric.hip", "2aade73456b3", 339886.4, 1190678.4),
+    (4, "convert"): ("rowwise.hip", "12cf7e50cf12", 30067.7, 85376.3),
+    (4, "sym_count"): ("rowwise.hip", "12cf7e50cf12", 13128123.4, 5356819.0),
+    (4, "scan_rows"): ("rowwise.hip", "12cf7e50cf12", 752.5, 1877.9),
+    (4, "numeric"): ("rowwise.hip", "12cf7e50cf12", 40557529.2, 23221014.1),
+    (5, "convert"): ("convert.hip", "30d2ada6508e", 14149.9, 36641.8),
+    (5, "sym_count"): ("symbolic.hip", "dffb5d515039", 4856.4, 1280.0),
+    (5, "scan_sym"): ("symbolic.hip", "dffb5d515039", 158.9, 98.8),
+    (5, "sym_emit"): ("symbolic.hip", "dffb5d515039", 8707.7, 16309.8),
+    (5, "scan_rows"): ("symbolic.hip", "dffb5d515039", 406.2, 1024.6),
+    (5, "numeric"): ("numeric.hip", "2aade73456b3", 53955.5, 270166.1),
 }
-
-KERNEL_SOURCE = {"convert": "convert.hip", "sym_count": "symbolic.hip", "scan_sym": "symbolic.hip",
-                 "sym_emit": "symbolic.hip", "count_masks": "symbolic.hip", "row_offsets": "symbolic.hip",
-                 "scan_rows": "symbolic.hip", "numeric": "numeric.hip"}
-
 
 def source_digest(name: str) -> str:
     with open(os.path.join(CSRC, name), "rb") as f:
         return hashlib.sha256(f.read()).hexdigest()[:12]
 
 
-def measured_traffic(workload: int, kernel: str):
+def measured_traffic(workload: int, kernel: str, by_rows: bool):
     rec = MEASURED_TRAFFIC.get((workload, kernel))
-    if rec is None or source_digest(rec[0]) != rec[1]:
+    if rec is None or (rec[0] == "rowwise.hip") != by_rows or source_digest(rec[0]) != rec[1]:
         return None
     return int(2048 * rec[2] + 1024 * rec[3])
 
@@ -135,6 +123,21 @@ def algorithmic_bytes(kernel, A, st):
         "sym_emit_fused": 16 * ta + 16 * ntr + 8 * pairs + 16 * ct + 32 * ta + 32 * ct + 4 * n,
     }
     return int(table[kernel])
+
+
+def row_bytes(kernel, A, st):
+    """The same where the product goes by rows (csrc/rowwise.hip): CSR in once, records of 8 bytes between the kernels (a
+    column and a value), the row lengths, C out once.  Rows of B are counted once, not for every entry of A that meets them,
+    and what the sizing keeps for the multiplication (small rows' entries, a bit per column of the others) is the layout's."""
+    n, nnz, cnnz = A.rows, A.nnz, st["c_nnz"]
+    table = {
+        "convert": 4 * (n + 1) + 6 * nnz + 8 * nnz + 4 * (n + 1),           # CSR in, records and row starts out
+        "scan_sym": 8 * n,
+        "sym_count": 8 * nnz + 4 * (n + 1) + 4 * n,                        # records in, entries per row out
+        "scan_rows": 4 * n + 8 * (n + 1),
+        "numeric": 8 * nnz + 4 * (n + 1) + 8 * cnnz + 8 * (n + 1),
+    }
+    return int(table.get(kernel, 0))
 
 
 def layout_bytes(kernel, A, st, groups_left, groups_right):
@@ -379,10 +382,12 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
     groups_right = int(popcount32(tv["right_group_mask"][valid].cpu().numpy().view(np.uint32)).sum())
     tiles.free()
 
-    fused_count = kavg.get("count_masks", 0.0) == 0.0       # the task-list kernel ran the counting pass as well
+    by_rows = st["pairs"] == 0 and st["c_nnz"] > 0
+    bytes_of = row_bytes if by_rows else algorithmic_bytes
+    fused_count = not by_rows and kavg.get("count_masks", 0.0) == 0.0       # the task-list kernel ran the counting pass as well
     dominant = max(kavg, key=kavg.get)
-    dom_bytes = algorithmic_bytes(dominant, A, st)
-    dom_layout = layout_bytes(dominant, A, st, groups_left, groups_right)
+    dom_bytes = bytes_of(dominant, A, st)
+    dom_layout = None if by_rows else layout_bytes(dominant, A, st, groups_left, groups_right)
     if dominant == "sym_emit" and fused_count:
         dom_bytes = algorithmic_bytes("sym_emit_fused", A, st)
         dom_layout += sum(layout_bytes(k, A, st, groups_left, groups_right) for k in ("count_masks", "row_offsets"))
@@ -390,7 +395,7 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
     achieved = dom_bytes / (dom_us * 1e-6) / 1e9 if dom_us > 0 else 0.0
     roofline = {"kernel": dominant, "bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 5),
-                "traffic": measured_traffic(index, dominant),
+                "traffic": measured_traffic(index, dominant, by_rows),
                 "algorithmic_bytes_per_launch": dom_bytes, "layout_bytes_per_launch": dom_layout,
                 "avg_launch_us": round(dom_us, 2)}
     # the numeric kernel is the one dense contraction: issued MFMA work against the matrix-core peak
@@ -400,7 +405,9 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
             "peak_tflops": MFMA_F16_PEAK_TFLOPS,
             "frac": round(mfma_flop / (num_us * 1e-6) / 1e12 / MFMA_F16_PEAK_TFLOPS, 5) if num_us else 0.0,
             "useful_fraction_of_issued": round(flop / mfma_flop, 4) if mfma_flop else 0.0}
-    if A.nnz <= 3 * st["a_tiles"] and not args.no_matrix_cores:
+    if by_rows:
+        mfma["note"] = "multiplied by rows: no block products"
+    elif A.nnz <= 3 * st["a_tiles"] and not args.no_matrix_cores:
         # (the kernel for tiles with a few entries packs the halves of pairs that meet, four to a step)
         mfma["note"] = ("counted as two of the four slots of a step per pair; on this workload the kernel fills a step "
                         "with the halves of up to four pairs that meet, so the issued work is lower")
@@ -410,17 +417,17 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
 
     # achieved HBM rate per pass (algorithmic bytes over the device time of the pass's kernels)
     sym_kernels = ("sym_count", "scan_sym", "sym_emit", "count_masks", "row_offsets", "scan_rows")
-    sym_bytes = sum(algorithmic_bytes(k, A, st) for k in sym_kernels if kavg[k] > 0.0 and not (fused_count and k == "sym_emit"))
+    sym_bytes = sum(bytes_of(k, A, st) for k in sym_kernels if kavg[k] > 0.0 and not (fused_count and k == "sym_emit"))
     if fused_count:
         sym_bytes += algorithmic_bytes("sym_emit_fused", A, st)
     phase_hbm = {
-        "convert": hbm(algorithmic_bytes("convert", A, st), kavg["convert"]),
+        "convert": hbm(bytes_of("convert", A, st), kavg["convert"]),
         "symbolic_and_count": hbm(sym_bytes, sum(kavg[k] for k in sym_kernels)),
-        "numeric_and_csr_emission": hbm(algorithmic_bytes("numeric", A, st), kavg["numeric"]),
+        "numeric_and_csr_emission": hbm(bytes_of("numeric", A, st), kavg["numeric"]),
     }
     if not args.compact_zeros:
         # the compaction of zero-valued entries (Section 4.4) as a call of its own on the result: counts the
-        # survivors per row, then copies them into a new matrix
+        # survivors per chunk of entries, then copies them into a new matrix
         raw = handle.spgemm_raw(sA, sA)
         cz = handle._lib.tsp_compact_zeros
         import ctypes
@@ -439,9 +446,9 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
             out_nnz = out.nnz
             handle._free_csr(out)
             us = ev0.elapsed_time(ev1) * 1e3                # the last repetition counts (the first sizes the workspace)
-        # counting pass: the values and row_ptr in, survivors per row out; prefix sum; copy pass: columns and values
-        # in, the survivors and the new row_ptr out
-        moved = (4 * raw.nnz + 8 * (A.rows + 1) + 4 * A.rows) + (4 * A.rows + 8 * (A.rows + 1)) + (8 * raw.nnz + 8 * out_nnz + 8 * (A.rows + 1))
+        # counting pass: the values and row_ptr in; copy pass: columns, values and row_ptr in, the survivors and the new
+        # row_ptr out
+        moved = (4 * raw.nnz + 8 * (A.rows + 1)) + (8 * raw.nnz + 8 * (A.rows + 1)) + (8 * out_nnz + 8 * (A.rows + 1))
         phase_hbm["compact_zeros"] = dict(hbm(moved, us), entries_removed=int(raw.nnz - out_nnz),
                                           note="separate call on the result, its host wait included")
         handle._free_csr(raw)
@@ -451,7 +458,7 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
         "value": round(gflops, 3), "ms_per_step": round(ms_per_step, 5), "steps": steps, "warmup": warmup,
         "config": {"workload": f"configs[{index - 1}]: {inputs.CONFIG_NAMES[index]}",
                    "rows": A.rows, "nnz_A": A.nnz, "products": products, "nnz_C": st["c_nnz"],
-                   "a_tiles": st["a_tiles"], "pairs": st["pairs"], "c_tiles": st["c_tiles"],
+                   "a_tiles": st["a_tiles"], "pairs": st["pairs"], "c_tiles": st["c_tiles"], "path": "rows" if by_rows else "tiles",
                    "validate_inputs": not args.no_validate, "matrix_cores": not args.no_matrix_cores,
                    "compact_zeros": args.compact_zeros, "first_call_ms": round(first * 1e3, 3),
                    "selection_criteria": regime},
@@ -460,7 +467,7 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
         "phase_us": {k: round(v, 2) for k, v in pavg.items()},
         "device_us_per_step_with_timers": round(total_us / tsteps, 2),
     }
-    if not args.no_paper_pipeline and st["pairs"] <= PAPER_PIPELINE_MAX_PAIRS:
+    if not args.no_paper_pipeline and (st["pairs"] or st["candidate_pairs"]) <= PAPER_PIPELINE_MAX_PAIRS:
         res["paper_pipeline"] = paper_pipeline_leg(handle, tsp, torch, dA, ms_per_step)
     if not args.no_cpu_baseline:
         leg = oracle_leg(A, handle, tsp, sA, 4e8 if headline else 2e7, 10.0 if headline else 0.0)
