@@ -576,7 +576,8 @@ struct SmallArgs {
 // are added up.  Then the rank of every column among the row's is found (each lane compares its columns with all), and
 // the wave's rows go in order into memory of their own: k_small_copy moves them into C when its row_ptr is known.  (Doing
 // all of it twice, once for the sizes, costs more than the copy.)
-// Bound by the vector instructions of every wave, many of which do not depend on what its rows hold.  Measured, this
+// Bound by the vector instructions of every wave (61 % of the time on the mesh, LDS 39 %), many of which do not depend on what
+// its rows hold.  Measured, this
 // kernel and the copy, against merging the lists in LDS once to size C and once to fill it: a 512x512 mesh 36 + 13 us (64
 // before), 65536 rows of 8 random entries 45 + 13 us (68), the light rows of R-MAT scale 14 31 + 6 us (135).
 // A whole group per row of B (kNarrow false): one row of B at a time, whose columns are distinct, so no two lanes meet at
@@ -949,7 +950,8 @@ struct CountArgs {
 // A block per heavy row ORs the words of the rows of B behind it into one bit per column in LDS; OR is free of order, so
 // the row may be spread over the block: entry i of the row of A goes to wave i mod the number of waves that get 16 and more.
 // Four waves: light rows are bound by the block's own steps (a graph's 4100 rows of 165 entries 114 -> 103 us for the whole
-// product with 8 -> 4 waves), heavy ones by the words they stream (R-MAT scale 14, 680 -> 660; scale 18, no difference).
+// product with 8 -> 4 waves), heavy ones by the words they stream (R-MAT scale 14, 680 -> 660; scale 18, no difference: 26.8 GB
+// past the L2 caches and 5.3 GB of pattern in 5.5 ms, 5.8 TB/s where a large copy reaches 5; vector ALUs busy 25 %, LDS 34 %).
 template <int kWin>
 __global__ __launch_bounds__(kCountThreads) void k_heavy_count(const CountArgs a) {
     extern __shared__ __align__(16) uint32_t bits[];
@@ -1062,6 +1064,8 @@ struct FillArgs {
 // 64 registers, so that 8 waves per SIMD hide the round trips to the elements of B, half of the time: R-MAT scale 18,
 // 4096 entries with 8 waves at 8 / 6 / 4 waves per SIMD 19.5 / 22.4 / 22.3 ms, with 4 waves 22.0, 8192 entries 24.3 ms;
 // the dense accumulator 22.3 ms.
+// Bound by the traffic past the L2 caches: there 83 GB read (30 MB of B, met again by every row and step, and 9 GB of
+// pattern) and 24 GB written in 18.9 ms, 5.6 TB/s; vector ALUs busy 51 %, LDS 36 %, a third of that in bank conflicts.
 //
 // The accumulator: LDS adds an fp32 number one lane after the other (193 cycles for a wave's 64 lanes, measured), an
 // integer or an fp64 number all lanes at a time (5, 8 and 8 to 16 cycles for 32-bit and 64-bit integers and fp64).  So
