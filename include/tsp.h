@@ -203,9 +203,9 @@ int tsp_trim(tsp_handle handle, void *stream);
  * caller, who releases them with tsp_csr_free.  Columns ascend strictly within each row.
  * On failure *C is zeroed and nothing is leaked.  The calling thread waits twice for results of
  * the device (the sizes of the task list and of C, which size the allocations: the steps Algorithm 1
- * calls AllocateMemGPU; it polls pinned memory for them for up to half a millisecond, then blocks);
- * the multiplication pass that fills col_idx and val is enqueued after the second wait and is NOT
- * waited for: C.nnz and the pointers are final when the call returns, the
+ * calls AllocateMemGPU; it polls pinned memory for them for up to half a millisecond, then blocks), or
+ * once for a product of the sizes of one of the handle's last eight, whose arrays follow what that one needed;
+ * the multiplication pass that fills col_idx and val is NOT waited for: C.nnz and the pointers are final when the call returns, the
  * contents once the stream has reached that point (hipStreamSynchronize, or further work on the
  * same stream).  With TSP_OPT_PHASE_TIMERS the call waits for the end.
  * Operands whose tiles hold little (graphs, meshes with one unknown per node, random matrices) are multiplied row by row
@@ -245,7 +245,7 @@ int tsp_csr_free(tsp_handle handle, tsp_csr *C, void *stream);
 int tsp_compact_zeros(tsp_handle handle, const tsp_csr *C, tsp_csr *out, void *stream);
 
 /*
- * tsp_compact_zeros for callers that cannot allocate device memory: code under HIP graph capture,
+ * tsp_compact_zeros for callers that cannot allocate device memory: while another stream captures a graph, in
  * tight serving loops, harnesses that forbid hipMalloc.  Same result as tsp_compact_zeros, but the call
  * allocates nothing, on the device or through the handle's allocator: the caller brings the output
  * arrays, and the pass's scratch (counts and prefix sums of chunks of entries) lives in a fixed device array
@@ -255,8 +255,8 @@ int tsp_compact_zeros(tsp_handle handle, const tsp_csr *C, tsp_csr *out, void *s
  * overlapping C's; on success rows, cols, nnz and the two type fields are filled in and the arrays hold
  * the compacted matrix (entries past nnz are not written).  Do not pass *out to tsp_csr_free.
  * Limits: 1 <= C.rows <= TSP_COMPACT_STATIC_MAX_ROWS, else TSP_ERR_UNSUPPORTED and nothing is enqueued.
- * Synchronises the stream once (the new nnz).  All calls on one GPU share the one scratch array, which
- * keeps the previous call's contents (every call overwrites what it reads): calls that overlap on the
+ * Synchronises the stream once (the new nnz), twice where row_ptr goes down somewhere.  All calls on one GPU share the one
+ * scratch array, which keeps the previous call's contents (every call overwrites what it reads): calls that overlap on the
  * same GPU, from any handle or stream, race.
  * Errors: INVALID_ARG, UNSUPPORTED, HIP.
  */
