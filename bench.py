@@ -23,7 +23,7 @@ library multiplies by rows (`config.path`) has no tiles and no task list: entrie
 records of 8 bytes between its kernels, entries of C out (`row_bytes`).
 phase_hbm: the same for the conversion, the symbolic phase (with the counting pass), the numeric
 phase with its CSR emission, and a separately timed tsp_compact_zeros call on the result.
-cpu_baseline: the CPU oracle (row-wise Gustavson, fp64) timed on this box's host cores.
+cpu_baseline: the CPU oracle (row-wise Gustavson, fp64) timed on this machine's host cores.
 """
 from __future__ import annotations
 
