@@ -404,6 +404,14 @@ __device__ __forceinline__ uint32_t group16_or(uint32_t v) {
     v |= (uint32_t)TSP_DPP((int)v, (int)v, 0x121, 0xf, false);
     return v;
 }
+// Inclusive prefix sum over every row of 16 lanes.
+__device__ __forceinline__ int row16_inclusive_scan(int v) {
+    v += TSP_DPP(0, v, 0x111, 0xf, true);     // row_shr:1
+    v += TSP_DPP(0, v, 0x112, 0xf, true);     // row_shr:2
+    v += TSP_DPP(0, v, 0x114, 0xf, true);     // row_shr:4
+    v += TSP_DPP(0, v, 0x118, 0xf, true);     // row_shr:8
+    return v;
+}
 // Inclusive prefix sum over the 64 lanes of a wave.
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
     int v = (int)x;

@@ -813,7 +813,7 @@ struct PackArgs {
     int64_t rows;
     const int32_t *start;
     const int2 *rec;
-    uint32_t *pack;
+    uint32_t *pack;                      // (the low five bits of the column inverted: a shift by them brings the column's bit to the top)
     uint2 *word;
     int32_t *words;                      // per row
     int32_t *table;                      // [rows][windows + 1], or null for one window
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
             const int2 x = a.rec[k];
             const int32_t before = k > s ? a.rec[k - 1].x : -1;
             const _Float16 v = (_Float16)__uint_as_float((uint32_t)x.y);
-            a.pack[k] = ((uint32_t)x.x & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
+            a.pack[k] = (((uint32_t)x.x ^ 31u) & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
             if (tab)
                 for (int w = (before >> a.shift) + 1; w <= (x.x >> a.shift) && w <= a.windows; ++w) tab[w] = k;
             word = x.x >> 5;
@@ -864,32 +864,59 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
     }
 }
 
+// 64 pieces of up to 16 elements of B, four to a step: lane 16 q + t describes piece 4 t + q by the byte offset of its first
+// element and `about`, its number of elements << 16 | 16 bits of its own, and step t hands both to the 16 lanes that read the
+// piece (row_newbcast: an operand modifier of the instructions that use them; reading descriptions back from LDS cost an LDS
+// instruction per step).  Up to eight steps' elements are requested together.  use(x, about, l) gets the elements of up to
+// four steps, what describes them, and this lane's place in the piece: lanes past the end of a piece have other elements, up
+// to 15 past the segment.
+template <int kFirst, typename X, typename Use, int... kStep>
+__device__ __forceinline__ void use_steps(int about, const X *x, Use &use, std::integer_sequence<int, kStep...>) {
+    const X y[] = {x[kStep]...};
+    const uint32_t d[] = {(uint32_t)TSP_DPP(0, about, 0x150 + kFirst + kStep, 0xf, true)...};
+    use(y, d, threadIdx.x % 16u);
+}
+template <int kFirst, typename X, typename Use, int... kStep>
+__device__ __forceinline__ void read_steps(int byte, int about, const X *from, Use &use, std::integer_sequence<int, kStep...>) {
+    constexpr int kCount = sizeof...(kStep), kFour = kCount < 4 ? kCount : 4;
+    const uint32_t my_byte = threadIdx.x % 16u * (uint32_t)sizeof(X);
+    const X x[] = {*reinterpret_cast<const X *>(reinterpret_cast<const char *>(from) +
+                                                ((uint32_t)TSP_DPP(0, byte, 0x150 + kFirst + kStep, 0xf, true) + my_byte))...};
+    // (four at a time: eight want more registers than there are)
+    use_steps<kFirst>(about, x, use, std::make_integer_sequence<int, kFour>{});
+    if constexpr (kCount > 4) use_steps<kFirst + 4>(about, x + 4, use, std::make_integer_sequence<int, kCount - 4>{});
+}
+template <typename X, typename Use>
+__device__ __forceinline__ void read_pieces(int byte, int about, int pieces, const X *from, Use &use) {
+    const int steps = (pieces + 3) / 4;
+    auto batch = [&](auto first, int n) {
+        constexpr int kFirst = decltype(first)::value;
+        if (n > 4) read_steps<kFirst>(byte, about, from, use, std::make_integer_sequence<int, 8>{});
+        else if (n > 2) read_steps<kFirst>(byte, about, from, use, std::make_integer_sequence<int, 4>{});
+        else if (n == 2) read_steps<kFirst>(byte, about, from, use, std::make_integer_sequence<int, 2>{});
+        else if (n == 1) read_steps<kFirst>(byte, about, from, use, std::make_integer_sequence<int, 1>{});
+    };
+    batch(std::integral_constant<int, 0>{}, steps);
+    batch(std::integral_constant<int, 8>{}, steps - 8);
+}
+
 // The segments of B behind up to 64 entries of A, one per lane (first element, length, 16 bits of its own), as pieces of G
-// elements, 64 / G pieces to a step of the wave.  The lanes describe 64 pieces at a time (lane j: piece j of the
-// concatenation; the segment it lies in from a running maximum over the marks the segments leave at their first pieces)
-// in LDS, and a step reads its pieces' descriptions back: nothing is scalar and nothing is selected per piece, and up to
-// eight steps' elements are requested together.  use(x, active, bits) gets every element once; lanes past the end of a piece
-// get other elements (up to G - 1 past the segment) with active = false.
-struct PieceLds {
-    uint2 piece[64];                     // {byte offset of the first element, elements << 16 | bits}
-    uint32_t mark[64];
-};
+// elements, 64 / G pieces to a step of the wave.  The lanes describe 64 pieces at a time: the segment that a piece lies in
+// from a running maximum over the marks the segments leave at their first pieces.
 template <int G, typename X, typename Use>
-__device__ __forceinline__ void stream_pieces(int p, int len, uint32_t own, const X *from, PieceLds *lds, Use use) {
-    constexpr int kPer = 64 / G;
+__device__ __forceinline__ void stream_pieces(int p, int len, uint32_t own, const X *from, uint32_t *mark, Use use) {
     const int lane = lane_id();
     const int count = len > 0 ? (len + G - 1) / G : 0;
     const int inc = (int)wave_inclusive_scan((uint32_t)count), first = inc - count;
     const int total = __builtin_amdgcn_readlane(inc, 63);
-    const uint32_t my_byte = (uint32_t)(lane % G) * sizeof(X);
-    const uint2 *my_piece = lds->piece + lane / G;
+    const int mine = G == 16 ? 4 * (lane % 16) + lane / 16 : lane;             // the piece this lane describes (read_pieces)
     int carry = 0;
     for (int j0 = 0; j0 < total; j0 += 64) {
-        lds->mark[lane] = 0;
+        mark[lane] = 0;
         wave_sync();
-        if (count > 0 && (uint32_t)(first - j0) < 64u) lds->mark[first - j0] = (uint32_t)lane + 1u;
+        if (count > 0 && (uint32_t)(first - j0) < 64u) mark[first - j0] = (uint32_t)lane + 1u;
         wave_sync();
-        int m = max((int)lds->mark[lane], lane == 0 ? carry : 0);
+        int m = max((int)mark[lane], lane == 0 ? carry : 0);
         m = max(m, TSP_DPP(m, m, 0x111, 0xf, false));
         m = max(m, TSP_DPP(m, m, 0x112, 0xf, false));
         m = max(m, TSP_DPP(m, m, 0x114, 0xf, false));
@@ -897,35 +924,40 @@ __device__ __forceinline__ void stream_pieces(int p, int len, uint32_t own, cons
         m = max(m, TSP_DPP(m, m, 0x142, 0xa, false));
         m = max(m, TSP_DPP(m, m, 0x143, 0xc, false));
         carry = __builtin_amdgcn_readlane(m, 63);
+        if constexpr (G == 16) m = __builtin_amdgcn_ds_bpermute(mine * 4, m);
         const int source = (m - 1) * 4;
-        const int skip = (j0 + lane - __builtin_amdgcn_ds_bpermute(source, first)) * G;
+        const int skip = (j0 + mine - __builtin_amdgcn_ds_bpermute(source, first)) * G;
         const int begin = __builtin_amdgcn_ds_bpermute(source, p) + skip;
         const int left = __builtin_amdgcn_ds_bpermute(source, len) - skip;
         const uint32_t bits = (uint32_t)__builtin_amdgcn_ds_bpermute(source, (int)own);
-        const bool live = j0 + lane < total;
-        lds->piece[lane] = make_uint2(live ? (uint32_t)begin * (uint32_t)sizeof(X) : 0u,
-                                      (live ? (uint32_t)min(left, G) << 16 : 0u) | bits);
-        wave_sync();
-        const int steps = (min(total - j0, 64) + kPer - 1) / kPer;
-        auto batch = [&](auto size, int t) {
-            constexpr int kBatch = decltype(size)::value;
-            uint2 d[kBatch];
-            X x[kBatch];
+        const bool live = j0 + mine < total;
+        const int byte = live ? (int)((uint32_t)begin * (uint32_t)sizeof(X)) : 0;
+        const int about = live ? (int)((uint32_t)min(left, G) << 16 | bits) : 0;
+        const int pieces = min(total - j0, 64);
+        if constexpr (G == 16) {
+            read_pieces(byte, about, pieces, from, use);
+        } else {
+            static_assert(G == 64, "a piece is a row of lanes or a wave");
+            auto batch = [&](auto size, int t) {
+                constexpr int kBatch = decltype(size)::value;
+                uint32_t d[kBatch];
+                X x[kBatch];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) d[u] = my_piece[min(t + u, G - 1) * kPer];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u)
-                x[u] = *reinterpret_cast<const X *>(reinterpret_cast<const char *>(from) + (d[u].x + my_byte));
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) use(x[u], (uint32_t)(lane % G) < (t + u < steps ? d[u].y >> 16 : 0u), d[u].y & 0xFFFFu);
-        };
-        int t = 0;
-        for (; t + 8 <= steps; t += 8) batch(std::integral_constant<int, 8>{}, t);
-        const int rest = steps - t;
-        if (rest > 4) batch(std::integral_constant<int, 8>{}, t);
-        else if (rest > 2) batch(std::integral_constant<int, 4>{}, t);
-        else if (rest == 2) batch(std::integral_constant<int, 2>{}, t);
-        else if (rest == 1) batch(std::integral_constant<int, 1>{}, t);
+                for (int u = 0; u < kBatch; ++u) {
+                    d[u] = (uint32_t)__builtin_amdgcn_readlane(about, t + u);
+                    x[u] = *reinterpret_cast<const X *>(reinterpret_cast<const char *>(from) +
+                                                        ((uint32_t)__builtin_amdgcn_readlane(byte, t + u) + (uint32_t)lane * (uint32_t)sizeof(X)));
+                }
+                use(x, d, (uint32_t)lane);
+            };
+            int t = 0;
+            for (; t + 8 <= pieces; t += 8) batch(std::integral_constant<int, 8>{}, t);
+            if (pieces - t >= 4) {
+                batch(std::integral_constant<int, 4>{}, t);
+                t += 4;
+            }
+            for (; t < pieces; ++t) batch(std::integral_constant<int, 1>{}, t);
+        }
         wave_sync();
     }
 }
@@ -956,7 +988,7 @@ template <int kWin>
 __global__ __launch_bounds__(kCountThreads) void k_heavy_count(const CountArgs a) {
     extern __shared__ __align__(16) uint32_t bits[];
     constexpr int kWaves = kCountThreads / 64;
-    __shared__ PieceLds s_piece[kWaves];
+    __shared__ uint32_t s_mark[kWaves][64];
     __shared__ uint32_t s_cnt[kSpanWindows];
     __shared__ uint32_t s_run;
     constexpr int kWords = kWin / 32, kPerLane = kWords / 64;
@@ -996,11 +1028,14 @@ __global__ __launch_bounds__(kCountThreads) void k_heavy_count(const CountArgs a
                 p += lo[0];
                 len = lo[1] - lo[0];
             }
-            stream_pieces<16, uint2>(p, len, 0u, a.b_word, &s_piece[wave], [&](uint2 x, bool active, uint32_t) {
+            stream_pieces<16, uint2>(p, len, 0u, a.b_word, s_mark[wave], [&](const auto &x, const auto &d, uint32_t l) {
                 // (lanes without an element, and words an operand that was not validated may hold out of order, go to
                 // words behind the bits that nothing reads)
-                const uint32_t at = x.x - first;
-                atomicOr(&bits[active && at < words ? at : words + lane], x.y);
+#pragma unroll
+                for (size_t u = 0; u < sizeof(x) / sizeof(x[0]); ++u) {
+                    const uint32_t at = x[u].x - first;
+                    atomicOr(&bits[l < d[u] >> 16 && at < words ? at : words + lane], x[u].y);
+                }
             });
         }
         __syncthreads();
@@ -1058,20 +1093,24 @@ struct FillArgs {
 // A block per task: a row of C, or some of its windows, a step at a time: as many windows as hold at most kCap entries
 // and kSpanColumns columns.  The pattern of the step, a bit per column, is known from the sizing pass, so its entries
 // have places of their own in LDS: column c's is the number of bits before it, looked up as {32 bits, entries before
-// them}.  The waves deal the entries of the row of A among them, 64 apiece, stream the segments of B behind them and add
-// the products at their places; then the values go out as they lie, and the columns, listed from the bits.  (A dense
-// accumulator per window of 8192 columns needs no look-up but up to 32 steps for a row, most of them nearly empty.)
-// 64 registers, so that 8 waves per SIMD hide the round trips to the elements of B, half of the time: R-MAT scale 18,
-// 4096 entries with 8 waves at 8 / 6 / 4 waves per SIMD 19.5 / 22.4 / 22.3 ms, with 4 waves 22.0, 8192 entries 24.3 ms;
-// the dense accumulator 22.3 ms.
-// Bound by the traffic past the L2 caches: there 83 GB read (30 MB of B, met again by every row and step, and 9 GB of
-// pattern) and 24 GB written in 18.9 ms, 5.6 TB/s; vector ALUs busy 51 %, LDS 36 %, a third of that in bank conflicts.
+// them}.  The waves stream the segments of B behind the row and add the products at their places; then the values go out
+// as they lie, and the columns, listed from the bits.  (A dense accumulator per window of 8192 columns needs no look-up but
+// up to 32 steps for a row, most of them nearly empty.)
+// Where every thread has at most one entry of A, a step's segments are cut into pieces of 16 elements and every wave takes as
+// many of them as the others, whichever segments they belong to.  (Dealt by entries of A, 64 apiece, the busiest wave had
+// 1.9 times the mean on R-MAT scale 18, 2.9 times on rows of 37 entries, and the others waited for it.)  Longer rows are
+// dealt by entries: many of them meet each wave.  What the next step needs of the pattern and of the segments' ends is
+// requested before this one's entries go out.
+// 64 registers and nothing in scratch memory, so that 8 waves per SIMD hide the round trips to the elements of B: R-MAT
+// scale 18 18.9 -> 16.4 ms (20 to 90 bytes of scratch: 17.2 to 26), 4100 rows of 37 entries 52 -> 44 us.  There the vector
+// ALUs are busy 63 %, half of it not with products but with what a step costs by its windows; LDS 37 %.  Traffic past the
+// L2 caches (82 GB read, 24 GB written) does not bind it: with all elements of B from 2 MB 5 % less.
 //
 // The accumulator: LDS adds an fp32 number one lane after the other (193 cycles for a wave's 64 lanes, measured), an
 // integer or an fp64 number all lanes at a time (5, 8 and 8 to 16 cycles for 32-bit and 64-bit integers and fp64).  So
 // the sums are integers where they are exact in them, and fp64 otherwise; fp64 only with a block of one wave, whose
-// steps follow one another (lanes of a step that meet at an entry are added by the LDS one after the other).  64-bit integers: p * 2^k + 1.5 * 2^52 in fp64 holds the integer p * 2^k in its low
-// bits (|p * 2^k| < 2^51).
+// steps follow one another (lanes of a step that meet at an entry are added by the LDS one after the other).  64-bit
+// integers: p * 2^k + 1.5 * 2^52 in fp64 holds the integer p * 2^k in its low bits (|p * 2^k| < 2^51).
 constexpr int kSpanColumns = 1 << 16;    // the elements of B hold 16 bits of the column
 // The table of a C of at most so many columns is a quarter as long, which is what many light rows spend their time on:
 // 6000 rows of 60 entries, 6000 columns, 139 -> 119 us; with more columns a row takes more steps (R-MAT scale 17, 2.75 ->
@@ -1083,12 +1122,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
     constexpr int kWaves = kThreads / 64, kWords = kSpan / 32;
     __shared__ __align__(16) Acc acc[kCap + 64];               // (behind the entries a place per lane for lanes without an element)
     __shared__ __align__(16) int2 places[kWords];              // {bits of 32 columns, entries before them, less one}
-    __shared__ PieceLds s_piece[kWaves];
-    __shared__ int s_total[kWaves];
+    __shared__ union {
+        uint32_t mark[kWaves][64];                             // of stream_pieces
+        struct {                                               // the segments of B behind the row, one per thread
+            int first[kThreads];                               // pieces before it
+            uint2 at[kThreads];                                // {first element, elements << 16 | value of A}
+        } segment;
+    } s_list;
+    __shared__ int2 s_total[kWaves];                           // of a wave's threads: {entries of C, pieces}
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     auto sync = [] {
         if constexpr (kThreads == 64) wave_sync();
         else __syncthreads();
+    };
+    // (what is derived from the thread's number is made again in every part of a step: kept over the reading of B it would take
+    // the registers that the elements in flight need)
+    auto thread = [] {
+        int t = (int)threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
     };
     const int64_t t = blockIdx.x;
     if (a.live ? !uniform_load(a.live) || t >= uniform_load(a.live + 1) : t >= a.n_tasks) return;
@@ -1103,93 +1155,191 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
     const int word_shift = a.window_shift - 5;                 // words per window
     const uint32_t *kept = a.bits + (((int64_t)(heavy - a.heavy_from) * a.windows) << word_shift);
     const bool one = a.table == nullptr;
-    const int dealt = min(kWaves, (deg + 15) / 16);            // waves that take entries of A
-    auto begin_of = [&](int v) { return v < a.windows ? uniform_load(offset + v) : row_len; };
-    // the end of the step that begins at window v: lane i says whether window v + i still fits
-    auto step_end = [&](int v, uint32_t first) {
-        const int last = v + lane + 1;
-        const bool fits = last <= w_end && lane < (kSpan >> a.window_shift) &&
-                          (last < a.windows ? offset[last] : row_len) - first <= (uint32_t)kCap;
-        return v + max(__popcll(__ballot(fits)), 1);
+    const bool even = kWaves > 1 && deg <= kThreads;
+    const int dealt = min(kWaves, (deg + 15) / 16);            // waves that take entries of A, where they are dealt
+    // (in bounds whatever an operand that was not validated holds)
+    const int32_t *ends_of = one ? a.b_start : a.table;        // where the segments of a row of B begin and end, from ends_at() on
+    auto ends_at = [&](int32_t column) { return one ? (uint32_t)column : (uint32_t)column * (uint32_t)(a.windows + 1); };
+    auto begin_in = [&](uint32_t at, int v) { return max(element(ends_of, at + (uint32_t)(one ? 0 : v)), 0); };
+    auto end_in = [&](uint32_t at, int v_end) { return min(element(ends_of, at + (uint32_t)(one ? 1 : v_end)), a.b_nnz); };
+    auto value_bits = [](const int2 &x) -> uint32_t { return __builtin_bit_cast(uint16_t, (_Float16)__uint_as_float((uint32_t)x.y)); };
+    // lane i: entries of the row up to the end of window ends_from + i
+    int ends_from = w;
+    auto window_ends = [&] { return ends_from + lane + 1 < a.windows ? offset[ends_from + lane + 1] : row_len; };
+    uint32_t ends = window_ends(), first = uniform_load(offset + w), next_first;
+    int w_next;
+    // the windows of the step that begins at w: as many as hold at most kCap entries and kSpan columns
+    auto end_of_step = [&] {
+        if (w - ends_from + (kSpan >> a.window_shift) > 64) {
+            ends_from = w;
+            ends = window_ends();
+        }
+        const int at_window = ends_from + lane;
+        const bool fits = at_window >= w && at_window < w_end && at_window - w < (kSpan >> a.window_shift) && ends - first <= (uint32_t)kCap;
+        w_next = w + max(__popcll(__ballot(fits)), 1);
+        next_first = (uint32_t)__builtin_amdgcn_readlane((int)ends, w_next - 1 - ends_from);
     };
-    uint32_t first = begin_of(w);
+    // This thread's entry of A, where each has one: its value, and where its segment of B in the step begins and ends
+    const bool mine = even && (int)threadIdx.x < deg;
+    uint32_t my_value = 0, my_ends = 0;
+    int my_begin = 0, my_end = 0;
+    if (mine) {
+        const int2 x = a.a_rec[s + (int)threadIdx.x];
+        my_ends = ends_at(x.x);
+        my_value = value_bits(x);
+        my_begin = begin_in(my_ends, w);
+    }
+    int half = 0;                                              // the largest power of two below deg
+    if (even && deg > 1) half = 1 << (31 - __builtin_clz(deg - 1));
+    end_of_step();
+    uint4 b = make_uint4(0, 0, 0, 0);                          // four words of the step's pattern (of its first, with one wave)
+    auto request = [&] {
+        if (mine) my_end = end_in(my_ends, w_next);
+        const int at = thread() * 4;
+        b = make_uint4(0, 0, 0, 0);
+        if (at < (w_next - w) << word_shift) b = *reinterpret_cast<const uint4 *>(kept + ((int64_t)w << word_shift) + at);
+    };
+    request();
     while (w < w_end) {
-        const int w_next = step_end(w, first);
-        const uint32_t next_first = begin_of(w_next);
         const int some = (int)min(next_first - first, (uint32_t)kCap);
+        const int w0 = w, w1 = w_next, p = my_begin;
+        const uint32_t from = first;
+        auto next_step = [&] {                                 // its requests are on their way while this step's entries go out
+            my_begin = max(my_end, 0);
+            w = w_next;
+            first = next_first;
+            if (w < w_end) {
+                end_of_step();
+                request();
+            }
+        };
         if (some > 0) {
-            // places of the step's entries, four words per thread and round
-            const int words = (w_next - w) << word_shift;
-            int run = 0;
+            int pieces = 0;
+            uint32_t about = 0;
+            if (mine) {
+                const int len = min(max(my_end - p, 0), 0xFFFF);
+                about = (uint32_t)len << 16 | my_value;
+                pieces = (len + kPiece - 1) / kPiece;
+            }
+            // places of the step's entries, four words per thread and round, and of its pieces
+            const int words = (w1 - w0) << word_shift;
+            int run = 0, total_pieces = 0;
+            static_assert(kWaves == 1 || kWords <= kThreads * 4, "one round");
+            const int tid = thread();
+            for (int i = tid; i * 16 < some * (int)sizeof(Acc); i += kThreads)
+                reinterpret_cast<int4 *>(acc)[i] = make_int4(0, 0, 0, 0);
             for (int base = 0; base < words; base += kThreads * 4) {
-                const int at = base + (int)threadIdx.x * 4;
-                uint4 b = make_uint4(0, 0, 0, 0);
-                if (at < words) b = *reinterpret_cast<const uint4 *>(kept + ((int64_t)w << word_shift) + at);
+                const int at = base + tid * 4;
+                if (base > 0) {
+                    b = make_uint4(0, 0, 0, 0);
+                    if (at < words) b = *reinterpret_cast<const uint4 *>(kept + ((int64_t)w0 << word_shift) + at);
+                }
                 const int n0 = __popc(b.x), n1 = n0 + __popc(b.y), n2 = n1 + __popc(b.z), n3 = n2 + __popc(b.w);
                 const int inc = (int)wave_inclusive_scan((uint32_t)n3);
                 int before = run + inc - n3 - 1;
                 if constexpr (kWaves > 1) {
-                    if (lane == 63) s_total[wave] = inc;
+                    const int pieces_inc = (int)wave_inclusive_scan((uint32_t)pieces);
+                    int pieces_before = pieces_inc - pieces;
+                    if (lane == 63) s_total[wave] = make_int2(inc, pieces_inc);
                     __syncthreads();
-#pragma unroll
-                    for (int v = 0; v < kWaves; ++v) {
-                        before += v < wave ? s_total[v] : 0;
-                        run += s_total[v];
+                    // (sums over the waves, which are fewer than a row of lanes)
+                    const int2 total = tid % 16 < kWaves ? s_total[tid % 16] : make_int2(0, 0);
+                    const int entries_to = row16_inclusive_scan(total.x), pieces_to = row16_inclusive_scan(total.y);
+                    if (wave > 0) {
+                        before += __builtin_amdgcn_readlane(entries_to, wave - 1);
+                        pieces_before += __builtin_amdgcn_readlane(pieces_to, wave - 1);
                     }
-                    if (base + kThreads * 4 < words) __syncthreads();
+                    total_pieces = __builtin_amdgcn_readlane(pieces_to, kWaves - 1);
+                    if (even) {
+                        s_list.segment.first[tid] = pieces_before;
+                        s_list.segment.at[tid] = make_uint2((uint32_t)p, about);
+                    }
                 } else {
                     run += __builtin_amdgcn_readlane(inc, 63);
                 }
                 if (at < words) {
-                    int4 *to = reinterpret_cast<int4 *>(places + at);
+                    int4 *to = reinterpret_cast<int4 *>(places + (((w0 << word_shift) + at) & (kWords - 1)));
                     to[0] = make_int4((int)b.x, before, (int)b.y, before + n0);
                     to[1] = make_int4((int)b.z, before + n1, (int)b.w, before + n2);
                 }
             }
-            for (int i = threadIdx.x; i < some; i += kThreads) acc[i] = Acc(0);
             sync();
-            const uint32_t c0 = (uint32_t)w << a.window_shift;
-            for (int base = 0; base < deg && wave < dealt; base += 64 * dealt) {
-                const int k = base + lane * dealt + wave;
-                int p = 0, len = 0;
-                uint32_t own = 0;
-                if (k < deg) {
-                    const int2 x = a.a_rec[s + k];
-                    const int32_t *from = one ? a.b_start + x.x : a.table + ((int64_t)x.x * (a.windows + 1) + w);
-                    // (in bounds whatever an operand that was not validated holds)
-                    p = max(from[0], 0);
-                    len = min(from[one ? 1 : w_next - w], a.b_nnz) - p;
-                    own = __builtin_bit_cast(uint16_t, (_Float16)__uint_as_float((uint32_t)x.y));
+            const uint32_t c0 = (uint32_t)w0 << a.window_shift;
+            // (all look-ups of a batch before the first addition, and nothing selected but whether a lane adds: a chain of
+            // look-up and addition for every element leaves the LDS idle for the latency of both)
+            auto use = [&](const auto &x, const auto &d, uint32_t l) {
+                constexpr int kBatch = (int)(sizeof(x) / sizeof(x[0]));
+                int2 place[kBatch];
+                uint32_t at[kBatch];
+                float product[kBatch];
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u)
+                    place[u] = *reinterpret_cast<const int2 *>(reinterpret_cast<const char *>(places) + ((x[u] >> 2) & (uint32_t)(kWords - 1) * 8u));
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    // (inside acc also for a column that the pattern does not have)
+                    at[u] = min((uint32_t)(__popc((uint32_t)place[u].x << (x[u] & 31u)) + place[u].y), (uint32_t)kCap);
+                    // the product of two fp16 numbers is exact; + 0 makes a positive zero of a negative one
+                    product[u] = __builtin_fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)(x[u] >> 16)),
+                                                (float)__builtin_bit_cast(_Float16, (uint16_t)d[u]), 0.f);
                 }
-                stream_pieces<kPiece, uint32_t>(
-                    p, len, own, a.pack, &s_piece[wave], [&](uint32_t x, bool active, uint32_t a16) {
-                        const uint32_t c = (x - c0) & (uint32_t)(kSpan - 1);
-                        const int2 place = places[c >> 5];
-                        const int rank = __popc((uint32_t)place.x << (31u - (c & 31u))) + place.y;
-                        // (inside acc also for a column that the pattern does not have)
-                        const int at = active ? min(max(rank, 0), kCap) : kCap + lane;
-                        // the product of two fp16 numbers is exact; + 0 makes a positive zero of a negative one
-                        const float product = __builtin_fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)(x >> 16)),
-                                                             (float)__builtin_bit_cast(_Float16, (uint16_t)a16), 0.f);
-                        if constexpr (std::is_floating_point<Acc>::value) {
-                            if (active) unsafeAtomicAdd(&acc[at], (double)product);
-                        } else if constexpr (sizeof(Acc) == 4) {
-                            atomicAdd(&acc[at], (int)(product * a.p_scale));
-                        } else {
-                            const double shifted = __builtin_fma((double)product, (double)a.p_scale, 6755399441055744.0);
-                            atomicAdd(reinterpret_cast<unsigned long long *>(&acc[at]),
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    const bool active = l < d[u] >> 16;
+                    if constexpr (std::is_floating_point<Acc>::value) {
+                        if (active) unsafeAtomicAdd(&acc[at[u]], (double)product[u]);
+                    } else if constexpr (sizeof(Acc) == 4) {
+                        const int whole = (int)(product[u] * a.p_scale);
+                        if (active) atomicAdd(&acc[at[u]], whole);
+                    } else {
+                        const double shifted = __builtin_fma((double)product[u], (double)a.p_scale, 6755399441055744.0);
+                        if (active)
+                            atomicAdd(reinterpret_cast<unsigned long long *>(&acc[at[u]]),
                                       __builtin_bit_cast(unsigned long long, shifted) - 0x4338000000000000ull);
-                        }
-                    });
+                    }
+                }
+            };
+            if (even) {
+                if constexpr (kWaves > 1) {
+                    const int share = (total_pieces + 4 * kWaves - 1) / (4 * kWaves) * 4;      // of a wave
+                    const int end = min((wave + 1) * share, total_pieces);
+                    for (int j0 = wave * share; j0 < end; j0 += 64) {
+                        const int j = j0 + 4 * (lane % 16) + lane / 16;    // the piece this lane describes (read_pieces)
+                        int at = 0;                                        // the last segment that begins at or before it
+                        for (int d = half; d > 0; d >>= 1)
+                            if (s_list.segment.first[at + d] <= j) at += d;
+                        const uint2 x = s_list.segment.at[at];
+                        const int skip = (j - s_list.segment.first[at]) * kPiece;
+                        const bool live = j < end;
+                        read_pieces(live ? (int)((x.x + (uint32_t)skip) * 4u) : 0,
+                                    live ? (int)((uint32_t)min((int)(x.y >> 16) - skip, kPiece) << 16 | (x.y & 0xFFFFu)) : 0,
+                                    min(end - j0, 64), a.pack, use);
+                    }
+                }
+            } else {
+                for (int base = 0; base < deg && wave < dealt; base += 64 * dealt) {
+                    const int k = base + (thread() & 63) * dealt + wave;
+                    int begin = 0, len = 0;
+                    uint32_t own = 0;
+                    if (k < deg) {
+                        const int2 x = a.a_rec[s + k];
+                        const uint32_t at = ends_at(x.x);
+                        begin = begin_in(at, w0);
+                        len = end_in(at, w1) - begin;
+                        own = value_bits(x);
+                    }
+                    stream_pieces<kPiece, uint32_t>(begin, len, own, a.pack, s_list.mark[wave], use);
+                }
             }
+            next_step();
             sync();
-            float *to_val = a.c_val + row_first + first;
-            for (int i = threadIdx.x; i < some; i += kThreads)
+            float *to_val = a.c_val + row_first + from;
+            for (int i = thread(); i < some; i += kThreads)
                 to_val[(unsigned)i] = std::is_floating_point<Acc>::value ? (float)acc[i] : (float)acc[i] * a.c_scale;
             sync();
             int32_t *col = reinterpret_cast<int32_t *>(acc);
-            for (int i = threadIdx.x; i < words; i += kThreads) {
-                const int2 place = places[i];
+            for (int i = thread(); i < words; i += kThreads) {
+                const int2 place = places[((w0 << word_shift) + i) & (kWords - 1)];
                 uint32_t word = (uint32_t)place.x;
                 int32_t *to = col + place.y;
                 while (word) {
@@ -1198,12 +1348,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
                 }
             }
             sync();
-            int32_t *to_col = a.c_col + row_first + first;
-            for (int i = threadIdx.x; i < some; i += kThreads) to_col[(unsigned)i] = col[i];
+            int32_t *to_col = a.c_col + row_first + from;
+            for (int i = thread(); i < some; i += kThreads) to_col[(unsigned)i] = col[i];
             sync();
+        } else {
+            next_step();
         }
-        w = w_next;
-        first = next_first;
     }
 }
 

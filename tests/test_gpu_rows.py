@@ -322,6 +322,25 @@ def test_tasks_of_very_long_rows(tsp, oracle, values, per_row, entries):
         h.close()
 
 
+@pytest.mark.parametrize("values", ["ones", "below one"])
+@pytest.mark.parametrize("cols", [6000, 70001])
+@pytest.mark.parametrize("entries", [17, 33, 511, 512, 513, 1025])
+def test_pieces_of_heavy_rows_dealt_to_waves(tsp, oracle, values, cols, entries):
+    """Rows of A of as many entries as a block has threads and either side, whose segments of B are cut into pieces of 16
+    elements: rows of B of no, one, 15 to 17, 33 and very many elements; tables of few and of many columns, several steps."""
+    rng = np.random.default_rng(entries + cols)
+    make = lambda m: _VALUES[values](rng, m)
+    lengths = np.full(300, 20)
+    lengths[::37] = entries
+    A = _exact_lengths(rng, 1100, lengths, make)
+    B = _exact_lengths(rng, cols, rng.choice([0, 1, 15, 16, 17, 33, 5000], 1100, p=[0.2, 0.2, 0.15, 0.15, 0.1, 0.18, 0.02]), make)
+    h = tsp.Handle()
+    try:
+        _check(h, tsp, oracle, A, B)
+    finally:
+        h.close()
+
+
 def test_values_that_integers_do_not_hold_by_tiles(tsp, oracle):
     """A product that is faster by rows while its sums are integers and by tiles otherwise."""
     rng = np.random.default_rng(4)
