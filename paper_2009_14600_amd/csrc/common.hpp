@@ -49,6 +49,7 @@ enum Scalar {
     S_ROW_SKIP = 30,         // != 0: clearly a product by tiles, and its pairs of tiles as estimated, plus one
     S_LARGE_A = 24,          // tile-rows of an operand whose entries do not fit the registers of k_convert_block
     S_LARGE_B = 25,
+    S_ROW_LARGE_TASKS = 24,   // blocks of k_heavy_fill for rows with many products (a slot of the tile converter's)
     S_DESCENDS = 27,         // != 0: the row pointers of a matrix to be compacted go down somewhere
     S_EMPTY_RUNS = 28,       // != 0: more of its rows may begin in 4096 entries than one block finds (a slot of k_row_sample's)
     S_PUBLISHED = 31,        // host mirror only: a slot without a value (publish_scalars tags every slot)
@@ -113,7 +114,7 @@ struct RowHint {
     int64_t candidates = 0;                        // pairs of tiles, by which that was decided
     bool estimated = false;                        // ... from some of the tile-rows
     bool sample = true;                            // (a look at some of the tile-rows has not misled yet)
-    int64_t heavy = 0, tasks = 0;
+    int64_t heavy = 0, tasks = 0, large_tasks = 0;
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows
     bool wide = false;                             // so many rows of 9 to 16 entries that 16 lanes per row pay

@@ -72,7 +72,10 @@ struct PrepareArgs {
     int small_lanes, small_products;     // most entries and products of a small row of A
     int windows;                         // of columns of C, for the heavy rows
     int32_t *heavy;                      // rows that are not small
-    int4 *tasks;                         // {row, index into heavy, first window, one past the last window}
+    // {row, index into heavy, first window, one past the last window}; of rows of large_products and more from the front on,
+    // of the others from the back
+    int4 *tasks;
+    int large_products;
     int64_t heavy_cap, task_cap;
     uint32_t *rows_of;                   // of every tile-row: pack_rows()
     int64_t *d_scalars;
@@ -260,21 +263,26 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
     for (int d = 1; d < T; d <<= 1) all += __shfl_xor(all, d, T);
     if (tid == 0) a.products[I] = all;
     const unsigned long long heavies = __ballot(tasks > 0);
-    if (heavies) {                       // places in both lists from one atomic
-        const uint32_t inc = wave_inclusive_scan((uint32_t)tasks);
-        unsigned long long at = 0;
-        if (lane == 63)
+    if (heavies) {                       // places in both lists from one atomic, and from another for the large ones
+        const bool large = ub >= (unsigned long long)a.large_products;
+        const uint32_t light_inc = wave_inclusive_scan(large ? 0u : (uint32_t)tasks), large_inc = wave_inclusive_scan(large ? (uint32_t)tasks : 0u);
+        unsigned long long at = 0, large_at = 0;
+        if (lane == 63) {
             at = atomicAdd(reinterpret_cast<unsigned long long *>(a.d_scalars + S_ROW_LISTS),
-                           ((unsigned long long)__popcll(heavies) << 36) | inc);
+                           ((unsigned long long)__popcll(heavies) << 36) | light_inc);
+            if (large_inc) large_at = atomicAdd(reinterpret_cast<unsigned long long *>(a.d_scalars + S_ROW_LARGE_TASKS), (unsigned long long)large_inc);
+        }
         at = __shfl(at, 63, 64);
+        large_at = __shfl(large_at, 63, 64);
         const int64_t h = (int64_t)(at >> 36) + __popcll(heavies & ((1ull << lane) - 1ull));
-        const int64_t t0 = (int64_t)(at & ((1ull << 36) - 1ull)) + inc - tasks;
+        const int64_t t0 = large ? (int64_t)large_at + large_inc - tasks
+                                : a.task_cap - ((int64_t)(at & ((1ull << 36) - 1ull)) + light_inc);
         if (tasks > 0 && h < a.heavy_cap) {
             a.heavy[h] = (int32_t)row;
             // (groups of windows, as even as they go; single ones where there are more tasks than groups)
             const int unit = tasks > groups ? 1 : kGroupWindows, units = tasks > groups ? a.windows : groups;
             for (int t = 0; t < tasks; ++t)
-                if (t0 + t < a.task_cap)
+                if ((uint64_t)(t0 + t) < (uint64_t)a.task_cap)
                     a.tasks[t0 + t] = make_int4((int)row, (int)h, (int)((int64_t)units * t / tasks) * unit,
                                                 min((int)((int64_t)units * (t + 1) / tasks) * unit, a.windows));
         }
@@ -420,10 +428,11 @@ __host__ __device__ inline FillKind fill_kind(const int64_t *h) {
 
 // What the kernels of the multiplication have been launched with before the host knows the sizes
 struct Expected {
-    int64_t nnz, heavy, tasks;
+    int64_t nnz, heavy, tasks, large;
     FillKind kind;
     __host__ __device__ bool holds(const int64_t *scalars) const {
-        return !scalars[S_INVALID] && scalars[S_C_NNZ] <= nnz && scalars[S_ROW_HEAVY] <= heavy && scalars[S_ROW_TASKS] <= tasks &&
+        return !scalars[S_INVALID] && scalars[S_C_NNZ] <= nnz && scalars[S_ROW_HEAVY] <= heavy && scalars[S_ROW_TASKS] - scalars[S_ROW_LARGE_TASKS] <= tasks - large &&
+               scalars[S_ROW_LARGE_TASKS] <= large &&
                fill_exact(kind, scalars[S_ROW_RANGE_A], scalars[S_ROW_RANGE_B], scalars[S_ROW_LONGEST]) &&
                // (fp64 does for any values, but where integers do their sums have other last bits)
                (kind.sum != FillKind::kDouble || fill_kind(scalars).sum == FillKind::kDouble);
@@ -441,7 +450,7 @@ struct FinishArgs {
     int64_t publish_tag;
     bool clear;                          // the scalar block, for the next call
     Expected expected;
-    int32_t *live;                       // [2]: whether what is expected holds, and the number of tasks
+    int32_t *live;                       // [3]: whether what is expected holds, and the numbers of all and of the large tasks
     const int64_t *skip;                 // S_ROW_SKIP, or null: nothing has been counted then
 };
 
@@ -514,7 +523,7 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
     if (!last) return;
     if (threadIdx.x == S_C_NNZ) own[S_C_NNZ] = a.rows > 0 ? (int64_t)(entries_before + total) : standing;
     if (threadIdx.x == S_INVALID) own[S_INVALID] = standing;
-    if (threadIdx.x == S_ROW_LISTS) own[S_ROW_LISTS] = standing;
+    if (threadIdx.x == S_ROW_LISTS || threadIdx.x == S_ROW_LARGE_TASKS) own[threadIdx.x] = standing;
     __syncthreads();
     if (threadIdx.x == 0) {
         if (a.rows > 0) a.c_row_ptr[a.rows] = (int64_t)(entries_before + total);
@@ -530,10 +539,11 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
         own[S_ROW_LONGEST] = (int64_t)s_max[4];
         const unsigned long long lists = (unsigned long long)own[S_ROW_LISTS];
         own[S_ROW_HEAVY] = (int64_t)(lists >> 36);
-        own[S_ROW_TASKS] = (int64_t)(lists & ((1ull << 36) - 1ull));
+        own[S_ROW_TASKS] = (int64_t)(lists & ((1ull << 36) - 1ull)) + own[S_ROW_LARGE_TASKS];
         if (a.live) {
             a.live[0] = a.expected.holds(own);
             a.live[1] = (int32_t)own[S_ROW_TASKS];
+            a.live[2] = (int32_t)own[S_ROW_LARGE_TASKS];
         }
     }
     constexpr uint32_t kOwn = own_slot(S_C_NNZ) | own_slot(S_CANDIDATES) | own_slot(S_TILES_A) | own_slot(S_TILES_B) |
@@ -962,6 +972,33 @@ __device__ __forceinline__ void stream_pieces(int p, int len, uint32_t own, cons
     }
 }
 
+// The segments of B behind up to kThreads entries of A, one per thread, cut into pieces of 16 elements that the waves share out
+// evenly.
+template <int kThreads>
+struct SegmentList {
+    int first[kThreads];                                       // pieces before the segment
+    uint2 at[kThreads];                                        // {first element, elements << 16 | 16 bits of its own}
+};
+// The segments of `entries` threads are in the list, `total` pieces; every wave streams its share.
+template <int kThreads, typename X, typename Use>
+__device__ __forceinline__ void stream_share(const SegmentList<kThreads> &list, int entries, int total, const X *from, Use &use) {
+    constexpr int kWaves = kThreads / 64;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int half = entries > 1 ? 1 << (31 - __builtin_clz(entries - 1)) : 0;     // the largest power of two below them
+    const int share = (total + 4 * kWaves - 1) / (4 * kWaves) * 4, end = min((wave + 1) * share, total);
+    for (int j0 = wave * share; j0 < end; j0 += 64) {
+        const int j = j0 + 4 * (lane % 16) + lane / 16;        // the piece this lane describes (read_pieces)
+        int at = 0;                                            // the last segment that begins at or before it
+        for (int d = half; d > 0; d >>= 1)
+            if (list.first[at + d] <= j) at += d;
+        const uint2 x = list.at[at];
+        const int skip = (j - list.first[at]) * 16;
+        const bool live = j < end;
+        read_pieces(live ? (int)((x.x + (uint32_t)skip) * (uint32_t)sizeof(X)) : 0,
+                    live ? (int)((uint32_t)min((int)(x.y >> 16) - skip, 16) << 16 | (x.y & 0xFFFFu)) : 0, min(end - j0, 64), from, use);
+    }
+}
+
 struct CountArgs {
     const int32_t *heavy;
     int64_t heavy_cap;
@@ -1071,8 +1108,9 @@ __global__ __launch_bounds__(kCountThreads) void k_heavy_count(const CountArgs a
 }
 
 struct FillArgs {
-    const int4 *tasks;
-    int64_t n_tasks;
+    const int4 *tasks;                   // [task_cap]: the large ones, then others or nothing, then the light ones
+    int64_t n_tasks, n_large, task_cap;
+    bool large, light;                    // which of them this launch is for
     const int32_t *a_start, *b_start;
     const int2 *a_rec;
     const uint32_t *pack;
@@ -1102,9 +1140,10 @@ struct FillArgs {
 // dealt by entries: many of them meet each wave.  What the next step needs of the pattern and of the segments' ends is
 // requested before this one's entries go out.
 // 64 registers and nothing in scratch memory, so that 8 waves per SIMD hide the round trips to the elements of B: R-MAT
-// scale 18 18.9 -> 16.4 ms (20 to 90 bytes of scratch: 17.2 to 26), 4100 rows of 37 entries 52 -> 44 us.  There the vector
+// scale 18 18.9 -> 16.4 ms (20 to 90 bytes of scratch: 17.2 to 26), 4100 rows of 37 entries 52 -> 44 us.  The vector
 // ALUs are busy 63 %, half of it not with products but with what a step costs by its windows; LDS 37 %.  Traffic past the
-// L2 caches (82 GB read, 24 GB written) does not bind it: with all elements of B from 2 MB 5 % less.
+// L2 caches (82 GB read, 24 GB written) does not bind it: with all elements of B from 2 MB 5 % less.  Entries go out four to a
+// thread (16.5 -> 16.3 ms).
 //
 // The accumulator: LDS adds an fp32 number one lane after the other (193 cycles for a wave's 64 lanes, measured), an
 // integer or an fp64 number all lanes at a time (5, 8 and 8 to 16 cycles for 32-bit and 64-bit integers and fp64).  So
@@ -1116,6 +1155,12 @@ constexpr int kSpanColumns = 1 << 16;    // the elements of B hold 16 bits of th
 // 6000 rows of 60 entries, 6000 columns, 139 -> 119 us; with more columns a row takes more steps (R-MAT scale 17, 2.75 ->
 // 3.05 ms with a table of 32768 columns, 3.67 with one of 16384; scales 13 and 14 the same with either).
 constexpr int kNarrowColumns = 1 << 14;
+// Rows of so many products, summed in 32 bits, are large: blocks of 1024 threads and steps of 12,288 entries, two blocks to a
+// CU.  A step costs every wave some 330 vector instructions whatever it holds, so that rows of many entries want few steps, and
+// rows of few entries few waves.  R-MAT scale 18, all rows by 512 threads and 4096 entries 16.3 ms, all by 1024 15.2, large from
+// 8192 / 16,384 / 32,768 products on 14.75 / 14.5 / 14.1; scale 14 (a table for few columns) 235 us, 230, 184 / 178 / 188, and
+// 168 with blocks of 256 threads for the light ones.
+constexpr int kLarge = 32768, kLargeNarrow = 16384;
 
 template <typename Acc, int kCap, int kThreads, int kSpan, int kPiece = 16>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThreads == 64 ? 1 : 8, 8))) void k_heavy_fill(const FillArgs a) {
@@ -1124,10 +1169,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
     __shared__ __align__(16) int2 places[kWords];              // {bits of 32 columns, entries before them, less one}
     __shared__ union {
         uint32_t mark[kWaves][64];                             // of stream_pieces
-        struct {                                               // the segments of B behind the row, one per thread
-            int first[kThreads];                               // pieces before it
-            uint2 at[kThreads];                                // {first element, elements << 16 | value of A}
-        } segment;
+        SegmentList<kThreads> segment;                         // (with the value of A)
     } s_list;
     __shared__ int2 s_total[kWaves];                           // of a wave's threads: {entries of C, pieces}
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -1142,8 +1184,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
         asm volatile("" : "+v"(t));
         return t;
     };
-    const int64_t t = blockIdx.x;
-    if (a.live ? !uniform_load(a.live) || t >= uniform_load(a.live + 1) : t >= a.n_tasks) return;
+    if (a.live && !uniform_load(a.live)) return;
+    const int64_t n_large = a.live ? uniform_load(a.live + 2) : a.n_large, n_light = (a.live ? uniform_load(a.live + 1) : a.n_tasks) - n_large;
+    int64_t t = blockIdx.x;
+    if (!a.large || t >= n_large) {
+        t -= a.large ? n_large : 0;
+        if (!a.light || t >= n_light) return;
+        t += a.task_cap - n_light;
+    }
     const int32_t row = uniform_load(&a.tasks[t].x), heavy = uniform_load(&a.tasks[t].y);
     int w = uniform_load(&a.tasks[t].z);
     const int w_end = uniform_load(&a.tasks[t].w);
@@ -1189,8 +1237,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
         my_value = value_bits(x);
         my_begin = begin_in(my_ends, w);
     }
-    int half = 0;                                              // the largest power of two below deg
-    if (even && deg > 1) half = 1 << (31 - __builtin_clz(deg - 1));
     end_of_step();
     uint4 b = make_uint4(0, 0, 0, 0);                          // four words of the step's pattern (of its first, with one wave)
     auto request = [&] {
@@ -1300,22 +1346,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
                 }
             };
             if (even) {
-                if constexpr (kWaves > 1) {
-                    const int share = (total_pieces + 4 * kWaves - 1) / (4 * kWaves) * 4;      // of a wave
-                    const int end = min((wave + 1) * share, total_pieces);
-                    for (int j0 = wave * share; j0 < end; j0 += 64) {
-                        const int j = j0 + 4 * (lane % 16) + lane / 16;    // the piece this lane describes (read_pieces)
-                        int at = 0;                                        // the last segment that begins at or before it
-                        for (int d = half; d > 0; d >>= 1)
-                            if (s_list.segment.first[at + d] <= j) at += d;
-                        const uint2 x = s_list.segment.at[at];
-                        const int skip = (j - s_list.segment.first[at]) * kPiece;
-                        const bool live = j < end;
-                        read_pieces(live ? (int)((x.x + (uint32_t)skip) * 4u) : 0,
-                                    live ? (int)((uint32_t)min((int)(x.y >> 16) - skip, kPiece) << 16 | (x.y & 0xFFFFu)) : 0,
-                                    min(end - j0, 64), a.pack, use);
-                    }
-                }
+                if constexpr (kWaves > 1) stream_share<kThreads>(s_list.segment, deg, total_pieces, a.pack, use);
             } else {
                 for (int base = 0; base < deg && wave < dealt; base += 64 * dealt) {
                     const int k = base + (thread() & 63) * dealt + wave;
@@ -1334,8 +1365,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
             next_step();
             sync();
             float *to_val = a.c_val + row_first + from;
-            for (int i = thread(); i < some; i += kThreads)
-                to_val[(unsigned)i] = std::is_floating_point<Acc>::value ? (float)acc[i] : (float)acc[i] * a.c_scale;
+            struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+            struct __attribute__((packed, aligned(4))) I4 { int x, y, z, w; };
+            auto value = [&](Acc v) { return std::is_floating_point<Acc>::value ? (float)v : (float)v * a.c_scale; };
+            struct alignas(16) A4 { Acc x, y, z, w; };
+            const int t4 = thread() * 4, rest = some & ~3;
+            for (int i = t4; i + 4 <= some; i += kThreads * 4) {
+                const A4 v = *reinterpret_cast<const A4 *>(acc + i);
+                *reinterpret_cast<F4 *>(to_val + (unsigned)i) = F4{value(v.x), value(v.y), value(v.z), value(v.w)};
+            }
+            if (t4 < (some & 3) * 4) to_val[(unsigned)(rest + t4 / 4)] = value(acc[rest + t4 / 4]);
             sync();
             int32_t *col = reinterpret_cast<int32_t *>(acc);
             for (int i = thread(); i < words; i += kThreads) {
@@ -1349,7 +1388,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
             }
             sync();
             int32_t *to_col = a.c_col + row_first + from;
-            for (int i = thread(); i < some; i += kThreads) to_col[(unsigned)i] = col[i];
+            const int u4 = thread() * 4;
+            for (int i = u4; i + 4 <= some; i += kThreads * 4) {
+                const int4 c = *reinterpret_cast<const int4 *>(col + i);
+                *reinterpret_cast<I4 *>(to_col + (unsigned)i) = I4{c.x, c.y, c.z, c.w};
+            }
+            if (u4 < (some & 3) * 4) to_col[(unsigned)(rest + u4 / 4)] = col[rest + u4 / 4];
             sync();
         } else {
             next_step();
@@ -1413,6 +1457,7 @@ struct LeftOperand {
     int windows;
     int32_t *heavy;
     int4 *tasks;
+    int large_products;
     int64_t heavy_cap, task_cap;
 };
 
@@ -1442,6 +1487,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
             a.windows = left->windows;
             a.heavy = left->heavy;
             a.tasks = left->tasks;
+            a.large_products = left->large_products;
             a.heavy_cap = left->heavy_cap;
             a.task_cap = left->task_cap;
             a.rows_of = left->rows_of;
@@ -1456,24 +1502,35 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
 }
 
 void launch_fill(FillArgs &f, FillKind kind, bool short_rows, hipStream_t s) {
-    auto launch = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)f.n_tasks), dim3(threads), 0, s, f);
+    auto launch = [&](auto kernel, int threads, bool large, bool light) {
+        f.large = large;
+        f.light = light;
+        const int64_t blocks = (large ? f.n_large : 0) + (light ? f.n_tasks - f.n_large : 0);
+        if (blocks > 0) hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, s, f);
     };
     f.p_scale = std::ldexp(1.0f, -kind.scale);
     f.c_scale = std::ldexp(1.0f, kind.scale);
     const bool narrow = (int64_t)f.windows << f.window_shift <= kNarrowColumns;
-    if (kind.sum == FillKind::kInt32)
-        launch(narrow ? k_heavy_fill<int32_t, 4096, 512, kNarrowColumns> : k_heavy_fill<int32_t, 4096, 512, kSpanColumns>, 512);
-    else if (kind.sum == FillKind::kInt64)
-        launch(narrow ? k_heavy_fill<long long, 4096, 512, kNarrowColumns> : k_heavy_fill<long long, 4096, 512, kSpanColumns>, 512);
-    // (rows of B shorter than a wave: four at a time.  20,000 rows of 3 entries, five of 6600, normal values: 2338 -> 1285 us)
-    else launch(short_rows ? k_heavy_fill<double, 4096, 64, kSpanColumns, 16> : k_heavy_fill<double, 4096, 64, kSpanColumns, 64>, 64);
+    if (kind.sum == FillKind::kInt32 && narrow) {
+        launch(k_heavy_fill<int32_t, 12288, 1024, kNarrowColumns>, 1024, true, false);
+        launch(k_heavy_fill<int32_t, 4096, 256, kNarrowColumns>, 256, false, true);
+    } else if (kind.sum == FillKind::kInt32) {
+        launch(k_heavy_fill<int32_t, 12288, 1024, kSpanColumns>, 1024, true, false);
+        launch(k_heavy_fill<int32_t, 4096, 512, kSpanColumns>, 512, false, true);
+    } else if (kind.sum == FillKind::kInt64 && narrow) {     // (4100 rows of 37 entries: 44 us with 512 threads, 42 with 256)
+        launch(k_heavy_fill<long long, 4096, 256, kNarrowColumns>, 256, true, true);
+    } else if (kind.sum == FillKind::kInt64) {
+        launch(k_heavy_fill<long long, 4096, 512, kSpanColumns>, 512, true, true);
+    } else {
+        // (rows of B shorter than a wave: four at a time.  20,000 rows of 3 entries, five of 6600, normal values: 2338 -> 1285 us)
+        launch(short_rows ? k_heavy_fill<double, 4096, 64, kSpanColumns, 16> : k_heavy_fill<double, 4096, 64, kSpanColumns, 64>, 64, true, true);
+    }
 }
 
 }  // namespace
 
 __global__ void k_clear_lists(int64_t *d_scalars) {
-    if (threadIdx.x == 0) d_scalars[S_ROW_LISTS] = 0;
+    if (threadIdx.x == 0) d_scalars[S_ROW_LISTS] = d_scalars[S_ROW_LARGE_TASKS] = 0;
 }
 // all but the count of products, which has run before anything else of the call
 __global__ void k_clear_rows(int64_t *d_scalars, int64_t products) {
@@ -1651,6 +1708,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     left.B = B;
     left.shape = shape;
     left.windows = windows;
+    left.large_products = (int64_t)windows << shift <= kNarrowColumns ? kLargeNarrow : kLarge;
     unsigned long long *partial = ws.get<unsigned long long>((size_t)kPlanBlocks * kPlanSums);
     // (tasks of a product not seen before: one per heavy row and some more; where that is too few the lists are made again)
     left.heavy_cap = known ? hint.heavy : A->rows;
@@ -1748,7 +1806,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         TSP_HIP_CHECK(ctx, hipGetLastError());
         return (int)TSP_OK;
     };
-    int64_t n_heavy = left.heavy_cap, n_tasks = left.task_cap;
+    int64_t n_heavy = left.heavy_cap, n_tasks = left.task_cap, n_large = known ? hint.large_tasks : 0;
     FillKind kind{};
     bool other_lanes = false;                // the product at hand wants its small rows by another number of lanes
     auto sizes_known = [&]() {               // the host has the numbers of k_row_finish
@@ -1756,6 +1814,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
         n_heavy = h[S_ROW_HEAVY];
         n_tasks = h[S_ROW_TASKS];
+        n_large = h[S_ROW_LARGE_TASKS];
         hint.ready = true;
         hint.wide = h[S_ROW_WIDE] > A->rows / 64;
         other_lanes = shape.slots <= 128 && shape.lanes != (hint.wide ? 16 : lanes_unless_wide);
@@ -1767,6 +1826,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hint.candidates = h[S_CANDIDATES];
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
+        hint.large_tasks = n_large;
         hint.small = h[S_ROW_SMALL] > 0;
         hint.nnz = row_ptr ? h[S_C_NNZ] : -1;
         hint.sum = kind.sum;
@@ -1901,6 +1961,8 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             FillArgs f{};
             f.tasks = left.tasks;
             f.n_tasks = n_tasks;
+            f.n_large = n_large;
+            f.task_cap = left.task_cap;
             f.a_start = ma.start;
             f.b_start = mb.start;
             f.a_rec = ma.rec;
@@ -1945,10 +2007,10 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         room = hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20);
         col = ws.get<int32_t>((size_t)room);
         val = ws.get<float>((size_t)room);
-        live = ws.get<int32_t>(2);
+        live = ws.get<int32_t>(3);
         if (ws.failed) return TSP_ERR_ALLOC_FAILED;
         kind = FillKind{(FillKind::Sum)hint.sum, hint.scale};
-        expected = Expected{room, n_heavy, n_tasks, kind};
+        expected = Expected{room, n_heavy, n_tasks, n_large, kind};
     }
     rc = size_rows(false);
     if (rc) return rc;

@@ -341,6 +341,28 @@ def test_pieces_of_heavy_rows_dealt_to_waves(tsp, oracle, values, cols, entries)
         h.close()
 
 
+@pytest.mark.parametrize("values", ["ones", "below one"])
+@pytest.mark.parametrize("cols,large", [(6000, 256), (70001, 512)])
+def test_large_and_light_rows(tsp, oracle, values, cols, large):
+    """Rows of A around the number of products from which a row is large; products in turn on one handle whose operands have
+    equal sizes and more large rows, fewer and none, so that what the last one left does not fit."""
+    rng = np.random.default_rng(cols)
+    make = lambda m: _VALUES[values](rng, m)
+    B = _exact_lengths(rng, cols, np.full(1100, 64), make)
+    total, all_of = 300 * (large - 1), []
+    for many in (0, 1, 40, 7, 299):
+        lengths = np.full(300, large - 1)
+        lengths[rng.choice(300, many, replace=False)] = large
+        lengths[np.argmin(lengths)] -= lengths.sum() - total
+        all_of.append(_exact_lengths(rng, 1100, np.maximum(lengths, 0), make))
+    h = tsp.Handle()
+    try:
+        for i in (0, 1, 2, 3, 0, 2, 4):
+            _check(h, tsp, oracle, all_of[i], B)
+    finally:
+        h.close()
+
+
 def test_values_that_integers_do_not_hold_by_tiles(tsp, oracle):
     """A product that is faster by rows while its sums are integers and by tiles otherwise."""
     rng = np.random.default_rng(4)
