@@ -28,7 +28,7 @@ constexpr int64_t kFinishRows = 1 << 21; // rows of which k_row_finish makes row
 constexpr int kChunkTileRows = 128, kChunkRows = kChunkTileRows * T;   // rows whose row_ptr one block writes
 constexpr int kPlanSums = 8;
 constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
-constexpr int kSpanWindows = 64;         // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
+constexpr int kSpanWindowsLog = 6, kSpanWindows = 1 << kSpanWindowsLog;   // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
 constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows, those of very long rows of A at any
 constexpr int kCountThreads = 256;       // of k_heavy_count
 constexpr int32_t kNoCol = 0x7FFFFFFF;
@@ -73,7 +73,9 @@ struct PrepareArgs {
     int windows;                         // of columns of C, for the heavy rows
     int32_t *heavy;                      // rows that are not small
     // {row, index into heavy, first window, one past the last window}; of rows of large_products and more from the front on,
-    // of the others from the back
+    // of the others from the back.  (The tile-rows of the longest rows are done last, so that the kernels take the large tasks
+    // from the last one on: R-MAT scale 14 sizing and multiplication of the large rows 49 + 94 -> 35 + 66 us, scale 18
+    // 3.8 + 10.3 -> 3.4 + 9.8 ms.)
     int4 *tasks;
     int large_products;
     int64_t heavy_cap, task_cap;
@@ -816,62 +818,79 @@ __global__ __launch_bounds__(256) void k_small_copy(const CopyArgs a) {
 
 // ---- heavy rows -------------------------------------------------------------------------------------------------
 // B for the heavy rows, L lanes per row.  For the multiplication: 4 bytes per entry {low 16 bits of the column, fp16
-// value}, and where every row of B enters every window of columns.  For the sizing: the columns of a row as words of 32
-// {index of the word, its bits}, at the position of the row's first entry (on a power-law graph, weighted by use, two
-// columns share a word).
+// value}, and where every row of B enters every window of columns.  For the sizing: the columns of a row as words of 16
+// {low 16 bits of the word's index, its bits << 16}, at the position of the row's first entry, and where every row enters
+// every span of kSpanWindows windows.  (Words of 32 columns in 8 bytes are 0.47 to a product on a power-law graph, weighted by
+// use, words of 16 in 4 bytes 0.58: 3.7 and 2.3 bytes.)
 struct PackArgs {
     int64_t rows;
     const int32_t *start;
     const int2 *rec;
     uint32_t *pack;                      // (the low five bits of the column inverted: a shift by them brings the column's bit to the top)
-    uint2 *word;
+    uint32_t *word;
     int32_t *words;                      // per row
     int32_t *table;                      // [rows][windows + 1], or null for one window
-    int windows, shift;                  // a window is 1 << shift columns
+    int32_t *span_table;                 // [rows][spans + 1], or null for one span
+    int windows, spans, shift;           // a window is 1 << shift columns
 };
 template <int L>
 __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
+    // (trips in flight: the longest row of an R-MAT graph of scale 18, 25,000 entries, kept the launch waiting for 240 us)
+    constexpr int kTrips = L == 64 ? 4 : 2;
     const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L;
-    const int l = threadIdx.x % L, lane = lane_id();
+    const int l = threadIdx.x % L, lane = lane_id(), span_shift = a.shift + kSpanWindowsLog;
     int32_t s = 0, e = 0;
     if (row < a.rows) {
         s = a.start[row];
         e = max(s, a.start[row + 1]);
     }
     int32_t *tab = a.table && row < a.rows ? a.table + row * (a.windows + 1) : nullptr;
+    int32_t *span_tab = a.span_table && row < a.rows ? a.span_table + row * (a.spans + 1) : nullptr;
     int32_t at = s;
-    for (int32_t k0 = s; __any(k0 < e); k0 += L) {
-        const int32_t k = k0 + l;
-        // A word's bits are the difference of the running sum of the bits (all distinct, so that carries cancel) at the two
-        // ends of its stretch; a word that goes on in the next trip is listed twice.
-        bool leads = false;
-        uint32_t bit = 0;
-        int32_t word = 0;
-        if (k < e) {
-            const int2 x = a.rec[k];
-            const int32_t before = k > s ? a.rec[k - 1].x : -1;
-            const _Float16 v = (_Float16)__uint_as_float((uint32_t)x.y);
-            a.pack[k] = (((uint32_t)x.x ^ 31u) & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
-            if (tab)
-                for (int w = (before >> a.shift) + 1; w <= (x.x >> a.shift) && w <= a.windows; ++w) tab[w] = k;
-            word = x.x >> 5;
-            bit = 1u << (x.x & 31);
-            leads = l == 0 || before < 0 || (before >> 5) != word;
+    for (int32_t base = s; __any(base < e); base += L * kTrips) {
+        int2 xs[kTrips];
+        int32_t befores[kTrips];
+#pragma unroll
+        for (int u = 0; u < kTrips; ++u) {
+            const int32_t k = max(min(base + u * L + l, e - 1), 0);
+            xs[u] = a.rec[k];
+            befores[u] = a.rec[max(k - 1, 0)].x;
         }
-        const unsigned long long all = __ballot(leads), live = __ballot(k < e);
-        const uint32_t sum = wave_inclusive_scan(bit);
-        const int start = 63 - __clzll((long long)(all & ((2ull << lane) - 1ull)));
-        const uint32_t before_start = (uint32_t)__shfl((int)(sum - bit), max(start, 0), 64);
-        const unsigned long long mine = L == 64 ? all : (all >> (lane & ~(L - 1))) & ((1ull << (L & 63)) - 1ull);
-        if (k < e && (l == L - 1 || !((live >> (lane + 1)) & 1ull) || ((all >> (lane + 1)) & 1ull)))
-            a.word[at + __popcll(mine & ((2ull << l) - 1ull)) - 1] = make_uint2((uint32_t)word, sum - before_start);
-        at += __popcll(mine);
+#pragma unroll
+        for (int u = 0; u < kTrips; ++u) {
+            const int32_t k0 = base + u * L, k = k0 + l;
+            if (!__any(k0 < e)) break;
+            // A word's bits are the difference of the running sum of the bits (all distinct, so that carries cancel) at the two
+            // ends of its stretch; a word that goes on in the next trip is listed twice.
+            const int2 x = xs[u];
+            const int32_t before = k > s ? befores[u] : -1, word = x.x >> 4;
+            const uint32_t bit = k < e ? 1u << (x.x & 15) : 0u;
+            const bool leads = k < e && (l == 0 || before < 0 || (before >> 4) != word);
+            if (k < e) {
+                const _Float16 v = (_Float16)__uint_as_float((uint32_t)x.y);
+                a.pack[k] = (((uint32_t)x.x ^ 31u) & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
+                if (tab)
+                    for (int w = (before >> a.shift) + 1; w <= (x.x >> a.shift) && w <= a.windows; ++w) tab[w] = k;
+            }
+            const unsigned long long all = __ballot(leads), live = __ballot(k < e);
+            const uint32_t sum = wave_inclusive_scan(bit);
+            const int start = 63 - __clzll((long long)(all & ((2ull << lane) - 1ull)));
+            const uint32_t before_start = (uint32_t)__shfl((int)(sum - bit), max(start, 0), 64);
+            const unsigned long long mine = L == 64 ? all : (all >> (lane & ~(L - 1))) & ((1ull << (L & 63)) - 1ull);
+            const int32_t place = at + __popcll(mine & ((2ull << l) - 1ull)) - 1;
+            if (k < e && (l == L - 1 || !((live >> (lane + 1)) & 1ull) || ((all >> (lane + 1)) & 1ull)))
+                a.word[place] = ((uint32_t)word & 0xFFFFu) | (sum - before_start) << 16;
+            if (span_tab && k < e)
+                for (int w = (before >> span_shift) + 1; w <= (x.x >> span_shift) && w <= a.spans; ++w) span_tab[w] = place;
+            at += __popcll(mine);
+        }
     }
     if (row < a.rows && l == 0) a.words[row] = at - s;
-    if (tab) {
-        const int last = e > s ? min(a.rec[e - 1].x >> a.shift, a.windows - 1) : -1;
-        for (int w = last + 1 + l; w <= a.windows; w += L) tab[w] = e;
-    }
+    const int32_t last_column = e > s && (tab || span_tab) ? a.rec[e - 1].x : -1;
+    if (tab)
+        for (int w = (last_column < 0 ? -1 : min(last_column >> a.shift, a.windows - 1)) + 1 + l; w <= a.windows; w += L) tab[w] = e;
+    if (span_tab)
+        for (int w = (last_column < 0 ? -1 : min(last_column >> span_shift, a.spans - 1)) + 1 + l; w <= a.spans; w += L) span_tab[w] = at;
 }
 
 // 64 pieces of up to 16 elements of B, four to a step: lane 16 q + t describes piece 4 t + q by the byte offset of its first
@@ -1005,78 +1024,123 @@ struct CountArgs {
     const int64_t *d_scalars;
     const int32_t *a_start, *b_start;
     const int2 *a_rec;
-    const uint2 *b_word;
+    const uint32_t *b_word;
     const int32_t *b_words;
+    const int32_t *b_spans;              // k_heavy_pack's span_table
+    int32_t b_nnz;
     int windows;                         // of kWin columns each
+    int spans;
     int span_windows;                    // windows whose bits the block's LDS holds
     int32_t *row_nnz;                    // null: only the pattern is wanted
     uint32_t *group_len;
     uint32_t *offset;                    // [heavy][windows] entries of the row before each window
     int heavy_from;                      // the rows of this launch begin here
     uint32_t *bits;                      // [heavy - heavy_from][windows][kWin / 32]; or null
+    // The launch for the large rows goes by the first of the tasks that each has in the list of k_heavy_fill, the other one by
+    // `heavy`; that leaves out rows of so many products (0: none).
+    const int4 *tasks;
+    int64_t n_large;
+    const int32_t *ub;
+    int large_products;
 };
 
 // A block per heavy row ORs the words of the rows of B behind it into one bit per column in LDS; OR is free of order, so
-// the row may be spread over the block: entry i of the row of A goes to wave i mod the number of waves that get 16 and more.
-// Four waves: light rows are bound by the block's own steps (a graph's 4100 rows of 165 entries 114 -> 103 us for the whole
-// product with 8 -> 4 waves), heavy ones by the words they stream (R-MAT scale 14, 680 -> 660; scale 18, no difference: 26.8 GB
-// past the L2 caches and 5.3 GB of pattern in 5.5 ms, 5.8 TB/s where a large copy reaches 5; vector ALUs busy 25 %, LDS 34 %).
-template <int kWin>
-__global__ __launch_bounds__(kCountThreads) void k_heavy_count(const CountArgs a) {
+// the row may be spread over the block: by pieces of 16 words where every thread has at most one entry of A, else entry i of
+// the row of A goes to wave i mod the number of waves that get 16 and more.
+// Large rows have blocks of 1024 threads, the others, which are bound by the block's own steps, of 256.  All rows by 256
+// threads: R-MAT scale 14 88 us, split 33 + 28; scale 18 5.3 ms, split 3.4 + 1.5.  No more than 80 scalar registers: with the
+// 106 that the compiler takes otherwise a SIMD has 7 waves, and a CU one block of 1024 threads (4.6 instead of 3.9 ms).
+// Bound by round trips to the words: with all words from 2 MB 2.75 instead of 3.7 ms, without the LDS additions no less, with
+// words of half the bytes, or twice as many in flight, no less either.
+template <int kWin, int kThreads, bool kLargeRows>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_heavy_count(const CountArgs a) {
     extern __shared__ __align__(16) uint32_t bits[];
-    constexpr int kWaves = kCountThreads / 64;
-    __shared__ uint32_t s_mark[kWaves][64];
+    constexpr int kWaves = kThreads / 64;
+    __shared__ union {
+        uint32_t mark[kWaves][64];
+        SegmentList<kThreads> segment;
+    } s_list;
+    __shared__ int s_total[kWaves];
     __shared__ uint32_t s_cnt[kSpanWindows];
     __shared__ uint32_t s_run;
     constexpr int kWords = kWin / 32, kPerLane = kWords / 64;
-    const int64_t h = a.heavy_from + (int64_t)blockIdx.x;
+    int64_t h;
+    int32_t row;
     // (the lists of a product whose numbers the host does not have yet may be shorter than the launch)
-    if (h >= a.heavy_cap || (a.d_scalars && h >= a.d_scalars[S_ROW_LISTS] >> 36)) return;
-    const int32_t row = a.heavy[h];
-    const int32_t s = a.a_start[row], e = a.a_start[row + 1];
+    if constexpr (kLargeRows) {
+        const int64_t t = min(a.n_large, uniform_load(a.d_scalars + S_ROW_LARGE_TASKS)) - 1 - (int64_t)blockIdx.x;
+        if (t < 0) return;
+        const int4 task = a.tasks[t];
+        if (task.z != 0) return;
+        row = __builtin_amdgcn_readfirstlane(task.x);
+        h = __builtin_amdgcn_readfirstlane(task.y);
+        if (h >= a.heavy_cap) return;
+    } else {
+        h = a.heavy_from + (int64_t)blockIdx.x;
+        if (h >= a.heavy_cap || (a.d_scalars && h >= uniform_load(a.d_scalars + S_ROW_LISTS) >> 36)) return;
+        row = uniform_load(a.heavy + h);
+        if (a.large_products > 0 && uniform_load(a.ub + row) >= a.large_products) return;
+    }
+    const int32_t s = uniform_load(a.a_start + row), e = uniform_load(a.a_start + row + 1);
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    for (int w = threadIdx.x; w < a.span_windows * kWords + 64; w += kCountThreads) bits[w] = 0;
+    for (int w = threadIdx.x; w < a.span_windows * kWords + 64; w += kThreads) bits[w] = 0;
     if (threadIdx.x == 0) s_run = 0;
+    const bool even = e - s <= kThreads;
     const int dealt = min(kWaves, (e - s + 15) / 16);
     for (int w0 = 0; w0 < a.windows; w0 += a.span_windows) {
         const int w1 = min(w0 + a.span_windows, a.windows);
-        const uint32_t first = (uint32_t)w0 * kWords, words = (uint32_t)(w1 - w0) * kWords;
-        __syncthreads();
-        for (int32_t base = s; base < e && wave < dealt; base += 64 * dealt) {
-            const int32_t k = base + lane * dealt + wave;
-            int32_t p = 0, len = 0;
-            if (k < e) {
-                const int32_t c = a.a_rec[k].x;
-                p = a.b_start[c];
-                len = a.b_words[c];
+        const uint32_t words = (uint32_t)(w1 - w0) * kWords;
+        auto segment = [&](int32_t k, int32_t *len) {        // of entry k of A
+            const int32_t c = a.a_rec[k].x;
+            if (a.b_spans) {
+                const int32_t *ends = a.b_spans + ((int64_t)c * (a.spans + 1) + w0 / kSpanWindows);
+                const int32_t p = max(ends[0], 0);           // (in bounds whatever an operand that was not validated holds)
+                *len = min(ends[1], a.b_nnz) - p;
+                return p;
             }
-            if (a.windows > a.span_windows) {                // the stretch of the row's words inside the span
-                int32_t lo[2];
-                for (int side = 0; side < 2; ++side) {
-                    const uint32_t bound = first + (side ? words : 0u);
-                    int32_t x = 0, y = len;
-                    while (x < y) {
-                        const int32_t mid = (x + y) >> 1;
-                        if (a.b_word[p + mid].x < bound) x = mid + 1;
-                        else y = mid;
-                    }
-                    lo[side] = x;
-                }
-                p += lo[0];
-                len = lo[1] - lo[0];
-            }
-            stream_pieces<16, uint2>(p, len, 0u, a.b_word, s_mark[wave], [&](const auto &x, const auto &d, uint32_t l) {
-                // (lanes without an element, and words an operand that was not validated may hold out of order, go to
-                // words behind the bits that nothing reads)
+            *len = a.b_words[c];
+            return a.b_start[c];
+        };
+        const uint32_t nothing = ((uint32_t)a.span_windows * kWords + lane) * 4;       // (for lanes without an element)
+        auto use = [&](const auto &x, const auto &d, uint32_t l) {
+            // (inside the bits whatever the operand holds: k_row_prepare leaves no column beyond B's, and a block has room for
+            // all kSpanWindows windows where there are more of them)
 #pragma unroll
-                for (size_t u = 0; u < sizeof(x) / sizeof(x[0]); ++u) {
-                    const uint32_t at = x[u].x - first;
-                    atomicOr(&bits[l < d[u] >> 16 && at < words ? at : words + lane], x[u].y);
-                }
-            });
+            for (size_t u = 0; u < sizeof(x) / sizeof(x[0]); ++u) {
+                const uint32_t byte = (x[u] & (uint32_t)(kSpanWindows * kWords * 2 - 2)) << 1, half = x[u] << 4;
+                const uint32_t columns = (x[u] >> 16) << (half & 31u);
+                atomicOr(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(bits) + (l < d[u] >> 16 ? byte : nothing)), columns);
+            }
+        };
+        if (even) {
+            // (of a row of B of more than 65,535 words the rest is a segment for the same thread's next turn)
+            int32_t p = 0, len = 0;
+            const int32_t k = s + (int32_t)threadIdx.x;
+            if (k < e) p = segment(k, &len);
+            do {
+                const int32_t now = min(max(len, 0), 0xFFFF);
+                const int pieces = (now + 15) / 16, inc = (int)wave_inclusive_scan((uint32_t)pieces);
+                if (lane == 63) s_total[wave] = inc;
+                __syncthreads();
+                const int to = row16_inclusive_scan(lane % 16 < kWaves ? s_total[lane % 16] : 0);
+                s_list.segment.first[threadIdx.x] = inc - pieces + (wave > 0 ? __builtin_amdgcn_readlane(to, wave - 1) : 0);
+                s_list.segment.at[threadIdx.x] = make_uint2((uint32_t)p, (uint32_t)now << 16);
+                __syncthreads();
+                stream_share<kThreads>(s_list.segment, e - s, __builtin_amdgcn_readlane(to, kWaves - 1), a.b_word, use);
+                p += now;
+                len -= now;
+            } while (__syncthreads_or(len > 0));
+        } else {
+            __syncthreads();
+            for (int32_t base = s; base < e && wave < dealt; base += 64 * dealt) {
+                const int32_t k = base + lane * dealt + wave;
+                int32_t p = 0, len = 0;
+                if (k < e) p = segment(k, &len);
+                stream_pieces<16, uint32_t>(p, len, 0u, a.b_word, s_list.mark[wave], use);
+            }
         }
         __syncthreads();
-        for (int w = wave; w < w1 - w0; w += kCountThreads / 64) {
+        for (int w = wave; w < w1 - w0; w += kWaves) {
             uint32_t n = 0, word[kPerLane];
 #pragma unroll
             for (int i = 0; i < kPerLane; ++i) {
@@ -1191,6 +1255,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
         t -= a.large ? n_large : 0;
         if (!a.light || t >= n_light) return;
         t += a.task_cap - n_light;
+    } else {
+        t = n_large - 1 - t;                                   // (see there)
     }
     const int32_t row = uniform_load(&a.tasks[t].x), heavy = uniform_load(&a.tasks[t].y);
     int w = uniform_load(&a.tasks[t].z);
@@ -1860,15 +1926,23 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     int64_t bit_rows = 0;                    // rows whose pattern `bits` holds
     bool pattern_kept = false;               // ... and the sizing pass has left that of all heavy rows there
     CountArgs c{};
-    auto count_heavy = [&](int64_t rows) {
+    auto count_heavy = [&](int64_t rows, int64_t large) {    // the large ones apart from the others, or all of them alike
         const size_t lds = ((size_t)c.span_windows << (shift - 3)) + 256;
-        auto kernel = shift == 11 ? k_heavy_count<2048> : k_heavy_count<4096>;
+        c.n_large = large;
+        c.large_products = large > 0 ? left.large_products : 0;
+        if (large > 0) {
+            auto kernel = shift == 11 ? k_heavy_count<2048, 1024, true> : k_heavy_count<4096, 1024, true>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)large), dim3(1024), lds, s, c);
+        }
+        auto kernel = shift == 11 ? k_heavy_count<2048, kCountThreads, false> : k_heavy_count<4096, kCountThreads, false>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(kCountThreads), lds, s, c);
     };
     // heavy rows whose pattern is kept at a time
     auto pattern_rows = [&](int64_t heavy) { return std::min(heavy, std::max<int64_t>(ctx->pattern_bytes / (((int64_t)windows << shift) / 8), 1)); };
     int32_t *table = nullptr, *words = nullptr;
-    uint2 *word = nullptr;
+    uint32_t *word = nullptr;
+    int32_t *span_table = nullptr;
+    const int spans = (windows + kSpanWindows - 1) / kSpanWindows;
     SmallArgs m{};
     m.shape = shape;
     m.rows = A->rows;
@@ -1890,7 +1964,8 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         if (n_heavy == 0) return (int)TSP_OK;
         if (!pack) {
             pack = ws.get<uint32_t>((size_t)B->nnz + 64);     // (a piece is read whole)
-            word = ws.get<uint2>((size_t)B->nnz + 64);
+            word = ws.get<uint32_t>((size_t)B->nnz + 64);
+            if (spans > 1) span_table = ws.get<int32_t>((size_t)B->rows * (spans + 1));
             words = ws.get<int32_t>((size_t)B->rows);
             if (windows > 1) table = ws.get<int32_t>((size_t)B->rows * (windows + 1));
         }
@@ -1924,7 +1999,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hipLaunchKernelGGL(kernel, dim3(small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums,
                            finish_too ? finish_args() : FinishArgs{});
         if (n_heavy > 0) {
-            PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, windows, shift};
+            PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, span_table, windows, spans, shift};
             if (B->nnz > 16 * B->rows)
                 hipLaunchKernelGGL(k_heavy_pack<64>, dim3((unsigned)((B->rows * 64 + 255) / 256)), dim3(256), 0, s, p);
             else
@@ -1937,6 +2012,9 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             c.a_rec = ma.rec;
             c.b_word = word;
             c.b_words = words;
+            c.b_spans = span_table;
+            c.b_nnz = (int32_t)B->nnz;
+            c.spans = spans;
             c.windows = windows;
             c.span_windows = std::min(windows, kSpanWindows);
             c.row_nnz = row_nnz;
@@ -1944,7 +2022,9 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             c.offset = offset;
             pattern_kept = bit_rows == n_heavy;
             c.bits = pattern_kept ? bits : nullptr;
-            count_heavy(n_heavy);
+            c.tasks = left.tasks;
+            c.ub = left.ub;
+            count_heavy(n_heavy, n_large);
         }
         return (int)TSP_OK;
     };
@@ -1987,7 +2067,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
                     c.heavy_cap = f.heavy_to;
                     c.heavy_from = f.heavy_from;
                     c.bits = bits;
-                    count_heavy(f.heavy_to - f.heavy_from);
+                    count_heavy(f.heavy_to - f.heavy_from, 0);
                 }
                 launch_fill(f, how, B->nnz <= 16 * B->rows, s);
             }
@@ -2023,7 +2103,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     if (!rc && ahead) rc = multiply(had_small, kind);
     if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);           // the wait that sizes C
     if (rc) return rc;
-    const int64_t had_heavy = n_heavy, had_tasks = n_tasks, products = ctx->h_scalars[S_PRODUCTS];
+    const int64_t had_heavy = n_heavy, had_tasks = n_tasks, had_large = n_large, products = ctx->h_scalars[S_PRODUCTS];
     rc = sizes_known();
     if (rc) return rc;
     if (hint.tiles || other_lanes) {         // another matrix of the same sizes: as it would be done if it had come first
@@ -2033,7 +2113,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     const bool done = ahead && expected.holds(ctx->h_scalars) && (had_small || ctx->h_scalars[S_ROW_SMALL] == 0);
     if (!done) {
         live = nullptr;
-        if (n_heavy > had_heavy || n_tasks > had_tasks) {            // another matrix of the same sizes, with more work in it
+        if (n_heavy > had_heavy || n_tasks > had_tasks || n_large > had_large) {            // another matrix of the same sizes, with more work in it
             ctx->scalars_clean = finish_too = false;
             rc = size_rows(true);
             if (rc) return rc;

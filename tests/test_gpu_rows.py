@@ -341,6 +341,29 @@ def test_pieces_of_heavy_rows_dealt_to_waves(tsp, oracle, values, cols, entries)
         h.close()
 
 
+@pytest.mark.parametrize("cols", [70016, 262144, 262145, 600000])
+def test_words_of_16_columns(tsp, oracle, cols):
+    """Rows of B of runs of columns that begin and end at the edges of words (16 columns), of places (32), of trips of the lanes
+    that make the words (64 and 16 entries) and of spans (262,144 columns), and one of more words than a segment takes."""
+    rng = np.random.default_rng(cols)
+    edges = np.array([0, 15, 16, 31, 32, 4095, 4096, 65535, 65536, cols // 2, cols - 700, 262143 % cols, 262130 % cols])
+    rows = []
+    for i in range(600):
+        start = edges[rng.integers(0, len(edges), 3)] - rng.integers(0, 3, 3)
+        rows.append(np.unique(np.clip(np.concatenate([a + np.arange(n) for a, n in zip(start, rng.choice([1, 15, 16, 17, 33, 64, 65, 250], 3))]), 0, cols - 1)))
+    rows[77] = np.arange(0, cols, 3)
+    if cols < 100000:                            # (16 lanes per row where the mean row is short)
+        rows = [r[:rng.integers(1, 24)] if i != 77 else r[:2000] for i, r in enumerate(rows)]
+    r = np.repeat(np.arange(600), [len(x) for x in rows])
+    B = inputs.from_coo(600, cols, r, np.concatenate(rows), rng.choice([-1.0, 1.0], len(r)), "runs of columns")
+    A = _exact_lengths(rng, 600, rng.choice([1, 17, 40, 300], 300), lambda m: rng.choice([-1.0, 1.0], m))
+    h = tsp.Handle()
+    try:
+        _check(h, tsp, oracle, A, B)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("values", ["ones", "below one"])
 @pytest.mark.parametrize("cols,large", [(6000, 256), (70001, 512)])
 def test_large_and_light_rows(tsp, oracle, values, cols, large):
