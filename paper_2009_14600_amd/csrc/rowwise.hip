@@ -32,6 +32,7 @@ constexpr int kSpanWindowsLog = 6, kSpanWindows = 1 << kSpanWindowsLog;   // win
 constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows, those of very long rows of A at any
 constexpr int kCountThreads = 256;       // of k_heavy_count
 constexpr int32_t kNoCol = 0x7FFFFFFF;
+constexpr int kLongRow = 512;            // entries, for the threads that k_row_prepare gives a tile-row
 constexpr int64_t kFoundEntries = (int64_t)2 << 30;   // of the small rows before they are moved into C, at most
 // Intermediate products behind one task of k_heavy_fill (a row, or some of its windows), and entries of the row of A times
 // windows: every step of a task goes through all entries, however few of them have anything in its windows.  (A row of 45,000
@@ -118,8 +119,8 @@ __device__ __forceinline__ bool small_row(int32_t entries, int32_t products, int
 // atomic returns the word before): those lanes list the tile.  At the end a lane per row of A says whether the row is
 // small or heavy and lists the heavy one with its tasks.
 template <int kTeam, int kU, typename RP, typename VT>
-__global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a) {
-    constexpr int kTeams = 256 / kTeam;
+__global__ __launch_bounds__(kTeam > 256 ? kTeam : 256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_prepare(const PrepareArgs<RP, VT> a) {
+    constexpr int kTeams = kTeam > 256 ? 1 : 256 / kTeam;
     if (a.skip && uniform_load(a.skip)) return;
     extern __shared__ uint32_t lds_bitmap[];
     __shared__ int32_t s_ptr[kTeams][T + 1];
@@ -160,9 +161,9 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
         const int32_t e0 = s_ptr[team][0], e1 = s_ptr[team][T];
         int32_t listed = 0;
         ValueRange range;
-        for (int32_t base = e0 + (tid & ~63); base < e1; base += kTeam * kU) {
-            int32_t c[kU], prev[kU], len[kU];
-            VT v[kU];
+        int32_t c[kU], prev[kU];
+        VT v[kU];
+        auto request = [&](int32_t base) {
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const int32_t k = min(base + u * kTeam + lane, e1 - 1);
@@ -170,6 +171,15 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                 prev[u] = a.col[max(k - 1, 0)];
                 v[u] = a.val[k];
             }
+        };
+        int32_t base = e0 + (tid & ~63);
+        if (base < e1) request(base);
+        for (; base < e1; base += kTeam * kU) {
+            // (every part for all entries in flight before the next part: look-ups and additions to LDS one behind the other
+            // made a trip of a long tile-row twice as long)
+            int32_t len[kU];
+            int r[kU];
+            bool first[kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 bad = bad || (uint32_t)c[u] >= (uint64_t)a.cols;
@@ -189,47 +199,71 @@ __global__ __launch_bounds__(256) void k_row_prepare(const PrepareArgs<RP, VT> a
                 }
             }
 #pragma unroll
+            for (int u = 0; u < kU; ++u) r[u] = 0;
+#pragma unroll
+            for (int step = T / 2; step >= 1; step >>= 1)
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+                    if (s_ptr[team][r[u] + step] <= base + u * kTeam + lane) r[u] += step;
+#pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const int32_t k = base + u * kTeam + lane;
-                if (base + u * kTeam >= e1) break;                   // (the whole wave)
-                const bool on = k < e1;
-                int r = T;
-                bool starts = false;
+                const bool on = k < e1, starts = k == s_ptr[team][r[u]];
+                bad = bad || (on && !starts && prev[u] >= c[u]);
                 if (on) {
-                    r = 0;
-#pragma unroll
-                    for (int step = T / 2; step >= 1; step >>= 1)
-                        if (s_ptr[team][r + step] <= k) r += step;
-                    starts = k == s_ptr[team][r];
-                    bad = bad || (!starts && prev[u] >= c[u]);
                     const uint32_t bits = half_bits(v[u]);
                     a.out.rec[k] = make_int2(c[u], (int)__float_as_uint((float)__builtin_bit_cast(_Float16, (uint16_t)bits)));
                     range.take(bits);
                 }
+                first[u] = on && (starts || (prev[u] >> 4) != (c[u] >> 4));
+            }
+            uint32_t had[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
                 const int32_t t = c[u] >> 4;
-                bool first = on && (starts || (prev[u] >> 4) != t);
-                if (first) {
-                    const uint32_t bit = 1u << (t & 31);
-                    first = !(atomicOr(&bitmap[t >> 5], bit) & bit);
-                }
-                const unsigned long long firsts = __ballot(first);
-                int32_t at = listed;
-                if constexpr (kTeam == 64) {
-                    listed += __popcll(firsts);
-                } else if (firsts) {
-                    if (lane == 0) at = atomicAdd(&s_count[team], __popcll(firsts));
-                    at = __builtin_amdgcn_readfirstlane(at);
-                }
-                if (first) a.out.tile_col[e0 + at + __popcll(firsts & ((1ull << lane) - 1ull))] = t;
-                if (a.ub && kTeam == 64) {
-                    if (on) atomicAdd(&s_ub[team][r], (unsigned long long)(uint32_t)len[u]);    // (rows of few entries)
-                } else if (a.ub) {
-                    // products per row: differences of the running sum at the ends of the rows' stretches in this wave
+                had[u] = first[u] ? atomicOr(&bitmap[t >> 5], 1u << (t & 31)) : 0u;
+            }
+            int32_t tile[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                tile[u] = c[u] >> 4;
+                first[u] = first[u] && !((had[u] >> (tile[u] & 31)) & 1u);
+            }
+            const int32_t next = base + kTeam * kU;
+            if (next < e1) request(next);
+            int32_t at = listed, found = 0;
+            unsigned long long firsts[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                firsts[u] = __ballot(first[u]);
+                found += __popcll(firsts[u]);
+            }
+            if constexpr (kTeam == 64) {
+                listed += found;
+            } else if (found) {
+                if (lane == 0) at = atomicAdd(&s_count[team], found);
+                at = __builtin_amdgcn_readfirstlane(at);
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                if (first[u]) a.out.tile_col[e0 + at + __popcll(firsts[u] & ((1ull << lane) - 1ull))] = tile[u];
+                at += __popcll(firsts[u]);
+            }
+            if (a.ub && kTeam == 64) {
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+                    if (base + u * kTeam + lane < e1) atomicAdd(&s_ub[team][r[u]], (unsigned long long)(uint32_t)len[u]);    // (rows of few entries)
+            } else if (a.ub) {
+                // products per row: differences of the running sum at the ends of the rows' stretches in this wave
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    if (base + u * kTeam >= e1) break;               // (the whole wave)
+                    const bool on = base + u * kTeam + lane < e1;
                     const uint32_t mine = on ? (uint32_t)len[u] : 0u, inc = wave_inclusive_scan(mine);
-                    const int r_next = __shfl_down(r, 1, 64), r_prev = __shfl_up(r, 1, 64);
-                    if (on && (lane == 63 || r_next != r)) atomicAdd(&s_ub[team][r], (unsigned long long)inc);
-                    if (on && lane > 0 && r_prev != r)
-                        atomicAdd(&s_ub[team][r], (unsigned long long)0 - (unsigned long long)(inc - mine));
+                    const int r_next = __shfl_down(r[u], 1, 64), r_prev = __shfl_up(r[u], 1, 64);
+                    if (on && (lane == 63 || r_next != r[u] || base + u * kTeam + lane == e1 - 1)) atomicAdd(&s_ub[team][r[u]], (unsigned long long)inc);
+                    if (on && lane > 0 && r_prev != r[u])
+                        atomicAdd(&s_ub[team][r[u]], (unsigned long long)0 - (unsigned long long)(inc - mine));
                 }
             }
         }
@@ -1500,7 +1534,7 @@ constexpr int kSampleEntries = 4096;     // ... and entries of each, at most
 bool sample_pays(int64_t rows, int64_t nnz) { return nnz >= (1 << 18) && nnz > 8 * rows; }
 
 template <typename RP, typename VT>
-void launch_prepare(const PrepareArgs<RP, VT> &a, hipStream_t s) {
+void launch_prepare(const PrepareArgs<RP, VT> &a, bool long_rows, hipStream_t s) {
     const int64_t tile_rows = (a.rows + T - 1) / T;
     if (tile_rows == 0) return;
     // A wave per tile-row of up to two trips; longer ones get a block, four entries per thread in flight (the hub rows of
@@ -1508,9 +1542,15 @@ void launch_prepare(const PrepareArgs<RP, VT> &a, hipStream_t s) {
     if (a.nnz <= 128 * tile_rows && (size_t)a.bitmap_words * 16 <= 60 * 1024)
         hipLaunchKernelGGL((k_row_prepare<64, 2, RP, VT>), dim3((unsigned)((tile_rows + 3) / 4)), dim3(256),
                            (size_t)a.bitmap_words * 16, s, a);
-    else
-        hipLaunchKernelGGL((k_row_prepare<256, 4, RP, VT>), dim3((unsigned)tile_rows), dim3(256),
-                           (size_t)a.bitmap_words * 4, s, a);
+    else {
+        auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)tile_rows), dim3(threads), (size_t)a.bitmap_words * 4, s, a); };
+        // The longest tile-row, 3 ns per entry with 256 threads, keeps the launch waiting, where the last product of these sizes
+        // had long rows: R-MAT scales 14 / 16 / 18 by 256 threads 64 / 197 / 515 us, by 512 43 / 120 / 345, by 1024 28 / 96 / 437.
+        // (Even rows, 80,000 of 12 entries: 20, 30, 38.)
+        if (!long_rows) launch(k_row_prepare<256, 4, RP, VT>, 256);
+        else if (tile_rows <= 4096) launch(k_row_prepare<1024, 2, RP, VT>, 1024);
+        else launch(k_row_prepare<512, 4, RP, VT>, 512);
+    }
 }
 
 // What k_row_prepare needs beyond the operand, for A (null members for B)
@@ -1524,6 +1564,7 @@ struct LeftOperand {
     int32_t *heavy;
     int4 *tasks;
     int large_products;
+    bool long_rows;                      // by the last product of these sizes
     int64_t heavy_cap, task_cap;
 };
 
@@ -1560,7 +1601,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
         }
         a.d_scalars = ctx->d_scalars;
         a.skip = skip;
-        launch_prepare(a, s);
+        launch_prepare(a, left && left->long_rows, s);
     };
     const bool f16 = M->val_type == TSP_F16;
     if (M->row_ptr_type == TSP_I32) f16 ? run(int32_t{}, uint16_t{}) : run(int32_t{}, float{});
@@ -1774,6 +1815,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     left.B = B;
     left.shape = shape;
     left.windows = windows;
+    left.long_rows = known && hint.longest >= kLongRow;
     left.large_products = (int64_t)windows << shift <= kNarrowColumns ? kLargeNarrow : kLarge;
     unsigned long long *partial = ws.get<unsigned long long>((size_t)kPlanBlocks * kPlanSums);
     // (tasks of a product not seen before: one per heavy row and some more; where that is too few the lists are made again)
@@ -1893,6 +1935,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
         hint.large_tasks = n_large;
+        hint.longest = h[S_ROW_LONGEST];
         hint.small = h[S_ROW_SMALL] > 0;
         hint.nnz = row_ptr ? h[S_C_NNZ] : -1;
         hint.sum = kind.sum;

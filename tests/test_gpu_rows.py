@@ -341,6 +341,25 @@ def test_pieces_of_heavy_rows_dealt_to_waves(tsp, oracle, values, cols, entries)
         h.close()
 
 
+@pytest.mark.parametrize("rows,left", [(300, 20), (65600, 9)])
+def test_long_tile_rows_by_more_threads(tsp, oracle, rows, left):
+    """Rows of 512 entries and more among short ones, in few tile-rows and in many: from the second call on k_row_prepare has more
+    threads to a tile-row, whatever the operand at hand holds."""
+    rng = np.random.default_rng(rows)
+    ones = lambda m: rng.choice([-1.0, 1.0], m)
+    B = _exact_lengths(rng, 900, np.full(800, 3), ones)
+    lengths = np.full(rows, left)
+    lengths[[0, 33, 34, rows - 1]] = [512, 799, 800, 513]
+    even = np.full(rows, left)
+    even[: lengths.sum() - even.sum()] += 1                 # the same number of entries, no long row
+    h = tsp.Handle()
+    try:
+        for l in (lengths, even, lengths):
+            _check(h, tsp, oracle, _exact_lengths(rng, 800, l, ones), B, calls=3 if l is lengths else 1)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("cols", [70016, 262144, 262145, 600000])
 def test_words_of_16_columns(tsp, oracle, cols):
     """Rows of B of runs of columns that begin and end at the edges of words (16 columns), of places (32), of trips of the lanes
