@@ -369,8 +369,11 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
     uint32_t range_a = 0, range_b = 0;
     int longest = 0;
     const int64_t most = max(a.a_tile_rows, a.same ? (int64_t)0 : a.b_tile_rows);
-    for (int64_t base = (int64_t)block * 16; base < most; base += (int64_t)blocks * 16) {
-        const int64_t I = base + (threadIdx.x >> 4);
+    // (neighbours to different blocks, and of a block's tile-rows one to each wave first: the tile-rows of the hubs of a graph
+    // lie side by side, and one by one they kept the launch waiting for 290 us on R-MAT scale 18)
+    const int at = (threadIdx.x >> 6) + 4 * ((threadIdx.x >> 4) & 3);
+    for (int64_t base = block; base < most; base += (int64_t)blocks * 16) {
+        const int64_t I = base + (int64_t)at * blocks;
         if (r == 0 && I < a.b_tile_rows && !a.same) {
             tiles_b += (unsigned)a.b_ntiles[I];
             range_b = range_max(range_b, a.b_range[I]);
@@ -388,16 +391,20 @@ __device__ __forceinline__ void sum_tile_rows(const SumArgs &a, int block, int b
                 small += rows / 17u;
                 wide += rows % 17u;
             }
-            for (int32_t j = r; j < min(n, 64); j += 16) {
-                const int32_t K = a.a_tile_col[e0 + j];
-                if (K < a.b_tile_rows) cand += (unsigned)a.b_ntiles[K];
+            for (int32_t j = r; j < min(n, 128); j += 64) {
+                int32_t K[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) K[u] = a.a_tile_col[e0 + min(j + 16 * u, n - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j + 16 * u < n && K[u] < a.b_tile_rows) cand += (unsigned)a.b_ntiles[K[u]];
             }
         }
         // long tile-rows: the rest of their tiles by the whole wave
-        for (unsigned long long more = __ballot(r == 0 && n > 64); more; more &= more - 1) {
+        for (unsigned long long more = __ballot(r == 0 && n > 128); more; more &= more - 1) {
             const int from = __ffsll((long long)more) - 1;
             const int32_t first = __builtin_amdgcn_readlane(e0, from), count = __builtin_amdgcn_readlane(n, from);
-            for (int32_t j = 64 + lane; j < count; j += 256) {
+            for (int32_t j = 128 + lane; j < count; j += 256) {
                 int32_t K[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) K[u] = a.a_tile_col[first + min(j + 64 * u, count - 1)];
@@ -612,7 +619,11 @@ struct SmallArgs {
     uint32_t *group_len;                 // entries per 16 rows
     int2 *found;                         // [waves][wave_rows * products] entries {column, value} of a wave's rows, in order
     int32_t *wave_total;                 // ... and how many
-    int blocks;                          // of rows; the ones behind them sum (SumArgs)
+    // The blocks that sum (SumArgs) are the first ones of the launch where their groups of lanes have several tile-rows each, else
+    // the last ones, which fill what the rows leave of the chip: R-MAT scale 18 490 us behind the rows, 300 before them, A*P on a
+    // 64^3 grid 29 and 24; 65,536 rows of 8 random entries 44 and 47.
+    int sum_blocks;
+    bool sums_first;
     int finish;                          // the last block does the work of k_row_finish (FinishArgs; rows of one chunk)
 };
 
@@ -638,7 +649,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
     extern __shared__ __align__(16) unsigned char small_lds[];
     __shared__ uint32_t s_len[256 / G];
     const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
-    const uint32_t row = blockIdx.x * (256 / G) + threadIdx.x / G;
+    const uint32_t block = blockIdx.x - (a.sums_first ? (uint32_t)a.sum_blocks : 0u), row = block * (256 / G) + threadIdx.x / G;
     const int slots = a.shape.slots, most = a.shape.products;
     unsigned char *lds = small_lds + wave * a.wave_bytes;
     int32_t *table = reinterpret_cast<int32_t *>(lds) + (lane / G) * slots;
@@ -738,7 +749,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
     const uint32_t inc = wave_inclusive_scan(l == 0 ? (uint32_t)n : 0u);
     const int total = __builtin_amdgcn_readlane((int)inc, 63), longest_row = wave_max(n);
     const int off = __builtin_amdgcn_ds_bpermute(group_shift * 4, (int)inc) - n;       // of the row among the entries of the wave
-    int2 *found = a.found + (size_t)(blockIdx.x * 4 + wave) * (kRows * most);
+    int2 *found = a.found + (size_t)(block * 4 + wave) * (kRows * most);
     int2 *stage = reinterpret_cast<int2 *>(lds);             // (the table is done with; the sums too for all but the widest rows)
     const bool staged = total * 8 <= kRows * slots * 4;
     int2 *to = staged ? stage : found;
@@ -771,14 +782,14 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
         wave_sync();
         for (int i = lane; i < total; i += 64) found[(unsigned)i] = stage[i];
     }
-    if (lane == 0) a.wave_total[blockIdx.x * 4 + wave] = total;
+    if (lane == 0) a.wave_total[block * 4 + wave] = total;
     if (l == 0) {
         // (rows of other kernels count as empty here)
         if (row < a.rows && (small || ub == 0 || deg <= 0)) put_for(a.finish, a.row_nnz + row, (int32_t)n);
         s_len[threadIdx.x / G] = (uint32_t)n;
     }
     __syncthreads();
-    const int64_t g = (int64_t)blockIdx.x * (256 / G / T) + threadIdx.x;
+    const int64_t g = (int64_t)block * (256 / G / T) + threadIdx.x;
     if (threadIdx.x < 256 / G / T && g * T < a.rows) {
         uint32_t sum_len = 0;
         for (int i = 0; i < T; ++i) sum_len += s_len[threadIdx.x * T + i];
@@ -789,7 +800,8 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
 template <int G, bool kNarrow>
 __global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin) {
     __shared__ int s_last;
-    if ((int)blockIdx.x >= a.blocks) sum_tile_rows(sums, (int)blockIdx.x - a.blocks, (int)gridDim.x - a.blocks, a.finish);
+    const int sum_block = (int)blockIdx.x - (a.sums_first ? 0 : (int)gridDim.x - a.sum_blocks);
+    if (sum_block >= 0 && sum_block < a.sum_blocks) sum_tile_rows(sums, sum_block, a.sum_blocks, a.finish);
     else row_small<G, kNarrow>(a);
     if (!a.finish) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left for the last block has arrived
@@ -1874,7 +1886,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     sums.same = alias;
     sums.partial = partial;
     sums.skip = skip;
-    const int sum_blocks = (int)std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, alias ? 0 : b_ntr) + 15) / 16);
+    const int sum_blocks = (int)std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, alias ? 0 : b_ntr) + 3) / 4);
     // row_ptr of C when the sizes of its rows are there, and the sizes of everything to the host
     int64_t *row_ptr = nullptr;
     auto finish_args = [&] {
@@ -2000,7 +2012,8 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     m.row_nnz = row_nnz;
     m.group_len = group_len;
     const unsigned small_blocks = (unsigned)(small_waves / 4);
-    m.blocks = (int)small_blocks;
+    m.sum_blocks = sum_blocks;
+    m.sums_first = std::max(a_ntr, alias ? 0 : b_ntr) > 16 * kPlanBlocks;
     // (a small product without heavy rows: the last block of the small ones finishes)
     bool finish_too = known && hint.nnz >= 0 && chunks == 1 && n_heavy == 0;
     auto heavy_arrays = [&]() {
