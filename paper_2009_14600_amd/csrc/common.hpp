@@ -116,6 +116,7 @@ struct RowHint {
     bool sample = true;                            // (a look at some of the tile-rows has not misled yet)
     int64_t heavy = 0, tasks = 0, large_tasks = 0;
     int64_t longest = 0;                           // entries of the longest heavy row of A
+    int64_t products = 0;                          // intermediate ones
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows
     bool wide = false;                             // so many rows of 9 to 16 entries that 16 lanes per row pay

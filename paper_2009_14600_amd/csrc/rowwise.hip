@@ -26,6 +26,8 @@ namespace tsp {
 constexpr int kPlanBlocks = 256;         // blocks that add up tile-rows, at most
 constexpr int64_t kFinishRows = 1 << 21; // rows of which k_row_finish makes row_ptr (every block reads all groups before it)
 constexpr int kChunkTileRows = 128, kChunkRows = kChunkTileRows * T;   // rows whose row_ptr one block writes
+// Rows whose entries k_row_small adds up, and where: additions to one line wait for each other
+constexpr int kPartTileRows = 128, kPartRows = kPartTileRows * T, kPartStride = 32;
 constexpr int kPlanSums = 8;
 constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
 constexpr int kSpanWindowsLog = 6, kSpanWindows = 1 << kSpanWindowsLog;   // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
@@ -81,6 +83,7 @@ struct PrepareArgs {
     int large_products;
     int64_t heavy_cap, task_cap;
     uint32_t *rows_of;                   // of every tile-row: pack_rows()
+    uint32_t *part_len;                  // SmallArgs', zeroed; or null
     int64_t *d_scalars;
     const int64_t *skip;                 // S_ROW_SKIP, or null
 };
@@ -280,6 +283,7 @@ __global__ __launch_bounds__(kTeam > 256 ? kTeam : 256) __attribute__((amdgpu_wa
     if (bad && a.validate) a.d_scalars[S_INVALID] = 1;
     if (tid == 0) {
         a.out.ntiles[I] = s_count[team];
+        if (a.ub && a.part_len && I % kPartTileRows == 0) a.part_len[I / kPartTileRows * kPartStride] = 0;
         a.out.range[I] = ValueRange::range(s_most[team], s_last[team]);
     }
     if (!a.ub || tid >= 64) return;
@@ -497,79 +501,54 @@ struct FinishArgs {
     const int64_t *skip;                 // S_ROW_SKIP, or null: nothing has been counted then
 };
 
-// row_ptr of C from the row lengths: block b takes rows [2048 b, 2048 b + 2048), adds up the groups of 16 rows before
-// them and scans its own.  The last block also adds up the sums over the tile-rows and hands all sizes to the host.
-// kShared: other blocks of the same launch have left row_nnz and partial (put_for).
+// What one block that knows that the others are done makes of the sums over the tile-rows, and all sizes to the host.
+// `standing`: standing_scalar; `entries`: of C, where rows > 0.
+struct PlanTotals {
+    unsigned long long sum[kPlanSums], most[kPlanSums];
+    int64_t own[kScalars];
+};
 template <bool kShared>
-__device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int blocks) {
-    __shared__ uint64_t lds[256 / 64];
-    __shared__ unsigned long long s_sum[kPlanSums], s_max[kPlanSums];
-    __shared__ int64_t own[kScalars];
-    const bool last = block == blocks - 1;
-    const int64_t standing = last ? standing_scalar(a.d_scalars) : 0;
-    constexpr int kItems = kChunkRows / 256;
-    const int64_t base = (int64_t)block * kChunkRows + (int64_t)threadIdx.x * kItems;
-    int32_t x[kItems];
+__device__ __forceinline__ void add_plan_sums(const FinishArgs &a, PlanTotals &totals) {       // (two sums per wave)
+    const int lane = lane_id(), slot0 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * 2;
+    unsigned long long v[2][kPlanBlocks / 64];                   // (both requested before either is waited for)
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) x[i] = base + i < a.rows ? get_shared<kShared>(a.row_nnz + base + i) : 0;
-    if (last) {                          // two sums per wave
-        const int lane = lane_id();
-        for (int slot = (int)(threadIdx.x >> 6) * 2; slot < (int)(threadIdx.x >> 6) * 2 + 2; ++slot) {
-            unsigned long long v[kPlanBlocks / 64], sum = 0;
+    for (int w = 0; w < 2; ++w)
 #pragma unroll
-            for (int u = 0; u < kPlanBlocks / 64; ++u)
-                v[u] = u * 64 + lane < a.partials ? get_shared<kShared>(a.partial + slot * kPlanBlocks + u * 64 + lane) : 0ull;
-            if (slot == kSumRanges || slot == kSumLongest) {
-                int most[4] = {0, 0, 0, 0};
+        for (int u = 0; u < kPlanBlocks / 64; ++u)
+            v[w][u] = u * 64 + lane < a.partials ? get_shared<kShared>(a.partial + (slot0 + w) * kPlanBlocks + u * 64 + lane) : 0ull;
 #pragma unroll
-                for (int u = 0; u < kPlanBlocks / 64; ++u) {
-                    if (slot == kSumLongest) most[0] = max(most[0], (int)v[u]);
-                    else
-                        for (int q = 0; q < 4; ++q) most[q] = max(most[q], (int)((v[u] >> (48 - 16 * q)) & 0xFFFFull));
-                }
-                for (int q = 0; q < 4; ++q) most[q] = wave_max(most[q]);
-                if (lane == 0)
-                    for (int q = 0; q < (slot == kSumLongest ? 1 : 4); ++q) s_max[slot == kSumLongest ? 4 : q] = (unsigned long long)most[q];
-            } else {
+    for (int w = 0; w < 2; ++w) {
+        const int slot = slot0 + w;
+        if (slot == kSumRanges || slot == kSumLongest) {
+            int most[4] = {0, 0, 0, 0};
 #pragma unroll
-                for (int u = 0; u < kPlanBlocks / 64; ++u) sum += v[u];
-                for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-                if (lane == 0) s_sum[slot] = sum;
+            for (int u = 0; u < kPlanBlocks / 64; ++u) {
+                if (slot == kSumLongest) most[0] = max(most[0], (int)v[w][u]);
+                else
+                    for (int q = 0; q < 4; ++q) most[q] = max(most[q], (int)((v[w][u] >> (48 - 16 * q)) & 0xFFFFull));
             }
+            for (int q = 0; q < 4; ++q) most[q] = wave_max(most[q]);
+            if (lane == 0)
+                for (int q = 0; q < (slot == kSumLongest ? 1 : 4); ++q) totals.most[slot == kSumLongest ? 4 : q] = (unsigned long long)most[q];
+        } else {
+            unsigned long long sum = 0;
+#pragma unroll
+            for (int u = 0; u < kPlanBlocks / 64; ++u) sum += v[w][u];
+            for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+            if (lane == 0) totals.sum[slot] = sum;
         }
-        __syncthreads();
     }
-    uint64_t before = 0;
-    const uint4 *groups4 = reinterpret_cast<const uint4 *>(a.group_len);
-    const int64_t quads = a.rows > 0 ? (int64_t)block * kChunkTileRows / 4 : 0;
-    // (all of them in flight up to 16384 groups: a round trip, not four)
-    for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 16 * 256) {
-        uint4 g[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) g[u] = groups4[min(q0 + u * 256, quads - 1)];
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (q0 + u * 256 < quads) before += (uint64_t)g[u].x + g[u].y + g[u].z + g[u].w;
-    }
-    uint64_t entries_before;
-    (void)block_exclusive_scan64<256>(before, &entries_before, lds);
-    uint64_t mine = 0;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) mine += (uint32_t)x[i];
-    uint64_t total;
-    uint64_t run = entries_before + block_exclusive_scan64<256>(mine, &total, lds);
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        if (base + i < a.rows) a.c_row_ptr[base + i] = (int64_t)run;
-        run += (uint32_t)x[i];
-    }
-    if (!last) return;
-    if (threadIdx.x == S_C_NNZ) own[S_C_NNZ] = a.rows > 0 ? (int64_t)(entries_before + total) : standing;
+    __syncthreads();
+}
+__device__ __forceinline__ void publish_sizes(const FinishArgs &a, PlanTotals &totals, int64_t standing, int64_t entries) {
+    int64_t *own = totals.own;
+    const unsigned long long *s_sum = totals.sum, *s_max = totals.most;
+    if (threadIdx.x == S_C_NNZ) own[S_C_NNZ] = a.rows > 0 ? entries : standing;
     if (threadIdx.x == S_INVALID) own[S_INVALID] = standing;
     if (threadIdx.x == S_ROW_LISTS || threadIdx.x == S_ROW_LARGE_TASKS) own[threadIdx.x] = standing;
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (a.rows > 0) a.c_row_ptr[a.rows] = (int64_t)(entries_before + total);
+        if (a.rows > 0) a.c_row_ptr[a.rows] = entries;
         own[S_CANDIDATES] = (int64_t)s_sum[kSumCandidates];
         own[S_TILES_A] = (int64_t)s_sum[kSumTilesA];
         own[S_TILES_B] = (int64_t)(a.same ? s_sum[kSumTilesA] : s_sum[kSumTilesB]);
@@ -594,6 +573,48 @@ __device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int b
                               own_slot(S_ROW_LONGEST) | own_slot(S_ROW_HEAVY) | own_slot(S_ROW_TASKS);
     publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, standing, own, kOwn, a.clear);
 }
+
+// row_ptr of C from the row lengths: block b takes rows [2048 b, 2048 b + 2048), adds up the groups of 16 rows before
+// them and scans its own.  The last block also adds up the sums over the tile-rows and hands all sizes to the host.
+// kShared: other blocks of the same launch have left row_nnz and partial (put_for).
+template <bool kShared>
+__device__ __forceinline__ void row_finish(const FinishArgs &a, int block, int blocks) {
+    __shared__ uint64_t lds[256 / 64];
+    __shared__ PlanTotals totals;
+    const bool last = block == blocks - 1;
+    const int64_t standing = last ? standing_scalar(a.d_scalars) : 0;
+    constexpr int kItems = kChunkRows / 256;
+    const int64_t base = (int64_t)block * kChunkRows + (int64_t)threadIdx.x * kItems;
+    int32_t x[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) x[i] = base + i < a.rows ? get_shared<kShared>(a.row_nnz + base + i) : 0;
+    if (last) add_plan_sums<kShared>(a, totals);
+    uint64_t before = 0;
+    const uint4 *groups4 = reinterpret_cast<const uint4 *>(a.group_len);
+    const int64_t quads = a.rows > 0 ? (int64_t)block * kChunkTileRows / 4 : 0;
+    // (all of them in flight up to 16384 groups: a round trip, not four)
+    for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 16 * 256) {
+        uint4 g[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) g[u] = groups4[min(q0 + u * 256, quads - 1)];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (q0 + u * 256 < quads) before += (uint64_t)g[u].x + g[u].y + g[u].z + g[u].w;
+    }
+    uint64_t entries_before = 0;
+    if (block > 0) (void)block_exclusive_scan64<256>(before, &entries_before, lds);
+    uint64_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) mine += (uint32_t)x[i];
+    uint64_t total;
+    uint64_t run = entries_before + block_exclusive_scan64<256>(mine, &total, lds);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        if (base + i < a.rows) a.c_row_ptr[base + i] = (int64_t)run;
+        run += (uint32_t)x[i];
+    }
+    if (last) publish_sizes(a, totals, standing, (int64_t)(entries_before + total));
+}
 __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
     if (a.skip && uniform_load(a.skip)) publish_scalars(a.d_scalars, a.h_scalars_dev, a.publish_tag, standing_scalar(a.d_scalars), nullptr, 0);
     else row_finish<false>(a, blockIdx.x, gridDim.x);
@@ -617,6 +638,11 @@ struct SmallArgs {
     const int2 *a_rec, *b_rec;
     int32_t *row_nnz;
     uint32_t *group_len;                 // entries per 16 rows
+    // For k_small_finish, or null: entries per part of kPartRows, zero before, and whether the operands are canonical and no
+    // row is heavy
+    uint32_t *part_len;
+    int32_t *only_small;
+    const int64_t *d_scalars;
     int2 *found;                         // [waves][wave_rows * products] entries {column, value} of a wave's rows, in order
     int32_t *wave_total;                 // ... and how many
     // The blocks that sum (SumArgs) are the first ones of the launch where their groups of lanes have several tile-rows each, else
@@ -687,7 +713,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
     products += TSP_DPP(0, products, 0x141, 0xf, true);
     if constexpr (G == 16) products += TSP_DPP(0, products, 0x140, 0xf, true);
     if (products > most) e = p;
-    const int lists = wave_max(small ? deg : 0), longest = wave_max(e - p);
+    const int lists = wave_max(small ? deg : 0);
     // round t: list t, or with narrow lists the lists t * (G / width) ... of the group, and element j of each
     const int width = kNarrow ? a.shape.list_lanes : G, per = kNarrow ? G / width : 1;
     const int j = kNarrow ? l & (width - 1) : l;
@@ -709,13 +735,16 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
     int listed = 0;                                          // columns of the row so far
     auto take = [&](const int2 &y, uint32_t f, bool on) {
         bool made = false;
-        uint32_t slot = ((uint32_t)__umul24((uint32_t)y.x, 0x9E3779u) >> (24 - bits)) & (uint32_t)(slots - 1);
+        // (an odd step, by which every slot is met, and of the column: one slot after the other, those of 65,536 rows of 8 random
+        // entries lie so that the kernel takes 44 us instead of 41)
+        const uint32_t hash = (uint32_t)__umul24((uint32_t)y.x, 0x9E3779u), step = hash >> (24 - 2 * bits) | 1u;
+        uint32_t slot = (hash >> (24 - bits)) & (uint32_t)(slots - 1);
         if (on)
             while (true) {                                   // (a free slot is always left: the row has been checked above)
                 const int32_t old = atomicCAS(&table[slot], kFree, y.x);
                 made = old == kFree;
                 if (made || old == y.x) break;
-                slot = (slot + 1) & (uint32_t)(slots - 1);
+                slot = (slot + step) & (uint32_t)(slots - 1);
             }
         const float product = __uint_as_float(f) * __uint_as_float((uint32_t)y.y);
         const uint32_t mine = (uint32_t)(__ballot(made) >> group_shift) & ((1u << G) - 1u);
@@ -738,13 +767,47 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
 #pragma unroll
     for (int t = 0; t < kAhead; ++t)
         if (t < rounds) take(x[t], (uint32_t)of_list(av, t), there[t]);
-    // lists that are longer than their lanes (the order of the sums stays fixed: by chunks, in them by lists)
-    for (int c = width; c < longest; c += width)
-        for (int t = 0; t < rounds; ++t) {
-            const int32_t k = of_list(p, t) + j + c;
-            const bool on = k < of_list(e, t);
-            take(element(a.b_rec, on ? (uint32_t)k : 0u), (uint32_t)of_list(av, t), on);
+    // Lists that are longer than their lanes, one round after the other to its end (the order of the sums is fixed: the first
+    // elements of all lists, then the others list by list).  The next elements are on their way while some are taken, and rounds
+    // without any are left out: chunk by chunk over all rounds, each load waited for, the light rows of graphs of 1000 to 16,000
+    // vertices took 27 to 35 us, 20 to 29 now.
+    uint32_t left = 0;                                       // rounds that go on, a bit each
+    {
+        const unsigned long long longer = __ballot(e - p > width);
+        uint32_t of_lane = 0;
+#pragma unroll
+        for (int g = 0; g < 64; g += G) of_lane |= (uint32_t)(longer >> g) & ((1u << G) - 1u);
+        if constexpr (kNarrow) {                             // (per lists to a round)
+            for (int t = 0; t < rounds; ++t) left |= (of_lane >> (t * per)) & ((1u << per) - 1u) ? 1u << t : 0u;
+        } else {
+            left = of_lane;
         }
+    }
+    if (left) {
+        int32_t at = 0, end = 0;
+        uint32_t factor = 0;
+        int2 y;
+        auto request = [&] { y = element(a.b_rec, at < end ? (uint32_t)at : 0u); };
+        auto next_round = [&] {
+            const int t = __builtin_ctz(left);
+            at = of_list(p, t) + j + width;
+            end = of_list(e, t);
+            factor = (uint32_t)of_list(av, t);
+            left &= left - 1u;
+            request();
+        };
+        next_round();
+        for (bool more = true; more;) {
+            const int2 now = y;
+            const uint32_t f = factor;
+            const bool on = at < end;
+            at += width;
+            if (__any(at < end)) request();
+            else if (left) next_round();
+            else more = false;
+            take(now, f, on);
+        }
+    }
     const int n = min(listed, most);
     const uint32_t inc = wave_inclusive_scan(l == 0 ? (uint32_t)n : 0u);
     const int total = __builtin_amdgcn_readlane((int)inc, 63), longest_row = wave_max(n);
@@ -790,11 +853,17 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
     }
     __syncthreads();
     const int64_t g = (int64_t)block * (256 / G / T) + threadIdx.x;
+    uint32_t sum_len = 0;
     if (threadIdx.x < 256 / G / T && g * T < a.rows) {
-        uint32_t sum_len = 0;
         for (int i = 0; i < T; ++i) sum_len += s_len[threadIdx.x * T + i];
         a.group_len[g] = sum_len;
     }
+    if (a.part_len && threadIdx.x < 64) {                       // (one addition per block, whose groups are of one chunk)
+        for (int i = 1; i < 256 / G / T; i <<= 1) sum_len += (uint32_t)__shfl_xor((int)sum_len, i, 64);
+        if (threadIdx.x == 0) atomicAdd(a.part_len + g / kPartTileRows * kPartStride, sum_len);
+    }
+    if (a.part_len && block == 0 && threadIdx.x == 0)
+        *a.only_small = !(a.d_scalars[S_INVALID] | a.d_scalars[S_ROW_LISTS] | a.d_scalars[S_ROW_LARGE_TASKS]);
 }
 
 template <int G, bool kNarrow>
@@ -859,6 +928,65 @@ __global__ __launch_bounds__(256) void k_small_copy(const CopyArgs a) {
             a.c_val[to + i] = __uint_as_float((uint32_t)x.y);
         }
         from += n;
+    }
+}
+
+// k_row_finish and k_small_copy at once, for a product launched ahead that is expected to have small rows only: a block takes
+// kSideRows rows, adds up the chunks before theirs and the groups before them in it, writes their row_ptr and moves their
+// entries, flat over the threads, if what is expected holds.  (On a 512 x 512 mesh the two take 7.4 and 12.4 us one behind the
+// other, most of the first in round trips; together 12.3 us, and k_row_small 2 more.)
+template <int kSideRows>
+__global__ __launch_bounds__(256) void k_small_finish(const FinishArgs a, const CopyArgs c, const uint32_t *part_len, const int32_t *only_small) {
+    __shared__ uint64_t lds[256 / 64];
+    __shared__ PlanTotals totals;
+    __shared__ uint32_t s_first[kSideRows / 4];                  // entries of the block before each wave of k_row_small
+    // (the first block hands the sizes to the host, which then has the time of this kernel for the next call)
+    const bool first = blockIdx.x == 0;
+    const int64_t standing = first ? standing_scalar(a.d_scalars) : 0;
+    const int64_t row0 = (int64_t)blockIdx.x * kSideRows, row = (int)threadIdx.x < kSideRows ? row0 + threadIdx.x : a.rows;
+    const int part = (int)(row0 / kPartRows), parts = (int)((a.rows + kPartRows - 1) / kPartRows);
+    const int group0 = part * kPartTileRows, groups = (int)(row0 / T) - group0;            // before the block's, in its part
+    uint64_t before = 0, all = 0;
+    for (int i = threadIdx.x; i < parts; i += 256) {
+        const uint32_t n = part_len[i * kPartStride];
+        all += n;
+        before += i < part ? n : 0u;
+    }
+    if ((int)threadIdx.x < groups) before += a.group_len[group0 + threadIdx.x];
+    const uint32_t mine = row < a.rows ? (uint32_t)a.row_nnz[row] : 0u;
+    if (first) add_plan_sums<false>(a, totals);
+    uint64_t entries_before, entries, own;
+    (void)block_exclusive_scan64<256>(before, &entries_before, lds);
+    (void)block_exclusive_scan64<256>(all, &entries, lds);
+    const uint32_t at = (uint32_t)block_exclusive_scan64<256>(mine, &own, lds);
+    if (row < a.rows) a.c_row_ptr[row] = (int64_t)(entries_before + at);
+    if (first) publish_sizes(a, totals, standing, (int64_t)entries);
+    // (what Expected::holds says where no heavy row is expected)
+    if (!uniform_load(only_small) || (int64_t)entries > a.expected.nnz) return;
+    const int wave_rows = 64 / c.shape.lanes, waves = kSideRows / wave_rows;
+    if ((int)threadIdx.x < kSideRows && threadIdx.x % wave_rows == 0) s_first[threadIdx.x / wave_rows] = at;
+    __syncthreads();
+    const int64_t wave0 = (int64_t)blockIdx.x * waves;
+    const int room = wave_rows * c.shape.products;
+    int32_t *col = c.c_col + entries_before;
+    float *val = c.c_val + entries_before;
+    for (int base = threadIdx.x; base < (int)own; base += 4 * 256) {
+        int2 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t e = (uint32_t)min(base + u * 256, (int)own - 1);
+            int w = 0;                                           // the last wave that begins at or before e
+#pragma unroll
+            for (int d = kSideRows / 8; d > 0; d >>= 1)
+                if (w + d < waves && s_first[w + d] <= e) w += d;
+            x[u] = c.found[(wave0 + w) * room + (e - s_first[w])];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (base + u * 256 < (int)own) {
+                col[base + u * 256] = x[u].x;
+                val[base + u * 256] = __uint_as_float((uint32_t)x[u].y);
+            }
     }
 }
 
@@ -1220,7 +1348,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 struct FillArgs {
     const int4 *tasks;                   // [task_cap]: the large ones, then others or nothing, then the light ones
     int64_t n_tasks, n_large, task_cap;
-    bool large, light;                    // which of them this launch is for
+    bool large, light;                   // which of them this launch is for
     const int32_t *a_start, *b_start;
     const int2 *a_rec;
     const uint32_t *pack;
@@ -1271,6 +1399,9 @@ constexpr int kNarrowColumns = 1 << 14;
 // 8192 / 16,384 / 32,768 products on 14.75 / 14.5 / 14.1; scale 14 (a table for few columns) 235 us, 230, 184 / 178 / 188, and
 // 168 with blocks of 256 threads for the light ones.
 constexpr int kLarge = 32768, kLargeNarrow = 16384;
+// ... in products of so many intermediate ones at least: two launches more pay where they fill the chip (graphs of 1000, 2000,
+// 4000 and 8000 vertices: 116 / 134, 117 / 132, 100 / 112 and 223 / 171 us without and with them).
+constexpr int64_t kSplitProducts = 8 << 20;
 
 template <typename Acc, int kCap, int kThreads, int kSpan, int kPiece = 16>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThreads == 64 ? 1 : 8, 8))) void k_heavy_fill(const FillArgs a) {
@@ -1568,7 +1699,7 @@ void launch_prepare(const PrepareArgs<RP, VT> &a, bool long_rows, hipStream_t s)
 // What k_row_prepare needs beyond the operand, for A (null members for B)
 struct LeftOperand {
     int32_t *ub;
-    uint32_t *rows_of;
+    uint32_t *rows_of, *part_len;
     unsigned long long *products;
     const tsp_csr *B;
     SmallShape shape;
@@ -1610,6 +1741,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
             a.heavy_cap = left->heavy_cap;
             a.task_cap = left->task_cap;
             a.rows_of = left->rows_of;
+            a.part_len = left->part_len;
         }
         a.d_scalars = ctx->d_scalars;
         a.skip = skip;
@@ -1620,7 +1752,7 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
     else f16 ? run(int64_t{}, uint16_t{}) : run(int64_t{}, float{});
 }
 
-void launch_fill(FillArgs &f, FillKind kind, bool short_rows, hipStream_t s) {
+void launch_fill(FillArgs &f, FillKind kind, bool short_rows, bool split, hipStream_t s) {
     auto launch = [&](auto kernel, int threads, bool large, bool light) {
         f.large = large;
         f.light = light;
@@ -1630,7 +1762,9 @@ void launch_fill(FillArgs &f, FillKind kind, bool short_rows, hipStream_t s) {
     f.p_scale = std::ldexp(1.0f, -kind.scale);
     f.c_scale = std::ldexp(1.0f, kind.scale);
     const bool narrow = (int64_t)f.windows << f.window_shift <= kNarrowColumns;
-    if (kind.sum == FillKind::kInt32 && narrow) {
+    if (kind.sum == FillKind::kInt32 && !split) {
+        launch(narrow ? k_heavy_fill<int32_t, 4096, 512, kNarrowColumns> : k_heavy_fill<int32_t, 4096, 512, kSpanColumns>, 512, true, true);
+    } else if (kind.sum == FillKind::kInt32 && narrow) {
         launch(k_heavy_fill<int32_t, 12288, 1024, kNarrowColumns>, 1024, true, false);
         launch(k_heavy_fill<int32_t, 4096, 256, kNarrowColumns>, 256, false, true);
     } else if (kind.sum == FillKind::kInt32) {
@@ -1837,8 +1971,11 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     left.tasks = ws.get<int4>((size_t)std::max<int64_t>(left.task_cap, 1));
     int32_t *row_nnz = ws.get<int32_t>((size_t)A->rows + 1);
     uint32_t *group_len = ws.get<uint32_t>((size_t)chunks * kChunkTileRows);
+    // a product of small rows only, by the last one of these sizes: k_small_finish
+    const bool finish_and_copy = known && hint.nnz >= 0 && hint.heavy == 0 && hint.small && chunks > 1 && A->rows <= kFinishRows;
+    if (finish_and_copy) left.part_len = ws.get<uint32_t>((size_t)((A->rows + kPartRows - 1) / kPartRows) * kPartStride);
     int2 *found = nullptr;
-    int32_t *wave_total = nullptr, *live = nullptr;
+    int32_t *wave_total = nullptr, *live = nullptr, *only_small = nullptr;
     Expected expected{};
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
 
@@ -1886,7 +2023,9 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     sums.same = alias;
     sums.partial = partial;
     sums.skip = skip;
-    const int sum_blocks = (int)std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, alias ? 0 : b_ntr) + 3) / 4);
+    // (a tile-row to a wave, whose tiles are more than a group of lanes takes; for the smallest products as few blocks as do)
+    const int per_block = chunks == 1 ? 16 : 4;
+    const int sum_blocks = (int)std::min<int64_t>(kPlanBlocks, (std::max(a_ntr, alias ? 0 : b_ntr) + per_block - 1) / per_block);
     // row_ptr of C when the sizes of its rows are there, and the sizes of everything to the host
     int64_t *row_ptr = nullptr;
     auto finish_args = [&] {
@@ -1926,7 +2065,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         TSP_HIP_CHECK(ctx, hipGetLastError());
         return (int)TSP_OK;
     };
-    int64_t n_heavy = left.heavy_cap, n_tasks = left.task_cap, n_large = known ? hint.large_tasks : 0;
+    int64_t n_heavy = left.heavy_cap, n_tasks = left.task_cap, n_large = known ? hint.large_tasks : 0, n_products = known ? hint.products : 0;
     FillKind kind{};
     bool other_lanes = false;                // the product at hand wants its small rows by another number of lanes
     auto sizes_known = [&]() {               // the host has the numbers of k_row_finish
@@ -1935,6 +2074,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         n_heavy = h[S_ROW_HEAVY];
         n_tasks = h[S_ROW_TASKS];
         n_large = h[S_ROW_LARGE_TASKS];
+        n_products = h[S_ROW_PRODUCTS];
         hint.ready = true;
         hint.wide = h[S_ROW_WIDE] > A->rows / 64;
         other_lanes = shape.slots <= 128 && shape.lanes != (hint.wide ? 16 : lanes_unless_wide);
@@ -1947,6 +2087,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
         hint.large_tasks = n_large;
+        hint.products = n_products;
         hint.longest = h[S_ROW_LONGEST];
         hint.small = h[S_ROW_SMALL] > 0;
         hint.nnz = row_ptr ? h[S_C_NNZ] : -1;
@@ -2056,7 +2197,8 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
                            finish_too ? finish_args() : FinishArgs{});
         if (n_heavy > 0) {
             PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, span_table, windows, spans, shift};
-            if (B->nnz > 16 * B->rows)
+            // (a wave per row also where some of the last product's were long: a graph of 4000 vertices 28 -> 8 us)
+            if (B->nnz > 16 * B->rows || left.long_rows)
                 hipLaunchKernelGGL(k_heavy_pack<64>, dim3((unsigned)((B->rows * 64 + 255) / 256)), dim3(256), 0, s, p);
             else
                 hipLaunchKernelGGL(k_heavy_pack<16>, dim3((unsigned)((B->rows * 16 + 255) / 256)), dim3(256), 0, s, p);
@@ -2080,7 +2222,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             c.bits = pattern_kept ? bits : nullptr;
             c.tasks = left.tasks;
             c.ub = left.ub;
-            count_heavy(n_heavy, n_large);
+            count_heavy(n_heavy, n_products >= kSplitProducts ? n_large : 0);
         }
         return (int)TSP_OK;
     };
@@ -2125,7 +2267,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
                     c.bits = bits;
                     count_heavy(f.heavy_to - f.heavy_from, 0);
                 }
-                launch_fill(f, how, B->nnz <= 16 * B->rows, s);
+                launch_fill(f, how, B->nnz <= 16 * B->rows, n_products >= kSplitProducts, s);
             }
         }
         phase_end(ctx, TSP_PHASE_NUMERIC, s);
@@ -2148,15 +2290,40 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         kind = FillKind{(FillKind::Sum)hint.sum, hint.scale};
         expected = Expected{room, n_heavy, n_tasks, n_large, kind};
     }
+    const bool had_small = hint.small;
+    if (finish_and_copy) {
+        only_small = ws.get<int32_t>(1);
+        if (!only_small) return TSP_ERR_ALLOC_FAILED;
+        m.part_len = left.part_len;
+        m.only_small = only_small;
+        m.d_scalars = ctx->d_scalars;
+    }
     rc = size_rows(false);
     if (rc) return rc;
     phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
-    const bool had_small = hint.small;
     phase_begin(ctx, TSP_PHASE_COUNT, s);
-    if (!finish_too) rc = finish(TSP_KERNEL_SCAN_ROWS);
+    if (finish_and_copy) {
+        KernelTimer kt(ctx, TSP_KERNEL_SCAN_ROWS, s);
+        FinishArgs a = finish_args();
+        a.live = nullptr;
+        const CopyArgs p{shape, A->rows, small_waves, ma.start, left.ub, found, wave_total, row_ptr, col, val, nullptr};
+        auto launch = [&](auto kernel, int rows) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((A->rows + rows - 1) / rows)), dim3(256), 0, s, a, p, left.part_len, only_small);
+        };
+        // (about 2000 entries to a block: a 512 x 512 mesh 13.5 / 12.4 / 15.4 us with 256 / 128 / 64 rows, 65,536 rows of 60 entries
+        // 17.7 / 13.6 / 12.4 / 15.5 with 128 / 64 / 32 / 16, A*P on a 64^3 grid 7.6 / 8.8 / 12.4 with 256 / 128 / 64)
+        const int64_t mean = hint.nnz / A->rows;
+        if (mean < 10) launch(k_small_finish<256>, 256);
+        else if (mean < 20) launch(k_small_finish<128>, 128);
+        else if (mean < 40) launch(k_small_finish<64>, 64);
+        else launch(k_small_finish<32>, 32);
+        TSP_HIP_CHECK(ctx, hipGetLastError());
+    } else if (!finish_too) {
+        rc = finish(TSP_KERNEL_SCAN_ROWS);
+    }
     ctx->scalars_clean = !rc;                // (it has cleared the scalar block for the next call)
     phase_end(ctx, TSP_PHASE_COUNT, s);
-    if (!rc && ahead) rc = multiply(had_small, kind);
+    if (!rc && ahead && !finish_and_copy) rc = multiply(had_small, kind);
     if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);           // the wait that sizes C
     if (rc) return rc;
     const int64_t had_heavy = n_heavy, had_tasks = n_tasks, had_large = n_large, products = ctx->h_scalars[S_PRODUCTS];

@@ -341,6 +341,46 @@ def test_pieces_of_heavy_rows_dealt_to_waves(tsp, oracle, values, cols, entries)
         h.close()
 
 
+@pytest.mark.parametrize("left,lengths", [(8, (1, 9)), (8, (0, 17, 5)), (16, (1, 100)), (16, (17, 0, 33, 2)), (12, (6, 6, 40)), (9, (1, 1, 1, 150))])
+def test_lists_longer_than_their_lanes(tsp, oracle, left, lengths):
+    """Small rows some of whose lists go on beyond the lanes of a group, none, one and several times, others empty, in every place."""
+    rng = np.random.default_rng(left + sum(lengths))
+    B = _exact_lengths(rng, 3000, rng.choice(lengths, 1500), lambda m: rng.uniform(-1, 1, m))
+    A = _exact_lengths(rng, 1500, rng.integers(0, left + 1, 1000), lambda m: rng.uniform(-1, 1, m))
+    h = tsp.Handle()
+    try:
+        _check(h, tsp, oracle, A, B, calls=3)
+    finally:
+        h.close()
+
+
+@pytest.mark.parametrize("rows", [2049, 4096, 4097, 6200])
+@pytest.mark.parametrize("left,right", [(2, 3), (5, 3), (8, 4), (5, 12), (16, 9)])
+def test_small_rows_finished_and_moved_together(tsp, oracle, rows, left, right):
+    """Products of small rows only, launched ahead (k_small_finish), of so few to so many entries per row that a block has 256, 128,
+    64 and 32 rows; then, of the same sizes, one with more entries than there is room for, one with heavy rows, one with an
+    empty end, and the first one again."""
+    rng = np.random.default_rng(rows + left)
+    ones = lambda m: rng.choice([-1.0, 1.0], m)
+    B = _exact_lengths(rng, 3000, np.full(2000, right), ones)
+    near = np.minimum(np.arange(rows)[:, None] % 7 + np.arange(left), 1999)
+    first = inputs.from_coo(rows, 2000, np.repeat(np.arange(rows), left), near.reshape(-1), ones(rows * left), "few rows of B")
+    spread = _exact_lengths(rng, 2000, np.full(rows, left), ones)
+    lengths = np.full(rows, left)
+    lengths[5], lengths[9:9 + 400 // left + 1] = left + 400, 0
+    lengths[9] = lengths.sum() * 0 + rows * left - (lengths.sum() - lengths[9])
+    heavy = _exact_lengths(rng, 2000, lengths, ones)
+    ends = np.full(rows, left)
+    ends[-64:] = 0
+    ends[:64] = 2 * left
+    h = tsp.Handle()
+    try:
+        for A in (first, spread, heavy, first, _exact_lengths(rng, 2000, ends, ones), first):
+            _check(h, tsp, oracle, A, B, calls=2)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("rows,left", [(300, 20), (65600, 9)])
 def test_long_tile_rows_by_more_threads(tsp, oracle, rows, left):
     """Rows of 512 entries and more among short ones, in few tile-rows and in many: from the second call on k_row_prepare has more
@@ -390,11 +430,12 @@ def test_large_and_light_rows(tsp, oracle, values, cols, large):
     equal sizes and more large rows, fewer and none, so that what the last one left does not fit."""
     rng = np.random.default_rng(cols)
     make = lambda m: _VALUES[values](rng, m)
+    rows = (9 << 20) // (64 * large)                       # (8 million products from which the large rows are apart)
     B = _exact_lengths(rng, cols, np.full(1100, 64), make)
-    total, all_of = 300 * (large - 1), []
-    for many in (0, 1, 40, 7, 299):
-        lengths = np.full(300, large - 1)
-        lengths[rng.choice(300, many, replace=False)] = large
+    total, all_of = rows * (large - 1), []
+    for many in (0, 1, 40, 7, rows - 1):
+        lengths = np.full(rows, large - 1)
+        lengths[rng.choice(rows, many, replace=False)] = large
         lengths[np.argmin(lengths)] -= lengths.sum() - total
         all_of.append(_exact_lengths(rng, 1100, np.maximum(lengths, 0), make))
     h = tsp.Handle()
