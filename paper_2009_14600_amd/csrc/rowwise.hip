@@ -1006,30 +1006,51 @@ struct PackArgs {
     int32_t *table;                      // [rows][windows + 1], or null for one window
     int32_t *span_table;                 // [rows][spans + 1], or null for one span
     int windows, spans, shift;           // a window is 1 << shift columns
+    int medium_from;                     // entries from which a row is left to the first blocks
 };
-template <int L>
-__global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
-    // (trips in flight: the longest row of an R-MAT graph of scale 18, 25,000 entries, kept the launch waiting for 240 us)
-    constexpr int kTrips = L == 64 ? 4 : 2;
-    const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L;
+// Bound by latency: a row's trips wait for each other, and the launch for its longest row (25,000 entries of an R-MAT graph
+// of scale 18).  So rows of more than pack_short entries are left to the first kLongBlocks blocks.  Each looks through a
+// kLongBlocks-th of the rows, works off rows of more than kPackLong with all waves, kTrips trips of every wave to a round, the
+// words before a wave's from the others' numbers, and the medium ones by a wave each.  A wave per row throughout was bound by
+// the coming and going of 262,144 waves as well.  R-MAT of scale 13/14/16/18: 14.5/24.5/70/209 -> 8.8/11.1/30/139 us (every
+// long row by all waves 11.5/16/55/245; medium ones up to 2048 entries 13.5/13.5/33/141; 1024 such blocks 10/13/33/136).
+constexpr int kPackThreads = 512, kPackWaves = kPackThreads / 64;
+constexpr unsigned kLongBlocks = 256;
+constexpr int kPackLong = 1024;
+constexpr int pack_short(int L) { return L == 64 ? kPackLong : 128; }
+template <int L, bool kLong>
+__device__ __forceinline__ void pack_rows(const PackArgs &a, int64_t first_row) {
+    constexpr int kTrips = kLong ? 4 : 2;
     const int l = threadIdx.x % L, lane = lane_id(), span_shift = a.shift + kSpanWindowsLog;
-    int32_t s = 0, e = 0;
-    if (row < a.rows) {
-        s = a.start[row];
-        e = max(s, a.start[row + 1]);
-    }
-    int32_t *tab = a.table && row < a.rows ? a.table + row * (a.windows + 1) : nullptr;
-    int32_t *span_tab = a.span_table && row < a.rows ? a.span_table + row * (a.spans + 1) : nullptr;
-    int32_t at = s;
-    for (int32_t base = s; __any(base < e); base += L * kTrips) {
-        int2 xs[kTrips];
-        int32_t befores[kTrips];
+    int64_t row = first_row;
+    int32_t s = 0, e = 0, at = 0;
+    int32_t *tab = nullptr, *span_tab = nullptr;
+    auto take_row = [&](int64_t r) {
+        row = r;
+        s = e = 0;
+        if (row < a.rows) {
+            s = a.start[row];
+            e = max(s, a.start[row + 1]);
+        }
+        at = s;
+        tab = a.table && row < a.rows ? a.table + row * (a.windows + 1) : nullptr;
+        span_tab = a.span_table && row < a.rows ? a.span_table + row * (a.spans + 1) : nullptr;
+    };
+    int2 xs[kTrips];
+    int32_t befores[kTrips];
+    auto read = [&](int32_t base) {
 #pragma unroll
         for (int u = 0; u < kTrips; ++u) {
             const int32_t k = max(min(base + u * L + l, e - 1), 0);
             xs[u] = a.rec[k];
             befores[u] = a.rec[max(k - 1, 0)].x;
         }
+    };
+    auto leads = [&](int u, int32_t k) {
+        const int32_t before = k > s ? befores[u] : -1;
+        return k < e && (l == 0 || before < 0 || (before >> 4) != xs[u].x >> 4);
+    };
+    auto write = [&](int32_t base) {
 #pragma unroll
         for (int u = 0; u < kTrips; ++u) {
             const int32_t k0 = base + u * L, k = k0 + l;
@@ -1039,14 +1060,13 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
             const int2 x = xs[u];
             const int32_t before = k > s ? befores[u] : -1, word = x.x >> 4;
             const uint32_t bit = k < e ? 1u << (x.x & 15) : 0u;
-            const bool leads = k < e && (l == 0 || before < 0 || (before >> 4) != word);
             if (k < e) {
                 const _Float16 v = (_Float16)__uint_as_float((uint32_t)x.y);
                 a.pack[k] = (((uint32_t)x.x ^ 31u) & 0xFFFFu) | ((uint32_t)__builtin_bit_cast(uint16_t, v) << 16);
                 if (tab)
                     for (int w = (before >> a.shift) + 1; w <= (x.x >> a.shift) && w <= a.windows; ++w) tab[w] = k;
             }
-            const unsigned long long all = __ballot(leads), live = __ballot(k < e);
+            const unsigned long long all = __ballot(leads(u, k)), live = __ballot(k < e);
             const uint32_t sum = wave_inclusive_scan(bit);
             const int start = 63 - __clzll((long long)(all & ((2ull << lane) - 1ull)));
             const uint32_t before_start = (uint32_t)__shfl((int)(sum - bit), max(start, 0), 64);
@@ -1058,13 +1078,74 @@ __global__ __launch_bounds__(256) void k_heavy_pack(const PackArgs a) {
                 for (int w = (before >> span_shift) + 1; w <= (x.x >> span_shift) && w <= a.spans; ++w) span_tab[w] = place;
             at += __popcll(mine);
         }
+    };
+    auto close_row = [&]() {
+        if (row < a.rows && l == 0) a.words[row] = at - s;
+        const int32_t last_column = e > s && (tab || span_tab) ? a.rec[e - 1].x : -1;
+        if (tab)
+            for (int w = (last_column < 0 ? -1 : min(last_column >> a.shift, a.windows - 1)) + 1 + l; w <= a.windows; w += L) tab[w] = e;
+        if (span_tab)
+            for (int w = (last_column < 0 ? -1 : min(last_column >> span_shift, a.spans - 1)) + 1 + l; w <= a.spans; w += L) span_tab[w] = at;
+    };
+
+    if constexpr (!kLong) {
+        take_row(first_row);
+        if (e - s > pack_short(L)) take_row(a.rows);         // (none)
+        for (int32_t base = s; __any(base < e); base += L * kTrips) {
+            read(base);
+            write(base);
+        }
+        close_row();
+    } else {
+        __shared__ int64_t s_long[kPackThreads];
+        __shared__ int32_t s_words[2][kPackWaves], s_n[2];
+        const int wave = threadIdx.x >> 6;
+        int round = 0;
+        // (neighbours are looked at by different blocks, and those of the next kLongBlocks rows by others again: in graphs the
+        // long rows lie together or at regular distances)
+        for (int64_t group = 0; group * kLongBlocks < a.rows; group += kPackThreads) {
+            const int64_t g = group + threadIdx.x, r = g * kLongBlocks + (blockIdx.x + 101 * g) % kLongBlocks;
+            if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+            __syncthreads();
+            const int32_t len = r < a.rows ? a.start[r + 1] - a.start[r] : 0;
+            if (len > kPackLong) s_long[atomicAdd(&s_n[0], 1)] = r;
+            else if (len >= a.medium_from) s_long[kPackThreads - 1 - atomicAdd(&s_n[1], 1)] = r;
+            __syncthreads();
+            const int n_long = s_n[0], n_medium = s_n[1];
+            for (int q = 0; q < n_long; ++q) {
+                take_row(s_long[q]);
+                for (int32_t first = s; first < e; first += kPackWaves * kTrips * 64, round ^= 1) {
+                    const int32_t base = first + wave * kTrips * 64;
+                    read(base);
+                    int n = 0;
+#pragma unroll
+                    for (int u = 0; u < kTrips; ++u) n += __popcll(__ballot(leads(u, base + u * 64 + l)));
+                    if (lane == 0) s_words[round][wave] = n;
+                    __syncthreads();         // (the other half is written next: nobody is more than a barrier ahead)
+                    const int32_t of = lane < kPackWaves ? s_words[round][lane] : 0;
+                    const int32_t inc = (int32_t)wave_inclusive_scan((uint32_t)of), begun = at;
+                    at = begun + __builtin_amdgcn_readlane(inc - of, wave);
+                    write(base);
+                    at = begun + __builtin_amdgcn_readlane(inc, 63);
+                }
+                if (wave == 0) close_row();
+            }
+            for (int q = wave; q < n_medium; q += kPackWaves) {
+                take_row(s_long[kPackThreads - 1 - q]);
+                for (int32_t base = s; base < e; base += kTrips * 64) {
+                    read(base);
+                    write(base);
+                }
+                close_row();
+            }
+            __syncthreads();
+        }
     }
-    if (row < a.rows && l == 0) a.words[row] = at - s;
-    const int32_t last_column = e > s && (tab || span_tab) ? a.rec[e - 1].x : -1;
-    if (tab)
-        for (int w = (last_column < 0 ? -1 : min(last_column >> a.shift, a.windows - 1)) + 1 + l; w <= a.windows; w += L) tab[w] = e;
-    if (span_tab)
-        for (int w = (last_column < 0 ? -1 : min(last_column >> span_shift, a.spans - 1)) + 1 + l; w <= a.spans; w += L) span_tab[w] = at;
+}
+template <int L>
+__global__ __launch_bounds__(kPackThreads) void k_heavy_pack(const PackArgs a) {
+    if (blockIdx.x < kLongBlocks) pack_rows<64, true>(a, 0);
+    else pack_rows<L, false>(a, ((int64_t)(blockIdx.x - kLongBlocks) * kPackThreads + threadIdx.x) / L);
 }
 
 // 64 pieces of up to 16 elements of B, four to a step: lane 16 q + t describes piece 4 t + q by the byte offset of its first
@@ -2196,12 +2277,14 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hipLaunchKernelGGL(kernel, dim3(small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums,
                            finish_too ? finish_args() : FinishArgs{});
         if (n_heavy > 0) {
-            PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, span_table, windows, spans, shift};
-            // (a wave per row also where some of the last product's were long: a graph of 4000 vertices 28 -> 8 us)
-            if (B->nnz > 16 * B->rows || left.long_rows)
-                hipLaunchKernelGGL(k_heavy_pack<64>, dim3((unsigned)((B->rows * 64 + 255) / 256)), dim3(256), 0, s, p);
-            else
-                hipLaunchKernelGGL(k_heavy_pack<16>, dim3((unsigned)((B->rows * 16 + 255) / 256)), dim3(256), 0, s, p);
+            PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, span_table, windows, spans, shift, 0};
+            // (a wave per row where the mean row fills it)
+            const bool dense = B->nnz > 64 * B->rows;
+            const int64_t lanes = dense ? 64 : 16;
+            p.medium_from = pack_short((int)lanes) + 1;
+            hipLaunchKernelGGL(dense ? k_heavy_pack<64> : k_heavy_pack<16>,
+                               dim3(kLongBlocks + (unsigned)((B->rows * lanes + kPackThreads - 1) / kPackThreads)),
+                               dim3(kPackThreads), 0, s, p);
             c.heavy = left.heavy;
             c.heavy_cap = n_heavy;
             c.d_scalars = ctx->d_scalars;

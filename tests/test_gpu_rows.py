@@ -400,6 +400,28 @@ def test_long_tile_rows_by_more_threads(tsp, oracle, rows, left):
         h.close()
 
 
+@pytest.mark.parametrize("rows,left", [(3000, 9), (3000, 70), (255, 3)])
+def test_long_rows_of_b_packed_by_blocks(tsp, oracle, rows, left):
+    """Rows of B around the lengths from which a wave, or all waves of a block, take them (128, 1024), at the ends of a block's
+    rounds (2048 entries), next to each other and 256 rows apart, among short ones (left: 16 lanes to a row, or 64)."""
+    rng = np.random.default_rng(rows + left)
+    ones = lambda m: rng.choice([-1.0, 1.0], m)
+    lengths = np.full(rows, left)
+    edges = [128, 129, 255, 257, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 9000, 0, 130, 1030]
+    lengths[: len(edges)] = edges
+    if rows > 600:
+        lengths[256 : 256 + len(edges)] = edges[::-1]
+        lengths[512 : 512 + len(edges)] = edges
+    lengths[-1] = 1025
+    B = _exact_lengths(rng, 140000, lengths, ones)
+    A = _exact_lengths(rng, rows, rng.choice([1, 17, 40, 250], 300), ones)
+    h = tsp.Handle()
+    try:
+        _check(h, tsp, oracle, A, B, calls=2)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("cols", [70016, 262144, 262145, 600000])
 def test_words_of_16_columns(tsp, oracle, cols):
     """Rows of B of runs of columns that begin and end at the edges of words (16 columns), of places (32), of trips of the lanes
