@@ -1995,18 +1995,26 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     }
     if (A->nnz >= (1 << 28) || B->nnz >= (1 << 28)) return TSP_OK;      // (32-bit byte offsets into 8-byte records)
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
-    // Small rows: 8 lanes where the mean row of A has no more entries, else 16, or where more than one row in 64 is small but
-    // for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the lanes 0.1 ns per row; by the last product
-    // of these sizes, and where the one at hand turns out otherwise it is started again); for a row of B as many as its mean has
-    // entries; a table of the row that is three quarters full at most, with a margin over the mean number of products, 256
-    // slots at most
-    const int lanes_unless_wide = A->nnz <= 8 * A->rows ? 8 : 16;
-    SmallShape shape{known && hint.wide ? 16 : lanes_unless_wide, 1, 32, 24};
+    // Small rows: a table of the row that is three quarters full at most, with a margin over the mean number of products, 256
+    // slots at most; for a row of B as many lanes as its mean has entries.  For the row 8 lanes where the mean row of A has no
+    // more entries, else 16.  16 also
+    // - for tables of more than 64 slots: a million, 262,144 and 65,536 rows of 8 random entries 899, 214, 65.2 -> 850, 205, 62.3
+    //   us, of 7 (49 products) 794, 187, 60.2 -> 781, 187, 59.5; smaller tables, of 6 (36 products) 518, 125, 50.6 -> 565, 136, 51.6;
+    // - for few rows, as long as the waves are few to a SIMD: 512 to 8192 rows of 8 entries 33.5 -> 29 to 32 us, meshes up to
+    //   110 x 110 29.2 -> 28.2, 16,384 rows of 2 to 8 the same or 1 us more;
+    // - where more than one row in 64 is small but for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the
+    //   lanes 0.1 ns per row; by the last product of these sizes, and where the one at hand turns out otherwise it is started
+    //   again).
+    constexpr int64_t kFewRows = 12288;
+    SmallShape shape{8, 1, 32, 24};
+    int lanes_unless_wide = 16, cost_lanes = 16;             // (rows_preferred's times are of 8 lanes for all of few entries)
     {
         const double list = (double)B->nnz / (double)std::max<int64_t>(B->rows, 1), mean = (double)A->nnz / (double)A->rows * list;
         while (shape.slots < 256 && shape.slots * 3 / 4 < 1.25 * mean) shape.slots *= 2;
         shape.products = shape.slots * 3 / 4;
-        if (shape.slots > 128) shape.lanes = 16;             // (eight rows of a wave would not fit LDS four times)
+        if (A->nnz <= 8 * A->rows && shape.slots <= 128) cost_lanes = 8;
+        if (A->nnz <= 8 * A->rows && shape.slots <= 64 && A->rows > kFewRows) lanes_unless_wide = 8;
+        shape.lanes = known && hint.wide ? 16 : lanes_unless_wide;
         while (shape.list_lanes < shape.lanes && shape.list_lanes < list) shape.list_lanes *= 2;
     }
     // (16 GiB for the entries of the small rows at most: up to 89 million rows)
@@ -2077,7 +2085,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             a.blocks[m] = m && alias ? 0 : (int)std::min<int64_t>(kSampleRows, m ? b_ntr : a_ntr);
             words = std::max(words, (M[m]->cols + T * 32 - 1) / (T * 32));
         }
-        a.small_lanes = shape.lanes;
+        a.small_lanes = known && hint.wide ? 16 : cost_lanes;
         a.small_products = shape.products;
         a.d_scalars = ctx->d_scalars;
         hipLaunchKernelGGL(k_row_sample, dim3((unsigned)(a.blocks[0] + a.blocks[1])), dim3(256), (size_t)words * 4, s, a);
@@ -2158,11 +2166,11 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         n_products = h[S_ROW_PRODUCTS];
         hint.ready = true;
         hint.wide = h[S_ROW_WIDE] > A->rows / 64;
-        other_lanes = shape.slots <= 128 && shape.lanes != (hint.wide ? 16 : lanes_unless_wide);
+        other_lanes = shape.lanes != (hint.wide ? 16 : lanes_unless_wide);
         const int64_t heavy = shape.lanes == 8 && hint.wide ? n_heavy - std::min(n_heavy, h[S_ROW_WIDE]) : n_heavy;
         const int64_t small = std::min(h[S_ROW_PRODUCTS], (A->rows - heavy) * shape.products);      // (at most)
         kind = fill_kind(h);
-        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : shape.lanes, heavy, kind.sum != FillKind::kDouble, h[S_CANDIDATES]) ||
+        hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : cost_lanes, heavy, kind.sum != FillKind::kDouble, h[S_CANDIDATES]) ||
                       (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
         hint.candidates = h[S_CANDIDATES];
         hint.heavy = n_heavy;

@@ -400,6 +400,27 @@ def test_long_tile_rows_by_more_threads(tsp, oracle, rows, left):
         h.close()
 
 
+@pytest.mark.parametrize("a_row,b_row", [(1, 1), (2, 9), (6, 6), (7, 7), (8, 2), (8, 12), (3, 17)])
+@pytest.mark.parametrize("rows", [12288, 12289])
+def test_lanes_of_few_rows(tsp, oracle, rows, a_row, b_row):
+    """Either side of the number of rows, and of the products per row (38), from which small rows have 16 lanes, lists of B
+    narrower than 8 lanes, than 16 and not; then an operand of the same sizes with many rows of 9 to 16 entries, and back."""
+    rng = np.random.default_rng(rows + 10 * a_row + b_row)
+    values = lambda m: rng.normal(size=m)
+    B = _exact_lengths(rng, 5003, np.full(2000, b_row), values)
+    even = np.full(rows, a_row)
+    wide = np.zeros(rows, np.int64)
+    wide[:: 15 if a_row == 1 else 5] = 15 if a_row == 1 else min(5 * a_row, 16)
+    wide[-1] += even.sum() - wide.sum()
+    h = tsp.Handle()
+    try:
+        for l in (even, wide, even):
+            if l.min() >= 0 and l.max() <= 2000:
+                _check(h, tsp, oracle, _exact_lengths(rng, 2000, l, values), B, by_rows=None)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("rows,left", [(3000, 9), (3000, 70), (255, 3)])
 def test_long_rows_of_b_packed_by_blocks(tsp, oracle, rows, left):
     """Rows of B around the lengths from which a wave, or all waves of a block, take them (128, 1024), at the ends of a block's
