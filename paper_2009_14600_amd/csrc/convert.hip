@@ -568,13 +568,22 @@ __global__ __launch_bounds__(conv_block_threads<G>()) __attribute__((amdgpu_wave
 // for such tile-rows (sixteen steps of the whole block, 127 registers): 27-point stencil with 3 unknowns on 48^3 nodes
 // 272 -> 152 us, 131072 rows of 4 half-full tiles 54 -> 45 us.  Asking for the next tile-row's entries ahead costs
 // registers, and with them more than it gives (213 and 48 us).
+// Of few entries per thread (kCache 3; registers for seven blocks on a CU) the LDS is kept to as many: the bitmap lies in the
+// second half of the image, which only windows of more than 16 tiles use, and where a tile-row has eight tiles at most both
+// forms are put together at once, three barriers less.  131072 rows of 4 half-full tiles, 512 entries per tile-row 43.3 -> 37.5
+// us, half of it from three registers per thread instead of four; 24576 rows of them, fp32, 10.8 -> 9.0.  For longer tile-rows,
+// which as a rule are of more tiles and whose registers allow six blocks anyway, it costs a barrier: the stencil 150 -> 157 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int kBlockTiles = 32;          // tiles of a window
 constexpr int kBlockWords = 1024;        // bitmap words: tile columns may span 32768
+static_assert(kBlockWords * 8 <= kBlockTiles * 16 * 16);
 template <int kCache, typename RP, typename VT>
-__global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_block(const ConvArgs<RP, VT> a) {
+__global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) void k_convert_block(const ConvArgs<RP, VT> a) {
     __shared__ uint4 s_image[kBlockTiles * 32];
-    __shared__ uint2 s_bm[kBlockWords];                          // {tile columns, tiles before the word}
+    // (few entries: of few tiles, as a rule, and the bitmap lies where the second half of the image will be)
+    constexpr bool kShared = kCache == 3;
+    __shared__ uint2 s_bitmap[kShared ? 1 : kBlockWords];        // {tile columns, tiles before the word}
+    uint2 *const s_bm = kShared ? reinterpret_cast<uint2 *>(s_image + kBlockTiles * 16) : s_bitmap;
     __shared__ uint32_t s_mask[kBlockTiles * 8];
     __shared__ uint32_t s_lm[kBlockTiles + 1], s_rm[kBlockTiles + 1], s_lat[kBlockTiles], s_rat[kBlockTiles];
     __shared__ int s_rp_all[kConvThreads / 64][20];
@@ -627,7 +636,7 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_bl
             p_reg[k] = a.col[max(e - 1, e0)];
             v_reg[k] = a.val[e];
         }
-        for (int i = tid; i < kBlockTiles * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
+        for (int i = tid; i < kBlockTiles * (kShared ? 16 : 32); i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
         if (tid < kBlockTiles * 8) s_mask[tid] = 0;
         rp = -wave_max(-lo) >> 4;                                // (from here on: first tile column)
         bad |= lo < 0;
@@ -691,12 +700,13 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_bl
     uint32_t lrun = (uint32_t)e0, rrun = (uint32_t)e0;
     uint16_t *const image16 = reinterpret_cast<uint16_t *>(s_image);
     const bool both = (a.forms & TSP_FORM_LEFT) && (a.forms & TSP_FORM_RIGHT);
+    const bool at_once = kShared && both && ntiles <= kBlockTiles / 4;      // half the image holds both forms
     for (int win0 = 0; win0 < ntiles; win0 += kBlockTiles) {
         const int nw = min(kBlockTiles, ntiles - win0);
-        if (win0 > 0) {
+        if (win0 > 0 || (kShared && nw > kBlockTiles / 2)) {
             __syncthreads();
-            for (int i = tid; i < nw * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
-            if (tid < kBlockTiles * 8) s_mask[tid] = 0;
+            for (int i = tid + (win0 > 0 ? 0 : kBlockTiles * 16); i < nw * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
+            if (win0 > 0 && tid < kBlockTiles * 8) s_mask[tid] = 0;
             __syncthreads();
         }
         // 3. bitmaps, and the values of the first form
@@ -711,6 +721,8 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_bl
                     const uint32_t at = left ? (x & ~0xFFu) | (x & 8u) << 4 | (x >> 1 & 0x78u) | (x & 7u)
                                              : (x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u);
                     image16[at] = to_half_bits(v_reg[k]);
+                    if (masks && at_once)                        // (the right form behind the left one)
+                        image16[kBlockTiles / 4 * 256 + ((x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u))] = to_half_bits(v_reg[k]);
                 }
             }
         };
@@ -742,11 +754,11 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_bl
         }
         if (wave == 1 && lane < nw * 2)
             reinterpret_cast<uint4 *>(a.row_mask + (int64_t)(e0 + win0) * T)[lane] = reinterpret_cast<const uint4 *>(s_mask)[lane];
-        auto write = [&](uint4 *data, const uint32_t *masks, const uint32_t *tile_at) {
+        auto write = [&](uint4 *data, const uint32_t *masks, const uint32_t *tile_at, const uint4 *image) {
             for (int t = wave * 2 + half; t < nw; t += kConvThreads / 32) {
                 const uint32_t mask = masks[t];
                 const uint32_t to = (uint32_t)tile_at[t] + (uint32_t)__popc(mask & ((1u << g) - 1u));
-                if ((mask >> g) & 1u) data[to] = s_image[t * 32 + g];
+                if ((mask >> g) & 1u) data[to] = image[t * 32 + g];
             }
         };
         if (lane < kBlockTiles) {                                // (the same from every wave)
@@ -754,15 +766,17 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : 6) void k_convert_bl
             s_rat[lane] = rat;
         }
         wave_sync();
-        if (a.forms & TSP_FORM_LEFT) write(a.ldata, s_lm, s_lat);
-        else write(a.rdata, s_rm, s_rat);
-        if (both) {
+        if (a.forms & TSP_FORM_LEFT) write(a.ldata, s_lm, s_lat, s_image);
+        else write(a.rdata, s_rm, s_rat, s_image);
+        if (at_once) {
+            write(a.rdata, s_rm, s_rat, s_image + kBlockTiles / 4 * 32);
+        } else if (both) {
             __syncthreads();
             for (int i = tid; i < nw * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
             __syncthreads();
             place(false, false);
             __syncthreads();
-            write(a.rdata, s_rm, s_rat);
+            write(a.rdata, s_rm, s_rat, s_image);
         }
         lrun += (uint32_t)__builtin_amdgcn_readlane((int)linc, 63);
         rrun += (uint32_t)__builtin_amdgcn_readlane((int)rinc, 63);
@@ -938,8 +952,10 @@ static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, in
         // nodes, 135 and 162 entries per row: 305 and 452 us, 597 and 848 with every tile-row listed)
         else if (per_row > kConvThreads * 8) hipLaunchKernelGGL((k_convert_rows<256, 8, RP, VT>), rows, threads, 0, s, a);
         else {
-            const int cache = want <= 4 ? 4 : want <= 6 ? 6 : 8;
-            auto kernel = cache == 4 ? k_convert_block<4, RP, VT> : cache == 6 ? k_convert_block<6, RP, VT> : k_convert_block<8, RP, VT>;
+            // (three registers: 30 % more than the mean, since the tile-rows beyond are listed)
+            const int cache = per_row * 13 / 10 <= 3 * kConvThreads ? 3 : want <= 4 ? 4 : want <= 6 ? 6 : 8;
+            auto kernel = cache == 3 ? k_convert_block<3, RP, VT> : cache == 4 ? k_convert_block<4, RP, VT>
+                          : cache == 6 ? k_convert_block<6, RP, VT> : k_convert_block<8, RP, VT>;
             hipLaunchKernelGGL(kernel, rows, threads, 0, s, a);
             if (which == kAllRows && std::min(A->nnz, A->cols * T) > kConvThreads * cache)
                 hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min(ntr, kLargeBlocks)), threads, 0, s, a, (int64_t)-1);

@@ -87,6 +87,20 @@ def test_tile_rows_of_many_entries(tsp, oracle, cols, tiles, entries, upload):
         h.close()
 
 
+@pytest.mark.parametrize("cols,tiles,entries", [
+    (4096, (8, 9, 7, 1), (600, 560, 500, 256)),                # both forms at once, up to eight tiles
+    (4096, (15, 16, 17, 18, 8), (767, 768, 769, 30, 400)),     # the bitmap's half of the image; three entries per thread
+    (4096, (32, 33, 65, 3, 250), (560, 570, 600, 500, 520)),   # windows of 32
+    (4096, (4, 5, 6), (590, 590, 590)),                        # the mean up to which three registers are taken
+    (4096, (4, 5, 6), (591, 591, 591)),
+    (524288, (8, 40, 0, 5), (700, 760, 0, 480)),               # spans about the bitmap's
+    (600000, (30, 2, 8), (500, 300, 600)),
+])
+@pytest.mark.parametrize("upload", [{}, {"value_dtype": "f32", "row_ptr_dtype": "i64"}])
+def test_tile_rows_of_500_entries(tsp, oracle, cols, tiles, entries, upload):
+    test_tile_rows_of_many_entries(tsp, oracle, cols, tiles, entries, upload)
+
+
 @pytest.mark.parametrize("tile_rows,large,small", [
     (40, 2100, 0), (40, 2049, 2049), (40, 2060, 2037),      # a mean either side of what k_convert_block is for, all or half of them large
     (1300, 2100, 1500), (2100, 2050, 60),                   # the same with more tile-rows than k_convert_large has blocks
