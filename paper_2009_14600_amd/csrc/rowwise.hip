@@ -7,9 +7,11 @@
 //   k_row_prepare   one pass over an operand: validation, entries as {column, value} records, tiles per tile-row,
 //                   and for A the number of intermediate products of every row and the lists of work
 //   k_row_finish    row_ptr of C; candidate tile pairs (the measure by which tsp_spgemm chooses this path) and other sums
-//   k_row_small     rows with few, short rows of B behind them: a hash table per row in LDS; k_small_copy puts them in place
-//   k_heavy_count   the other rows: a block per row, one bit per column of C in LDS
-//   k_heavy_fill    a block per row and some windows of columns, a dense accumulator in LDS
+//   k_row_small     rows with few, short rows of B behind them: a hash table per row in LDS; k_small_copy puts them in place,
+//                   or k_small_finish, which makes row_ptr as well, where no other rows are expected
+//   k_heavy_pack    B for the other rows: words of 16 columns, entries of 4 bytes
+//   k_heavy_count   their sizes: a block per row, one bit per column of C in LDS
+//   k_heavy_fill    a block per row and some windows of columns, an accumulator in LDS for some thousand entries at a time
 //
 // A product that is repeated on a handle has the same bits every time.  Products of fp16 numbers are exact in fp32.  An entry of a small row is summed in fp32 in
 // the order of the entries of A.  A heavy entry is summed in integers where every partial sum is exact in them (all products
@@ -661,8 +663,8 @@ struct SmallArgs {
 // all of it twice, once for the sizes, costs more than the copy.)
 // Bound by the vector instructions of every wave (61 % of the time on the mesh, LDS 39 %), many of which do not depend on what
 // its rows hold.  Measured, this
-// kernel and the copy, against merging the lists in LDS once to size C and once to fill it: a 512x512 mesh 36 + 13 us (64
-// before), 65536 rows of 8 random entries 45 + 13 us (68), the light rows of R-MAT scale 14 31 + 6 us (135).
+// kernel and the copy, against merging the lists in LDS once to size C and once to fill it: a 512x512 mesh 39 + 12 us (64
+// before), 65536 rows of 8 random entries 39 + 12 us (68), the light rows of R-MAT scale 14 28 + 6 us (135).
 // A whole group per row of B (kNarrow false): one row of B at a time, whose columns are distinct, so no two lanes meet at
 // an entry and the fp32 sums form in the order of the entries of A.  Short rows of B (kNarrow): several at a time, added
 // with LDS atomics in fp64.
@@ -736,7 +738,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
     auto take = [&](const int2 &y, uint32_t f, bool on) {
         bool made = false;
         // (an odd step, by which every slot is met, and of the column: one slot after the other, those of 65,536 rows of 8 random
-        // entries lie so that the kernel takes 44 us instead of 41)
+        // entries lie so that the kernel takes 44 us instead of 41, by 8 lanes to a row)
         const uint32_t hash = (uint32_t)__umul24((uint32_t)y.x, 0x9E3779u), step = hash >> (24 - 2 * bits) | 1u;
         uint32_t slot = (hash >> (24 - bits)) & (uint32_t)(slots - 1);
         if (on)
@@ -2392,9 +2394,11 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     rc = size_rows(false);
     if (rc) return rc;
     phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
-    phase_begin(ctx, TSP_PHASE_COUNT, s);
+    // (row_ptr and the entries by one kernel: it counts as the multiplication)
+    const auto finish_phase = finish_and_copy ? TSP_PHASE_NUMERIC : TSP_PHASE_COUNT;
+    phase_begin(ctx, finish_phase, s);
     if (finish_and_copy) {
-        KernelTimer kt(ctx, TSP_KERNEL_SCAN_ROWS, s);
+        KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
         FinishArgs a = finish_args();
         a.live = nullptr;
         const CopyArgs p{shape, A->rows, small_waves, ma.start, left.ub, found, wave_total, row_ptr, col, val, nullptr};
@@ -2413,7 +2417,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         rc = finish(TSP_KERNEL_SCAN_ROWS);
     }
     ctx->scalars_clean = !rc;                // (it has cleared the scalar block for the next call)
-    phase_end(ctx, TSP_PHASE_COUNT, s);
+    phase_end(ctx, finish_phase, s);
     if (!rc && ahead && !finish_and_copy) rc = multiply(had_small, kind);
     if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);           // the wait that sizes C
     if (rc) return rc;
