@@ -53,29 +53,28 @@ CSRC = os.path.join(ROOT, "paper_2009_14600_amd", "csrc")
 # sym_count the sizing of the small and of the heavy rows, numeric the move into C and the multiplication of the heavy rows.
 #   (workload, kernel): (source file, sha256[:12] at the time, FETCH_SIZE, WRITE_SIZE)
 MEASURED_TRAFFIC = {
-    (1, "convert"): ("rowwise.hip", "1de2d52b8bb4", 87.1, 88.6),
-    (1, "sym_count"): ("rowwise.hip", "1de2d52b8bb4", 360.8, 515.6),
-    (1, "numeric"): ("rowwise.hip", "1de2d52b8bb4", 283.0, 500.2),
-    (2, "convert"): ("rowwise.hip", "1de2d52b8bb4", 5383.2, 13668.6),
-    (2, "sym_count"): ("rowwise.hip", "1de2d52b8bb4", 9904.2, 28152.0),
-    (2, "scan_rows"): ("rowwise.hip", "1de2d52b8bb4", 752.5, 1877.9),
-    (2, "numeric"): ("rowwise.hip", "1de2d52b8bb4", 17402.2, 27069.3),
-    (3, "convert"): ("convert.hip", "30d2ada6508e", 83544.7, 241148.2),
-    (3, "sym_count"): ("symbolic.hip", "dffb5d515039", 22560.9, 3241.8),
-    (3, "scan_sym"): ("symbolic.hip", "dffb5d515039", 317.9, 251.3),
-    (3, "sym_emit"): ("symbolic.hip", "dffb5d515039", 77298.0, 267213.2),
+    (1, "convert"): ("rowwise.hip", "f2fa3320655c", 89.9, 88.6),
+    (1, "sym_count"): ("rowwise.hip", "f2fa3320655c", 357.1, 523.7),
+    (1, "numeric"): ("rowwise.hip", "f2fa3320655c", 289.5, 501.9),
+    (2, "convert"): ("rowwise.hip", "f2fa3320655c", 5386.3, 13671.7),
+    (2, "sym_count"): ("rowwise.hip", "f2fa3320655c", 11149.6, 28384.8),
+    (2, "numeric"): ("rowwise.hip", "f2fa3320655c", 15153.5, 28816.1),
+    (3, "convert"): ("convert.hip", "258e14ff8cb7", 83543.6, 241187.2),
+    (3, "sym_count"): ("symbolic.hip", "dffb5d515039", 22573.7, 3240.9),
+    (3, "scan_sym"): ("symbolic.hip", "dffb5d515039", 318.2, 250.0),
+    (3, "sym_emit"): ("symbolic.hip", "dffb5d515039", 76941.1, 267118.3),
     (3, "scan_rows"): ("symbolic.hip", "dffb5d515039", 994.3, 2592.6),
-    (3, "numeric"): ("numeric.hip", "2aade73456b3", 339906.9, 1188227.1),
-    (4, "convert"): ("rowwise.hip", "1de2d52b8bb4", 30111.4, 85359.7),
-    (4, "sym_count"): ("rowwise.hip", "1de2d52b8bb4", 13099154.8, 5356811.1),
-    (4, "scan_rows"): ("rowwise.hip", "1de2d52b8bb4", 752.5, 1877.9),
-    (4, "numeric"): ("rowwise.hip", "1de2d52b8bb4", 40555674.8, 23220958.4),
-    (5, "convert"): ("convert.hip", "30d2ada6508e", 14149.8, 36641.8),
+    (3, "numeric"): ("numeric.hip", "2aade73456b3", 339914.1, 1188241.3),
+    (4, "convert"): ("rowwise.hip", "f2fa3320655c", 30061.9, 85598.5),
+    (4, "sym_count"): ("rowwise.hip", "f2fa3320655c", 6842474.1, 5335392.4),
+    (4, "scan_rows"): ("rowwise.hip", "f2fa3320655c", 754.0, 1877.9),
+    (4, "numeric"): ("rowwise.hip", "f2fa3320655c", 25737409.8, 23205383.9),
+    (5, "convert"): ("convert.hip", "258e14ff8cb7", 14144.8, 36641.8),
     (5, "sym_count"): ("symbolic.hip", "dffb5d515039", 4856.4, 1280.0),
-    (5, "scan_sym"): ("symbolic.hip", "dffb5d515039", 158.6, 98.8),
-    (5, "sym_emit"): ("symbolic.hip", "dffb5d515039", 8707.7, 16309.8),
-    (5, "scan_rows"): ("symbolic.hip", "dffb5d515039", 406.2, 1024.6),
-    (5, "numeric"): ("numeric.hip", "2aade73456b3", 53966.8, 270099.6),
+    (5, "scan_sym"): ("symbolic.hip", "dffb5d515039", 158.4, 98.8),
+    (5, "sym_emit"): ("symbolic.hip", "dffb5d515039", 8707.8, 16309.8),
+    (5, "scan_rows"): ("symbolic.hip", "dffb5d515039", 406.3, 1024.6),
+    (5, "numeric"): ("numeric.hip", "2aade73456b3", 54049.6, 269995.7),
 }
 
 def source_digest(name: str) -> str:
