@@ -34,7 +34,7 @@ constexpr int kPlanSums = 8;
 constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
 constexpr int kSpanWindowsLog = 6, kSpanWindows = 1 << kSpanWindowsLog;   // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
 constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows, those of very long rows of A at any
-constexpr int kCountThreads = 256;       // of k_heavy_count
+constexpr int kCountThreads = 256, kCountThreadsWide = 512;   // of k_heavy_count, and where four of its blocks fill the LDS
 constexpr int32_t kNoCol = 0x7FFFFFFF;
 constexpr int kLongRow = 512;            // entries, for the threads that k_row_prepare gives a tile-row
 constexpr int64_t kFoundEntries = (int64_t)2 << 30;   // of the small rows before they are moved into C, at most
@@ -1252,6 +1252,7 @@ __device__ __forceinline__ void stream_pieces(int p, int len, uint32_t own, cons
 // evenly.
 template <int kThreads>
 struct SegmentList {
+    static_assert((kThreads & (kThreads - 1)) == 0, "the search of stream_share stays inside the list");
     int first[kThreads];                                       // pieces before the segment
     uint2 at[kThreads];                                        // {first element, elements << 16 | 16 bits of its own}
 };
@@ -1304,8 +1305,9 @@ struct CountArgs {
 // A block per heavy row ORs the words of the rows of B behind it into one bit per column in LDS; OR is free of order, so
 // the row may be spread over the block: by pieces of 16 words where every thread has at most one entry of A, else entry i of
 // the row of A goes to wave i mod the number of waves that get 16 and more.
-// Large rows have blocks of 1024 threads, the others, which are bound by the block's own steps, of 256.  All rows by 256
-// threads: R-MAT scale 14 88 us, split 33 + 28; scale 18 5.3 ms, split 3.4 + 1.5.  No more than 80 scalar registers: with the
+// Large rows have blocks of 1024 threads, the others, which are bound by the block's own steps, of 256, or of 512 where C is so
+// wide that the LDS holds four blocks (scale 18 1.54 -> 1.39 ms; scale 16, whose bits are an eighth, 135 -> 220 us).  All rows
+// by 256 threads: R-MAT scale 14 88 us, split 33 + 28; scale 18 5.3 ms, split 3.4 + 1.4.  No more than 80 scalar registers: with the
 // 106 that the compiler takes otherwise a SIMD has 7 waves, and a CU one block of 1024 threads (4.6 instead of 3.9 ms).
 // Bound by round trips to the words: with all words from 2 MB 2.75 instead of 3.7 ms, without the LDS additions no less, with
 // words of half the bytes, or twice as many in flight, no less either.
@@ -2221,8 +2223,10 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             auto kernel = shift == 11 ? k_heavy_count<2048, 1024, true> : k_heavy_count<4096, 1024, true>;
             hipLaunchKernelGGL(kernel, dim3((unsigned)large), dim3(1024), lds, s, c);
         }
-        auto kernel = shift == 11 ? k_heavy_count<2048, kCountThreads, false> : k_heavy_count<4096, kCountThreads, false>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(kCountThreads), lds, s, c);
+        const bool wide = c.span_windows > kSpanWindows / 2;
+        auto kernel = shift == 11 ? k_heavy_count<2048, kCountThreads, false>
+                      : wide      ? k_heavy_count<4096, kCountThreadsWide, false> : k_heavy_count<4096, kCountThreads, false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(wide ? kCountThreadsWide : kCountThreads), lds, s, c);
     };
     // heavy rows whose pattern is kept at a time
     auto pattern_rows = [&](int64_t heavy) { return std::min(heavy, std::max<int64_t>(ctx->pattern_bytes / (((int64_t)windows << shift) / 8), 1)); };

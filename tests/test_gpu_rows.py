@@ -466,6 +466,12 @@ def test_words_of_16_columns(tsp, oracle, cols):
         h.close()
 
 
+@pytest.mark.parametrize("cols", [131072, 131073])
+def test_sizing_of_wide_and_narrow_rows(tsp, oracle, cols):
+    """Either side of the number of columns from which k_heavy_count has 512 threads to a row."""
+    test_words_of_16_columns(tsp, oracle, cols)
+
+
 @pytest.mark.parametrize("values", ["ones", "below one"])
 @pytest.mark.parametrize("cols,large", [(6000, 256), (70001, 512)])
 def test_large_and_light_rows(tsp, oracle, values, cols, large):
