@@ -123,9 +123,27 @@ __device__ __forceinline__ bool small_row(int32_t entries, int32_t products, int
 // them per lane in flight.  The team's bitmap over the tile columns tells the first entry that falls into a tile (the
 // atomic returns the word before): those lanes list the tile.  At the end a lane per row of A says whether the row is
 // small or heavy and lists the heavy one with its tasks.
-template <int kTeam, int kU, typename RP, typename VT>
-__global__ __launch_bounds__(kTeam > 256 ? kTeam : 256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_prepare(const PrepareArgs<RP, VT> a) {
-    constexpr int kTeams = kTeam > 256 ? 1 : 256 / kTeam;
+// Both operands at once (Second not empty) where they are of the same types and take teams of the same size: neither pass
+// needs the other, and one behind the other each waits for its own way to memory and for its last blocks.  A*P on a 64^3 grid
+// 19 + 10 -> 25 us, 4099 rows of 37 entries times as many 11 + 6 -> 11.
+constexpr int prepare_teams(int team) { return team > 256 ? 1 : 256 / team; }     // in a block
+struct NoSecond {};
+template <typename RP, typename VT>
+struct Second {
+    PrepareArgs<RP, VT> args;
+    uint32_t from;                       // the blocks from this one on are for it
+};
+template <int kTeam, int kU, typename RP, typename VT, typename Other = NoSecond>
+__global__ __launch_bounds__(kTeam > 256 ? kTeam : 256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_prepare(const PrepareArgs<RP, VT> operand, const Other other) {
+    constexpr int kTeams = prepare_teams(kTeam);
+    constexpr bool kBoth = !std::is_same<Other, NoSecond>::value;
+    typename std::conditional<kBoth, PrepareArgs<RP, VT>, const PrepareArgs<RP, VT> &>::type a = operand;
+    uint32_t block = blockIdx.x;
+    if constexpr (kBoth)
+        if (block >= other.from) {
+            a = other.args;
+            block -= other.from;
+        }
     if (a.skip && uniform_load(a.skip)) return;
     extern __shared__ uint32_t lds_bitmap[];
     __shared__ int32_t s_ptr[kTeams][T + 1];
@@ -135,7 +153,7 @@ __global__ __launch_bounds__(kTeam > 256 ? kTeam : 256) __attribute__((amdgpu_wa
     const int team = threadIdx.x / kTeam, tid = threadIdx.x % kTeam, lane = lane_id();
     uint32_t *bitmap = lds_bitmap + team * a.bitmap_words;
     const int64_t tile_rows = (a.rows + T - 1) / T;
-    const int64_t I = (int64_t)blockIdx.x * kTeams + team;
+    const int64_t I = (int64_t)block * kTeams + team;
     const bool live = I < tile_rows;
     bool bad = false;
     if (live) {
@@ -1761,17 +1779,21 @@ constexpr int kSampleEntries = 4096;     // ... and entries of each, at most
 // takes 26 ns per thousand entries, the look and the launches that then find nothing to do 20 us together.
 bool sample_pays(int64_t rows, int64_t nnz) { return nnz >= (1 << 18) && nnz > 8 * rows; }
 
+// A wave per tile-row of up to two trips; longer ones get a block, four entries per thread in flight (the hub rows of a graph:
+// one wave took 1.9 ms for the longest tile-row of an R-MAT graph of scale 18)
+template <typename RP, typename VT>
+bool wave_per_tile_row(const PrepareArgs<RP, VT> &a) {
+    return a.nnz <= 128 * ((a.rows + T - 1) / T) && (size_t)a.bitmap_words * 16 <= 60 * 1024;
+}
 template <typename RP, typename VT>
 void launch_prepare(const PrepareArgs<RP, VT> &a, bool long_rows, hipStream_t s) {
     const int64_t tile_rows = (a.rows + T - 1) / T;
     if (tile_rows == 0) return;
-    // A wave per tile-row of up to two trips; longer ones get a block, four entries per thread in flight (the hub rows of
-    // a graph: one wave took 1.9 ms for the longest tile-row of an R-MAT graph of scale 18)
-    if (a.nnz <= 128 * tile_rows && (size_t)a.bitmap_words * 16 <= 60 * 1024)
+    if (wave_per_tile_row(a))
         hipLaunchKernelGGL((k_row_prepare<64, 2, RP, VT>), dim3((unsigned)((tile_rows + 3) / 4)), dim3(256),
-                           (size_t)a.bitmap_words * 16, s, a);
+                           (size_t)a.bitmap_words * 16, s, a, NoSecond{});
     else {
-        auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)tile_rows), dim3(threads), (size_t)a.bitmap_words * 4, s, a); };
+        auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)tile_rows), dim3(threads), (size_t)a.bitmap_words * 4, s, a, NoSecond{}); };
         // The longest tile-row, 3 ns per entry with 256 threads, keeps the launch waiting, where the last product of these sizes
         // had long rows: R-MAT scales 14 / 16 / 18 by 256 threads 64 / 197 / 515 us, by 512 43 / 120 / 345, by 1024 28 / 96 / 437.
         // (Even rows, 80,000 of 12 entries: 20, 30, 38.)
@@ -1779,6 +1801,20 @@ void launch_prepare(const PrepareArgs<RP, VT> &a, bool long_rows, hipStream_t s)
         else if (tile_rows <= 4096) launch(k_row_prepare<1024, 2, RP, VT>, 1024);
         else launch(k_row_prepare<512, 4, RP, VT>, 512);
     }
+}
+template <typename RP, typename VT>
+void launch_prepare_both(const PrepareArgs<RP, VT> &a, const PrepareArgs<RP, VT> &b, bool long_rows, hipStream_t s) {
+    const int64_t a_tile_rows = (a.rows + T - 1) / T, b_tile_rows = (b.rows + T - 1) / T;
+    const bool waves = wave_per_tile_row(a);
+    if (a_tile_rows == 0 || b_tile_rows == 0 || waves != wave_per_tile_row(b) || (!waves && long_rows)) {
+        launch_prepare(a, long_rows, s);
+        launch_prepare(b, false, s);
+        return;
+    }
+    const int teams = prepare_teams(waves ? 64 : 256);
+    const uint32_t a_blocks = (uint32_t)((a_tile_rows + teams - 1) / teams), b_blocks = (uint32_t)((b_tile_rows + teams - 1) / teams);
+    hipLaunchKernelGGL((waves ? k_row_prepare<64, 2, RP, VT, Second<RP, VT>> : k_row_prepare<256, 4, RP, VT, Second<RP, VT>>), dim3(a_blocks + b_blocks), dim3(256),
+                       (size_t)std::max(a.bitmap_words, b.bitmap_words) * 4 * teams, s, a, Second<RP, VT>{b, a_blocks});
 }
 
 // What k_row_prepare needs beyond the operand, for A (null members for B)
@@ -1796,8 +1832,10 @@ struct LeftOperand {
     int64_t heavy_cap, task_cap;
 };
 
-void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const LeftOperand *left, hipStream_t s, const int64_t *skip = nullptr) {
-    auto run = [&](auto rp, auto v) {
+// A, and B unless it is null or A itself
+void prepare(tsp_context *ctx, const tsp_csr *A, const RowMatrix &a_out, const LeftOperand &left, const tsp_csr *B, const RowMatrix &b_out,
+             hipStream_t s, const int64_t *skip) {
+    auto args = [&](auto rp, auto v, const tsp_csr *M, const RowMatrix &out) {
         using RP = decltype(rp);
         using VT = decltype(v);
         PrepareArgs<RP, VT> a{};
@@ -1810,31 +1848,39 @@ void prepare(tsp_context *ctx, const tsp_csr *M, const RowMatrix &out, const Lef
         a.bitmap_words = (int)((M->cols + T * 32 - 1) / (T * 32) + 3) & ~3;
         a.validate = ctx->validate;
         a.out = out;
-        if (left) {
-            a.ub = left->ub;
-            a.products = left->products;
-            a.b_row_ptr = left->B->row_ptr;
-            a.b_is_i64 = left->B->row_ptr_type == TSP_I64;
-            a.b_rows = left->B->rows;
-            a.b_nnz = (int32_t)left->B->nnz;
-            a.small_lanes = left->shape.lanes;
-            a.small_products = left->shape.products;
-            a.windows = left->windows;
-            a.heavy = left->heavy;
-            a.tasks = left->tasks;
-            a.large_products = left->large_products;
-            a.heavy_cap = left->heavy_cap;
-            a.task_cap = left->task_cap;
-            a.rows_of = left->rows_of;
-            a.part_len = left->part_len;
+        if (M == A) {
+            a.ub = left.ub;
+            a.products = left.products;
+            a.b_row_ptr = left.B->row_ptr;
+            a.b_is_i64 = left.B->row_ptr_type == TSP_I64;
+            a.b_rows = left.B->rows;
+            a.b_nnz = (int32_t)left.B->nnz;
+            a.small_lanes = left.shape.lanes;
+            a.small_products = left.shape.products;
+            a.windows = left.windows;
+            a.heavy = left.heavy;
+            a.tasks = left.tasks;
+            a.large_products = left.large_products;
+            a.heavy_cap = left.heavy_cap;
+            a.task_cap = left.task_cap;
+            a.rows_of = left.rows_of;
+            a.part_len = left.part_len;
         }
         a.d_scalars = ctx->d_scalars;
         a.skip = skip;
-        launch_prepare(a, left && left->long_rows, s);
+        return a;
     };
-    const bool f16 = M->val_type == TSP_F16;
-    if (M->row_ptr_type == TSP_I32) f16 ? run(int32_t{}, uint16_t{}) : run(int32_t{}, float{});
-    else f16 ? run(int64_t{}, uint16_t{}) : run(int64_t{}, float{});
+    auto of_types = [](const tsp_csr *M, auto run) {
+        const bool f16 = M->val_type == TSP_F16;
+        if (M->row_ptr_type == TSP_I32) f16 ? run(int32_t{}, uint16_t{}) : run(int32_t{}, float{});
+        else f16 ? run(int64_t{}, uint16_t{}) : run(int64_t{}, float{});
+    };
+    const bool both = B && B != A && A->row_ptr_type == B->row_ptr_type && A->val_type == B->val_type;
+    of_types(A, [&](auto rp, auto v) {
+        if (both) launch_prepare_both(args(rp, v, A, a_out), args(rp, v, B, b_out), left.long_rows, s);
+        else launch_prepare(args(rp, v, A, a_out), left.long_rows, s);
+    });
+    if (B && B != A && !both) of_types(B, [&](auto rp, auto v) { launch_prepare(args(rp, v, B, b_out), false, s); });
 }
 
 void launch_fill(FillArgs &f, FillKind kind, bool short_rows, bool split, hipStream_t s) {
@@ -2096,8 +2142,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     }
     {
         KernelTimer kt(ctx, TSP_KERNEL_CONVERT, s);
-        prepare(ctx, A, ma, &left, s, skip);
-        if (!alias) prepare(ctx, B, mb, nullptr, s, skip);
+        prepare(ctx, A, ma, left, alias ? nullptr : B, mb, s, skip);
     }
     phase_end(ctx, TSP_PHASE_CONVERT, s);
     TSP_HIP_CHECK(ctx, hipGetLastError());
@@ -2278,7 +2323,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             left.tasks = ws.get<int4>((size_t)std::max<int64_t>(n_tasks, 1));
             if (ws.failed) return (int)TSP_ERR_ALLOC_FAILED;
             hipLaunchKernelGGL(k_clear_lists, dim3(1), dim3(64), 0, s, ctx->d_scalars);
-            prepare(ctx, A, ma, &left, s);
+            prepare(ctx, A, ma, left, nullptr, mb, s, nullptr);
             if (again) {
                 const int rc = heavy_arrays();
                 if (rc) return rc;

@@ -421,6 +421,32 @@ def test_lanes_of_few_rows(tsp, oracle, rows, a_row, b_row):
         h.close()
 
 
+@pytest.mark.parametrize("a_row,b_row", [(4, 3), (40, 30), (4, 30), (40, 3)])
+@pytest.mark.parametrize("b_types", [{}, {"value_dtype": "f32"}, {"row_ptr_dtype": "i64"}])
+def test_both_operands_prepared_at_once(tsp, oracle, a_row, b_row, b_types):
+    """Operands of the same and of other types, by a wave per tile-row, by a block, and one by each, with numbers of tile-rows
+    that are no multiple of a block's; repeated, and B not canonical in its last row."""
+    rng = np.random.default_rng(a_row + 10 * b_row)
+    values = lambda m: rng.choice([-1.0, 0.5, 2.0], m)
+    A, B = _exact_lengths(rng, 3005, np.full(333, a_row), values), _exact_lengths(rng, 1777, np.full(3005, b_row), values)
+    dA, dB = tsp.to_device(A), tsp.to_device(B, **b_types)
+    ref = oracle.spgemm(A, B, threads=4)
+    broken = inputs.from_coo(B.rows, B.cols, np.repeat(np.arange(B.rows), b_row), B.col_idx, B.val, "broken")
+    broken.col_idx[-2:] = broken.col_idx[-2:][::-1]
+    h = tsp.Handle(validate=True)
+    try:
+        for _ in range(3):
+            C = h.spgemm(dA, dB)
+            row_ptr, col, val = C.to_host()
+            C.free()
+            assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+            assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+        with pytest.raises(tsp.TspError):
+            h.spgemm(dA, tsp.to_device(broken, **b_types))
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("rows,left", [(3000, 9), (3000, 70), (255, 3)])
 def test_long_rows_of_b_packed_by_blocks(tsp, oracle, rows, left):
     """Rows of B around the lengths from which a wave, or all waves of a block, take them (128, 1024), at the ends of a block's
