@@ -13,10 +13,11 @@
 //   k_heavy_count   their sizes: a block per row, one bit per column of C in LDS
 //   k_heavy_fill    a block per row and some windows of columns, an accumulator in LDS for some thousand entries at a time
 //
-// A product that is repeated on a handle has the same bits every time.  Products of fp16 numbers are exact in fp32.  An entry of a small row is summed in fp32 in
-// the order of the entries of A.  A heavy entry is summed in integers where every partial sum is exact in them (all products
-// are multiples of a power of two that the operands' values say; then the order of the additions does not matter and a
-// whole block shares the accumulator), and otherwise in fp64 by one wave, entry after entry of A or four at a time.
+// A product that is repeated on a handle has the same bits every time.  Products of fp16 numbers are exact in fp32.  An entry of a
+// small row is summed in fp32 in the order of the entries of A, or in fp64 where several short rows of B go at a time.  A heavy
+// entry is summed in integers where every partial sum is exact in them (all products are multiples of a power of two that the
+// operands' values say; then the order of the additions does not matter and a whole block shares the accumulator), and otherwise
+// in fp64 by one wave, entry after entry of A or four at a time.
 #include "common.hpp"
 
 #include <algorithm>
@@ -687,7 +688,7 @@ struct SmallArgs {
 // an entry and the fp32 sums form in the order of the entries of A.  Short rows of B (kNarrow): several at a time, added
 // with LDS atomics in fp64.
 template <int G, bool kNarrow>
-__device__ __forceinline__ void row_small(const SmallArgs &a) {
+__device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t block) {
     constexpr int kRows = 64 / G;        // per wave
     constexpr int kAhead = kNarrow ? G / 2 : G;
     constexpr int32_t kFree = -1;
@@ -695,7 +696,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
     extern __shared__ __align__(16) unsigned char small_lds[];
     __shared__ uint32_t s_len[256 / G];
     const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
-    const uint32_t block = blockIdx.x - (a.sums_first ? (uint32_t)a.sum_blocks : 0u), row = block * (256 / G) + threadIdx.x / G;
+    const uint32_t row = block * (256 / G) + threadIdx.x / G;
     const int slots = a.shape.slots, most = a.shape.products;
     unsigned char *lds = small_lds + wave * a.wave_bytes;
     int32_t *table = reinterpret_cast<int32_t *>(lds) + (lane / G) * slots;
@@ -886,21 +887,6 @@ __device__ __forceinline__ void row_small(const SmallArgs &a) {
         *a.only_small = !(a.d_scalars[S_INVALID] | a.d_scalars[S_ROW_LISTS] | a.d_scalars[S_ROW_LARGE_TASKS]);
 }
 
-template <int G, bool kNarrow>
-__global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin) {
-    __shared__ int s_last;
-    const int sum_block = (int)blockIdx.x - (a.sums_first ? 0 : (int)gridDim.x - a.sum_blocks);
-    if (sum_block >= 0 && sum_block < a.sum_blocks) sum_tile_rows(sums, sum_block, a.sum_blocks, a.finish);
-    else row_small<G, kNarrow>(a);
-    if (!a.finish) return;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left for the last block has arrived
-    __syncthreads();
-    if (threadIdx.x == 0)
-        s_last = atomicAdd(reinterpret_cast<unsigned long long *>(fin.d_scalars + S_ROW_ARRIVED), 1ull) == gridDim.x - 1;
-    __syncthreads();
-    if (s_last) row_finish<true>(fin, 0, 1);
-}
-
 struct CopyArgs {
     SmallShape shape;
     int64_t rows, waves;
@@ -1027,6 +1013,8 @@ struct PackArgs {
     int32_t *span_table;                 // [rows][spans + 1], or null for one span
     int windows, spans, shift;           // a window is 1 << shift columns
     int medium_from;                     // entries from which a row is left to the first blocks
+    int lanes;                           // to a row, of the others
+    uint32_t blocks;
 };
 // Bound by latency: a row's trips wait for each other, and the launch for its longest row (25,000 entries of an R-MAT graph
 // of scale 18).  So rows of more than pack_short entries are left to the first kLongBlocks blocks.  Each looks through a
@@ -1034,13 +1022,13 @@ struct PackArgs {
 // words before a wave's from the others' numbers, and the medium ones by a wave each.  A wave per row throughout was bound by
 // the coming and going of 262,144 waves as well.  R-MAT of scale 13/14/16/18: 14.5/24.5/70/209 -> 8.8/11.1/30/139 us (every
 // long row by all waves 11.5/16/55/245; medium ones up to 2048 entries 13.5/13.5/33/141; 1024 such blocks 10/13/33/136).
-constexpr int kPackThreads = 512, kPackWaves = kPackThreads / 64;
+constexpr int kPackThreads = 512;        // of k_heavy_pack
 constexpr unsigned kLongBlocks = 256;
 constexpr int kPackLong = 1024;
 constexpr int pack_short(int L) { return L == 64 ? kPackLong : 128; }
-template <int L, bool kLong>
+template <int L, bool kLong, int kThreads>
 __device__ __forceinline__ void pack_rows(const PackArgs &a, int64_t first_row) {
-    constexpr int kTrips = kLong ? 4 : 2;
+    constexpr int kTrips = kLong ? 4 : 2, kWaves = kThreads / 64;
     const int l = threadIdx.x % L, lane = lane_id(), span_shift = a.shift + kSpanWindowsLog;
     int64_t row = first_row;
     int32_t s = 0, e = 0, at = 0;
@@ -1117,24 +1105,24 @@ __device__ __forceinline__ void pack_rows(const PackArgs &a, int64_t first_row) 
         }
         close_row();
     } else {
-        __shared__ int64_t s_long[kPackThreads];
-        __shared__ int32_t s_words[2][kPackWaves], s_n[2];
+        __shared__ int64_t s_long[kThreads];
+        __shared__ int32_t s_words[2][kWaves], s_n[2];
         const int wave = threadIdx.x >> 6;
         int round = 0;
         // (neighbours are looked at by different blocks, and those of the next kLongBlocks rows by others again: in graphs the
         // long rows lie together or at regular distances)
-        for (int64_t group = 0; group * kLongBlocks < a.rows; group += kPackThreads) {
+        for (int64_t group = 0; group * kLongBlocks < a.rows; group += kThreads) {
             const int64_t g = group + threadIdx.x, r = g * kLongBlocks + (blockIdx.x + 101 * g) % kLongBlocks;
             if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
             __syncthreads();
             const int32_t len = r < a.rows ? a.start[r + 1] - a.start[r] : 0;
             if (len > kPackLong) s_long[atomicAdd(&s_n[0], 1)] = r;
-            else if (len >= a.medium_from) s_long[kPackThreads - 1 - atomicAdd(&s_n[1], 1)] = r;
+            else if (len >= a.medium_from) s_long[kThreads - 1 - atomicAdd(&s_n[1], 1)] = r;
             __syncthreads();
             const int n_long = s_n[0], n_medium = s_n[1];
             for (int q = 0; q < n_long; ++q) {
                 take_row(s_long[q]);
-                for (int32_t first = s; first < e; first += kPackWaves * kTrips * 64, round ^= 1) {
+                for (int32_t first = s; first < e; first += kWaves * kTrips * 64, round ^= 1) {
                     const int32_t base = first + wave * kTrips * 64;
                     read(base);
                     int n = 0;
@@ -1142,7 +1130,7 @@ __device__ __forceinline__ void pack_rows(const PackArgs &a, int64_t first_row) 
                     for (int u = 0; u < kTrips; ++u) n += __popcll(__ballot(leads(u, base + u * 64 + l)));
                     if (lane == 0) s_words[round][wave] = n;
                     __syncthreads();         // (the other half is written next: nobody is more than a barrier ahead)
-                    const int32_t of = lane < kPackWaves ? s_words[round][lane] : 0;
+                    const int32_t of = lane < kWaves ? s_words[round][lane] : 0;
                     const int32_t inc = (int32_t)wave_inclusive_scan((uint32_t)of), begun = at;
                     at = begun + __builtin_amdgcn_readlane(inc - of, wave);
                     write(base);
@@ -1150,8 +1138,8 @@ __device__ __forceinline__ void pack_rows(const PackArgs &a, int64_t first_row) 
                 }
                 if (wave == 0) close_row();
             }
-            for (int q = wave; q < n_medium; q += kPackWaves) {
-                take_row(s_long[kPackThreads - 1 - q]);
+            for (int q = wave; q < n_medium; q += kWaves) {
+                take_row(s_long[kThreads - 1 - q]);
                 for (int32_t base = s; base < e; base += kTrips * 64) {
                     read(base);
                     write(base);
@@ -1162,10 +1150,42 @@ __device__ __forceinline__ void pack_rows(const PackArgs &a, int64_t first_row) 
         }
     }
 }
-template <int L>
-__global__ __launch_bounds__(kPackThreads) void k_heavy_pack(const PackArgs a) {
-    if (blockIdx.x < kLongBlocks) pack_rows<64, true>(a, 0);
-    else pack_rows<L, false>(a, ((int64_t)(blockIdx.x - kLongBlocks) * kPackThreads + threadIdx.x) / L);
+template <int kThreads>
+__device__ __forceinline__ void pack_block(const PackArgs &a, uint32_t block) {
+    if (block < kLongBlocks) pack_rows<64, true, kThreads>(a, 0);
+    else if (a.lanes == 16) pack_rows<16, false, kThreads>(a, ((int64_t)(block - kLongBlocks) * kThreads + threadIdx.x) / 16);
+    else pack_rows<64, false, kThreads>(a, ((int64_t)(block - kLongBlocks) * kThreads + threadIdx.x) / 64);
+}
+__global__ __launch_bounds__(kPackThreads) void k_heavy_pack(const PackArgs a) { pack_block<kPackThreads>(a, blockIdx.x); }
+struct NoPack {};
+
+// The blocks that sum come first or last.  Before them those of k_heavy_pack (Pack) where B has up to kPackRows rows: they need
+// nothing of the small rows, and both are bound by latency.  The two kernels, one behind the other and at once: 4099 rows of 37
+// entries times as many 15.5 and 11.6 us, R-MAT of scale 14 39 and 35; products of scale 11 60 and 54, of scale 16, with 12 entries
+// per row, 945 and 950; of scale 18, which fills the chip either way and has fewer waves here, the two 434 and 476.
+constexpr int64_t kPackRows = 1 << 15;
+template <int G, bool kNarrow, typename Pack = NoPack>
+__global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin, const Pack pack) {
+    __shared__ int s_last;
+    uint32_t block = blockIdx.x, blocks = gridDim.x;
+    if constexpr (!std::is_same<Pack, NoPack>::value) {
+        if (block < pack.blocks) {
+            pack_block<256>(pack, block);
+            return;
+        }
+        block -= pack.blocks;
+        blocks -= pack.blocks;
+    }
+    const int sum_block = (int)block - (a.sums_first ? 0 : (int)blocks - a.sum_blocks);
+    if (sum_block >= 0 && sum_block < a.sum_blocks) sum_tile_rows(sums, sum_block, a.sum_blocks, a.finish);
+    else row_small<G, kNarrow>(a, block - (a.sums_first ? (uint32_t)a.sum_blocks : 0u));
+    if (!a.finish) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left for the last block has arrived
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_last = atomicAdd(reinterpret_cast<unsigned long long *>(fin.d_scalars + S_ROW_ARRIVED), 1ull) == blocks - 1;
+    __syncthreads();
+    if (s_last) row_finish<true>(fin, 0, 1);
 }
 
 // 64 pieces of up to 16 elements of B, four to a step: lane 16 q + t describes piece 4 t + q by the byte offset of its first
@@ -1325,8 +1345,8 @@ struct CountArgs {
 // the row of A goes to wave i mod the number of waves that get 16 and more.
 // Large rows have blocks of 1024 threads, the others, which are bound by the block's own steps, of 256, or of 512 where C is so
 // wide that the LDS holds four blocks (scale 18 1.54 -> 1.39 ms; scale 16, whose bits are an eighth, 135 -> 220 us).  All rows
-// by 256 threads: R-MAT scale 14 88 us, split 33 + 28; scale 18 5.3 ms, split 3.4 + 1.4.  No more than 80 scalar registers: with the
-// 106 that the compiler takes otherwise a SIMD has 7 waves, and a CU one block of 1024 threads (4.6 instead of 3.9 ms).
+// by 256 threads: R-MAT scale 14 88 us, split 33 + 28; scale 18 5.3 ms, split 3.4 + 1.4.  No more than 80 scalar registers: with
+// the 106 that the compiler takes otherwise a SIMD has 7 waves, and a CU one block of 1024 threads (4.6 instead of 3.9 ms).
 // Bound by round trips to the words: with all words from 2 MB 2.75 instead of 3.7 ms, without the LDS additions no less, with
 // words of half the bytes, or twice as many in flight, no less either.
 template <int kWin, int kThreads, bool kLargeRows>
@@ -2330,20 +2350,24 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
             }
         }
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
-        auto kernel = shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true> : k_row_small<8, false>)
-                                       : (shape.narrow() ? k_row_small<16, true> : k_row_small<16, false>);
         m.finish = finish_too;
-        hipLaunchKernelGGL(kernel, dim3(small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums,
-                           finish_too ? finish_args() : FinishArgs{});
+        auto launch = [&](auto kernel, const auto &p, unsigned pack_blocks) {
+            hipLaunchKernelGGL(kernel, dim3(pack_blocks + small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums,
+                               finish_too ? finish_args() : FinishArgs{}, p);
+        };
+        const bool at_once = n_heavy > 0 && B->rows <= kPackRows;
+        PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, span_table, windows, spans, shift, 0, 0, 0};
+        p.lanes = B->nnz > 64 * B->rows ? 64 : 16;                       // (a wave per row where the mean row fills it)
+        p.medium_from = pack_short(p.lanes) + 1;
+        p.blocks = kLongBlocks + (uint32_t)((B->rows * p.lanes + (at_once ? 255 : kPackThreads - 1)) / (at_once ? 256 : kPackThreads));
+        if (at_once)
+            launch(shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true, PackArgs> : k_row_small<8, false, PackArgs>)
+                                    : (shape.narrow() ? k_row_small<16, true, PackArgs> : k_row_small<16, false, PackArgs>), p, p.blocks);
+        else
+            launch(shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true> : k_row_small<8, false>)
+                                    : (shape.narrow() ? k_row_small<16, true> : k_row_small<16, false>), NoPack{}, 0);
         if (n_heavy > 0) {
-            PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, span_table, windows, spans, shift, 0};
-            // (a wave per row where the mean row fills it)
-            const bool dense = B->nnz > 64 * B->rows;
-            const int64_t lanes = dense ? 64 : 16;
-            p.medium_from = pack_short((int)lanes) + 1;
-            hipLaunchKernelGGL(dense ? k_heavy_pack<64> : k_heavy_pack<16>,
-                               dim3(kLongBlocks + (unsigned)((B->rows * lanes + kPackThreads - 1) / kPackThreads)),
-                               dim3(kPackThreads), 0, s, p);
+            if (!at_once) hipLaunchKernelGGL(k_heavy_pack, dim3(p.blocks), dim3(kPackThreads), 0, s, p);
             c.heavy = left.heavy;
             c.heavy_cap = n_heavy;
             c.d_scalars = ctx->d_scalars;

@@ -447,7 +447,7 @@ def test_both_operands_prepared_at_once(tsp, oracle, a_row, b_row, b_types):
         h.close()
 
 
-@pytest.mark.parametrize("rows,left", [(3000, 9), (3000, 70), (255, 3)])
+@pytest.mark.parametrize("rows,left", [(3000, 9), (3000, 70), (255, 3), (32768, 1), (32769, 2)])      # (either side of a launch for B alone)
 def test_long_rows_of_b_packed_by_blocks(tsp, oracle, rows, left):
     """Rows of B around the lengths from which a wave, or all waves of a block, take them (128, 1024), at the ends of a block's
     rounds (2048 entries), next to each other and 256 rows apart, among short ones (left: 16 lanes to a row, or 64)."""
