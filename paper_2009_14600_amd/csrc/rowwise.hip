@@ -14,10 +14,13 @@
 //   k_heavy_fill    a block per row and some windows of columns, an accumulator in LDS for some thousand entries at a time
 //
 // A product that is repeated on a handle has the same bits every time.  Products of fp16 numbers are exact in fp32.  An entry of a
-// small row is summed in fp32 in the order of the entries of A, or in fp64 where several short rows of B go at a time.  A heavy
-// entry is summed in integers where every partial sum is exact in them (all products are multiples of a power of two that the
-// operands' values say; then the order of the additions does not matter and a whole block shares the accumulator), and otherwise
-// in fp64 by one wave, entry after entry of A or four at a time.
+// small row is summed in fp64 and rounded once where several short rows of B go at a time, and where 16 lanes go to a row though
+// the mean row of A has at most 8 entries (SmallShape::fp64).  Otherwise it is summed in fp32, a row of B at a time: first the
+// products with elements of B that are among the first of their rows (as many as a row has lanes), in the order of the entries
+// of A, then those with elements further on, in the same order.  A heavy entry is summed in integers where every partial sum is
+// exact in them (all products are multiples of a power of two that the operands' values say; then the order of the additions
+// does not matter and a whole block shares the accumulator), and otherwise in fp64 by one wave, entry after entry of A or four
+// at a time.
 #include "common.hpp"
 
 #include <algorithm>
@@ -646,9 +649,10 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
 // many), slots of the row's table (a power of two), and the most products of a small row.
 struct SmallShape {
     int lanes, list_lanes, slots, products;
+    bool fp64;                           // the sums are, also with lists as wide as the group
     bool narrow() const { return list_lanes < lanes; }
     int wave_rows() const { return 64 / lanes; }
-    size_t wave_bytes() const { return (size_t)wave_rows() * (slots * 5 + products * (narrow() ? 12 : 8)); }   // LDS
+    size_t wave_bytes() const { return (size_t)wave_rows() * (slots * 5 + products * (narrow() || fp64 ? 12 : 8)); }   // LDS
 };
 
 struct SmallArgs {
@@ -685,14 +689,15 @@ struct SmallArgs {
 // kernel and the copy, against merging the lists in LDS once to size C and once to fill it: a 512x512 mesh 39 + 12 us (64
 // before), 65536 rows of 8 random entries 39 + 12 us (68), the light rows of R-MAT scale 14 28 + 6 us (135).
 // A whole group per row of B (kNarrow false): one row of B at a time, whose columns are distinct, so no two lanes meet at
-// an entry and the fp32 sums form in the order of the entries of A.  Short rows of B (kNarrow): several at a time, added
-// with LDS atomics in fp64.
-template <int G, bool kNarrow>
+// an entry, and the sums form in a fixed order, in fp32 or in fp64 (kFp64: SmallShape::fp64).  Short rows of B (kNarrow):
+// several at a time, added with LDS atomics in fp64.
+template <int G, bool kNarrow, bool kFp64>
 __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t block) {
     constexpr int kRows = 64 / G;        // per wave
     constexpr int kAhead = kNarrow ? G / 2 : G;
     constexpr int32_t kFree = -1;
-    using Sum = typename std::conditional<kNarrow, double, float>::type;
+    using Sum = typename std::conditional<kFp64, double, float>::type;
+    static_assert(kFp64 || !kNarrow, "several lists at a time add in no order of their own");
     extern __shared__ __align__(16) unsigned char small_lds[];
     __shared__ uint32_t s_len[256 / G];
     const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
@@ -1164,7 +1169,7 @@ struct NoPack {};
 // entries times as many 15.5 and 11.6 us, R-MAT of scale 14 39 and 35; products of scale 11 60 and 54, of scale 16, with 12 entries
 // per row, 945 and 950; of scale 18, which fills the chip either way and has fewer waves here, the two 434 and 476.
 constexpr int64_t kPackRows = 1 << 15;
-template <int G, bool kNarrow, typename Pack = NoPack>
+template <int G, bool kNarrow, bool kFp64, typename Pack = NoPack>
 __global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin, const Pack pack) {
     __shared__ int s_last;
     uint32_t block = blockIdx.x, blocks = gridDim.x;
@@ -1178,7 +1183,7 @@ __global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumA
     }
     const int sum_block = (int)block - (a.sums_first ? 0 : (int)blocks - a.sum_blocks);
     if (sum_block >= 0 && sum_block < a.sum_blocks) sum_tile_rows(sums, sum_block, a.sum_blocks, a.finish);
-    else row_small<G, kNarrow>(a, block - (a.sums_first ? (uint32_t)a.sum_blocks : 0u));
+    else row_small<G, kNarrow, kFp64>(a, block - (a.sums_first ? (uint32_t)a.sum_blocks : 0u));
     if (!a.finish) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left for the last block has arrived
     __syncthreads();
@@ -2075,8 +2080,12 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     // - where more than one row in 64 is small but for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the
     //   lanes 0.1 ns per row; by the last product of these sizes, and where the one at hand turns out otherwise it is started
     //   again).
+    // With 8 lanes rows of 9 to 16 entries are heavy and their sums rounded once; where the first two give them 16 the sums are in
+    // fp64, so that they are rounded once as well, also with a whole group per row of B.  Rows of 5 entries with 9 behind each, 8
+    // lanes / 16 and fp32 / 16 and fp64: 8000 rows 40.7 / 37.4 / 36.4 us, 65,536 70.9 / 64.0 / 65.1, 262,144 196 / 160 / 171; of 3
+    // with 17: 41.5 / 39.2 / 38.0, 72.2 / 67.9 / 69.7, 205 / 176 / 187.
     constexpr int64_t kFewRows = 12288;
-    SmallShape shape{8, 1, 32, 24};
+    SmallShape shape{8, 1, 32, 24, false};
     int lanes_unless_wide = 16, cost_lanes = 16;             // (rows_preferred's times are of 8 lanes for all of few entries)
     {
         const double list = (double)B->nnz / (double)std::max<int64_t>(B->rows, 1), mean = (double)A->nnz / (double)A->rows * list;
@@ -2084,6 +2093,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         shape.products = shape.slots * 3 / 4;
         if (A->nnz <= 8 * A->rows && shape.slots <= 128) cost_lanes = 8;
         if (A->nnz <= 8 * A->rows && shape.slots <= 64 && A->rows > kFewRows) lanes_unless_wide = 8;
+        shape.fp64 = cost_lanes == 8 && lanes_unless_wide == 16;
         shape.lanes = known && hint.wide ? 16 : lanes_unless_wide;
         while (shape.list_lanes < shape.lanes && shape.list_lanes < list) shape.list_lanes *= 2;
     }
@@ -2360,12 +2370,14 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         p.lanes = B->nnz > 64 * B->rows ? 64 : 16;                       // (a wave per row where the mean row fills it)
         p.medium_from = pack_short(p.lanes) + 1;
         p.blocks = kLongBlocks + (uint32_t)((B->rows * p.lanes + (at_once ? 255 : kPackThreads - 1)) / (at_once ? 256 : kPackThreads));
-        if (at_once)
-            launch(shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true, PackArgs> : k_row_small<8, false, PackArgs>)
-                                    : (shape.narrow() ? k_row_small<16, true, PackArgs> : k_row_small<16, false, PackArgs>), p, p.blocks);
-        else
-            launch(shape.lanes == 8 ? (shape.narrow() ? k_row_small<8, true> : k_row_small<8, false>)
-                                    : (shape.narrow() ? k_row_small<16, true> : k_row_small<16, false>), NoPack{}, 0);
+        auto small_rows = [&](auto pack, unsigned pack_blocks) {
+            using Pack = decltype(pack);
+            if (shape.lanes == 8) launch(shape.narrow() ? k_row_small<8, true, true, Pack> : k_row_small<8, false, false, Pack>, pack, pack_blocks);
+            else launch(shape.narrow() ? k_row_small<16, true, true, Pack> : shape.fp64 ? k_row_small<16, false, true, Pack> : k_row_small<16, false, false, Pack>,
+                        pack, pack_blocks);
+        };
+        if (at_once) small_rows(p, p.blocks);
+        else small_rows(NoPack{}, 0);
         if (n_heavy > 0) {
             if (!at_once) hipLaunchKernelGGL(k_heavy_pack, dim3(p.blocks), dim3(kPackThreads), 0, s, p);
             c.heavy = left.heavy;

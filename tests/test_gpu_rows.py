@@ -421,6 +421,41 @@ def test_lanes_of_few_rows(tsp, oracle, rows, a_row, b_row):
         h.close()
 
 
+@pytest.mark.parametrize("rows,a_row,b_row", [(2000, 3, 12), (12288, 2, 9), (12288, 8, 9), (12289, 5, 9), (12289, 3, 13), (20000, 5, 12), (12289, 2, 9), (3000, 7, 3), (3000, 9, 12)])
+def test_sums_of_9_to_16_entries_round_once(tsp, oracle, rows, a_row, b_row):
+    """Rows of 9 to 16 entries with short rows of B behind them, too few of them to be what the lanes are chosen for: where the
+    mean row of A has at most 8 entries they are heavy with 8 lanes to a row (exact sums), and with 16 they are small and have to
+    be summed as well, by narrow lists of B and by wide ones, either side of 12,288 rows and of 48 products.  All products are
+    multiples of 2^-30 below 1: 16 of them add up exactly in fp64 and in integers, and fp32 does not hold them."""
+    rng = np.random.default_rng(rows + 10 * a_row + b_row)
+    values = lambda m: (rng.uniform(2.0 ** -4, 1, m).astype(np.float16) * rng.choice([-1, 1], m)).astype(np.float64)
+    lengths = np.full(rows, a_row)
+    some = np.sort(rng.choice(rows, rows // 70, replace=False))
+    if a_row <= 8:
+        lengths[some] = rng.integers(9, 17, some.size)
+        lengths[np.setdiff1d(np.arange(rows), some)[: int(lengths.sum()) - a_row * rows]] -= 1
+    first = np.where(np.isin(np.arange(rows), some), 0, 100)                    # of 100 rows of B of one entry, or of 400 others
+    col = np.concatenate([np.sort(rng.choice(100 if f == 0 else 400, k, replace=False)) + f for f, k in zip(first, lengths)])
+    A = inputs.from_coo(rows, 500, np.repeat(np.arange(rows), lengths), col, values(col.size), "some of 9 to 16")
+    b_col = np.concatenate([rng.integers(0, 3, 100)] + [np.sort(rng.choice(150, b_row * 5 // 4, replace=False)) for _ in range(400)])
+    B = inputs.from_coo(500, 150, np.repeat(np.arange(500), [1] * 100 + [b_row * 5 // 4] * 400), b_col, values(b_col.size), "short and longer")
+    ref = oracle.spgemm(A, B, threads=4)
+    rounded = np.repeat((lengths > 8) & (a_row <= 8), np.diff(ref.row_ptr))
+    dA, dB = tsp.to_device(A), tsp.to_device(B)
+    h = tsp.Handle()
+    try:
+        for _ in range(3):
+            C = h.spgemm(dA, dB)
+            assert h.stats()["pairs"] == 0
+            row_ptr, col, val = C.to_host()
+            C.free()
+            assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+            assert np.all(np.abs(val - ref.val) <= 16 * 2.0 ** -24 * ref.mag)
+            assert np.array_equal(val[rounded], ref.val[rounded].astype(np.float32))
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("a_row,b_row", [(4, 3), (40, 30), (4, 30), (40, 3)])
 @pytest.mark.parametrize("b_types", [{}, {"value_dtype": "f32"}, {"row_ptr_dtype": "i64"}])
 def test_both_operands_prepared_at_once(tsp, oracle, a_row, b_row, b_types):
