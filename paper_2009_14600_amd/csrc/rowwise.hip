@@ -1827,16 +1827,29 @@ void launch_prepare(const PrepareArgs<RP, VT> &a, bool long_rows, hipStream_t s)
         else launch(k_row_prepare<512, 4, RP, VT>, 512);
     }
 }
+// Two operands go in one launch of k_row_prepare, whose blocks all have the wider one's bitmaps, where neither has less than three
+// quarters of the blocks on a CU for that which it has on its own (registers are for eight; bitmaps of a block in bytes).  A of
+// 262,144 rows and 4000 columns times B of 4000 rows and 700,000 / 800,000 / 1,000,000 / 1,900,000 columns (7, 6, 5, 2 blocks):
+// apart 21 us each, at once 18 / 18 / 22 / 34; 20,000 rows times B of 700,000 / 800,000 / 1,000,000 / 1,900,000 rows and 1000
+// columns: apart 31 / 33 / 38 / 61, at once 27 / 32 / 49 / 151; by 256 threads a tile-row, 3, 4 and 7.8 million columns (6, 5, 2):
+// apart 22, at once 21 / 23 / 42.
+constexpr int prepare_blocks_per_cu(size_t bitmaps) { return (int)std::min<size_t>(8, 160 * 1024 / (bitmaps + 1024)); }
+constexpr bool prepare_at_once(size_t a_bitmaps, size_t b_bitmaps) {
+    return 4 * prepare_blocks_per_cu(std::max(a_bitmaps, b_bitmaps)) >= 3 * prepare_blocks_per_cu(std::min(a_bitmaps, b_bitmaps));
+}
+static_assert(prepare_at_once(64, 64) && prepare_at_once(64, 25 * 1024) && !prepare_at_once(64, 26 * 1024) && !prepare_at_once(64, 60 * 1024));
+static_assert(!prepare_at_once(60 * 1024, 64) && prepare_at_once(59 * 1024, 60 * 1024), "whichever is the wide one");
 template <typename RP, typename VT>
 void launch_prepare_both(const PrepareArgs<RP, VT> &a, const PrepareArgs<RP, VT> &b, bool long_rows, hipStream_t s) {
     const int64_t a_tile_rows = (a.rows + T - 1) / T, b_tile_rows = (b.rows + T - 1) / T;
     const bool waves = wave_per_tile_row(a);
-    if (a_tile_rows == 0 || b_tile_rows == 0 || waves != wave_per_tile_row(b) || (!waves && long_rows)) {
+    const int teams = prepare_teams(waves ? 64 : 256);
+    if (a_tile_rows == 0 || b_tile_rows == 0 || waves != wave_per_tile_row(b) || (!waves && long_rows) ||
+        !prepare_at_once((size_t)a.bitmap_words * 4 * teams, (size_t)b.bitmap_words * 4 * teams)) {
         launch_prepare(a, long_rows, s);
         launch_prepare(b, false, s);
         return;
     }
-    const int teams = prepare_teams(waves ? 64 : 256);
     const uint32_t a_blocks = (uint32_t)((a_tile_rows + teams - 1) / teams), b_blocks = (uint32_t)((b_tile_rows + teams - 1) / teams);
     hipLaunchKernelGGL((waves ? k_row_prepare<64, 2, RP, VT, Second<RP, VT>> : k_row_prepare<256, 4, RP, VT, Second<RP, VT>>), dim3(a_blocks + b_blocks), dim3(256),
                        (size_t)std::max(a.bitmap_words, b.bitmap_words) * 4 * teams, s, a, Second<RP, VT>{b, a_blocks});

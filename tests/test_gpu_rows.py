@@ -482,6 +482,26 @@ def test_both_operands_prepared_at_once(tsp, oracle, a_row, b_row, b_types):
         h.close()
 
 
+@pytest.mark.parametrize("inner,cols", [(3005, 839680), (3005, 839681), (3005, 1966080), (3005, 1966081), (839680, 500), (839681, 500), (1900000, 500), (700000, 839681)])
+@pytest.mark.parametrize("a_row,b_row", [(4, 3), (40, 30)])
+def test_operands_of_unequal_widths(tsp, oracle, inner, cols, a_row, b_row):
+    """One operand of few columns and one of many, either side of the widths up to which both go in one launch of k_row_prepare and
+    up to which a wave takes a tile-row; columns at both ends of the width."""
+    rng = np.random.default_rng(inner + cols + a_row)
+    def even(rows, width, k, of_row):
+        x = np.sort(rng.integers(0, width - k + 1, (rows, k)), axis=1) + np.arange(k)
+        x[::7] += width - 1 - x[::7, -1:]                      # (the last column)
+        return inputs.from_coo(of_row[-1] + 1, width, np.repeat(of_row, k), x.ravel(), rng.choice([-1.0, 0.5, 2.0], rows * k), "even")
+    A = even(333, inner, a_row, np.arange(333))
+    used = np.unique(A.col_idx)
+    B = even(used.size + (used[-1] != inner - 1), cols, b_row, used if used[-1] == inner - 1 else np.append(used, inner - 1))
+    h = tsp.Handle()
+    try:
+        _check(h, tsp, oracle, A, B, calls=3)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("rows,left", [(3000, 9), (3000, 70), (255, 3), (32768, 1), (32769, 2)])      # (either side of a launch for B alone)
 def test_long_rows_of_b_packed_by_blocks(tsp, oracle, rows, left):
     """Rows of B around the lengths from which a wave, or all waves of a block, take them (128, 1024), at the ends of a block's
