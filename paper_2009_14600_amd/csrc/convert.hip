@@ -577,6 +577,11 @@ __global__ __launch_bounds__(conv_block_threads<G>()) __attribute__((amdgpu_wave
 constexpr int kBlockTiles = 32;          // tiles of a window
 constexpr int kBlockWords = 1024;        // bitmap words: tile columns may span 32768
 static_assert(kBlockWords * 8 <= kBlockTiles * 16 * 16);
+// Entries of a tile-row that a block holds.  With three registers a thread's fourth entry, if there is one, waits in LDS: longer
+// tile-rows beside a mean of 500 would be listed otherwise, for a second launch and, in tsp_convert, a second wait (4096
+// tile-rows, one, 1 % or 30 % of them of 900 entries, half of 770: 49.0, 50.1, 71.6, 89.8 us listed, 30.9, 31.4, 33.3, 34.9 here).
+constexpr int conv_block_entries(int cache) { return kConvThreads * (cache == 3 ? 4 : cache); }
+static_assert(conv_block_entries(3) >= conv_block_entries(4), "fewer registers list no more tile-rows");
 template <int kCache, typename RP, typename VT>
 __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) void k_convert_block(const ConvArgs<RP, VT> a) {
     __shared__ uint4 s_image[kBlockTiles * 32];
@@ -584,6 +589,7 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
     constexpr bool kShared = kCache == 3;
     __shared__ uint2 s_bitmap[kShared ? 1 : kBlockWords];        // {tile columns, tiles before the word}
     uint2 *const s_bm = kShared ? reinterpret_cast<uint2 *>(s_image + kBlockTiles * 16) : s_bitmap;
+    __shared__ uint2 s_tail[kShared ? kConvThreads : 1];         // {as p_reg, value} of a thread's fourth entry
     __shared__ uint32_t s_mask[kBlockTiles * 8];
     __shared__ uint32_t s_lm[kBlockTiles + 1], s_rm[kBlockTiles + 1], s_lat[kBlockTiles], s_rat[kBlockTiles];
     __shared__ int s_rp_all[kConvThreads / 64][20];
@@ -604,7 +610,8 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
         bad = raw != (int64_t)rp || (row == 0 && raw != 0) || (row == a.rows && raw != a.nnz);
     }
     const int e0 = __builtin_amdgcn_readlane(rp, 0), e1 = __builtin_amdgcn_readlane(rp, T);
-    const bool large = e1 - e0 > kConvThreads * kCache;
+    const bool large = e1 - e0 > conv_block_entries(kCache);
+    const bool tail = kShared && e1 - e0 > kConvThreads * kCache;    // (the whole block)
     auto finish = [&](int ntiles, int row_class) {
         if (tid == 0) {
             a.tile_row_ptr[I] = e0;
@@ -652,20 +659,24 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
         __syncthreads();
         // 1. tile columns: the first entry of a row in a tile marks it
         const int jmin = rp;
-#pragma unroll
-        for (int k = 0; k < kCache; ++k) {
-            const int e = e0 + tid + k * kConvThreads;
+        auto mark = [&](int e, int c, int before) {
             int r = e >= s_rp[8] ? 8 : 0;
             r += e >= s_rp[r + 4] ? 4 : 0;
             r += e >= s_rp[r + 2] ? 2 : 0;
             r += e >= s_rp[r + 1] ? 1 : 0;
-            const int c = c_reg[k];
             const uint32_t j = (uint32_t)((c >> 4) - jmin);
             const bool on = e < e1, first = e == s_rp[r];
-            if (on && j < (uint32_t)span && (first || (p_reg[k] >> 4) != (c >> 4))) atomicOr(&s_bm[j >> 5].x, 1u << (j & 31));
-            bad |= on && (c < 0 || c >= a.cols || j >= (uint32_t)span || (!first && c <= p_reg[k]));
+            if (on && j < (uint32_t)span && (first || (before >> 4) != (c >> 4))) atomicOr(&s_bm[j >> 5].x, 1u << (j & 31));
+            bad |= on && (c < 0 || c >= a.cols || j >= (uint32_t)span || (!first && c <= before));
             // column in the tile-row's span (all ones: none), row
-            p_reg[k] = on && j < (uint32_t)span ? (int)(j << 8 | r << 4 | (c & 15)) : -1;
+            return on && j < (uint32_t)span ? (int)(j << 8 | r << 4 | (c & 15)) : -1;
+        };
+#pragma unroll
+        for (int k = 0; k < kCache; ++k) p_reg[k] = mark(e0 + tid + k * kConvThreads, c_reg[k], p_reg[k]);
+        if (tail) {
+            const int e = e0 + tid + kCache * kConvThreads, at = min(e, e1 - 1);
+            const VT v = a.val[at];
+            s_tail[tid] = make_uint2((uint32_t)mark(e, a.col[at], a.col[at - 1]), to_half_bits(v));
         }
         __syncthreads();
         // 2. tiles before every word: each wave for itself, a stretch of words per lane
@@ -687,13 +698,15 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
             before += (uint32_t)__popc(s_bm[w].x);
         }
         wave_sync();
-#pragma unroll
-        for (int k = 0; k < kCache; ++k) {
-            const uint32_t x = (uint32_t)p_reg[k], j = x >> 8;
+        auto in_tile = [&](uint32_t x) {
+            const uint32_t j = x >> 8;
             const uint2 word = s_bm[x == 0xFFFFFFFFu ? 0 : j >> 5];
             const uint32_t t = word.y + (uint32_t)__popc(word.x & ((1u << (j & 31)) - 1u));
-            p_reg[k] = x == 0xFFFFFFFFu ? -1 : (int)(t << 8 | (x & 255u));
-        }
+            return x == 0xFFFFFFFFu ? -1 : (int)(t << 8 | (x & 255u));
+        };
+#pragma unroll
+        for (int k = 0; k < kCache; ++k) p_reg[k] = in_tile((uint32_t)p_reg[k]);
+        if (tail) s_tail[tid].x = (uint32_t)in_tile(s_tail[tid].x);
         rp = __builtin_amdgcn_readlane((int)inc, 63);                                        // (from here on: tiles)
     }
     const int ntiles = rp;
@@ -711,20 +724,22 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
         }
         // 3. bitmaps, and the values of the first form
         auto place = [&](bool left, bool masks) {
-#pragma unroll
-            for (int k = 0; k < kCache; ++k) {
+            auto put = [&](uint32_t entry, uint16_t value) {
                 // bits of x: 7-4 row, 3-0 column; the place in the image has the upper bit of the one, the other, and the
                 // lower bits of the one
-                const uint32_t x = (uint32_t)p_reg[k] - (uint32_t)win0 * 256u;
+                const uint32_t x = entry - (uint32_t)win0 * 256u;
                 if (x < (uint32_t)nw * 256u) {
                     if (masks) atomicOr(&s_mask[x >> 5], 1u << (x & 31u));
                     const uint32_t at = left ? (x & ~0xFFu) | (x & 8u) << 4 | (x >> 1 & 0x78u) | (x & 7u)
                                              : (x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u);
-                    image16[at] = to_half_bits(v_reg[k]);
+                    image16[at] = value;
                     if (masks && at_once)                        // (the right form behind the left one)
-                        image16[kBlockTiles / 4 * 256 + ((x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u))] = to_half_bits(v_reg[k]);
+                        image16[kBlockTiles / 4 * 256 + ((x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u))] = value;
                 }
-            }
+            };
+#pragma unroll
+            for (int k = 0; k < kCache; ++k) put((uint32_t)p_reg[k], to_half_bits(v_reg[k]));
+            if (tail) put(s_tail[tid].x, (uint16_t)s_tail[tid].y);
         };
         place((a.forms & TSP_FORM_LEFT) != 0, true);
         __syncthreads();
@@ -952,12 +967,12 @@ static int launch_convert(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, in
         // nodes, 135 and 162 entries per row: 305 and 452 us, 597 and 848 with every tile-row listed)
         else if (per_row > kConvThreads * 8) hipLaunchKernelGGL((k_convert_rows<256, 8, RP, VT>), rows, threads, 0, s, a);
         else {
-            // (three registers: 30 % more than the mean, since the tile-rows beyond are listed)
+            // (three registers: 30 % more than the mean, beyond which many tile-rows would have their fourth entries in LDS)
             const int cache = per_row * 13 / 10 <= 3 * kConvThreads ? 3 : want <= 4 ? 4 : want <= 6 ? 6 : 8;
             auto kernel = cache == 3 ? k_convert_block<3, RP, VT> : cache == 4 ? k_convert_block<4, RP, VT>
                           : cache == 6 ? k_convert_block<6, RP, VT> : k_convert_block<8, RP, VT>;
             hipLaunchKernelGGL(kernel, rows, threads, 0, s, a);
-            if (which == kAllRows && std::min(A->nnz, A->cols * T) > kConvThreads * cache)
+            if (which == kAllRows && std::min(A->nnz, A->cols * T) > conv_block_entries(cache))
                 hipLaunchKernelGGL((k_convert_large<RP, VT>), dim3((unsigned)std::min(ntr, kLargeBlocks)), threads, 0, s, a, (int64_t)-1);
         }
         if (may_merge)

@@ -93,7 +93,10 @@ def test_tile_rows_of_many_entries(tsp, oracle, cols, tiles, entries, upload):
     (4096, (32, 33, 65, 3, 250), (560, 570, 600, 500, 520)),   # windows of 32
     (4096, (4, 5, 6), (590, 590, 590)),                        # the mean up to which three registers are taken
     (4096, (4, 5, 6), (591, 591, 591)),
+    (4096, (8, 8, 9, 4, 1, 5, 1), (1024, 1023, 1025, 769, 100, 100, 16)),      # a fourth entry of all threads, of one, one entry too many
+    (4096, (16, 17, 33, 2, 3), (1024, 900, 770, 30, 20)),
     (524288, (8, 40, 0, 5), (700, 760, 0, 480)),               # spans about the bitmap's
+    (524288, (40, 8, 2, 1), (1000, 800, 100, 30)),
     (600000, (30, 2, 8), (500, 300, 600)),
 ])
 @pytest.mark.parametrize("upload", [{}, {"value_dtype": "f32", "row_ptr_dtype": "i64"}])
