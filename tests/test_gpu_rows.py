@@ -409,14 +409,17 @@ def test_lanes_of_few_rows(tsp, oracle, rows, a_row, b_row):
     values = lambda m: rng.normal(size=m)
     B = _exact_lengths(rng, 5003, np.full(2000, b_row), values)
     even = np.full(rows, a_row)
-    wide = np.zeros(rows, np.int64)
-    wide[:: 15 if a_row == 1 else 5] = 15 if a_row == 1 else min(5 * a_row, 16)
-    wide[-1] += even.sum() - wide.sum()
+    # every 15th or 5th row of 10 to 16 entries, the others as even as what is left for them goes
+    every, entries = (15, 15) if a_row == 1 else (5, min(5 * a_row, 16))
+    longer = np.arange(rows) % every == 3
+    longer[rows // every * every:] = False
+    left, others = rows * a_row - entries * longer.sum(), rows - longer.sum()
+    wide = np.where(longer, entries, left // others + (np.cumsum(~longer) <= left % others))
+    assert wide.sum() == even.sum() and wide.min() >= 0 and 9 <= wide.max() <= 16
     h = tsp.Handle()
     try:
         for l in (even, wide, even):
-            if l.min() >= 0 and l.max() <= 2000:
-                _check(h, tsp, oracle, _exact_lengths(rng, 2000, l, values), B, by_rows=None)
+            _check(h, tsp, oracle, _exact_lengths(rng, 2000, l, values), B, by_rows=None)
     finally:
         h.close()
 
