@@ -264,9 +264,10 @@ class Handle:
         raise RuntimeError("device pointer does not belong to this handle")
 
     def close(self):
-        if self._h:
-            self._lib.tsp_destroy(self._h)
-            self._h = ctypes.c_void_p()
+        # (given up first, and by nothing that is gone when the interpreter ends: destroyed once, whatever fails afterwards)
+        handle, self._h = self._h, None
+        if handle:
+            self._lib.tsp_destroy(handle)
             self._blocks.clear()
             self._typed.clear()
 

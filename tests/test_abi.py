@@ -77,3 +77,25 @@ def test_every_result_is_a_tensor_of_its_own():
     second.resize_(10)
     assert h._view(block.data_ptr(), 100, torch.float32).shape == (100,)
     assert h._view(block.data_ptr(), 7, torch.int64).shape == (7,)
+
+
+def test_a_handle_is_destroyed_once(monkeypatch):
+    """Also where a program that ends has lost the modules: __del__ closes again what a close before it did not come through."""
+    from paper_2009_14600_amd import tsp
+    destroyed = []
+
+    class Lib:
+        def tsp_destroy(self, handle):
+            destroyed.append(handle)
+            return 0
+    h = object.__new__(tsp.Handle)
+    h._lib, h._h, h._blocks, h._typed = Lib(), ctypes.c_void_p(16), {1: 2}, {}
+    with monkeypatch.context() as gone:
+        gone.setattr(tsp, "ctypes", None)
+        try:
+            h.close()
+        except AttributeError:
+            pass
+        h.__del__()
+    h.close()
+    assert len(destroyed) == 1 and not h._blocks
