@@ -569,10 +569,11 @@ __global__ __launch_bounds__(conv_block_threads<G>()) __attribute__((amdgpu_wave
 // 272 -> 152 us, 131072 rows of 4 half-full tiles 54 -> 45 us.  Asking for the next tile-row's entries ahead costs
 // registers, and with them more than it gives (213 and 48 us).
 // Of few entries per thread (kCache 3; registers for seven blocks on a CU) the LDS is kept to as many: the bitmap lies in the
-// second half of the image, which only windows of more than 16 tiles use, and where a tile-row has eight tiles at most both
-// forms are put together at once, three barriers less.  131072 rows of 4 half-full tiles, 512 entries per tile-row 43.3 -> 37.5
-// us, half of it from three registers per thread instead of four; 24576 rows of them, fp32, 10.8 -> 9.0.  For longer tile-rows,
-// which as a rule are of more tiles and whose registers allow six blocks anyway, it costs a barrier: the stencil 150 -> 157 us.
+// second half of the image, which only windows of more than 16 tiles use.  131072 rows of 4 half-full tiles, 512 entries per
+// tile-row, 36.6 us: with four registers 40.4, with a bitmap of its own 43.0; 24576 rows of them, fp32, 8.9: 9.8 and 10.4.
+// (Both forms put together at once where a tile-row has eight tiles at most, three barriers less, gave 0.2 us of the 36.6 and
+// nothing of the 8.9.)  For longer tile-rows, which as a rule are of more tiles and whose registers allow six blocks anyway, the
+// shared half costs a barrier: the stencil 150 -> 157 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int kBlockTiles = 32;          // tiles of a window
 constexpr int kBlockWords = 1024;        // bitmap words: tile columns may span 32768
@@ -713,7 +714,6 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
     uint32_t lrun = (uint32_t)e0, rrun = (uint32_t)e0;
     uint16_t *const image16 = reinterpret_cast<uint16_t *>(s_image);
     const bool both = (a.forms & TSP_FORM_LEFT) && (a.forms & TSP_FORM_RIGHT);
-    const bool at_once = kShared && both && ntiles <= kBlockTiles / 4;      // half the image holds both forms
     for (int win0 = 0; win0 < ntiles; win0 += kBlockTiles) {
         const int nw = min(kBlockTiles, ntiles - win0);
         if (win0 > 0 || (kShared && nw > kBlockTiles / 2)) {
@@ -733,8 +733,6 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
                     const uint32_t at = left ? (x & ~0xFFu) | (x & 8u) << 4 | (x >> 1 & 0x78u) | (x & 7u)
                                              : (x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u);
                     image16[at] = value;
-                    if (masks && at_once)                        // (the right form behind the left one)
-                        image16[kBlockTiles / 4 * 256 + ((x & ~0x7Fu) | (x & 15u) << 3 | (x >> 4 & 7u))] = value;
                 }
             };
 #pragma unroll
@@ -769,11 +767,11 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
         }
         if (wave == 1 && lane < nw * 2)
             reinterpret_cast<uint4 *>(a.row_mask + (int64_t)(e0 + win0) * T)[lane] = reinterpret_cast<const uint4 *>(s_mask)[lane];
-        auto write = [&](uint4 *data, const uint32_t *masks, const uint32_t *tile_at, const uint4 *image) {
+        auto write = [&](uint4 *data, const uint32_t *masks, const uint32_t *tile_at) {
             for (int t = wave * 2 + half; t < nw; t += kConvThreads / 32) {
                 const uint32_t mask = masks[t];
                 const uint32_t to = (uint32_t)tile_at[t] + (uint32_t)__popc(mask & ((1u << g) - 1u));
-                if ((mask >> g) & 1u) data[to] = image[t * 32 + g];
+                if ((mask >> g) & 1u) data[to] = s_image[t * 32 + g];
             }
         };
         if (lane < kBlockTiles) {                                // (the same from every wave)
@@ -781,17 +779,15 @@ __global__ __launch_bounds__(kConvThreads, kCache > 6 ? 5 : kCache > 3 ? 6 : 7) 
             s_rat[lane] = rat;
         }
         wave_sync();
-        if (a.forms & TSP_FORM_LEFT) write(a.ldata, s_lm, s_lat, s_image);
-        else write(a.rdata, s_rm, s_rat, s_image);
-        if (at_once) {
-            write(a.rdata, s_rm, s_rat, s_image + kBlockTiles / 4 * 32);
-        } else if (both) {
+        if (a.forms & TSP_FORM_LEFT) write(a.ldata, s_lm, s_lat);
+        else write(a.rdata, s_rm, s_rat);
+        if (both) {
             __syncthreads();
             for (int i = tid; i < nw * 32; i += kConvThreads) s_image[i] = make_uint4(0, 0, 0, 0);
             __syncthreads();
             place(false, false);
             __syncthreads();
-            write(a.rdata, s_rm, s_rat, s_image);
+            write(a.rdata, s_rm, s_rat);
         }
         lrun += (uint32_t)__builtin_amdgcn_readlane((int)linc, 63);
         rrun += (uint32_t)__builtin_amdgcn_readlane((int)rinc, 63);

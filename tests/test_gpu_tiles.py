@@ -88,7 +88,7 @@ def test_tile_rows_of_many_entries(tsp, oracle, cols, tiles, entries, upload):
 
 
 @pytest.mark.parametrize("cols,tiles,entries", [
-    (4096, (8, 9, 7, 1), (600, 560, 500, 256)),                # both forms at once, up to eight tiles
+    (4096, (8, 9, 7, 1), (600, 560, 500, 256)),                # few tiles
     (4096, (15, 16, 17, 18, 8), (767, 768, 769, 30, 400)),     # the bitmap's half of the image; three entries per thread
     (4096, (32, 33, 65, 3, 250), (560, 570, 600, 500, 520)),   # windows of 32
     (4096, (4, 5, 6), (590, 590, 590)),                        # the mean up to which three registers are taken
