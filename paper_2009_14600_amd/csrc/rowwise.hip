@@ -761,8 +761,9 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
     int listed = 0;                                          // columns of the row so far
     auto take = [&](const int2 &y, uint32_t f, bool on) {
         bool made = false;
-        // (an odd step, by which every slot is met, and of the column: one slot after the other, those of 65,536 rows of 8 random
-        // entries lie so that the kernel takes 44 us instead of 41, by 8 lanes to a row)
+        // (an odd step, by which every slot is met, and of the column: one slot after the other the product of 65,536 rows of 8
+        // random entries takes 66.0 us instead of 61.4, of 6 entries, 8 lanes to a row, 52.9 instead of 48.9, a 512 x 512 mesh 66.7
+        // instead of 65.7)
         const uint32_t hash = (uint32_t)__umul24((uint32_t)y.x, 0x9E3779u), step = hash >> (24 - 2 * bits) | 1u;
         uint32_t slot = (hash >> (24 - bits)) & (uint32_t)(slots - 1);
         if (on)
@@ -945,7 +946,8 @@ __global__ __launch_bounds__(256) void k_small_copy(const CopyArgs a) {
 // k_row_finish and k_small_copy at once, for a product launched ahead that is expected to have small rows only: a block takes
 // kSideRows rows, adds up the chunks before theirs and the groups before them in it, writes their row_ptr and moves their
 // entries, flat over the threads, if what is expected holds.  (On a 512 x 512 mesh the two take 7.4 and 12.4 us one behind the
-// other, most of the first in round trips; together 12.3 us, and k_row_small 2 more.)
+// other, most of the first in round trips; together 12.0 us, and k_row_small 2 more.  The products: that mesh 69.5 -> 65.7 us,
+// 65,536 rows of 8 random entries 65.4 -> 61.4, A*P on a 64^3 grid 65.7 -> 63.8.)
 template <int kSideRows>
 __global__ __launch_bounds__(256) void k_small_finish(const FinishArgs a, const CopyArgs c, const uint32_t *part_len, const int32_t *only_small) {
     __shared__ uint64_t lds[256 / 64];
@@ -972,7 +974,8 @@ __global__ __launch_bounds__(256) void k_small_finish(const FinishArgs a, const 
     const uint32_t at = (uint32_t)block_exclusive_scan64<256>(mine, &own, lds);
     if (row < a.rows) a.c_row_ptr[row] = (int64_t)(entries_before + at);
     if (first) publish_sizes(a, totals, standing, (int64_t)entries);
-    // (what Expected::holds says where no heavy row is expected)
+    // (No more than this matters where no row is heavy.  Expected::holds also asks whether the heavy rows' accumulator of the last
+    // product of these sizes would do for the values: where it would not the host has k_small_copy move the entries once more.)
     if (!uniform_load(only_small) || (int64_t)entries > a.expected.nnz) return;
     const int wave_rows = 64 / c.shape.lanes, waves = kSideRows / wave_rows;
     if ((int)threadIdx.x < kSideRows && threadIdx.x % wave_rows == 0) s_first[threadIdx.x / wave_rows] = at;
@@ -1350,8 +1353,10 @@ struct CountArgs {
 // the row of A goes to wave i mod the number of waves that get 16 and more.
 // Large rows have blocks of 1024 threads, the others, which are bound by the block's own steps, of 256, or of 512 where C is so
 // wide that the LDS holds four blocks (scale 18 1.54 -> 1.39 ms; scale 16, whose bits are an eighth, 135 -> 220 us).  All rows
-// by 256 threads: R-MAT scale 14 88 us, split 33 + 28; scale 18 5.3 ms, split 3.4 + 1.4.  No more than 80 scalar registers: with
-// the 106 that the compiler takes otherwise a SIMD has 7 waves, and a CU one block of 1024 threads (4.6 instead of 3.9 ms).
+// by 256 threads: R-MAT scale 14 88 us, split 33 + 28; scale 18 5.3 ms, split 3.4 + 1.4.  All by the threads of the light ones,
+// the products of scale 13 / 14 / 16 / 18: 158 / 294 / 2397 / 19,360 us, split 155 / 273 / 2235 / 19,720.  No more than 80 scalar
+// registers: with the 106 that the compiler takes otherwise a SIMD has 7 waves, and a CU one block of 1024 threads (4.6 instead
+// of 3.9 ms).
 // Bound by round trips to the words: with all words from 2 MB 2.75 instead of 3.7 ms, without the LDS additions no less, with
 // words of half the bytes, or twice as many in flight, no less either.
 template <int kWin, int kThreads, bool kLargeRows>
@@ -1527,8 +1532,11 @@ constexpr int kNarrowColumns = 1 << 14;
 // 8192 / 16,384 / 32,768 products on 14.75 / 14.5 / 14.1; scale 14 (a table for few columns) 235 us, 230, 184 / 178 / 188, and
 // 168 with blocks of 256 threads for the light ones.
 constexpr int kLarge = 32768, kLargeNarrow = 16384;
-// ... in products of so many intermediate ones at least: two launches more pay where they fill the chip (graphs of 1000, 2000,
-// 4000 and 8000 vertices: 116 / 134, 117 / 132, 100 / 112 and 223 / 171 us without and with them).
+// ... in products of so many intermediate ones at least: two launches more pay where they fill the chip.  The products of R-MAT
+// graphs without them and with them, us: of scale 10 and 11 (1.9 and 3.3 million intermediate products) 64 / 83 and 68 / 83,
+// 12 (6.9 and 9.5 million) 87 / 100 and 89 / 104, 13 (27 million) 148 / 155, 14 (101 million) 308 / 273, 16 (1.2 billion)
+// 2452 / 2235, 18 21,860 / 19,720.  (The line was set when more than one kernel was slower; the two meet between 27 and 101 million
+// now.)
 constexpr int64_t kSplitProducts = 8 << 20;
 
 template <typename Acc, int kCap, int kThreads, int kSpan, int kPiece = 16>
@@ -2380,7 +2388,9 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         };
         const bool at_once = n_heavy > 0 && B->rows <= kPackRows;
         PackArgs p{B->rows, mb.start, mb.rec, pack, word, words, table, span_table, windows, spans, shift, 0, 0, 0};
-        p.lanes = B->nnz > 64 * B->rows ? 64 : 16;                       // (a wave per row where the mean row fills it)
+        // (a wave per row where the mean row fills it; for all of them the products of R-MAT graphs of scale 10 to 16 take 1 to 5 %
+        // longer: 12 87.4 -> 91.5 us, 14 274 -> 280, 16 2235 -> 2255)
+        p.lanes = B->nnz > 64 * B->rows ? 64 : 16;
         p.medium_from = pack_short(p.lanes) + 1;
         p.blocks = kLongBlocks + (uint32_t)((B->rows * p.lanes + (at_once ? 255 : kPackThreads - 1)) / (at_once ? 256 : kPackThreads));
         auto small_rows = [&](auto pack, unsigned pack_blocks) {
