@@ -209,7 +209,7 @@ int tsp_trim(tsp_handle handle, void *stream);
  * contents once the stream has reached that point (hipStreamSynchronize, or further work on the
  * same stream).  With TSP_OPT_PHASE_TIMERS the call waits for the end.
  * Operands whose tiles hold little (graphs, meshes with one unknown per node, random matrices) are multiplied row by row
- * instead, with the same result up to the order of the fp32 additions, where that is the faster by an estimate: on one
+ * instead, with the same result up to the rounding of the sums, where that is the faster by an estimate: on one
  * side the rows with many products, the intermediate products and whether integers hold their sums, on the other the
  * candidate pairs of tiles.  C of fewer than 256 rows, or operands of more than 7.8 million columns, 134 million rows or
  * 268 million entries, go by tiles; so do products for whose row kernels the allocator has no memory.  An option that
