@@ -564,10 +564,10 @@ __global__ __launch_bounds__(conv_block_threads<G>()) __attribute__((amdgpu_wave
 // there have to be enough blocks on a CU to wait side by side).  The groups are put together in a dense image of a
 // window of tiles in LDS, where every entry has a place of its own without knowing the others, first the left form, then
 // the right one; empty groups are left out when the image is written.
-// Bound by vector instructions (77 % of the time on the stencil, 61 % on blocks), with LDS beside them (45 %, half of it conflicts,
-// and 30 %) and the barriers.  Measured against convert_rows for such tile-rows (sixteen steps of the whole block, 127 registers): 27-point stencil with 3 unknowns on 48^3 nodes
-// 272 -> 152 us, 131072 rows of 4 half-full tiles 54 -> 45 us.  Asking for the next tile-row's entries ahead costs
-// registers, and with them more than it gives (213 and 48 us).
+// Bound by vector instructions (77 % of the time on the stencil, 61 % on blocks), with LDS beside them (45 %, half of it
+// conflicts, and 30 %) and the barriers.  Measured against convert_rows for such tile-rows (sixteen steps of the whole block,
+// 127 registers): 27-point stencil with 3 unknowns on 48^3 nodes 272 -> 152 us, 131072 rows of 4 half-full tiles 54 -> 45 us.
+// Asking for the next tile-row's entries ahead costs registers, and with them more than it gives (213 and 48 us).
 // Of few entries per thread (kCache 3; registers for seven blocks on a CU) the LDS is kept to as many: the bitmap lies in the
 // second half of the image, which only windows of more than 16 tiles use.  131072 rows of 4 half-full tiles, 512 entries per
 // tile-row, 36.6 us: with four registers 40.4, with a bitmap of its own 43.0; 24576 rows of them, fp32, 8.9: 9.8 and 10.4.
