@@ -57,24 +57,24 @@ MEASURED_TRAFFIC = {
     (1, "sym_count"): ("rowwise.hip", "32e90804bed2", 359.4, 523.7),
     (1, "numeric"): ("rowwise.hip", "32e90804bed2", 289.6, 501.9),
     (2, "convert"): ("rowwise.hip", "32e90804bed2", 5386.2, 13671.7),
-    (2, "sym_count"): ("rowwise.hip", "32e90804bed2", 11156.1, 28384.8),
-    (2, "numeric"): ("rowwise.hip", "32e90804bed2", 15159.9, 28820.5),
-    (3, "convert"): ("convert.hip", "626d7ce04841", 82408.7, 223128.1),
-    (3, "sym_count"): ("symbolic.hip", "dffb5d515039", 22564.2, 3240.9),
-    (3, "scan_sym"): ("symbolic.hip", "dffb5d515039", 318.5, 250.0),
-    (3, "sym_emit"): ("symbolic.hip", "dffb5d515039", 76909.8, 267106.9),
+    (2, "sym_count"): ("rowwise.hip", "32e90804bed2", 11157.0, 28384.8),
+    (2, "numeric"): ("rowwise.hip", "32e90804bed2", 15159.9, 28826.0),
+    (3, "convert"): ("convert.hip", "f06485e6d4a5", 82406.2, 223128.0),
+    (3, "sym_count"): ("symbolic.hip", "dffb5d515039", 22561.5, 3241.0),
+    (3, "scan_sym"): ("symbolic.hip", "dffb5d515039", 317.8, 250.0),
+    (3, "sym_emit"): ("symbolic.hip", "dffb5d515039", 77212.5, 267212.9),
     (3, "scan_rows"): ("symbolic.hip", "dffb5d515039", 994.3, 2592.6),
-    (3, "numeric"): ("numeric.hip", "2aade73456b3", 339925.4, 1188196.8),
-    (4, "convert"): ("rowwise.hip", "32e90804bed2", 30062.6, 85603.7),
-    (4, "sym_count"): ("rowwise.hip", "32e90804bed2", 6845348.6, 5335257.7),
+    (3, "numeric"): ("numeric.hip", "2aade73456b3", 339919.9, 1190282.5),
+    (4, "convert"): ("rowwise.hip", "32e90804bed2", 30075.8, 85601.1),
+    (4, "sym_count"): ("rowwise.hip", "32e90804bed2", 6844956.7, 5335256.2),
     (4, "scan_rows"): ("rowwise.hip", "32e90804bed2", 754.0, 1877.9),
-    (4, "numeric"): ("rowwise.hip", "32e90804bed2", 25755927.4, 23205438.4),
-    (5, "convert"): ("convert.hip", "626d7ce04841", 14146.9, 36641.8),
+    (4, "numeric"): ("rowwise.hip", "32e90804bed2", 25736702.5, 23205265.9),
+    (5, "convert"): ("convert.hip", "f06485e6d4a5", 14146.8, 36641.8),
     (5, "sym_count"): ("symbolic.hip", "dffb5d515039", 4856.4, 1280.0),
-    (5, "scan_sym"): ("symbolic.hip", "dffb5d515039", 159.3, 98.8),
+    (5, "scan_sym"): ("symbolic.hip", "dffb5d515039", 158.9, 98.8),
     (5, "sym_emit"): ("symbolic.hip", "dffb5d515039", 8707.7, 16309.8),
     (5, "scan_rows"): ("symbolic.hip", "dffb5d515039", 406.2, 1024.6),
-    (5, "numeric"): ("numeric.hip", "2aade73456b3", 53984.4, 269853.7),
+    (5, "numeric"): ("numeric.hip", "2aade73456b3", 53956.3, 270016.3),
 }
 
 def source_digest(name: str) -> str:
