@@ -7,17 +7,15 @@
 //   k_row_prepare   one pass over an operand: validation, entries as {column, value} records, tiles per tile-row,
 //                   and for A the number of intermediate products of every row and the lists of work
 //   k_row_finish    row_ptr of C; candidate tile pairs (the measure by which tsp_spgemm chooses this path) and other sums
-//   k_row_small     rows with few, short rows of B behind them: a hash table per row in LDS; k_small_copy puts them in place,
+//   k_row_small     rows with few, short rows of B behind them: products sorted in registers; k_small_copy puts them in place,
 //                   or k_small_finish, which makes row_ptr as well, where no other rows are expected
 //   k_heavy_pack    B for the other rows: words of 16 columns, entries of 4 bytes
 //   k_heavy_count   their sizes: a block per row, one bit per column of C in LDS
 //   k_heavy_fill    a block per row and some windows of columns, an accumulator in LDS for some thousand entries at a time
 //
 // A product that is repeated on a handle has the same bits every time.  Products of fp16 numbers are exact in fp32.  An entry of a
-// small row is summed in fp64 and rounded once where several short rows of B go at a time, and where 16 lanes go to a row though
-// the mean row of A has at most 8 entries (SmallShape::fp64).  Otherwise it is summed in fp32, a row of B at a time: first the
-// products with elements of B that are among the first of their rows (as many as a row has lanes), in the order of the entries
-// of A, then those with elements further on, in the same order.  A heavy entry is summed in integers where every partial sum is
+// small row is summed in fp64 and rounded once, in the order of the entries of A but for what the lanes of a long sum have, which
+// is added up by halves.  A heavy entry is summed in integers where every partial sum is
 // exact in them (all products are multiples of a power of two that the operands' values say; then the order of the additions
 // does not matter and a whole block shares the accumulator), and otherwise in fp64 by one wave, entry after entry of A or four
 // at a time.
@@ -646,13 +644,13 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
 
 // ---- small rows -------------------------------------------------------------------------------------------------
 // How the small rows of a launch are worked off: lanes per row of A, lanes per row of B (a power of two, at most as
-// many), slots of the row's table (a power of two), and the most products of a small row.
+// many), and the most products of a small row (three quarters of a power of two, 192 at most).
 struct SmallShape {
-    int lanes, list_lanes, slots, products;
-    bool fp64;                           // the sums are, also with lists as wide as the group
+    int lanes, list_lanes, products;
     bool narrow() const { return list_lanes < lanes; }
     int wave_rows() const { return 64 / lanes; }
-    size_t wave_bytes() const { return (size_t)wave_rows() * (slots * 5 + products * (narrow() || fp64 ? 12 : 8)); }   // LDS
+    size_t wave_bytes() const { return (size_t)(wave_rows() * products + 2) * 8; }   // LDS
+    static constexpr size_t kReadPast = 64 * 8;              // ... behind the last wave's
 };
 
 struct SmallArgs {
@@ -678,43 +676,137 @@ struct SmallArgs {
     int finish;                          // the last block does the work of k_row_finish (FinishArgs; rows of one chunk)
 };
 
+// The wave's groups of G lanes each sort G * R keys, number l * R + r of a group in lane l's key[r]: merges of ascending halves,
+// of which the first step compares mirrored places, so that every step puts the smaller key first and no lane needs to know a
+// direction.  med3 with 0 is a minimum, with the largest number a maximum.  (Templates, not loops: sixteen keys are too many for the
+// compiler to take the loops apart, and then lie in scratch memory.)
+template <int kControl>
+__device__ __forceinline__ uint32_t from_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kControl, 0xf, 0xf, true); }
+template <int kXor>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t x) {
+    if constexpr (kXor == 1) return from_lane<0xB1>(x);
+    else if constexpr (kXor == 2) return from_lane<0x4E>(x);
+    else if constexpr (kXor == 3) return from_lane<0x1B>(x);
+    else if constexpr (kXor == 4) return from_lane<0x1B>(from_lane<0x141>(x));
+    else if constexpr (kXor == 7) return from_lane<0x141>(x);
+    else if constexpr (kXor == 15) return from_lane<0x140>(x);
+    else static_assert(kXor == 1, "not needed");
+}
+__device__ __forceinline__ uint32_t median(uint32_t x, uint32_t y, uint32_t z) {
+    return max(min(x, y), min(max(x, y), z));                // (v_med3_u32)
+}
+template <int R, int kStride>
+__device__ __forceinline__ void sort_strides(uint32_t (&key)[R]) {       // kStride, kStride / 2, ... 1
+    if constexpr (kStride >= 1) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (!(r & kStride)) {
+                const uint32_t x = min(key[r], key[r + kStride]);
+                key[r + kStride] = max(key[r], key[r + kStride]);
+                key[r] = x;
+            }
+        sort_strides<R, kStride / 2>(key);
+    }
+}
+template <int R, int kSorted>
+__device__ __forceinline__ void sort_own(uint32_t (&key)[R]) {           // stretches of kSorted keys are sorted
+    if constexpr (kSorted < R) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (!(r & kSorted)) {
+                const int other = r ^ (2 * kSorted - 1);
+                const uint32_t x = min(key[r], key[other]);
+                key[other] = max(key[r], key[other]);
+                key[r] = x;
+            }
+        sort_strides<R, kSorted / 2>(key);
+        sort_own<R, 2 * kSorted>(key);
+    }
+}
+template <int kXor, bool kMirror, int R>
+__device__ __forceinline__ void sort_across(uint32_t (&key)[R], uint32_t upper) {
+    uint32_t other[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) other[r] = from_lane_xor<kXor>(key[kMirror ? r ^ (R - 1) : r]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) key[r] = median(key[r], other[r], upper);
+}
+template <int G, int R>
+__device__ __forceinline__ void sort_group(uint32_t (&key)[R], int l) {
+    const uint32_t upper1 = l & 1 ? ~0u : 0u, upper2 = l & 2 ? ~0u : 0u, upper4 = l & 4 ? ~0u : 0u, upper8 = l & 8 ? ~0u : 0u;
+    sort_own<R, 1>(key);
+    sort_across<1, true>(key, upper1);
+    sort_strides<R, R / 2>(key);
+    sort_across<3, true>(key, upper2);
+    sort_across<1, false>(key, upper1);
+    sort_strides<R, R / 2>(key);
+    sort_across<7, true>(key, upper4);
+    sort_across<2, false>(key, upper2);
+    sort_across<1, false>(key, upper1);
+    sort_strides<R, R / 2>(key);
+    if constexpr (G == 16) {
+        sort_across<15, true>(key, upper8);
+        sort_across<4, false>(key, upper4);
+        sort_across<2, false>(key, upper2);
+        sort_across<1, false>(key, upper1);
+        sort_strides<R, R / 2>(key);
+    }
+}
+
+// What the lane of each round's list holds: from one lane of the group to all of it, in the registers, or where a round has several
+// lists through LDS.
+template <bool kNarrow, int G, int kRound, typename OfList>
+__device__ __forceinline__ int of_round(int v, OfList &of_list) {
+    if constexpr (kNarrow) return of_list(v, kRound);
+    else if constexpr (G == 16) return __builtin_amdgcn_mov_dpp(v, 0x150 + kRound, 0xf, 0xf, true);
+    else return __builtin_amdgcn_update_dpp(__builtin_amdgcn_mov_dpp(v, 0x150 + kRound, 0xf, 0xf, true), v, 0x158 + kRound, 0xf, 0xc, false);
+}
+template <bool kNarrow, int G, int kFrom, typename OfList, int... kRound>
+__device__ __forceinline__ void each_list(int *out, int v, OfList &of_list, std::integer_sequence<int, kRound...>) {
+    ((out[kRound] = of_round<kNarrow, G, kFrom + kRound>(v, of_list)), ...);
+}
+template <int kFrom, int kTo, typename Run>
+__device__ __forceinline__ void each_round(Run &run) {
+    if constexpr (kFrom < kTo) {
+        run(std::integral_constant<int, kFrom>{});
+        each_round<kFrom + 1, kTo>(run);
+    }
+}
+// The bits of the wave's groups of G lanes, one over the other
+template <int G>
+__device__ __forceinline__ uint32_t fold_groups(unsigned long long bits) {
+    uint32_t x = (uint32_t)bits | (uint32_t)(bits >> 32);
+    x |= x >> 16;
+    if constexpr (G == 8) x |= x >> 8;
+    return x & ((1u << G) - 1u);
+}
+
 // A group of G lanes per row of A with at most G entries and shape.products intermediate products.  The rows of B behind
 // it are fetched by the group's lanes side by side (a lane per list costs the load path a cycle per lane), all before the
-// first is used, and go through a hash table of the row in LDS.  New columns get places in a list, where the products
-// are added up.  Then the rank of every column among the row's is found (each lane compares its columns with all), and
-// the wave's rows go in order into memory of their own: k_small_copy moves them into C when its row_ptr is known.  (Doing
-// all of it twice, once for the sizes, costs more than the copy.)
-// Bound by the vector instructions of every wave (61 % of the time on the mesh, LDS 39 %), many of which do not depend on what
-// its rows hold.  Measured, this
-// kernel and the copy, against merging the lists in LDS once to size C and once to fill it: a 512x512 mesh 39 + 12 us (64
-// before), 65536 rows of 8 random entries 39 + 12 us (68), the light rows of R-MAT scale 14 28 + 6 us (135).
-// A whole group per row of B (kNarrow false): one row of B at a time, whose columns are distinct, so no two lanes meet at
-// an entry, and the sums form in a fixed order, in fp32 or in fp64 (kFp64: SmallShape::fp64).  Short rows of B (kNarrow):
-// several at a time, added with LDS atomics in fp64.
-template <int G, bool kNarrow, bool kFp64>
+// first is used.  The products go to LDS, in the order of A's entries and behind them of B's; their keys {column << 8 | place} are
+// sorted in the lanes' registers, and the products of a column, which then follow one another, are added up in fp64, in a lane one
+// after the other and over the lanes by a scan.  The wave's rows go in order into memory of their own: k_small_copy moves them into
+// C when its row_ptr is known.  (Doing all of it twice, once for the sizes, costs more than the copy.)
+// A whole group per row of B (kNarrow false): one row of B at a time.  Short rows of B (kNarrow): several at a time.
+// Bound by the round trips of a wave (row of A, its entries, the starts of B's rows, their entries) and the few waves that are there
+// to hide them while a launch begins and ends; vector instructions 63 % on a 512 x 512 mesh, 37 % with rows of 8 random entries.
+// Sorting needs no LDS but for the products, so that 8 waves fit a SIMD, and no LDS operation waits for another one.  A hash table of
+// the row in LDS (a compare-and-swap per product and look, sums there, ranks of the columns by comparing all with all) had room for
+// 4 to 7: this kernel 38.8 -> 28.4 us on the mesh, 39.6 -> 24.4 with 65,536 rows of 8 random entries, 12.8 -> 9.3 with 1024 of them,
+// 25.6 -> 19.2 for A*P on a 64^3 grid.  With the table's compare-and-swaps and additions requested eight rows of B at a time 45, 56
+// and 29: the LDS takes 8 to 12 cycles for each, 30 where eight lanes count in one place, 12 to 17 for an fp64 addition.
+template <int G, bool kNarrow>
 __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t block) {
     constexpr int kRows = 64 / G;        // per wave
     constexpr int kAhead = kNarrow ? G / 2 : G;
-    constexpr int32_t kFree = -1;
-    using Sum = typename std::conditional<kFp64, double, float>::type;
-    static_assert(kFp64 || !kNarrow, "several lists at a time add in no order of their own");
     extern __shared__ __align__(16) unsigned char small_lds[];
     __shared__ uint32_t s_len[256 / G];
     const int lane = lane_id(), l = lane % G, wave = threadIdx.x >> 6;
     const uint32_t row = block * (256 / G) + threadIdx.x / G;
-    const int slots = a.shape.slots, most = a.shape.products;
-    unsigned char *lds = small_lds + wave * a.wave_bytes;
-    int32_t *table = reinterpret_cast<int32_t *>(lds) + (lane / G) * slots;
-    Sum *sum = reinterpret_cast<Sum *>(lds + kRows * slots * 4) + (lane / G) * most;
-    int32_t *keys = reinterpret_cast<int32_t *>(lds + kRows * (slots * 4 + most * (int)sizeof(Sum))) + (lane / G) * most;
-    uint8_t *place = lds + kRows * (slots * 4 + most * ((int)sizeof(Sum) + 4)) + (lane / G) * slots;
-    for (int i = lane; i < kRows * slots / 4; i += 64) reinterpret_cast<int4 *>(lds)[i] = make_int4(kFree, kFree, kFree, kFree);
-    if constexpr (kNarrow) {
-        int4 *zero = reinterpret_cast<int4 *>(lds + kRows * slots * 4);
-        for (int i = lane; i < kRows * most / 2; i += 64) zero[i] = make_int4(0, 0, 0, 0);
-    }
-    int4 *no_keys = reinterpret_cast<int4 *>(lds + kRows * (slots * 4 + most * (int)sizeof(Sum)));
-    for (int i = lane; i < kRows * most / 4; i += 64) no_keys[i] = make_int4(kNoCol, kNoCol, kNoCol, kNoCol);
+    const int most = a.shape.products;
+    // {key, product} of the row's products, and behind the wave's rows a place for lanes without an element
+    uint2 *wave_products = reinterpret_cast<uint2 *>(small_lds + __umul24(wave, a.wave_bytes));
+    uint2 *products = wave_products + __umul24(lane / G, most);
     int32_t p = 0, e = 0, deg = 0, ub = 0;
     uint32_t av = 0;
     bool small = false;
@@ -722,156 +814,178 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
         const int32_t s = element(a.a_start, row);
         deg = element(a.a_start, row + 1) - s;
         ub = element(a.ub, row);
-        small = ub > 0 && deg > 0 && small_row(deg, ub, G, most);
-        if (small && l < deg) {
+        small = (ub > 0) & (deg > 0) & small_row(deg, ub, G, most);
+        if (small & (l < deg)) {
             const int2 x = element(a.a_rec, (uint32_t)(s + l));
             p = element(a.b_start, (uint32_t)x.x);
             e = element(a.b_start, (uint32_t)x.x + 1);
             av = (uint32_t)x.y;
         }
     }
-    // The search for a slot ends because the row has no more products than three quarters of them.  ub says so, and so do the
-    // start arrays of operands that are canonical; of others the lists are counted here, and a row that has more takes none.
-    // (A counter in the search itself makes 65536 rows of 8 random entries take 74 us instead of 70.)
-    int products = min(max(e - p, 0), most + 1);
-    products += TSP_DPP(0, products, 0xB1, 0xf, true);                     // of the group: pairs, quads, halves of a row, rows
-    products += TSP_DPP(0, products, 0x4E, 0xf, true);
-    products += TSP_DPP(0, products, 0x141, 0xf, true);
-    if constexpr (G == 16) products += TSP_DPP(0, products, 0x140, 0xf, true);
-    if (products > most) e = p;
-    const int lists = wave_max(small ? deg : 0);
+    // The LDS has room for the row's products: ub says so, and so do the start arrays of operands that are canonical; of others the
+    // lists are counted here, and a row that has more takes none.
+    int len = min(max(e - p, 0), most + 1);
+    const int inc16 = row16_inclusive_scan(len);
+    int n_products = from_lane<0x15F>(inc16), before = inc16 - len;
+    if constexpr (G == 8) {
+        const int low = from_lane<0x157>(inc16);
+        n_products = lane & 8 ? n_products - low : low;
+        before -= lane & 8 ? low : 0;
+    }
+    if (n_products > most) n_products = len = 0;
+    const uint32_t of_lists = fold_groups<G>(__ballot(len > 0));          // lists that any of the groups has, a bit each
+    const int lists = 32 - __builtin_clz(of_lists | 1u);                   // (one, without elements, where there are none)
     // round t: list t, or with narrow lists the lists t * (G / width) ... of the group, and element j of each
     const int width = kNarrow ? a.shape.list_lanes : G, per = kNarrow ? G / width : 1;
     const int j = kNarrow ? l & (width - 1) : l;
     const int rounds = kNarrow ? (lists + per - 1) / per : lists;
     const int from0 = (lane - l + (kNarrow ? l / width : 0)) * 4;          // lane of the round's list, in bytes
-    auto of_list = [&](auto v, int t) { return __builtin_amdgcn_ds_bpermute(from0 + t * per * 4, (int)v); };
-    // (all requested before any is used, and without branches, which the waits could not see through)
-    int2 x[kAhead];
-    bool there[kAhead];
-#pragma unroll
-    for (int t = 0; t < kAhead; ++t) {
-        const int32_t k = of_list(p, t) + j;
-        there[t] = t < rounds && k < of_list(e, t);
-        x[t] = element(a.b_rec, there[t] ? (uint32_t)k : 0u);
-    }
-    wave_sync();
-    const int group_shift = lane & ~(G - 1);
-    const int bits = 31 - __builtin_clz(slots);
-    int listed = 0;                                          // columns of the row so far
-    auto take = [&](const int2 &y, uint32_t f, bool on) {
-        bool made = false;
-        // (an odd step, by which every slot is met, and of the column: one slot after the other the product of 65,536 rows of 8
-        // random entries takes 66.0 us instead of 61.4, of 6 entries, 8 lanes to a row, 52.9 instead of 48.9, a 512 x 512 mesh 66.7
-        // instead of 65.7)
-        const uint32_t hash = (uint32_t)__umul24((uint32_t)y.x, 0x9E3779u), step = hash >> (24 - 2 * bits) | 1u;
-        uint32_t slot = (hash >> (24 - bits)) & (uint32_t)(slots - 1);
-        if (on)
-            while (true) {                                   // (a free slot is always left: the row has been checked above)
-                const int32_t old = atomicCAS(&table[slot], kFree, y.x);
-                made = old == kFree;
-                if (made || old == y.x) break;
-                slot = (slot + step) & (uint32_t)(slots - 1);
-            }
-        const float product = __uint_as_float(f) * __uint_as_float((uint32_t)y.y);
-        const uint32_t mine = (uint32_t)(__ballot(made) >> group_shift) & ((1u << G) - 1u);
-        // (no more than `most`, whatever an operand that was not validated holds)
-        int at = min(listed + __popc(mine & ((1u << l) - 1u)), most - 1);
-        if (made) {
-            place[slot] = (uint8_t)at;
-            keys[at] = y.x;
-            if constexpr (!kNarrow) sum[at] = product + 0.f;
-        }
-        listed += __popc(mine);
-        if constexpr (kNarrow) {
-            wave_sync();                                     // (another list of the round may have made the place)
-            if (on) unsafeAtomicAdd(&sum[min((int)place[slot], most - 1)], (double)product);
-        } else {
-            if (on && !made) sum[min((int)place[slot], most - 1)] += product;
-        }
-        wave_sync();
+    auto of_list = [&](int v, int t) { return __builtin_amdgcn_ds_bpermute(from0 + t * per * 4, v); };
+    const int about = before | len << 16;
+    const uint32_t idle = (uint32_t)__umul24(kRows - lane / G, most);           // (of the wave, from `products`)
+    auto put = [&](const int2 &y, int f, int at, bool on) {
+        const float product = __uint_as_float((uint32_t)f) * __uint_as_float((uint32_t)y.y);
+        products[on ? (uint32_t)at : idle] = make_uint2((uint32_t)y.x << 8 | (uint32_t)at, __float_as_uint(product));
     };
-#pragma unroll
-    for (int t = 0; t < kAhead; ++t)
-        if (t < rounds) take(x[t], (uint32_t)of_list(av, t), there[t]);
-    // Lists that are longer than their lanes, one round after the other to its end (the order of the sums is fixed: the first
-    // elements of all lists, then the others list by list).  The next elements are on their way while some are taken, and rounds
-    // without any are left out: chunk by chunk over all rounds, each load waited for, the light rows of graphs of 1000 to 16,000
-    // vertices took 27 to 35 us, 20 to 29 now.
-    uint32_t left = 0;                                       // rounds that go on, a bit each
+    // (all requested before any is used; a half, a quarter and a quarter of the rounds there may be, as far as there are any)
     {
-        const unsigned long long longer = __ballot(e - p > width);
-        uint32_t of_lane = 0;
+        int2 x[kAhead];
+        int abouts[kAhead];
+        auto request = [&](auto from, auto count) {
+            constexpr int kFrom = decltype(from)::value, kCount = decltype(count)::value;
+            int begin[kCount];
+            each_list<kNarrow, G, kFrom>(begin, p, of_list, std::make_integer_sequence<int, kCount>{});
+            each_list<kNarrow, G, kFrom>(abouts + kFrom, about, of_list, std::make_integer_sequence<int, kCount>{});
 #pragma unroll
-        for (int g = 0; g < 64; g += G) of_lane |= (uint32_t)(longer >> g) & ((1u << G) - 1u);
-        if constexpr (kNarrow) {                             // (per lists to a round)
-            for (int t = 0; t < rounds; ++t) left |= (of_lane >> (t * per)) & ((1u << per) - 1u) ? 1u << t : 0u;
-        } else {
-            left = of_lane;
-        }
+            for (int t = 0; t < kCount; ++t) {
+                // (rounds of several lists: those past the last one would have lists of other groups)
+                if (kNarrow && kFrom + t >= rounds) abouts[kFrom + t] = 0;
+                uint32_t byte = (uint32_t)(j < abouts[kFrom + t] >> 16 ? begin[t] + j : 0) * 8u;
+                asm volatile("" : "+v"(byte));               // (a 32-bit offset from a scalar base)
+                x[kFrom + t] = *reinterpret_cast<const int2 *>(reinterpret_cast<const char *>(a.b_rec) + byte);
+            }
+        };
+        auto put_round = [&](auto round) {
+            constexpr int t = decltype(round)::value;
+            put(x[t], of_round<kNarrow, G, t>((int)av, of_list), (abouts[t] & 0xFFFF) + j, j < abouts[t] >> 16);
+        };
+        constexpr std::integral_constant<int, 0> k0{};
+        constexpr std::integral_constant<int, kAhead / 2> kHalf{};
+        constexpr std::integral_constant<int, kAhead / 4> kQuarter{};
+        constexpr std::integral_constant<int, kAhead * 3 / 4> kThree{};
+        request(k0, kHalf);
+        if (rounds > kAhead / 2) request(kHalf, kQuarter);
+        if (rounds > kAhead * 3 / 4) request(kThree, kQuarter);
+        each_round<0, kAhead / 2>(put_round);
+        if (rounds > kAhead / 2) each_round<kAhead / 2, kAhead * 3 / 4>(put_round);
+        if (rounds > kAhead * 3 / 4) each_round<kAhead * 3 / 4, kAhead>(put_round);
     }
-    if (left) {
-        int32_t at = 0, end = 0;
-        uint32_t factor = 0;
+    // Lists that are longer than their lanes, one round after the other to its end.  The next elements are on their way while some
+    // are taken, and rounds without any are left out: chunk by chunk over all rounds, each load waited for, the light rows of graphs
+    // of 1000 to 16,000 vertices took 27 to 35 us, 20 to 29 now.
+    if (const uint32_t longer = fold_groups<G>(__ballot(len > width))) {
+        uint32_t left = longer;                              // rounds that go on, a bit each
+        if constexpr (kNarrow) {                             // (per lists to a round)
+            left = 0;
+            for (int t = 0; t < rounds; ++t) left |= (longer >> (t * per)) & ((1u << per) - 1u) ? 1u << t : 0u;
+        }
+        int at = 0, end = 0, from = 0, factor = 0;           // of the list's elements, and what is added for their places in B
         int2 y;
-        auto request = [&] { y = element(a.b_rec, at < end ? (uint32_t)at : 0u); };
+        auto request = [&] { y = element(a.b_rec, at < end ? (uint32_t)(at + from) : 0u); };
         auto next_round = [&] {
             const int t = __builtin_ctz(left);
-            at = of_list(p, t) + j + width;
-            end = of_list(e, t);
-            factor = (uint32_t)of_list(av, t);
+            const int of = of_list(about, t);
+            at = (of & 0xFFFF) + j + width;
+            end = (of & 0xFFFF) + (of >> 16);
+            from = of_list(p, t) - (of & 0xFFFF);
+            factor = of_list((int)av, t);
             left &= left - 1u;
             request();
         };
         next_round();
         for (bool more = true; more;) {
             const int2 now = y;
-            const uint32_t f = factor;
+            const int f = factor, place = at;
             const bool on = at < end;
             at += width;
             if (__any(at < end)) request();
             else if (left) next_round();
             else more = false;
-            take(now, f, on);
+            put(now, f, place, on);
         }
     }
-    const int n = min(listed, most);
-    const uint32_t inc = wave_inclusive_scan(l == 0 ? (uint32_t)n : 0u);
-    const int total = __builtin_amdgcn_readlane((int)inc, 63), longest_row = wave_max(n);
-    const int off = __builtin_amdgcn_ds_bpermute(group_shift * 4, (int)inc) - n;       // of the row among the entries of the wave
+    wave_sync();
     int2 *found = a.found + (size_t)(block * 4 + wave) * (kRows * most);
-    int2 *stage = reinterpret_cast<int2 *>(lds);             // (the table is done with; the sums too for all but the widest rows)
-    const bool staged = total * 8 <= kRows * slots * 4;
-    int2 *to = staged ? stage : found;
-    // ranks: eight of the row's columns at a time (behind the last one: kNoCol) against some of every lane's
-    auto place_columns = [&](auto lane_columns) {
-        constexpr int kQ = decltype(lane_columns)::value;
-        for (int q0 = l; q0 < longest_row + l; q0 += kQ * G) {
-            int32_t k[kQ];
-            int r[kQ];
+    int n = 0, total = 0;
+    auto add_sorted = [&](auto lane_keys) {
+        constexpr int R = decltype(lane_keys)::value;
+        constexpr uint32_t kNone = ~255u;                    // (place 0: it is read and added to nothing that is wanted)
+        uint32_t key[R];
 #pragma unroll
-            for (int q = 0; q < kQ; ++q) {
-                k[q] = q0 + q * G < n ? keys[q0 + q * G] : kNoCol;
-                r[q] = off;
-            }
-            for (int i = 0; i < longest_row; i += 8) {
-                const int4 y = *reinterpret_cast<const int4 *>(keys + i), z = *reinterpret_cast<const int4 *>(keys + i + 4);
+        for (int r = 0; r < R; ++r) {                        // (kReadPast: also behind the row's)
+            const uint32_t own = products[l * R + r].x;
+            key[r] = l * R + r < n_products ? own : kNone;
+        }
+        sort_group<G, R>(key, l);
+        float product[R];
 #pragma unroll
-                for (int q = 0; q < kQ; ++q)
-                    r[q] += (y.x < k[q]) + (y.y < k[q]) + (y.z < k[q]) + (y.w < k[q]) + (z.x < k[q]) + (z.y < k[q]) +
-                            (z.z < k[q]) + (z.w < k[q]);
-            }
+        for (int r = 0; r < R; ++r) product[r] = __uint_as_float(products[key[r] & 255u].y);
+        // the first and the last of a column's
+        bool first[R], last[R];
+        const uint32_t previous = from_lane<0x111>(key[R - 1]);
 #pragma unroll
-            for (int q = 0; q < kQ; ++q)
-                if (q0 + q * G < n) to[r[q]] = make_int2(k[q], (int)__float_as_uint((float)sum[q0 + q * G]));
+        for (int r = 0; r < R; ++r) first[r] = r == 0 ? (l == 0) | ((key[0] ^ previous) > 255u) : (key[r] ^ key[r - 1]) > 255u;
+        const uint32_t next = from_lane<0x101>(key[0]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) last[r] = ((r == R - 1 ? (l == G - 1) | ((key[r] ^ next) > 255u) : first[r == R - 1 ? r : r + 1])) & (key[r] < kNone);
+        // what the lanes before have of the column that this one begins with
+        double sum = 0;
+        bool begun = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            sum = (first[r] ? 0.0 : sum) + (double)product[r];
+            begun = begun | first[r];
+        }
+        auto of_before = [&](auto control, double v) {
+            const unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
+            return __builtin_bit_cast(double, (unsigned long long)from_lane<decltype(control)::value>((uint32_t)(bits >> 32)) << 32 |
+                                                  from_lane<decltype(control)::value>((uint32_t)bits));
+        };
+        uint32_t closed = begun ? 1u : 0u;                   // (the first lane of a group always is)
+        auto scan_step = [&](auto control) {
+            const double other = of_before(control, sum);
+            const uint32_t other_closed = from_lane<decltype(control)::value>(closed);
+            sum = closed ? sum : sum + other;
+            closed |= other_closed;
+        };
+        scan_step(std::integral_constant<int, 0x111>{});
+        scan_step(std::integral_constant<int, 0x112>{});
+        scan_step(std::integral_constant<int, 0x114>{});
+        if constexpr (G == 16) scan_step(std::integral_constant<int, 0x118>{});
+        sum = of_before(std::integral_constant<int, 0x111>{}, sum);
+        int own = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) own += last[r] ? 1 : 0;
+        const int inc = (int)wave_inclusive_scan((uint32_t)own);
+        total = __builtin_amdgcn_readlane(inc, 63);
+        n = own;                                             // of the group: pairs, quads, halves of a row, rows
+        n += TSP_DPP(0, n, 0xB1, 0xf, true);
+        n += TSP_DPP(0, n, 0x4E, 0xf, true);
+        n += TSP_DPP(0, n, 0x141, 0xf, true);
+        if constexpr (G == 16) n += TSP_DPP(0, n, 0x140, 0xf, true);
+        uint32_t to = (uint32_t)(inc - own);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            sum = (first[r] ? 0.0 : sum) + (double)product[r];
+            if (last[r]) found[to] = make_int2((int)(key[r] >> 8), (int)__float_as_uint((float)sum));
+            to += last[r] ? 1u : 0u;
         }
     };
-    if (longest_row > 2 * G) place_columns(std::integral_constant<int, 4>{});
-    else place_columns(std::integral_constant<int, 2>{});
-    if (staged) {
-        wave_sync();
-        for (int i = lane; i < total; i += 64) found[(unsigned)i] = stage[i];
-    }
+    if (!__any(n_products > G)) add_sorted(std::integral_constant<int, 1>{});
+    else if (!__any(n_products > 2 * G)) add_sorted(std::integral_constant<int, 2>{});
+    else if (!__any(n_products > 4 * G)) add_sorted(std::integral_constant<int, 4>{});
+    else if (!__any(n_products > 8 * G)) add_sorted(std::integral_constant<int, 8>{});
+    else if constexpr (G == 16) add_sorted(std::integral_constant<int, 16>{});
     if (lane == 0) a.wave_total[block * 4 + wave] = total;
     if (l == 0) {
         // (rows of other kernels count as empty here)
@@ -976,7 +1090,8 @@ __global__ __launch_bounds__(256) void k_small_finish(const FinishArgs a, const 
     if (first) publish_sizes(a, totals, standing, (int64_t)entries);
     // (No more than this matters where no row is heavy.  Expected::holds also asks whether the heavy rows' accumulator of the last
     // product of these sizes would do for the values: where it would not the host has k_small_copy move the entries once more.)
-    if (!uniform_load(only_small) || (int64_t)entries > a.expected.nnz) return;
+    // (Also of the block's own end, so that it writes inside C's arrays whatever the sums say.)
+    if (!uniform_load(only_small) || (int64_t)entries > a.expected.nnz || (int64_t)(entries_before + own) > a.expected.nnz) return;
     const int wave_rows = 64 / c.shape.lanes, waves = kSideRows / wave_rows;
     if ((int)threadIdx.x < kSideRows && threadIdx.x % wave_rows == 0) s_first[threadIdx.x / wave_rows] = at;
     __syncthreads();
@@ -1172,8 +1287,8 @@ struct NoPack {};
 // entries times as many 15.5 and 11.6 us, R-MAT of scale 14 39 and 35; products of scale 11 60 and 54, of scale 16, with 12 entries
 // per row, 945 and 950; of scale 18, which fills the chip either way and has fewer waves here, the two 434 and 476.
 constexpr int64_t kPackRows = 1 << 15;
-template <int G, bool kNarrow, bool kFp64, typename Pack = NoPack>
-__global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin, const Pack pack) {
+template <int G, bool kNarrow, typename Pack = NoPack>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin, const Pack pack) {
     __shared__ int s_last;
     uint32_t block = blockIdx.x, blocks = gridDim.x;
     if constexpr (!std::is_same<Pack, NoPack>::value) {
@@ -1186,7 +1301,7 @@ __global__ __launch_bounds__(256) void k_row_small(const SmallArgs a, const SumA
     }
     const int sum_block = (int)block - (a.sums_first ? 0 : (int)blocks - a.sum_blocks);
     if (sum_block >= 0 && sum_block < a.sum_blocks) sum_tile_rows(sums, sum_block, a.sum_blocks, a.finish);
-    else row_small<G, kNarrow, kFp64>(a, block - (a.sums_first ? (uint32_t)a.sum_blocks : 0u));
+    else row_small<G, kNarrow>(a, block - (a.sums_first ? (uint32_t)a.sum_blocks : 0u));
     if (!a.finish) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left for the last block has arrived
     __syncthreads();
@@ -2091,39 +2206,30 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     }
     if (A->nnz >= (1 << 28) || B->nnz >= (1 << 28)) return TSP_OK;      // (32-bit byte offsets into 8-byte records)
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
-    // Small rows: a table of the row that is three quarters full at most, with a margin over the mean number of products, 256
-    // slots at most; for a row of B as many lanes as its mean has entries.  For the row 8 lanes where the mean row of A has no
-    // more entries, else 16.  16 also
-    // - for tables of more than 64 slots: a million, 262,144 and 65,536 rows of 8 random entries 899, 214, 65.2 -> 850, 205, 62.3
+    // Small rows: up to 24, 48, 96 or 192 products, with a margin over the mean number; for a row of B as many lanes as its mean has
+    // entries.  For the row 8 lanes where the mean row of A has no more entries, else 16.  16 also
+    // - for more than 48 products: a million, 262,144 and 65,536 rows of 8 random entries 899, 214, 65.2 -> 850, 205, 62.3
     //   us, of 7 (49 products) 794, 187, 60.2 -> 781, 187, 59.5; smaller tables, of 6 (36 products) 518, 125, 50.6 -> 565, 136, 51.6;
     // - for few rows, as long as the waves are few to a SIMD: 512 to 8192 rows of 8 entries 33.5 -> 29 to 32 us, meshes up to
     //   110 x 110 29.2 -> 28.2, 16,384 rows of 2 to 8 the same or 1 us more;
     // - where more than one row in 64 is small but for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the
     //   lanes 0.1 ns per row; by the last product of these sizes, and where the one at hand turns out otherwise it is started
     //   again).
-    // With 8 lanes rows of 9 to 16 entries are heavy and their sums rounded once; where the first two give them 16 the sums are in
-    // fp64, so that they are rounded once as well, also with a whole group per row of B.  Rows of 5 entries with 9 behind each, 8
-    // lanes / 16 and fp32 / 16 and fp64: 8000 rows 40.7 / 37.4 / 36.4 us, 65,536 70.9 / 64.0 / 65.1, 262,144 196 / 160 / 171; of 3
-    // with 17: 41.5 / 39.2 / 38.0, 72.2 / 67.9 / 69.7, 205 / 176 / 187.
+    // (Sums are rounded once whichever it is.)
     constexpr int64_t kFewRows = 12288;
-    SmallShape shape{8, 1, 32, 24, false};
+    SmallShape shape{8, 1, 24};
     int lanes_unless_wide = 16, cost_lanes = 16;             // (rows_preferred's times are of 8 lanes for all of few entries)
     {
         const double list = (double)B->nnz / (double)std::max<int64_t>(B->rows, 1), mean = (double)A->nnz / (double)A->rows * list;
-        while (shape.slots < 256 && shape.slots * 3 / 4 < 1.25 * mean) shape.slots *= 2;
-        shape.products = shape.slots * 3 / 4;
-        if (A->nnz <= 8 * A->rows && shape.slots <= 128) cost_lanes = 8;
-        if (A->nnz <= 8 * A->rows && shape.slots <= 64 && A->rows > kFewRows) lanes_unless_wide = 8;
-        shape.fp64 = cost_lanes == 8 && lanes_unless_wide == 16;
+        while (shape.products < 192 && shape.products < 1.25 * mean) shape.products *= 2;
+        if (A->nnz <= 8 * A->rows && shape.products <= 96) cost_lanes = 8;
+        if (A->nnz <= 8 * A->rows && shape.products <= 48 && A->rows > kFewRows) lanes_unless_wide = 8;
         shape.lanes = known && hint.wide ? 16 : lanes_unless_wide;
         while (shape.list_lanes < shape.lanes && shape.list_lanes < list) shape.list_lanes *= 2;
     }
     // (16 GiB for the entries of the small rows at most: up to 89 million rows)
     auto found_entries = [&] { return ((A->rows * shape.lanes + 255) / 256) * 256 / shape.lanes * shape.products; };
-    while (shape.slots > 32 && found_entries() > kFoundEntries) {
-        shape.slots /= 2;
-        shape.products = shape.slots * 3 / 4;
-    }
+    while (shape.products > 24 && found_entries() > kFoundEntries) shape.products /= 2;
     if (found_entries() > kFoundEntries) return TSP_OK;
     const int64_t small_waves = ((A->rows * shape.lanes + 255) / 256) * 4;
     const int shift = B->cols <= 2048 ? 11 : 12;
@@ -2383,7 +2489,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
         m.finish = finish_too;
         auto launch = [&](auto kernel, const auto &p, unsigned pack_blocks) {
-            hipLaunchKernelGGL(kernel, dim3(pack_blocks + small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes(), s, m, sums,
+            hipLaunchKernelGGL(kernel, dim3(pack_blocks + small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes() + SmallShape::kReadPast, s, m, sums,
                                finish_too ? finish_args() : FinishArgs{}, p);
         };
         const bool at_once = n_heavy > 0 && B->rows <= kPackRows;
@@ -2395,9 +2501,8 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         p.blocks = kLongBlocks + (uint32_t)((B->rows * p.lanes + (at_once ? 255 : kPackThreads - 1)) / (at_once ? 256 : kPackThreads));
         auto small_rows = [&](auto pack, unsigned pack_blocks) {
             using Pack = decltype(pack);
-            if (shape.lanes == 8) launch(shape.narrow() ? k_row_small<8, true, true, Pack> : k_row_small<8, false, false, Pack>, pack, pack_blocks);
-            else launch(shape.narrow() ? k_row_small<16, true, true, Pack> : shape.fp64 ? k_row_small<16, false, true, Pack> : k_row_small<16, false, false, Pack>,
-                        pack, pack_blocks);
+            if (shape.lanes == 8) launch(shape.narrow() ? k_row_small<8, true, Pack> : k_row_small<8, false, Pack>, pack, pack_blocks);
+            else launch(shape.narrow() ? k_row_small<16, true, Pack> : k_row_small<16, false, Pack>, pack, pack_blocks);
         };
         if (at_once) small_rows(p, p.blocks);
         else small_rows(NoPack{}, 0);

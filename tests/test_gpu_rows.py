@@ -459,6 +459,39 @@ def test_sums_of_9_to_16_entries_round_once(tsp, oracle, rows, a_row, b_row):
         h.close()
 
 
+# rows of A of `a_row` entries, all but one with b_row entries of B behind them and one with `other`: products either side of what
+# fills one, two, four, ... registers of 8 lanes (more than 12,288 rows) and of 16, single rounds and several, longer lists than lanes
+@pytest.mark.parametrize("rows,a_row,b_row,other", [
+    (12291, 1, 1, 1), (12291, 7, 1, 2), (12291, 8, 1, 2), (12291, 3, 5, 6), (12291, 3, 5, 7), (12291, 8, 4, 4), (12291, 8, 4, 5), (12291, 5, 9, 2), (12291, 2, 30, 2),
+    (12291, 6, 7, 13), (259, 1, 1, 1), (259, 16, 1, 1), (259, 16, 1, 2), (259, 4, 8, 8), (259, 4, 8, 9), (259, 8, 8, 8), (259, 8, 8, 9), (259, 11, 12, 8),
+    (259, 11, 12, 9), (259, 16, 12, 12), (259, 6, 30, 42), (259, 3, 16, 17), (259, 2, 33, 90), (259, 13, 2, 40)])
+@pytest.mark.parametrize("columns", ["the same", "others", "some of both"])
+def test_products_of_small_rows_sorted(tsp, oracle, rows, a_row, b_row, other, columns):
+    """Sums over one lane and over many, with all products of a row in one column of C each and with each in its own.  Products are
+    multiples of 2^-30 below 1, so that fp64 sums are exact and an entry is the exact sum, rounded once."""
+    rng = np.random.default_rng(rows + 1000 * a_row + 100 * b_row + other)
+    values = lambda m: (rng.uniform(2.0 ** -4, 1, m).astype(np.float16) * rng.choice([-1, 1], m)).astype(np.float64)
+    many, width = 60, {"the same": max(b_row, other), "others": 7001, "some of both": 2 * max(b_row, other)}[columns]
+    lengths = np.r_[np.full(many, b_row), np.full(many, other)]
+    B = inputs.from_coo(2 * many, 7001, np.repeat(np.arange(2 * many), lengths),
+                        np.concatenate([np.sort(rng.choice(width, k, replace=False)) for k in lengths]), values(lengths.sum()), "lists")
+    a_col = np.sort(np.concatenate([np.argsort(rng.random((rows, many)), axis=1)[:, : a_row - 1], many + rng.integers(0, many, (rows, 1))], axis=1), axis=1)
+    A = inputs.from_coo(rows, 2 * many, np.repeat(np.arange(rows), a_row), a_col.ravel(), values(rows * a_row), "rows")
+    ref = oracle.spgemm(A, B, threads=4)
+    dA, dB = tsp.to_device(A), tsp.to_device(B)
+    h = tsp.Handle()
+    try:
+        for _ in range(2):
+            C = h.spgemm(dA, dB)
+            row_ptr, col, val = C.to_host()
+            C.free()
+            assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+            if h.stats()["pairs"] == 0:                         # (tiles where they are preferred)
+                assert np.array_equal(val, ref.val.astype(np.float32))
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("a_row,b_row", [(4, 3), (40, 30), (4, 30), (40, 3)])
 @pytest.mark.parametrize("b_types", [{}, {"value_dtype": "f32"}, {"row_ptr_dtype": "i64"}])
 def test_both_operands_prepared_at_once(tsp, oracle, a_row, b_row, b_types):
