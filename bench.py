@@ -20,7 +20,7 @@ duration (HIP events on the launch stream, recorded by the library around every 
 8 TB/s HBM peak.  `layout_bytes_per_launch` is the same count for the arrays this library actually
 keeps (operand groups of 16 bytes, row offsets per output tile), for comparison.  A product that the
 library multiplies by rows (`config.path`) has no tiles and no task list: entries in, entries as
-records of 8 bytes between its kernels, entries of C out (`row_bytes`).
+records of 8 bytes between its kernels unless all rows are small, entries of C out (`row_bytes`).
 phase_hbm: the same for the conversion, the symbolic phase (with the counting pass), the numeric
 phase with its CSR emission, and a separately timed tsp_compact_zeros call on the result.
 cpu_baseline: the CPU oracle (row-wise Gustavson, fp64) timed on this machine's host cores.
@@ -123,11 +123,14 @@ def algorithmic_bytes(kernel, A, st):
     return int(table[kernel])
 
 
-def row_bytes(kernel, A, st):
+def row_bytes(kernel, A, st, given):
     """The same where the product goes by rows (csrc/rowwise.hip): CSR in once, records of 8 bytes between the kernels (a
     column and a value), the row lengths, C out once.  Rows of B are counted once, not for every entry of A that meets them,
-    and what the sizing keeps for the multiplication (small rows' entries, a bit per column of the others) is the layout's."""
+    and what the sizing keeps for the multiplication (small rows' entries, a bit per column of the others) is the layout's.
+    given: the sizing takes the rows straight from the operands, without records."""
     n, nnz, cnnz = A.rows, A.nnz, st["c_nnz"]
+    if given:
+        return int({"sym_count": 4 * (n + 1) + 6 * nnz + 4 * n, "numeric": 8 * cnnz + 4 * n + 8 * (n + 1)}.get(kernel, 0))
     table = {
         "convert": 4 * (n + 1) + 6 * nnz + 8 * nnz + 4 * (n + 1),           # CSR in, records and row starts out
         "scan_sym": 8 * n,
@@ -381,7 +384,7 @@ def run_workload(index, steps, warmup, args, tsp, inputs, torch, headline):
     tiles.free()
 
     by_rows = st["pairs"] == 0 and st["c_nnz"] > 0
-    bytes_of = row_bytes if by_rows else algorithmic_bytes
+    bytes_of = (lambda k, A, st: row_bytes(k, A, st, kavg["convert"] == 0.0)) if by_rows else algorithmic_bytes
     fused_count = not by_rows and kavg.get("count_masks", 0.0) == 0.0       # the task-list kernel ran the counting pass as well
     dominant = max(kavg, key=kavg.get)
     dom_bytes = bytes_of(dominant, A, st)

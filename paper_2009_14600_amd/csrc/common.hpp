@@ -15,6 +15,8 @@ namespace tsp {
 
 constexpr int T = 16;               // tile edge: one output tile = one 16x16 MFMA accumulator
 constexpr int kScalars = 32;        // device/host scalar slots of a handle
+// counters of groups of blocks (k_row_given), each in a line of its own
+constexpr int kArriveCounters = 1024, kArriveStride = 16;
 
 // Slots of the handle's device scalar block (int64 each).
 enum Scalar {
@@ -46,6 +48,7 @@ enum Scalar {
     S_ROW_ARRIVED = 16,      // blocks of k_row_small, or of k_row_sample, that are done
     S_SAMPLE_TILES = 28,     // k_row_sample: tiles in the tile-rows looked at, of A and (<< 32) of B
     S_SAMPLE_COST = 29,      // ... and what their rows cost by rows
+    S_GIVEN_ARRIVED = 28,    // groups of blocks of k_row_given for the tiles that are done (a slot of k_row_sample's)
     S_ROW_SKIP = 30,         // != 0: clearly a product by tiles, and its pairs of tiles as estimated, plus one
     S_LARGE_A = 24,          // tile-rows of an operand whose entries do not fit the registers of k_convert_block
     S_LARGE_B = 25,
@@ -119,6 +122,7 @@ struct RowHint {
     int64_t products = 0;                          // intermediate ones
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows
+    bool others = false;                           // k_row_given has met rows that are not for it
     bool wide = false;                             // so many rows of 9 to 16 entries that 16 lanes per row pay
     int sum = 0, scale = 0;                        // how the heavy rows are summed
 };
@@ -184,6 +188,7 @@ struct tsp_context {
     int64_t chain_capacity = 0;                    // slots allocated
     unsigned chain_epoch = 0;                      // tag of the last chained scan
     int64_t *d_scalars = nullptr;                  // device, kScalars entries
+    unsigned long long *d_arrivals = nullptr;      // device, kArriveCounters counters, zero between launches (behind the scalars)
     bool scalars_clean = false;                    // all zero: the last kernel of the previous call left them so
     int64_t *h_scalars = nullptr;                  // pinned host mirror
     int64_t *h_scalars_dev = nullptr;              // the mirror's address on the device

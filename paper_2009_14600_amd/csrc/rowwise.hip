@@ -9,6 +9,8 @@
 //   k_row_finish    row_ptr of C; candidate tile pairs (the measure by which tsp_spgemm chooses this path) and other sums
 //   k_row_small     rows with few, short rows of B behind them: products sorted in registers; k_small_copy puts them in place,
 //                   or k_small_finish, which makes row_ptr as well, where no other rows are expected
+//   k_row_given     where the last product of these sizes had no other rows: k_row_prepare's validation and tiles, and k_row_small
+//                   straight from the operands, at once; k_given_finish makes row_ptr and puts the entries in place
 //   k_heavy_pack    B for the other rows: words of 16 columns, entries of 4 bytes
 //   k_heavy_count   their sizes: a block per row, one bit per column of C in LDS
 //   k_heavy_fill    a block per row and some windows of columns, an accumulator in LDS for some thousand entries at a time
@@ -33,11 +35,9 @@ constexpr int kChunkTileRows = 128, kChunkRows = kChunkTileRows * T;   // rows w
 // Rows whose entries k_row_small adds up, and where: additions to one line wait for each other
 constexpr int kPartTileRows = 128, kPartRows = kPartTileRows * T, kPartStride = 32;
 constexpr int kPlanSums = 8;
-constexpr int kWindow = 4096;            // columns of C per window of the heavy rows (2048 where C is no wider)
 constexpr int kSpanWindowsLog = 6, kSpanWindows = 1 << kSpanWindowsLog;   // windows whose bits the LDS of a block of k_heavy_count holds (32 KB)
 constexpr int kGroupWindows = 4;         // tasks begin at a multiple of this many windows, those of very long rows of A at any
 constexpr int kCountThreads = 256, kCountThreadsWide = 512;   // of k_heavy_count, and where four of its blocks fill the LDS
-constexpr int32_t kNoCol = 0x7FFFFFFF;
 constexpr int kLongRow = 512;            // entries, for the threads that k_row_prepare gives a tile-row
 constexpr int64_t kFoundEntries = (int64_t)2 << 30;   // of the small rows before they are moved into C, at most
 // Intermediate products behind one task of k_heavy_fill (a row, or some of its windows), and entries of the row of A times
@@ -657,8 +657,6 @@ struct SmallArgs {
     SmallShape shape;
     int wave_bytes;
     int64_t rows;
-    const int32_t *a_start, *b_start, *ub;
-    const int2 *a_rec, *b_rec;
     int32_t *row_nnz;
     uint32_t *group_len;                 // entries per 16 rows
     // For k_small_finish, or null: entries per part of kPartRows, zero before, and whether the operands are canonical and no
@@ -666,6 +664,7 @@ struct SmallArgs {
     uint32_t *part_len;
     int32_t *only_small;
     const int64_t *d_scalars;
+    uint32_t *block_len;                 // GivenOperands: entries of a block's rows
     int2 *found;                         // [waves][wave_rows * products] entries {column, value} of a wave's rows, in order
     int32_t *wave_total;                 // ... and how many
     // The blocks that sum (SumArgs) are the first ones of the launch where their groups of lanes have several tile-rows each, else
@@ -674,6 +673,70 @@ struct SmallArgs {
     int sum_blocks;
     bool sums_first;
     int finish;                          // the last block does the work of k_row_finish (FinishArgs; rows of one chunk)
+};
+
+// Where k_row_small finds its rows: as k_row_prepare has left the operands.  list: entry l of a row of A, if it is small and has one:
+// its value as fp32 bits, and where its row of B lies.  element: an entry of B, as it is read and as {column, value as fp32 bits}.
+struct PreparedOperands {
+    const int32_t *a_start, *b_start, *ub;
+    const int2 *a_rec, *b_rec;
+    static constexpr bool kDirect = false;
+    using Element = int2;
+    template <int G>
+    __device__ __forceinline__ void list(uint32_t row, int l, int most, int32_t &p, int32_t &e, uint32_t &value, bool &other) const {
+        const int32_t s = element(a_start, row), deg = element(a_start, row + 1) - s, products = element(ub, row);
+        const bool small = (products > 0) & (deg > 0) & small_row(deg, products, G, most);
+        other = !small & (products != 0) & (deg > 0);
+        if (small & (l < deg)) {
+            const int2 x = element(a_rec, (uint32_t)(s + l));
+            p = element(b_start, (uint32_t)x.x);
+            e = element(b_start, (uint32_t)x.x + 1);
+            value = (uint32_t)x.y;
+        }
+    }
+    __device__ __forceinline__ Element read(uint32_t k) const {
+        uint32_t byte = k * 8u;
+        asm volatile("" : "+v"(byte));                       // (a 32-bit offset from a scalar base)
+        return *reinterpret_cast<const int2 *>(reinterpret_cast<const char *>(b_rec) + byte);
+    }
+    __device__ __forceinline__ int2 entry(const Element &x) const { return x; }
+};
+// ... or as the caller gave them, of the same types; nothing is read outside their arrays whatever they hold.  Reading columns and
+// values apart takes k_row_small of a 512 x 512 mesh 29.5 us instead of 28.3, and spares the pass that puts them together (16).
+template <typename RP, typename VT>
+struct GivenOperands {
+    const RP *a_row_ptr, *b_row_ptr;
+    const int32_t *a_col, *b_col;
+    const VT *a_val, *b_val;
+    int32_t a_nnz, b_nnz;
+    uint32_t a_last, b_last;                                 // columns, less one
+    static constexpr bool kDirect = true;
+    struct Element {
+        int32_t col;
+        VT val;
+    };
+    static __device__ __forceinline__ int32_t pointer(const RP *row_ptr, uint32_t row, int32_t nnz) {
+        return (int32_t)min(max(element(row_ptr, row), (RP)0), (RP)nnz);
+    }
+    static __device__ __forceinline__ uint32_t value_bits(VT v) { return __float_as_uint((float)__builtin_bit_cast(_Float16, (uint16_t)half_bits(v))); }
+    template <int G>
+    __device__ __forceinline__ void list(uint32_t row, int l, int, int32_t &p, int32_t &e, uint32_t &value, bool &other) const {
+        const int32_t s = pointer(a_row_ptr, row, a_nnz), deg = pointer(a_row_ptr, row + 1, a_nnz) - s;
+        other = deg > G;
+        if (!other & (l < deg)) {
+            const uint32_t c = min((uint32_t)element(a_col, (uint32_t)(s + l)), a_last);
+            value = value_bits(element(a_val, (uint32_t)(s + l)));
+            p = pointer(b_row_ptr, c, b_nnz);
+            e = pointer(b_row_ptr, c + 1, b_nnz);
+        }
+    }
+    __device__ __forceinline__ Element read(uint32_t k) const {
+        uint32_t byte = k * (uint32_t)sizeof(VT);
+        asm volatile("" : "+v"(byte));
+        return {*reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(b_col) + byte * (4u / (uint32_t)sizeof(VT))),
+                *reinterpret_cast<const VT *>(reinterpret_cast<const char *>(b_val) + byte)};
+    }
+    __device__ __forceinline__ int2 entry(const Element &x) const { return make_int2((int)min((uint32_t)x.col, b_last), (int)value_bits(x.val)); }
 };
 
 // The wave's groups of G lanes each sort G * R keys, number l * R + r of a group in lane l's key[r]: merges of ascending halves,
@@ -795,8 +858,9 @@ __device__ __forceinline__ uint32_t fold_groups(unsigned long long bits) {
 // 4 to 7: this kernel 38.8 -> 28.4 us on the mesh, 39.6 -> 24.4 with 65,536 rows of 8 random entries, 12.8 -> 9.3 with 1024 of them,
 // 25.6 -> 19.2 for A*P on a 64^3 grid.  With the table's compare-and-swaps and additions requested eight rows of B at a time 45, 56
 // and 29: the LDS takes 8 to 12 cycles for each, 30 where eight lanes count in one place, 12 to 17 for an fp64 addition.
-template <int G, bool kNarrow>
-__device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t block) {
+// totals: GivenOperands, of each wave: entries, products, and whether there are rows of other kernels
+template <int G, bool kNarrow, typename Operands>
+__device__ __forceinline__ void row_small(const SmallArgs &a, const Operands &operands, const uint32_t block, uint3 *totals = nullptr) {
     constexpr int kRows = 64 / G;        // per wave
     constexpr int kAhead = kNarrow ? G / 2 : G;
     extern __shared__ __align__(16) unsigned char small_lds[];
@@ -807,23 +871,12 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
     // {key, product} of the row's products, and behind the wave's rows a place for lanes without an element
     uint2 *wave_products = reinterpret_cast<uint2 *>(small_lds + __umul24(wave, a.wave_bytes));
     uint2 *products = wave_products + __umul24(lane / G, most);
-    int32_t p = 0, e = 0, deg = 0, ub = 0;
+    int32_t p = 0, e = 0;
     uint32_t av = 0;
-    bool small = false;
-    if (row < a.rows) {
-        const int32_t s = element(a.a_start, row);
-        deg = element(a.a_start, row + 1) - s;
-        ub = element(a.ub, row);
-        small = (ub > 0) & (deg > 0) & small_row(deg, ub, G, most);
-        if (small & (l < deg)) {
-            const int2 x = element(a.a_rec, (uint32_t)(s + l));
-            p = element(a.b_start, (uint32_t)x.x);
-            e = element(a.b_start, (uint32_t)x.x + 1);
-            av = (uint32_t)x.y;
-        }
-    }
-    // The LDS has room for the row's products: ub says so, and so do the start arrays of operands that are canonical; of others the
-    // lists are counted here, and a row that has more takes none.
+    bool other = false;                                      // the row is for other kernels
+    if (row < a.rows) operands.template list<G>(row, l, most, p, e, av, other);
+    // The LDS has room for the row's products: of prepared operands ub says so, and so do the start arrays of those that are
+    // canonical; of others the lists are counted here, and a row that has more takes none.
     int len = min(max(e - p, 0), most + 1);
     const int inc16 = row16_inclusive_scan(len);
     int n_products = from_lane<0x15F>(inc16), before = inc16 - len;
@@ -832,7 +885,10 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
         n_products = lane & 8 ? n_products - low : low;
         before -= lane & 8 ? low : 0;
     }
-    if (n_products > most) n_products = len = 0;
+    if (n_products > most) {
+        n_products = len = 0;
+        other = other | Operands::kDirect;
+    }
     const uint32_t of_lists = fold_groups<G>(__ballot(len > 0));          // lists that any of the groups has, a bit each
     const int lists = 32 - __builtin_clz(of_lists | 1u);                   // (one, without elements, where there are none)
     // round t: list t, or with narrow lists the lists t * (G / width) ... of the group, and element j of each
@@ -849,7 +905,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
     };
     // (all requested before any is used; a half, a quarter and a quarter of the rounds there may be, as far as there are any)
     {
-        int2 x[kAhead];
+        typename Operands::Element x[kAhead];
         int abouts[kAhead];
         auto request = [&](auto from, auto count) {
             constexpr int kFrom = decltype(from)::value, kCount = decltype(count)::value;
@@ -860,14 +916,12 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
             for (int t = 0; t < kCount; ++t) {
                 // (rounds of several lists: those past the last one would have lists of other groups)
                 if (kNarrow && kFrom + t >= rounds) abouts[kFrom + t] = 0;
-                uint32_t byte = (uint32_t)(j < abouts[kFrom + t] >> 16 ? begin[t] + j : 0) * 8u;
-                asm volatile("" : "+v"(byte));               // (a 32-bit offset from a scalar base)
-                x[kFrom + t] = *reinterpret_cast<const int2 *>(reinterpret_cast<const char *>(a.b_rec) + byte);
+                x[kFrom + t] = operands.read((uint32_t)(j < abouts[kFrom + t] >> 16 ? begin[t] + j : 0));
             }
         };
         auto put_round = [&](auto round) {
             constexpr int t = decltype(round)::value;
-            put(x[t], of_round<kNarrow, G, t>((int)av, of_list), (abouts[t] & 0xFFFF) + j, j < abouts[t] >> 16);
+            put(operands.entry(x[t]), of_round<kNarrow, G, t>((int)av, of_list), (abouts[t] & 0xFFFF) + j, j < abouts[t] >> 16);
         };
         constexpr std::integral_constant<int, 0> k0{};
         constexpr std::integral_constant<int, kAhead / 2> kHalf{};
@@ -890,8 +944,8 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
             for (int t = 0; t < rounds; ++t) left |= (longer >> (t * per)) & ((1u << per) - 1u) ? 1u << t : 0u;
         }
         int at = 0, end = 0, from = 0, factor = 0;           // of the list's elements, and what is added for their places in B
-        int2 y;
-        auto request = [&] { y = element(a.b_rec, at < end ? (uint32_t)(at + from) : 0u); };
+        typename Operands::Element y;
+        auto request = [&] { y = operands.read(at < end ? (uint32_t)(at + from) : 0u); };
         auto next_round = [&] {
             const int t = __builtin_ctz(left);
             const int of = of_list(about, t);
@@ -904,14 +958,14 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
         };
         next_round();
         for (bool more = true; more;) {
-            const int2 now = y;
+            const typename Operands::Element now = y;
             const int f = factor, place = at;
             const bool on = at < end;
             at += width;
             if (__any(at < end)) request();
             else if (left) next_round();
             else more = false;
-            put(now, f, place, on);
+            put(operands.entry(now), f, place, on);
         }
     }
     wave_sync();
@@ -987,9 +1041,16 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const uint32_t blo
     else if (!__any(n_products > 8 * G)) add_sorted(std::integral_constant<int, 8>{});
     else if constexpr (G == 16) add_sorted(std::integral_constant<int, 16>{});
     if (lane == 0) a.wave_total[block * 4 + wave] = total;
+    if constexpr (Operands::kDirect) {
+        // (rows of other kernels count as empty here, and are told of)
+        if (l == 0 && row < a.rows) put_for(a.finish, a.row_nnz + row, (int32_t)n);
+        const uint32_t of_wave = wave_sum((uint32_t)len), others = __any(other) ? 1u : 0u;
+        if (lane == 0) totals[wave] = make_uint3((uint32_t)total, of_wave, others);
+        return;
+    }
     if (l == 0) {
         // (rows of other kernels count as empty here)
-        if (row < a.rows && (small || ub == 0 || deg <= 0)) put_for(a.finish, a.row_nnz + row, (int32_t)n);
+        if (row < a.rows && !other) put_for(a.finish, a.row_nnz + row, (int32_t)n);
         s_len[threadIdx.x / G] = (uint32_t)n;
     }
     __syncthreads();
@@ -1042,6 +1103,7 @@ __global__ __launch_bounds__(256) void k_small_copy(const CopyArgs a) {
         }
         return;
     }
+    if (!a.ub) return;                       // (k_row_given: no rows of other kernels)
     int from = 0;
     for (int64_t r = r0; r < r1; ++r) {
         const int32_t deg = uniform_load(a.a_start + r + 1) - uniform_load(a.a_start + r), ub = uniform_load(a.ub + r);
@@ -1054,6 +1116,37 @@ __global__ __launch_bounds__(256) void k_small_copy(const CopyArgs a) {
             a.c_val[to + i] = __uint_as_float((uint32_t)x.y);
         }
         from += n;
+    }
+}
+
+// The entries of kSideRows rows into C, flat over the threads: `entries_before` them in C, `at` of the block's before this thread's
+// row, `own` of the block.
+template <int kSideRows>
+__device__ __forceinline__ void move_entries(const CopyArgs &c, int64_t side, uint64_t entries_before, uint32_t at, uint64_t own, uint32_t *s_first) {
+    const int wave_rows = 64 / c.shape.lanes, waves = kSideRows / wave_rows;
+    if ((int)threadIdx.x < kSideRows && threadIdx.x % wave_rows == 0) s_first[threadIdx.x / wave_rows] = at;
+    __syncthreads();
+    const int64_t wave0 = side * waves;
+    const int room = wave_rows * c.shape.products;
+    int32_t *col = c.c_col + entries_before;
+    float *val = c.c_val + entries_before;
+    for (int base = threadIdx.x; base < (int)own; base += 4 * 256) {
+        int2 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t e = (uint32_t)min(base + u * 256, (int)own - 1);
+            int w = 0;                                           // the last wave that begins at or before e
+#pragma unroll
+            for (int d = kSideRows / 8; d > 0; d >>= 1)
+                if (w + d < waves && s_first[w + d] <= e) w += d;
+            x[u] = c.found[(wave0 + w) * room + (e - s_first[w])];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (base + u * 256 < (int)own) {
+                col[base + u * 256] = x[u].x;
+                val[base + u * 256] = __uint_as_float((uint32_t)x[u].y);
+            }
     }
 }
 
@@ -1092,31 +1185,7 @@ __global__ __launch_bounds__(256) void k_small_finish(const FinishArgs a, const 
     // product of these sizes would do for the values: where it would not the host has k_small_copy move the entries once more.)
     // (Also of the block's own end, so that it writes inside C's arrays whatever the sums say.)
     if (!uniform_load(only_small) || (int64_t)entries > a.expected.nnz || (int64_t)(entries_before + own) > a.expected.nnz) return;
-    const int wave_rows = 64 / c.shape.lanes, waves = kSideRows / wave_rows;
-    if ((int)threadIdx.x < kSideRows && threadIdx.x % wave_rows == 0) s_first[threadIdx.x / wave_rows] = at;
-    __syncthreads();
-    const int64_t wave0 = (int64_t)blockIdx.x * waves;
-    const int room = wave_rows * c.shape.products;
-    int32_t *col = c.c_col + entries_before;
-    float *val = c.c_val + entries_before;
-    for (int base = threadIdx.x; base < (int)own; base += 4 * 256) {
-        int2 x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t e = (uint32_t)min(base + u * 256, (int)own - 1);
-            int w = 0;                                           // the last wave that begins at or before e
-#pragma unroll
-            for (int d = kSideRows / 8; d > 0; d >>= 1)
-                if (w + d < waves && s_first[w + d] <= e) w += d;
-            x[u] = c.found[(wave0 + w) * room + (e - s_first[w])];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (base + u * 256 < (int)own) {
-                col[base + u * 256] = x[u].x;
-                val[base + u * 256] = __uint_as_float((uint32_t)x[u].y);
-            }
-    }
+    move_entries<kSideRows>(c, blockIdx.x, entries_before, at, own, s_first);
 }
 
 // ---- heavy rows -------------------------------------------------------------------------------------------------
@@ -1288,7 +1357,7 @@ struct NoPack {};
 // per row, 945 and 950; of scale 18, which fills the chip either way and has fewer waves here, the two 434 and 476.
 constexpr int64_t kPackRows = 1 << 15;
 template <int G, bool kNarrow, typename Pack = NoPack>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_small(const SmallArgs a, const SumArgs sums, const FinishArgs fin, const Pack pack) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_small(const SmallArgs a, const PreparedOperands operands, const SumArgs sums, const FinishArgs fin, const Pack pack) {
     __shared__ int s_last;
     uint32_t block = blockIdx.x, blocks = gridDim.x;
     if constexpr (!std::is_same<Pack, NoPack>::value) {
@@ -1301,7 +1370,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     }
     const int sum_block = (int)block - (a.sums_first ? 0 : (int)blocks - a.sum_blocks);
     if (sum_block >= 0 && sum_block < a.sum_blocks) sum_tile_rows(sums, sum_block, a.sum_blocks, a.finish);
-    else row_small<G, kNarrow>(a, block - (a.sums_first ? (uint32_t)a.sum_blocks : 0u));
+    else row_small<G, kNarrow>(a, operands, block - (a.sums_first ? (uint32_t)a.sum_blocks : 0u));
     if (!a.finish) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left for the last block has arrived
     __syncthreads();
@@ -1309,6 +1378,359 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         s_last = atomicAdd(reinterpret_cast<unsigned long long *>(fin.d_scalars + S_ROW_ARRIVED), 1ull) == blocks - 1;
     __syncthreads();
     if (s_last) row_finish<true>(fin, 0, 1);
+}
+
+// ---- small rows straight from the operands ------------------------------------------------------------------------
+// A product of sizes whose last product had small rows only needs no records of its entries, and no list of other rows.  One launch
+// has blocks that look the operands over (validation, tiles), blocks that take rows as the caller gave them (GivenOperands), and
+// blocks that add up the pairs of tiles; the last of all hands the sizes to the host, which has the time of the next launch for the
+// next call.  That one makes row_ptr and moves the entries into C (k_given_finish); for products of one chunk of rows the last block
+// makes row_ptr, and k_small_copy moves them.  Where a row turns out to be for other kernels the product is started again with
+// k_row_prepare.
+// Bound, as k_row_small is, by round trips and by how few waves there are to hide them while a launch begins and ends; so fewer
+// launches, with more of different kinds in each.  k_row_prepare, k_row_small and k_small_finish, one behind the other, against these
+// two: a 512 x 512 mesh 16.1 + 28.4 + 12.1 us and 36.7 + 12.8, 65,536 rows of 8 random entries 10.8 + 24.4 + 12.3 and 29.6 + 13.0,
+// A*P on a 64^3 grid 25.6 + 19.2 + 6.7 and 32.4 + 7.4; the products 56.4 -> 46.7, 47.3 -> 41.0, 58.5 -> 41.7, a 37 x 37 mesh 26.6 ->
+// 22.9, 1024 rows of 8 entries 27.0 -> 24.5.  Without the pairs of tiles 33.6, 24.3 and 28.3 us, but added up by blocks of the second
+// launch they hand the sizes over so late that the GPU waits for the next call (58.3, 49.1, 53.6).  Blocks that count themselves with
+// an addition whose result they wait for, 38.4, 33.6 and 38.4 us; one block that looks at the counters needs no such wait.
+template <typename RP>
+struct TileArgs {                        // of an operand
+    const RP *row_ptr;
+    const int32_t *col;
+    int64_t rows, cols, nnz;
+    int bitmap_words;
+    // of every tile-row: its first entry, its tiles, and their columns, from there on, in any order (null: they are not wanted)
+    int32_t *first, *ntiles, *tile_col;
+};
+
+// A wave for `per_wave` (1 or 4) tile-rows, two entries per lane in flight and the next tile-row's first ones: k_row_prepare without
+// what is kept of the entries.  Other blocks of the launch read what it leaves.  The number of tiles of the wave's.
+template <typename RP>
+__device__ __forceinline__ int32_t count_tiles(const TileArgs<RP> &a, uint32_t block, int per_wave, bool validate, int64_t *d_scalars) {
+    extern __shared__ __align__(16) unsigned char small_lds[];
+    __shared__ uint32_t s_starts[4][4];  // of the entries of a trip, those that begin a row
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    uint32_t *bitmap = reinterpret_cast<uint32_t *>(small_lds) + wave * a.bitmap_words, *starts = s_starts[wave];
+    const int64_t I0 = ((int64_t)block * 4 + wave) * per_wave;
+    if (I0 * T >= a.rows) return 0;
+    // lane 16 t + r: row r of tile-row t, and of all lanes the row behind the last
+    const int64_t i = min(I0 * T + lane, a.rows), behind = min((I0 + per_wave) * T, a.rows);
+    auto clamped = [&](RP raw) { return (int32_t)min(max(raw, (RP)0), (RP)a.nnz); };
+    const RP raw = a.row_ptr[i], raw_behind = a.row_ptr[behind];
+    const int32_t q = clamped(raw), end = clamped(raw_behind);
+    int32_t p = q;
+    p = max(p, TSP_DPP(p, p, 0x111, 0xf, false));
+    p = max(p, TSP_DPP(p, p, 0x112, 0xf, false));
+    p = max(p, TSP_DPP(p, p, 0x114, 0xf, false));
+    p = max(p, TSP_DPP(p, p, 0x118, 0xf, false));
+    bool bad = lane < per_wave * T && (raw != (RP)p || (i == 0 && raw != 0) || (i == a.rows && raw != (RP)a.nnz));
+    bad = bad | (raw_behind != (RP)end) | (behind == a.rows && raw_behind != (RP)a.nnz);
+    auto begin_of = [&](int t) { return t < per_wave ? __builtin_amdgcn_readlane(q, t * T) : end; };
+    int32_t all = 0;
+    int32_t next[2];                     // columns of the tile-row's first entries
+    auto request = [&](int32_t from, int32_t to) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) next[u] = a.col[max(min(from + u * 64 + lane, to - 1), 0)];
+    };
+    auto end_of = [&](int t) { return max(__builtin_amdgcn_readlane(p, t * T + T - 1), begin_of(t + 1)); };
+    request(begin_of(0), end_of(0));
+    for (int t = 0; t < per_wave && (I0 + t) * T < a.rows; ++t) {
+        const int32_t e0 = begin_of(t), e1 = end_of(t);
+        // (what follows a tile-row is no less than its end, or the operand is not canonical)
+        bad = bad | (e1 != begin_of(t + 1));
+        for (int w = lane; w < a.bitmap_words / 4; w += 64) reinterpret_cast<uint4 *>(bitmap)[w] = make_uint4(0, 0, 0, 0);
+        int32_t c[2] = {next[0], next[1]};
+        if (t + 1 < per_wave) request(begin_of(t + 1), end_of(t + 1));
+        int32_t listed = 0, before = 0;  // column of the entry before the trip
+        for (int32_t base = e0; base < e1; base += 128) {
+            if (base > e0)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) c[u] = a.col[min(base + u * 64 + lane, e1 - 1)];
+            if (lane < 4) starts[lane] = 0;
+            wave_sync();
+            if (lane / T == t && (uint32_t)(p - base) < 128u) atomicOr(&starts[(p - base) >> 5], 1u << ((p - base) & 31));
+            wave_sync();
+            uint32_t begins[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) begins[u] = starts[2 * u + (lane >> 5)] >> (lane & 31);
+            int32_t prev[2];
+            prev[0] = TSP_DPP(before, c[0], 0x138, 0xf, false);            // wave_shr:1
+            prev[1] = TSP_DPP(__builtin_amdgcn_readlane(c[0], 63), c[1], 0x138, 0xf, false);
+            before = __builtin_amdgcn_readlane(c[1], 63);
+            uint32_t had[2];
+            bool first[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int32_t k = base + u * 64 + lane;
+                const bool on = k < e1, outside = (uint32_t)c[u] >= (uint64_t)a.cols;
+                bad = bad | (on & (outside | (!(begins[u] & 1u) & (prev[u] >= c[u]))));
+                if (outside) c[u] = 0;
+                // (of the entries of a tile one behind the other, also over the end of a row, the first)
+                first[u] = on & ((k == e0) | ((prev[u] >> 4) != (c[u] >> 4)));
+                had[u] = first[u] ? atomicOr(&bitmap[c[u] >> 9], 1u << ((c[u] >> 4) & 31)) : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                first[u] = first[u] & !((had[u] >> ((c[u] >> 4) & 31)) & 1u);
+                const unsigned long long firsts = __ballot(first[u]);
+                if (first[u] && a.tile_col) put_for(true, a.tile_col + e0 + listed + __popcll(firsts & ((1ull << lane) - 1ull)), c[u] >> 4);
+                listed += __popcll(firsts);
+            }
+        }
+        if (lane == 0) {
+            if (a.first) put_for(true, a.first + I0 + t, e0);
+            put_for(true, a.ntiles + I0 + t, listed);
+        }
+        all += listed;
+        wave_sync();
+    }
+    if (bad && validate) put_for(true, d_scalars + S_INVALID, (int64_t)1);
+    return all;
+}
+
+// Blocks of a launch that count themselves, in groups of kArriveGroup, with what they have to add up: a counter per group, zero
+// before and after.  (An addition to one counter is 9 ns; 8192 of them would outlast the launch.)  Blocks in the upper 8 bits, below
+// them what the blocks add up.
+constexpr int kArriveGroup = 64;
+constexpr int kArriveShift = 56;
+constexpr unsigned long long kArriveSum = (1ull << kArriveShift) - 1ull;
+__host__ __device__ constexpr uint32_t arrive_groups(uint32_t blocks) { return (blocks + kArriveGroup - 1) / kArriveGroup; }
+__device__ __forceinline__ uint32_t arrive_blocks(uint32_t group, uint32_t blocks) { return min(blocks - group * kArriveGroup, (uint32_t)kArriveGroup); }
+// The blocks of a launch are dispatched in order, so those before a block that waits run or are done.  Waits are bounded all the same:
+// so many looks, a microsecond each, and the host starts the product again.
+constexpr unsigned kArriveSpins = 1u << 18;
+template <typename X, typename Done>
+__device__ __forceinline__ X wait_for(const X *p, Done done, bool *failed) {
+    X v;
+    unsigned spins = 0;
+    while (!done(v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) && ++spins < kArriveSpins) __builtin_amdgcn_s_sleep(2);
+    *failed = *failed | (spins >= kArriveSpins);
+    return v;
+}
+__device__ __forceinline__ unsigned long long add_scalar(int64_t *d_scalars, int slot, unsigned long long v) {
+    return atomicAdd(reinterpret_cast<unsigned long long *>(d_scalars + slot), v);
+}
+
+struct GivenPublishArgs {
+    int64_t rows, room;                  // room: entries that the arrays of C hold
+    int64_t *c_row_ptr;
+    int64_t *d_scalars, *h_scalars_dev;
+    int64_t publish_tag;
+    int32_t *live;                       // of k_small_copy, or null: whether it may run
+    int same;                            // A and B are one matrix
+};
+// publish_scalars by one wave; `candidates` and `failed` beyond what stands in the scalar block
+__device__ __forceinline__ void publish_given(const GivenPublishArgs &a, int64_t entries, int64_t products, int64_t others, int64_t candidates, int64_t failed) {
+    const int lane = lane_id();
+    int64_t v = 0;
+    if (lane < kScalars) v = __hip_atomic_load(a.d_scalars + (a.same && lane == S_TILES_B ? (int)S_TILES_A : lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v = lane == S_C_NNZ ? entries : lane == S_ROW_PRODUCTS ? products : lane == S_ROW_HEAVY ? others : lane == S_CANDIDATES ? v + candidates : lane == S_INTERNAL ? v + failed : v;
+    const bool invalid = __any((lane == S_INVALID || lane == S_INTERNAL) && v != 0);
+    if (lane < kScalars) {
+        const uint64_t slot = (publish_tag16(a.publish_tag) << kPublishTagShift) | ((uint64_t)v & ((1ull << kPublishTagShift) - 1u));
+        __hip_atomic_store(&a.h_scalars_dev[lane], (int64_t)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        a.d_scalars[lane] = 0;
+    }
+    if (lane == 0) {
+        a.c_row_ptr[a.rows] = entries;
+        if (a.live) *a.live = !invalid && !others && entries <= a.room;
+    }
+}
+
+template <typename RP, typename VT>
+struct GivenArgs {
+    SmallArgs small;
+    GivenOperands<RP, VT> operands;
+    TileArgs<RP> a, b;
+    int64_t a_tile_rows, b_tile_rows;
+    const int32_t *b_ntiles;
+    // blocks of the launch: tiles of A, of B (none if it is A), rows, with those for the pairs of tiles (none for one chunk of rows)
+    // among them, and one that waits for all others
+    uint32_t a_blocks, b_blocks, row_blocks, pair_blocks;
+    int per_wave;                        // tile-rows
+    int validate;
+    unsigned long long *counters;        // of groups of blocks: tiles of A, of B, rows
+    GivenPublishArgs publish;
+};
+
+// The pairs of tiles of 16 tile-rows of A at a time, every `blocks`-th 16: 16 lanes to a tile-row, four tile-rows and of each 64
+// tiles in flight.  The thread's share.
+template <typename RP, typename VT>
+__device__ __forceinline__ unsigned long long count_pairs(const GivenArgs<RP, VT> &a, uint32_t block, uint32_t blocks) {
+    const int r = threadIdx.x & 15;
+    unsigned long long pairs = 0;
+    for (int64_t base = (int64_t)block * 16 + (threadIdx.x >> 4); base < a.a_tile_rows; base += (int64_t)blocks * 64) {
+        int32_t first[4], n[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t I = base + (int64_t)blocks * 16 * u;
+            first[u] = n[u] = 0;
+            if (I < a.a_tile_rows) {
+                first[u] = get_shared<true>(a.a.first + I);
+                n[u] = get_shared<true>(a.a.ntiles + I);
+            }
+        }
+        for (int32_t j = r; __any(j < max(max(n[0], n[1]), max(n[2], n[3]))); j += 64) {
+            int32_t K[4][4], of_b[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) K[u][v] = j + 16 * v < n[u] ? get_shared<true>(a.a.tile_col + first[u] + j + 16 * v) : INT32_MAX;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) of_b[u][v] = K[u][v] < a.b_tile_rows ? get_shared<true>(a.b_ntiles + K[u][v]) : 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) pairs += (uint32_t)of_b[u][v];
+        }
+    }
+    return pairs;
+}
+// The sum over the block, in its first thread
+__device__ __forceinline__ unsigned long long add_threads(unsigned long long v, unsigned long long (&s_sum)[4]) {
+    const unsigned long long of_wave = wave_inclusive_scan64(v);
+    __syncthreads();
+    if (lane_id() == 63) s_sum[threadIdx.x >> 6] = of_wave;
+    __syncthreads();
+    return s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+}
+
+template <int G, bool kNarrow, typename RP, typename VT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_given(const GivenArgs<RP, VT> a) {
+    __shared__ uint3 s_totals[4];
+    __shared__ unsigned long long s_sum[4];
+    const uint32_t tile_blocks = a.a_blocks + a.b_blocks, tile_groups = arrive_groups(a.a_blocks) + arrive_groups(a.b_blocks), row_groups = arrive_groups(a.row_blocks);
+    const bool one_chunk = a.small.finish;
+    int64_t *d_scalars = a.publish.d_scalars;
+    if (blockIdx.x < tile_blocks) {
+        const bool of_b = blockIdx.x >= a.a_blocks;
+        const uint32_t block = blockIdx.x - (of_b ? a.a_blocks : 0u), blocks = of_b ? a.b_blocks : a.a_blocks;
+        const int32_t tiles = count_tiles(of_b ? a.b : a.a, block, a.per_wave, a.validate, d_scalars);
+        if (lane_id() == 0) s_totals[threadIdx.x >> 6].x = (uint32_t)tiles;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // what this wave has left for other blocks has arrived
+        __syncthreads();
+        if (threadIdx.x > 0) return;
+        // the last of its group tells the others
+        unsigned long long *counter = a.counters + ((of_b ? arrive_groups(a.a_blocks) : 0u) + block / kArriveGroup) * kArriveStride;
+        const unsigned long long mine = (unsigned long long)s_totals[0].x + s_totals[1].x + s_totals[2].x + s_totals[3].x;
+        const unsigned long long had = atomicAdd(counter, mine + (1ull << kArriveShift));
+        if ((had >> kArriveShift) + 1 != arrive_blocks(block / kArriveGroup, blocks)) return;
+        __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        (void)add_scalar(d_scalars, of_b ? S_TILES_B : S_TILES_A, (had & kArriveSum) + mine);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        (void)add_scalar(d_scalars, S_GIVEN_ARRIVED, 1);
+        return;
+    }
+    // (the pairs after half of the rows: the tiles are done by then, and their round trips pass beside the other half)
+    const uint32_t at = blockIdx.x - tile_blocks, half = a.row_blocks / 2;
+    if (at < half || (at >= half + a.pair_blocks && at < a.row_blocks + a.pair_blocks)) {
+        const uint32_t block = at < half ? at : at - a.pair_blocks;
+        row_small<G, kNarrow>(a.small, a.operands, block, s_totals);
+        if (one_chunk) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (the last block reads row_nnz)
+        __syncthreads();
+        if (threadIdx.x > 0) return;
+        uint32_t entries = 0, products = 0, others = 0;
+        for (int w = 0; w < 4; ++w) {
+            entries += s_totals[w].x;
+            products += s_totals[w].y;
+            others |= s_totals[w].z;
+        }
+        if (!one_chunk) a.small.block_len[block] = entries;
+        static_assert(kArriveGroup * 16 * 192 < 1 << 20 && kArriveGroup * 32 * 96 < 1 << 20, "sums over a group");
+        atomicAdd(a.counters + (tile_groups + block / kArriveGroup) * kArriveStride,
+                  1ull << kArriveShift | (unsigned long long)others << 40 | (unsigned long long)products << 20 | entries);
+        return;
+    }
+    const bool last = at == a.row_blocks + a.pair_blocks;
+    bool failed = false;
+    unsigned long long pairs = 0;
+    if (one_chunk || !last) {
+        if (threadIdx.x == 0) (void)wait_for(d_scalars + S_GIVEN_ARRIVED, [&](int64_t v) { return v == (int64_t)tile_groups; }, &failed);
+        __syncthreads();
+        pairs = add_threads(count_pairs(a, one_chunk ? 0u : at - half, one_chunk ? 1u : a.pair_blocks), s_sum);
+        if (!one_chunk) {
+            if (threadIdx.x > 0) return;
+            (void)add_scalar(d_scalars, S_CANDIDATES, pairs);
+            if (failed) (void)add_scalar(d_scalars, S_INTERNAL, 1);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            (void)add_scalar(d_scalars, S_ROW_ARRIVED, 1);
+            return;
+        }
+    }
+    // the last block: the groups of blocks of rows, and the other blocks of pairs
+    unsigned long long sum = 0;
+    if (threadIdx.x < row_groups) {
+        unsigned long long *counter = a.counters + (tile_groups + threadIdx.x) * kArriveStride;
+        sum = wait_for(counter, [&](unsigned long long v) { return (v >> kArriveShift) == arrive_blocks(threadIdx.x, a.row_blocks); }, &failed);
+        __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (threadIdx.x == 0) (void)wait_for(d_scalars + S_ROW_ARRIVED, [&](int64_t v) { return v == (int64_t)a.pair_blocks; }, &failed);
+    const uint32_t of_wave[3] = {wave_sum((uint32_t)sum & 0xFFFFFu), wave_sum((uint32_t)(sum >> 20) & 0xFFFFFu), wave_sum((uint32_t)(sum >> 40) & 0xFFFFu)};
+    const bool any_failed = __any(failed);
+    if (lane_id() == 0) s_totals[threadIdx.x >> 6] = make_uint3(of_wave[0], of_wave[1], of_wave[2] | (any_failed ? 1u << 31 : 0u));
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        int64_t entries = 0, products = 0, others = 0, failures = 0;
+        for (int w = 0; w < 4; ++w) {
+            entries += s_totals[w].x;
+            products += s_totals[w].y;
+            others += s_totals[w].z & 0x7FFFFFFFu;
+            failures += s_totals[w].z >> 31;
+        }
+        publish_given(a.publish, entries, products, others, (int64_t)pairs, failures);
+    }
+    if (!one_chunk) return;
+    // row_ptr of one chunk of rows
+    __shared__ uint64_t lds[256 / 64];
+    constexpr int kItems = kChunkRows / 256;
+    const int base = (int)threadIdx.x * kItems;
+    uint32_t x[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) x[i] = base + i < a.small.rows ? (uint32_t)get_shared<true>(a.small.row_nnz + base + i) : 0u;
+    uint64_t of_thread = 0, total;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) of_thread += x[i];
+    uint64_t run = block_exclusive_scan64<256>(of_thread, &total, lds);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        if (base + i < a.small.rows) a.publish.c_row_ptr[base + i] = (int64_t)run;
+        run += x[i];
+    }
+}
+
+// Behind k_row_given, kSideRows rows to a block: their row_ptr, and their entries into C.  The entries before theirs from the numbers
+// of the blocks of rows.
+template <int kSideRows>
+__global__ __launch_bounds__(256) void k_given_finish(const CopyArgs c, int64_t *c_row_ptr, const int32_t *row_nnz, const uint32_t *block_len, int64_t room) {
+    __shared__ uint64_t lds[256 / 64];
+    __shared__ uint32_t s_first[kSideRows / 4];                  // entries of the block before each wave of k_row_given
+    const int64_t row0 = (int64_t)blockIdx.x * kSideRows, row = (int)threadIdx.x < kSideRows ? row0 + threadIdx.x : c.rows;
+    const int blocks_before = (int)(row0 * c.shape.lanes / 256);
+    const uint32_t mine = row < c.rows ? (uint32_t)row_nnz[row] : 0u;
+    uint64_t before = 0;
+    const uint4 *len4 = reinterpret_cast<const uint4 *>(block_len);
+    for (int i0 = threadIdx.x; i0 * 4 < blocks_before; i0 += 8 * 256) {
+        uint4 len[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) len[u] = len4[min(i0 + u * 256, (blocks_before - 1) / 4)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int left = blocks_before - (i0 + u * 256) * 4;
+            before += left > 0 ? len[u].x : 0u;
+            before += left > 1 ? len[u].y : 0u;
+            before += left > 2 ? len[u].z : 0u;
+            before += left > 3 ? len[u].w : 0u;
+        }
+    }
+    uint64_t entries_before, own;
+    (void)block_exclusive_scan64<256>(before, &entries_before, lds);
+    const uint32_t at = (uint32_t)block_exclusive_scan64<256>(mine, &own, lds);
+    if (row < c.rows) c_row_ptr[row] = (int64_t)(entries_before + at);
+    if ((int64_t)(entries_before + own) > room) return;         // (the host has k_small_copy move all entries once more)
+    move_entries<kSideRows>(c, blockIdx.x, entries_before, at, own, s_first);
 }
 
 // 64 pieces of up to 16 elements of B, four to a step: lane 16 q + t describes piece 4 t + q by the byte offset of its first
@@ -2077,6 +2499,7 @@ void launch_fill(FillArgs &f, FillKind kind, bool short_rows, bool split, hipStr
 __global__ void k_clear_lists(int64_t *d_scalars) {
     if (threadIdx.x == 0) d_scalars[S_ROW_LISTS] = d_scalars[S_ROW_LARGE_TASKS] = 0;
 }
+__global__ void k_clear_arrivals(unsigned long long *counters) { counters[(blockIdx.x * 256 + threadIdx.x) * kArriveStride] = 0; }
 // all but the count of products, which has run before anything else of the call
 __global__ void k_clear_rows(int64_t *d_scalars, int64_t products) {
     if (threadIdx.x < kScalars) d_scalars[threadIdx.x] = threadIdx.x == S_PRODUCTS ? products : 0;
@@ -2188,7 +2611,141 @@ __global__ __launch_bounds__(256) void k_row_sample(const SampleArgs a) {
 }
 
 // What a run of the row kernels has come to
-enum RowsEnd { kRowsNotTaken, kRowsTaken, kRowsOtherLanes };
+enum RowsEnd { kRowsNotTaken, kRowsTaken, kRowsAgain };     // (again: with other lanes, or with the operands prepared)
+
+// A product of sizes whose last product had small rows only, straight from the operands (k_row_given).  Up to kGivenBlocks blocks of
+// rows, whose numbers every block of k_given_finish adds up, and bitmaps of no more LDS than leaves a CU its eight blocks.
+constexpr int64_t kGivenBlocks = 16384;
+constexpr size_t kGivenBitmaps = 16 * 1024;
+constexpr int64_t kGivenRows = kGivenBlocks * 32, kGivenColumns = (int64_t)kGivenBitmaps / 16 * 32 * T;     // at most, of A
+static_assert(arrive_groups(kGivenBlocks) + arrive_groups(kGivenRows / T / 4) + arrive_groups(kGivenColumns / T / 4) <= kArriveCounters, "of the rows, the tiles of A and of B");
+template <typename RP, typename VT>
+static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, RowHint &hint,
+                         const SmallShape &shape, int cost_lanes, RowsEnd *end) {
+    const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
+    const int64_t row_blocks = (A->rows * shape.lanes + 255) / 256;
+    const bool one_chunk = A->rows <= kChunkRows;
+    Workspace ws{ctx, s, {}};
+    GivenArgs<RP, VT> a{};
+    auto tiles_of = [&](const tsp_csr *M, int64_t ntr, bool left) {
+        TileArgs<RP> t{static_cast<const RP *>(M->row_ptr), M->col_idx, M->rows, M->cols, M->nnz, (int)((M->cols + T * 32 - 1) / (T * 32) + 3) & ~3, nullptr, nullptr, nullptr};
+        t.ntiles = ws.get<int32_t>((size_t)ntr);
+        if (left) {
+            t.first = ws.get<int32_t>((size_t)ntr);
+            t.tile_col = ws.get<int32_t>((size_t)M->nnz);
+        }
+        return t;
+    };
+    a.a = tiles_of(A, a_ntr, true);
+    a.per_wave = one_chunk ? 1 : 4;
+    const int per_block = 4 * a.per_wave;
+    a.a_blocks = (uint32_t)((a_ntr + per_block - 1) / per_block);
+    if (!alias) {
+        a.b = tiles_of(B, b_ntr, false);
+        a.b_blocks = (uint32_t)((b_ntr + per_block - 1) / per_block);
+    }
+    a.a_tile_rows = a_ntr;
+    a.b_tile_rows = b_ntr;
+    a.b_ntiles = alias ? a.a.ntiles : a.b.ntiles;
+    a.row_blocks = (uint32_t)row_blocks;
+    a.pair_blocks = one_chunk ? 0u : (uint32_t)std::min<int64_t>(kPlanBlocks, (a_ntr + 15) / 16);
+    a.validate = ctx->validate;
+    a.counters = ctx->d_arrivals;
+    a.operands = {static_cast<const RP *>(A->row_ptr), static_cast<const RP *>(B->row_ptr), A->col_idx, B->col_idx, static_cast<const VT *>(A->val),
+                  static_cast<const VT *>(B->val), (int32_t)A->nnz, (int32_t)B->nnz, (uint32_t)(A->cols - 1), (uint32_t)(B->cols - 1)};
+    SmallArgs &m = a.small;
+    m.shape = shape;
+    m.wave_bytes = (int)shape.wave_bytes();
+    m.rows = A->rows;
+    m.finish = one_chunk;
+    m.row_nnz = ws.get<int32_t>((size_t)A->rows);
+    m.found = ws.get<int2>((size_t)(row_blocks * (256 / shape.lanes) * shape.products));
+    m.wave_total = ws.get<int32_t>((size_t)row_blocks * 4);
+    m.block_len = ws.get<uint32_t>((size_t)row_blocks + 3);               // (read four at a time)
+    int64_t *row_ptr = ws.get<int64_t>((size_t)A->rows + 1);
+    const int64_t room = hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20);
+    int32_t *col = ws.get<int32_t>((size_t)room), *live = one_chunk ? ws.get<int32_t>(1) : nullptr;
+    float *val = ws.get<float>((size_t)room);
+    if (ws.failed) return TSP_ERR_ALLOC_FAILED;
+    a.publish = GivenPublishArgs{A->rows, room, row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, live, alias};
+
+    phase_begin(ctx, TSP_PHASE_SYMBOLIC, s);
+    {
+        KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
+        const size_t lds = std::max(4 * shape.wave_bytes() + SmallShape::kReadPast, (size_t)std::max(a.a.bitmap_words, a.b.bitmap_words) * 16);
+        auto kernel = shape.lanes == 8 ? (shape.narrow() ? k_row_given<8, true, RP, VT> : k_row_given<8, false, RP, VT>)
+                                       : (shape.narrow() ? k_row_given<16, true, RP, VT> : k_row_given<16, false, RP, VT>);
+        hipLaunchKernelGGL(kernel, dim3(a.a_blocks + a.b_blocks + a.row_blocks + a.pair_blocks + 1u), dim3(256), lds, s, a);
+    }
+    phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
+    CopyArgs copy{shape, A->rows, row_blocks * 4, nullptr, nullptr, m.found, m.wave_total, row_ptr, col, val, live};
+    auto move = [&] { hipLaunchKernelGGL(k_small_copy, dim3((unsigned)row_blocks), dim3(256), 0, s, copy); };
+    phase_begin(ctx, TSP_PHASE_NUMERIC, s);
+    {
+        KernelTimer kt(ctx, TSP_KERNEL_NUMERIC, s);
+        auto launch = [&](auto kernel, int rows) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((A->rows + rows - 1) / rows)), dim3(256), 0, s, copy, row_ptr, m.row_nnz, m.block_len, room);
+        };
+        // (about 2000 entries to a block: see k_small_finish)
+        const int64_t mean = hint.nnz / A->rows;
+        if (one_chunk) move();
+        else if (mean < 10) launch(k_given_finish<256>, 256);
+        else if (mean < 20) launch(k_given_finish<128>, 128);
+        else if (mean < 40) launch(k_given_finish<64>, 64);
+        else launch(k_given_finish<32>, 32);
+    }
+    phase_end(ctx, TSP_PHASE_NUMERIC, s);
+    TSP_HIP_CHECK(ctx, hipGetLastError());
+    const int rc = wait_published_scalars(ctx, ctx->publish_tag, s);
+    if (rc) return rc;
+    ctx->scalars_clean = true;               // (cleared for the next call)
+    const int64_t *h = ctx->h_scalars;
+    if (h[S_INVALID]) return TSP_ERR_NOT_CANONICAL;
+    if (h[S_INTERNAL]) hipLaunchKernelGGL(k_clear_arrivals, dim3(kArriveCounters / 256), dim3(256), 0, s, ctx->d_arrivals);
+    if (h[S_ROW_HEAVY] || h[S_INTERNAL]) {
+        hint.others = true;
+        *end = kRowsAgain;
+        return TSP_OK;
+    }
+    const int64_t nnz = h[S_C_NNZ];
+    hint.candidates = h[S_CANDIDATES];
+    hint.products = h[S_ROW_PRODUCTS];
+    hint.nnz = nnz;
+    hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], h[S_ROW_PRODUCTS], hint.wide ? 16 : cost_lanes, 0, true, h[S_CANDIDATES]);
+    if (hint.tiles) {
+        *end = kRowsNotTaken;
+        return TSP_OK;
+    }
+    if (nnz > room) {
+        copy.c_col = col = ws.get<int32_t>((size_t)nnz);
+        copy.c_val = val = ws.get<float>((size_t)nnz);
+        copy.live = nullptr;
+        if (ws.failed) return TSP_ERR_ALLOC_FAILED;
+        move();
+        TSP_HIP_CHECK(ctx, hipGetLastError());
+    }
+    ctx->stats.a_tiles = h[S_TILES_A];
+    ctx->stats.b_tiles = h[S_TILES_B];
+    ctx->stats.candidate_pairs = h[S_CANDIDATES];
+    ctx->stats.pairs = 0;
+    ctx->stats.c_tiles = 0;
+    ctx->stats.c_nnz = nnz;
+    fill_selection_criteria(ctx, A->rows, A->nnz, h[S_TILES_A]);
+    ws.keep(row_ptr);
+    ws.keep(col);
+    ws.keep(val);
+    *C = tsp_csr{};
+    C->rows = A->rows;
+    C->cols = B->cols;
+    C->nnz = nnz;
+    C->row_ptr = row_ptr;
+    C->col_idx = col;
+    C->val = val;
+    C->row_ptr_type = TSP_I64;
+    C->val_type = TSP_F32;
+    *end = kRowsTaken;
+    return TSP_OK;
+}
 
 static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, RowsEnd *end,
                        RowHint **remembered) {
@@ -2231,6 +2788,14 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     auto found_entries = [&] { return ((A->rows * shape.lanes + 255) / 256) * 256 / shape.lanes * shape.products; };
     while (shape.products > 24 && found_entries() > kFoundEntries) shape.products /= 2;
     if (found_entries() > kFoundEntries) return TSP_OK;
+    // straight from the operands, by the last product of these sizes
+    auto of_waves = [](const tsp_csr *M) { return M->nnz <= 128 * ((M->rows + T - 1) / T) && ((M->cols + T * 32 - 1) / (T * 32) + 3) / 4 * 64 <= (int64_t)kGivenBitmaps; };
+    if (known && hint.nnz >= 0 && hint.heavy == 0 && hint.small && !hint.others && shape.lanes == lanes_unless_wide && A->rows <= kFinishRows &&
+        (A->rows * shape.lanes + 255) / 256 <= kGivenBlocks && A->row_ptr_type == B->row_ptr_type && A->val_type == B->val_type && of_waves(A) && (alias || of_waves(B))) {
+        const bool f16 = A->val_type == TSP_F16, i32 = A->row_ptr_type == TSP_I32;
+        auto run = i32 ? (f16 ? rowwise_given<int32_t, uint16_t> : rowwise_given<int32_t, float>) : f16 ? rowwise_given<int64_t, uint16_t> : rowwise_given<int64_t, float>;
+        return run(ctx, A, B, alias, C, s, hint, shape, cost_lanes, end);
+    }
     const int64_t small_waves = ((A->rows * shape.lanes + 255) / 256) * 4;
     const int shift = B->cols <= 2048 ? 11 : 12;
     const int windows = (int)((B->cols + (1 << shift) - 1) >> shift);
@@ -2403,7 +2968,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         if (!rc) rc = sizes_known();
         if (rc) return rc;
         if (hint.tiles || other_lanes) {     // (the tile kernels start over; the scalars they use are cleared for them)
-            *end = hint.tiles ? kRowsNotTaken : kRowsOtherLanes;
+            *end = hint.tiles ? kRowsNotTaken : kRowsAgain;
             return TSP_OK;
         }
     }
@@ -2439,11 +3004,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     SmallArgs m{};
     m.shape = shape;
     m.rows = A->rows;
-    m.a_start = ma.start;
-    m.b_start = mb.start;
-    m.ub = left.ub;
-    m.a_rec = ma.rec;
-    m.b_rec = mb.rec;
+    const PreparedOperands prepared{ma.start, mb.start, left.ub, ma.rec, mb.rec};
     m.wave_bytes = (int)shape.wave_bytes();
     m.found = found;
     m.wave_total = wave_total;
@@ -2489,7 +3050,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
         m.finish = finish_too;
         auto launch = [&](auto kernel, const auto &p, unsigned pack_blocks) {
-            hipLaunchKernelGGL(kernel, dim3(pack_blocks + small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes() + SmallShape::kReadPast, s, m, sums,
+            hipLaunchKernelGGL(kernel, dim3(pack_blocks + small_blocks + (unsigned)sum_blocks), dim3(256), 4 * shape.wave_bytes() + SmallShape::kReadPast, s, m, prepared, sums,
                                finish_too ? finish_args() : FinishArgs{}, p);
         };
         const bool at_once = n_heavy > 0 && B->rows <= kPackRows;
@@ -2638,7 +3199,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     rc = sizes_known();
     if (rc) return rc;
     if (hint.tiles || other_lanes) {         // another matrix of the same sizes: as it would be done if it had come first
-        *end = hint.tiles ? kRowsNotTaken : kRowsOtherLanes;
+        *end = hint.tiles ? kRowsNotTaken : kRowsAgain;
         return TSP_OK;
     }
     const bool done = ahead && expected.holds(ctx->h_scalars) && (had_small || ctx->h_scalars[S_ROW_SMALL] == 0);
@@ -2695,7 +3256,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
     *remembered = nullptr;
     RowsEnd end = kRowsNotTaken;
     int rc = TSP_OK;
-    for (int runs = 0; runs < 2; ++runs) {
+    for (int runs = 0; runs < 3; ++runs) {                   // (straight from the operands, by 8 lanes, by 16)
         const int64_t tag = ctx->publish_tag;
         rc = rowwise_run(ctx, A, B, alias, C, s, &end, remembered);
         if (rc || end == kRowsTaken) break;
@@ -2703,7 +3264,7 @@ int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool al
             hipLaunchKernelGGL(k_clear_rows, dim3(1), dim3(64), 0, s, ctx->d_scalars, ctx->h_scalars[S_PRODUCTS]);
             ctx->scalars_clean = false;
         }
-        if (end != kRowsOtherLanes) break;
+        if (end != kRowsAgain) break;
     }
     *taken = end == kRowsTaken;
     return rc;

@@ -492,6 +492,96 @@ def test_products_of_small_rows_sorted(tsp, oracle, rows, a_row, b_row, other, c
         h.close()
 
 
+def _short(rng, rows, cols, most, dense=0):
+    """Rows of 0 to `most` entries; with `dense`, a few rows of so many that no entry of the left operand meets (columns from 64 on)."""
+    lengths = rng.integers(0, most + 1, rows)
+    if dense:
+        lengths[:3] = dense
+    col = np.concatenate([np.sort(rng.choice(cols - 64, k, replace=False)) + 64 if k < 64 else np.sort(rng.choice(cols, k, replace=False)) for k in lengths])
+    return inputs.from_coo(rows, cols, np.repeat(np.arange(rows), lengths), col, rng.uniform(-1, 1, col.size), "short rows")
+
+
+# one chunk of rows (2048) and more, ends of tile-rows, of a wave's four, of a block's, of a group of 64 blocks (2048 rows of 8 lanes, 1024
+# of 16), rows whose blocks are too many for it (262,144 by 16 lanes), bitmaps of 16 KB (524,288 columns) and beyond
+@pytest.mark.parametrize("rows,inner,cols,a_most,b_most,dense", [
+    (257, 300, 200, 4, 4, 0), (2047, 1999, 3001, 3, 5, 0), (2048, 2048, 2048, 6, 9, 0), (2049, 70, 5000, 3, 3, 0), (2065, 5000, 70, 5, 2, 0),
+    (4099, 4099, 4099, 8, 12, 0), (16384, 700, 900, 2, 2, 600), (20001, 20001, 20001, 5, 7, 0), (65537, 3000, 4000, 3, 3, 2000), (3000, 90001, 90001, 3, 4, 0),
+    (30000, 524288, 2000, 2, 3, 0), (30000, 524289, 2000, 2, 3, 0), (2100, 1500, 524288, 4, 3, 0), (2100, 1500, 524289, 4, 3, 0), (262200, 400, 500, 1, 2, 0), (262200, 400, 500, 9, 9, 0)])
+@pytest.mark.parametrize("types", [{}, {"value_dtype": "f32", "row_ptr_dtype": "i64"}])
+def test_small_rows_straight_from_the_operands(tsp, oracle, rows, inner, cols, a_most, b_most, dense, types):
+    """The second and later products of sizes whose first one had small rows only: the same bits as the first where sums are exact,
+    and the same numbers of tiles and of their pairs."""
+    rng = np.random.default_rng(rows + cols)
+    A, B = _short(rng, rows, inner, a_most), _short(rng, inner, cols, b_most, dense)
+    if dense:                                                  # (the dense rows of B are met by nobody)
+        assert A.col_idx.min() >= 64
+    dA, dB = tsp.to_device(A, **types), tsp.to_device(B, **types)
+    ref = oracle.spgemm(A, B, threads=4)
+    h = tsp.Handle()
+    try:
+        stats = []
+        for _ in range(3):
+            C = h.spgemm(dA, dB)
+            row_ptr, col, val = C.to_host()
+            C.free()
+            assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+            assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+            stats.append([h.stats()[k] for k in ("a_tiles", "b_tiles", "candidate_pairs", "c_nnz", "pairs")])
+        assert stats[0] == stats[1] == stats[2]
+    finally:
+        h.close()
+
+
+@pytest.mark.parametrize("rows", [1800, 30000])
+def test_what_is_not_for_it_straight_from_the_operands(tsp, oracle, rows):
+    """Operands of the sizes of a product of small rows that are not canonical, that have more entries in C than the last one and some,
+    or rows that are not small: refused, or multiplied all the same; then one of small rows again."""
+    rng = np.random.default_rng(rows)
+    lengths, cols = np.full(rows, 3), 5003
+    def make(lengths, width=cols):
+        col = np.concatenate([np.sort(rng.choice(width, k, replace=False)) for k in lengths])
+        return inputs.from_coo(rows, cols, np.repeat(np.arange(rows), lengths), col, rng.uniform(-1, 1, col.size), "left")
+    B = inputs.from_coo(cols, 4001, np.repeat(np.arange(cols), 4), np.sort(rng.integers(0, 1000, (cols, 4)) * 4 + np.arange(4), axis=1).ravel(),
+                        rng.uniform(-1, 1, 4 * cols), "right")
+    ordinary, narrow = make(lengths), make(lengths, 5)
+    long_row = lengths.copy()
+    long_row[7], long_row[20:40] = 23, 2
+    many_products = lengths.copy()
+    many_products[100], many_products[200:205] = 8, 2
+    dB = tsp.to_device(B)
+    h = tsp.Handle(validate=True)
+    try:
+        def good(A):
+            ref = oracle.spgemm(A, B, threads=4)
+            C = h.spgemm(tsp.to_device(A), dB)
+            row_ptr, col, val = C.to_host()
+            C.free()
+            assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+            assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+        for _ in range(2):
+            good(narrow)
+        good(ordinary)                                         # (more entries in C than there is room for)
+        for where, broken_col in ((0, -1), (500, cols), (3 * rows - 1, 1 << 30), (301, None), (302, "same")):
+            broken = make(lengths)
+            broken.col_idx[where] = broken.col_idx[where - 1] if broken_col == "same" else broken.col_idx[where + 1] if broken_col is None else broken_col
+            with pytest.raises(tsp.TspError):
+                h.spgemm(tsp.to_device(broken), dB)
+        for at, value in ((0, 1), (5, 1 << 30), (6, -3), (rows, 3 * rows - 1), (16, 0), (64, 190), (rows - 1, 0)):
+            broken = make(lengths)
+            broken.row_ptr[at] = value
+            with pytest.raises(tsp.TspError):
+                h.spgemm(tsp.to_device(broken), dB)
+        good(ordinary)
+        assert make(long_row).nnz == make(many_products).nnz == ordinary.nnz
+        good(make(many_products))
+        good(ordinary)
+        good(make(long_row))
+        for _ in range(2):
+            good(ordinary)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("a_row,b_row", [(4, 3), (40, 30), (4, 30), (40, 3)])
 @pytest.mark.parametrize("b_types", [{}, {"value_dtype": "f32"}, {"row_ptr_dtype": "i64"}])
 def test_both_operands_prepared_at_once(tsp, oracle, a_row, b_row, b_types):
