@@ -17,6 +17,8 @@ constexpr int T = 16;               // tile edge: one output tile = one 16x16 MF
 constexpr int kScalars = 32;        // device/host scalar slots of a handle
 // counters of groups of blocks (k_row_given), each in a line of its own
 constexpr int kArriveCounters = 1024, kArriveStride = 16;
+// slots of tile-rows and of groups of 64 of them (k_sym_emit_block)
+constexpr int kListSlots = 32768, kListSlotWords = kListSlots + kListSlots / 64;
 
 // Slots of the handle's device scalar block (int64 each).
 enum Scalar {
@@ -188,6 +190,8 @@ struct tsp_context {
     int64_t chain_capacity = 0;                    // slots allocated
     unsigned chain_epoch = 0;                      // tag of the last chained scan
     int64_t *d_scalars = nullptr;                  // device, kScalars entries
+    unsigned long long *d_list_slots = nullptr;    // device, kListSlotWords, by the number of the call that wrote them (behind those)
+    uint32_t list_call = 0;
     unsigned long long *d_arrivals = nullptr;      // device, kArriveCounters counters, zero between launches (behind the scalars)
     bool scalars_clean = false;                    // all zero: the last kernel of the previous call left them so
     int64_t *h_scalars = nullptr;                  // pinned host mirror

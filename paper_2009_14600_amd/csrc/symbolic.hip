@@ -1001,6 +1001,8 @@ __device__ __forceinline__ uint32_t boolean_row_product(uint32_t am, const uint4
 constexpr int kPairsPerTrip = 2;       // pairs a lane group of the fused counting pass takes per trip
 constexpr int kListCap = 1024;
 constexpr int kListTeamLanes = 32;     // lanes that share a tile-row where tile-rows have few candidates (16: slower)
+constexpr int64_t kSizingWords = 768;
+constexpr size_t kLdsLimit = 64 * 1024;      // of one launch
 constexpr int64_t kResidentTileRows = 4096;   // blocks of 128 threads that are on the chip at once
 constexpr int kListTiles = 512;        // and at most this many C tiles per tile-row (their bitmaps sit in LDS)
 // kFuseMasks: also run the counting pass (worth it when there are enough tile-rows to fill the chip;
@@ -1243,48 +1245,128 @@ __global__ __launch_bounds__(kTeamLanes ? 64 : kSymThreads) void k_sym_emit_list
 // 27-point stencil with 3 unknowns on 48^3 nodes (27 tiles of A and 567 pairs per tile-row) 244 us; 318 us with sixteen
 // lanes per pair, which select rows of B through a table in LDS and fetch every bitmap sixteen times.
 // Dynamic LDS: 2*words_cap + 11*window words.
+// kSizes: no kernel has counted the tile-rows before.  The block marks the tile columns anyway; it tells the other blocks its numbers
+// of C tiles and pairs at once, forms the products, and has the sums before it when it writes: of the tile-rows of its 64 from them,
+// of those before from the last block of each 64, which adds them up.  What it waits for is a block before it, which runs or is done
+// (blocks are dispatched in order); the wait is bounded like that of a chained scan.  k_row_ptr adds up what the host wants to know.
+// On the stencil 262 us (k_sym_count, k_sym_row_scan and the kernel without it: 50 + 9 + 235, and two launches); six waves per SIMD
+// rather than the five its registers would allow: 273.
 constexpr int kBlockATiles = 64, kBlockListThreads = 128;
-__global__ __launch_bounds__(kBlockListThreads) void k_sym_emit_block(
+constexpr int kListGroup = 64;
+static_assert(kListGroup * kListTiles < 1 << 17 && kListGroup * kListCap < 1 << 17, "sums over a group, beside 30 bits of the call's number");
+struct ListSizing {
+    int words;                           // of a bitmap over B's tile columns
+    unsigned long long *slots;           // of the tile-rows, and behind kListSlots of them of the groups: {call, pairs, C tiles}
+    uint32_t call;
+    uint4 *info;                         // of every tile-row {C tiles, pairs, candidates, tiles of A}
+    int32_t *c_tile_row_ptr;
+};
+__device__ __forceinline__ void put_slot(unsigned long long *slot, uint32_t call, uint32_t pairs, uint32_t tiles) {
+    __hip_atomic_store(slot, (unsigned long long)call << 34 | (unsigned long long)pairs << 17 | tiles, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long wait_slot(const unsigned long long *slot, uint32_t call, int64_t *error) {
+    for (unsigned spins = 0;; ++spins) {
+        const unsigned long long v = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)(v >> 34) == call) return v;
+        if (spins > kChainSpinLimit) {
+            *error = 1;
+            return 0;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+// Sums over the tile-rows before I: of its group's (kMembers), of the groups before (kGroups; a load past the XCD's L2 takes about
+// 1 us: all at once), by a wave, in every lane
+struct ListBefore {
+    uint32_t tiles, pairs;
+};
+template <bool kMembers, bool kGroups>
+__device__ __forceinline__ ListBefore sums_before(const ListSizing &sizing, int I, int lane, int64_t *error) {
+    constexpr int kLoads = kListSlots / kListGroup / 64;
+    const int member = I % kListGroup, group = I / kListGroup;
+    const unsigned long long *const members = sizing.slots + (I - member), *const groups = sizing.slots + kListSlots;
+    unsigned long long own = 0, v[kLoads];
+    uint32_t tiles = 0, pairs = 0;
+    if (kMembers && lane < member) own = __hip_atomic_load(members + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+        v[u] = kGroups && lane + 64 * u < group ? __hip_atomic_load(groups + lane + 64 * u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+    auto add = [&](unsigned long long x, const unsigned long long *slot) {
+        if ((uint32_t)(x >> 34) != sizing.call) x = wait_slot(slot, sizing.call, error);
+        tiles += (uint32_t)x & 0x1FFFFu;
+        pairs += (uint32_t)(x >> 17) & 0x1FFFFu;
+    };
+    if (kMembers && lane < member) add(own, members + lane);
+    if (kGroups) {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u)
+            if (lane + 64 * u < group) add(v[u], groups + lane + 64 * u);
+    }
+    static_assert(kListSlots * kListCap < INT32_MAX, "the sums are of 32 bits");
+    return {wave_sum(tiles), wave_sum(pairs)};   // (of all tile-rows at most kListSlots * kListCap)
+}
+__global__ __launch_bounds__(256) void k_clear_list_slots(unsigned long long *slots) {
+    const int i = (int)blockIdx.x * 256 + threadIdx.x;
+    if (i < kListSlotWords) slots[i] = 0;
+}
+template <bool kSizes>
+__global__ __launch_bounds__(kBlockListThreads, 6) void k_sym_emit_block(
     TileRefs A, TileRefs B, int words_cap, int window, const int32_t *__restrict__ row_jmin,
     const int32_t *__restrict__ row_words, const int32_t *__restrict__ c_tile_row_ptr, const int64_t *__restrict__ row_pair_ptr,
     int32_t *__restrict__ c_tile_row, int32_t *__restrict__ c_tile_col, int64_t *__restrict__ pair_off,
     int2 *__restrict__ pair_ab, const uint16_t *__restrict__ a_row_mask, const uint16_t *__restrict__ b_row_mask,
     uint16_t *__restrict__ c_row_mask, uint32_t *__restrict__ c_row_off, int32_t *__restrict__ row_nnz, int64_t c_rows,
-    int64_t *d_scalars, uint32_t *__restrict__ tile_row_entries, int64_t c_tiles_most, int64_t pairs_most) {
+    int64_t *d_scalars, uint32_t *__restrict__ tile_row_entries, int64_t c_tiles_most, int64_t pairs_most, const ListSizing sizing) {
     constexpr int kThreads = kBlockListThreads, kLanes = 4;
     extern __shared__ __align__(16) uint32_t lds_dyn[];
     __shared__ uint32_t s_part[kThreads / 16][T];
+    __shared__ uint32_t s_sum[2][kThreads / 64];
     unsigned long long *const cmask = reinterpret_cast<unsigned long long *>(lds_dyn);   // four row masks each, four per C tile
     unsigned long long *const contrib = cmask + window * 4;                              // tiles of A that contribute
     uint32_t *const cnt = reinterpret_cast<uint32_t *>(contrib + window);                // pairs of the C tiles before
     uint32_t *const bm = cnt + window, *const wpre = bm + words_cap;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & (kLanes - 1);
     const int I = (int)blockIdx.x;
-    const int c0 = uniform_load(c_tile_row_ptr + I), nC = uniform_load(c_tile_row_ptr + I + 1) - c0;
-    const int64_t row_base = uniform_load(row_pair_ptr + I), row_end = uniform_load(row_pair_ptr + I + 1);
-    if (I == A.tile_rows - 1 && tid == 0 && c_tile_row_ptr[A.tile_rows] <= c_tiles_most)
-        pair_off[c_tile_row_ptr[A.tile_rows]] = row_pair_ptr[A.tile_rows];
+    int c0 = 0, nC = 0;
+    int64_t row_base = 0;
     const int a0 = uniform_load(A.trp + I), nA = uniform_load(A.tend + I) - a0;
-    const int jmin = uniform_load(row_jmin + I), words = uniform_load(row_words + I);
+    const int jmin = kSizes ? 0 : uniform_load(row_jmin + I), words = kSizes ? sizing.words : uniform_load(row_words + I);
+    bool fits = words <= words_cap && nA <= kBlockATiles;
+    if constexpr (!kSizes) {
+        c0 = uniform_load(c_tile_row_ptr + I);
+        nC = uniform_load(c_tile_row_ptr + I + 1) - c0;
+        row_base = uniform_load(row_pair_ptr + I);
+        if (I == A.tile_rows - 1 && tid == 0 && c_tile_row_ptr[A.tile_rows] <= c_tiles_most)
+            pair_off[c_tile_row_ptr[A.tile_rows]] = row_pair_ptr[A.tile_rows];
+        fits = fits && nC > 0 && nC <= window && c0 + nC <= c_tiles_most && uniform_load(row_pair_ptr + I + 1) <= pairs_most;
+    }
     // an empty tile-row of C: its 16 rows are empty; so is one that does not fit the arrays (the kernel then runs again)
-    if (nC <= 0 || nC > window || c0 + nC > c_tiles_most || words > words_cap || row_end > pairs_most || nA > kBlockATiles) {
+    auto leave_empty = [&]() {
         if (tid < T && (int64_t)I * T + tid < c_rows) row_nnz[(int64_t)I * T + tid] = 0;
         if (tid == 0) tile_row_entries[I] = 0;
+    };
+    if (!kSizes && !fits) {
+        leave_empty();
         return;
     }
     const uint32_t span = (uint32_t)words * 32u;
     for (int w = tid; w < words; w += kThreads) bm[w] = 0;
-    for (int w = tid; w < nC * 4; w += kThreads) cmask[w] = 0;
-    for (int c = tid; c < nC; c += kThreads) contrib[c] = 0;
+    auto clear_tiles = [&]() {
+        for (int w = tid; w < nC * 4; w += kThreads) cmask[w] = 0;
+        for (int c = tid; c < nC; c += kThreads) contrib[c] = 0;
+    };
+    if constexpr (!kSizes) clear_tiles();
     __syncthreads();
     // f(A tile, B tile, column from jmin) for every surviving pair, four lanes per tile of A side by side over the tiles of
     // B, four each per trip
+    uint32_t candidates = 0;
     auto for_each_pair = [&](auto f) {
         for (int a = a0 + tid / kLanes; a < a0 + nA; a += kThreads / kLanes) {
             const uint32_t K = (uint32_t)element(A.tcol, (uint32_t)a);
             if (K >= (uint32_t)B.tile_rows) continue;            // only possible for a non-canonical input
             const uint32_t col_occ = fold16(element(A.rmask, (uint32_t)a));
             const int b0 = element(B.trp, K), b1 = element(B.tend, K);
+            if (kSizes && l == 0) candidates += (uint32_t)(b1 - b0);
             for (int b = b0 + l; b < b1; b += 4 * kLanes) {
                 uint32_t occ[4], at[4];
                 int col[4];
@@ -1302,31 +1384,85 @@ __global__ __launch_bounds__(kBlockListThreads) void k_sym_emit_block(
             }
         }
     };
-    for_each_pair([&](int, int, uint32_t j) { atomicOr(&bm[j >> 5], 1u << (j & 31)); });
+    uint32_t pairs = 0;
+    if (fits)
+        for_each_pair([&](int, int, uint32_t j) {
+            atomicOr(&bm[j >> 5], 1u << (j & 31));
+            if constexpr (kSizes) ++pairs;
+        });
+    if constexpr (kSizes) {
+        pairs = wave_sum(pairs);
+        candidates = wave_sum(candidates);
+        if (lane == 0) {
+            s_sum[0][wave] = pairs;
+            s_sum[1][wave] = candidates;
+        }
+    }
     __syncthreads();
-    {   // C tiles before every word, each wave for itself; their coordinates, ascending J
-        const int stretch = (words + 63) >> 6;
+    // C tiles before every word, each wave for itself
+    const int stretch_words = (words + 63) >> 6;
+    {
         uint32_t mine = 0;
-        for (int i = 0; i < stretch; ++i) mine += lane * stretch + i < words ? (uint32_t)__popc(bm[lane * stretch + i]) : 0u;
-        uint32_t before = wave_inclusive_scan(mine) - mine;
-        for (int i = 0; i < stretch; ++i) {
-            const int w = lane * stretch + i;
+        for (int i = 0; i < stretch_words; i += 4) {         // (four reads in flight)
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = bm[min(lane * stretch_words + i + u, words - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) mine += i + u < stretch_words && lane * stretch_words + i + u < words ? (uint32_t)__popc(v[u]) : 0u;
+        }
+        const uint32_t inc = wave_inclusive_scan(mine);
+        uint32_t before = inc - mine;
+        if constexpr (kSizes) nC = __builtin_amdgcn_readlane((int)inc, 63);
+        for (int i = 0; i < stretch_words; i += 4) {
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = bm[min(lane * stretch_words + i + u, words - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int w = lane * stretch_words + i + u;
+                if (i + u >= stretch_words || w >= words) break;
+                wpre[w] = before;
+                before += (uint32_t)__popc(v[u]);
+            }
+        }
+        wave_sync();
+    }
+    // ... and their coordinates, ascending J
+    auto list_tiles = [&]() {
+        for (int i = 0; i < stretch_words; ++i) {
+            const int w = lane * stretch_words + i;
             if (w >= words) break;
-            const uint32_t bits = bm[w];
-            wpre[w] = before;
             if ((lane & (kThreads / 64 - 1)) == wave) {
-                int c = c0 + (int)before;
-                for (uint32_t left = bits; left; left &= left - 1, ++c) {
+                int c = c0 + (int)wpre[w];
+                for (uint32_t left = bm[w]; left; left &= left - 1, ++c) {
                     c_tile_row[c] = I;
                     c_tile_col[c] = jmin + w * 32 + __ffs(left) - 1;
                 }
             }
-            before += (uint32_t)__popc(bits);
         }
-        wave_sync();
+    };
+    if constexpr (kSizes) {
+        pairs = s_sum[0][0] + s_sum[0][1];
+        static_assert(kThreads == 128, "two waves");
+        fits = fits && nC <= window && pairs <= (uint32_t)kListCap;
+        if (wave == 0) {
+            const uint32_t own_tiles = fits ? (uint32_t)nC : 0u, own_pairs = fits ? pairs : 0u;
+            if (lane == 0) {
+                put_slot(sizing.slots + I, sizing.call, own_pairs, own_tiles);
+                sizing.info[I] = make_uint4((uint32_t)nC, pairs, s_sum[1][0] + s_sum[1][1], (uint32_t)nA);
+            }
+            if (I % kListGroup == kListGroup - 1) {              // the group's sum
+                const ListBefore members = sums_before<true, false>(sizing, I, lane, d_scalars + S_INTERNAL);
+                if (lane == 0) put_slot(sizing.slots + kListSlots + I / kListGroup, sizing.call, own_pairs + members.pairs, own_tiles + members.tiles);
+            }
+        }
+        if (fits) clear_tiles();
+        __syncthreads();
+    } else {
+        list_tiles();
     }
     auto rank = [&](uint32_t j) -> int { return (int)(wpre[j >> 5] + (uint32_t)__popc(bm[j >> 5] & ((1u << (j & 31)) - 1u))); };
-    for (int a = a0 + tid / kLanes; a < a0 + nA; a += kThreads / kLanes) {
+    for (int a = a0 + tid / kLanes; a < (fits ? a0 + nA : a0); a += kThreads / kLanes) {
         const uint32_t K = (uint32_t)A.tcol[a];
         const bool in = K < (uint32_t)B.tile_rows;                // (otherwise a non-canonical input)
         const int b0 = in ? B.trp[K] : 0, b1 = in ? B.tend[K] : 0;
@@ -1393,7 +1529,31 @@ __global__ __launch_bounds__(kBlockListThreads) void k_sym_emit_block(
             }
         }
     }
-    __syncthreads();
+    if constexpr (kSizes) {
+        // C tiles and pairs before the tile-row: the first wave adds up its group's, the second the groups before
+        const ListBefore sums = wave == 0 ? sums_before<true, false>(sizing, I, lane, d_scalars + S_INTERNAL)
+                                          : sums_before<false, true>(sizing, I, lane, d_scalars + S_INTERNAL);
+        if (lane == 0) {
+            s_sum[0][wave] = sums.tiles;
+            s_sum[1][wave] = sums.pairs;
+        }
+        __syncthreads();
+        c0 = (int)(s_sum[0][0] + s_sum[0][1]);
+        row_base = (int64_t)s_sum[1][0] + s_sum[1][1];
+        const bool last = I == A.tile_rows - 1;
+        if (tid == 0) {
+            sizing.c_tile_row_ptr[I] = c0;
+            if (last) sizing.c_tile_row_ptr[I + 1] = c0 + (fits ? nC : 0);
+        }
+        if (tid == 0 && last && fits && c0 + nC <= c_tiles_most) pair_off[c0 + nC] = row_base + pairs;
+        if (!fits || nC == 0 || c0 + nC > c_tiles_most || row_base + pairs > pairs_most) {
+            leave_empty();
+            return;
+        }
+        list_tiles();
+    } else {
+        __syncthreads();
+    }
     {   // pairs of the C tiles before, each wave for itself
         const int stretch = (nC + 63) >> 6;
         uint32_t mine = 0;
@@ -1451,6 +1611,209 @@ __global__ __launch_bounds__(kBlockListThreads) void k_sym_emit_block(
     for (int c = cb; c < ce; ++c) {
         c_row_off[(int64_t)(c0 + c) * T + r] = run;
         run += __popc((masks[c * 8 + word] >> shift) & 0xFFFFu);
+    }
+}
+
+// The same for tile-rows of few pairs (at most list_cap of them, 64 tiles of A): a wave takes one.  What bounds it is the chain of
+// loads from the tile-row's bounds to the bitmaps, five of them one after the other, so all tile-rows are to be on the chip at once.
+// The candidates lie side by side over the lanes, whatever the tile-rows of B hold of them; the pairs are kept in LDS.
+// (20 us for 8192 tile-rows of 16 pairs; the count, its prefix sums and k_sym_emit_listed with two tile-rows per wave take
+// 13.6 + 8.2 + 19.5, a block per tile-row that finds the sizes too 56.)
+constexpr int kFewWaves = 4;
+constexpr int64_t kFewPairs = 256, kFewPairsFewRows = 64, kFewRows = 1024;
+// A wave per tile-row, or a block of two with the bitmaps of four rows to a lane (k_sym_emit_block): up to about 200 pairs the wave
+// (us, wave and block; 8192 tile-rows of 36 pairs 27 and 58, 6000 of 180 27 and 51, 2250 of 100 15 and 23, 1500 of 36 13 and 17), unless
+// there are too few tile-rows to fill the chip with one wave each (750 of 180 pairs: 17 and 16; 375 of 150: 13 and 12); with more pairs
+// the block (1700 tile-rows of 330 pairs: 47 and 30).
+static bool few_pairs(int64_t most_pairs, int64_t tile_rows) { return most_pairs <= (tile_rows > kFewRows ? kFewPairs : kFewPairsFewRows); }
+// words of LDS of a wave (a multiple of four)
+static int64_t few_words(int64_t words, int64_t window, int64_t list_cap) { return (2 * words + 11 * window + 2 * list_cap + 3) / 4 * 4; }
+__global__ __launch_bounds__(64 * kFewWaves, 8) void k_sym_emit_few(
+    TileRefs A, TileRefs B, int window, int list_cap, int wave_words, int32_t *__restrict__ c_tile_row, int32_t *__restrict__ c_tile_col,
+    int64_t *__restrict__ pair_off, int2 *__restrict__ pair_ab, const uint16_t *__restrict__ a_row_mask, const uint16_t *__restrict__ b_row_mask,
+    uint16_t *__restrict__ c_row_mask, uint32_t *__restrict__ c_row_off, int32_t *__restrict__ row_nnz, int64_t c_rows, int64_t *d_scalars,
+    uint32_t *__restrict__ tile_row_entries, int64_t c_tiles_most, int64_t pairs_most, const ListSizing sizing) {
+    extern __shared__ __align__(16) uint32_t lds_dyn[];
+    __shared__ RowSelectTable row_select;
+    __shared__ int s_end[kFewWaves][64];                         // candidates up to the tile of A
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int I = (int)blockIdx.x * kFewWaves + wave, words = sizing.words;
+    uint32_t *const own = lds_dyn + wave * wave_words;
+    unsigned long long *const contrib = reinterpret_cast<unsigned long long *>(own);      // tiles of A that contribute, per C tile
+    uint2 *const list = reinterpret_cast<uint2 *>(own + 2 * window);                      // {tile of B, tile column or C tile << 6 | tile of A}
+    uint32_t *const cmask = own + 2 * window + 2 * list_cap, *const cnt = cmask + 8 * window;
+    uint32_t *const bm = cnt + window, *const wpre = bm + words;
+    row_select.fill();
+    __syncthreads();
+    if (I >= A.tile_rows) return;
+    const int a0 = uniform_load(A.trp + I), nA = uniform_load(A.tend + I) - a0;
+    // a lane per tile of A
+    int b0 = 0, count = 0;
+    uint32_t occ = 0;
+    if (nA <= 64 && lane < nA) {
+        const uint32_t K = (uint32_t)element(A.tcol, (uint32_t)(a0 + lane));
+        occ = fold16(element(A.rmask, (uint32_t)(a0 + lane)));
+        if (K < (uint32_t)B.tile_rows) {                         // (otherwise a non-canonical input)
+            b0 = element(B.trp, K);
+            count = element(B.tend, K) - b0;
+        }
+    }
+    for (int w = lane; w < words; w += 64) bm[w] = 0;
+    for (int c = lane; c < window; c += 64) contrib[c] = 0;
+    for (int w = lane; w < 8 * window; w += 64) cmask[w] = 0;
+    const int end = (int)wave_inclusive_scan((uint32_t)count);
+    const int candidates = __builtin_amdgcn_readlane(end, 63);
+    s_end[wave][lane] = end;
+    const int first = b0 - (end - count);
+    wave_sync();
+    int n = 0;
+    for (int from = 0; from < candidates; from += 64) {
+        const int k = min(from + lane, candidates - 1);
+        int i = 0;
+#pragma unroll
+        for (int step = 32; step >= 1; step >>= 1) i += s_end[wave][i + step - 1] <= k ? step : 0;
+        const int b = __shfl(first, i) + k;
+        const uint32_t occ_a = (uint32_t)__shfl((int)occ, i);
+        const uint32_t occ_b = element(B.lmask, (uint32_t)b), j = (uint32_t)element(B.tcol, (uint32_t)b);
+        const bool is = from + lane < candidates && (occ_a & fold16(occ_b)) && j < (uint32_t)words * 32u;
+        const unsigned long long all = __ballot(is);
+        const int at = n + __popcll(all & ((1ull << lane) - 1ull));
+        if (is) {
+            atomicOr(&bm[j >> 5], 1u << (j & 31));
+            if (at < list_cap) list[at] = make_uint2((uint32_t)b, j << 6 | (uint32_t)i);
+        }
+        n += __popcll(all);
+    }
+    wave_sync();
+    const int stretch_words = (words + 63) >> 6;
+    int nC = 0;
+    {
+        uint32_t mine = 0;
+        for (int i = 0; i < stretch_words; i += 4) {             // (four reads in flight)
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = bm[min(lane * stretch_words + i + u, words - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) mine += i + u < stretch_words && lane * stretch_words + i + u < words ? (uint32_t)__popc(v[u]) : 0u;
+        }
+        const uint32_t inc = wave_inclusive_scan(mine);
+        uint32_t before = inc - mine;
+        nC = __builtin_amdgcn_readlane((int)inc, 63);
+        for (int i = 0; i < stretch_words; ++i) {
+            const int w = lane * stretch_words + i;
+            if (w >= words) break;
+            wpre[w] = before;
+            before += (uint32_t)__popc(bm[w]);
+        }
+    }
+    const bool fits = nA <= 64 && n <= list_cap && nC <= window;
+    const uint32_t own_tiles = fits ? (uint32_t)nC : 0u, own_pairs = fits ? (uint32_t)n : 0u;
+    if (lane == 0) {
+        put_slot(sizing.slots + I, sizing.call, own_pairs, own_tiles);
+        sizing.info[I] = make_uint4((uint32_t)nC, (uint32_t)n, (uint32_t)candidates, (uint32_t)nA);
+    }
+    if (I % kListGroup == kListGroup - 1) {                      // the group's sum
+        const ListBefore members = sums_before<true, false>(sizing, I, lane, d_scalars + S_INTERNAL);
+        if (lane == 0) put_slot(sizing.slots + kListSlots + I / kListGroup, sizing.call, own_pairs + members.pairs, own_tiles + members.tiles);
+    }
+    wave_sync();
+    const int r = lane & 15, g = lane >> 4, word = r >> 1, shift = (r & 1) * 16;
+    if (fits) {
+        for (int k = lane; k < n; k += 64) {
+            const uint32_t y = list[k].y, j = y >> 6;
+            const uint32_t c = wpre[j >> 5] + (uint32_t)__popc(bm[j >> 5] & ((1u << (j & 31)) - 1u));
+            list[k].y = c << 6 | (y & 63u);
+            atomicOr(&contrib[c], 1ull << (y & 63u));
+        }
+        wave_sync();
+        // counting pass: 16 lanes per pair, lane r forms row r of the boolean product; two pairs per trip, requested together
+        for (int k0 = g * 2; k0 < n; k0 += 8) {
+            uint32_t am[2], c_of[2];
+            uint4 x[2], y[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint2 pair = list[min(k0 + u, n - 1)];
+                am[u] = k0 + u < n ? element(a_row_mask, (uint32_t)(a0 + (int)(pair.y & 63u)) * T + r) : 0u;
+                x[u] = element(reinterpret_cast<const uint4 *>(b_row_mask), 2 * pair.x);
+                y[u] = element(reinterpret_cast<const uint4 *>(b_row_mask), 2 * pair.x + 1);
+                c_of[u] = pair.y >> 6;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t m = boolean_row_product(am[u], x[u], y[u], row_select);
+                const uint32_t m16 = (m | (m >> 16)) & 0xFFFFu;
+                if (m16) atomicOr(&cmask[c_of[u] * 8 + word], m16 << shift);
+            }
+        }
+    }
+    const ListBefore before_all = sums_before<true, true>(sizing, I, lane, d_scalars + S_INTERNAL);
+    const int c0 = (int)before_all.tiles;
+    const int64_t row_base = before_all.pairs;
+    const bool last = I == A.tile_rows - 1;
+    if (lane == 0) {
+        sizing.c_tile_row_ptr[I] = c0;
+        if (last) sizing.c_tile_row_ptr[I + 1] = c0 + (int)own_tiles;
+        if (last && c0 + (int)own_tiles <= c_tiles_most) pair_off[c0 + own_tiles] = row_base + own_pairs;
+    }
+    const int64_t row = (int64_t)I * T + r;
+    if (!fits || nC == 0 || c0 + nC > c_tiles_most || row_base + n > pairs_most) {
+        if (g == 0 && row < c_rows) row_nnz[row] = 0;
+        if (lane == 0) tile_row_entries[I] = 0;
+        return;
+    }
+    wave_sync();
+    // C tiles, ascending J, and the pairs before each
+    for (int w = lane; w < words; w += 64) {
+        int c = c0 + (int)wpre[w];
+        for (uint32_t left = bm[w]; left; left &= left - 1, ++c) {
+            c_tile_row[c] = I;
+            c_tile_col[c] = w * 32 + __ffs(left) - 1;
+        }
+    }
+    uint32_t carry = 0;
+    for (int from = 0; from < nC; from += 64) {
+        const int c = from + lane;
+        const uint32_t own_count = c < nC ? (uint32_t)__popcll(contrib[c]) : 0u;
+        const uint32_t inc = wave_inclusive_scan(own_count);
+        if (c < nC) {
+            cnt[c] = carry + inc - own_count;
+            pair_off[c0 + c] = row_base + (int64_t)(carry + inc - own_count);
+        }
+        carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    }
+    wave_sync();
+    for (int k = lane; k < n; k += 64) {
+        const uint2 pair = list[k];
+        const uint32_t c = pair.y >> 6, a = pair.y & 63u;
+        const int64_t pos = row_base + (int64_t)(cnt[c] + (uint32_t)__popcll(contrib[c] & ((1ull << a) - 1ull)));
+        pair_ab[pos] = make_int2(a0 + (int)a, (int)pair.x);      // (n different places from row_base on: every pair has its bit)
+    }
+    uint32_t *const out = reinterpret_cast<uint32_t *>(c_row_mask) + (int64_t)c0 * 8;
+    for (int w = lane; w < nC * 8; w += 64) out[w] = cmask[w];
+    // lengths of the rows and places of the tiles' entries in them: lane r of every 16 takes row r for a quarter of the C tiles
+    const int stretch = (nC + 3) >> 2, cb = min(nC, g * stretch), ce = min(nC, cb + stretch);
+    uint32_t part = 0;
+    for (int c = cb; c < ce; ++c) part += __popc((cmask[c * 8 + word] >> shift) & 0xFFFFu);
+    uint32_t total = 0, earlier = 0;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const uint32_t v = (uint32_t)__shfl((int)part, h * 16 + r);
+        total += v;
+        earlier += h < g ? v : 0u;
+    }
+    int up_to = (int)total;                                      // inclusive prefix over the 16 rows
+    up_to += TSP_DPP(0, up_to, 0x111, 0xf, true);
+    up_to += TSP_DPP(0, up_to, 0x112, 0xf, true);
+    up_to += TSP_DPP(0, up_to, 0x114, 0xf, true);
+    up_to += TSP_DPP(0, up_to, 0x118, 0xf, true);
+    if (g == 0) {
+        if (row < c_rows) row_nnz[row] = (int32_t)total;
+        if (r == T - 1) tile_row_entries[I] = (uint32_t)up_to;
+    }
+    uint32_t run = (uint32_t)up_to - total + earlier;
+    for (int c = cb; c < ce; ++c) {
+        c_row_off[(int64_t)(c0 + c) * T + r] = run;
+        run += __popc((cmask[c * 8 + word] >> shift) & 0xFFFFu);
     }
 }
 
@@ -1524,15 +1887,27 @@ __global__ __launch_bounds__(256) void k_count_masks(int64_t c_tiles, const int6
 // row_ptr of C from the row lengths: block b takes rows [2048 b, 2048 b + 2048), starts from the
 // entries of the tile-rows before them and scans its own rows.  The last block has read every
 // tile-row and also leaves nnz(C) and the largest tile-row.
+// kSizes: behind k_sym_emit_block of the same kind.  Every block adds up what that has left of its own tile-rows (and its share of B's),
+// and the last one to do so hands all sizes over (8192 tile-rows: 9.5 us instead of 5.8, and 8.2 for k_sym_row_scan that there is not).
+enum { kListTilesC, kListPairs, kListCandidates, kListEntries, kListTilesA, kListTilesB, kListSums, kListMostTiles = kListSums, kListMostPairs, kListMostATiles,
+       kListMostEntries, kListParts };
+struct ListSums {
+    const uint4 *info;
+    const int32_t *a_trp, *a_tend, *b_trp, *b_tend;          // null: the host knows the tiles of that operand
+    int64_t b_tile_rows;
+    int a_slot, b_slot;
+    uint32_t *partial;                   // [blocks][16]
+};
+template <bool kSizes>
 __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row_nnz, int64_t c_rows,
                                                  const uint32_t *__restrict__ tile_row_entries, int64_t c_tile_rows,
                                                  int64_t *__restrict__ c_row_ptr, int64_t *d_scalars,
-                                                 int64_t *h_scalars_dev, int64_t publish_tag, bool clear, const ListExpected expected, int32_t *live) {
+                                                 int64_t *h_scalars_dev, int64_t publish_tag, bool clear, const ListExpected expected, int32_t *live, const ListSums sums) {
     __shared__ uint64_t lds[256 / 64];
     __shared__ int64_t own[kScalars];
     constexpr int kItems = kChunkRows / 256;
     const bool last = blockIdx.x == gridDim.x - 1;
-    const int64_t standing = last ? standing_scalar(d_scalars) : 0;
+    int64_t standing = !kSizes && last ? standing_scalar(d_scalars) : 0;
     const int64_t tile_rows_before = (int64_t)blockIdx.x * kChunkTileRows;
     // the block's own row lengths, requested first: they travel while the tile-rows before are added up
     const int64_t base = (int64_t)blockIdx.x * kChunkRows + (int64_t)threadIdx.x * kItems;
@@ -1543,7 +1918,25 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
     uint32_t largest = 0;
     // four tile-rows per load, four loads in flight (the array is padded to a multiple of four)
     const uint4 *entries4 = reinterpret_cast<const uint4 *>(tile_row_entries);
-    const int64_t quads = ((last ? c_tile_rows : tile_rows_before) + 3) / 4;
+    const int64_t quads = ((!kSizes && last ? c_tile_rows : tile_rows_before) + 3) / 4;
+    // (kSizes: a tile-row of this block's to a thread, of B's every one of this block's share)
+    uint32_t sum[kListParts] = {};                 // (of a block's tile-rows, and of the tiles of an operand: 32 bits hold them)
+    if constexpr (kSizes) {
+        static_assert(kChunkTileRows <= 256, "a thread each");
+        const int64_t I = tile_rows_before + threadIdx.x;
+        if (threadIdx.x < kChunkTileRows && I < c_tile_rows) {
+            const uint4 x = sums.info[I];
+            sum[kListTilesC] = sum[kListMostTiles] = x.x;
+            sum[kListPairs] = sum[kListMostPairs] = x.y;
+            sum[kListCandidates] = x.z;
+            sum[kListMostATiles] = x.w;
+            sum[kListEntries] = sum[kListMostEntries] = tile_row_entries[I];
+            if (sums.a_trp) sum[kListTilesA] = (uint32_t)(sums.a_tend[I] - sums.a_trp[I]);
+        }
+        if (sums.b_trp)
+            for (int64_t K = (int64_t)blockIdx.x * 256 + threadIdx.x; K < sums.b_tile_rows; K += (int64_t)gridDim.x * 256)
+                sum[kListTilesB] += (uint32_t)(sums.b_tend[K] - sums.b_trp[K]);
+    }
     for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 4 * 256) {
         uint4 e[4];
 #pragma unroll
@@ -1572,7 +1965,63 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
         if (base + i < c_rows) c_row_ptr[base + i] = (int64_t)run;
         run += (uint32_t)x[i];
     }
-    if (last) {
+    if constexpr (kSizes) {
+        __shared__ uint32_t s_part[4][kListParts];
+        __shared__ int s_last;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int i = 0; i < kListParts; ++i) {
+            const uint32_t v = i < kListSums ? wave_sum(sum[i]) : (uint32_t)wave_max((int)sum[i]);
+            if (lane == 0) s_part[wave][i] = v;
+        }
+        __syncthreads();
+        if (threadIdx.x < kListParts) {
+            const uint32_t a = s_part[0][threadIdx.x], b = s_part[1][threadIdx.x], c = s_part[2][threadIdx.x], d = s_part[3][threadIdx.x];
+            __hip_atomic_store(sums.partial + blockIdx.x * 16 + threadIdx.x, threadIdx.x < kListSums ? a + b + c + d : max(max(a, b), max(c, d)),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (the first wave's have arrived)
+        if (threadIdx.x == 0) s_last = atomicAdd(reinterpret_cast<unsigned long long *>(d_scalars + S_ROW_ARRIVED), 1ull) == gridDim.x - 1;
+        __syncthreads();
+        if (s_last) {
+            standing = standing_scalar(d_scalars);
+            // number i of all blocks: a lane of 16 per block, sixteen of them at a time, then the 16 that are left
+            unsigned long long v = 0;
+            const int i = threadIdx.x & 15;
+            if (i < kListParts)
+                for (int b = threadIdx.x >> 4; b < (int)gridDim.x; b += 8 * 16) {      // (eight loads in flight)
+                    uint32_t x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        x[u] = b + 16 * u < (int)gridDim.x ? __hip_atomic_load(sums.partial + (b + 16 * u) * 16 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v = i < kListSums ? v + x[u] : max(v, (unsigned long long)x[u]);
+                }
+            __shared__ unsigned long long s_all[16][kListParts];
+            if (i < kListParts) s_all[threadIdx.x >> 4][i] = v;
+            if (threadIdx.x < kScalars) own[threadIdx.x] = threadIdx.x == S_ROW_ARRIVED ? 0 : standing;
+            __syncthreads();
+            if (threadIdx.x < kListParts) {
+                const int at = threadIdx.x;
+                unsigned long long all = 0;
+                for (int h = 0; h < 16; ++h) all = at < kListSums ? all + s_all[h][at] : max(all, s_all[h][at]);
+                const int slot = at == kListTilesC ? S_C_TILES : at == kListPairs ? S_PAIRS : at == kListCandidates ? S_CANDIDATES
+                               : at == kListEntries ? S_C_NNZ : at == kListTilesA ? sums.a_slot : at == kListTilesB ? sums.b_slot
+                               : at == kListMostTiles ? S_MAX_ROW_C_TILES : at == kListMostPairs ? S_MAX_ROW_PAIRS
+                               : at == kListMostATiles ? S_MAX_ROW_A_TILES : S_MAX_ROW_ENTRIES;
+                if ((at != kListTilesA || sums.a_trp) && (at != kListTilesB || sums.b_trp)) own[slot] = (int64_t)all;
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                c_row_ptr[c_rows] = own[S_C_NNZ];
+                if (live) {
+                    live[0] = expected.holds(own);
+                    live[1] = (int32_t)own[S_C_TILES];
+                }
+            }
+            publish_scalars(d_scalars, h_scalars_dev, publish_tag, standing, own, 0xFFFFFFFFu, clear);
+        }
+    } else if (last) {
         largest = (uint32_t)wave_max((int)min(largest, 0x7FFFFFFFu));
         __syncthreads();
         if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = largest;
@@ -1753,6 +2202,8 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     int saved_words = 0;
     int64_t *row_pair_ptr = nullptr, *tmp = nullptr;
     int32_t *live = nullptr;
+    uint4 *tile_row_info = nullptr;
+    uint32_t *partial = nullptr;
     auto drop_order = [&](ListHint &h) {
         ctx_free(ctx, h.order, s);
         h.order = nullptr;
@@ -1769,6 +2220,8 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     auto cleanup = [&](int code) {
         drop_ahead();
         ctx_free(ctx, live, s);
+        ctx_free(ctx, tile_row_info, s);
+        ctx_free(ctx, partial, s);
         ctx_free(ctx, row_jmin, s);
         ctx_free(ctx, row_c_tiles, s);
         ctx_free(ctx, row_pairs, s);
@@ -1794,17 +2247,10 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         if (e_ != hipSuccess) return cleanup(hip_fail(ctx, e_));     \
     } while (0)
     phase_begin(ctx, TSP_PHASE_SYMBOLIC, s);
-    row_jmin = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
-    row_c_tiles = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
-    row_pairs = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
-    row_words = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
-    row_cand = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
-    row_pair_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)ntr + 1, s);
     P->c_tile_row_ptr = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
     const int64_t scan_n = ntr > P->c_rows ? ntr : P->c_rows;
     tmp = ctx_alloc_n<int64_t>(ctx, scan_tmp_entries(scan_n), s);
-    if (!row_jmin || !row_c_tiles || !row_pairs || !row_words || !row_cand || !row_pair_ptr || !P->c_tile_row_ptr || !tmp)
-        return cleanup(TSP_ERR_ALLOC_FAILED);
+    if (!P->c_tile_row_ptr || !tmp) return cleanup(TSP_ERR_ALLOC_FAILED);
 
     const int64_t n_chunks = (ntr + kChunkTileRows - 1) / kChunkTileRows;     // blocks of k_row_ptr
     TileRefs ra{A->tile_row_ptr, A->tile_row_end, A->tile_col, A->lmask, A->rmask, (int32_t)A->tile_rows};
@@ -1824,85 +2270,111 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
             long_rows = (double)B->ntiles > 8.0 * (double)B->tile_rows;
         }
     }
-    if (ntr > 0) {
-        KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
-        // the bitmap cannot be wider than B's tile grid; short tile-rows get one wave each, so that
-        // many more of them are in flight (the kernels are bound by dependent loads, not by work)
-        const int max_words = (int)std::min<int64_t>(kMaxWords, (B->tile_cols + 31) / 32 + 1);
-        const int64_t per_row = A->nnz / ntr;
-        int threads = per_row <= 256 ? 64 : per_row <= 4096 ? 128 : kSymThreads;
-        // where B's tile grid is narrow the bitmap simply covers all of it (worth it while the two sweeps
-        // over the whole bitmap cost a block less than the three dependent gathers they replace:
-        // measured, up to about six words per thread)
-        const int64_t grid_words = (B->tile_cols + 31) / 32;
-        const int direct_words = grid_words <= std::min<int64_t>(kDirectWords, 6 * threads) ? (int)grid_words : 0;
-        // short tile-rows of A: two per wave (with more of them than the chip holds waves, half the time);
-        // against a wide B with the bitmap in segments, and a second launch for the tile-rows it leaves over
-        const bool halves = threads == 64 && direct_words == 0 && per_row <= 128;
-        // A product that takes the general task-list kernel, against a B whose tile grid fits the bitmap (hubs of
-        // a graph meet most of B): the pass keeps the bitmaps and the pairs per tile column for that kernel, which
-        // then walks the candidates twice instead of four times.  The counters cost the pass LDS and time (on
-        // such a graph 26 -> 42 ms, for 133 -> 100 ms in the task-list kernel), and where the list kernel runs
-        // they are wasted; which kernel will run is known only after this pass, so the handle goes by what the
-        // previous call with operands of the same sizes did.  The result is the same either way.
-        size_t count_lds = (size_t)max_words * sizeof(uint32_t);
-        const bool general_expected = hint.general;
-        if (direct_words > 0 && general_expected && (int64_t)ntr * direct_words * 17 * 4 <= ((int64_t)1 << 30) &&
-            (size_t)direct_words * 17 * sizeof(uint32_t) <= 60 * 1024) {
-            saved_words = direct_words;
-            saved_bitmap = ctx_alloc_n<uint32_t>(ctx, (size_t)ntr * direct_words, s);
-            saved_cnt = ctx_alloc_n<uint32_t>(ctx, (size_t)ntr * direct_words * 16, s);
-            if (!saved_bitmap || !saved_cnt) return cleanup(TSP_ERR_ALLOC_FAILED);
-            count_lds = std::max(count_lds, (size_t)direct_words * 17 * sizeof(uint32_t));
-            // (the counters take LDS, LDS decides how many blocks a CU holds, and the pass lives on waves in
-            // flight: larger blocks keep as many; the heaviest tile-rows, one block each, decide when the launch
-            // ends: 128, 256, 512, 1024 threads: 76, 42, 29, 32 ms on an R-MAT graph of scale 18)
-            if (count_lds > 8 * 1024) threads = kSymThreadsLong;
+    // The tile-rows' sizes and the sums before them
+    auto count_tile_rows = [&]() {
+        row_jmin = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
+        row_c_tiles = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
+        row_pairs = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
+        row_words = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
+        row_cand = ctx_alloc_n<int32_t>(ctx, (size_t)ntr + 1, s);
+        row_pair_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)ntr + 1, s);
+        if (!row_jmin || !row_c_tiles || !row_pairs || !row_words || !row_cand || !row_pair_ptr) return (int)TSP_ERR_ALLOC_FAILED;
+        if (ntr > 0) {
+            KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
+            // the bitmap cannot be wider than B's tile grid; short tile-rows get one wave each, so that
+            // many more of them are in flight (the kernels are bound by dependent loads, not by work)
+            const int max_words = (int)std::min<int64_t>(kMaxWords, (B->tile_cols + 31) / 32 + 1);
+            const int64_t per_row = A->nnz / ntr;
+            int threads = per_row <= 256 ? 64 : per_row <= 4096 ? 128 : kSymThreads;
+            // where B's tile grid is narrow the bitmap simply covers all of it (worth it while the two sweeps
+            // over the whole bitmap cost a block less than the three dependent gathers they replace:
+            // measured, up to about six words per thread)
+            const int64_t grid_words = (B->tile_cols + 31) / 32;
+            const int direct_words = grid_words <= std::min<int64_t>(kDirectWords, 6 * threads) ? (int)grid_words : 0;
+            // short tile-rows of A: two per wave (with more of them than the chip holds waves, half the time);
+            // against a wide B with the bitmap in segments, and a second launch for the tile-rows it leaves over
+            const bool halves = threads == 64 && direct_words == 0 && per_row <= 128;
+            // A product that takes the general task-list kernel, against a B whose tile grid fits the bitmap (hubs of
+            // a graph meet most of B): the pass keeps the bitmaps and the pairs per tile column for that kernel, which
+            // then walks the candidates twice instead of four times.  The counters cost the pass LDS and time (on
+            // such a graph 26 -> 42 ms, for 133 -> 100 ms in the task-list kernel), and where the list kernel runs
+            // they are wasted; which kernel will run is known only after this pass, so the handle goes by what the
+            // previous call with operands of the same sizes did.  The result is the same either way.
+            size_t count_lds = (size_t)max_words * sizeof(uint32_t);
+            const bool general_expected = hint.general;
+            if (direct_words > 0 && general_expected && (int64_t)ntr * direct_words * 17 * 4 <= ((int64_t)1 << 30) &&
+                (size_t)direct_words * 17 * sizeof(uint32_t) <= 60 * 1024) {
+                saved_words = direct_words;
+                saved_bitmap = ctx_alloc_n<uint32_t>(ctx, (size_t)ntr * direct_words, s);
+                saved_cnt = ctx_alloc_n<uint32_t>(ctx, (size_t)ntr * direct_words * 16, s);
+                if (!saved_bitmap || !saved_cnt) return (int)TSP_ERR_ALLOC_FAILED;
+                count_lds = std::max(count_lds, (size_t)direct_words * 17 * sizeof(uint32_t));
+                // (the counters take LDS, LDS decides how many blocks a CU holds, and the pass lives on waves in
+                // flight: larger blocks keep as many; the heaviest tile-rows, one block each, decide when the launch
+                // ends: 128, 256, 512, 1024 threads: 76, 42, 29, 32 ms on an R-MAT graph of scale 18)
+                if (count_lds > 8 * 1024) threads = kSymThreadsLong;
+            }
+            if (halves && max_words > 1024) {
+                hipLaunchKernelGGL(long_rows ? k_sym_count_segmented<true> : k_sym_count_segmented<false>,
+                                   dim3((unsigned)((ntr + 1) / 2)), dim3(64), 0, s, ra, rb, std::min(lanes, 8), max_words,
+                                   row_jmin, row_c_tiles, row_pairs, row_words, row_cand, ctx->d_scalars);
+                hipLaunchKernelGGL(long_rows ? k_sym_count<true> : k_sym_count<false>, dim3((unsigned)ntr), dim3(threads),
+                                   max_words * sizeof(uint32_t), s, ra, rb, lanes, max_words, 0, /*only_marked=*/1,
+                                   row_jmin, row_c_tiles, row_pairs, row_words, row_cand, ctx->d_scalars, nullptr, nullptr,
+                                   nullptr);
+            } else if (halves)
+                hipLaunchKernelGGL(long_rows ? k_sym_count_half<true> : k_sym_count_half<false>,
+                                   dim3((unsigned)((ntr + 1) / 2)), dim3(64), 2 * max_words * sizeof(uint32_t), s, ra, rb,
+                                   std::min(lanes, 8), max_words, row_jmin, row_c_tiles, row_pairs, row_words, row_cand,
+                                   ctx->d_scalars);
+            else
+                hipLaunchKernelGGL(long_rows ? k_sym_count<true> : k_sym_count<false>, dim3((unsigned)ntr), dim3(threads),
+                                   count_lds, s, ra, rb, lanes, max_words, direct_words,
+                                   /*only_marked=*/0, row_jmin, row_c_tiles, row_pairs, row_words, row_cand, ctx->d_scalars,
+                                   saved_bitmap, saved_cnt,
+                                   general_expected && hint.order_rows == ntr ? hint.order : nullptr);
+            if (const hipError_t e = hipGetLastError(); e != hipSuccess) return hip_fail(ctx, e);
         }
-        if (halves && max_words > 1024) {
-            hipLaunchKernelGGL(long_rows ? k_sym_count_segmented<true> : k_sym_count_segmented<false>,
-                               dim3((unsigned)((ntr + 1) / 2)), dim3(64), 0, s, ra, rb, std::min(lanes, 8), max_words,
-                               row_jmin, row_c_tiles, row_pairs, row_words, row_cand, ctx->d_scalars);
-            hipLaunchKernelGGL(long_rows ? k_sym_count<true> : k_sym_count<false>, dim3((unsigned)ntr), dim3(threads),
-                               max_words * sizeof(uint32_t), s, ra, rb, lanes, max_words, 0, /*only_marked=*/1,
-                               row_jmin, row_c_tiles, row_pairs, row_words, row_cand, ctx->d_scalars, nullptr, nullptr,
-                               nullptr);
-        } else if (halves)
-            hipLaunchKernelGGL(long_rows ? k_sym_count_half<true> : k_sym_count_half<false>,
-                               dim3((unsigned)((ntr + 1) / 2)), dim3(64), 2 * max_words * sizeof(uint32_t), s, ra, rb,
-                               std::min(lanes, 8), max_words, row_jmin, row_c_tiles, row_pairs, row_words, row_cand,
-                               ctx->d_scalars);
-        else
-            hipLaunchKernelGGL(long_rows ? k_sym_count<true> : k_sym_count<false>, dim3((unsigned)ntr), dim3(threads),
-                               count_lds, s, ra, rb, lanes, max_words, direct_words,
-                               /*only_marked=*/0, row_jmin, row_c_tiles, row_pairs, row_words, row_cand, ctx->d_scalars,
-                               saved_bitmap, saved_cnt,
-                               general_expected && hint.order_rows == ntr ? hint.order : nullptr);
-        SYM_CHECK(hipGetLastError());
-    }
-    {
-        KernelTimer kt(ctx, TSP_KERNEL_SCAN_SYM, s);
-        // the same launch sums the tiles of operands that come straight from the converter
-        const TileCount ca{A->tile_row_ptr, A->tile_row_end, A->tile_rows, A->ntiles < 0 ? A->scalar_slot : -1};
-        const TileCount cb{B->tile_row_ptr, B->tile_row_end, B->tile_rows, B->ntiles < 0 && B != A ? B->scalar_slot : -1};
-        int64_t rows_covered = ntr;
-        if (ca.slot >= 0) rows_covered = std::max(rows_covered, ca.tile_rows);
-        if (cb.slot >= 0) rows_covered = std::max(rows_covered, cb.tile_rows);
-        const int64_t blocks = rows_covered > 0 ? (rows_covered + kRowScanBlock - 1) / kRowScanBlock : 1;
-        unsigned epoch = 0;
-        ChainSlot *slots = static_cast<ChainSlot *>(chain_prepare(ctx, blocks, &epoch, s));
-        if (!slots) return cleanup(TSP_ERR_ALLOC_FAILED);
-        hipLaunchKernelGGL(k_sym_row_scan, dim3((unsigned)blocks), dim3(kRowScanThreads), 0, s, ntr, row_c_tiles,
-                           row_pairs, row_words, row_cand, P->c_tile_row_ptr, row_pair_ptr, slots, epoch,
-                           A->tile_row_ptr, A->tile_row_end, ctx->d_scalars, ca, cb, ctx->h_scalars_dev, ++ctx->publish_tag);
-        SYM_CHECK(hipGetLastError());
-    }
+        {
+            KernelTimer kt(ctx, TSP_KERNEL_SCAN_SYM, s);
+            // the same launch sums the tiles of operands that come straight from the converter
+            const TileCount ca{A->tile_row_ptr, A->tile_row_end, A->tile_rows, A->ntiles < 0 ? A->scalar_slot : -1};
+            const TileCount cb{B->tile_row_ptr, B->tile_row_end, B->tile_rows, B->ntiles < 0 && B != A ? B->scalar_slot : -1};
+            int64_t rows_covered = ntr;
+            if (ca.slot >= 0) rows_covered = std::max(rows_covered, ca.tile_rows);
+            if (cb.slot >= 0) rows_covered = std::max(rows_covered, cb.tile_rows);
+            const int64_t blocks = rows_covered > 0 ? (rows_covered + kRowScanBlock - 1) / kRowScanBlock : 1;
+            unsigned epoch = 0;
+            ChainSlot *slots = static_cast<ChainSlot *>(chain_prepare(ctx, blocks, &epoch, s));
+            if (!slots) return (int)TSP_ERR_ALLOC_FAILED;
+            hipLaunchKernelGGL(k_sym_row_scan, dim3((unsigned)blocks), dim3(kRowScanThreads), 0, s, ntr, row_c_tiles,
+                               row_pairs, row_words, row_cand, P->c_tile_row_ptr, row_pair_ptr, slots, epoch,
+                               A->tile_row_ptr, A->tile_row_end, ctx->d_scalars, ca, cb, ctx->h_scalars_dev, ++ctx->publish_tag);
+            if (const hipError_t e = hipGetLastError(); e != hipSuccess) return hip_fail(ctx, e);
+        }
+        return (int)TSP_OK;
+    };
     // Sizes of the task list.  For operands of the sizes of earlier products of this handle that the list kernel has worked
     // off, counting pass and all, its arrays get the largest sizes seen (and a sixteenth more) without waiting for the
     // ones of this product: k_sym_emit_listed leaves out a tile-row that does not fit, and the numbers of the product at
     // hand, checked below, then say that it has to run again with arrays that do.
     const int64_t *h = ctx->h_scalars;
     bool hinted = key_known && hint.usable && ntr > 0 && n_chunks <= kMaxChunks && !strips_wanted(ctx, P, B);
+    // ... and the list kernel finds the sizes of the tile-rows itself, where B's whole tile grid fits its bitmap,
+    const int64_t grid_words = (B->tile_cols + 31) / 32;
+    auto block_lds = [](int64_t words, int64_t window) { return (size_t)(2 * words + 11 * window) * sizeof(uint32_t); };
+    auto by_block = [&](const ListSizes &n, int64_t words) {
+        return n.max_row_a_tiles <= kBlockATiles && block_lds(words, std::max<int64_t>(std::min<int64_t>(n.max_row_c_tiles, kWindow), 1)) <= kLdsLimit &&
+               std::max(A->tile_capacity, B->tile_capacity) < (int64_t)1 << 27;       // (32-bit offsets into the bitmaps)
+    };
+    // by a wave or by a block per tile-row (k_sym_emit_few, k_sym_emit_block); with more tile-rows than the chip holds blocks, most of
+    // them short but some not for a wave, the count and k_sym_emit_listed with two of them per wave take less (above)
+    const int64_t most_pairs = std::max<int64_t>(hint.most.max_row_pairs, 1);
+    const int64_t wave_words = few_words(grid_words, std::max<int64_t>(hint.most.max_row_c_tiles, 1), most_pairs);
+    const bool few = few_pairs(most_pairs, ntr) && wave_words * kFewWaves * (int64_t)sizeof(uint32_t) <= (int64_t)kLdsLimit;
+    bool fused_sizes = hinted && grid_words <= kSizingWords && hint.most.max_row_pairs <= kListCap && hint.most.max_row_c_tiles <= kListTiles &&
+                       by_block(hint.most, grid_words) && (few || hint.most.candidates / ntr > 256 || ntr <= kResidentTileRows);
+    bool counted_again = false;
     bool ran_again = false, arrived = false;                          // the host has the numbers of the counting kernels
     int64_t first_numbers[kScalars];               // ... and got them before the list kernel ran again
     auto free_lists = [&]() {
@@ -1934,6 +2406,10 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         return true_ones;
     };
 list_kernels:
+    if (!fused_sizes && !row_jmin) {
+        rc = count_tile_rows();
+        if (rc) return cleanup(rc);
+    }
     if (!hinted) {
         if (!arrived) {
             if (!rc) rc = wait_published_scalars(ctx, ctx->publish_tag, s);        // ---- sync 1: sizes of the task list
@@ -1962,7 +2438,7 @@ list_kernels:
         return cleanup(TSP_ERR_ALLOC_FAILED);
 
     if (ntr > 0) {
-        const int words_cap = (int)(z.max_row_words > 0 ? z.max_row_words : 1);
+        const int words_cap = (int)std::max<int64_t>(fused_sizes ? grid_words : z.max_row_words, 1);
         int window = (int)(z.max_row_c_tiles < kWindow ? z.max_row_c_tiles : kWindow);
         if (window < 1) window = 1;
         const size_t lds = (size_t)(2 * words_cap + 2 * window) * sizeof(uint32_t);
@@ -1983,24 +2459,21 @@ list_kernels:
         // the row masks of the window when it also runs the counting pass.  A launch may ask for 64 KB: a product
         // against a very wide B (a bitmap of thousands of words) takes one tile-row per block instead of two
         // per wave, and the general kernel when even that does not fit.
-        constexpr size_t kLdsLimit = 64 * 1024;
         constexpr int kTeamsPerWave = 64 / kListTeamLanes;
         const int list_cap = (int)std::max<int64_t>(z.max_row_pairs, 1);
         int team_words = 0;
         bool halves = false;
-        const size_t block_lds = (size_t)(2 * words_cap + 11 * window) * sizeof(uint32_t);
-        const bool by_block = z.max_row_a_tiles <= kBlockATiles && block_lds <= kLdsLimit &&
-                              std::max(A->tile_capacity, B->tile_capacity) < (int64_t)1 << 27;    // (32-bit offsets into the bitmaps)
+        const bool block_each = by_block(z, words_cap);
         if (listed) {
             // (k_sym_emit_block at any number of tile-rows: with the counting pass and the row offsets in launches of their
             // own the product of 300 blocks of 16x16, 48 entries per row, takes 59 us instead of 49)
-            fused_masks = ntr >= 1024 || by_block;
+            fused_masks = fused_sizes || ntr >= 1024 || block_each;
             team_words = 2 * words_cap + 2 * window + 3 * list_cap + (fused_masks ? 8 * window : 0);
             // tile-rows with few candidates: two per wave (see k_sym_count_half), where there are more of them than the
             // chip holds blocks of two waves (36 pairs per tile-row, 1536 tile-rows: 12 us with a block each, 18 us so; 16
             // pairs, 8192 tile-rows: 26 and 20 us)
-            halves = fused_masks && threads == 64 && ntr > kResidentTileRows && (size_t)team_words * kTeamsPerWave * sizeof(uint32_t) <= kLdsLimit;
-            if ((size_t)team_words * sizeof(uint32_t) > kLdsLimit) {
+            halves = !fused_sizes && fused_masks && threads == 64 && ntr > kResidentTileRows && (size_t)team_words * kTeamsPerWave * sizeof(uint32_t) <= kLdsLimit;
+            if (!fused_sizes && (size_t)team_words * sizeof(uint32_t) > kLdsLimit) {
                 listed = false;
                 fused_masks = false;
             }
@@ -2012,11 +2485,28 @@ list_kernels:
         hint.general = !listed;
         // (the order of the previous product goes; the general branch below may keep a new one)
         drop_order(hint);
-        if (listed && fused_masks && !halves && by_block) {
-            hipLaunchKernelGGL(k_sym_emit_block, dim3((unsigned)ntr), dim3(kBlockListThreads),
-                               block_lds, s, ra, rb, words_cap, window, row_jmin, row_words, P->c_tile_row_ptr, row_pair_ptr,
-                               P->c_tile_row, P->c_tile_col, P->pair_off, P->pair_ab, A->row_mask, B->row_mask, P->c_row_mask,
-                               P->c_row_off, row_nnz, P->c_rows, ctx->d_scalars, tile_row_entries, z.c_tiles, z.pairs);
+        if (listed && fused_masks && !halves && block_each) {
+            ListSizing sizing{};
+            if (fused_sizes) {
+                tile_row_info = ctx_alloc_n<uint4>(ctx, (size_t)ntr, s);
+                partial = ctx_alloc_n<uint32_t>(ctx, (size_t)n_chunks * 16, s);
+                if (!tile_row_info || !partial) return cleanup(TSP_ERR_ALLOC_FAILED);
+                if (ctx->list_call >= (1u << 30) - 1) {          // the numbers start again: no slot holds one
+                    hipLaunchKernelGGL(k_clear_list_slots, dim3((kListSlotWords + 255) / 256), dim3(256), 0, s, ctx->d_list_slots);
+                    ctx->list_call = 0;
+                }
+                sizing = {(int)grid_words, ctx->d_list_slots, ++ctx->list_call, tile_row_info, P->c_tile_row_ptr};
+            }
+            if (fused_sizes && few)                // (window and list_cap are what `few` went by)
+                hipLaunchKernelGGL(k_sym_emit_few, dim3((unsigned)((ntr + kFewWaves - 1) / kFewWaves)), dim3(64 * kFewWaves),
+                                   wave_words * kFewWaves * sizeof(uint32_t), s, ra, rb, window, list_cap, (int)wave_words,
+                                   P->c_tile_row, P->c_tile_col, P->pair_off, P->pair_ab, A->row_mask, B->row_mask, P->c_row_mask, P->c_row_off,
+                                   row_nnz, P->c_rows, ctx->d_scalars, tile_row_entries, z.c_tiles, z.pairs, sizing);
+            else
+                hipLaunchKernelGGL(fused_sizes ? k_sym_emit_block<true> : k_sym_emit_block<false>, dim3((unsigned)ntr), dim3(kBlockListThreads),
+                                   block_lds(words_cap, window), s, ra, rb, words_cap, window, row_jmin, row_words, P->c_tile_row_ptr, row_pair_ptr,
+                                   P->c_tile_row, P->c_tile_col, P->pair_off, P->pair_ab, A->row_mask, B->row_mask, P->c_row_mask,
+                                   P->c_row_off, row_nnz, P->c_rows, ctx->d_scalars, tile_row_entries, z.c_tiles, z.pairs, sizing);
         } else if (listed) {
             auto kernel = !fused_masks ? (long_rows ? k_sym_emit_listed<true, false, 0> : k_sym_emit_listed<false, false, 0>)
                           : halves     ? (long_rows ? k_sym_emit_listed<true, true, kListTeamLanes> : k_sym_emit_listed<false, true, kListTeamLanes>)
@@ -2116,8 +2606,14 @@ list_kernels:
     {
         KernelTimer kt(ctx, TSP_KERNEL_SCAN_ROWS, s);
         if (n_chunks > 0 && n_chunks <= kMaxChunks) {
-            hipLaunchKernelGGL(k_row_ptr, dim3((unsigned)n_chunks), dim3(256), 0, s, row_nnz, P->c_rows, tile_row_entries,
-                               ntr, P->c_row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, true, expected, live);
+            ListSums sums{};
+            if (fused_sizes) {
+                const bool count_a = A->ntiles < 0, count_b = B->ntiles < 0 && B != A;
+                sums = {tile_row_info, count_a ? A->tile_row_ptr : nullptr, count_a ? A->tile_row_end : nullptr,
+                        count_b ? B->tile_row_ptr : nullptr, count_b ? B->tile_row_end : nullptr, B->tile_rows, A->scalar_slot, B->scalar_slot, partial};
+            }
+            hipLaunchKernelGGL(fused_sizes ? k_row_ptr<true> : k_row_ptr<false>, dim3((unsigned)n_chunks), dim3(256), 0, s, row_nnz, P->c_rows,
+                               tile_row_entries, ntr, P->c_row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, true, expected, live, sums);
             SYM_CHECK(hipGetLastError());
             published = true;
             ctx->scalars_clean = true;             // (nothing of this call uses the block any more)
@@ -2141,7 +2637,13 @@ list_kernels:
         if (rc) return cleanup(rc);
         if (!z.holds(true_sizes())) {              // another product of the same sizes, with more in it
             std::copy(h, h + kScalars, first_numbers);
-            ran_again = true;
+            if (fused_sizes) {                     // (those of tile-rows that did not fit were not counted)
+                fused_sizes = arrived = false;
+                ctx->scalars_clean = false;
+                counted_again = true;
+            } else {
+                ran_again = true;
+            }
             drop_ahead();
             ctx_free(ctx, live, s);
             live = nullptr;
@@ -2152,6 +2654,7 @@ list_kernels:
     if (ran_again)                                 // (the scalars were cleared after the first time)
         for (int i = 0; i < kScalars; ++i)
             if (i != S_C_NNZ && i != S_MAX_ROW_ENTRIES && i != S_UNSUPPORTED && i != S_INTERNAL) ctx->h_scalars[i] = first_numbers[i];
+    if (counted_again) ctx->h_scalars[S_PRODUCTS] = first_numbers[S_PRODUCTS];
     if (ctx->h_scalars[S_UNSUPPORTED]) return cleanup(TSP_ERR_UNSUPPORTED);
     if (ctx->h_scalars[S_INTERNAL]) return cleanup(TSP_ERR_HIP);
     // (by the kernel that its own sizes ask for, so that a product has the same bits whatever came before it)

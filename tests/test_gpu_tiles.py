@@ -240,6 +240,61 @@ def test_prefix_sums_over_tile_rows(tsp, oracle, tile_rows):
         h.close()
 
 
+@pytest.mark.parametrize("tile_rows,tile_cols,right_tiles", [
+    (1, 1, 3), (3, 64, 60), (63, 40, 3), (64, 2000, 3), (64, 2000, 60), (65, 24576, 3), (129, 24576, 60), (129, 24577, 3), (4096, 31, 3),
+    (4160, 33, 3), (4160, 130, 60), (32768, 20, 3), (32769, 20, 3)])
+def test_sizes_of_tile_rows_found_with_the_task_list(tsp, oracle, tile_rows, tile_cols, right_tiles):
+    """Products of sizes that the handle knows, whose task list is made without a count of the tile-rows first: as many of them as a
+    group and one more or less, as many as there are slots for, few pairs and many, B as wide as the bitmap holds and one tile more; empty
+    tile-rows, and the last one with and without an entry.  The plan is that of the first product, array by array, also after one with
+    more in it, whose arrays do not do."""
+    rng = np.random.default_rng(tile_rows)
+    inner = 70
+
+    def operand(rows, cols, tiles):
+        r, c = [], []
+        for i in range(rows):
+            for j in rng.choice(cols, min(cols, tiles(i)), replace=False):
+                r.append(i * 16 + rng.integers(0, 16, 3))
+                c.append(j * 16 + rng.integers(0, 16, 3))
+        key = np.unique(np.concatenate(r) * (16 * cols) + np.concatenate(c))
+        return key // (16 * cols), key % (16 * cols)
+
+    def same_number(entries, rows, cols):
+        n = min(x[0].size for x in entries)
+        out = []
+        for r, c in entries:
+            keep = np.sort(rng.permutation(r.size)[:n])
+            out.append(inputs.from_coo(16 * rows, 16 * cols, r[keep], c[keep], rng.uniform(-1, 1, n), "tiles"))
+        return out
+
+    few = operand(tile_rows, inner, lambda i: 0 if i % 7 == 5 and i else 1 + i % 3)
+    more = operand(tile_rows, inner, lambda i: 66 if i in (0, tile_rows - 1) else 2 + i % 2)
+    As = same_number([few, more], tile_rows, inner)
+    r, c = operand(inner, tile_cols, lambda i: right_tiles + i % 5)
+    B = inputs.from_coo(16 * inner, 16 * tile_cols, r, c, rng.uniform(-1, 1, r.size), "right")
+    want = [oracle.spgemm(A, B, threads=4) for A in As]
+    h = tsp.Handle(validate=True)
+    try:
+        dA, dB = [tsp.to_device(A) for A in As], tsp.to_device(B)
+        first = {}
+        for which in (0, 0, 0, 1, 0, 1, 1):
+            ta, tb = h.convert(dA[which], tsp.FORM_LEFT), h.convert(dB, tsp.FORM_RIGHT)
+            plan = h.symbolic(ta, tb)
+            view = {k: x.cpu().numpy() if hasattr(x, "cpu") else x for k, x in plan.view().items()}
+            C = h.numeric(ta, tb, plan)
+            row_ptr, col, val = C.to_host()
+            for x in (C, plan, ta, tb):
+                x.free()
+            ref = want[which]
+            assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+            assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+            for k, v in first.setdefault(which, view).items():
+                assert np.array_equal(view[k], v), k
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("left_tiles", [1, 31, 32, 33, 63, 64, 65])
 def test_tile_rows_of_many_left_tiles(tsp, oracle, left_tiles):
     """A tile-row of A with as many tiles as the words of contributors hold, one more and one less, among short ones."""
