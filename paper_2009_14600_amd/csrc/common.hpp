@@ -92,6 +92,7 @@ struct ListHint {
     ListSizes most;
     int64_t nnz = -1, c_tiles = 0, a_tiles = 0;    // of the last one
     int64_t max_row_entries = 0;
+    bool large = true;                             // an operand had tile-rows for k_convert_large
     bool general = false;                          // it took the general task-list kernel ...
     int32_t *order = nullptr;                      // ... and its tile-rows in this order (heaviest first), or null
     int64_t order_rows = 0;
@@ -100,12 +101,13 @@ struct ListHint {
 struct ListExpected {
     ListSizes most;
     int64_t nnz, max_row_entries;
+    bool no_large;                                 // ... of operands whose large tile-rows have not been converted: none of those
     static __host__ __device__ ListSizes sizes(const int64_t *scalars) {
         return ListSizes{scalars[S_C_TILES], scalars[S_PAIRS], scalars[S_CANDIDATES], scalars[S_MAX_ROW_C_TILES], scalars[S_MAX_ROW_PAIRS],
                          scalars[S_MAX_ROW_WORDS], scalars[S_MAX_ROW_A_TILES], 0};
     }
     __host__ __device__ bool holds(const int64_t *scalars) const {
-        return !scalars[S_INVALID] && !scalars[S_UNSUPPORTED] && !scalars[S_INTERNAL] && most.holds(sizes(scalars)) &&
+        return !scalars[S_INVALID] && !scalars[S_UNSUPPORTED] && !scalars[S_INTERNAL] && !(no_large && (scalars[S_LARGE_A] || scalars[S_LARGE_B])) && most.holds(sizes(scalars)) &&
                scalars[S_C_NNZ] <= nnz && scalars[S_MAX_ROW_ENTRIES] <= max_row_entries;
     }
 };
@@ -141,6 +143,12 @@ struct HintMemory {
     Sizes sizes[kProducts];
     Hint hints[kProducts];
     int64_t used[kProducts] = {}, uses = 0;
+    // The hint for these sizes, or null
+    const Hint *look(const Sizes &of) const {
+        for (int i = 0; i < kProducts; ++i)
+            if (sizes[i] == of) return &hints[i];
+        return nullptr;
+    }
     // The hint for these sizes, a new one in the place of the one not used for longest where there is none; drop(hint) gets
     // that one first.
     template <typename Drop>
@@ -219,6 +227,8 @@ struct tsp_tiles_s {
     uint2 *lhead = nullptr, *rhead = nullptr;      // per form: {group mask, index of the tile's first group}
     uint4 *ldata = nullptr, *rdata = nullptr;
     int64_t group_capacity = 0;
+    bool large = false;                            // some tile-rows went through k_convert_large
+    int32_t *large_rows = nullptr;                 // tile-rows of many entries that are not converted yet (and how many, in the scalars)
 };
 
 struct tsp_plan_s {
@@ -294,8 +304,10 @@ void fill_selection_criteria(tsp_context *ctx, int64_t rows, int64_t nnz, int64_
 // did, *remembered that it did not by what it found earlier.  Both operands have passed check_csr_host; the scalar block is zero.
 int rowwise_spgemm(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s,
                    bool *taken, RowHint **remembered);
+// leave_large: tile-rows of many entries are listed only, and count as empty until convert_large has taken them.
 int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out,
-                    hipStream_t s);
+                    bool leave_large, hipStream_t s);
+int convert_large(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, int64_t listed, hipStream_t s);
 void tiles_release(tsp_context *ctx, tsp_tiles_s *t, hipStream_t s);
 // C of a multiplication that symbolic_run has launched itself (`done`): its arrays
 struct TilesAhead {
@@ -303,6 +315,8 @@ struct TilesAhead {
     float *val = nullptr;
     bool done = false;
 };
+// kLargeLeft: an operand has tile-rows that convert_enqueue has left, as the host's mirror of the scalars says; nothing is done.
+constexpr int kLargeLeft = 1;
 int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **out, hipStream_t s, TilesAhead *ahead = nullptr);
 void plan_release(tsp_context *ctx, tsp_plan_s *p, hipStream_t s);
 // Order of work in vertical strips for the kernels that walk the task list of a plan with long tile-rows.

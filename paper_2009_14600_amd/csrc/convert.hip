@@ -1002,6 +1002,7 @@ void tiles_release(tsp_context *ctx, tsp_tiles_s *t, hipStream_t s) {
     ctx_free(ctx, t->rhead, s);
     ctx_free(ctx, t->ldata, s);
     ctx_free(ctx, t->rdata, s);
+    ctx_free(ctx, t->large_rows, s);
     delete t;
 }
 
@@ -1068,8 +1069,18 @@ static int convert_begin(tsp_context *ctx, const tsp_csr *A, int forms, int scal
     return TSP_OK;
 }
 
-int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out, hipStream_t s) {
-    return convert_begin(ctx, A, forms, scalar_slot, out, nullptr, s);
+int convert_enqueue(tsp_context *ctx, const tsp_csr *A, int forms, int scalar_slot, tsp_tiles_s **out, bool leave_large, hipStream_t s) {
+    int32_t *scratch = nullptr;
+    const int rc = convert_begin(ctx, A, forms, scalar_slot, out, leave_large ? &scratch : nullptr, s);
+    if (!rc) (*out)->large_rows = scratch;
+    return rc;
+}
+int convert_large(tsp_context *ctx, const tsp_csr *A, tsp_tiles_s *t, int64_t listed, hipStream_t s) {
+    const int rc = listed > 0 ? convert_kernels(ctx, A, t, t->large_rows, listed, s) : TSP_OK;
+    t->large = listed > 0;
+    ctx_free(ctx, t->large_rows, s);
+    t->large_rows = nullptr;
+    return rc;
 }
 
 // Number of tiles of a tile matrix (tsp_convert only; tsp_spgemm lets the symbolic phase add them up), by one block, which
@@ -1157,6 +1168,7 @@ extern "C" int tsp_convert(tsp_handle ctx, const tsp_csr *A, int forms, tsp_tile
         const int64_t large = ctx->h_scalars[S_LARGE_A];
         if (!ctx->scalars_clean) hipLaunchKernelGGL(k_clear_scalars, dim3(1), dim3(64), 0, s, ctx->d_scalars);
         rc = convert_kernels(ctx, A, t, scratch, large, s);
+        t->large = true;
         if (!rc) rc = total();
     }
     ctx_free(ctx, scratch, s);

@@ -84,10 +84,23 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
             if (ctx->count_products) count_products(ctx, A, B, s);
         }
         phase_begin(ctx, TSP_PHASE_CONVERT, s);
-        rc = convert_enqueue(ctx, A, alias ? (TSP_FORM_LEFT | TSP_FORM_RIGHT) : TSP_FORM_LEFT, S_TILES_A, &ta, s);
-        if (!rc && !alias) rc = convert_enqueue(ctx, B, TSP_FORM_RIGHT, S_TILES_B, &tb, s);
+        // (the kernel for tile-rows of many entries is not launched where the last product of these sizes had none: with nothing to do
+        // it takes 4.6 us, of 25 to 200 for the whole call)
+        const ListHint *const hint = ctx->list_hints.look({{A->rows, A->nnz, B->rows, B->nnz, B->cols, alias}});
+        const bool leave_large = hint && !hint->large;
+        rc = convert_enqueue(ctx, A, alias ? (TSP_FORM_LEFT | TSP_FORM_RIGHT) : TSP_FORM_LEFT, S_TILES_A, &ta, leave_large, s);
+        if (!rc && !alias) rc = convert_enqueue(ctx, B, TSP_FORM_RIGHT, S_TILES_B, &tb, leave_large, s);
         phase_end(ctx, TSP_PHASE_CONVERT, s);
         if (!rc) rc = symbolic_run(ctx, ta, alias ? ta : tb, &plan, s, &ahead);
+        if (rc == kLargeLeft) {                    // this one has some
+            const int64_t in_a = ctx->h_scalars[S_LARGE_A], in_b = ctx->h_scalars[S_LARGE_B];
+            hipLaunchKernelGGL(k_clear_scalars_all, dim3(1), dim3(64), 0, s, ctx->d_scalars);
+            ctx->scalars_clean = false;
+            if (ctx->count_products) count_products(ctx, A, B, s);
+            rc = convert_large(ctx, A, ta, in_a, s);
+            if (!rc && !alias) rc = convert_large(ctx, B, tb, in_b, s);
+            if (!rc) rc = symbolic_run(ctx, ta, alias ? ta : tb, &plan, s, &ahead);
+        }
     }
     ctx->stats.products = !rc && ctx->count_products ? ctx->h_scalars[S_PRODUCTS] : -1;
     // Tiles because an earlier product of the same sizes was for them, and this one has other pairs of tiles: the operands are

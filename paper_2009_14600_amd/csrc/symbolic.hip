@@ -2391,6 +2391,7 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
         if (h[S_UNSUPPORTED]) return (int)TSP_ERR_UNSUPPORTED;
         if (h[S_INTERNAL]) return (int)TSP_ERR_HIP;
+        if ((A->large_rows && h[S_LARGE_A]) || (B->large_rows && h[S_LARGE_B])) return kLargeLeft;
         if (A->ntiles < 0) A->ntiles = h[A->scalar_slot];
         if (B->ntiles < 0) B->ntiles = h[B->scalar_slot];
         P->c_tiles = h[S_C_TILES];
@@ -2593,7 +2594,7 @@ list_kernels:
     NumericLaunch launched{};
     const bool early = ahead && hinted && hint.nnz > 0;
     if (early) {
-        expected = {z, hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20), hint.max_row_entries};
+        expected = {z, hint.nnz + std::min<int64_t>(hint.nnz / 16, 1 << 20), hint.max_row_entries, A->large_rows || B->large_rows};
         // (no more output tiles than that one had: the XCDs get equal shares of the tiles the launch is for; an eighth of
         // them with a sixteenth to spare took 2 % longer on a stencil)
         expected.most.c_tiles = hint.c_tiles;
@@ -2654,7 +2655,8 @@ list_kernels:
     if (ran_again)                                 // (the scalars were cleared after the first time)
         for (int i = 0; i < kScalars; ++i)
             if (i != S_C_NNZ && i != S_MAX_ROW_ENTRIES && i != S_UNSUPPORTED && i != S_INTERNAL) ctx->h_scalars[i] = first_numbers[i];
-    if (counted_again) ctx->h_scalars[S_PRODUCTS] = first_numbers[S_PRODUCTS];
+    if (counted_again)
+        for (int i : {S_PRODUCTS, S_LARGE_A, S_LARGE_B}) ctx->h_scalars[i] = first_numbers[i];
     if (ctx->h_scalars[S_UNSUPPORTED]) return cleanup(TSP_ERR_UNSUPPORTED);
     if (ctx->h_scalars[S_INTERNAL]) return cleanup(TSP_ERR_HIP);
     // (by the kernel that its own sizes ask for, so that a product has the same bits whatever came before it)
@@ -2667,6 +2669,7 @@ list_kernels:
     hint.c_tiles = P->c_tiles;
     hint.max_row_entries = std::max(key_known ? hint.max_row_entries : 0, ctx->h_scalars[S_MAX_ROW_ENTRIES]);
     hint.usable = listed && fused_masks;
+    hint.large = A->large || B->large || ctx->h_scalars[S_LARGE_A] || ctx->h_scalars[S_LARGE_B];
     hint.most = key_known ? hint.most.with(true_sizes()) : true_sizes();
     P->c_nnz = ctx->h_scalars[S_C_NNZ];
     P->max_row_entries = ctx->h_scalars[S_MAX_ROW_ENTRIES];

@@ -295,6 +295,42 @@ def test_sizes_of_tile_rows_found_with_the_task_list(tsp, oracle, tile_rows, til
         h.close()
 
 
+@pytest.mark.parametrize("left,right", [((1, 0), (0, 0)), ((0, 0), (1, 0)), ((1, 1), (0, 1)), (None, None)])
+def test_tile_rows_of_many_entries_where_there_were_none(tsp, oracle, left, right):
+    """Products of the same sizes with and without tile-rows for the kernel that is not launched where the last one had none."""
+    n, tiles = 40, 40
+    rng = np.random.default_rng(7)
+
+    def operand(large):
+        entries = np.full(n, 700)
+        if large:
+            entries = np.where(np.isin(np.arange(n), (0, 17, n - 1)), 3000, 514)       # (about as many entries altogether)
+        A = _tile_rows(rng, 16 * n, np.full(n, tiles), entries)
+        keep = np.sort(rng.permutation(A.nnz)[:27000])
+        row = np.repeat(np.arange(A.rows), np.diff(A.row_ptr))[keep]
+        return inputs.from_coo(A.rows, A.cols, row, A.col_idx[keep], rng.uniform(-1, 1, keep.size), "large" if large else "even")
+
+    kinds = [operand(False), operand(True)]
+    dev = [tsp.to_device(A) for A in kinds]
+    h = tsp.Handle(validate=True)
+    try:
+        h.set_option(tsp.OPT_WORK_ORDER, 2)        # (the tile kernels, whatever the operands)
+        pairs = [(0, 0), (0, 0), (1, 1), (0, 0), (1, 1), (1, 1)] if left is None else [(0, 0), (0, 0), left, (0, 0), right, right, (0, 0)]
+        others = dev if left is None else [tsp.to_device(A) for A in kinds]
+        want = {}
+        for i, j in pairs:
+            if (i, j) not in want:
+                want[i, j] = oracle.spgemm(kinds[i], kinds[j], threads=4)
+            C = h.spgemm(dev[i], others[j])
+            row_ptr, col, val = C.to_host()
+            C.free()
+            ref = want[i, j]
+            assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
+            assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("left_tiles", [1, 31, 32, 33, 63, 64, 65])
 def test_tile_rows_of_many_left_tiles(tsp, oracle, left_tiles):
     """A tile-row of A with as many tiles as the words of contributors hold, one more and one less, among short ones."""
