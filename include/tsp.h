@@ -238,8 +238,9 @@ int tsp_csr_free(tsp_handle handle, tsp_csr *C, void *stream);
  * [0, C.nnz], and one that is smaller than one before it counts as that one, so that any row_ptr gives a well-formed
  * result of no more than C.nnz entries and none an out-of-bounds access (at the price of another pass and wait).  *out:
  * row_ptr (TSP_I64), col_idx, val (TSP_F32) from the handle's allocator, owned by the caller
- * (tsp_csr_free); zeroed on failure.  Synchronises the stream once (the new nnz sizes the
- * allocation).  C and out must be different objects.
+ * (tsp_csr_free); zeroed on failure.  Synchronises the stream once (the new nnz).  The arrays have room for
+ * the new nnz, or, on a handle that has compacted a matrix of these sizes before, for what was left of that one and a
+ * sixteenth more.  C and out must be different objects.
  * Errors: INVALID_ARG, ALLOC_FAILED, INDEX_OVERFLOW, HIP.
  */
 int tsp_compact_zeros(tsp_handle handle, const tsp_csr *C, tsp_csr *out, void *stream);

@@ -112,6 +112,10 @@ struct ListExpected {
     }
 };
 
+// Entries that were left of the last matrix of these sizes (compact.hip)
+struct CompactHint {
+    int64_t nnz = -1;
+};
 // What the row kernels found for the last product of the same sizes (rowwise.hip): whether the tile kernels
 // suit it better, and how long its lists of work are.  Only the choice of kernels and the sizes of workspaces follow
 // from it; the numbers of the product at hand are checked against it.
@@ -200,6 +204,7 @@ struct tsp_context {
     int64_t *d_scalars = nullptr;                  // device, kScalars entries
     unsigned long long *d_list_slots = nullptr;    // device, kListSlotWords, by the number of the call that wrote them (behind those)
     uint32_t list_call = 0;
+    tsp::HintMemory<tsp::CompactHint> compact_hints;
     unsigned long long *d_arrivals = nullptr;      // device, kArriveCounters counters, zero between launches (behind the scalars)
     bool scalars_clean = false;                    // all zero: the last kernel of the previous call left them so
     int64_t *h_scalars = nullptr;                  // pinned host mirror
@@ -407,6 +412,15 @@ __device__ __forceinline__ void publish_scalars(int64_t *d_scalars, int64_t *h_s
         __hip_atomic_store(&h_scalars_dev[threadIdx.x], (int64_t)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (clear) d_scalars[threadIdx.x] = 0;
         else if (mine) d_scalars[threadIdx.x] = (int64_t)v;
+    }
+}
+// ... of a block that leaves the scalar block itself alone: all that the host is to read, in LDS
+__device__ __forceinline__ void publish_mirror(int64_t *h_scalars_dev, int64_t tag, const int64_t *all) {
+    __syncthreads();
+    if (threadIdx.x < kScalars) {
+        const uint64_t v = threadIdx.x == S_PUBLISHED ? 0u : (uint64_t)all[threadIdx.x];
+        __hip_atomic_store(&h_scalars_dev[threadIdx.x], (int64_t)((publish_tag16(tag) << kPublishTagShift) | (v & ((1ull << kPublishTagShift) - 1u))),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

@@ -8,7 +8,8 @@
 // All three passes go by the entries and not by the rows, so that rows of any length weigh the same: a block takes a
 // chunk of 4096 consecutive entries (a multiple of that on very large matrices) and finds the rows that begin in it by a
 // search in row_ptr.  Bound by memory: the values twice, the columns once, the survivors.  200,003 rows of 60 entries on
-// average, a fifth zero: count 9 us, prefix sum 3 us, copy 31 us (by rows, 16 lanes to a row: 35 + 8 + 51 us).
+// average, a fifth zero: count 8.7 us, copy 31 us, the sums in it (with a launch of their own 8.7 + 4.6 + 30).  One pass that reads the
+// values once and waits for the sums of the blocks before takes 39: of blocks that all load, then all wait, then all write.
 // Only the entries between the first and the last row pointer are C's.  A block finds the new pointers of the first 4096 rows
 // that begin in its part; where there are more (empty ones, then), blocks for 4096 rows each find the others (300,000 rows
 // of 2000 entries 37 us for the call, 663 with all rows of a part left to its block; 81 by rows).
@@ -25,6 +26,10 @@ namespace tsp {
 constexpr int kCompactThreads = 256;
 constexpr int kCompactPart = 4096;             // entries a block holds at a time, 16 per thread
 constexpr int64_t kCompactChunks = 65536;      // at most
+// Up to so many blocks of the counting pass the copying blocks add up the counts before theirs themselves (a block reads two bytes for every
+// one), and the host gets the total from one of them that does nothing else; beyond, one block makes all the sums, in a launch of its
+// own (200,003 rows of 60 entries, 3126 blocks: 4.6 us and the gap before it).
+constexpr int64_t kCompactSums = 16384;
 constexpr int kCheckRows = 1024;               // rows per block that looks whether row pointers ascend
 constexpr int kCompactRows = 4096;             // rows whose new pointers a part's block finds, and rows of a block of their own
 
@@ -37,6 +42,10 @@ struct CompactArgs {
     int64_t last;                              // index of the last row pointer
     int64_t chunk;                             // entries per block, a multiple of kCompactPart
     int chunks;
+    // Counts of the blocks of the counting pass (those of rows first) to be added up, with what they have found in the two upper bits; or
+    // null: `before` has the sums.
+    const uint16_t *counts;
+    int64_t capacity;                          // of the result's columns and values
     // blocks for `per` rows each; they come before the chunks' in a launch (behind them they would end it)
     __host__ __device__ int row_blocks(int per) const { return rows < 0 ? 0 : (int)(rows / per) + 1; }
 };
@@ -88,7 +97,8 @@ __device__ __forceinline__ void load_part(const X *from, int64_t begin, int64_t 
     }
 }
 
-// Survivors per chunk, and where the entries begin and end (before[chunks + 1], before[chunks + 2]); the blocks of the rows look
+// Survivors per chunk, and where the entries begin and end (before[chunks + 1], before[chunks + 2]); the blocks of the rows, whose
+// counts come first, look
 // whether the row pointers ascend, and whether more than kCompactRows rows may begin in one part.
 template <typename RP>
 __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<RP> a, uint32_t *__restrict__ count,
@@ -102,12 +112,19 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<R
             const int64_t r = (int64_t)blockIdx.x * kCheckRows + u * kCompactThreads + threadIdx.x;
             down |= clamped(a, min(r, a.last)) > clamped(a, min(r + 1, a.last));
         }
-        if (down) d_scalars[S_DESCENDS] = 1;
+        bool runs = false;
         // (such rows have the first row of some block among them, and 3072 behind it)
         if (threadIdx.x == 0) {
             const int64_t r = (int64_t)blockIdx.x * kCheckRows, last = min(r + kCompactRows - kCheckRows, a.last);
             auto part = [&](int64_t row) { return min(clamped(a, row), max(a.nnz - 1, (int64_t)0)) / kCompactPart; };
-            if (r < a.last && part(r) == part(last)) d_scalars[S_EMPTY_RUNS] = 1;
+            runs = r < a.last && part(r) == part(last);
+        }
+        const int any_down = __syncthreads_or(down);
+        if (a.counts) {
+            if (threadIdx.x == 0) reinterpret_cast<uint16_t *>(count)[blockIdx.x] = (uint16_t)((any_down ? 1u << 14 : 0u) | (runs ? 1u << 15 : 0u));
+        } else {
+            if (any_down && threadIdx.x == 0) d_scalars[S_DESCENDS] = 1;
+            if (runs) d_scalars[S_EMPTY_RUNS] = 1;
         }
         return;
     }
@@ -128,7 +145,48 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<R
     n = wave_sum(n);
     if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = n;
     __syncthreads();
-    if (threadIdx.x == 0) count[b] = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+    if (threadIdx.x == 0) {
+        const uint32_t all = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+        if (a.counts) reinterpret_cast<uint16_t *>(count)[blockIdx.x] = (uint16_t)all;
+        else count[b] = all;
+    }
+}
+
+// The sum of the first n counts, and what was found, by the whole block (two barriers)
+struct CountSum {
+    int64_t survivors;
+    int found;                                 // 1: row pointers go down, 2: long runs of empty rows
+};
+__device__ __forceinline__ CountSum sum_counts(const uint16_t *counts, int n, uint32_t *s_wave, uint32_t *s_found) {
+    uint32_t sum = 0, found = 0;
+    const uint4 *const eights = reinterpret_cast<const uint4 *>(counts);
+    const int whole = (n + 7) / 8;
+    for (int q = threadIdx.x; q < whole; q += 2 * kCompactThreads) {
+        uint4 x[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) x[u] = eights[min(q + u * kCompactThreads, whole - 1)];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t y[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+            const int left = n - (q + u * kCompactThreads) * 8;      // counts of these that are to be added up
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t two = left >= 2 * k + 2 ? y[k] : left > 2 * k ? y[k] & 0xFFFFu : 0u;
+                sum += (two & 0x3FFFu) + (two >> 16 & 0x3FFFu);
+                found |= two;
+            }
+        }
+    }
+    found = (found | found >> 16) >> 14 & 3u;
+    sum = wave_sum(sum);                       // (fewer than 2^31 entries)
+    found = (__any(found & 1u) ? 1u : 0u) | (__any(found & 2u) ? 2u : 0u);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        s_wave[threadIdx.x >> 6] = sum;
+        s_found[threadIdx.x >> 6] = found;
+    }
+    __syncthreads();
+    return {(int64_t)s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3], (int)(s_found[0] | s_found[1] | s_found[2] | s_found[3])};
 }
 
 // Survivors before every chunk, by one block, 4096 chunks at a time; the total to the host.  (At most 65,536 numbers.)
@@ -202,18 +260,31 @@ template <typename RP>
 __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP> a, const int64_t *__restrict__ before,
                                                                  int64_t *__restrict__ new_row_ptr,
                                                                  int32_t *__restrict__ out_col,
-                                                                 float *__restrict__ out_val) {
+                                                                 float *__restrict__ out_val, int64_t *d_scalars,
+                                                                 int64_t *h_scalars_dev, int64_t publish_tag) {
     __shared__ unsigned long long s_mask[kCompactPart / 64];
-    // (where the row pointers go down nothing is written, and the host makes the pass again, see compact_descending)
-    const int64_t found = uniform_load(before + a.chunks);
+    __shared__ uint32_t s_wave[kCompactThreads / 64], s_found[kCompactThreads / 64];
+    const int checks = a.counts ? a.row_blocks(kCheckRows) : 0, teller = a.counts ? 1 : 0;
+    if (teller && blockIdx.x == 0) {           // (the scalar block stays as it is)
+        __shared__ int64_t own[kScalars];
+        if (!publish_tag) return;
+        const int64_t standing = standing_scalar(d_scalars);
+        const CountSum all = sum_counts(a.counts, checks + a.chunks, s_wave, s_found);
+        if (threadIdx.x < kScalars)
+            own[threadIdx.x] = threadIdx.x == S_C_NNZ ? all.survivors : threadIdx.x == S_DESCENDS ? (all.found & 1) : threadIdx.x == S_EMPTY_RUNS ? 0 : standing;
+        publish_mirror(h_scalars_dev, publish_tag, own);
+        return;
+    }
     const EntryRange range{uniform_load(before + a.chunks + 1), uniform_load(before + a.chunks + 2)};
-    const bool descends = found & 1;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const int b = (int)blockIdx.x - a.row_blocks(kCompactRows);
+    const int b = (int)blockIdx.x - teller - a.row_blocks(kCompactRows);
     if (b < 0) {
+        // (where the row pointers go down nothing is written, and the host makes the pass again, see compact_descending)
+        const int64_t found = a.counts ? sum_counts(a.counts, checks, s_wave, s_found).found : uniform_load(before + a.chunks);
+        const bool descends = found & 1;
         if (!(found & 2)) return;
         // 4096 rows: those that begin in the part in which the first of them does, and behind the first 4096 that do
-        const int64_t r0 = (int64_t)blockIdx.x * kCompactRows, at0 = clamped(a, r0);
+        const int64_t r0 = ((int64_t)blockIdx.x - teller) * kCompactRows, at0 = clamped(a, r0);
         // (the end of the arrays belongs to the last chunk's last part)
         const int64_t chunk = min(at0 / a.chunk, (int64_t)a.chunks - 1), c0 = chunk * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
         const int64_t parts = max((c1 - c0 + kCompactPart - 1) / kCompactPart, (int64_t)1);
@@ -222,7 +293,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
         const bool rest = chunk == a.chunks - 1 && part == parts - 1;
         const int64_t from = (begin == 0 ? 0 : first_row_from(a.row_ptr, a.rows, begin)) + kCompactRows;
         if (from >= r0 + kCompactRows || descends) return;
-        int64_t base = before[chunk];
+        int64_t base = a.counts ? sum_counts(a.counts, checks + (int)chunk, s_wave, s_found).survivors : before[chunk];
         float v[16];
         unsigned long long word;
         uint32_t prefix, all;
@@ -248,7 +319,17 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
     }
     const int64_t c0 = (int64_t)b * a.chunk, c1 = min(c0 + a.chunk, a.nnz);
     const bool last_chunk = b == a.chunks - 1;
-    int64_t base = before[b];
+    // (before the part is requested: beside it, the registers of the sums cost a wave per SIMD)
+    int64_t base;
+    bool descends;
+    if (a.counts) {
+        const CountSum sum = sum_counts(a.counts, checks + b, s_wave, s_found);
+        base = sum.survivors;
+        descends = sum.found & 1;
+    } else {
+        base = before[b];
+        descends = uniform_load(before + a.chunks) & 1;
+    }
     int64_t row = c0 == 0 ? 0 : first_row_from(a.row_ptr, a.rows, c0);
     for (int64_t begin = c0; begin < c1 || begin == c0; begin += kCompactPart) {
         const int64_t end = min(begin + kCompactPart, c1);
@@ -266,8 +347,8 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
             const int w = u * (kCompactThreads / 64) + wave;
             const unsigned long long m = __ballot(survives(v[u]));
             const int first = __builtin_amdgcn_readlane((int)prefix, __builtin_amdgcn_readfirstlane(w));
-            if (survives(v[u])) {
-                const int64_t p = base + first + __popcll(m & ((1ull << lane) - 1ull));
+            const int64_t p = base + first + __popcll(m & ((1ull << lane) - 1ull));
+            if (survives(v[u]) && p < a.capacity) {
                 out_col[p] = c[u];
                 out_val[p] = v[u];
             }
@@ -328,16 +409,31 @@ __global__ __launch_bounds__(256) void k_compact_row_ptr(int64_t *__restrict__ r
 template <typename RP>
 static CompactArgs<RP> compact_args(const tsp_csr *C) {
     return {static_cast<const RP *>(C->row_ptr), C->col_idx, static_cast<const float *>(C->val), C->rows, C->nnz, C->rows,
-            compact_chunk(C->nnz), (int)compact_chunks(C->nnz)};
+            compact_chunk(C->nnz), (int)compact_chunks(C->nnz), nullptr, C->nnz};
 }
+// Blocks of the counting pass; whether those of the copying pass add up their counts
+template <typename RP>
+static int64_t count_blocks(const CompactArgs<RP> &a) { return a.row_blocks(kCheckRows) + a.chunks; }
+template <typename RP>
+static bool sums_in_copy(const CompactArgs<RP> &a) { return count_blocks(a) <= kCompactSums; }
 template <typename RP>
 static dim3 compact_grid(const CompactArgs<RP> &a, int rows_per_block) {
     return dim3((unsigned)(a.chunks + a.row_blocks(rows_per_block)));
 }
 template <typename RP>
-static void compact_launch(tsp_context *ctx, const CompactArgs<RP> &a, uint32_t *count, int64_t *before, hipStream_t s) {
+static void compact_copy(tsp_context *ctx, const CompactArgs<RP> &a, const int64_t *before, int64_t *row_ptr, int32_t *col, float *val, bool tell,
+                         hipStream_t s) {
+    hipLaunchKernelGGL(k_compact_fill<RP>, dim3((unsigned)((a.counts ? 1 : 0) + a.row_blocks(kCompactRows) + a.chunks)), dim3(kCompactThreads), 0, s, a,
+                       before, row_ptr, col, val, ctx->d_scalars, ctx->h_scalars_dev, tell ? ++ctx->publish_tag : (int64_t)0);
+}
+// The counts, and where no copying pass behind them does it, the sums and the total to the host
+template <typename RP>
+static void compact_launch(tsp_context *ctx, const CompactArgs<RP> &a, uint32_t *count, int64_t *before, bool copy_tells, hipStream_t s) {
     hipLaunchKernelGGL(k_compact_count<RP>, compact_grid(a, kCheckRows), dim3(kCompactThreads), 0, s, a, count, before, ctx->d_scalars);
-    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, s, count, a.chunks, before, ctx->d_scalars, ctx->h_scalars_dev,
+    if (a.counts && copy_tells) return;
+    if (a.counts) hipLaunchKernelGGL(k_compact_fill<RP>, dim3(1), dim3(kCompactThreads), 0, s, a, before, (int64_t *)nullptr, (int32_t *)nullptr,
+                                     (float *)nullptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag);
+    else hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, s, count, a.chunks, before, ctx->d_scalars, ctx->h_scalars_dev,
                        ++ctx->publish_tag);
 }
 // The pass again for a matrix whose row pointers go down, with ascending ones in `row_ptr`: the counts, for which it waits.
@@ -345,21 +441,21 @@ template <typename RP>
 static int compact_descending(tsp_context *ctx, const CompactArgs<RP> &a, int64_t *row_ptr, uint32_t *count, int64_t *before,
                               CompactArgs<int64_t> *again, hipStream_t s) {
     hipLaunchKernelGGL(k_compact_ascending<RP>, dim3(1), dim3(1024), 0, s, a, row_ptr);
-    *again = {row_ptr, a.col, a.val, -1, a.nnz, a.rows, a.chunk, a.chunks};
-    compact_launch(ctx, *again, count, before, s);
+    *again = {row_ptr, a.col, a.val, -1, a.nnz, a.rows, a.chunk, a.chunks, nullptr, a.nnz};
+    compact_launch(ctx, *again, count, before, false, s);
     TSP_HIP_CHECK(ctx, hipGetLastError());
     return wait_published_scalars(ctx, ctx->publish_tag, s);
 }
-static void compact_descending_fill(const CompactArgs<int64_t> &a, const int64_t *before, int64_t *row_ptr, int32_t *col, float *val, hipStream_t s) {
-    hipLaunchKernelGGL(k_compact_fill<int64_t>, compact_grid(a, kCompactRows), dim3(kCompactThreads), 0, s, a, before, row_ptr, col, val);
+static void compact_descending_fill(tsp_context *ctx, const CompactArgs<int64_t> &a, const int64_t *before, int64_t *row_ptr, int32_t *col, float *val, hipStream_t s) {
+    compact_copy(ctx, a, before, row_ptr, col, val, false, s);
     hipLaunchKernelGGL(k_compact_row_ptr, dim3((unsigned)((a.last + 4) / 4)), dim3(256), 0, s, row_ptr, a.last, a.val, a.chunk,
                        a.chunks, before);
 }
 
 template <typename RP>
 static int compact_run(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStream_t s, bool *taken) {
-    const CompactArgs<RP> a = compact_args<RP>(C);
-    uint32_t *count = ctx_alloc_n<uint32_t>(ctx, (size_t)a.chunks, s);
+    CompactArgs<RP> a = compact_args<RP>(C);
+    uint32_t *count = ctx_alloc_n<uint32_t>(ctx, (size_t)count_blocks(a) + 3, s);      // (read four at a time)
     int64_t *before = ctx_alloc_n<int64_t>(ctx, (size_t)a.chunks + 3, s);
     int64_t *new_row_ptr = nullptr;
     int32_t *col = nullptr;
@@ -373,12 +469,39 @@ static int compact_run(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStre
         return code;
     };
     if (!count || !before) return fail(TSP_ERR_ALLOC_FAILED);
-    compact_launch(ctx, a, count, before, s);
+    if (sums_in_copy(a)) a.counts = reinterpret_cast<const uint16_t *>(count);
+    // Without waiting for the new nnz, into arrays for as many entries as the last matrix of these sizes had left and some more, where it
+    // was to be copied
+    CompactHint &hint = ctx->compact_hints.find({{C->rows, C->nnz, C->cols, 0, 0, 0}}, [](CompactHint &) {});
+    const int64_t expected = std::min(hint.nnz + hint.nnz / 16, C->nnz);
+    bool ahead = a.counts && hint.nnz >= 0 && !(taken && hint.nnz == C->nnz);
+    auto allocate_result = [&](int64_t entries) {
+        if (!new_row_ptr) new_row_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)C->rows + 1, s);
+        col = ctx_alloc_n<int32_t>(ctx, (size_t)entries, s);
+        val = ctx_alloc_n<float>(ctx, (size_t)entries, s);
+        return new_row_ptr && col && val;
+    };
+    auto drop_result = [&]() {
+        for (auto p : {(void **)&new_row_ptr, (void **)&col, (void **)&val}) {
+            ctx_free(ctx, *p, s);
+            *p = nullptr;
+        }
+        ahead = false;
+    };
+    if (ahead && !allocate_result(expected)) drop_result();
+    compact_launch(ctx, a, count, before, ahead, s);
+    if (ahead) {
+        CompactArgs<RP> bounded = a;
+        bounded.capacity = expected;
+        compact_copy(ctx, bounded, before, new_row_ptr, col, val, true, s);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(hip_fail(ctx, e));
     int rc = wait_published_scalars(ctx, ctx->publish_tag, s);            // host synchronisation: the new nnz
     if (rc) return fail(rc);
     const bool descends = ctx->h_scalars[S_DESCENDS] != 0;
+    hint.nnz = ctx->h_scalars[S_C_NNZ];
+    if (ahead && (descends || hint.nnz > expected || (taken && hint.nnz == C->nnz))) drop_result();
     CompactArgs<int64_t> again{};
     if (descends) {
         new_row_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)C->rows + 1, s);
@@ -392,14 +515,13 @@ static int compact_run(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStre
         *taken = true;
         return TSP_OK;
     }
-    if (!new_row_ptr) new_row_ptr = ctx_alloc_n<int64_t>(ctx, (size_t)C->rows + 1, s);
-    col = ctx_alloc_n<int32_t>(ctx, (size_t)nnz, s);
-    val = ctx_alloc_n<float>(ctx, (size_t)nnz, s);
-    if (!new_row_ptr || !col || !val) return fail(TSP_ERR_ALLOC_FAILED);
-    if (descends) compact_descending_fill(again, before, new_row_ptr, col, val, s);
-    else hipLaunchKernelGGL(k_compact_fill<RP>, compact_grid(a, kCompactRows), dim3(kCompactThreads), 0, s, a, before, new_row_ptr, col, val);
-    e = hipGetLastError();
-    if (e != hipSuccess) return fail(hip_fail(ctx, e));
+    if (!ahead) {
+        if (!allocate_result(nnz)) return fail(TSP_ERR_ALLOC_FAILED);
+        if (descends) compact_descending_fill(ctx, again, before, new_row_ptr, col, val, s);
+        else compact_copy(ctx, a, before, new_row_ptr, col, val, false, s);
+        e = hipGetLastError();
+        if (e != hipSuccess) return fail(hip_fail(ctx, e));
+    }
     ctx_free(ctx, count, s);
     ctx_free(ctx, before, s);
     out->rows = C->rows;
@@ -462,12 +584,13 @@ static int compact_run_static(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, 
     if (rc) return rc;
     int64_t *before = reinterpret_cast<int64_t *>(base);
     uint32_t *count = reinterpret_cast<uint32_t *>(base + kStaticBeforeBytes);
-    const CompactArgs<RP> a = compact_args<RP>(C);
+    CompactArgs<RP> a = compact_args<RP>(C);
+    if (sums_in_copy(a)) a.counts = reinterpret_cast<const uint16_t *>(count);
     int64_t *const new_row_ptr = static_cast<int64_t *>(out->row_ptr);
     float *const val = static_cast<float *>(out->val);
     // (nothing in the scratch array has to start at zero; the copy does not wait for the host)
-    compact_launch(ctx, a, count, before, s);
-    hipLaunchKernelGGL(k_compact_fill<RP>, compact_grid(a, kCompactRows), dim3(kCompactThreads), 0, s, a, before, new_row_ptr, out->col_idx, val);
+    compact_launch(ctx, a, count, before, true, s);
+    compact_copy(ctx, a, before, new_row_ptr, out->col_idx, val, a.counts != nullptr, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e);
     rc = wait_published_scalars(ctx, ctx->publish_tag, s);       // host synchronisation: the new nnz
@@ -476,7 +599,7 @@ static int compact_run_static(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, 
         CompactArgs<int64_t> again{};
         rc = compact_descending(ctx, a, new_row_ptr, count, before, &again, s);
         if (rc) return rc;
-        compact_descending_fill(again, before, new_row_ptr, out->col_idx, val, s);
+        compact_descending_fill(ctx, again, before, new_row_ptr, out->col_idx, val, s);
         TSP_HIP_CHECK(ctx, hipGetLastError());
     }
     const int64_t nnz = ctx->h_scalars[S_C_NNZ];

@@ -94,3 +94,63 @@ def test_row_pointers_that_go_down(tsp, i64, seed):
         p[int(rng.integers(0, len(p)))] = int(rng.choice([-far, far, 0, nnz, int(rng.integers(0, nnz)), -1, nnz + 1]))
     _check(tsp, "pointers that go down", p, nnz, i64, seed)
     _check(tsp, "negative and none", [-5, -7, 0, 0], 2 * PART, i64)
+
+
+@pytest.mark.parametrize("nnz", [0, 1, PART - 1, PART, PART + 1, 64 * PART, 70 * PART + 3, 200 * PART + 1])
+def test_matrices_of_sizes_met_before(tsp, nnz):
+    """One handle and one size: few zeros and many, none and nothing else, rows of all kinds, row pointers that go down; each into
+    arrays sized after the matrix before it, and without allocation.  As many parts as a group of blocks, fewer and more."""
+    import torch
+    rows, rng = 2 * ROWS + 77, np.random.default_rng(nnz)
+
+    def pointers(lengths):
+        return np.concatenate([[0], np.sort(rng.integers(0, nnz + 1, rows - 1)) if lengths is None else np.minimum(np.cumsum(lengths)[:-1], nnz), [nnz]])
+
+    spread = pointers(None)
+    down = spread.copy()
+    down[rows // 2] = 0
+    run = pointers(np.where(np.arange(rows) < rows // 3, 0, 3 * nnz // rows + 1))
+    h = tsp.Handle()
+    try:
+        for what, share, p in (("first", 0.3, spread), ("as many", 0.3, spread), ("fewer zeros", 0.1, spread), ("more", 0.8, spread), ("none", 0.0, spread),
+                               ("none again", 0.0, spread), ("some", 0.2, run), ("a run of empty rows", 0.2, run), ("down", 0.2, down), ("all", 1.0, run),
+                               ("after all", 0.5, spread), ("at last", 0.5, spread)):
+            val = np.where(rng.random(nnz) < share, 0.0, rng.uniform(0.5, 1, nnz)).astype(np.float32)
+            col = np.arange(nnz, dtype=np.int32)
+            want = _expected(p, col, val)
+            dev = [torch.from_numpy(x).cuda() for x in (p.astype(np.int64), col, val)]
+            A = tsp.DeviceCSR(rows, max(nnz, 1), *dev)
+            C = h.compact_zeros(A)
+            out = [torch.full((rows + 1,), -7, dtype=torch.int64, device="cuda"), torch.full((max(nnz, 1),), -7, dtype=torch.int32, device="cuda"),
+                   torch.full((max(nnz, 1),), -7.0, dtype=torch.float32, device="cuda")]
+            n = h.compact_zeros_static(A, *out)
+            assert n == C.nnz == want[2].size, what
+            for got in (C.to_host(), [out[0].cpu().numpy(), out[1][:n].cpu().numpy(), out[2][:n].cpu().numpy()]):
+                for x, y in zip(got, want):
+                    assert np.array_equal(x, y), what
+            assert not nnz or bool((out[1][n:] == -7).all()) and bool((out[2][n:] == -7.0).all()), what    # (nothing behind them)
+            C.free()
+    finally:
+        h.close()
+
+
+@pytest.mark.parametrize("parts", [16384 - 2, 16384 - 1, 16384])
+def test_as_many_parts_as_the_copying_blocks_add_up(tsp, parts):
+    """Either side of the number of counts (one of them of the rows) that the copying blocks add up themselves; the second time into
+    arrays sized after the first."""
+    import torch
+    nnz = parts * PART - 7
+    col = torch.arange(nnz, dtype=torch.int32, device="cuda")
+    row_ptr = torch.tensor([0, nnz // 3, nnz], device="cuda")
+    h = tsp.Handle()
+    try:
+        for every in (3, 3, 2):
+            val = (col % every != 0).float()
+            keep = torch.nonzero(val).flatten().int()
+            C = h.compact_zeros(tsp.DeviceCSR(2, nnz, row_ptr, col, val))
+            assert C.nnz == keep.numel()
+            assert torch.equal(C.col_idx[:C.nnz], keep) and bool((C.val[:C.nnz] == 1).all())
+            assert C.row_ptr.tolist() == [0, int((val[:nnz // 3] != 0).sum()), keep.numel()]
+            C.free()
+    finally:
+        h.close()
