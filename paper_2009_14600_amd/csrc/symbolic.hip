@@ -1305,6 +1305,25 @@ __device__ __forceinline__ ListBefore sums_before(const ListSizing &sizing, int 
     static_assert(kListSlots * kListCap < INT32_MAX, "the sums are of 32 bits");
     return {wave_sum(tiles), wave_sum(pairs)};   // (of all tile-rows at most kListSlots * kListCap)
 }
+// First word of a bitmap that is not zero and how many there are from it to the last such, by a wave (of up to 64 words all)
+__device__ __forceinline__ int2 words_used(const uint32_t *bm, int words, int lane) {
+    if (words <= 64) return make_int2(0, words);
+    int first = INT_MAX, last = -1;
+    for (int w0 = lane; w0 < words; w0 += 4 * 64) {              // (four reads in flight)
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = bm[min(w0 + 64 * u, words - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (v[u]) {
+                first = min(first, min(w0 + 64 * u, words - 1));
+                last = min(w0 + 64 * u, words - 1);
+            }
+    }
+    first = -wave_max(-first);
+    last = wave_max(last);
+    return last < 0 ? make_int2(0, 0) : make_int2(first, last - first + 1);
+}
 __global__ __launch_bounds__(256) void k_clear_list_slots(unsigned long long *slots) {
     const int i = (int)blockIdx.x * 256 + threadIdx.x;
     if (i < kListSlotWords) slots[i] = 0;
@@ -1399,39 +1418,31 @@ __global__ __launch_bounds__(kBlockListThreads, 6) void k_sym_emit_block(
         }
     }
     __syncthreads();
-    // C tiles before every word, each wave for itself
-    const int stretch_words = (words + 63) >> 6;
+    // C tiles before every word, each wave for itself (a stretch of the words to a lane)
+    const int2 used = kSizes ? words_used(bm, words, lane) : make_int2(0, words);
+    const int first_word = used.x, end_word = used.x + used.y, stretch_words = (used.y + 63) >> 6;
     {
         uint32_t mine = 0;
-        for (int i = 0; i < stretch_words; i += 4) {         // (four reads in flight)
-            uint32_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = bm[min(lane * stretch_words + i + u, words - 1)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) mine += i + u < stretch_words && lane * stretch_words + i + u < words ? (uint32_t)__popc(v[u]) : 0u;
+        for (int i = 0; i < stretch_words; ++i) {
+            const int w = first_word + lane * stretch_words + i;
+            mine += w < end_word ? (uint32_t)__popc(bm[w]) : 0u;
         }
         const uint32_t inc = wave_inclusive_scan(mine);
         uint32_t before = inc - mine;
         if constexpr (kSizes) nC = __builtin_amdgcn_readlane((int)inc, 63);
-        for (int i = 0; i < stretch_words; i += 4) {
-            uint32_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = bm[min(lane * stretch_words + i + u, words - 1)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int w = lane * stretch_words + i + u;
-                if (i + u >= stretch_words || w >= words) break;
-                wpre[w] = before;
-                before += (uint32_t)__popc(v[u]);
-            }
+        for (int i = 0; i < stretch_words; ++i) {
+            const int w = first_word + lane * stretch_words + i;
+            if (w >= end_word) break;
+            wpre[w] = before;
+            before += (uint32_t)__popc(bm[w]);
         }
         wave_sync();
     }
     // ... and their coordinates, ascending J
     auto list_tiles = [&]() {
         for (int i = 0; i < stretch_words; ++i) {
-            const int w = lane * stretch_words + i;
-            if (w >= words) break;
+            const int w = first_word + lane * stretch_words + i;
+            if (w >= end_word) break;
             if ((lane & (kThreads / 64 - 1)) == wave) {
                 int c = c0 + (int)wpre[w];
                 for (uint32_t left = bm[w]; left; left &= left - 1, ++c) {
@@ -1442,7 +1453,7 @@ __global__ __launch_bounds__(kBlockListThreads, 6) void k_sym_emit_block(
         }
     };
     if constexpr (kSizes) {
-        pairs = s_sum[0][0] + s_sum[0][1];
+        pairs = (uint32_t)__builtin_amdgcn_readfirstlane((int)(s_sum[0][0] + s_sum[0][1]));
         static_assert(kThreads == 128, "two waves");
         fits = fits && nC <= window && pairs <= (uint32_t)kListCap;
         if (wave == 0) {
@@ -1538,8 +1549,8 @@ __global__ __launch_bounds__(kBlockListThreads, 6) void k_sym_emit_block(
             s_sum[1][wave] = sums.pairs;
         }
         __syncthreads();
-        c0 = (int)(s_sum[0][0] + s_sum[0][1]);
-        row_base = (int64_t)s_sum[1][0] + s_sum[1][1];
+        c0 = __builtin_amdgcn_readfirstlane((int)(s_sum[0][0] + s_sum[0][1]));
+        row_base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(s_sum[1][0] + s_sum[1][1]));
         const bool last = I == A.tile_rows - 1;
         if (tid == 0) {
             sizing.c_tile_row_ptr[I] = c0;
@@ -1685,23 +1696,21 @@ __global__ __launch_bounds__(64 * kFewWaves, 8) void k_sym_emit_few(
         n += __popcll(all);
     }
     wave_sync();
-    const int stretch_words = (words + 63) >> 6;
+    const int2 used = words_used(bm, words, lane);
+    const int first_word = used.x, end_word = used.x + used.y, stretch_words = (used.y + 63) >> 6;
     int nC = 0;
     {
         uint32_t mine = 0;
-        for (int i = 0; i < stretch_words; i += 4) {             // (four reads in flight)
-            uint32_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = bm[min(lane * stretch_words + i + u, words - 1)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) mine += i + u < stretch_words && lane * stretch_words + i + u < words ? (uint32_t)__popc(v[u]) : 0u;
+        for (int i = 0; i < stretch_words; ++i) {
+            const int w = first_word + lane * stretch_words + i;
+            mine += w < end_word ? (uint32_t)__popc(bm[w]) : 0u;
         }
         const uint32_t inc = wave_inclusive_scan(mine);
         uint32_t before = inc - mine;
         nC = __builtin_amdgcn_readlane((int)inc, 63);
         for (int i = 0; i < stretch_words; ++i) {
-            const int w = lane * stretch_words + i;
-            if (w >= words) break;
+            const int w = first_word + lane * stretch_words + i;
+            if (w >= end_word) break;
             wpre[w] = before;
             before += (uint32_t)__popc(bm[w]);
         }
@@ -1763,7 +1772,7 @@ __global__ __launch_bounds__(64 * kFewWaves, 8) void k_sym_emit_few(
     }
     wave_sync();
     // C tiles, ascending J, and the pairs before each
-    for (int w = lane; w < words; w += 64) {
+    for (int w = first_word + lane; w < end_word; w += 64) {
         int c = c0 + (int)wpre[w];
         for (uint32_t left = bm[w]; left; left &= left - 1, ++c) {
             c_tile_row[c] = I;
