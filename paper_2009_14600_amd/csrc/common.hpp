@@ -18,7 +18,8 @@ constexpr int kScalars = 32;        // device/host scalar slots of a handle
 // counters of groups of blocks (k_row_given), each in a line of its own
 constexpr int kArriveCounters = 1024, kArriveStride = 16;
 // slots of tile-rows and of groups of 64 of them (k_sym_emit_block)
-constexpr int kListSlots = 32768, kListSlotWords = kListSlots + kListSlots / 64;
+constexpr int kListSlots = 32768, kListPartials = 256 * 16;         // ... and of the blocks of k_row_ptr
+constexpr int kListSlotWords = kListSlots + kListSlots / 64 + kListPartials;
 
 // Slots of the handle's device scalar block (int64 each).
 enum Scalar {

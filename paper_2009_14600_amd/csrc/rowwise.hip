@@ -2393,9 +2393,11 @@ void launch_prepare(const PrepareArgs<RP, VT> &a, bool long_rows, hipStream_t s)
         auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)tile_rows), dim3(threads), (size_t)a.bitmap_words * 4, s, a, NoSecond{}); };
         // The longest tile-row, 3 ns per entry with 256 threads, keeps the launch waiting, where the last product of these sizes
         // had long rows: R-MAT scales 14 / 16 / 18 by 256 threads 64 / 197 / 515 us, by 512 43 / 120 / 345, by 1024 28 / 96 / 437.
+        // (By 1024 with one, two and four entries of a thread in flight: scale 13 14.8 / 16.3 / 15.3, 14 27.4 / 30.1 / 28.5, 15 38.8 /
+        // 41.5 / 43.4, 16 81 / 84 / 94: it is the instructions of one CU that bind.)
         // (Even rows, 80,000 of 12 entries: 20, 30, 38.)
         if (!long_rows) launch(k_row_prepare<256, 4, RP, VT>, 256);
-        else if (tile_rows <= 4096) launch(k_row_prepare<1024, 2, RP, VT>, 1024);
+        else if (tile_rows <= 4096) launch(k_row_prepare<1024, 1, RP, VT>, 1024);
         else launch(k_row_prepare<512, 4, RP, VT>, 512);
     }
 }

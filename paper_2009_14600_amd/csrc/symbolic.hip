@@ -1897,7 +1897,7 @@ __global__ __launch_bounds__(256) void k_count_masks(int64_t c_tiles, const int6
 // entries of the tile-rows before them and scans its own rows.  The last block has read every
 // tile-row and also leaves nnz(C) and the largest tile-row.
 // kSizes: behind k_sym_emit_block of the same kind.  Every block adds up what that has left of its own tile-rows (and its share of B's),
-// and the last one to do so hands all sizes over (8192 tile-rows: 9.5 us instead of 5.8, and 8.2 for k_sym_row_scan that there is not).
+// and the last block waits for all of them and hands the sizes over (at most kMaxChunks blocks, all on the chip at once).
 enum { kListTilesC, kListPairs, kListCandidates, kListEntries, kListTilesA, kListTilesB, kListSums, kListMostTiles = kListSums, kListMostPairs, kListMostATiles,
        kListMostEntries, kListParts };
 struct ListSums {
@@ -1905,7 +1905,8 @@ struct ListSums {
     const int32_t *a_trp, *a_tend, *b_trp, *b_tend;          // null: the host knows the tiles of that operand
     int64_t b_tile_rows;
     int a_slot, b_slot;
-    uint32_t *partial;                   // [blocks][16]
+    unsigned long long *partial;         // [blocks][16]: {call, number}, the last block waits for them
+    uint32_t call;
 };
 template <bool kSizes>
 __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row_nnz, int64_t c_rows,
@@ -1916,7 +1917,7 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
     __shared__ int64_t own[kScalars];
     constexpr int kItems = kChunkRows / 256;
     const bool last = blockIdx.x == gridDim.x - 1;
-    int64_t standing = !kSizes && last ? standing_scalar(d_scalars) : 0;
+    const int64_t standing = last ? standing_scalar(d_scalars) : 0;
     const int64_t tile_rows_before = (int64_t)blockIdx.x * kChunkTileRows;
     // the block's own row lengths, requested first: they travel while the tile-rows before are added up
     const int64_t base = (int64_t)blockIdx.x * kChunkRows + (int64_t)threadIdx.x * kItems;
@@ -1945,6 +1946,19 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
         if (sums.b_trp)
             for (int64_t K = (int64_t)blockIdx.x * 256 + threadIdx.x; K < sums.b_tile_rows; K += (int64_t)gridDim.x * 256)
                 sum[kListTilesB] += (uint32_t)(sums.b_tend[K] - sums.b_trp[K]);
+        __shared__ uint32_t s_part[4][kListParts];
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int i = 0; i < kListParts; ++i) {
+            const uint32_t v = i < kListSums ? wave_sum(sum[i]) : (uint32_t)wave_max((int)sum[i]);
+            if (lane == 0) s_part[wave][i] = v;
+        }
+        __syncthreads();
+        if (threadIdx.x < kListParts) {
+            const uint32_t a = s_part[0][threadIdx.x], b = s_part[1][threadIdx.x], c = s_part[2][threadIdx.x], d = s_part[3][threadIdx.x];
+            const uint32_t all = threadIdx.x < kListSums ? a + b + c + d : max(max(a, b), max(c, d));
+            __hip_atomic_store(sums.partial + blockIdx.x * 16 + threadIdx.x, (unsigned long long)sums.call << 34 | all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     for (int64_t q0 = threadIdx.x; q0 < quads; q0 += 4 * 256) {
         uint4 e[4];
@@ -1975,40 +1989,30 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
         run += (uint32_t)x[i];
     }
     if constexpr (kSizes) {
-        __shared__ uint32_t s_part[4][kListParts];
-        __shared__ int s_last;
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int i = 0; i < kListParts; ++i) {
-            const uint32_t v = i < kListSums ? wave_sum(sum[i]) : (uint32_t)wave_max((int)sum[i]);
-            if (lane == 0) s_part[wave][i] = v;
-        }
-        __syncthreads();
-        if (threadIdx.x < kListParts) {
-            const uint32_t a = s_part[0][threadIdx.x], b = s_part[1][threadIdx.x], c = s_part[2][threadIdx.x], d = s_part[3][threadIdx.x];
-            __hip_atomic_store(sums.partial + blockIdx.x * 16 + threadIdx.x, threadIdx.x < kListSums ? a + b + c + d : max(max(a, b), max(c, d)),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (the first wave's have arrived)
-        if (threadIdx.x == 0) s_last = atomicAdd(reinterpret_cast<unsigned long long *>(d_scalars + S_ROW_ARRIVED), 1ull) == gridDim.x - 1;
-        __syncthreads();
-        if (s_last) {
-            standing = standing_scalar(d_scalars);
+        __shared__ int64_t s_failed;
+        if (last) {
+            if (threadIdx.x == 0) s_failed = 0;
+            __syncthreads();
             // number i of all blocks: a lane of 16 per block, sixteen of them at a time, then the 16 that are left
             unsigned long long v = 0;
             const int i = threadIdx.x & 15;
             if (i < kListParts)
                 for (int b = threadIdx.x >> 4; b < (int)gridDim.x; b += 8 * 16) {      // (eight loads in flight)
-                    uint32_t x[8];
+                    unsigned long long x[8];
 #pragma unroll
                     for (int u = 0; u < 8; ++u)
-                        x[u] = b + 16 * u < (int)gridDim.x ? __hip_atomic_load(sums.partial + (b + 16 * u) * 16 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                        x[u] = b + 16 * u < (int)gridDim.x ? __hip_atomic_load(sums.partial + (b + 16 * u) * 16 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v = i < kListSums ? v + x[u] : max(v, (unsigned long long)x[u]);
+                    for (int u = 0; u < 8; ++u) {
+                        if (b + 16 * u >= (int)gridDim.x) continue;
+                        if ((uint32_t)(x[u] >> 34) != sums.call) x[u] = wait_slot(sums.partial + (b + 16 * u) * 16 + i, sums.call, &s_failed);
+                        const unsigned long long number = x[u] & ((1ull << 34) - 1ull);
+                        v = i < kListSums ? v + number : max(v, number);
+                    }
                 }
             __shared__ unsigned long long s_all[16][kListParts];
             if (i < kListParts) s_all[threadIdx.x >> 4][i] = v;
-            if (threadIdx.x < kScalars) own[threadIdx.x] = threadIdx.x == S_ROW_ARRIVED ? 0 : standing;
+            if (threadIdx.x < kScalars) own[threadIdx.x] = standing;
             __syncthreads();
             if (threadIdx.x < kListParts) {
                 const int at = threadIdx.x;
@@ -2022,6 +2026,7 @@ __global__ __launch_bounds__(256) void k_row_ptr(const int32_t *__restrict__ row
             }
             __syncthreads();
             if (threadIdx.x == 0) {
+                if (s_failed) own[S_INTERNAL] = 1;
                 c_row_ptr[c_rows] = own[S_C_NNZ];
                 if (live) {
                     live[0] = expected.holds(own);
@@ -2212,7 +2217,6 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     int64_t *row_pair_ptr = nullptr, *tmp = nullptr;
     int32_t *live = nullptr;
     uint4 *tile_row_info = nullptr;
-    uint32_t *partial = nullptr;
     auto drop_order = [&](ListHint &h) {
         ctx_free(ctx, h.order, s);
         h.order = nullptr;
@@ -2230,7 +2234,6 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         drop_ahead();
         ctx_free(ctx, live, s);
         ctx_free(ctx, tile_row_info, s);
-        ctx_free(ctx, partial, s);
         ctx_free(ctx, row_jmin, s);
         ctx_free(ctx, row_c_tiles, s);
         ctx_free(ctx, row_pairs, s);
@@ -2499,8 +2502,7 @@ list_kernels:
             ListSizing sizing{};
             if (fused_sizes) {
                 tile_row_info = ctx_alloc_n<uint4>(ctx, (size_t)ntr, s);
-                partial = ctx_alloc_n<uint32_t>(ctx, (size_t)n_chunks * 16, s);
-                if (!tile_row_info || !partial) return cleanup(TSP_ERR_ALLOC_FAILED);
+                if (!tile_row_info) return cleanup(TSP_ERR_ALLOC_FAILED);
                 if (ctx->list_call >= (1u << 30) - 1) {          // the numbers start again: no slot holds one
                     hipLaunchKernelGGL(k_clear_list_slots, dim3((kListSlotWords + 255) / 256), dim3(256), 0, s, ctx->d_list_slots);
                     ctx->list_call = 0;
@@ -2620,7 +2622,8 @@ list_kernels:
             if (fused_sizes) {
                 const bool count_a = A->ntiles < 0, count_b = B->ntiles < 0 && B != A;
                 sums = {tile_row_info, count_a ? A->tile_row_ptr : nullptr, count_a ? A->tile_row_end : nullptr,
-                        count_b ? B->tile_row_ptr : nullptr, count_b ? B->tile_row_end : nullptr, B->tile_rows, A->scalar_slot, B->scalar_slot, partial};
+                        count_b ? B->tile_row_ptr : nullptr, count_b ? B->tile_row_end : nullptr, B->tile_rows, A->scalar_slot, B->scalar_slot,
+                        ctx->d_list_slots + kListSlots + kListSlots / kListGroup, ctx->list_call};
             }
             hipLaunchKernelGGL(fused_sizes ? k_row_ptr<true> : k_row_ptr<false>, dim3((unsigned)n_chunks), dim3(256), 0, s, row_nnz, P->c_rows,
                                tile_row_entries, ntr, P->c_row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, true, expected, live, sums);
