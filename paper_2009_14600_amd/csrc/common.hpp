@@ -17,6 +17,8 @@ constexpr int T = 16;               // tile edge: one output tile = one 16x16 MF
 constexpr int kScalars = 32;        // device/host scalar slots of a handle
 // counters of groups of blocks (k_row_given), each in a line of its own
 constexpr int kArriveCounters = 1024, kArriveStride = 16;
+// tile-rows of A that have a tile in a tile column, for so many of those (k_row_given)
+constexpr int kTileCounts = 32768;
 // slots of tile-rows and of groups of 64 of them (k_sym_emit_block)
 constexpr int kListSlots = 32768, kListPartials = 256 * 16;         // ... and of the blocks of k_row_ptr
 constexpr int kListSlotWords = kListSlots + kListSlots / 64 + kListPartials;
@@ -125,6 +127,7 @@ struct RowHint {
     bool tiles = false;
     int64_t candidates = 0;                        // pairs of tiles, by which that was decided
     bool estimated = false;                        // ... from some of the tile-rows
+    int64_t a_tiles = 0;
     bool sample = true;                            // (a look at some of the tile-rows has not misled yet)
     int64_t heavy = 0, tasks = 0, large_tasks = 0;
     int64_t longest = 0;                           // entries of the longest heavy row of A
@@ -206,6 +209,7 @@ struct tsp_context {
     unsigned long long *d_list_slots = nullptr;    // device, kListSlotWords, by the number of the call that wrote them (behind those)
     uint32_t list_call = 0;
     tsp::HintMemory<tsp::CompactHint> compact_hints;
+    uint32_t *d_tile_counts = nullptr;             // device, kTileCounts, zero between launches (behind those)
     unsigned long long *d_arrivals = nullptr;      // device, kArriveCounters counters, zero between launches (behind the scalars)
     bool scalars_clean = false;                    // all zero: the last kernel of the previous call left them so
     int64_t *h_scalars = nullptr;                  // pinned host mirror

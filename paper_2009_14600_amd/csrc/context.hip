@@ -235,12 +235,13 @@ extern "C" int tsp_create(tsp_handle *handle, const tsp_allocator *allocator) {
     hipError_t e = hipGetDevice(&ctx->device);
     // (one slot behind the scalar block counts the words of guard zones found changed; no kernel clears it)
     constexpr size_t kArrivalsAt = 64, kListSlotsAt = kArrivalsAt + (size_t)kArriveCounters * kArriveStride,
-                     kDeviceWords = kListSlotsAt + kListSlotWords;
+                     kTileCountsAt = kListSlotsAt + kListSlotWords, kDeviceWords = kTileCountsAt + kTileCounts / 2;
     static_assert(kArrivalsAt > kScalars && kArrivalsAt % kArriveStride == 0, "behind the scalars and the count, lines of 128 bytes");
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->d_scalars, sizeof(int64_t) * kDeviceWords);
     if (e == hipSuccess) e = hipMemset(ctx->d_scalars, 0, sizeof(int64_t) * kDeviceWords);
     ctx->d_arrivals = reinterpret_cast<unsigned long long *>(ctx->d_scalars) + kArrivalsAt;
     ctx->d_list_slots = reinterpret_cast<unsigned long long *>(ctx->d_scalars) + kListSlotsAt;
+    ctx->d_tile_counts = reinterpret_cast<uint32_t *>(ctx->d_scalars + kTileCountsAt);
     if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->h_scalars, sizeof(int64_t) * kScalars,
                                              hipHostMallocCoherent | hipHostMallocMapped);   // polled: fine-grained whatever the environment says
     if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&ctx->h_scalars_dev, ctx->h_scalars, 0);

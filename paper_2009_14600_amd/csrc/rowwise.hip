@@ -1389,9 +1389,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // k_row_prepare.
 // Bound, as k_row_small is, by round trips and by how few waves there are to hide them while a launch begins and ends; so fewer
 // launches, with more of different kinds in each.  k_row_prepare, k_row_small and k_small_finish, one behind the other, against these
-// two: a 512 x 512 mesh 16.1 + 28.4 + 12.1 us and 36.7 + 12.8, 65,536 rows of 8 random entries 10.8 + 24.4 + 12.3 and 29.6 + 13.0,
-// A*P on a 64^3 grid 25.6 + 19.2 + 6.7 and 32.4 + 7.4; the products 56.4 -> 46.7, 47.3 -> 41.0, 58.5 -> 41.7, a 37 x 37 mesh 26.6 ->
-// 22.9, 1024 rows of 8 entries 27.0 -> 24.5.  Without the pairs of tiles 33.6, 24.3 and 28.3 us, but added up by blocks of the second
+// two: a 512 x 512 mesh 16.1 + 28.4 + 12.1 us and 36.0 + 12.7, 65,536 rows of 8 random entries 10.8 + 24.4 + 12.3 and 29.6 + 12.8,
+// A*P on a 64^3 grid 25.6 + 19.2 + 6.7 and 30.6 + 7.4; the products 56.4 -> 45.5, 47.3 -> 40.5, 58.5 -> 39.1, a 37 x 37 mesh 26.6 ->
+// 17.9, 1024 rows of 8 entries 27.0 -> 19.2.  The pairs of tiles from lists of A's tiles in every tile-row take three round trips, from
+// A's tiles in every tile column one (the choice: rowwise_given): 37 x 37 mesh 15.5 -> 9.7 us of the launch, 135 x 135 14.8 -> 13.0.  Without the pairs of tiles 33.6, 24.3 and 28.3 us, but added up by blocks of the second
 // launch they hand the sizes over so late that the GPU waits for the next call (58.3, 49.1, 53.6).  Blocks that count themselves with
 // an addition whose result they wait for, 38.4, 33.6 and 38.4 us; one block that looks at the counters needs no such wait.
 template <typename RP>
@@ -1400,13 +1401,16 @@ struct TileArgs {                        // of an operand
     const int32_t *col;
     int64_t rows, cols, nnz;
     int bitmap_words;
-    // of every tile-row: its first entry, its tiles, and their columns, from there on, in any order (null: they are not wanted)
-    int32_t *first, *ntiles, *tile_col;
+    int32_t *ntiles;                     // of every tile-row
+    // Of A: per tile column, how many tile-rows have a tile in it; or of every tile-row the first entry and, from there on, the columns of
+    // its tiles in any order (null: not wanted)
+    uint32_t *counts;
+    int32_t *first, *tile_col;
 };
 
 // A wave for `per_wave` (1 or 4) tile-rows, two entries per lane in flight and the next tile-row's first ones: k_row_prepare without
 // what is kept of the entries.  Other blocks of the launch read what it leaves.  The number of tiles of the wave's.
-template <typename RP>
+template <bool kCounts, typename RP>
 __device__ __forceinline__ int32_t count_tiles(const TileArgs<RP> &a, uint32_t block, int per_wave, bool validate, int64_t *d_scalars) {
     extern __shared__ __align__(16) unsigned char small_lds[];
     __shared__ uint32_t s_starts[4][4];  // of the entries of a trip, those that begin a row
@@ -1474,12 +1478,13 @@ __device__ __forceinline__ int32_t count_tiles(const TileArgs<RP> &a, uint32_t b
             for (int u = 0; u < 2; ++u) {
                 first[u] = first[u] & !((had[u] >> ((c[u] >> 4) & 31)) & 1u);
                 const unsigned long long firsts = __ballot(first[u]);
-                if (first[u] && a.tile_col) put_for(true, a.tile_col + e0 + listed + __popcll(firsts & ((1ull << lane) - 1ull)), c[u] >> 4);
+                if (kCounts && first[u] && a.counts) atomicAdd(a.counts + (c[u] >> 4), 1u);
+                if (!kCounts && first[u] && a.tile_col) put_for(true, a.tile_col + e0 + listed + __popcll(firsts & ((1ull << lane) - 1ull)), c[u] >> 4);
                 listed += __popcll(firsts);
             }
         }
         if (lane == 0) {
-            if (a.first) put_for(true, a.first + I0 + t, e0);
+            if (!kCounts && a.first) put_for(true, a.first + I0 + t, e0);
             put_for(true, a.ntiles + I0 + t, listed);
         }
         all += listed;
@@ -1520,12 +1525,14 @@ struct GivenPublishArgs {
     int32_t *live;                       // of k_small_copy, or null: whether it may run
     int same;                            // A and B are one matrix
 };
-// publish_scalars by one wave; `candidates` and `failed` beyond what stands in the scalar block
-__device__ __forceinline__ void publish_given(const GivenPublishArgs &a, int64_t entries, int64_t products, int64_t others, int64_t candidates, int64_t failed) {
+// publish_scalars by one wave; the numbers of tiles, `candidates` and `failed` beyond what stands in the scalar block
+__device__ __forceinline__ void publish_given(const GivenPublishArgs &a, int64_t entries, int64_t products, int64_t others, int64_t tiles_a, int64_t tiles_b,
+                                              int64_t candidates, int64_t failed) {
     const int lane = lane_id();
     int64_t v = 0;
     if (lane < kScalars) v = __hip_atomic_load(a.d_scalars + (a.same && lane == S_TILES_B ? (int)S_TILES_A : lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     v = lane == S_C_NNZ ? entries : lane == S_ROW_PRODUCTS ? products : lane == S_ROW_HEAVY ? others : lane == S_CANDIDATES ? v + candidates : lane == S_INTERNAL ? v + failed : v;
+    v += lane == S_TILES_A || (a.same && lane == S_TILES_B) ? tiles_a : lane == S_TILES_B ? tiles_b : 0;
     const bool invalid = __any((lane == S_INVALID || lane == S_INTERNAL) && v != 0);
     if (lane < kScalars) {
         const uint64_t slot = (publish_tag16(a.publish_tag) << kPublishTagShift) | ((uint64_t)v & ((1ull << kPublishTagShift) - 1u));
@@ -1538,6 +1545,8 @@ __device__ __forceinline__ void publish_given(const GivenPublishArgs &a, int64_t
     }
 }
 
+// B's tile-rows, of a product of one chunk of rows, up to which the last block has the pairs of tiles itself; otherwise other blocks do.
+constexpr int kPairsByOne = 4096;
 template <typename RP, typename VT>
 struct GivenArgs {
     SmallArgs small;
@@ -1554,10 +1563,32 @@ struct GivenArgs {
     GivenPublishArgs publish;
 };
 
+// The pairs of tiles: of every column A's tiles times the tiles of B's tile-row, 256 at a time, every `blocks`-th of those; the counts are
+// zero behind it.  The thread's share.
+template <typename RP, typename VT>
+__device__ __forceinline__ unsigned long long count_pairs(const GivenArgs<RP, VT> &a, uint32_t block, uint32_t blocks) {
+    unsigned long long pairs = 0;
+    const int64_t step = (int64_t)blocks * 256;
+    for (int64_t K0 = (int64_t)block * 256 + threadIdx.x; K0 < a.b_tile_rows; K0 += 4 * step) {
+        uint32_t of_a[4], of_b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t K = K0 + u * step;
+            of_a[u] = K < a.b_tile_rows ? get_shared<true>(a.a.counts + K) : 0u;
+            of_b[u] = K < a.b_tile_rows ? (uint32_t)get_shared<true>(a.b_ntiles + K) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            pairs += (unsigned long long)of_a[u] * of_b[u];
+            if (K0 + u * step < a.b_tile_rows) put_for(true, a.a.counts + K0 + u * step, 0u);
+        }
+    }
+    return pairs;
+}
 // The pairs of tiles of 16 tile-rows of A at a time, every `blocks`-th 16: 16 lanes to a tile-row, four tile-rows and of each 64
 // tiles in flight.  The thread's share.
 template <typename RP, typename VT>
-__device__ __forceinline__ unsigned long long count_pairs(const GivenArgs<RP, VT> &a, uint32_t block, uint32_t blocks) {
+__device__ __forceinline__ unsigned long long count_listed_pairs(const GivenArgs<RP, VT> &a, uint32_t block, uint32_t blocks) {
     const int r = threadIdx.x & 15;
     unsigned long long pairs = 0;
     for (int64_t base = (int64_t)block * 16 + (threadIdx.x >> 4); base < a.a_tile_rows; base += (int64_t)blocks * 64) {
@@ -1598,7 +1629,7 @@ __device__ __forceinline__ unsigned long long add_threads(unsigned long long v, 
     return s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
 }
 
-template <int G, bool kNarrow, typename RP, typename VT>
+template <int G, bool kNarrow, bool kCounts, typename RP, typename VT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_row_given(const GivenArgs<RP, VT> a) {
     __shared__ uint3 s_totals[4];
     __shared__ unsigned long long s_sum[4];
@@ -1608,14 +1639,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     if (blockIdx.x < tile_blocks) {
         const bool of_b = blockIdx.x >= a.a_blocks;
         const uint32_t block = blockIdx.x - (of_b ? a.a_blocks : 0u), blocks = of_b ? a.b_blocks : a.a_blocks;
-        const int32_t tiles = count_tiles(of_b ? a.b : a.a, block, a.per_wave, a.validate, d_scalars);
+        const int32_t tiles = count_tiles<kCounts>(of_b ? a.b : a.a, block, a.per_wave, a.validate, d_scalars);
         if (lane_id() == 0) s_totals[threadIdx.x >> 6].x = (uint32_t)tiles;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // what this wave has left for other blocks has arrived
         __syncthreads();
         if (threadIdx.x > 0) return;
-        // the last of its group tells the others
         unsigned long long *counter = a.counters + ((of_b ? arrive_groups(a.a_blocks) : 0u) + block / kArriveGroup) * kArriveStride;
         const unsigned long long mine = (unsigned long long)s_totals[0].x + s_totals[1].x + s_totals[2].x + s_totals[3].x;
+        if (kCounts && !a.pair_blocks) {                       // (the last block looks at the counters itself)
+            atomicAdd(counter, mine + (1ull << kArriveShift));
+            return;
+        }
+        // the last of its group tells the others
         const unsigned long long had = atomicAdd(counter, mine + (1ull << kArriveShift));
         if ((had >> kArriveShift) + 1 != arrive_blocks(block / kArriveGroup, blocks)) return;
         __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1646,19 +1681,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     }
     const bool last = at == a.row_blocks + a.pair_blocks;
     bool failed = false;
-    unsigned long long pairs = 0;
-    if (one_chunk || !last) {
+    unsigned long long pairs = 0, tiles_a = 0, tiles_b = 0;
+    if (!last) {
         if (threadIdx.x == 0) (void)wait_for(d_scalars + S_GIVEN_ARRIVED, [&](int64_t v) { return v == (int64_t)tile_groups; }, &failed);
         __syncthreads();
-        pairs = add_threads(count_pairs(a, one_chunk ? 0u : at - half, one_chunk ? 1u : a.pair_blocks), s_sum);
-        if (!one_chunk) {
-            if (threadIdx.x > 0) return;
-            (void)add_scalar(d_scalars, S_CANDIDATES, pairs);
-            if (failed) (void)add_scalar(d_scalars, S_INTERNAL, 1);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            (void)add_scalar(d_scalars, S_ROW_ARRIVED, 1);
-            return;
+        pairs = add_threads(kCounts ? count_pairs(a, at - half, a.pair_blocks) : count_listed_pairs(a, at - half, a.pair_blocks), s_sum);
+        if (threadIdx.x > 0) return;
+        (void)add_scalar(d_scalars, S_CANDIDATES, pairs);
+        if (failed) (void)add_scalar(d_scalars, S_INTERNAL, 1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        (void)add_scalar(d_scalars, S_ROW_ARRIVED, 1);
+        return;
+    }
+    if (kCounts && !a.pair_blocks) {
+        static_assert(arrive_groups(kChunkTileRows / 4) + arrive_groups(kPairsByOne / 4) <= 64, "the first wave has them all");
+        const uint32_t a_groups = arrive_groups(a.a_blocks);
+        if (threadIdx.x < 64) {
+            unsigned long long tiles = 0;
+            if (threadIdx.x < tile_groups) {
+                const bool of_b = threadIdx.x >= a_groups;
+                unsigned long long *counter = a.counters + threadIdx.x * kArriveStride;
+                const unsigned long long want = arrive_blocks(of_b ? threadIdx.x - a_groups : threadIdx.x, of_b ? a.b_blocks : a.a_blocks);
+                tiles = wait_for(counter, [&](unsigned long long v) { return (v >> kArriveShift) == want; }, &failed) & kArriveSum;
+                __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            tiles_a = wave_sum(threadIdx.x < a_groups ? (uint32_t)tiles : 0u);
+            tiles_b = wave_sum(threadIdx.x < a_groups ? 0u : (uint32_t)tiles);
         }
+        __syncthreads();
+        pairs = add_threads(count_pairs(a, 0u, 1u), s_sum);
     }
     // the last block: the groups of blocks of rows, and the other blocks of pairs
     unsigned long long sum = 0;
@@ -1667,7 +1718,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         sum = wait_for(counter, [&](unsigned long long v) { return (v >> kArriveShift) == arrive_blocks(threadIdx.x, a.row_blocks); }, &failed);
         __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (threadIdx.x == 0) (void)wait_for(d_scalars + S_ROW_ARRIVED, [&](int64_t v) { return v == (int64_t)a.pair_blocks; }, &failed);
+    if (threadIdx.x == 0 && a.pair_blocks) (void)wait_for(d_scalars + S_ROW_ARRIVED, [&](int64_t v) { return v == (int64_t)a.pair_blocks; }, &failed);
     const uint32_t of_wave[3] = {wave_sum((uint32_t)sum & 0xFFFFFu), wave_sum((uint32_t)(sum >> 20) & 0xFFFFFu), wave_sum((uint32_t)(sum >> 40) & 0xFFFFu)};
     const bool any_failed = __any(failed);
     if (lane_id() == 0) s_totals[threadIdx.x >> 6] = make_uint3(of_wave[0], of_wave[1], of_wave[2] | (any_failed ? 1u << 31 : 0u));
@@ -1680,7 +1731,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
             others += s_totals[w].z & 0x7FFFFFFFu;
             failures += s_totals[w].z >> 31;
         }
-        publish_given(a.publish, entries, products, others, (int64_t)pairs, failures);
+        publish_given(a.publish, entries, products, others, (int64_t)tiles_a, (int64_t)tiles_b, (int64_t)pairs, failures);
     }
     if (!one_chunk) return;
     // row_ptr of one chunk of rows
@@ -2528,7 +2579,11 @@ void launch_fill(FillArgs &f, FillKind kind, bool short_rows, bool split, hipStr
 __global__ void k_clear_lists(int64_t *d_scalars) {
     if (threadIdx.x == 0) d_scalars[S_ROW_LISTS] = d_scalars[S_ROW_LARGE_TASKS] = 0;
 }
-__global__ void k_clear_arrivals(unsigned long long *counters) { counters[(blockIdx.x * 256 + threadIdx.x) * kArriveStride] = 0; }
+__global__ void k_clear_arrivals(unsigned long long *counters, uint32_t *tile_counts) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    counters[i * kArriveStride] = 0;
+    for (int k = i; k < kTileCounts; k += kArriveCounters) tile_counts[k] = 0;
+}
 // all but the count of products, which has run before anything else of the call
 __global__ void k_clear_rows(int64_t *d_scalars, int64_t products) {
     if (threadIdx.x < kScalars) d_scalars[threadIdx.x] = threadIdx.x == S_PRODUCTS ? products : 0;
@@ -2647,6 +2702,7 @@ enum RowsEnd { kRowsNotTaken, kRowsTaken, kRowsAgain };     // (again: with othe
 constexpr int64_t kGivenBlocks = 16384;
 constexpr size_t kGivenBitmaps = 16 * 1024;
 constexpr int64_t kGivenRows = kGivenBlocks * 32, kGivenColumns = (int64_t)kGivenBitmaps / 16 * 32 * T;     // at most, of A
+static_assert(kGivenColumns <= (int64_t)kTileCounts * T, "a count for every tile column of A");
 static_assert(arrive_groups(kGivenBlocks) + arrive_groups(kGivenRows / T / 4) + arrive_groups(kGivenColumns / T / 4) <= kArriveCounters, "of the rows, the tiles of A and of B");
 template <typename RP, typename VT>
 static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, bool alias, tsp_csr *C, hipStream_t s, RowHint &hint,
@@ -2656,12 +2712,23 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     const bool one_chunk = A->rows <= kChunkRows;
     Workspace ws{ctx, s, {}};
     GivenArgs<RP, VT> a{};
+    // Counts of A's tiles in every tile column, where there are few of them (of the last product), or lists of them.  An addition is 0.11 ns
+    // of the launch, a list three round trips more before the pairs are known; a row is 0.14 to 0.45 ns.  us, lists and counts: 37^2 mesh
+    // (1.1 thousand tiles) 22.9 and 17.9, 1024 rows of 8 random entries (8 thousand) 24.7 and 19.2, A*P on 18^3 25.5 and 22.4, on 64^3 41.5
+    // and 39.5, 512^2 mesh (180 thousand) 46.6 and 44.9; 12,725 and 65,536 rows of 8 random entries (8 tiles to a row) 28.3 and 39.9, 40.8
+    // and 66.7.
+    const bool counts = hint.a_tiles <= std::max<int64_t>(A->rows, 24576);
     auto tiles_of = [&](const tsp_csr *M, int64_t ntr, bool left) {
-        TileArgs<RP> t{static_cast<const RP *>(M->row_ptr), M->col_idx, M->rows, M->cols, M->nnz, (int)((M->cols + T * 32 - 1) / (T * 32) + 3) & ~3, nullptr, nullptr, nullptr};
+        TileArgs<RP> t{static_cast<const RP *>(M->row_ptr), M->col_idx, M->rows, M->cols, M->nnz, (int)((M->cols + T * 32 - 1) / (T * 32) + 3) & ~3, nullptr, nullptr, nullptr, nullptr};
         t.ntiles = ws.get<int32_t>((size_t)ntr);
-        if (left) {
-            t.first = ws.get<int32_t>((size_t)ntr);
-            t.tile_col = ws.get<int32_t>((size_t)M->nnz);
+        if (left) {                          // (memory for the lists either way: which way a product goes does not say whether there is enough)
+            int32_t *const first = ws.get<int32_t>((size_t)ntr), *const tile_col = ws.get<int32_t>((size_t)M->nnz);
+            if (counts) {
+                t.counts = ctx->d_tile_counts;
+            } else {
+                t.first = first;
+                t.tile_col = tile_col;
+            }
         }
         return t;
     };
@@ -2677,7 +2744,8 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     a.b_tile_rows = b_ntr;
     a.b_ntiles = alias ? a.a.ntiles : a.b.ntiles;
     a.row_blocks = (uint32_t)row_blocks;
-    a.pair_blocks = one_chunk ? 0u : (uint32_t)std::min<int64_t>(kPlanBlocks, (a_ntr + 15) / 16);
+    a.pair_blocks = !counts ? (uint32_t)std::min<int64_t>(kPlanBlocks, (a_ntr + 15) / 16)
+                  : one_chunk && b_ntr <= kPairsByOne ? 0u : (uint32_t)std::min<int64_t>(kPlanBlocks, (b_ntr + 255) / 256);
     a.validate = ctx->validate;
     a.counters = ctx->d_arrivals;
     a.operands = {static_cast<const RP *>(A->row_ptr), static_cast<const RP *>(B->row_ptr), A->col_idx, B->col_idx, static_cast<const VT *>(A->val),
@@ -2702,9 +2770,15 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     {
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
         const size_t lds = std::max(4 * shape.wave_bytes() + SmallShape::kReadPast, (size_t)std::max(a.a.bitmap_words, a.b.bitmap_words) * 16);
-        auto kernel = shape.lanes == 8 ? (shape.narrow() ? k_row_given<8, true, RP, VT> : k_row_given<8, false, RP, VT>)
-                                       : (shape.narrow() ? k_row_given<16, true, RP, VT> : k_row_given<16, false, RP, VT>);
-        hipLaunchKernelGGL(kernel, dim3(a.a_blocks + a.b_blocks + a.row_blocks + a.pair_blocks + 1u), dim3(256), lds, s, a);
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.a_blocks + a.b_blocks + a.row_blocks + a.pair_blocks + 1u), dim3(256), lds, s, a); };
+        // (two kernels: with both ways in one the lists cost 2 % on 12,725 rows of 8 entries)
+        auto launch_for = [&](auto with) {
+            constexpr bool kCounts = decltype(with)::value;
+            if (shape.lanes == 8) launch(shape.narrow() ? k_row_given<8, true, kCounts, RP, VT> : k_row_given<8, false, kCounts, RP, VT>);
+            else launch(shape.narrow() ? k_row_given<16, true, kCounts, RP, VT> : k_row_given<16, false, kCounts, RP, VT>);
+        };
+        if (counts) launch_for(std::true_type{});
+        else launch_for(std::false_type{});
     }
     phase_end(ctx, TSP_PHASE_SYMBOLIC, s);
     CopyArgs copy{shape, A->rows, row_blocks * 4, nullptr, nullptr, m.found, m.wave_total, row_ptr, col, val, live};
@@ -2730,7 +2804,7 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     ctx->scalars_clean = true;               // (cleared for the next call)
     const int64_t *h = ctx->h_scalars;
     if (h[S_INVALID]) return TSP_ERR_NOT_CANONICAL;
-    if (h[S_INTERNAL]) hipLaunchKernelGGL(k_clear_arrivals, dim3(kArriveCounters / 256), dim3(256), 0, s, ctx->d_arrivals);
+    if (h[S_INTERNAL]) hipLaunchKernelGGL(k_clear_arrivals, dim3(kArriveCounters / 256), dim3(256), 0, s, ctx->d_arrivals, ctx->d_tile_counts);
     if (h[S_ROW_HEAVY] || h[S_INTERNAL]) {
         hint.others = true;
         *end = kRowsAgain;
@@ -2738,6 +2812,7 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     }
     const int64_t nnz = h[S_C_NNZ];
     hint.candidates = h[S_CANDIDATES];
+    hint.a_tiles = h[S_TILES_A];
     hint.products = h[S_ROW_PRODUCTS];
     hint.nnz = nnz;
     hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], h[S_ROW_PRODUCTS], hint.wide ? 16 : cost_lanes, 0, true, h[S_CANDIDATES]);
@@ -2973,6 +3048,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], small, hint.wide ? 16 : cost_lanes, heavy, kind.sum != FillKind::kDouble, h[S_CANDIDATES]) ||
                       (n_heavy > 0 && !table_fits) || n_tasks >= INT32_MAX;
         hint.candidates = h[S_CANDIDATES];
+        hint.a_tiles = h[S_TILES_A];
         hint.heavy = n_heavy;
         hint.tasks = n_tasks;
         hint.large_tasks = n_large;

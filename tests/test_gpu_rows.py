@@ -532,6 +532,34 @@ def test_small_rows_straight_from_the_operands(tsp, oracle, rows, inner, cols, a
         h.close()
 
 
+# pairs of tiles by the last block (one chunk of rows, B of up to 4096 tile-rows), by others from counts, and from lists (more tiles in A
+# than rows and than 24,576)
+@pytest.mark.parametrize("shapes", [
+    ((300, 65536, 140, 2, 2), (300, 65537, 140, 2, 2)), ((2048, 65535, 300, 12, 1), (2048, 70000, 300, 13, 1)), ((2049, 2049, 2049, 3, 3), (2049, 300, 500, 9, 6)),
+    ((2000, 524288, 100, 3, 1), (700, 524288, 100, 2, 1)), ((9000, 9000, 700, 2, 3), (9000, 9001, 700, 9, 3))])
+def test_pairs_of_tiles_straight_from_the_operands(tsp, shapes):
+    """Two products in turn on one handle: the numbers of tiles and of their pairs as counted here, every time."""
+    def tiles(M):
+        row = np.repeat(np.arange(M.rows), np.diff(M.row_ptr)) // 16
+        return np.unique(row * ((M.cols + 15) // 16) + M.col_idx // 16)
+
+    cases = []
+    for rows, inner, cols, a_most, b_most in shapes:
+        rng = np.random.default_rng(inner)
+        A, B = _short(rng, rows, inner, a_most), _short(rng, inner, cols, b_most)
+        of_a, of_b = tiles(A), tiles(B)
+        per_row = np.bincount(of_b // ((cols + 15) // 16), minlength=(inner + 15) // 16)
+        cases.append((tsp.to_device(A), tsp.to_device(B), [of_a.size, of_b.size, int(per_row[of_a % ((inner + 15) // 16)].sum())]))
+    h = tsp.Handle()
+    try:
+        for _ in range(4):
+            for dA, dB, want in cases:
+                h.spgemm(dA, dB).free()
+                assert [h.stats()[k] for k in ("a_tiles", "b_tiles", "candidate_pairs")] == want
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("rows", [1800, 30000])
 def test_what_is_not_for_it_straight_from_the_operands(tsp, oracle, rows):
     """Operands of the sizes of a product of small rows that are not canonical, that have more entries in C than the last one and some,
