@@ -2869,10 +2869,11 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     const int64_t a_ntr = (A->rows + T - 1) / T, b_ntr = (B->rows + T - 1) / T;
     // Small rows: up to 24, 48, 96 or 192 products, with a margin over the mean number; for a row of B as many lanes as its mean has
     // entries.  For the row 8 lanes where the mean row of A has no more entries, else 16.  16 also
-    // - for more than 48 products: a million, 262,144 and 65,536 rows of 8 random entries 899, 214, 65.2 -> 850, 205, 62.3
-    //   us, of 7 (49 products) 794, 187, 60.2 -> 781, 187, 59.5; smaller tables, of 6 (36 products) 518, 125, 50.6 -> 565, 136, 51.6;
-    // - for few rows, as long as the waves are few to a SIMD: 512 to 8192 rows of 8 entries 33.5 -> 29 to 32 us, meshes up to
-    //   110 x 110 29.2 -> 28.2, 16,384 rows of 2 to 8 the same or 1 us more;
+    // - for more than 32 products on average, for which 8 lanes sort 64 keys, eight to a lane (they have no more than 64): 65,536 and
+    //   20,000 rows of 6 random entries, 36 products, 37.1 and 25.3 us of kernels by 8 lanes, 34.9 and 24.9 by 16; meshes, 25 products,
+    //   300 x 300 25.9 and 29.2, 512 x 512 47.6 and 62.6; 65,536 rows of 3 entries 27.7 and 28.1;
+    // - for few rows, whose rows of 9 to 16 entries are then no work for other kernels (where there are none 8 lanes take 1 us less of 13 to
+    //   17 on meshes of 37, 80 and 110 squared, and the call as long as before);
     // - where more than one row in 64 is small but for its 9 to 16 entries (such a row costs 13 ns as a heavy one, and twice the
     //   lanes 0.1 ns per row; by the last product of these sizes, and where the one at hand turns out otherwise it is started
     //   again).
@@ -2884,7 +2885,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         const double list = (double)B->nnz / (double)std::max<int64_t>(B->rows, 1), mean = (double)A->nnz / (double)A->rows * list;
         while (shape.products < 192 && shape.products < 1.25 * mean) shape.products *= 2;
         if (A->nnz <= 8 * A->rows && shape.products <= 96) cost_lanes = 8;
-        if (A->nnz <= 8 * A->rows && shape.products <= 48 && A->rows > kFewRows) lanes_unless_wide = 8;
+        if (A->nnz <= 8 * A->rows && mean <= 32 && A->rows > kFewRows) lanes_unless_wide = 8;
         shape.lanes = known && hint.wide ? 16 : lanes_unless_wide;
         while (shape.list_lanes < shape.lanes && shape.list_lanes < list) shape.list_lanes *= 2;
     }

@@ -1249,8 +1249,8 @@ __global__ __launch_bounds__(kTeamLanes ? 64 : kSymThreads) void k_sym_emit_list
 // of C tiles and pairs at once, forms the products, and has the sums before it when it writes: of the tile-rows of its 64 from them,
 // of those before from the last block of each 64, which adds them up.  What it waits for is a block before it, which runs or is done
 // (blocks are dispatched in order); the wait is bounded like that of a chained scan.  k_row_ptr adds up what the host wants to know.
-// On the stencil 262 us (k_sym_count, k_sym_row_scan and the kernel without it: 50 + 9 + 235, and two launches); six waves per SIMD
-// rather than the five its registers would allow: 273.
+// On the stencil 259 us (k_sym_count, k_sym_row_scan and the kernel without it: 50 + 9 + 235, and two launches); six waves per SIMD
+// rather than the five its registers would allow: 273 and 262 before the words in use were looked for.
 constexpr int kBlockATiles = 64, kBlockListThreads = 128;
 constexpr int kListGroup = 64;
 static_assert(kListGroup * kListTiles < 1 << 17 && kListGroup * kListCap < 1 << 17, "sums over a group, beside 30 bits of the call's number");

@@ -532,6 +532,53 @@ def test_small_rows_straight_from_the_operands(tsp, oracle, rows, inner, cols, a
         h.close()
 
 
+@pytest.mark.parametrize("rows", [700, 2049, 12288, 12289])
+def test_rows_of_nine_entries_where_there_were_none(tsp, oracle, rows):
+    """Products of the same sizes without rows of more than 8 entries, with one, with many and with one that no lanes are enough for: the
+    same bits as on a handle of their own."""
+    rng = np.random.default_rng(rows)
+    inner, total = 900, 3 * rows
+
+    def left(longest, many=1):
+        lengths = np.full(rows, 3)
+        lengths[np.arange(many) * 7 % rows] = longest
+        spare = lengths.sum() - total
+        give = np.flatnonzero(lengths == 3)[:spare // 2 + 1]
+        lengths[give[:spare // 2]] -= 2
+        lengths[give[spare // 2]] -= spare % 2
+        assert lengths.sum() == total
+        col = np.concatenate([np.sort(rng.choice(inner, k, replace=False)) for k in lengths])
+        return inputs.from_coo(rows, inner, np.repeat(np.arange(rows), lengths), col, rng.uniform(-1, 1, total), "left")
+
+    B = _short(rng, inner, 800, 6)
+    As = [left(8), left(9), left(16, rows // 20), left(17), left(3)]
+    dB, dev = tsp.to_device(B), [tsp.to_device(A) for A in As]
+
+    def product(h, k):
+        C = h.spgemm(dev[k], dB)
+        out = C.to_host()
+        C.free()
+        return out
+
+    alone = []
+    for k in range(len(As)):
+        h = tsp.Handle()
+        try:
+            alone.append(product(h, k))
+        finally:
+            h.close()
+        ref = oracle.spgemm(As[k], B, threads=4)
+        assert np.array_equal(alone[k][0], ref.row_ptr) and np.array_equal(alone[k][1], ref.col)
+        assert np.all(np.abs(alone[k][2].astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+    h = tsp.Handle()
+    try:
+        for k in (0, 4, 0, 1, 1, 0, 2, 2, 0, 0, 3, 0, 0, 1):
+            for x, y in zip(product(h, k), alone[k]):
+                assert np.array_equal(x, y), k
+    finally:
+        h.close()
+
+
 # pairs of tiles by the last block (one chunk of rows, B of up to 4096 tile-rows), by others from counts, and from lists (more tiles in A
 # than rows and than 24,576)
 @pytest.mark.parametrize("shapes", [
