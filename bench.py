@@ -53,28 +53,22 @@ CSRC = os.path.join(ROOT, "paper_2009_14600_amd", "csrc")
 # sym_count the sizing of the small and of the heavy rows, numeric the move into C and the multiplication of the heavy rows.
 #   (workload, kernel): (source file, sha256[:12] at the time, FETCH_SIZE, WRITE_SIZE)
 MEASURED_TRAFFIC = {
-    (1, "convert"): ("rowwise.hip", "32e90804bed2", 90.1, 88.6),
-    (1, "sym_count"): ("rowwise.hip", "32e90804bed2", 359.4, 523.7),
-    (1, "numeric"): ("rowwise.hip", "32e90804bed2", 289.6, 501.9),
-    (2, "convert"): ("rowwise.hip", "32e90804bed2", 5386.2, 13671.7),
-    (2, "sym_count"): ("rowwise.hip", "32e90804bed2", 11157.0, 28384.8),
-    (2, "numeric"): ("rowwise.hip", "32e90804bed2", 15159.9, 28826.0),
-    (3, "convert"): ("convert.hip", "f06485e6d4a5", 82406.2, 223128.0),
-    (3, "sym_count"): ("symbolic.hip", "dffb5d515039", 22561.5, 3241.0),
-    (3, "scan_sym"): ("symbolic.hip", "dffb5d515039", 317.8, 250.0),
-    (3, "sym_emit"): ("symbolic.hip", "dffb5d515039", 77212.5, 267212.9),
-    (3, "scan_rows"): ("symbolic.hip", "dffb5d515039", 994.3, 2592.6),
-    (3, "numeric"): ("numeric.hip", "2aade73456b3", 339919.9, 1190282.5),
-    (4, "convert"): ("rowwise.hip", "32e90804bed2", 30075.8, 85601.1),
-    (4, "sym_count"): ("rowwise.hip", "32e90804bed2", 6844956.7, 5335256.2),
-    (4, "scan_rows"): ("rowwise.hip", "32e90804bed2", 754.0, 1877.9),
-    (4, "numeric"): ("rowwise.hip", "32e90804bed2", 25736702.5, 23205265.9),
-    (5, "convert"): ("convert.hip", "f06485e6d4a5", 14146.8, 36641.8),
-    (5, "sym_count"): ("symbolic.hip", "dffb5d515039", 4856.4, 1280.0),
-    (5, "scan_sym"): ("symbolic.hip", "dffb5d515039", 158.9, 98.8),
-    (5, "sym_emit"): ("symbolic.hip", "dffb5d515039", 8707.7, 16309.8),
-    (5, "scan_rows"): ("symbolic.hip", "dffb5d515039", 406.2, 1024.6),
-    (5, "numeric"): ("numeric.hip", "2aade73456b3", 53956.3, 270016.3),
+    (1, "sym_count"): ("rowwise.hip", "0262fd27ebb0", 343.6, 555.0),
+    (1, "numeric"): ("rowwise.hip", "0262fd27ebb0", 281.5, 501.9),
+    (2, "sym_count"): ("rowwise.hip", "0262fd27ebb0", 9586.0, 31038.3),
+    (2, "numeric"): ("rowwise.hip", "0262fd27ebb0", 14995.7, 28768.3),
+    (3, "convert"): ("convert.hip", "81b698620209", 82387.9, 223128.0),
+    (3, "sym_emit"): ("symbolic.hip", "19c8b8db244e", 105837.9, 312288.3),
+    (3, "scan_rows"): ("symbolic.hip", "19c8b8db244e", 1267.5, 2607.8),
+    (3, "numeric"): ("numeric.hip", "2aade73456b3", 339916.8, 1188384.5),
+    (4, "convert"): ("rowwise.hip", "0262fd27ebb0", 30057.1, 85597.6),
+    (4, "sym_count"): ("rowwise.hip", "0262fd27ebb0", 6853447.3, 5353713.0),
+    (4, "scan_rows"): ("rowwise.hip", "0262fd27ebb0", 756.0, 1877.9),
+    (4, "numeric"): ("rowwise.hip", "0262fd27ebb0", 27662252.2, 24983591.6),
+    (5, "convert"): ("convert.hip", "81b698620209", 14127.4, 36641.8),
+    (5, "sym_emit"): ("symbolic.hip", "19c8b8db244e", 8630.2, 16538.5),
+    (5, "scan_rows"): ("symbolic.hip", "19c8b8db244e", 526.4, 1030.6),
+    (5, "numeric"): ("numeric.hip", "2aade73456b3", 53903.8, 269538.4),
 }
 
 def source_digest(name: str) -> str:
