@@ -58,16 +58,16 @@ MEASURED_TRAFFIC = {
     (2, "sym_count"): ("rowwise.hip", "0262fd27ebb0", 9586.0, 31038.3),
     (2, "numeric"): ("rowwise.hip", "0262fd27ebb0", 14995.7, 28768.3),
     (3, "convert"): ("convert.hip", "81b698620209", 82387.9, 223128.0),
-    (3, "sym_emit"): ("symbolic.hip", "19c8b8db244e", 105837.9, 312288.3),
-    (3, "scan_rows"): ("symbolic.hip", "19c8b8db244e", 1267.5, 2607.8),
+    (3, "sym_emit"): ("symbolic.hip", "08ac357a5d35", 105768.5, 312279.4),
+    (3, "scan_rows"): ("symbolic.hip", "08ac357a5d35", 1267.3, 2607.8),
     (3, "numeric"): ("numeric.hip", "2aade73456b3", 339916.8, 1188384.5),
     (4, "convert"): ("rowwise.hip", "0262fd27ebb0", 30057.1, 85597.6),
     (4, "sym_count"): ("rowwise.hip", "0262fd27ebb0", 6853447.3, 5353713.0),
     (4, "scan_rows"): ("rowwise.hip", "0262fd27ebb0", 756.0, 1877.9),
     (4, "numeric"): ("rowwise.hip", "0262fd27ebb0", 27662252.2, 24983591.6),
     (5, "convert"): ("convert.hip", "81b698620209", 14127.4, 36641.8),
-    (5, "sym_emit"): ("symbolic.hip", "19c8b8db244e", 8630.2, 16538.5),
-    (5, "scan_rows"): ("symbolic.hip", "19c8b8db244e", 526.4, 1030.6),
+    (5, "sym_emit"): ("symbolic.hip", "08ac357a5d35", 8637.2, 16538.5),
+    (5, "scan_rows"): ("symbolic.hip", "08ac357a5d35", 526.3, 1030.6),
     (5, "numeric"): ("numeric.hip", "2aade73456b3", 53903.8, 269538.4),
 }
 

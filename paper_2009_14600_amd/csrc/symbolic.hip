@@ -22,7 +22,8 @@
 // each, k_sym_count_segmented does so against a very wide B), k_sym_row_scan (their prefix sums, one chained launch), then either k_sym_emit_listed (tile-rows
 // with few pairs: survivors enumerated once into an LDS list; with enough tile-rows it also runs the
 // counting pass and the row offsets; a block or half a wave per tile-row), k_sym_emit_block (the same where a tile-row of
-// A has few tiles, a block per tile-row) or k_sym_emit (any tile-row; more
+// A has few tiles, a block per tile-row; for sizes that the handle knows it finds the tile-rows' sizes too, without the first two
+// kernels, and so does k_sym_emit_few, a wave per tile-row of few pairs) or k_sym_emit (any tile-row; more
 // C tiles than the LDS window holds are worked off window by window; on skewed products the heaviest
 // tile-rows first, in the order k_work_hist and k_work_order set up), k_count_masks and k_row_offsets
 // (k_row_offsets_wide for tile-rows with many tiles) where the list kernel has not done their work, and
