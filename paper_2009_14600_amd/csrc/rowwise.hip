@@ -676,14 +676,15 @@ struct SmallArgs {
 };
 
 // Where k_row_small finds its rows: as k_row_prepare has left the operands.  list: entry l of a row of A, if it is small and has one:
-// its value as fp32 bits, and where its row of B lies.  element: an entry of B, as it is read and as {column, value as fp32 bits}.
+// its value as fp32 bits, and where its row of B lies; of GivenOperands also whether the row has more than 8 entries.  element: an
+// entry of B, as it is read and as {column, value as fp32 bits}.
 struct PreparedOperands {
     const int32_t *a_start, *b_start, *ub;
     const int2 *a_rec, *b_rec;
     static constexpr bool kDirect = false;
     using Element = int2;
     template <int G>
-    __device__ __forceinline__ void list(uint32_t row, int l, int most, int32_t &p, int32_t &e, uint32_t &value, bool &other) const {
+    __device__ __forceinline__ void list(uint32_t row, int l, int most, int32_t &p, int32_t &e, uint32_t &value, bool &other, bool &) const {
         const int32_t s = element(a_start, row), deg = element(a_start, row + 1) - s, products = element(ub, row);
         const bool small = (products > 0) & (deg > 0) & small_row(deg, products, G, most);
         other = !small & (products != 0) & (deg > 0);
@@ -720,9 +721,10 @@ struct GivenOperands {
     }
     static __device__ __forceinline__ uint32_t value_bits(VT v) { return __float_as_uint((float)__builtin_bit_cast(_Float16, (uint16_t)half_bits(v))); }
     template <int G>
-    __device__ __forceinline__ void list(uint32_t row, int l, int, int32_t &p, int32_t &e, uint32_t &value, bool &other) const {
+    __device__ __forceinline__ void list(uint32_t row, int l, int, int32_t &p, int32_t &e, uint32_t &value, bool &other, bool &wide) const {
         const int32_t s = pointer(a_row_ptr, row, a_nnz), deg = pointer(a_row_ptr, row + 1, a_nnz) - s;
         other = deg > G;
+        wide = deg > 8;
         if (!other & (l < deg)) {
             const uint32_t c = min((uint32_t)element(a_col, (uint32_t)(s + l)), a_last);
             value = value_bits(element(a_val, (uint32_t)(s + l)));
@@ -858,7 +860,8 @@ __device__ __forceinline__ uint32_t fold_groups(unsigned long long bits) {
 // 4 to 7: this kernel 38.8 -> 28.4 us on the mesh, 39.6 -> 24.4 with 65,536 rows of 8 random entries, 12.8 -> 9.3 with 1024 of them,
 // 25.6 -> 19.2 for A*P on a 64^3 grid.  With the table's compare-and-swaps and additions requested eight rows of B at a time 45, 56
 // and 29: the LDS takes 8 to 12 cycles for each, 30 where eight lanes count in one place, 12 to 17 for an fp64 addition.
-// totals: GivenOperands, of each wave: entries, products, and whether there are rows of other kernels
+// totals: GivenOperands, of each wave: entries, products, and rows of 9 to 16 entries (S_ROW_WIDE) << 1 | whether there are rows of
+// other kernels
 template <int G, bool kNarrow, typename Operands>
 __device__ __forceinline__ void row_small(const SmallArgs &a, const Operands &operands, const uint32_t block, uint3 *totals = nullptr) {
     constexpr int kRows = 64 / G;        // per wave
@@ -873,8 +876,8 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const Operands &op
     uint2 *products = wave_products + __umul24(lane / G, most);
     int32_t p = 0, e = 0;
     uint32_t av = 0;
-    bool other = false;                                      // the row is for other kernels
-    if (row < a.rows) operands.template list<G>(row, l, most, p, e, av, other);
+    bool other = false, wide = false;                        // the row is for other kernels; has 9 entries and more
+    if (row < a.rows) operands.template list<G>(row, l, most, p, e, av, other, wide);
     // The LDS has room for the row's products: of prepared operands ub says so, and so do the start arrays of those that are
     // canonical; of others the lists are counted here, and a row that has more takes none.
     int len = min(max(e - p, 0), most + 1);
@@ -889,6 +892,8 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const Operands &op
         n_products = len = 0;
         other = other | Operands::kDirect;
     }
+    uint32_t wides = 0;
+    if constexpr (Operands::kDirect && G == 16) wides = (uint32_t)__popcll(__ballot((l == 0) & wide & (n_products > 0)));
     const uint32_t of_lists = fold_groups<G>(__ballot(len > 0));          // lists that any of the groups has, a bit each
     const int lists = 32 - __builtin_clz(of_lists | 1u);                   // (one, without elements, where there are none)
     // round t: list t, or with narrow lists the lists t * (G / width) ... of the group, and element j of each
@@ -1045,7 +1050,7 @@ __device__ __forceinline__ void row_small(const SmallArgs &a, const Operands &op
         // (rows of other kernels count as empty here, and are told of)
         if (l == 0 && row < a.rows) put_for(a.finish, a.row_nnz + row, (int32_t)n);
         const uint32_t of_wave = wave_sum((uint32_t)len), others = __any(other) ? 1u : 0u;
-        if (lane == 0) totals[wave] = make_uint3((uint32_t)total, of_wave, others);
+        if (lane == 0) totals[wave] = make_uint3((uint32_t)total, of_wave, wides << 1 | others);
         return;
     }
     if (l == 0) {
@@ -1500,6 +1505,19 @@ __device__ __forceinline__ int32_t count_tiles(const TileArgs<RP> &a, uint32_t b
 constexpr int kArriveGroup = 64;
 constexpr int kArriveShift = 56;
 constexpr unsigned long long kArriveSum = (1ull << kArriveShift) - 1ull;
+// ... of rows: entries, products, blocks with rows of other kernels, rows of 9 to 16 entries
+struct GroupOfRows {
+    static constexpr int kProducts = 18, kOthers = 36, kWide = 43;
+    static constexpr unsigned long long pack(uint32_t entries, uint32_t products, uint32_t others, uint32_t wide) {
+        return 1ull << kArriveShift | (unsigned long long)wide << kWide | (unsigned long long)others << kOthers | (unsigned long long)products << kProducts | entries;
+    }
+    static_assert(kArriveGroup * 16 * 192 < 1 << kProducts && kArriveGroup * 32 * 96 < 1 << kProducts && kOthers - kProducts == kProducts, "sums over a group");
+    static_assert(kArriveGroup < 1 << (kWide - kOthers) && kArriveGroup * 16 < 1 << (kArriveShift - kWide), "(8 lanes to a row have no rows of 9 entries)");
+    uint32_t entries, products, others, wide;
+    __device__ explicit GroupOfRows(unsigned long long sum)
+        : entries((uint32_t)sum & ((1u << kProducts) - 1u)), products((uint32_t)(sum >> kProducts) & ((1u << kProducts) - 1u)),
+          others((uint32_t)(sum >> kOthers) & ((1u << (kWide - kOthers)) - 1u)), wide((uint32_t)(sum >> kWide) & ((1u << (kArriveShift - kWide)) - 1u)) {}
+};
 __host__ __device__ constexpr uint32_t arrive_groups(uint32_t blocks) { return (blocks + kArriveGroup - 1) / kArriveGroup; }
 __device__ __forceinline__ uint32_t arrive_blocks(uint32_t group, uint32_t blocks) { return min(blocks - group * kArriveGroup, (uint32_t)kArriveGroup); }
 // The blocks of a launch are dispatched in order, so those before a block that waits run or are done.  Waits are bounded all the same:
@@ -1526,12 +1544,12 @@ struct GivenPublishArgs {
     int same;                            // A and B are one matrix
 };
 // publish_scalars by one wave; the numbers of tiles, `candidates` and `failed` beyond what stands in the scalar block
-__device__ __forceinline__ void publish_given(const GivenPublishArgs &a, int64_t entries, int64_t products, int64_t others, int64_t tiles_a, int64_t tiles_b,
-                                              int64_t candidates, int64_t failed) {
+__device__ __forceinline__ void publish_given(const GivenPublishArgs &a, int64_t entries, int64_t products, int64_t others, int64_t wide, int64_t tiles_a,
+                                              int64_t tiles_b, int64_t candidates, int64_t failed) {
     const int lane = lane_id();
     int64_t v = 0;
     if (lane < kScalars) v = __hip_atomic_load(a.d_scalars + (a.same && lane == S_TILES_B ? (int)S_TILES_A : lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v = lane == S_C_NNZ ? entries : lane == S_ROW_PRODUCTS ? products : lane == S_ROW_HEAVY ? others : lane == S_CANDIDATES ? v + candidates : lane == S_INTERNAL ? v + failed : v;
+    v = lane == S_C_NNZ ? entries : lane == S_ROW_PRODUCTS ? products : lane == S_ROW_HEAVY ? others : lane == S_ROW_WIDE ? wide : lane == S_CANDIDATES ? v + candidates : lane == S_INTERNAL ? v + failed : v;
     v += lane == S_TILES_A || (a.same && lane == S_TILES_B) ? tiles_a : lane == S_TILES_B ? tiles_b : 0;
     const bool invalid = __any((lane == S_INVALID || lane == S_INTERNAL) && v != 0);
     if (lane < kScalars) {
@@ -1667,16 +1685,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         if (one_chunk) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (the last block reads row_nnz)
         __syncthreads();
         if (threadIdx.x > 0) return;
-        uint32_t entries = 0, products = 0, others = 0;
+        uint32_t entries = 0, products = 0, others = 0, wide = 0;
         for (int w = 0; w < 4; ++w) {
             entries += s_totals[w].x;
             products += s_totals[w].y;
-            others |= s_totals[w].z;
+            others |= s_totals[w].z & 1u;
+            wide += s_totals[w].z >> 1;
         }
         if (!one_chunk) a.small.block_len[block] = entries;
-        static_assert(kArriveGroup * 16 * 192 < 1 << 20 && kArriveGroup * 32 * 96 < 1 << 20, "sums over a group");
-        atomicAdd(a.counters + (tile_groups + block / kArriveGroup) * kArriveStride,
-                  1ull << kArriveShift | (unsigned long long)others << 40 | (unsigned long long)products << 20 | entries);
+        atomicAdd(a.counters + (tile_groups + block / kArriveGroup) * kArriveStride, GroupOfRows::pack(entries, products, others, wide));
         return;
     }
     const bool last = at == a.row_blocks + a.pair_blocks;
@@ -1719,19 +1736,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (threadIdx.x == 0 && a.pair_blocks) (void)wait_for(d_scalars + S_ROW_ARRIVED, [&](int64_t v) { return v == (int64_t)a.pair_blocks; }, &failed);
-    const uint32_t of_wave[3] = {wave_sum((uint32_t)sum & 0xFFFFFu), wave_sum((uint32_t)(sum >> 20) & 0xFFFFFu), wave_sum((uint32_t)(sum >> 40) & 0xFFFFu)};
+    const GroupOfRows group(sum);
+    const uint32_t of_wave[4] = {wave_sum(group.entries), wave_sum(group.products), wave_sum(group.others), wave_sum(group.wide)};
     const bool any_failed = __any(failed);
-    if (lane_id() == 0) s_totals[threadIdx.x >> 6] = make_uint3(of_wave[0], of_wave[1], of_wave[2] | (any_failed ? 1u << 31 : 0u));
+    // (of a wave's 64 groups at most 2^12 blocks and 2^16 rows)
+    if (lane_id() == 0) s_totals[threadIdx.x >> 6] = make_uint3(of_wave[0], of_wave[1], of_wave[2] << 18 | of_wave[3] | (any_failed ? 1u << 31 : 0u));
     __syncthreads();
     if (threadIdx.x < 64) {
-        int64_t entries = 0, products = 0, others = 0, failures = 0;
+        int64_t entries = 0, products = 0, others = 0, wide = 0, failures = 0;
         for (int w = 0; w < 4; ++w) {
             entries += s_totals[w].x;
             products += s_totals[w].y;
-            others += s_totals[w].z & 0x7FFFFFFFu;
+            others += (s_totals[w].z & 0x7FFFFFFFu) >> 18;
+            wide += s_totals[w].z & ((1u << 18) - 1u);
             failures += s_totals[w].z >> 31;
         }
-        publish_given(a.publish, entries, products, others, (int64_t)tiles_a, (int64_t)tiles_b, (int64_t)pairs, failures);
+        publish_given(a.publish, entries, products, others, wide, (int64_t)tiles_a, (int64_t)tiles_b, (int64_t)pairs, failures);
     }
     if (!one_chunk) return;
     // row_ptr of one chunk of rows
@@ -2815,6 +2835,8 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     hint.a_tiles = h[S_TILES_A];
     hint.products = h[S_ROW_PRODUCTS];
     hint.nnz = nnz;
+    // (as k_row_prepare counts them; by 8 lanes there are none, or the product has been started again)
+    hint.wide = h[S_ROW_WIDE] > A->rows / 64;
     hint.tiles = !rows_preferred(h[S_ROW_PRODUCTS], h[S_ROW_PRODUCTS], hint.wide ? 16 : cost_lanes, 0, true, h[S_CANDIDATES]);
     if (hint.tiles) {
         *end = kRowsNotTaken;

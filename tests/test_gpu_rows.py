@@ -579,6 +579,54 @@ def test_rows_of_nine_entries_where_there_were_none(tsp, oracle, rows):
         h.close()
 
 
+@pytest.mark.parametrize("rows", [9000, 40000])
+def test_rows_or_tiles_whatever_came_before(tsp, oracle, rows):
+    """Products of the same sizes with more than 32 products per row, one with many rows of 9 to 16 entries and one without any: the same
+    way, by rows or by tiles, and the same bits as on a handle of their own.  (16 lanes to a row whichever it is, but what the rows cost
+    is reckoned by their number, and with entries near the diagonal that decides.)"""
+    rng = np.random.default_rng(rows)
+    lengths = np.full(rows, 7)
+    lengths[::20], lengths[5::20] = 13, 1
+
+    def left(lengths, spread):
+        first = np.minimum(np.arange(rows) // 4 * 4, rows - spread)
+        col = np.concatenate([np.sort(rng.choice(spread, k, replace=False)) + f for f, k in zip(first, lengths)])
+        return inputs.from_coo(rows, rows, np.repeat(np.arange(rows), lengths), col, rng.uniform(-1, 1, col.size), "left")
+
+    near = np.minimum(np.arange(rows) // 16 * 16, rows - 16)
+    B = inputs.from_coo(rows, rows, np.repeat(np.arange(rows), 6), np.concatenate([np.sort(rng.choice(16, 6, replace=False)) + f for f in near]),
+                        rng.uniform(-1, 1, 6 * rows), "right")
+    As = [left(lengths, rows // 2), left(np.full(rows, 7), 20), left(lengths, 20)]
+    dB, dev = tsp.to_device(B), [tsp.to_device(A) for A in As]
+
+    def product(h, k):
+        C = h.spgemm(dev[k], dB)
+        out = C.to_host()
+        C.free()
+        return [h.stats()["pairs"] == 0] + list(out)
+
+    alone = []
+    for k, A in enumerate(As):
+        h = tsp.Handle()
+        try:
+            alone.append(product(h, k))
+        finally:
+            h.close()
+        ref = oracle.spgemm(A, B, threads=4)
+        assert np.array_equal(alone[k][1], ref.row_ptr) and np.array_equal(alone[k][2], ref.col)
+        assert np.all(np.abs(alone[k][3].astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+    if rows == 40000:
+        assert [x[0] for x in alone] == [True, True, False]
+    # (the last one's tiles stay for products with about as many pairs of them, so it comes last)
+    h = tsp.Handle()
+    try:
+        for k in (0, 0, 1, 1, 0, 1, 2):
+            for x, y in zip(product(h, k), alone[k]):
+                assert np.array_equal(x, y), k
+    finally:
+        h.close()
+
+
 # pairs of tiles by the last block (one chunk of rows, B of up to 4096 tile-rows), by others from counts, and from lists (more tiles in A
 # than rows and than 24,576)
 @pytest.mark.parametrize("shapes", [
