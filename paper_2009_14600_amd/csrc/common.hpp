@@ -119,6 +119,23 @@ struct ListExpected {
 struct CompactHint {
     int64_t nnz = -1;
 };
+// When products of the same sizes go straight from the operands (rowwise_given).  One that turned out not to be for it has cost a launch, so
+// the next is to come after some without rows for other kernels, one behind the other: after 4, and after twice as many every further
+// time, 1024 at most; half as many again when as many as that have gone well.
+struct GivenHint {
+    int wanted = 0, seen = 0, done = 0;
+    bool allowed() const { return seen >= wanted; }
+    void prepared(bool suitable) { seen = suitable ? std::min(seen + 1, wanted) : 0; }
+    void missed() {
+        wanted = std::min(std::max(2 * wanted, 4), 1024);
+        seen = done = 0;
+    }
+    void taken() {
+        if (++done < wanted) return;
+        wanted = seen = wanted / 2;
+        done = 0;
+    }
+};
 // What the row kernels found for the last product of the same sizes (rowwise.hip): whether the tile kernels
 // suit it better, and how long its lists of work are.  Only the choice of kernels and the sizes of workspaces follow
 // from it; the numbers of the product at hand are checked against it.
@@ -134,7 +151,7 @@ struct RowHint {
     int64_t products = 0;                          // intermediate ones
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows
-    bool others = false;                           // k_row_given has met rows that are not for it
+    GivenHint given;
     bool wide = false;                             // so many rows of 9 to 16 entries that 16 lanes per row pay
     int sum = 0, scale = 0;                        // how the heavy rows are summed
 };

@@ -2826,7 +2826,7 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     if (h[S_INVALID]) return TSP_ERR_NOT_CANONICAL;
     if (h[S_INTERNAL]) hipLaunchKernelGGL(k_clear_arrivals, dim3(kArriveCounters / 256), dim3(256), 0, s, ctx->d_arrivals, ctx->d_tile_counts);
     if (h[S_ROW_HEAVY] || h[S_INTERNAL]) {
-        hint.others = true;
+        hint.given.missed();
         *end = kRowsAgain;
         return TSP_OK;
     }
@@ -2860,6 +2860,7 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     ws.keep(row_ptr);
     ws.keep(col);
     ws.keep(val);
+    hint.given.taken();
     *C = tsp_csr{};
     C->rows = A->rows;
     C->cols = B->cols;
@@ -2917,7 +2918,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     if (found_entries() > kFoundEntries) return TSP_OK;
     // straight from the operands, by the last product of these sizes
     auto of_waves = [](const tsp_csr *M) { return M->nnz <= 128 * ((M->rows + T - 1) / T) && ((M->cols + T * 32 - 1) / (T * 32) + 3) / 4 * 64 <= (int64_t)kGivenBitmaps; };
-    if (known && hint.nnz >= 0 && hint.heavy == 0 && hint.small && !hint.others && shape.lanes == lanes_unless_wide && A->rows <= kFinishRows &&
+    if (known && hint.nnz >= 0 && hint.heavy == 0 && hint.small && hint.given.allowed() && shape.lanes == lanes_unless_wide && A->rows <= kFinishRows &&
         (A->rows * shape.lanes + 255) / 256 <= kGivenBlocks && A->row_ptr_type == B->row_ptr_type && A->val_type == B->val_type && of_waves(A) && (alias || of_waves(B))) {
         const bool f16 = A->val_type == TSP_F16, i32 = A->row_ptr_type == TSP_I32;
         auto run = i32 ? (f16 ? rowwise_given<int32_t, uint16_t> : rowwise_given<int32_t, float>) : f16 ? rowwise_given<int64_t, uint16_t> : rowwise_given<int64_t, float>;
@@ -3073,6 +3074,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hint.candidates = h[S_CANDIDATES];
         hint.a_tiles = h[S_TILES_A];
         hint.heavy = n_heavy;
+        hint.given.prepared(n_heavy == 0);
         hint.tasks = n_tasks;
         hint.large_tasks = n_large;
         hint.products = n_products;

@@ -579,6 +579,38 @@ def test_rows_of_nine_entries_where_there_were_none(tsp, oracle, rows):
         h.close()
 
 
+@pytest.mark.parametrize("rows", [700, 2500])
+def test_straight_from_the_operands_again(tsp, rows):
+    """After a product with a row that is not small, products of the same sizes without any go straight from the operands again, and
+    not at once; with such products in turn they no longer try.  (The pass over the operands is the convert kernel.)"""
+    rng = np.random.default_rng(rows)
+    B = _short(rng, 900, 800, 6)
+    lengths = np.full(rows, 3)
+    lengths[5], lengths[20:34] = 31, 1
+    As = [inputs.from_coo(rows, 900, np.repeat(np.arange(rows), l), np.concatenate([np.sort(rng.choice(900, k, replace=False)) for k in l]),
+                          rng.uniform(-1, 1, 3 * rows), "left") for l in (np.full(rows, 3), lengths)]
+    dB, dev = tsp.to_device(B), [tsp.to_device(A) for A in As]
+    h = tsp.Handle(phase_timers=True)
+
+    def straight(k):
+        h.spgemm(dev[k], dB).free()
+        return h.stats()["kernel_us"]["convert"] == 0
+
+    try:
+        straight(0)
+        assert [straight(0) for _ in range(3)] == [True] * 3
+        assert not straight(1)
+        assert [straight(0) for _ in range(6)] == [False] * 4 + [True] * 2
+        assert not straight(1)
+        assert [straight(0) for _ in range(9)] == [False] * 8 + [True]
+        for _ in range(4):
+            assert not straight(1)
+            assert not any(straight(0) for _ in range(8))
+        assert any(straight(0) for _ in range(16))
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("rows", [9000, 40000])
 def test_rows_or_tiles_whatever_came_before(tsp, oracle, rows):
     """Products of the same sizes with more than 32 products per row, one with many rows of 9 to 16 entries and one without any: the same
