@@ -118,6 +118,11 @@ enum {
                                /*    when it multiplies by rows; beyond that it is found again, some */
                                /*    rows at a time (one at least).  0 (default): 16 GiB.  The       */
                                /*    result does not depend on it                                    */
+    TSP_OPT_GIVE_UP_WAITS = 13, /* 1: where tsp_spgemm multiplies short rows in one launch whose last  */
+                               /*    blocks wait for the others, those blocks give up without a look, */
+                               /*    as they do after 2^18, and the product is started again by the  */
+                               /*    kernels that do not wait.  A debugging aid: the result does not */
+                               /*    depend on it.  0 (default): they wait                           */
     TSP_OPT_STRIP_ORDER = 8    /* order in which the counting and the multiplication kernel (4.2,   */
                                /*    4.3) take the output tiles: 1: in vertical strips of tile      */
                                /*    columns sized so that the tiles of B a strip meets stay in the  */

@@ -228,6 +228,8 @@ struct tsp_context {
     tsp::HintMemory<tsp::CompactHint> compact_hints;
     uint32_t *d_tile_counts = nullptr;             // device, kTileCounts, zero between launches (behind those)
     unsigned long long *d_arrivals = nullptr;      // device, kArriveCounters counters, zero between launches (behind the scalars)
+    bool arrivals_clean = true;                    // ... both of them: the last launch that uses them has ended as it should
+    int give_up = 0;                               // TSP_OPT_GIVE_UP_WAITS
     bool scalars_clean = false;                    // all zero: the last kernel of the previous call left them so
     int64_t *h_scalars = nullptr;                  // pinned host mirror
     int64_t *h_scalars_dev = nullptr;              // the mirror's address on the device

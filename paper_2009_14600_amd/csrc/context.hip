@@ -296,6 +296,7 @@ extern "C" int tsp_set_option(tsp_handle ctx, int key, int64_t value) {
             ctx->canaries = value != 0;
             ctx->canaries_used = ctx->canaries_used || value != 0;
             return TSP_OK;
+        case TSP_OPT_GIVE_UP_WAITS: ctx->give_up = value != 0; return TSP_OK;
         case TSP_OPT_PATTERN_BYTES:
             if (value < 0) return TSP_ERR_INVALID_ARG;
             ctx->pattern_bytes = value ? value : (int64_t)16 << 30;

@@ -1521,14 +1521,17 @@ struct GroupOfRows {
 __host__ __device__ constexpr uint32_t arrive_groups(uint32_t blocks) { return (blocks + kArriveGroup - 1) / kArriveGroup; }
 __device__ __forceinline__ uint32_t arrive_blocks(uint32_t group, uint32_t blocks) { return min(blocks - group * kArriveGroup, (uint32_t)kArriveGroup); }
 // The blocks of a launch are dispatched in order, so those before a block that waits run or are done.  Waits are bounded all the same:
-// so many looks, a microsecond each, and the host starts the product again.
+// so many looks (0: none that counts), a microsecond each, and the host starts the product again.
 constexpr unsigned kArriveSpins = 1u << 18;
 template <typename X, typename Done>
-__device__ __forceinline__ X wait_for(const X *p, Done done, bool *failed) {
-    X v;
+__device__ __forceinline__ X wait_for(const X *p, unsigned looks, Done done, bool *failed) {
+    X v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned spins = 0;
-    while (!done(v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) && ++spins < kArriveSpins) __builtin_amdgcn_s_sleep(2);
-    *failed = *failed | (spins >= kArriveSpins);
+    while (spins < looks && !done(v)) {
+        if (++spins < looks) __builtin_amdgcn_s_sleep(2);
+        v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    *failed = *failed | (spins >= looks);
     return v;
 }
 __device__ __forceinline__ unsigned long long add_scalar(int64_t *d_scalars, int slot, unsigned long long v) {
@@ -1577,6 +1580,7 @@ struct GivenArgs {
     uint32_t a_blocks, b_blocks, row_blocks, pair_blocks;
     int per_wave;                        // tile-rows
     int validate;
+    unsigned looks;                      // of a block that waits
     unsigned long long *counters;        // of groups of blocks: tiles of A, of B, rows
     GivenPublishArgs publish;
 };
@@ -1700,7 +1704,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     bool failed = false;
     unsigned long long pairs = 0, tiles_a = 0, tiles_b = 0;
     if (!last) {
-        if (threadIdx.x == 0) (void)wait_for(d_scalars + S_GIVEN_ARRIVED, [&](int64_t v) { return v == (int64_t)tile_groups; }, &failed);
+        if (threadIdx.x == 0) (void)wait_for(d_scalars + S_GIVEN_ARRIVED, a.looks, [&](int64_t v) { return v == (int64_t)tile_groups; }, &failed);
         __syncthreads();
         pairs = add_threads(kCounts ? count_pairs(a, at - half, a.pair_blocks) : count_listed_pairs(a, at - half, a.pair_blocks), s_sum);
         if (threadIdx.x > 0) return;
@@ -1719,7 +1723,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
                 const bool of_b = threadIdx.x >= a_groups;
                 unsigned long long *counter = a.counters + threadIdx.x * kArriveStride;
                 const unsigned long long want = arrive_blocks(of_b ? threadIdx.x - a_groups : threadIdx.x, of_b ? a.b_blocks : a.a_blocks);
-                tiles = wait_for(counter, [&](unsigned long long v) { return (v >> kArriveShift) == want; }, &failed) & kArriveSum;
+                tiles = wait_for(counter, a.looks, [&](unsigned long long v) { return (v >> kArriveShift) == want; }, &failed) & kArriveSum;
                 __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             tiles_a = wave_sum(threadIdx.x < a_groups ? (uint32_t)tiles : 0u);
@@ -1732,10 +1736,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     unsigned long long sum = 0;
     if (threadIdx.x < row_groups) {
         unsigned long long *counter = a.counters + (tile_groups + threadIdx.x) * kArriveStride;
-        sum = wait_for(counter, [&](unsigned long long v) { return (v >> kArriveShift) == arrive_blocks(threadIdx.x, a.row_blocks); }, &failed);
+        sum = wait_for(counter, a.looks, [&](unsigned long long v) { return (v >> kArriveShift) == arrive_blocks(threadIdx.x, a.row_blocks); }, &failed);
         __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (threadIdx.x == 0 && a.pair_blocks) (void)wait_for(d_scalars + S_ROW_ARRIVED, [&](int64_t v) { return v == (int64_t)a.pair_blocks; }, &failed);
+    if (threadIdx.x == 0 && a.pair_blocks) (void)wait_for(d_scalars + S_ROW_ARRIVED, a.looks, [&](int64_t v) { return v == (int64_t)a.pair_blocks; }, &failed);
     const GroupOfRows group(sum);
     const uint32_t of_wave[4] = {wave_sum(group.entries), wave_sum(group.products), wave_sum(group.others), wave_sum(group.wide)};
     const bool any_failed = __any(failed);
@@ -2767,6 +2771,7 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     a.pair_blocks = !counts ? (uint32_t)std::min<int64_t>(kPlanBlocks, (a_ntr + 15) / 16)
                   : one_chunk && b_ntr <= kPairsByOne ? 0u : (uint32_t)std::min<int64_t>(kPlanBlocks, (b_ntr + 255) / 256);
     a.validate = ctx->validate;
+    a.looks = ctx->give_up ? 0u : kArriveSpins;
     a.counters = ctx->d_arrivals;
     a.operands = {static_cast<const RP *>(A->row_ptr), static_cast<const RP *>(B->row_ptr), A->col_idx, B->col_idx, static_cast<const VT *>(A->val),
                   static_cast<const VT *>(B->val), (int32_t)A->nnz, (int32_t)B->nnz, (uint32_t)(A->cols - 1), (uint32_t)(B->cols - 1)};
@@ -2786,6 +2791,9 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     if (ws.failed) return TSP_ERR_ALLOC_FAILED;
     a.publish = GivenPublishArgs{A->rows, room, row_ptr, ctx->d_scalars, ctx->h_scalars_dev, ++ctx->publish_tag, live, alias};
 
+    // (where blocks have given up, others have counted themselves, tiles and pairs after those had taken what was there)
+    if (!ctx->arrivals_clean) hipLaunchKernelGGL(k_clear_arrivals, dim3(kArriveCounters / 256), dim3(256), 0, s, ctx->d_arrivals, ctx->d_tile_counts);
+    ctx->arrivals_clean = false;
     phase_begin(ctx, TSP_PHASE_SYMBOLIC, s);
     {
         KernelTimer kt(ctx, TSP_KERNEL_SYM_COUNT, s);
@@ -2821,10 +2829,9 @@ static int rowwise_given(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, b
     TSP_HIP_CHECK(ctx, hipGetLastError());
     const int rc = wait_published_scalars(ctx, ctx->publish_tag, s);
     if (rc) return rc;
-    ctx->scalars_clean = true;               // (cleared for the next call)
     const int64_t *h = ctx->h_scalars;
+    ctx->scalars_clean = ctx->arrivals_clean = !h[S_INTERNAL];       // (cleared for the next call)
     if (h[S_INVALID]) return TSP_ERR_NOT_CANONICAL;
-    if (h[S_INTERNAL]) hipLaunchKernelGGL(k_clear_arrivals, dim3(kArriveCounters / 256), dim3(256), 0, s, ctx->d_arrivals, ctx->d_tile_counts);
     if (h[S_ROW_HEAVY] || h[S_INTERNAL]) {
         hint.given.missed();
         *end = kRowsAgain;

@@ -23,6 +23,7 @@ OPT_STRIP_ORDER = 8
 OPT_COUNT_PRODUCTS = 10
 OPT_WORKSPACE_CANARIES = 11
 OPT_PATTERN_BYTES = 12
+OPT_GIVE_UP_WAITS = 13
 PHASES = ("convert", "symbolic", "count", "numeric")
 KERNELS = ("convert", "sym_count", "scan_sym", "sym_emit", "count_masks", "row_offsets", "scan_rows", "numeric")
 

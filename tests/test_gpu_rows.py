@@ -579,6 +579,48 @@ def test_rows_of_nine_entries_where_there_were_none(tsp, oracle, rows):
         h.close()
 
 
+# one chunk of rows, with the pairs of tiles by the last block and by others; more rows
+@pytest.mark.parametrize("rows,inner,a_most,b_most", [(700, 900, 3, 6), (2048, 70000, 13, 1), (2500, 2500, 2, 3)])
+def test_blocks_that_wait_give_up(tsp, oracle, rows, inner, a_most, b_most):
+    """Blocks that do not wait for what the others of the launch count, on canonical operands and on others: the product is made the
+    other way, or refused, and the next one that waits has nothing of it in its numbers."""
+    rng = np.random.default_rng(rows)
+    A, B = _short(rng, rows, inner, a_most), _short(rng, inner, 700, b_most)
+    broken = inputs.from_coo(A.rows, A.cols, np.repeat(np.arange(A.rows), np.diff(A.row_ptr)), A.col_idx, A.val, "broken")
+    broken.col_idx[-1] = inner
+    dA, dB, bad = tsp.to_device(A), tsp.to_device(B), tsp.to_device(broken)
+    ref = oracle.spgemm(A, B, threads=4)
+    h = tsp.Handle(phase_timers=True)
+    try:
+        first = None
+        def product(straight):
+            nonlocal first
+            C = h.spgemm(dA, dB)
+            row_ptr, col, val = C.to_host()
+            C.free()
+            stats = h.stats()
+            assert straight is None or (stats["kernel_us"]["convert"] == 0) == straight
+            now = [row_ptr, col, val, [stats[k] for k in ("a_tiles", "b_tiles", "candidate_pairs", "c_nnz", "pairs")]]
+            first = first or now
+            assert all(np.array_equal(x, y) for x, y in zip(now, first))
+        product(False)
+        product(True)
+        assert np.array_equal(first[0], ref.row_ptr) and np.array_equal(first[1], ref.col)
+        h.set_option(tsp.OPT_GIVE_UP_WAITS, 1)
+        product(False)
+        h.set_option(tsp.OPT_GIVE_UP_WAITS, 0)
+        for straight in (False, False, False, True, True, True):       # (three more before the next try)
+            product(straight)
+        h.set_option(tsp.OPT_GIVE_UP_WAITS, 1)
+        with pytest.raises(tsp.TspError):                      # (by whichever kernels have seen it first)
+            h.spgemm(bad, dB)
+        h.set_option(tsp.OPT_GIVE_UP_WAITS, 0)
+        for straight in [None] * 8 + [True, True]:
+            product(straight)
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("rows", [700, 2500])
 def test_straight_from_the_operands_again(tsp, rows):
     """After a product with a row that is not small, products of the same sizes without any go straight from the operands again, and
