@@ -1705,8 +1705,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     unsigned long long pairs = 0, tiles_a = 0, tiles_b = 0;
     if (!last) {
         if (threadIdx.x == 0) (void)wait_for(d_scalars + S_GIVEN_ARRIVED, a.looks, [&](int64_t v) { return v == (int64_t)tile_groups; }, &failed);
-        __syncthreads();
-        pairs = add_threads(kCounts ? count_pairs(a, at - half, a.pair_blocks) : count_listed_pairs(a, at - half, a.pair_blocks), s_sum);
+        // (lists that are not there yet could lead anywhere)
+        if (!__syncthreads_or(failed))
+            pairs = add_threads(kCounts ? count_pairs(a, at - half, a.pair_blocks) : count_listed_pairs(a, at - half, a.pair_blocks), s_sum);
         if (threadIdx.x > 0) return;
         (void)add_scalar(d_scalars, S_CANDIDATES, pairs);
         if (failed) (void)add_scalar(d_scalars, S_INTERNAL, 1);

@@ -579,8 +579,8 @@ def test_rows_of_nine_entries_where_there_were_none(tsp, oracle, rows):
         h.close()
 
 
-# one chunk of rows, with the pairs of tiles by the last block and by others; more rows
-@pytest.mark.parametrize("rows,inner,a_most,b_most", [(700, 900, 3, 6), (2048, 70000, 13, 1), (2500, 2500, 2, 3)])
+# one chunk of rows, with the pairs of tiles by the last block and by others; more rows, from counts and from lists
+@pytest.mark.parametrize("rows,inner,a_most,b_most", [(700, 900, 3, 6), (2048, 70000, 13, 1), (2500, 2500, 2, 3), (9000, 9001, 9, 3)])
 def test_blocks_that_wait_give_up(tsp, oracle, rows, inner, a_most, b_most):
     """Blocks that do not wait for what the others of the launch count, on canonical operands and on others: the product is made the
     other way, or refused, and the next one that waits has nothing of it in its numbers."""
