@@ -2382,11 +2382,16 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
     };
     // by a wave or by a block per tile-row (k_sym_emit_few, k_sym_emit_block); with more tile-rows than the chip holds blocks, most of
     // them short but some not for a wave, the count and k_sym_emit_listed with two of them per wave take less (above)
-    const int64_t most_pairs = std::max<int64_t>(hint.most.max_row_pairs, 1);
-    const int64_t wave_words = few_words(grid_words, std::max<int64_t>(hint.most.max_row_c_tiles, 1), most_pairs);
-    const bool few = few_pairs(most_pairs, ntr) && wave_words * kFewWaves * (int64_t)sizeof(uint32_t) <= (int64_t)kLdsLimit;
-    bool fused_sizes = hinted && grid_words <= kSizingWords && hint.most.max_row_pairs <= kListCap && hint.most.max_row_c_tiles <= kListTiles &&
-                       by_block(hint.most, grid_words) && (few || hint.most.candidates / ntr > 256 || ntr <= kResidentTileRows);
+    bool fused_sizes = false, few = false;
+    int64_t wave_words = 0;
+    auto find_sizes_for = [&](const ListSizes &n) {
+        const int64_t pairs = std::max<int64_t>(n.max_row_pairs, 1);
+        wave_words = few_words(grid_words, std::max<int64_t>(n.max_row_c_tiles, 1), pairs);
+        few = few_pairs(pairs, ntr) && wave_words * kFewWaves * (int64_t)sizeof(uint32_t) <= (int64_t)kLdsLimit;
+        fused_sizes = grid_words <= kSizingWords && n.max_row_pairs <= kListCap && n.max_row_c_tiles <= kListTiles && by_block(n, grid_words) &&
+                      (few || n.candidates / ntr > 256 || ntr <= kResidentTileRows);
+    };
+    if (hinted) find_sizes_for(hint.most);
     bool counted_again = false;
     bool ran_again = false, arrived = false;                          // the host has the numbers of the counting kernels
     int64_t first_numbers[kScalars];               // ... and got them before the list kernel ran again
@@ -2502,7 +2507,7 @@ list_kernels:
         if (listed && fused_masks && !halves && block_each) {
             ListSizing sizing{};
             if (fused_sizes) {
-                tile_row_info = ctx_alloc_n<uint4>(ctx, (size_t)ntr, s);
+                if (!tile_row_info) tile_row_info = ctx_alloc_n<uint4>(ctx, (size_t)ntr, s);
                 if (!tile_row_info) return cleanup(TSP_ERR_ALLOC_FAILED);
                 if (ctx->list_call >= (1u << 30) - 1) {          // the numbers start again: no slot holds one
                     hipLaunchKernelGGL(k_clear_list_slots, dim3((kListSlotWords + 255) / 256), dim3(256), 0, s, ctx->d_list_slots);
@@ -2651,12 +2656,15 @@ list_kernels:
         if (rc) return cleanup(rc);
         if (!z.holds(true_sizes())) {              // another product of the same sizes, with more in it
             std::copy(h, h + kScalars, first_numbers);
-            if (fused_sizes) {                     // (those of tile-rows that did not fit were not counted)
-                fused_sizes = arrived = false;
+            // The list kernels that find the sizes have those of tile-rows that they left out too, but for tile-rows of too many tiles of A:
+            // they run again as the others do, or else the tile-rows are counted after all.
+            const bool found_sizes = fused_sizes;
+            if (found_sizes) find_sizes_for(true_sizes());
+            counted_again = found_sizes && !fused_sizes;
+            ran_again = !counted_again;
+            if (counted_again) {
+                arrived = false;
                 ctx->scalars_clean = false;
-                counted_again = true;
-            } else {
-                ran_again = true;
             }
             drop_ahead();
             ctx_free(ctx, live, s);

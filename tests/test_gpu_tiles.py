@@ -295,6 +295,58 @@ def test_sizes_of_tile_rows_found_with_the_task_list(tsp, oracle, tile_rows, til
         h.close()
 
 
+# a wave per tile-row before and after, a block before and after, first a wave and then a block, and then neither: for more than 1024 pairs,
+# for more than 64 tiles of A, and for a few long tile-rows among more than 4096
+@pytest.mark.parametrize("tile_rows,tiles,more,right_tiles,counted", [
+    (30, 4, 6, 3, False), (30, 4, 50, 3, False), (30, 40, 60, 3, False), (30, 20, 30, 40, True), (90, 4, 70, 3, True), (4200, 2, 7, 3, False), (4200, 2, 60, 12, True)])
+def test_a_tile_row_with_more_than_any_before(tsp, oracle, tile_rows, tiles, more, right_tiles, counted):
+    """A product of sizes that the handle knows, one of whose tile-rows has more pairs than any had: the tile-rows, whose sizes the task
+    list has found by then, are not counted (its first kernel) unless their sizes are beyond it, and the product is what it is on a
+    handle of its own."""
+    rng = np.random.default_rng(tile_rows + more)
+    inner = 70
+
+    def operand(rows, cols, number, total):
+        r = np.repeat(np.arange(rows), number)
+        c = np.concatenate([np.sort(rng.choice(cols, k, replace=False)) for k in number])
+        r, c = np.repeat(r, 4) * 16 + np.tile(np.arange(4), r.size), np.repeat(c, 4) * 16 + np.tile(np.arange(4) * 5, c.size)
+        keep = np.sort(rng.permutation(r.size)[:total])
+        return inputs.from_coo(16 * rows, 16 * cols, r[keep], c[keep], rng.uniform(-1, 1, total), "tiles")
+
+    number = np.full(tile_rows, tiles)
+    other = number.copy()
+    other[tile_rows // 2] = more
+    total = int(number.sum()) * 4
+    As = [operand(tile_rows, inner, n, total) for n in (number, other)]
+    B = operand(inner, 50, np.full(inner, right_tiles), inner * right_tiles * 4)
+    dB, dev = tsp.to_device(B), [tsp.to_device(A) for A in As]
+    ref = oracle.spgemm(As[1], B, threads=4)
+
+    def product(h, k):
+        C = h.spgemm(dev[k], dB)
+        out = C.to_host()
+        C.free()
+        stats = h.stats()
+        return list(out) + [[stats[k] for k in ("a_tiles", "b_tiles", "candidate_pairs", "pairs", "c_tiles", "c_nnz")], stats["kernel_us"]["sym_count"]]
+
+    h, alone = tsp.Handle(phase_timers=True), tsp.Handle()
+    try:
+        for x in (h, alone):
+            x.set_option(tsp.OPT_WORK_ORDER, 2)        # (the tile kernels, whatever the operands)
+        want = product(alone, 1)
+        assert np.array_equal(want[0], ref.row_ptr) and np.array_equal(want[1], ref.col)
+        assert np.all(np.abs(want[2].astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
+        assert product(h, 0)[4] > 0 and product(h, 0)[4] == 0
+        for _ in range(2):
+            got = product(h, 1)
+            assert (got[4] > 0) == counted
+            assert all(np.array_equal(x, y) for x, y in zip(got[:4], want[:4]))
+            assert (product(h, 0)[4] > 0) == counted
+    finally:
+        h.close()
+        alone.close()
+
+
 @pytest.mark.parametrize("left,right", [((1, 0), (0, 0)), ((0, 0), (1, 0)), ((1, 1), (0, 1)), (None, None)])
 def test_tile_rows_of_many_entries_where_there_were_none(tsp, oracle, left, right):
     """Products of the same sizes with and without tile-rows for the kernel that is not launched where the last one had none."""
