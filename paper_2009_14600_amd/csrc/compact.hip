@@ -46,6 +46,9 @@ struct CompactArgs {
     // null: `before` has the sums.
     const uint16_t *counts;
     int64_t capacity;                          // of the result's columns and values
+    // Not 0 where nothing is to be copied unless an entry is dropped: what before[chunks] then holds, from the blocks of the counting pass
+    // that drop one (with `counts`; never the same twice on a handle, so the word needs no other value before)
+    int64_t mark;
     // blocks for `per` rows each; they come before the chunks' in a launch (behind them they would end it)
     __host__ __device__ int row_blocks(int per) const { return rows < 0 ? 0 : (int)(rows / per) + 1; }
 };
@@ -149,6 +152,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_count(CompactArgs<R
         const uint32_t all = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
         if (a.counts) reinterpret_cast<uint16_t *>(count)[blockIdx.x] = (uint16_t)all;
         else count[b] = all;
+        if (a.mark && all < c1 - c0) before[a.chunks] = a.mark;
     }
 }
 
@@ -275,6 +279,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_fill(CompactArgs<RP
         publish_mirror(h_scalars_dev, publish_tag, own);
         return;
     }
+    if (a.mark && uniform_load(before + a.chunks) != a.mark) return;
     const EntryRange range{uniform_load(before + a.chunks + 1), uniform_load(before + a.chunks + 2)};
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int b = (int)blockIdx.x - teller - a.row_blocks(kCompactRows);
@@ -471,7 +476,8 @@ static int compact_run(tsp_context *ctx, const tsp_csr *C, tsp_csr *out, hipStre
     if (!count || !before) return fail(TSP_ERR_ALLOC_FAILED);
     if (sums_in_copy(a)) a.counts = reinterpret_cast<const uint16_t *>(count);
     // Without waiting for the new nnz, into arrays for as many entries as the last matrix of these sizes had left and some more, where it
-    // was to be copied
+    // was to be copied; for a caller that takes C as it is where nothing is dropped the blocks of the copy look at that first
+    if (taken && a.counts) a.mark = ctx->publish_tag + 1;
     CompactHint &hint = ctx->compact_hints.find({{C->rows, C->nnz, C->cols, 0, 0, 0}}, [](CompactHint &) {});
     const int64_t expected = std::min(hint.nnz + hint.nnz / 16, C->nnz);
     bool ahead = a.counts && hint.nnz >= 0 && !(taken && hint.nnz == C->nnz);

@@ -154,3 +154,37 @@ def test_as_many_parts_as_the_copying_blocks_add_up(tsp, parts):
             C.free()
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("nnz", [20, PART - 1, PART, PART + 1, 3 * PART + 5])
+@pytest.mark.parametrize("zero", [0, -1, 7])
+def test_nothing_to_drop_after_a_product_that_lost_entries(tsp, nnz, zero):
+    """Products with the compaction, one that loses an entry (the first of all, the last, one of a few) or several and one of the same
+    sizes that loses none: that one copies nothing into the arrays it was given ahead, and keeps those of the multiplication."""
+    import torch
+    from paper_2009_14600_amd import inputs
+    rows, cols = 97, 300
+    rng = np.random.default_rng(nnz)
+    key = np.sort(rng.choice(rows * cols, nnz, replace=False))
+    A = inputs.from_coo(rows, cols, key // cols, key % cols, rng.uniform(0.5, 1, nnz), "left")
+    unit = tsp.to_device(inputs.from_coo(cols, cols, np.arange(cols), np.arange(cols), np.ones(cols), "unit"))
+    whole, one, several = tsp.to_device(A), tsp.to_device(A), tsp.to_device(A)
+    one.val[zero] = 0
+    several.val[::3] = 0
+    h = tsp.Handle()
+    try:
+        h.set_option(tsp.OPT_COMPACT_ZEROS, 1)
+        for M in (whole, one, one, whole, whole, several, several, whole, one):
+            h.trim()                                           # (no block that holds what an earlier product has left)
+            C = h.spgemm(M, unit)
+            want = M.val.cpu().numpy().astype(np.float32)
+            keep = want != 0
+            row_ptr, col, val = C.to_host()
+            assert np.array_equal(row_ptr, np.concatenate([[0], np.cumsum(keep)])[A.row_ptr])
+            assert np.array_equal(col, A.col_idx[keep]) and np.array_equal(val, want[keep])
+            if M is whole:                                     # (ahead there is room for two thirds of it at least)
+                bits, n = C.col_idx.view(torch.uint8), 4 * (nnz // 2)
+                assert sum(1 for block in h._blocks.values() if block.numel() >= n and bool((block[:n] == bits[:n]).all())) == 1
+            C.free()
+    finally:
+        h.close()
