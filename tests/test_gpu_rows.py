@@ -502,32 +502,42 @@ def _short(rng, rows, cols, most, dense=0):
 
 
 # one chunk of rows (2048) and more, ends of tile-rows, of a wave's four, of a block's, of a group of 64 blocks (2048 rows of 8 lanes, 1024
-# of 16), rows whose blocks are too many for it (262,144 by 16 lanes), bitmaps of 16 KB (524,288 columns) and beyond
-@pytest.mark.parametrize("rows,inner,cols,a_most,b_most,dense", [
-    (257, 300, 200, 4, 4, 0), (2047, 1999, 3001, 3, 5, 0), (2048, 2048, 2048, 6, 9, 0), (2049, 70, 5000, 3, 3, 0), (2065, 5000, 70, 5, 2, 0),
-    (4099, 4099, 4099, 8, 12, 0), (16384, 700, 900, 2, 2, 600), (20001, 20001, 20001, 5, 7, 0), (65537, 3000, 4000, 3, 3, 2000), (3000, 90001, 90001, 3, 4, 0),
-    (30000, 524288, 2000, 2, 3, 0), (30000, 524289, 2000, 2, 3, 0), (2100, 1500, 524288, 4, 3, 0), (2100, 1500, 524289, 4, 3, 0), (262200, 400, 500, 1, 2, 0), (262200, 400, 500, 9, 9, 0)])
+# of 16), as many blocks of rows as it takes (262,144 rows by 16 lanes) and more, bitmaps of 16 KB (524,288 columns) and beyond, 128 entries
+# per tile-row and more, rows of up to 9 entries that 8 lanes are not for, and rows of more products than its LDS has room for
+@pytest.mark.parametrize("rows,inner,cols,a_row,b_row,dense,straight", [
+    (257, 300, 200, 4, 4, 0, True), (2047, 1999, 3001, 3, 5, 0, True), (2048, 2048, 2048, 6, 4, 0, True), (2048, 2048, 2048, 6, 9, 0, False),
+    (2049, 70, 5000, 3, 3, 0, True), (2065, 5000, 70, 5, 2, 0, True), (4099, 4099, 4099, 8, 3, 0, True), (4099, 4099, 4099, 8, 12, 0, False),
+    (16384, 700, 900, 2, 2, 600, True), (20001, 20001, 20001, 5, 4, 0, True), (20001, 20001, 20001, 5, 7, 0, False), (65537, 3000, 4000, 3, 3, 2000, True),
+    (3000, 90001, 90001, 3, 4, 0, True), (30000, 524288, 2000, 2, 3, 0, True), (30000, 524289, 2000, 2, 3, 0, False), (2100, 1500, 524288, 4, 3, 0, True),
+    (2100, 1500, 524289, 4, 3, 0, False), (262200, 400, 500, 1, 2, 0, True), (262200, 400, 500, 9, 9, 0, False), (262144, 400, 500, "7", "5", 0, True),
+    (262145, 400, 500, "7", "5", 0, False), (3008, 900, 800, "8", "3", 0, True), (3008, 900, 800, "9", "3", 0, False)])
 @pytest.mark.parametrize("types", [{}, {"value_dtype": "f32", "row_ptr_dtype": "i64"}])
-def test_small_rows_straight_from_the_operands(tsp, oracle, rows, inner, cols, a_most, b_most, dense, types):
-    """The second and later products of sizes whose first one had small rows only: the same bits as the first where sums are exact,
-    and the same numbers of tiles and of their pairs."""
+def test_small_rows_straight_from_the_operands(tsp, oracle, rows, inner, cols, a_row, b_row, dense, straight, types):
+    """The second and later products of sizes whose first one had small rows only: the same bits as the first and the same numbers of
+    tiles and of their pairs, without the pass over the operands (the convert kernel) inside the limits and with it beyond them.  Rows of
+    up to so many entries, or of exactly so many where the number is a text."""
     rng = np.random.default_rng(rows + cols)
-    A, B = _short(rng, rows, inner, a_most), _short(rng, inner, cols, b_most, dense)
+    exactly = lambda n, m, k: _exact_lengths(rng, m, np.full(n, int(k)), lambda size: rng.uniform(-1, 1, size))
+    A = exactly(rows, inner, a_row) if isinstance(a_row, str) else _short(rng, rows, inner, a_row)
+    B = exactly(inner, cols, b_row) if isinstance(b_row, str) else _short(rng, inner, cols, b_row, dense)
     if dense:                                                  # (the dense rows of B are met by nobody)
         assert A.col_idx.min() >= 64
     dA, dB = tsp.to_device(A, **types), tsp.to_device(B, **types)
     ref = oracle.spgemm(A, B, threads=4)
-    h = tsp.Handle()
+    h = tsp.Handle(phase_timers=True)
     try:
-        stats = []
-        for _ in range(3):
+        first = None
+        for call in range(3):
             C = h.spgemm(dA, dB)
             row_ptr, col, val = C.to_host()
             C.free()
+            stats = h.stats()
             assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
             assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
-            stats.append([h.stats()[k] for k in ("a_tiles", "b_tiles", "candidate_pairs", "c_nnz", "pairs")])
-        assert stats[0] == stats[1] == stats[2]
+            assert stats["pairs"] == 0 and (stats["kernel_us"]["convert"] == 0) == (straight and call > 0)
+            now = [val.view(np.uint32), [stats[k] for k in ("a_tiles", "b_tiles", "candidate_pairs", "c_nnz")]]
+            first = first or now
+            assert np.array_equal(now[0], first[0]) and now[1] == first[1]
     finally:
         h.close()
 
@@ -707,7 +717,8 @@ def test_rows_or_tiles_whatever_came_before(tsp, oracle, rows):
     ((300, 65536, 140, 2, 2), (300, 65537, 140, 2, 2)), ((2048, 65535, 300, 12, 1), (2048, 70000, 300, 13, 1)), ((2049, 2049, 2049, 3, 3), (2049, 300, 500, 9, 6)),
     ((2000, 524288, 100, 3, 1), (700, 524288, 100, 2, 1)), ((9000, 9000, 700, 2, 3), (9000, 9001, 700, 9, 3))])
 def test_pairs_of_tiles_straight_from_the_operands(tsp, shapes):
-    """Two products in turn on one handle: the numbers of tiles and of their pairs as counted here, every time."""
+    """Two products in turn on one handle: the numbers of tiles and of their pairs as counted here, every time, and from the second on
+    without the pass over the operands (the convert kernel), unless rows of up to 9 entries have too many products."""
     def tiles(M):
         row = np.repeat(np.arange(M.rows), np.diff(M.row_ptr)) // 16
         return np.unique(row * ((M.cols + 15) // 16) + M.col_idx // 16)
@@ -719,12 +730,14 @@ def test_pairs_of_tiles_straight_from_the_operands(tsp, shapes):
         of_a, of_b = tiles(A), tiles(B)
         per_row = np.bincount(of_b // ((cols + 15) // 16), minlength=(inner + 15) // 16)
         cases.append((tsp.to_device(A), tsp.to_device(B), [of_a.size, of_b.size, int(per_row[of_a % ((inner + 15) // 16)].sum())]))
-    h = tsp.Handle()
+    h = tsp.Handle(phase_timers=True)
     try:
-        for _ in range(4):
-            for dA, dB, want in cases:
+        for call in range(4):
+            for (*_, a_most, b_most), (dA, dB, want) in zip(shapes, cases):
                 h.spgemm(dA, dB).free()
-                assert [h.stats()[k] for k in ("a_tiles", "b_tiles", "candidate_pairs")] == want
+                stats = h.stats()
+                assert [stats[k] for k in ("a_tiles", "b_tiles", "candidate_pairs")] == want
+                assert (stats["kernel_us"]["convert"] == 0) == (call > 0 and (a_most, b_most) != (9, 6))
     finally:
         h.close()
 
@@ -732,7 +745,8 @@ def test_pairs_of_tiles_straight_from_the_operands(tsp, shapes):
 @pytest.mark.parametrize("rows", [1800, 30000])
 def test_what_is_not_for_it_straight_from_the_operands(tsp, oracle, rows):
     """Operands of the sizes of a product of small rows that are not canonical, that have more entries in C than the last one and some,
-    or rows that are not small: refused, or multiplied all the same; then one of small rows again."""
+    or rows that are not small: refused, or multiplied all the same; then one of small rows again.  `straight`: without the pass over the
+    operands (the convert kernel)."""
     rng = np.random.default_rng(rows)
     lengths, cols = np.full(rows, 3), 5003
     def make(lengths, width=cols):
@@ -746,18 +760,19 @@ def test_what_is_not_for_it_straight_from_the_operands(tsp, oracle, rows):
     many_products = lengths.copy()
     many_products[100], many_products[200:205] = 8, 2
     dB = tsp.to_device(B)
-    h = tsp.Handle(validate=True)
+    h = tsp.Handle(validate=True, phase_timers=True)
     try:
-        def good(A):
+        def good(A, straight):
             ref = oracle.spgemm(A, B, threads=4)
             C = h.spgemm(tsp.to_device(A), dB)
             row_ptr, col, val = C.to_host()
             C.free()
             assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(col, ref.col)
             assert np.all(np.abs(val.astype(np.float64) - ref.val) <= 1e-5 * ref.mag + 1e-7)
-        for _ in range(2):
-            good(narrow)
-        good(ordinary)                                         # (more entries in C than there is room for)
+            assert (h.stats()["kernel_us"]["convert"] == 0) == straight
+        for straight in (False, True):
+            good(narrow, straight)
+        good(ordinary, True)                                   # (more entries in C than there is room for)
         for where, broken_col in ((0, -1), (500, cols), (3 * rows - 1, 1 << 30), (301, None), (302, "same")):
             broken = make(lengths)
             broken.col_idx[where] = broken.col_idx[where - 1] if broken_col == "same" else broken.col_idx[where + 1] if broken_col is None else broken_col
@@ -768,13 +783,13 @@ def test_what_is_not_for_it_straight_from_the_operands(tsp, oracle, rows):
             broken.row_ptr[at] = value
             with pytest.raises(tsp.TspError):
                 h.spgemm(tsp.to_device(broken), dB)
-        good(ordinary)
+        good(ordinary, True)
         assert make(long_row).nnz == make(many_products).nnz == ordinary.nnz
-        good(make(many_products))
-        good(ordinary)
-        good(make(long_row))
-        for _ in range(2):
-            good(ordinary)
+        good(make(many_products), False)
+        good(ordinary, False)
+        good(make(long_row), False)
+        for straight in [False] * 4 + [True]:                  # (four products without such rows before the next try)
+            good(ordinary, straight)
     finally:
         h.close()
 
