@@ -43,7 +43,7 @@ enum Scalar {
     // the row kernels (rowwise.hip):
     S_ROW_LISTS = 15,        // heavy rows and their tasks listed so far (one packed counter)
     S_ROW_PRODUCTS = 17,     // intermediate products
-    S_ROW_SMALL = 18,        // rows of C that go through a table in LDS
+    S_ROW_SMALL = 18,        // rows of C whose products a group of lanes sorts (k_row_small)
     S_ROW_HEAVY = 19,        // rows of C that are not
     S_ROW_TASKS = 20,        // blocks of k_heavy_fill
     S_ROW_RANGE_A = 21,      // magnitude and granularity of the values (ValueRange)

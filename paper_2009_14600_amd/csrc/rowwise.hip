@@ -644,7 +644,8 @@ __global__ __launch_bounds__(256) void k_row_finish(const FinishArgs a) {
 
 // ---- small rows -------------------------------------------------------------------------------------------------
 // How the small rows of a launch are worked off: lanes per row of A, lanes per row of B (a power of two, at most as
-// many), and the most products of a small row (three quarters of a power of two, 192 at most).
+// many), and the most products of a small row: 24, 48, 96 or 192, three quarters of the keys that the group sorts then.  (From a hash
+// table that was to stay that empty; the sort would take the last quarter at the same price, which has not been timed.)
 struct SmallShape {
     int lanes, list_lanes, products;
     bool narrow() const { return list_lanes < lanes; }
@@ -744,7 +745,9 @@ struct GivenOperands {
 // The wave's groups of G lanes each sort G * R keys, number l * R + r of a group in lane l's key[r]: merges of ascending halves,
 // of which the first step compares mirrored places, so that every step puts the smaller key first and no lane needs to know a
 // direction.  med3 with 0 is a minimum, with the largest number a maximum.  (Templates, not loops: sixteen keys are too many for the
-// compiler to take the loops apart, and then lie in scratch memory.)
+// compiler to take the loops apart, and then all lie in scratch memory.  As it is, the 64 registers that leave room for eight waves
+// are too few for sixteen keys by 9 to 12, which are stored and read back around that sort; rows of up to 128 products have none of
+// it but for one register of k_row_given with lists of tiles.)
 template <int kControl>
 __device__ __forceinline__ uint32_t from_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kControl, 0xf, 0xf, true); }
 template <int kXor>
@@ -1392,8 +1395,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // next call.  That one makes row_ptr and moves the entries into C (k_given_finish); for products of one chunk of rows the last block
 // makes row_ptr, and k_small_copy moves them.  Where a row turns out to be for other kernels the product is started again with
 // k_row_prepare.
-// Bound, as k_row_small is, by round trips and by how few waves there are to hide them while a launch begins and ends; so fewer
-// launches, with more of different kinds in each.  k_row_prepare, k_row_small and k_small_finish, one behind the other, against these
+// Bound by vector instructions where there are many rows (70 % of the time on the 512 x 512 mesh, with 4.8 waves per SIMD that wait for
+// 42 % of theirs), and by round trips where there are few or a launch begins and ends (37 x 37: waves wait for 74 %); so fewer launches,
+// with more of different kinds in each.  k_row_prepare, k_row_small and k_small_finish, one behind the other, against these
 // two: a 512 x 512 mesh 16.1 + 28.4 + 12.1 us and 36.0 + 12.7, 65,536 rows of 8 random entries 10.8 + 24.4 + 12.3 and 29.6 + 12.8,
 // A*P on a 64^3 grid 25.6 + 19.2 + 6.7 and 30.6 + 7.4; the products 56.4 -> 45.5, 47.3 -> 40.5, 58.5 -> 39.1, a 37 x 37 mesh 26.6 ->
 // 17.9, 1024 rows of 8 entries 27.0 -> 19.2.  The pairs of tiles from lists of A's tiles in every tile-row take three round trips, from
@@ -2615,7 +2619,10 @@ __global__ void k_clear_rows(int64_t *d_scalars, int64_t products) {
 }
 
 // Whether the row kernels are faster for A*B than the tile kernels: what the two take beyond the 30 us that both do, from
-// times of 90 products of meshes, stencils, blocks, random and power-law graphs (in ns).  Rows: 13 per heavy row, 1 per
+// times of 90 products of meshes, stencils, blocks, random and power-law graphs (in ns).  Those times, and all figures here, are of
+// kernels before the present ones: small rows went through a hash table, and repeated products by tiles took more launches.  Small rows
+// take less now (reckoned and timed: 65,536 rows of 8 random entries 68 and 40 us, a 512^2 mesh 89 and 45), repeated products by tiles up to
+// 15 % less; the line has not been drawn again.  Rows: 13 per heavy row, 1 per
 // thousand products, 8 where the heavy rows are summed in fp64 (3 on even rows, 8 to 20 on graphs), and 1 per thousand
 // products of the small rows and lane of such a row.  Tiles: 19 us (more launches) and 0.15 per candidate pair of tiles, which
 // is what they cost at least.  So a stencil or dense blocks go by tiles from 1500 rows on (27 points on a 24^3 grid: 69 us, by
@@ -2723,7 +2730,8 @@ __global__ __launch_bounds__(256) void k_row_sample(const SampleArgs a) {
 enum RowsEnd { kRowsNotTaken, kRowsTaken, kRowsAgain };     // (again: with other lanes, or with the operands prepared)
 
 // A product of sizes whose last product had small rows only, straight from the operands (k_row_given).  Up to kGivenBlocks blocks of
-// rows, whose numbers every block of k_given_finish adds up, and bitmaps of no more LDS than leaves a CU its eight blocks.
+// rows, whose numbers every block of k_given_finish adds up (64 KB for the last of them), and bitmaps of no more LDS than leaves a CU its
+// eight blocks.  More blocks are left to the other kernels without having been timed.
 constexpr int64_t kGivenBlocks = 16384;
 constexpr size_t kGivenBitmaps = 16 * 1024;
 constexpr int64_t kGivenRows = kGivenBlocks * 32, kGivenColumns = (int64_t)kGivenBitmaps / 16 * 32 * T;     // at most, of A
@@ -2924,7 +2932,8 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
     auto found_entries = [&] { return ((A->rows * shape.lanes + 255) / 256) * 256 / shape.lanes * shape.products; };
     while (shape.products > 24 && found_entries() > kFoundEntries) shape.products /= 2;
     if (found_entries() > kFoundEntries) return TSP_OK;
-    // straight from the operands, by the last product of these sizes
+    // straight from the operands, by the last product of these sizes.  Up to 128 entries per tile-row on average, the two trips of a wave
+    // for which k_row_prepare gives it tile-rows as well; count_tiles would take more, which has not been timed.
     auto of_waves = [](const tsp_csr *M) { return M->nnz <= 128 * ((M->rows + T - 1) / T) && ((M->cols + T * 32 - 1) / (T * 32) + 3) / 4 * 64 <= (int64_t)kGivenBitmaps; };
     if (known && hint.nnz >= 0 && hint.heavy == 0 && hint.small && hint.given.allowed() && shape.lanes == lanes_unless_wide && A->rows <= kFinishRows &&
         (A->rows * shape.lanes + 255) / 256 <= kGivenBlocks && A->row_ptr_type == B->row_ptr_type && A->val_type == B->val_type && of_waves(A) && (alias || of_waves(B))) {
