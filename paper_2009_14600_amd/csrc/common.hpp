@@ -89,6 +89,23 @@ struct ListSizes {
                 std::max(max_row_words, o.max_row_words), std::max(max_row_a_tiles, o.max_row_a_tiles), std::max(b_tiles, o.b_tiles)};
     }
 };
+// When products of the same sizes take a way that suits only some of them.  One that turned out not to be for it has cost what was
+// launched in vain, so the next is to come after some that would have suited it, one behind the other: after 4, and after twice as many
+// every further time, 1024 at most; half as many again when as many as that have gone well.
+struct WayHint {
+    int wanted = 0, seen = 0, done = 0;
+    bool allowed() const { return seen >= wanted; }
+    void other_way(bool suitable) { seen = suitable ? std::min(seen + 1, wanted) : 0; }
+    void missed() {
+        wanted = std::min(std::max(2 * wanted, 4), 1024);
+        seen = done = 0;
+    }
+    void taken() {
+        if (++done < wanted) return;
+        wanted = seen = wanted / 2;
+        done = 0;
+    }
+};
 // What symbolic_run goes by for a product of the sizes of an earlier one, see there
 struct ListHint {
     bool usable = false;
@@ -96,6 +113,7 @@ struct ListHint {
     int64_t nnz = -1, c_tiles = 0, a_tiles = 0;    // of the last one
     int64_t max_row_entries = 0;
     bool large = true;                             // an operand had tile-rows for k_convert_large
+    WayHint without_large;                         // ... which is not launched
     bool general = false;                          // it took the general task-list kernel ...
     int32_t *order = nullptr;                      // ... and its tile-rows in this order (heaviest first), or null
     int64_t order_rows = 0;
@@ -119,23 +137,6 @@ struct ListExpected {
 struct CompactHint {
     int64_t nnz = -1;
 };
-// When products of the same sizes go straight from the operands (rowwise_given).  One that turned out not to be for it has cost a launch, so
-// the next is to come after some without rows for other kernels, one behind the other: after 4, and after twice as many every further
-// time, 1024 at most; half as many again when as many as that have gone well.
-struct GivenHint {
-    int wanted = 0, seen = 0, done = 0;
-    bool allowed() const { return seen >= wanted; }
-    void prepared(bool suitable) { seen = suitable ? std::min(seen + 1, wanted) : 0; }
-    void missed() {
-        wanted = std::min(std::max(2 * wanted, 4), 1024);
-        seen = done = 0;
-    }
-    void taken() {
-        if (++done < wanted) return;
-        wanted = seen = wanted / 2;
-        done = 0;
-    }
-};
 // What the row kernels found for the last product of the same sizes (rowwise.hip): whether the tile kernels
 // suit it better, and how long its lists of work are.  Only the choice of kernels and the sizes of workspaces follow
 // from it; the numbers of the product at hand are checked against it.
@@ -151,7 +152,7 @@ struct RowHint {
     int64_t products = 0;                          // intermediate ones
     int64_t nnz = -1;                              // of C
     bool small = false;                            // small rows among its rows
-    GivenHint given;
+    WayHint given;                                 // straight from the operands (rowwise_given)
     bool wide = false;                             // so many rows of 9 to 16 entries that 16 lanes per row pay
     int sum = 0, scale = 0;                        // how the heavy rows are summed
 };

@@ -3091,7 +3091,7 @@ static int rowwise_run(tsp_context *ctx, const tsp_csr *A, const tsp_csr *B, boo
         hint.candidates = h[S_CANDIDATES];
         hint.a_tiles = h[S_TILES_A];
         hint.heavy = n_heavy;
-        hint.given.prepared(n_heavy == 0);
+        hint.given.other_way(n_heavy == 0);
         hint.tasks = n_tasks;
         hint.large_tasks = n_large;
         hint.products = n_products;

@@ -85,9 +85,9 @@ extern "C" int tsp_spgemm(tsp_handle ctx, const tsp_csr *A, const tsp_csr *B, ts
         }
         phase_begin(ctx, TSP_PHASE_CONVERT, s);
         // (the kernel for tile-rows of many entries is not launched where the last product of these sizes had none: with nothing to do
-        // it takes 4.6 us, of 25 to 200 for the whole call)
+        // it takes 4.6 us, of 25 to 200 for the whole call; where this one has some the task list is made, and waited for, twice)
         const ListHint *const hint = ctx->list_hints.look({{A->rows, A->nnz, B->rows, B->nnz, B->cols, alias}});
-        const bool leave_large = hint && !hint->large;
+        const bool leave_large = hint && !hint->large && hint->without_large.allowed();
         rc = convert_enqueue(ctx, A, alias ? (TSP_FORM_LEFT | TSP_FORM_RIGHT) : TSP_FORM_LEFT, S_TILES_A, &ta, leave_large, s);
         if (!rc && !alias) rc = convert_enqueue(ctx, B, TSP_FORM_RIGHT, S_TILES_B, &tb, leave_large, s);
         phase_end(ctx, TSP_PHASE_CONVERT, s);

@@ -2409,7 +2409,10 @@ int symbolic_run(tsp_context *ctx, tsp_tiles_s *A, tsp_tiles_s *B, tsp_plan_s **
         if (h[S_INVALID]) return (int)TSP_ERR_NOT_CANONICAL;
         if (h[S_UNSUPPORTED]) return (int)TSP_ERR_UNSUPPORTED;
         if (h[S_INTERNAL]) return (int)TSP_ERR_HIP;
-        if ((A->large_rows && h[S_LARGE_A]) || (B->large_rows && h[S_LARGE_B])) return kLargeLeft;
+        if ((A->large_rows && h[S_LARGE_A]) || (B->large_rows && h[S_LARGE_B])) {
+            hint.without_large.missed();
+            return kLargeLeft;
+        }
         if (A->ntiles < 0) A->ntiles = h[A->scalar_slot];
         if (B->ntiles < 0) B->ntiles = h[B->scalar_slot];
         P->c_tiles = h[S_C_TILES];
@@ -2691,6 +2694,8 @@ list_kernels:
     hint.max_row_entries = std::max(key_known ? hint.max_row_entries : 0, ctx->h_scalars[S_MAX_ROW_ENTRIES]);
     hint.usable = listed && fused_masks;
     hint.large = A->large || B->large || ctx->h_scalars[S_LARGE_A] || ctx->h_scalars[S_LARGE_B];
+    if (A->large_rows || B->large_rows) hint.without_large.taken();
+    else hint.without_large.other_way(!hint.large);
     hint.most = key_known ? hint.most.with(true_sizes()) : true_sizes();
     P->c_nnz = ctx->h_scalars[S_C_NNZ];
     P->max_row_entries = ctx->h_scalars[S_MAX_ROW_ENTRIES];

@@ -383,6 +383,46 @@ def test_tile_rows_of_many_entries_where_there_were_none(tsp, oracle, left, righ
         h.close()
 
 
+def test_tile_rows_of_many_entries_again_and_again(tsp):
+    """Products of the same sizes with tile-rows for that kernel and without: after one that has some where it was not launched, it is
+    launched for all until four without any have come one behind the other, and then for eight.  (Where it is not launched the list of
+    those tile-rows is kept, a block more than the product takes otherwise.)"""
+    n, rng = 40, np.random.default_rng(8)
+
+    def operand(entries):
+        A = _tile_rows(rng, 16 * n, np.full(n, 40), entries)
+        keep = np.sort(rng.permutation(A.nnz)[:27000])
+        row = np.repeat(np.arange(A.rows), np.diff(A.row_ptr))[keep]
+        return tsp.to_device(inputs.from_coo(A.rows, A.cols, row, A.col_idx[keep], rng.uniform(-1, 1, keep.size), "tile-rows"))
+
+    even, large = operand(np.full(n, 700)), operand(np.where(np.isin(np.arange(n), (0, 17, n - 1)), 3000, 514))
+    h = tsp.Handle()
+    try:
+        h.set_option(tsp.OPT_WORK_ORDER, 2)        # (the tile kernels, whatever the operands)
+
+        def blocks(A):
+            h.trim()
+            before = set(h._blocks)
+            C = h.spgemm(A, A)
+            new = len(set(h._blocks) - before)
+            C.free()
+            return new
+
+        blocks(even)
+        left = blocks(even)                                    # (not launched)
+        blocks(large)                                          # (missed)
+        always = blocks(large)
+        assert left == always + 1
+        assert [blocks(even) for _ in range(6)] == [always] * 4 + [left] * 2
+        blocks(large)
+        for _ in range(2):
+            assert [blocks(even) for _ in range(7)] == [always] * 7
+            assert blocks(large) == always
+        assert [blocks(even) for _ in range(10)] == [always] * 8 + [left] * 2
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("left_tiles", [1, 31, 32, 33, 63, 64, 65])
 def test_tile_rows_of_many_left_tiles(tsp, oracle, left_tiles):
     """A tile-row of A with as many tiles as the words of contributors hold, one more and one less, among short ones."""
