@@ -133,9 +133,10 @@ struct ListExpected {
     }
 };
 
-// Entries that were left of the last matrix of these sizes (compact.hip)
+// Entries that were left of the last matrix of these sizes (compact.hip), and whether the copy is launched by it
 struct CompactHint {
     int64_t nnz = -1;
+    WayHint ahead;
 };
 // What the row kernels found for the last product of the same sizes (rowwise.hip): whether the tile kernels
 // suit it better, and how long its lists of work are.  Only the choice of kernels and the sizes of workspaces follow

@@ -188,3 +188,43 @@ def test_nothing_to_drop_after_a_product_that_lost_entries(tsp, nnz, zero):
             C.free()
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("descends", [False, True])
+def test_more_left_than_last_time_again_and_again(tsp, descends):
+    """Matrices of the same sizes with many zeros, and with few (or with a row pointer that goes down), in turn: after one that did not
+    fit what was launched ahead nothing is, until four have come one behind the other that would have fitted.  (Seen by the bytes that
+    a call takes: those of a copy ahead have room for a sixteenth more, and one in vain leaves its arrays.)"""
+    import torch
+    rng = np.random.default_rng(3)
+    rows, n = 500, 3 * PART + 77
+    row_ptr = np.sort(np.concatenate([[0, n], rng.integers(0, n, rows - 1)])).astype(np.int64)
+    other_ptr = row_ptr.copy()
+    if descends:
+        other_ptr[200] = 0
+    made = []
+    for pointers, share in ((row_ptr, 0.5), (other_ptr, 0.5 if descends else 0.1)):
+        val = np.where(rng.random(n) < share, 0, rng.uniform(0.5, 1, n)).astype(np.float32)
+        col = np.arange(n, dtype=np.int32)
+        made.append((tsp.DeviceCSR(rows, n, *(torch.from_numpy(x).cuda() for x in (pointers, col, val))), _expected(pointers, col, val)))
+    h = tsp.Handle()
+    try:
+        def blocks(k):
+            C, want = made[k]
+            h.trim()
+            before = set(h._blocks)
+            out = h.compact_zeros(C)
+            new = sum(h._blocks[p].numel() for p in set(h._blocks) - before)
+            for x, y in zip(out.to_host(), want):
+                assert np.array_equal(x, y)
+            out.free()
+            return new
+
+        plain, few = blocks(0), blocks(0)                      # (the second into arrays for a sixteenth more)
+        assert few > plain
+        missed = blocks(1)
+        assert [blocks(0) for _ in range(3)] == [plain] * 3
+        assert blocks(1) < missed
+        assert [blocks(0) for _ in range(6)] == [plain] * 4 + [few] * 2
+    finally:
+        h.close()
